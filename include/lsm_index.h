@@ -285,7 +285,7 @@ size_t lsm_compact_workspace_bytes(const uint64_t* run_lens, uint32_t n_runs);
  * lsm_flush_workspace_bytes(n) bytes, 256-byte aligned (4 * n bytes up to 8,192 entries; beyond that about 70 bytes
  * per entry: room for the sorted segments and for the merge).  Up to 8,192 entries every entry is compared with
  * every other (key compares from LDS); a larger buffer is cut into segments of 4,096 entries in write order, the
- * segments are sorted that way in one launch and then merged by the compaction kernels.  The call does not wait.
+ * segments are sorted in one launch and then merged by the compaction kernels.  The call does not wait.
  * Errors: LSM_ERR_NULL, LSM_ERR_BAD_ARG (n > LSM_MAX_BUFFER, misaligned), LSM_ERR_CAPACITY, LSM_ERR_WORKSPACE, LSM_ERR_HIP.
  */
 size_t lsm_flush_workspace_bytes(uint64_t n);

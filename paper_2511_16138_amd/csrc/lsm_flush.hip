@@ -1,27 +1,20 @@
 // lsm_flush_buffer: the write buffer as a sorted run (paper section 2.2: the in-memory buffer is flushed as a
-// sorted run).  A buffer of a few thousand entries is sorted by comparing every entry with every other; a larger one is
-// cut into segments of kFlushSegment entries in write order, every segment is sorted that way (all segments in one
-// launch), and the sorted segments are merged by the compaction kernels (the segment written last is the newest run,
-// so that among equal sequence numbers the later write wins there as well).  The all-pairs step:
-//   winner_kernel  entry i survives unless some entry j has the same key and is newer (larger seqno, or the same
-//                  seqno and written later);
-//   place_kernel   a surviving entry goes to position |{surviving j : key_j < key_i}|; the survivors are counted.
-// Both kernels stream the whole buffer through LDS in tiles (key + seqno, and the winner flag in the second),
-// and all threads of a workgroup read the same tile record at the same time (LDS broadcast).
+// sorted run).  Total order of the buffer's entries: key ascending, then newest first (larger seqno; equal seqnos: the
+// one written later); an entry survives unless its predecessor in that order has the same key.
+//
+// Up to kFlushDirect entries: by counting, in two launches without a clearing pass or global atomics.
+//   flush_rank_kernel   the number of entries that precede entry i in the total order (its rank), and whether i is
+//                       shadowed, by comparing it with every other entry;
+//   flush_place_kernel  an entry that is not shadowed goes to position rank - |{shadowed j : rank_j < rank_i}|, from a
+//                       bitmap of the shadowed ranks that every workgroup makes for itself in LDS.
+// A larger buffer is cut into segments of kFlushSegment entries in write order, every segment is sorted by one workgroup
+// (flush_sort_kernel), and the sorted segments are merged by the compaction kernels (the segment written last is the
+// newest run, so that among equal sequence numbers the later write wins there as well).
 #include <hip/hip_runtime.h>
 
 #include "lsm_common.h"
 
 namespace lsm {
-
-constexpr int kFlushThreads = 256;
-
-struct FlushTile {
-    uint4 lo[kFlushThreads];   // key bytes 0..15
-    uint4 hi[kFlushThreads];   // key bytes 16..31
-    uint64_t seq[kFlushThreads];
-    uint32_t wins[kFlushThreads];
-};
 
 __device__ __forceinline__ int key_cmp(const Key& a, const Key& b) {
     for (int w = 0; w < 4; w++)
@@ -29,77 +22,319 @@ __device__ __forceinline__ int key_cmp(const Key& a, const Key& b) {
     return 0;
 }
 
-// kPlace = false: winner flags; kPlace = true: output positions of the winners, the copy, the count.
-// blockIdx.y = segment: the entries [y * segment, min(n, (y + 1) * segment)) are sorted among themselves, written to
-// out + y * segment, and counted in n_out[y] (one segment that is the whole buffer: the plain case).
-template <bool kPlace>
-__global__ void __launch_bounds__(kFlushThreads) flush_kernel(const lsm_entry_t* buffer, uint32_t n, uint32_t segment, uint32_t* winner,
-                                                               lsm_entry_t* out, uint64_t* n_out, uint4* fence_out, uint32_t fence_stride) {
-    __shared__ FlushTile tile;
-    const uint32_t seg_lo = blockIdx.y * segment, seg_hi = min(n, seg_lo + segment);
-    const uint32_t i = seg_lo + blockIdx.x * kFlushThreads + threadIdx.x;
-    const bool mine = i < seg_hi;
-    const uint4* me = reinterpret_cast<const uint4*>(buffer + (mine ? i : seg_lo));
-    const Key key = key_from_raw(me[0], me[1]);
-    const uint64_t seq = buffer[mine ? i : seg_lo].seqno;
-    bool alive = mine && (!kPlace || winner[i] != 0);
-    uint32_t before = 0;  // surviving entries of the segment with a smaller key
-    for (uint32_t t0 = seg_lo; t0 < seg_hi; t0 += kFlushThreads) {
-        const uint32_t j = t0 + threadIdx.x;
-        if (j < seg_hi) {
-            const uint4* e = reinterpret_cast<const uint4*>(buffer + j);
-            tile.lo[threadIdx.x] = e[0];
-            tile.hi[threadIdx.x] = e[1];
-            tile.seq[threadIdx.x] = buffer[j].seqno;
-            if (kPlace) tile.wins[threadIdx.x] = winner[j];
+constexpr uint32_t kShadowed = 0x80000000u;  // flag in a packed rank
+
+// n^2 compares of 16-byte key halves.  A workgroup ranks only kRankEntries entries, so that a buffer of a few thousand
+// is hundreds of workgroups (one thread per entry left 15 workgroups with 3,600 serial compares each: 387 us for this
+// step on 3,600 entries, 1009 us for the whole call; now 21 us): 16 lanes hold 16 entries, and the 32 groups of 16 lanes share the other entries out, which are
+// staged in LDS (first 16 key bytes as two numbers; the lanes of a wave read four records at a time).  The rest of a key
+// and the seqno are read from the buffer on a 16-byte tie only: an entry with itself, versions of a key.
+constexpr int kRankThreads = 512;
+constexpr int kRankEntries = 16;
+constexpr int kRankTile = 2048;  // records staged at a time
+__global__ void __launch_bounds__(kRankThreads) flush_rank_kernel(const lsm_entry_t* buffer, uint32_t n, uint32_t* packed) {
+    __shared__ ulonglong2 tile[kRankTile];
+    __shared__ uint32_t part[kRankThreads / kWave][kRankEntries];
+    constexpr int kSlices = kRankThreads / kRankEntries;
+    const uint32_t i = blockIdx.x * kRankEntries + threadIdx.x % kRankEntries;
+    const uint32_t slice = threadIdx.x / kRankEntries;
+    const lsm_entry_t* me = buffer + (i < n ? i : 0);
+    const Key key = load_key(me);
+    const uint64_t seq = me->seqno;
+    uint32_t rank = 0;
+    bool shadowed = false;
+    for (uint32_t t0 = 0; t0 < n; t0 += kRankTile) {
+        const uint32_t count = min((uint32_t)kRankTile, n - t0);
+        __syncthreads();
+        for (uint32_t c = threadIdx.x; c < count; c += kRankThreads) {
+            const uint4 q = *reinterpret_cast<const uint4*>(buffer + t0 + c);
+            tile[c] = make_ulonglong2(__builtin_bswap64(((uint64_t)q.y << 32) | q.x), __builtin_bswap64(((uint64_t)q.w << 32) | q.z));
         }
         __syncthreads();
-        const uint32_t count = min((uint32_t)kFlushThreads, seg_hi - t0);
-        if (alive) {
-            for (uint32_t c = 0; c < count; c++) {
-                const int cmp = key_cmp(key_from_raw(tile.lo[c], tile.hi[c]), key);
-                if (kPlace) {
-                    before += (cmp < 0 && tile.wins[c]) ? 1 : 0;
-                } else if (cmp == 0) {
-                    const uint64_t other = tile.seq[c];
-                    if (other > seq || (other == seq && t0 + c > i)) alive = false;  // a newer version of the same key
-                }
+#pragma unroll 4
+        for (uint32_t c = slice; c < count; c += kSlices) {
+            const ulonglong2 o = tile[c];
+            const bool tie = (o.x == key.w[0]) & (o.y == key.w[1]);
+            rank += ((o.x < key.w[0]) | ((o.x == key.w[0]) & (o.y < key.w[1]))) ? 1 : 0;
+            if (tie && t0 + c != i) {
+                const lsm_entry_t* other = buffer + t0 + c;
+                const int cmp = key_cmp(load_key(other), key);
+                const bool newer = cmp == 0 && (other->seqno > seq || (other->seqno == seq && t0 + c > i));
+                shadowed = shadowed || newer;
+                rank += (cmp < 0 || newer) ? 1 : 0;
+            }
+        }
+    }
+    // both results of the 32 slices in one word: the sums stay below 2^16 (rank) and 2^6 (slices that saw a newer version)
+    uint32_t v = rank | (shadowed ? 1u << 16 : 0u);
+    v += __shfl_xor(v, 16, kWave);
+    v += __shfl_xor(v, 32, kWave);
+    if ((threadIdx.x & (kWave - 1)) < kRankEntries) part[threadIdx.x / kWave][threadIdx.x % kRankEntries] = v;
+    __syncthreads();
+    if (threadIdx.x < kRankEntries && i < n) {
+        v = 0;
+        for (int w = 0; w < kRankThreads / kWave; w++) v += part[w][threadIdx.x];
+        packed[i] = (v & 0xFFFF) | ((v >> 16) != 0 ? kShadowed : 0u);
+    }
+}
+
+// Up to here ranks by comparing all pairs: 8,192 entries are 67M compares, some 25 us of the whole chip, where sorting
+// segments and merging them is three dependent launches of about 15 us each.
+constexpr uint64_t kFlushDirect = 8192;
+
+// Four lanes per entry.  Every workgroup reads all packed ranks (at most 32 KB, from the L2).
+constexpr int kPlaceThreads = 256;
+static_assert(kFlushDirect == kPlaceThreads * 32, "one 32-bit word of the bitmap per thread");
+__global__ void __launch_bounds__(kPlaceThreads) flush_place_kernel(const lsm_entry_t* buffer, uint32_t n, const uint32_t* packed,
+                                                                   lsm_entry_t* out, uint64_t* n_out, uint4* fence_out, uint32_t fence_stride) {
+    __shared__ uint32_t bits[kPlaceThreads];    // bit r: the entry of rank r is shadowed
+    __shared__ uint32_t before[kPlaceThreads];  // shadowed ranks below the word
+    __shared__ uint32_t wave_sum[kPlaceThreads / kWave];
+    const int tid = threadIdx.x;
+    bits[tid] = 0;
+    __syncthreads();
+    const uint32_t i = blockIdx.x * (kPlaceThreads / 4) + tid / 4;
+    const uint32_t p = i < n ? packed[i] : kShadowed;
+    const uint4 part = i < n ? reinterpret_cast<const uint4*>(buffer + i)[tid & 3] : make_uint4(0, 0, 0, 0);
+    for (uint32_t e = tid; e < n; e += kPlaceThreads) {
+        const uint32_t r = packed[e];
+        if (r & kShadowed) atomicOr(&bits[(r & ~kShadowed) >> 5], 1u << (r & 31));
+    }
+    __syncthreads();
+    const uint32_t count = __popc(bits[tid]);
+    uint32_t incl = count;
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t v = __shfl_up(incl, off, kWave);
+        if ((tid & (kWave - 1)) >= off) incl += v;
+    }
+    if ((tid & (kWave - 1)) == kWave - 1) wave_sum[tid / kWave] = incl;
+    __syncthreads();
+    uint32_t total = 0, lead = 0;
+    for (int w = 0; w < kPlaceThreads / kWave; w++) {
+        if (w < tid / kWave) lead += wave_sum[w];
+        total += wave_sum[w];
+    }
+    before[tid] = lead + incl - count;
+    __syncthreads();
+    if (blockIdx.x == 0 && tid == 0) *n_out = n - total;
+    if (p & kShadowed) return;
+    const uint32_t at = p - before[p >> 5] - __popc(bits[p >> 5] & ((1u << (p & 31)) - 1));
+    reinterpret_cast<uint4*>(out + at)[tid & 3] = part;
+    if (fence_out != nullptr && (tid & 3) < 2 && at % fence_stride == 0) fence_out[(at / fence_stride) * 2 + (tid & 3)] = part;
+}
+
+// ---------------------------------------------------------------------------------------
+// One workgroup sorts one segment.
+// What moves through LDS is a 16-byte record per entry: the first 14 key bytes as a 112-bit number and, below, the
+// entry's age (0 = written last), so records are distinct and versions of a key come in write order, newest write
+// first.  Every thread sorts eight consecutive records in registers, then log2(segment / 8) rounds of merge-path merges
+// double the sorted lists, a thread producing eight outputs per round from eight records of either list (bitonic
+// half-cleaner and merge network).  Positions whose 14 bytes equal a neighbour's (versions of a key, and keys that
+// differ further on) are settled afterwards, each by comparing itself with the whole group: by the rest of the key,
+// seqno and age.  Bound by LDS operations of one compute unit per segment; all pairs of a segment instead (the step
+// that this one replaced) took 936 us for 100,001 entries, the whole call 1052 us against 149 us.  The entries themselves are read a second time for the output (they come from the L2).
+// ---------------------------------------------------------------------------------------
+constexpr uint64_t kFlushSegment = 4096;
+constexpr int kSortThreads = 512;
+constexpr int kSortItems = 8;
+static_assert(kSortThreads * kSortItems == kFlushSegment, "a segment fills the workgroup");
+static_assert(kFlushSegment * LSM_MAX_RUNS >= LSM_MAX_BUFFER, "the segments of the largest buffer must fit one compaction");
+
+struct SortShared {
+    uint4 buf[2][kFlushSegment];       // records, two sides; then the rest of the key and the seqno of tied positions
+    uint16_t order[kFlushSegment];     // final position -> age
+    uint32_t wave_count[kSortThreads / kWave];
+    alignas(4) uint8_t flag[kFlushSegment + 8];  // sorted position: 1 = same 14 bytes as the one before
+    alignas(4) uint8_t lose[kFlushSegment];      // final position: 1 = shadowed
+};
+
+struct Rec {
+    uint64_t hi, lo;
+};
+__device__ __forceinline__ Rec rec_load(const uint4* p) {
+    const uint4 v = *p;
+    return Rec{((uint64_t)v.y << 32) | v.x, ((uint64_t)v.w << 32) | v.z};
+}
+__device__ __forceinline__ void rec_store(uint4* p, const Rec& v) {
+    *p = make_uint4((uint32_t)v.hi, (uint32_t)(v.hi >> 32), (uint32_t)v.lo, (uint32_t)(v.lo >> 32));
+}
+__device__ __forceinline__ bool rec_less(const Rec& a, const Rec& b) { return (a.hi < b.hi) | ((a.hi == b.hi) & (a.lo < b.lo)); }
+__device__ __forceinline__ void rec_order(Rec& a, Rec& b) {
+    const bool swap = rec_less(b, a);
+    const Rec t = a;
+    a.hi = swap ? b.hi : a.hi, a.lo = swap ? b.lo : a.lo;
+    b.hi = swap ? t.hi : b.hi, b.lo = swap ? t.lo : b.lo;
+}
+// where position p sits in the 16-byte arrays: threads own eight consecutive positions (a stride of 128 bytes, one bank
+// quarter), so the positions of a group of eight are permuted by the group's number
+__device__ __forceinline__ uint32_t rec_at(uint32_t p) { return p ^ ((p >> 3) & 7); }
+
+__global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entry_t* buffer, uint32_t n, lsm_entry_t* out, uint64_t* counts) {
+    __shared__ SortShared s;
+    const uint32_t tid = threadIdx.x;
+    // segments are numbered newest first, the order in which the merge takes them as runs
+    const uint32_t seg = gridDim.x - 1 - blockIdx.x;
+    const uint32_t first = seg * (uint32_t)kFlushSegment;
+    const uint32_t len = min((uint32_t)kFlushSegment, n - first);
+    const lsm_entry_t* src = buffer + first;
+
+    // ---- records; age a = entry len - 1 - a of the segment.  Unused positions hold the largest value.
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++) {
+        const uint32_t e = tid + i * kSortThreads;
+        Rec r = {~0ull, ~0ull};
+        if (e < len) {
+            const uint4 q = *reinterpret_cast<const uint4*>(src + e);
+            r.hi = __builtin_bswap64(((uint64_t)q.y << 32) | q.x);
+            r.lo = (__builtin_bswap64(((uint64_t)q.w << 32) | q.z) & ~0xFFFFull) | (len - 1 - e);
+        }
+        rec_store(&s.buf[0][rec_at(e)], r);
+    }
+    __syncthreads();
+    const uint32_t o = tid * kSortItems;
+    Rec c[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++) c[i] = rec_load(&s.buf[0][rec_at(o + i)]);
+    // odd-even merge sort of eight (Batcher): 19 exchanges
+    rec_order(c[0], c[1]), rec_order(c[2], c[3]), rec_order(c[4], c[5]), rec_order(c[6], c[7]);
+    rec_order(c[0], c[2]), rec_order(c[1], c[3]), rec_order(c[4], c[6]), rec_order(c[5], c[7]);
+    rec_order(c[1], c[2]), rec_order(c[5], c[6]);
+    rec_order(c[0], c[4]), rec_order(c[1], c[5]), rec_order(c[2], c[6]), rec_order(c[3], c[7]);
+    rec_order(c[2], c[4]), rec_order(c[3], c[5]);
+    rec_order(c[1], c[2]), rec_order(c[3], c[4]), rec_order(c[5], c[6]);
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++) rec_store(&s.buf[0][rec_at(o + i)], c[i]);
+    __syncthreads();
+    // ---- merge rounds
+    uint32_t cur = 0;
+    for (uint32_t width = kSortItems; width < len; width <<= 1) {
+        const uint4* in = s.buf[cur];
+        uint4* dst = s.buf[cur ^ 1];
+        const uint32_t sa = o & ~(2 * width - 1), sb = sa + width, d = o - sa;  // both lists are `width` long (padding included)
+        uint32_t lo = d > width ? d - width : 0, hi = min(d, width);
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (rec_less(rec_load(&in[rec_at(sa + mid)]), rec_load(&in[rec_at(sb + (d - 1 - mid))]))) lo = mid + 1;
+            else hi = mid;
+        }
+        const uint32_t a = lo, b = d - lo;
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) {
+            // the eight smallest of two ascending lists of eight: element i of one against element 7 - i of the other
+            Rec x = {~0ull, ~0ull}, y = {~0ull, ~0ull};
+            if (a + i < width) x = rec_load(&in[rec_at(sa + a + i)]);
+            if (b + kSortItems - 1 - i < width) y = rec_load(&in[rec_at(sb + b + kSortItems - 1 - i)]);
+            c[i] = rec_less(x, y) ? x : y;
+        }
+#pragma unroll
+        for (int step = kSortItems / 2; step > 0; step >>= 1)
+#pragma unroll
+            for (int i = 0; i < kSortItems; i++)
+                if ((i & step) == 0) rec_order(c[i], c[i + step]);
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) rec_store(&dst[rec_at(o + i)], c[i]);
+        __syncthreads();
+        cur ^= 1;
+    }
+
+    // ---- which positions share their 14 bytes with a neighbour?  c[] holds this thread's eight sorted records.
+    bool any = false;
+    {
+        Rec prev = c[0];
+        if (o > 0) prev = rec_load(&s.buf[cur][rec_at(o - 1)]);
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) {
+            const bool eq = o + i > 0 && o + i < len && prev.hi == c[i].hi && ((prev.lo ^ c[i].lo) >> 16) == 0;
+            s.flag[o + i] = eq ? 1 : 0;
+            s.lose[o + i] = 0;
+            s.order[o + i] = (uint16_t)(c[i].lo & 0xFFFF);
+            any = any || eq;
+            prev = c[i];
+        }
+    }
+    if (tid == 0) s.flag[kFlushSegment] = 0;
+    if (__syncthreads_or(any)) {
+        // members of groups post the rest of their key, seqno and age at their sorted position
+        uint4* info0 = s.buf[0];  // {seqno, key bytes 14..15, age}
+        uint4* info1 = s.buf[1];  // key bytes 16..31
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) {
+            const uint32_t p = o + i;
+            if (p < len && (s.flag[p] | s.flag[p + 1]) != 0) {
+                const uint32_t age = (uint32_t)c[i].lo & 0xFFFF;
+                const uint4* e = reinterpret_cast<const uint4*>(src + (len - 1 - age));
+                const uint4 k0 = e[0], meta = e[2];
+                info0[p] = make_uint4(meta.x, meta.y, __builtin_bswap32(k0.w) & 0xFFFF, age);
+                info1[p] = e[1];
             }
         }
         __syncthreads();
-    }
-    if (!kPlace) {
-        if (mine) winner[i] = alive ? 1 : 0;
-        return;
-    }
-    if (alive) {
-        const uint4* src = reinterpret_cast<const uint4*>(buffer + i);
-        uint4* dst = reinterpret_cast<uint4*>(out + seg_lo + before);
-        for (int part = 0; part < 4; part++) dst[part] = src[part];
-        if (fence_out != nullptr && before % fence_stride == 0) {
-            fence_out[(before / fence_stride) * 2] = src[0];
-            fence_out[(before / fence_stride) * 2 + 1] = src[1];
+        for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
+            const uint32_t p = o + i;
+            if (p >= len || (s.flag[p] | s.flag[p + 1]) == 0) continue;
+            uint32_t start = p;
+            while (s.flag[start] != 0) start--;  // flag[0] is 0
+            const uint4 a0 = info0[p], a1 = info1[p];
+            const uint64_t seq = ((uint64_t)a0.y << 32) | a0.x;
+            const uint64_t t2 = __builtin_bswap64(((uint64_t)a1.y << 32) | a1.x), t3 = __builtin_bswap64(((uint64_t)a1.w << 32) | a1.z);
+            uint32_t rank = 0;
+            bool shadowed = false;
+            uint32_t q = start;
+            do {
+                if (q != p) {
+                    const uint4 b0 = info0[q], b1 = info1[q];
+                    const uint64_t oseq = ((uint64_t)b0.y << 32) | b0.x;
+                    const uint64_t u2 = __builtin_bswap64(((uint64_t)b1.y << 32) | b1.x), u3 = __builtin_bswap64(((uint64_t)b1.w << 32) | b1.z);
+                    const bool same = b0.z == a0.z && u2 == t2 && u3 == t3;
+                    const bool less = b0.z != a0.z ? b0.z < a0.z : (u2 != t2 ? u2 < t2 : u3 < t3);
+                    const bool newer = same && (oseq > seq || (oseq == seq && b0.w < a0.w));
+                    shadowed = shadowed || newer;
+                    rank += (same ? newer : less) ? 1 : 0;
+                }
+                q++;
+            } while (s.flag[q] != 0);  // flag[len ..] is 0
+            s.order[start + rank] = (uint16_t)a0.w;
+            s.lose[start + rank] = shadowed ? 1 : 0;
         }
+        __syncthreads();
     }
-    // survivors of this workgroup -> the segment's total (cleared by flush_clear_kernel)
-    const uint64_t votes = __ballot(alive);
-    if ((threadIdx.x & (kWave - 1)) == 0 && votes)
-        atomicAdd(reinterpret_cast<unsigned long long*>(n_out + blockIdx.y), (unsigned long long)__popcll(votes));
-}
 
-__global__ void flush_clear_kernel(uint64_t* n_out, uint32_t count) {
-    if (threadIdx.x < count) n_out[threadIdx.x] = 0;
+    // ---- positions of the survivors (block-wide prefix sum); order[] becomes output slot -> entry of the segment
+    uint32_t keep = 0, mine[kSortItems];
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++) {
+        const uint32_t p = o + i;
+        mine[i] = p < len && s.lose[p] == 0 ? len - 1 - s.order[p] : ~0u;
+        keep += mine[i] != ~0u ? 1 : 0;
+    }
+    uint32_t incl = keep;
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t v = __shfl_up(incl, off, kWave);
+        if ((int)(tid & (kWave - 1)) >= off) incl += v;
+    }
+    if ((tid & (kWave - 1)) == kWave - 1) s.wave_count[tid / kWave] = incl;
+    __syncthreads();
+    uint32_t slot = incl - keep, total = 0;
+    for (uint32_t w = 0; w < kSortThreads / kWave; w++) {
+        if (w < tid / kWave) slot += s.wave_count[w];
+        total += s.wave_count[w];
+    }
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++)
+        if (mine[i] != ~0u) s.order[slot++] = (uint16_t)mine[i];
+    if (tid == 0) counts[blockIdx.x] = total;
+    __syncthreads();
+    // ---- output, four lanes per entry
+    const uint4* from = reinterpret_cast<const uint4*>(src);
+    uint4* to = reinterpret_cast<uint4*>(out + first);
+    for (uint32_t x = tid; x < total * 4; x += kSortThreads) to[x] = from[(uint32_t)s.order[x >> 2] * 4 + (x & 3)];
 }
-
-constexpr uint64_t kFlushDirect = 8192;    // up to here one all-pairs sort of the whole buffer
-constexpr uint64_t kFlushSegment = 4096;   // beyond: segments of this many entries, then one merge of the segments
-static_assert(kFlushSegment * LSM_MAX_RUNS >= LSM_MAX_BUFFER, "the segments of the largest buffer must fit one compaction");
 
 __host__ inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Workspace of the segmented path: sorted segments | winner flags | segment counts | compaction workspace.
+// Workspace of the segmented path: sorted segments | segment counts | compaction workspace.
 struct FlushLayout {
-    size_t sorted, winner, counts, compact, total;
+    size_t sorted, counts, compact, total;
     uint32_t segments;
     uint64_t upper[LSM_MAX_RUNS];  // entries per segment, newest segment first (the order the compaction takes them in)
 };
@@ -112,16 +347,10 @@ static FlushLayout flush_layout(uint64_t n) {
         l.upper[l.segments - 1 - g] = (n - lo < kFlushSegment) ? n - lo : kFlushSegment;
     }
     l.sorted = 0;
-    l.winner = up256(n * sizeof(lsm_entry_t));
-    l.counts = l.winner + up256(n * sizeof(uint32_t));
-    l.compact = l.counts + up256(2 * LSM_MAX_RUNS * sizeof(uint64_t));
+    l.counts = up256(n * sizeof(lsm_entry_t));
+    l.compact = l.counts + up256(LSM_MAX_RUNS * sizeof(uint64_t));
     l.total = l.compact + lsm_compact_workspace_bytes(l.upper, l.segments);
     return l;
-}
-
-// counts of the segments in write order -> the same counts in the order of the compaction's runs (newest first)
-__global__ void flush_reverse_counts_kernel(const uint64_t* in, uint64_t* out, uint32_t segments) {
-    if (threadIdx.x < segments) out[threadIdx.x] = in[segments - 1 - threadIdx.x];
 }
 
 }  // namespace lsm
@@ -150,33 +379,23 @@ extern "C" int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm
     uint4* fence_out = reinterpret_cast<uint4*>(out->fence_keys);
     const uint32_t fence_stride = out->fence_keys ? out->fence_stride : 1u;
     if (direct) {
-        hipLaunchKernelGGL(flush_clear_kernel, dim3(1), dim3(64), 0, stream, out->n_out, 1u);
-        if (n > 0) {
-            const uint32_t blocks = (uint32_t)((n + kFlushThreads - 1) / kFlushThreads);
-            uint32_t* winner = static_cast<uint32_t*>(workspace);
-            hipLaunchKernelGGL(flush_kernel<false>, dim3(blocks), dim3(kFlushThreads), 0, stream, buffer, (uint32_t)n, (uint32_t)n, winner,
-                               out->entries, out->n_out, fence_out, fence_stride);
-            hipLaunchKernelGGL(flush_kernel<true>, dim3(blocks), dim3(kFlushThreads), 0, stream, buffer, (uint32_t)n, (uint32_t)n, winner,
-                               out->entries, out->n_out, fence_out, fence_stride);
-        }
+        uint32_t* packed = static_cast<uint32_t*>(workspace);
+        const uint32_t per_block = kPlaceThreads / 4;
+        if (n > 0)
+            hipLaunchKernelGGL(flush_rank_kernel, dim3(((uint32_t)n + kRankEntries - 1) / kRankEntries), dim3(kRankThreads), 0, stream, buffer, (uint32_t)n, packed);
+        hipLaunchKernelGGL(flush_place_kernel, dim3(n > 0 ? ((uint32_t)n + per_block - 1) / per_block : 1), dim3(kPlaceThreads), 0, stream, buffer,
+                           (uint32_t)n, packed, out->entries, out->n_out, fence_out, fence_stride);
         return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
     // segments sorted on their own, into the workspace
     const FlushLayout l = flush_layout(n);
     char* base = static_cast<char*>(workspace);
     lsm_entry_t* sorted = reinterpret_cast<lsm_entry_t*>(base + l.sorted);
-    uint32_t* winner = reinterpret_cast<uint32_t*>(base + l.winner);
-    uint64_t* counts = reinterpret_cast<uint64_t*>(base + l.counts);  // [segments] in write order, then [segments] newest first
-    hipLaunchKernelGGL(flush_clear_kernel, dim3(1), dim3(64), 0, stream, counts, l.segments);
-    const dim3 grid((uint32_t)(kFlushSegment / kFlushThreads), l.segments);
-    hipLaunchKernelGGL(flush_kernel<false>, grid, dim3(kFlushThreads), 0, stream, buffer, (uint32_t)n, (uint32_t)kFlushSegment, winner, sorted,
-                       counts, (uint4*)nullptr, 1u);
-    hipLaunchKernelGGL(flush_kernel<true>, grid, dim3(kFlushThreads), 0, stream, buffer, (uint32_t)n, (uint32_t)kFlushSegment, winner, sorted,
-                       counts, (uint4*)nullptr, 1u);
-    hipLaunchKernelGGL(flush_reverse_counts_kernel, dim3(1), dim3(64), 0, stream, counts, counts + LSM_MAX_RUNS, l.segments);
+    uint64_t* counts = reinterpret_cast<uint64_t*>(base + l.counts);  // newest segment first
+    hipLaunchKernelGGL(flush_sort_kernel, dim3(l.segments), dim3(kSortThreads), 0, stream, buffer, (uint32_t)n, sorted, counts);
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
     // one merge of the sorted segments, the one written last first; their lengths stay on the device
     const lsm_entry_t* ptr[LSM_MAX_RUNS];
     for (uint32_t j = 0; j < l.segments; j++) ptr[j] = sorted + (uint64_t)(l.segments - 1 - j) * kFlushSegment;
-    return compact_device_lengths(ptr, l.upper, counts + LSM_MAX_RUNS, l.segments, 0, out, base + l.compact, workspace_bytes - l.compact, stream);
+    return compact_device_lengths(ptr, l.upper, counts, l.segments, 0, out, base + l.compact, workspace_bytes - l.compact, stream);
 }

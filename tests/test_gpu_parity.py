@@ -606,6 +606,31 @@ def test_flush_of_the_write_buffer(g, oracle, n, n_keys):
         assert np.array_equal(as_bytes(compact_gpu(g, [out[:m].contiguous()], 0)).reshape(-1, 64), want)
 
 
+@pytest.mark.parametrize("n", [2, 16, 17, 63, 65, 2048, 2049, 4097, 8192,          # ranks by comparing all pairs: tiles, slices
+                               8193, 12288, 12289, 16385 + 4095])                  # segments sorted in LDS: full, one entry, ragged
+@pytest.mark.parametrize("shared", [8, 14, 29])
+def test_flush_of_keys_with_common_prefixes(g, oracle, n, shared):
+    """Keys that agree in their first `shared` bytes, so that the order is decided behind the 14 (or 16) bytes that are
+    compared first; a few thousand distinct keys and seqnos that repeat.  Exact: bytes are copied, not computed."""
+    print("flush, common prefix", n, shared, flush=True)
+    rs = np.random.RandomState(n * 31 + shared)
+    a = np.zeros((n, 64), dtype=np.uint8)
+    a[:, :32] = 0x5A
+    a[:, shared:32] = rs.randint(0, 14 if shared == 29 else 256, size=(n, 32 - shared))
+    if shared < 29:  # tails from a small set: groups of equal and of nearly equal keys
+        a[:, shared:32] = a[rs.randint(0, max(1, n // 3), size=n), shared:32]
+        a[:, 31] = rs.randint(0, 3, size=n)
+    rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+    rec["seqno"] = rs.randint(0, 5, size=n)
+    rec["type"] = (rs.rand(n) < 0.2).astype(np.uint8)
+    rec["vptr"] = np.arange(n)
+    out, n_out = g.lsm_flush_buffer(to_dev(a))
+    torch.cuda.synchronize()
+    want = oracle.flush_buffer(a)
+    assert int(n_out.item()) == want.shape[0]
+    assert np.array_equal(as_bytes(out[: want.shape[0]]).reshape(-1, 64), want)
+
+
 # ------------------------------------------------------------------ range lookups (section 2.2, appendix B get_batch)
 def test_range_scan_equals_filtered_compaction(g, oracle, cfg1):
     """Entries of a key range, newest version of each, live only = the checker's last-level compaction of all runs
