@@ -42,8 +42,6 @@ __device__ __forceinline__ bool key_equal(const Key& a, const Key& b) {
     return ((a.w[0] ^ b.w[0]) | (a.w[1] ^ b.w[1]) | (a.w[2] ^ b.w[2]) | (a.w[3] ^ b.w[3])) == 0;
 }
 
-__device__ __forceinline__ bool key_less_equal(const Key& a, const Key& b) { return !key_less(b, a); }
-
 // key < k for a key kept as two separate halves (bytes 0..15 at lo, bytes 16..31 at hi); the second
 // half is read only when the first 16 bytes tie.
 __device__ __forceinline__ bool entry_key_less(const uint4* lo, const uint4* hi, const Key& k) {

@@ -27,6 +27,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <type_traits>
 
 #include "lsm_common.h"
 
@@ -41,7 +42,6 @@ constexpr int kRoundItems = 4;                         // outputs per thread in 
 __host__ __device__ inline uint64_t tile_nominal(uint32_t k) { return (uint64_t)kTileCap - k; }
 constexpr uint64_t kCoarseStride = 16;                 // every 16th boundary is searched over whole sequences first
 constexpr uint64_t kSampleStride = 32;                 // one key in 32 is copied for the sampled partition
-constexpr uint64_t kShortRunsTotal = 262144;           // inputs of at most this many entries (16 MiB) are searched as cached data
 constexpr uint64_t kSampledMinTiles = 2048;            // inputs of fewer tiles search the runs directly (measured crossover)
 constexpr uint32_t kSpinLimit = 1u << 22;              // polls of one look-back window before giving up
 
@@ -232,13 +232,157 @@ __device__ __forceinline__ void split_two(const lsm_entry_t* a, const uint64_t n
     while (lo < hi) {
         const uint64_t mid = lo + (hi - lo + 1) / 2;  // lo < mid <= hi, so d - mid < nb
         // mid entries of a fit among the first d iff a[mid - 1] does not come after b[d - mid]
-        if (key_less_equal(load_key(a + mid - 1), load_key(b + (d - mid)))) lo = mid;
+        if (!key_less(load_key(b + (d - mid)), load_key(a + mid - 1))) lo = mid;
         else hi = mid - 1;
     }
     ia = lo;
     ib = d - lo;
     // a's version of a key just before the boundary and b's just after it: the key starts one entry earlier
     if (ia > 0 && ib < nb && key_equal(load_key(a + ia - 1), load_key(b + ib))) ia--;
+}
+
+// ---------------------------------------------------------------------------------------
+// The same selection by one wave per boundary, for inputs of up to a few thousand boundaries: there the pivoting above
+// is bound by its chain of some ninety dependent reads (4 x 16,384 entries: 68 us; 8 x 500,000: 178 us).
+// The window [lo_j, hi_j) of run j is kept by the lanes with lane % group == j, so all of the wave's 64 / group groups
+// know all windows.  A round reads `m` evenly spaced records of every window at once (one round trip) into LDS.  A
+// record P with y_j records of window j below it has a lower bound there between xmin_j and xmax_j (the neighbouring
+// records' positions), so Lmin(P) <= L(P) <= Lmax(P): if Lmax <= r, P is not above the answer and every lo_j moves up to
+// its xmin_j; if Lmin > r, every hi_j moves down to its xmax_j.  Every step in LDS tries one record per group, evenly
+// spaced in the window with the most records left, until the records that are left are in doubt; the next round reads
+// the windows that remain more finely.  Once no window is longer than m all bounds are exact.
+// Usually some three gaps per run remain of a window.  Where the runs' keys lie so that less than half of the
+// candidates goes, one pivot is placed exactly (searched in the runs themselves), which halves the widest window.
+// ---------------------------------------------------------------------------------------
+// Sum / max over aligned groups of 1, 2, 4, ... 64 lanes; every lane of the wave must call.  Up to 16 lanes by DPP.
+template <typename Op>
+__device__ __forceinline__ uint32_t group_reduce(uint32_t v, int group, Op op) {
+    if (group > 1) v = op(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0xB1, 0xF, 0xF, true));    // lane ^ 1
+    if (group > 2) v = op(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x4E, 0xF, 0xF, true));    // lane ^ 2
+    if (group > 4) v = op(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xF, 0xF, true));   // mirrored inside 8 lanes
+    if (group > 8) v = op(v, (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x140, 0xF, 0xF, true));   // mirrored inside 16 lanes
+    if (group > 16) v = op(v, (uint32_t)__shfl_xor((int)v, 16, kWave));
+    if (group > 32) v = op(v, (uint32_t)__shfl_xor((int)v, 32, kWave));
+    return v;
+}
+__device__ __forceinline__ uint32_t group_sum_u32(uint32_t v, int group) {
+    return group_reduce(v, group, [](uint32_t a, uint32_t b) { return a + b; });
+}
+__device__ __forceinline__ uint32_t group_max_u32(uint32_t v, int group) {
+    return group_reduce(v, group, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+}
+
+template <int kPerLane>  // records a lane reads per round
+struct WindowShared {
+    ulonglong2 lo[kWave * kPerLane + kWave];  // key bytes 0..15 of record i of window j at j * (m + 1) + i: lists start in different banks
+    ulonglong2 hi[kWave * kPerLane + kWave];  // key bytes 16..31
+};
+
+// The lower bound in run j = lane % group of the key with the largest L <= r.  The whole wave calls; lanes without a run
+// pass len = 0.  Fewer than 2^32 entries in all.
+template <int kPerLane>
+__device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, const lsm_entry_t* run, const uint32_t len, const uint32_t r,
+                                                 const int group_log) {
+    const int lane = threadIdx.x & (kWave - 1), group = 1 << group_log;
+    const uint32_t j = lane & (group - 1), g = (uint32_t)lane >> group_log;
+    const int groups_log = 6 - group_log;
+    const uint32_t groups = 1u << groups_log, m = groups * kPerLane;
+    ulonglong2* const my_lo = s.lo + j * (m + 1);
+    ulonglong2* const my_hi = s.hi + j * (m + 1);
+    uint32_t lo = 0, hi = len;
+    for (;;) {
+        const uint32_t width = hi - lo;
+        const bool exact = __ballot(width > m) == 0;
+        const uint32_t gap = width > m ? width / m : 1;
+        const uint32_t first = lo + (width > m ? gap >> 1 : 0);  // record i of the window is at first + i * gap
+        const uint32_t count = width < m ? width : m;
+        __syncthreads();  // one wave: the last round's reads are done
+        {
+            uint4 a[kPerLane], b[kPerLane];
+#pragma unroll
+            for (int c = 0; c < kPerLane; c++) {
+                const uint32_t i = g + c * groups;
+                if (i < count) {
+                    const uint4* e = reinterpret_cast<const uint4*>(run + first + i * gap);
+                    a[c] = load_global_u4(e);
+                    b[c] = load_global_u4(e + 1);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < kPerLane; c++) {
+                const uint32_t i = g + c * groups;
+                if (i < count) {
+                    const Key key = key_from_raw(a[c], b[c]);
+                    my_lo[i] = make_ulonglong2(key.w[0], key.w[1]);
+                    my_hi[i] = make_ulonglong2(key.w[2], key.w[3]);
+                }
+            }
+        }
+        __syncthreads();
+        uint32_t left = 0, right = count;         // records of this window that are not settled
+        uint32_t next_lo = lo, next_hi = hi;
+        for (;;) {
+            const uint32_t widest = (uint32_t)__builtin_amdgcn_readfirstlane((int)group_max_u32(((right - left) << 6) | j, group));
+            const uint32_t w = widest >> 6, jw = widest & 63;
+            if (w == 0) break;
+            const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)left, (int)jw);
+            const uint32_t at_w = from + (w >= groups ? ((2 * g + 1) * w) >> (groups_log + 1) : (g < w ? g : w - 1));
+            const ulonglong2 plo = s.lo[jw * (m + 1) + at_w], phi = s.hi[jw * (m + 1) + at_w];
+            const bool own = j == jw;
+            uint32_t y = left, end = right;
+            bool same = own;  // record y is the pivot's key: a version of it in another run, or the pivot itself
+            if (own) y = end = at_w;
+            while (y < end) {
+                const uint32_t mid = (y + end) >> 1;
+                const ulonglong2 a = my_lo[mid];
+                bool less = (a.x < plo.x) | ((a.x == plo.x) & (a.y < plo.y)), equal = false;
+                if ((a.x == plo.x) & (a.y == plo.y)) {
+                    const ulonglong2 b = my_hi[mid];
+                    less = (b.x < phi.x) | ((b.x == phi.x) & (b.y < phi.y));
+                    equal = (b.x == phi.x) & (b.y == phi.y);
+                }
+                y = less ? mid + 1 : y;
+                end = less ? end : mid;
+                same = less ? same : equal;
+            }
+            const uint32_t at = first + y * gap;
+            const uint32_t xmax = own || y < count ? at : hi;
+            const uint32_t xmin = own ? at : (y > 0 ? at - gap + 1 : lo);
+            const uint64_t below = __ballot(group_sum_u32(xmax, group) <= r), above = __ballot(group_sum_u32(xmin, group) > r);
+            if ((below | above) == 0) break;  // all in doubt
+            // the groups' records ascend: the last one that is not above the answer, the first one that is
+            if (below != 0) {
+                const int src = ((63 - __builtin_clzll(below)) & ~(group - 1)) | (int)j;
+                left = (uint32_t)__shfl((int)(y + (same ? 1 : 0)), src, kWave);
+                next_lo = (uint32_t)__shfl((int)xmin, src, kWave);
+            }
+            if (above != 0) {
+                const int src = (__builtin_ctzll(above) & ~(group - 1)) | (int)j;
+                right = (uint32_t)__shfl((int)y, src, kWave);
+                next_hi = (uint32_t)__shfl((int)xmax, src, kWave);
+            }
+            right = right < left ? left : right;  // crossed bounds, here and below: only inputs that break the precondition
+        }
+        if (exact) return next_lo;
+        next_hi = next_hi < next_lo ? next_lo : next_hi;
+        const bool slow = group_sum_u32(next_hi - next_lo, group) > group_sum_u32(hi - lo, group) / 2;
+        lo = next_lo;
+        hi = next_hi;
+        if (__builtin_amdgcn_readfirstlane(slow ? 1 : 0)) {
+            const uint32_t len_w = group_max_u32(hi - lo, group);
+            const int src = (int)__builtin_ctzll(__ballot(hi - lo == len_w));
+            const uint32_t mid = (uint32_t)__shfl((int)(lo + len_w / 2), src, kWave);
+            const lsm_entry_t* run_w = reinterpret_cast<const lsm_entry_t*>(__shfl(reinterpret_cast<uint64_t>(run), src, kWave));
+            if (len_w > 1) {  // true: some window was longer than m
+                const Key pivot = load_key(run_w + mid);
+                bool eq;
+                uint32_t lb = (uint32_t)lower_bound_eq4(run, lo, hi, pivot, eq);
+                if (lane == src || (int)j == (src & (group - 1))) lb = mid;
+                if (group_sum_u32(lb, group) <= r) lo = lb;
+                else hi = lb;
+            }
+        }
+    }
 }
 
 // Lane bookkeeping shared by the partition kernels: which problem and which sequence a lane has.
@@ -256,36 +400,52 @@ __device__ __forceinline__ GroupLane group_lane(int group) {
     return g;
 }
 
-// Direct search over whole runs, for inputs of a few dozen tiles: one launch, one group per interior boundary.
+// Search over whole runs, for inputs of up to kSampledMinTiles tiles, and of two runs at any size: one launch.
 // kInit: the launch also clears the tile status words and writes the first and last split rows, which saves the
-// separate init launch (a small compaction is then two launches: this one and the merge).  kShort: the runs are
-// short enough to stay in cache, where four-way search steps (half the dependent round trips) are the faster ones.
-template <bool kInit, bool kShort>
-__global__ void __launch_bounds__(256) partition_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, int group) {
-    if (kInit) {
-        const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
-        for (uint64_t t = i; t < n_tiles; t += stride) ws.status[t] = 0;
-        if (i < rt.k) {
-            ws.splits[i] = 0;
-            ws.splits[n_tiles * rt.k + i] = run_len(rt, (uint32_t)i);
-        }
+// separate init launch (a small compaction is then two launches: this one and the merge).
+template <bool kInit>
+__device__ __forceinline__ void partition_init(const RunTable& rt, const Workspace& ws, uint64_t n_tiles) {
+    if (!kInit) return;
+    const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t t = i; t < n_tiles; t += stride) ws.status[t] = 0;
+    if (i < rt.k) {
+        ws.splits[i] = 0;
+        ws.splits[n_tiles * rt.k + i] = run_len(rt, (uint32_t)i);
     }
-    const GroupLane g = group_lane(group);
-    const uint64_t b = g.slot + 1;
-    const bool own = b < n_tiles && g.member < (int)rt.k;
-    if (rt.k == 2) {  // two runs (every merge of a leveled tree): the merge path is a plain bisection
-        if (own && g.member == 0) {
-            uint64_t ia, ib;
-            split_two(rt.ptr[0], run_len(rt, 0), rt.ptr[1], run_len(rt, 1), b * tile_nominal(2), ia, ib);
-            ws.splits[b * 2 + 0] = ia;
-            ws.splits[b * 2 + 1] = ib;
-        }
-        return;
-    }
-    const lsm_entry_t* run = own ? rt.ptr[g.member] : nullptr;
-    const uint64_t best = select_split<kShort>(run, 0, own ? run_len(rt, g.member) : 0, b * tile_nominal(rt.k), own, g.member, group, g.group_base);
-    if (own) ws.splits[b * rt.k + g.member] = best;
 }
+
+// two runs (every merge of a leveled tree): one lane per boundary
+constexpr int kTwoThreads = 64;
+template <bool kInit>
+__global__ void __launch_bounds__(kTwoThreads) partition_two_kernel(RunTable rt, Workspace ws, uint64_t n_tiles) {
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint64_t b = (uint64_t)blockIdx.x * kTwoThreads + threadIdx.x + 1;
+    if (b >= n_tiles) return;
+    uint64_t ia, ib;
+    split_two(rt.ptr[0], run_len(rt, 0), rt.ptr[1], run_len(rt, 1), b * tile_nominal(2), ia, ib);
+    ws.splits[b * 2 + 0] = ia;
+    ws.splits[b * 2 + 1] = ib;
+}
+
+// other run counts: one wave per boundary
+template <bool kInit, int kPerLane>
+__global__ void __launch_bounds__(kWave) partition_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, int group_log) {
+    __shared__ WindowShared<kPerLane> s;
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint32_t b = blockIdx.x + 1, lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
+    const uint32_t best = window_split<kPerLane>(s, j < rt.k ? rt.ptr[j] : nullptr, j < rt.k ? (uint32_t)run_len(rt, j) : 0,
+                                                 b * (uint32_t)tile_nominal(rt.k), group_log);
+    if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
+}
+static_assert(kSampledMinTiles * kTileCap < (1ull << 32), "the window search counts in 32 bits");
+
+static int log2_ceil(uint32_t k) {
+    int log = 0;
+    while ((1u << log) < k) log++;
+    return log;
+}
+// Records a lane reads per round of the window search: 256 records in all for up to 16 runs, 512 beyond (16 or 8 per run).
+static int records_per_lane(int group_log) { return group_log <= 4 ? 4 : 8; }
 
 // ---------------------------------------------------------------------------------------
 // Sampled partition, for large inputs.  Searching the runs directly costs tens of scattered
@@ -1085,37 +1245,34 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
 }
 
 // ---------------------------------------------------------------------------------------
-// Partition of a batch of independent compactions: one group of lanes per tile of the launch.  The group of a
-// job's tile number t > 0 searches boundary t over the job's whole runs (the jobs of a batch are small); the groups
-// of a job's first and last tile also write the first (all zero) and the last (run lengths) row of its split table,
-// and every group clears its tile's status word.
+// Partition of a batch of independent compactions: one wave per tile of the launch.  The wave of a job's tile number
+// t > 0 searches boundary t over the job's whole runs (the jobs of a batch are small); the waves of a job's first and
+// last tile also write the first (all zero) and the last (run lengths) row of its split table, and every wave clears its
+// tile's status word.
 // ---------------------------------------------------------------------------------------
-__global__ void __launch_bounds__(256) partition_batch_kernel(Workspace ws, ModeArgs ma, uint64_t n_tiles, int group) {
-    const GroupLane g = group_lane(group);
-    const bool live = g.slot < n_tiles;
-    JobDesc d = {};
-    if (live) d = ma.jobs[ma.tile_job[g.slot]];
-    const uint64_t t = live ? g.slot - d.first_tile : 0;
-    const bool own = live && g.member < (int)d.k;
-    const lsm_entry_t* run = own ? ma.run_ptr[d.run_off + g.member] : nullptr;
-    const uint64_t len = own ? ma.run_n[d.run_off + g.member] : 0;
-    const bool search = t > 0;  // the same for all lanes of a group
+template <int kPerLane>
+__global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, ModeArgs ma, int group_log) {
+    __shared__ WindowShared<kPerLane> s;
+    const JobDesc d = ma.jobs[ma.tile_job[blockIdx.x]];
+    const uint32_t t = (uint32_t)(blockIdx.x - d.first_tile);
+    const uint32_t lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
+    const bool own = j < d.k;
+    const lsm_entry_t* run = own ? ma.run_ptr[d.run_off + j] : nullptr;
+    const uint64_t len = own ? ma.run_n[d.run_off + j] : 0;
     uint64_t best = 0;
-    if (d.k == 2) {  // the two lanes of the group walk the merge path together (the same reads) and keep one bound each
-        if (own && search) {
-            uint64_t ia, ib;
-            split_two(ma.run_ptr[d.run_off], ma.run_n[d.run_off], ma.run_ptr[d.run_off + 1], ma.run_n[d.run_off + 1], t * tile_nominal(2), ia, ib);
-            best = g.member == 0 ? ia : ib;
-        }
-    } else {
-        best = select_split<false>(run, 0, (own && search) ? len : 0, t * tile_nominal(d.k ? d.k : 1), own && search, g.member, group, g.group_base);
+    if (t > 0 && d.k == 2) {  // every lane walks the merge path (the same reads)
+        uint64_t ia, ib;
+        split_two(ma.run_ptr[d.run_off], ma.run_n[d.run_off], ma.run_ptr[d.run_off + 1], ma.run_n[d.run_off + 1], t * tile_nominal(2), ia, ib);
+        best = j == 0 ? ia : ib;
+    } else if (t > 0) {
+        best = window_split<kPerLane>(s, run, (uint32_t)len, t * (uint32_t)tile_nominal(d.k), group_log);
     }
-    if (own) {
+    if (lane < d.k) {
         uint64_t* rows = ws.splits + d.splits_off;
-        rows[t * d.k + g.member] = search ? best : 0;
-        if (t + 1 == d.n_tiles) rows[(t + 1) * d.k + g.member] = len;
+        rows[t * d.k + lane] = best;
+        if (t + 1 == d.n_tiles) rows[(t + 1) * d.k + lane] = len;
     }
-    if (live && g.member == 0) ws.status[g.slot] = 0;
+    if (lane == 0) ws.status[blockIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1221,13 +1378,20 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
         const uint64_t per_block = (uint64_t)(256 / kWave) * (kWave / group);  // selection problems per workgroup
         auto blocks = [&](uint64_t problems) { return dim3((uint32_t)((problems + per_block - 1) / per_block)); };
         if (direct) {
-            // a few dozen boundaries: every one searched over whole runs (a coarse pass first would be a second
-            // dependent launch, which costs more than the longer searches)
-            const bool brief = total <= kShortRunsTotal;
-            if (fused_init && brief) hipLaunchKernelGGL((partition_kernel<true, true>), blocks(n_tiles - 1), dim3(256), 0, stream, rt, ws, n_tiles, group);
-            else if (fused_init) hipLaunchKernelGGL((partition_kernel<true, false>), blocks(n_tiles - 1), dim3(256), 0, stream, rt, ws, n_tiles, group);
-            else if (brief) hipLaunchKernelGGL((partition_kernel<false, true>), blocks(n_tiles - 1), dim3(256), 0, stream, rt, ws, n_tiles, group);
-            else hipLaunchKernelGGL((partition_kernel<false, false>), blocks(n_tiles - 1), dim3(256), 0, stream, rt, ws, n_tiles, group);
+            const int group_log = log2_ceil(n_runs);
+            const dim3 waves((uint32_t)(n_tiles - 1));
+            auto launch = [&](auto init) {
+                constexpr bool kInit = decltype(init)::value;
+                if (n_runs == 2)
+                    hipLaunchKernelGGL(partition_two_kernel<kInit>, dim3((uint32_t)((n_tiles - 1 + kTwoThreads - 1) / kTwoThreads)), dim3(kTwoThreads), 0,
+                                       stream, rt, ws, n_tiles);
+                else if (records_per_lane(group_log) == 4)
+                    hipLaunchKernelGGL((partition_kernel<kInit, 4>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+                else
+                    hipLaunchKernelGGL((partition_kernel<kInit, 8>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+            };
+            if (fused_init) launch(std::true_type{});
+            else launch(std::false_type{});
         } else {
             uint64_t m_max = 0;
             for (uint32_t j = 0; j < n_runs; j++) m_max = ws.st.m[j] > m_max ? ws.st.m[j] : m_max;
@@ -1520,10 +1684,11 @@ extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs,
     ma.jobs = reinterpret_cast<const JobDesc*>(base + l.jobs);
     ma.run_ptr = reinterpret_cast<const lsm_entry_t* const*>(base + l.run_ptr);
     ma.run_n = reinterpret_cast<const uint64_t*>(base + l.run_n);
-    int group = 1;
-    while (group < (int)l.k_max) group <<= 1;
-    const uint64_t per_block = (uint64_t)(256 / kWave) * (kWave / group);
-    hipLaunchKernelGGL(partition_batch_kernel, dim3((uint32_t)((l.tiles + per_block - 1) / per_block)), dim3(256), 0, stream, ws, ma, l.tiles, group);
+    const int group_log = log2_ceil(l.k_max);
+    if (records_per_lane(group_log) == 4)
+        hipLaunchKernelGGL(partition_batch_kernel<4>, dim3((uint32_t)l.tiles), dim3(kWave), 0, stream, ws, ma, group_log);
+    else
+        hipLaunchKernelGGL(partition_batch_kernel<8>, dim3((uint32_t)l.tiles), dim3(kWave), 0, stream, ws, ma, group_log);
     RunTable rt = {};
     rt.k = 1;
     if (any_fences)  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)

@@ -84,6 +84,37 @@ def test_run_counts_and_ragged_lengths(g, oracle, k):
         _check_compact(g, oracle, runs, flags)
 
 
+@pytest.mark.parametrize("k", [3, 4, 5, 16, 32, 33, 64])
+@pytest.mark.parametrize("shape", ["nested", "stairs", "copies", "one long"])
+def test_tile_boundaries_of_uneven_runs(g, oracle, k, shape):
+    """Boundary searches where evenly spaced records say little: every run inside one gap of the run before, runs one
+    behind the other, the same keys in every run, one long run beside runs of a few entries."""
+    print("boundaries", k, shape, flush=True)
+    rs = np.random.RandomState(k)
+    total = 30000
+    runs = []
+    for j in range(k):
+        n = total // k if shape != "one long" else (total if j == k // 2 else 3)
+        if shape == "nested":
+            half = 1 << (62 - (58 * j) // k)
+            lead = (1 << 62) + rs.randint(-(half >> 1), half >> 1, size=n)
+        elif shape == "stairs":
+            lead = ((k - j) << 56) + rs.randint(0, 1 << 56, size=n)
+        elif shape == "copies":
+            lead = np.arange(n, dtype=np.int64) * 12345
+        else:
+            lead = rs.randint(0, 1 << 40, size=n)
+        a = np.zeros((n, 64), dtype=np.uint8)
+        a[:, :8] = lead.astype(">u8").view(np.uint8).reshape(n, 8)
+        a = a[np.unique(lead, return_index=True)[1]]
+        rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+        rec["seqno"] = rs.randint(0, 1 << 40, size=rec.shape[0])
+        rec["type"] = (rs.rand(rec.shape[0]) < 0.1).astype(np.uint8)
+        runs.append(to_dev(a))
+    for flags in (0, 1):
+        _check_compact(g, oracle, runs, flags)
+
+
 @pytest.mark.parametrize("case", ["same_keys", "interleaved", "one_inside_the_other", "short_and_long", "batch"])
 def test_two_runs_many_tiles(g, oracle, case):
     """Two runs (boundaries by bisection on the merge path): every key in both runs (each boundary falls between the
