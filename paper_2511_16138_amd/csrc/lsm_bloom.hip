@@ -57,76 +57,101 @@ __global__ void bloom_insert_batch_kernel(BloomJobs jobs) {
     }
 }
 
-// A filter of at most kBloomSmallBlocks blocks (64 KiB) is built by one workgroup in LDS and written out once: one
-// launch and no global atomics, for the short runs of a tree's upper levels.  blockIdx.y = run.
+// A filter of at most kBloomSmallBlocks blocks (64 KiB) is built in LDS, for the short runs of a tree's upper levels.
+// blockIdx.y = run, blockIdx.x = a share of kBloomShare keys of it.  A run of one share is written out by its only
+// workgroup; the shares of a longer one are combined by atomics in the order of the words (whole lines at a time and
+// one per word, where an atomic per key goes to a line of its own: 16 x 30,000 keys took 39 us that way), on a
+// filter that an earlier launch has cleared.  One workgroup for 36,000 keys took 22 us: it reads 2.3 MB.
 constexpr uint32_t kBloomSmallBlocks = 4096;
-constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a filter is left to the whole device
+constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a filter is left to the atomics
 constexpr int kBloomSmallThreads = 1024;
+constexpr uint32_t kBloomShare = 4 * kBloomSmallThreads;
+static uint32_t bloom_shares(uint64_t n) { return n ? (uint32_t)((n + kBloomShare - 1) / kBloomShare) : 1; }
 __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs jobs) {
-    __shared__ uint32_t f[kBloomSmallBlocks * 4];
+    __shared__ uint64_t words[kBloomSmallBlocks * 2];
+    uint32_t* f = reinterpret_cast<uint32_t*>(words);
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
-    const uint64_t n = jobs.n[blockIdx.y];
+    const uint64_t n = jobs.n[blockIdx.y], first = (uint64_t)blockIdx.x * kBloomShare;
+    if (blockIdx.x > 0 && first >= n) return;             // a shorter run than the longest of the batch
     const uint32_t n_blocks = jobs.n_blocks[blockIdx.y];  // <= kBloomSmallBlocks (checked by the host)
-    for (uint32_t w = threadIdx.x; w < n_blocks * 4; w += kBloomSmallThreads) f[w] = 0;
+    // all keys of a thread are read before the first is hashed
+    constexpr int kAhead = kBloomShare / kBloomSmallThreads;
+    Key key[kAhead];
+#pragma unroll
+    for (int a = 0; a < kAhead; a++) {
+        const uint64_t i = first + threadIdx.x + (uint64_t)a * kBloomSmallThreads;
+        if (i < n) key[a] = load_key(entries + i);
+    }
+    for (uint32_t w = threadIdx.x; w < n_blocks * 2; w += kBloomSmallThreads) words[w] = 0;
     __syncthreads();
-    // four keys per thread and step, all read before the first is hashed: a short run is one or two round trips
-    constexpr int kAhead = 4;
-    for (uint64_t i0 = threadIdx.x; i0 < n; i0 += (uint64_t)kAhead * kBloomSmallThreads) {
-        Key key[kAhead];
 #pragma unroll
-        for (int a = 0; a < kAhead; a++) {
-            const uint64_t i = i0 + (uint64_t)a * kBloomSmallThreads;
-            key[a] = load_key(entries + (i < n ? i : i0));
-        }
-#pragma unroll
-        for (int a = 0; a < kAhead; a++) {
-            if (i0 + (uint64_t)a * kBloomSmallThreads >= n) break;
-            uint4 mask;
-            const uint32_t block = bloom_block(bloom_hash(key[a], mask), n_blocks);
-            if (mask.x) atomicOr(&f[block * 4 + 0], mask.x);
-            if (mask.y) atomicOr(&f[block * 4 + 1], mask.y);
-            if (mask.z) atomicOr(&f[block * 4 + 2], mask.z);
-            if (mask.w) atomicOr(&f[block * 4 + 3], mask.w);
-        }
+    for (int a = 0; a < kAhead; a++) {
+        if (first + threadIdx.x + (uint64_t)a * kBloomSmallThreads >= n) break;
+        uint4 mask;
+        const uint32_t block = bloom_block(bloom_hash(key[a], mask), n_blocks);
+        if (mask.x) atomicOr(&f[block * 4 + 0], mask.x);
+        if (mask.y) atomicOr(&f[block * 4 + 1], mask.y);
+        if (mask.z) atomicOr(&f[block * 4 + 2], mask.z);
+        if (mask.w) atomicOr(&f[block * 4 + 3], mask.w);
     }
     __syncthreads();
-    uint4* out = reinterpret_cast<uint4*>(jobs.words[blockIdx.y]);
-    const uint4* src = reinterpret_cast<const uint4*>(f);
-    for (uint32_t b = threadIdx.x; b < n_blocks; b += kBloomSmallThreads) out[b] = src[b];
+    if (n <= kBloomShare) {
+        uint4* out = reinterpret_cast<uint4*>(jobs.words[blockIdx.y]);
+        for (uint32_t b = threadIdx.x; b < n_blocks; b += kBloomSmallThreads) out[b] = reinterpret_cast<const uint4*>(words)[b];
+    } else {
+        unsigned long long* out = reinterpret_cast<unsigned long long*>(jobs.words[blockIdx.y]);
+        for (uint32_t w = threadIdx.x; w < n_blocks * 2; w += kBloomSmallThreads)
+            if (words[w]) atomicOr(out + w, (unsigned long long)words[w]);
+    }
+}
+
+// the runs of `jobs`, all with small filters
+static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, hipStream_t stream) {
+    uint32_t shares = 1, most_blocks = 0;
+    for (uint32_t j = 0; j < count; j++) {
+        const uint32_t s = bloom_shares(jobs.n[j]);
+        shares = s > shares ? s : shares;
+        most_blocks = jobs.n_blocks[j] > most_blocks ? jobs.n_blocks[j] : most_blocks;
+    }
+    if (shares > 1) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
+    hipLaunchKernelGGL(bloom_small_kernel, dim3(shares, count), dim3(kBloomSmallThreads), 0, stream, jobs);
 }
 
 // ---------------------------------------------------------------------------------------
 // Filter of a long run without global atomics.  The atomic build above is bound by the rate of read-modify-write
 // operations on scattered 8-byte words (two per key); this one moves the keys' 8-byte hashes instead: they are sorted
-// by ranges of kBucketBlocks consecutive filter blocks ("buckets", 64 KiB; the passes of lsm_partition.h), then one
-// workgroup per bucket builds the bucket's 64 KiB of filter in LDS from the bucket's hashes and writes it out once.
-// The order of the hashes inside a bucket does not matter: bits are only ever set.
+// by ranges of consecutive filter blocks (at most 4,096 blocks = 64 KiB; the passes of lsm_partition.h), then one
+// workgroup per range builds the range's part of the filter in LDS from its hashes and writes it out once.
+// The order of the hashes inside a range does not matter: bits are only ever set.
 // ---------------------------------------------------------------------------------------
-constexpr uint32_t kBucketBlocks = kRangeUnits;  // filter blocks per bucket (64 KiB of LDS)
-
 __global__ void hash_keys_kernel(const lsm_entry_t* entries, uint64_t n, uint64_t* hashes) {
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) hashes[i] = bloom_key_hash(load_key(entries + i));
 }
 
-// one workgroup per bucket; after the scatter pass cursors[b] is the END of bucket b's hashes, totals[b] their number
-__global__ void __launch_bounds__(kPartThreads) bucket_fill_kernel(const uint64_t* bucketed, const unsigned long long* totals,
-                                                                  const unsigned long long* cursors, uint32_t n_blocks, uint4* filter) {
-    __shared__ uint32_t f[kBucketBlocks * 4];
-    const uint32_t bucket = blockIdx.x, first_block = bucket * kBucketBlocks;
-    const uint32_t blocks = n_blocks - first_block < kBucketBlocks ? n_blocks - first_block : kBucketBlocks;
+// one workgroup per range; kScan: `hashes` are all n hashes as they came (totals is not used), else they are sorted by range
+template <bool kScan>
+__global__ void __launch_bounds__(kPartThreads) bloom_fill_kernel(const uint64_t* hashes, uint64_t n, const uint32_t* totals, uint32_t n_blocks,
+                                                                 uint32_t unit_log, uint4* filter) {
+    __shared__ uint32_t f[kMaxRangeUnits * 4];
+    const uint32_t range = blockIdx.x, first_block = range << unit_log;
+    const uint32_t blocks = min(1u << unit_log, n_blocks - first_block);
     for (uint32_t w = threadIdx.x; w < blocks * 4; w += kPartThreads) f[w] = 0;
-    __syncthreads();
-    const uint64_t end = cursors[bucket], begin = end - totals[bucket];
-    for (uint64_t i = begin + threadIdx.x; i < end; i += kPartThreads) {
-        const uint64_t h = bucketed[i];
-        const uint4 mask = bloom_mask(h);
-        const uint32_t at = (bloom_block(h, n_blocks) - first_block) * 4;  // inside this bucket by construction
-        if (mask.x) atomicOr(&f[at + 0], mask.x);
-        if (mask.y) atomicOr(&f[at + 1], mask.y);
-        if (mask.z) atomicOr(&f[at + 2], mask.z);
-        if (mask.w) atomicOr(&f[at + 3], mask.w);
+    uint64_t begin = 0, end = n;
+    if (!kScan) {
+        begin = range_begin(totals, range);
+        end = begin + totals[range];
     }
+    __syncthreads();
+    part_for_each(begin, end, [&](uint64_t i) { return hashes[i]; }, [&](uint64_t, uint64_t h) {
+        const uint32_t block = bloom_block(h, n_blocks) - first_block;  // wraps for the blocks before the range
+        if (kScan && block >= blocks) return;
+        const uint4 mask = bloom_mask(h);
+        if (mask.x) atomicOr(&f[block * 4 + 0], mask.x);
+        if (mask.y) atomicOr(&f[block * 4 + 1], mask.y);
+        if (mask.z) atomicOr(&f[block * 4 + 2], mask.z);
+        if (mask.w) atomicOr(&f[block * 4 + 3], mask.w);
+    });
     __syncthreads();
     const uint4* src = reinterpret_cast<const uint4*>(f);
     for (uint32_t b = threadIdx.x; b < blocks; b += kPartThreads) filter[first_block + b] = src[b];
@@ -163,11 +188,13 @@ extern "C" int lsm_build_bloom_hashed(const uint64_t* hashes, uint64_t n, void* 
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     launch_range_partition<false>(hashes, n, n_blocks, l, workspace, stream);
     char* base = static_cast<char*>(workspace);
-    const unsigned long long* totals = reinterpret_cast<const unsigned long long*>(base + l.totals);
-    const unsigned long long* cursors = reinterpret_cast<const unsigned long long*>(base + l.cursors);
-    const uint64_t* bucketed = reinterpret_cast<const uint64_t*>(base + l.ranged);
-    hipLaunchKernelGGL(bucket_fill_kernel, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, bucketed, totals, cursors, (uint32_t)n_blocks,
-                       static_cast<uint4*>(filter_out));
+    const uint32_t* totals = reinterpret_cast<const uint32_t*>(base + l.totals);
+    if (l.scan)
+        hipLaunchKernelGGL(bloom_fill_kernel<true>, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, hashes, n, totals, (uint32_t)n_blocks, l.unit_log,
+                           static_cast<uint4*>(filter_out));
+    else
+        hipLaunchKernelGGL(bloom_fill_kernel<false>, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, reinterpret_cast<const uint64_t*>(base + l.ranged), n,
+                           totals, (uint32_t)n_blocks, l.unit_log, static_cast<uint4*>(filter_out));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 
@@ -192,7 +219,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
         jobs.n[0] = run->n;
         jobs.words[0] = static_cast<uint32_t*>(filter_out);
         jobs.n_blocks[0] = (uint32_t)n_blocks;
-        hipLaunchKernelGGL(bloom_small_kernel, dim3(1, 1), dim3(kBloomSmallThreads), 0, stream, jobs);
+        launch_bloom_small(jobs, 1, stream);
         return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
     uint64_t clear_blocks = (n_blocks + 255) / 256;
@@ -232,7 +259,7 @@ extern "C" int lsm_build_bloom_batch(const lsm_run_t* runs, void* const* filters
             most_entries = runs[first + j].n > most_entries ? runs[first + j].n : most_entries;
         }
         if (most_blocks <= kBloomSmallBlocks && most_entries <= kBloomSmallKeys) {
-            hipLaunchKernelGGL(bloom_small_kernel, dim3(1, count), dim3(kBloomSmallThreads), 0, stream, jobs);
+            launch_bloom_small(jobs, count, stream);
             continue;
         }
         uint64_t cx = (most_blocks + 255) / 256, ix = (most_entries + 255) / 256;

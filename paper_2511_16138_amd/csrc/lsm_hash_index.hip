@@ -10,7 +10,7 @@
 // slot), the rest is zero.  A bucket that more than eight keys fall into holds eight of them and has bit 15 of its
 // first tag field set, which sends a lookup that finds nothing among the eight to the fence index.
 //
-// Build: the hashes and their positions are sorted by ranges of 4,096 buckets (lsm_partition.h); one workgroup per
+// Build: the hashes and their positions are sorted by ranges of at most 4,096 buckets (lsm_partition.h); one workgroup per
 // range hands out the slots of its buckets with counters in LDS, assembles the buckets there, and writes every byte of
 // its range exactly once.
 // Which keys of a crowded bucket are kept, and the order of the slots in a bucket, depend on the order the
@@ -22,18 +22,24 @@
 
 namespace lsm {
 
-// One workgroup per range of kRangeUnits buckets.  The range is built a quarter at a time in LDS (1,024 buckets = 64 KiB)
-// and each quarter leaves with contiguous 16-byte stores: scattered 2- and 4-byte stores straight into the table cost
-// 4.6 bytes of HBM writes per byte of table.  Every pass reads the range's hashes again (they stay in the caches).
+// One workgroup per range.  The range is built 1,024 buckets (64 KiB) at a time in LDS and each part leaves with
+// contiguous 16-byte stores: scattered 2- and 4-byte stores straight into the table cost 4.6 bytes of HBM writes per byte
+// of table.  Every part reads the range's hashes again (they stay in the caches).  kScan: the hashes are not sorted
+// (`hashes` are all n of them, totals is not used), and the range picks its own.
 constexpr uint32_t kFillBuckets = 1024;
-__global__ void __launch_bounds__(kPartThreads) index_fill_kernel(const uint4* ranged, const unsigned long long* totals,
-                                                                 const unsigned long long* cursors, uint32_t n_buckets, uint4* table) {
+template <bool kScan>
+__global__ void __launch_bounds__(kPartThreads) index_fill_kernel(const uint64_t* hashes, const uint4* ranged, uint64_t n, const uint32_t* totals,
+                                                                 uint32_t n_buckets, uint32_t unit_log, uint4* table) {
     __shared__ uint4 part[kFillBuckets * 4];  // the buckets of this pass
     __shared__ uint32_t count[kFillBuckets];
-    const uint32_t range_first = blockIdx.x * kRangeUnits;
-    const uint64_t end = cursors[blockIdx.x], begin = end - totals[blockIdx.x];
-    for (uint32_t first_bucket = range_first; first_bucket < range_first + kRangeUnits && first_bucket < n_buckets; first_bucket += kFillBuckets) {
-        const uint32_t buckets = n_buckets - first_bucket < kFillBuckets ? n_buckets - first_bucket : kFillBuckets;
+    const uint32_t range_first = blockIdx.x << unit_log, range_last = min(n_buckets, range_first + (1u << unit_log));
+    uint64_t begin = 0, end = n;
+    if (!kScan) {
+        begin = range_begin(totals, blockIdx.x);
+        end = begin + totals[blockIdx.x];
+    }
+    for (uint32_t first_bucket = range_first; first_bucket < range_last; first_bucket += kFillBuckets) {
+        const uint32_t buckets = min(range_last - first_bucket, kFillBuckets);
         // every bucket starts empty: tag fields 0, positions all ones, the rest 0
         for (uint32_t i = threadIdx.x; i < buckets * 4; i += kPartThreads) {
             const uint32_t fill = ((i & 3) == 1 || (i & 3) == 2) ? kIndexNoEntry : 0u;
@@ -43,16 +49,16 @@ __global__ void __launch_bounds__(kPartThreads) index_fill_kernel(const uint4* r
         __syncthreads();
         uint16_t* tags = reinterpret_cast<uint16_t*>(part);
         uint32_t* words = reinterpret_cast<uint32_t*>(part);
-        for (uint64_t i = begin + threadIdx.x; i < end; i += kPartThreads) {
-            const uint4 rec = ranged[i];  // {h, position, 0}
-            const uint64_t h = ((uint64_t)rec.y << 32) | rec.x;
+        auto put = [&](uint64_t h, uint32_t position) {
             const uint32_t b = bloom_block(h, n_buckets) - first_bucket;  // wraps for the buckets before this pass
-            if (b >= buckets) continue;
+            if (b >= buckets) return;
             const uint32_t k = atomicAdd(&count[b], 1u);
-            if (k >= kIndexSlots) continue;  // a crowded bucket keeps the first eight keys that arrive
+            if (k >= kIndexSlots) return;  // a crowded bucket keeps the first eight keys that arrive
             tags[b * 32 + k] = (uint16_t)(h & kIndexTagMask);
-            words[b * 16 + 4 + k] = rec.z;
-        }
+            words[b * 16 + 4 + k] = position;
+        };
+        if (kScan) part_for_each(begin, end, [&](uint64_t i) { return hashes[i]; }, [&](uint64_t i, uint64_t h) { put(h, (uint32_t)i); });
+        else part_for_each(begin, end, [&](uint64_t i) { return ranged[i]; }, [&](uint64_t, const uint4 rec) { put(((uint64_t)rec.y << 32) | rec.x, rec.z); });
         __syncthreads();
         for (uint32_t b = threadIdx.x; b < buckets; b += kPartThreads)
             if (count[b] > kIndexSlots) tags[b * 32] |= 0x8000u;  // crowded
@@ -84,8 +90,13 @@ extern "C" int lsm_build_hash_index(const uint64_t* hashes, uint64_t n, void* ta
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     launch_range_partition<true>(hashes, n, n_buckets, l, workspace, stream);
     char* base = static_cast<char*>(workspace);
-    hipLaunchKernelGGL(index_fill_kernel, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, reinterpret_cast<const uint4*>(base + l.ranged),
-                       reinterpret_cast<const unsigned long long*>(base + l.totals),
-                       reinterpret_cast<const unsigned long long*>(base + l.cursors), (uint32_t)n_buckets, static_cast<uint4*>(table_out));
+    const uint4* ranged = reinterpret_cast<const uint4*>(base + l.ranged);
+    const uint32_t* totals = reinterpret_cast<const uint32_t*>(base + l.totals);
+    if (l.scan)
+        hipLaunchKernelGGL(index_fill_kernel<true>, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, hashes, ranged, n, totals, (uint32_t)n_buckets, l.unit_log,
+                           static_cast<uint4*>(table_out));
+    else
+        hipLaunchKernelGGL(index_fill_kernel<false>, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, hashes, ranged, n, totals, (uint32_t)n_buckets,
+                           l.unit_log, static_cast<uint4*>(table_out));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }

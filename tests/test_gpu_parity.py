@@ -557,6 +557,28 @@ def test_filter_built_from_hashes_equals_the_checker(g, oracle, n, bits):
         assert np.array_equal(as_bytes(tiny).reshape(-1, 16), oracle.build_bloom(run.cpu(), 3))
 
 
+@pytest.mark.parametrize("n", [4096, 4097, 32_768, 32_769,     # filters in LDS: one share, two, the largest, atomics
+                               65_535, 65_536, 65_537, 262_145])  # from hashes: unsorted up to 65,536, sorted by range beyond
+def test_filter_and_index_at_the_edges_of_their_builds(g, oracle, n):
+    """lsm_build_bloom, lsm_build_bloom_batch, lsm_build_bloom_hashed and lsm_build_hash_index where the build changes."""
+    from workloads import lsm
+    print("filter and index edges", n, flush=True)
+    w = lsm.config3(device=dev(), scale=64)
+    run = torch.from_numpy(oracle.compact([r.cpu() for r in w.runs[:8]], 0)[:n].view(np.int64).reshape(-1, 8).copy()).to(dev())
+    assert int(run.shape[0]) == n
+    want = oracle.build_bloom(run.cpu(), g.lsm_bloom_blocks(n, 16))
+    hashes = g.lsm_hash_keys(run)
+    short = run[:77].contiguous()
+    batch = g.lsm_build_bloom_batch([short, run], 16)
+    for got in (g.lsm_build_bloom(run, 16), batch[1], g.lsm_build_bloom_hashed(hashes, g.lsm_bloom_blocks(n, 16))):
+        torch.cuda.synchronize()
+        assert np.array_equal(as_bytes(got).reshape(-1, 16), want)
+    assert np.array_equal(as_bytes(batch[0]).reshape(-1, 16), oracle.build_bloom(short.cpu(), int(batch[0].shape[0])))
+    table = g.lsm_build_hash_index(hashes)
+    torch.cuda.synchronize()
+    assert oracle.hash_index_check(run.cpu(), table.cpu().numpy()) == 0
+
+
 # ------------------------------------------------------------------ prefix length by search (appendix B)
 def test_probe_length_equals_probe_on_prefix_closed_data(g, oracle, cfg1):
     """The generator evicts leaf first, so its trees are prefix-closed: the search over the prefix length gives the
