@@ -57,25 +57,35 @@ __global__ void bloom_insert_batch_kernel(BloomJobs jobs) {
     }
 }
 
-// A filter of at most kBloomSmallBlocks blocks (64 KiB) is built in LDS, for the short runs of a tree's upper levels.
-// blockIdx.y = run, blockIdx.x = a share of kBloomShare keys of it.  A run of one share is written out by its only
-// workgroup; the shares of a longer one are combined by atomics in the order of the words (whole lines at a time and
+// Sets the six bits of hash h in a filter block in LDS, one atomic per bit: putting them together as a mask first costs
+// more vector instructions than the one or two atomics it saves.
+__device__ __forceinline__ void bloom_set_lds(uint32_t* block, uint64_t h) {
+    const uint64_t g = bloom_bits(h);
+#pragma unroll
+    for (int j = 0; j < 6; j++) {
+        const uint32_t b = (uint32_t)(g >> (7 * j)) & 127;
+        atomicOr(&block[b >> 5], 1u << (b & 31));
+    }
+}
+
+// A filter of at most kBloomSmallBlocks blocks (128 KiB) is built in LDS, for the short runs of a tree's upper levels.
+// blockIdx.y = run, blockIdx.x = a share of its keys, `ahead` keys per thread.  A run of one share is written out by its
+// only workgroup; the shares of a longer one are combined by atomics in the order of the words (whole lines at a time and
 // one per word, where an atomic per key goes to a line of its own: 16 x 30,000 keys took 39 us that way), on a
 // filter that an earlier launch has cleared.  One workgroup for 36,000 keys took 22 us: it reads 2.3 MB.
-constexpr uint32_t kBloomSmallBlocks = 4096;
+constexpr uint32_t kBloomSmallBlocks = 8192;
 constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a filter is left to the atomics
 constexpr int kBloomSmallThreads = 1024;
-constexpr uint32_t kBloomShare = 4 * kBloomSmallThreads;
-static uint32_t bloom_shares(uint64_t n) { return n ? (uint32_t)((n + kBloomShare - 1) / kBloomShare) : 1; }
+template <uint32_t kBlocks, int kAhead>
 __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs jobs) {
-    __shared__ uint64_t words[kBloomSmallBlocks * 2];
+    __shared__ uint64_t words[kBlocks * 2];
     uint32_t* f = reinterpret_cast<uint32_t*>(words);
+    constexpr uint32_t kShare = kAhead * kBloomSmallThreads;
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
-    const uint64_t n = jobs.n[blockIdx.y], first = (uint64_t)blockIdx.x * kBloomShare;
+    const uint64_t n = jobs.n[blockIdx.y], first = (uint64_t)blockIdx.x * kShare;
     if (blockIdx.x > 0 && first >= n) return;             // a shorter run than the longest of the batch
-    const uint32_t n_blocks = jobs.n_blocks[blockIdx.y];  // <= kBloomSmallBlocks (checked by the host)
+    const uint32_t n_blocks = jobs.n_blocks[blockIdx.y];  // <= kBlocks (checked by the host)
     // all keys of a thread are read before the first is hashed
-    constexpr int kAhead = kBloomShare / kBloomSmallThreads;
     Key key[kAhead];
 #pragma unroll
     for (int a = 0; a < kAhead; a++) {
@@ -87,15 +97,11 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
 #pragma unroll
     for (int a = 0; a < kAhead; a++) {
         if (first + threadIdx.x + (uint64_t)a * kBloomSmallThreads >= n) break;
-        uint4 mask;
-        const uint32_t block = bloom_block(bloom_hash(key[a], mask), n_blocks);
-        if (mask.x) atomicOr(&f[block * 4 + 0], mask.x);
-        if (mask.y) atomicOr(&f[block * 4 + 1], mask.y);
-        if (mask.z) atomicOr(&f[block * 4 + 2], mask.z);
-        if (mask.w) atomicOr(&f[block * 4 + 3], mask.w);
+        const uint64_t h = bloom_key_hash(key[a]);
+        bloom_set_lds(f + (uint64_t)bloom_block(h, n_blocks) * 4, h);
     }
     __syncthreads();
-    if (n <= kBloomShare) {
+    if (n <= kShare) {
         uint4* out = reinterpret_cast<uint4*>(jobs.words[blockIdx.y]);
         for (uint32_t b = threadIdx.x; b < n_blocks; b += kBloomSmallThreads) out[b] = reinterpret_cast<const uint4*>(words)[b];
     } else {
@@ -105,16 +111,26 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
     }
 }
 
-// the runs of `jobs`, all with small filters
-static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, hipStream_t stream) {
-    uint32_t shares = 1, most_blocks = 0;
+// The runs of `jobs`, all with small filters; `cleared`: the filters are known to be all zero.  A thread hashes one key
+// (hashing is some 800 cycles a key and wave: four per thread took 11 us where one takes 6), or two when one would be
+// more than a workgroup of them for every compute unit (16 x 30,000 keys: 19 us against 22).
+static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, bool cleared, hipStream_t stream) {
+    uint64_t most_keys = 0, all_keys = 0;
+    uint32_t most_blocks = 0;
     for (uint32_t j = 0; j < count; j++) {
-        const uint32_t s = bloom_shares(jobs.n[j]);
-        shares = s > shares ? s : shares;
+        most_keys = jobs.n[j] > most_keys ? jobs.n[j] : most_keys;
         most_blocks = jobs.n_blocks[j] > most_blocks ? jobs.n_blocks[j] : most_blocks;
+        all_keys += jobs.n[j];
     }
-    if (shares > 1) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
-    hipLaunchKernelGGL(bloom_small_kernel, dim3(shares, count), dim3(kBloomSmallThreads), 0, stream, jobs);
+    const bool two = all_keys > 256ull * kBloomSmallThreads || (most_keys > kBloomSmallThreads && most_keys <= 2 * kBloomSmallThreads);
+    const uint64_t share = (two ? 2 : 1) * (uint64_t)kBloomSmallThreads;
+    const dim3 grid(most_keys ? (uint32_t)((most_keys + share - 1) / share) : 1, count), threads(kBloomSmallThreads);
+    if (grid.x > 1 && !cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
+    const bool large = most_blocks > kBloomSmallBlocks / 2;
+    if (large && two) hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks, 2>), grid, threads, 0, stream, jobs);
+    else if (large) hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks, 1>), grid, threads, 0, stream, jobs);
+    else if (two) hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks / 2, 2>), grid, threads, 0, stream, jobs);
+    else hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks / 2, 1>), grid, threads, 0, stream, jobs);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -146,11 +162,7 @@ __global__ void __launch_bounds__(kPartThreads) bloom_fill_kernel(const uint64_t
     part_for_each(begin, end, [&](uint64_t i) { return hashes[i]; }, [&](uint64_t, uint64_t h) {
         const uint32_t block = bloom_block(h, n_blocks) - first_block;  // wraps for the blocks before the range
         if (kScan && block >= blocks) return;
-        const uint4 mask = bloom_mask(h);
-        if (mask.x) atomicOr(&f[block * 4 + 0], mask.x);
-        if (mask.y) atomicOr(&f[block * 4 + 1], mask.y);
-        if (mask.z) atomicOr(&f[block * 4 + 2], mask.z);
-        if (mask.w) atomicOr(&f[block * 4 + 3], mask.w);
+        bloom_set_lds(f + block * 4, h);
     });
     __syncthreads();
     const uint4* src = reinterpret_cast<const uint4*>(f);
@@ -219,7 +231,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
         jobs.n[0] = run->n;
         jobs.words[0] = static_cast<uint32_t*>(filter_out);
         jobs.n_blocks[0] = (uint32_t)n_blocks;
-        launch_bloom_small(jobs, 1, stream);
+        launch_bloom_small(jobs, 1, false, stream);
         return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
     uint64_t clear_blocks = (n_blocks + 255) / 256;
@@ -234,6 +246,42 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 
+namespace lsm {
+int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t stream) {
+    // a launch takes runs of one kind: small filters, or any
+    for (int large = 0; large < 2; large++) {
+        BloomJobs jobs = {};
+        uint32_t count = 0;
+        uint64_t most_blocks = 1, most_entries = 0;
+        for (uint32_t j = 0; j <= n_runs; j++) {
+            if (count == kBloomBatch || (j == n_runs && count > 0)) {
+                if (large == 0) {
+                    launch_bloom_small(jobs, count, cleared, stream);
+                } else {
+                    uint64_t cx = (most_blocks + 255) / 256, ix = (most_entries + 255) / 256;
+                    if (cx > 1024) cx = 1024;
+                    if (ix > 4096) ix = 4096;
+                    if (!cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((uint32_t)cx, count), dim3(256), 0, stream, jobs);
+                    if (most_entries > 0) hipLaunchKernelGGL(bloom_insert_batch_kernel, dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs);
+                }
+                jobs = BloomJobs{};
+                count = 0, most_blocks = 1, most_entries = 0;
+            }
+            if (j == n_runs) break;
+            if ((n_blocks[j] > kBloomSmallBlocks || runs[j].n > kBloomSmallKeys) != (large == 1)) continue;
+            jobs.entries[count] = runs[j].entries;
+            jobs.n[count] = runs[j].n;
+            jobs.words[count] = static_cast<uint32_t*>(filters_out[j]);
+            jobs.n_blocks[count] = (uint32_t)n_blocks[j];
+            most_blocks = n_blocks[j] > most_blocks ? n_blocks[j] : most_blocks;
+            most_entries = runs[j].n > most_entries ? runs[j].n : most_entries;
+            count++;
+        }
+    }
+    return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+}
+}  // namespace lsm
+
 extern "C" int lsm_build_bloom_batch(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs,
                                      void* stream_v) {
     using namespace lsm;
@@ -245,28 +293,5 @@ extern "C" int lsm_build_bloom_batch(const lsm_run_t* runs, void* const* filters
         if ((reinterpret_cast<uintptr_t>(filters_out[j]) & 15) != 0 || (reinterpret_cast<uintptr_t>(runs[j].entries) & 63) != 0)
             return LSM_ERR_BAD_ARG;
     }
-    hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    for (uint32_t first = 0; first < n_runs; first += kBloomBatch) {
-        const uint32_t count = n_runs - first < kBloomBatch ? n_runs - first : kBloomBatch;
-        BloomJobs jobs = {};
-        uint64_t most_blocks = 1, most_entries = 0;
-        for (uint32_t j = 0; j < count; j++) {
-            jobs.entries[j] = runs[first + j].entries;
-            jobs.n[j] = runs[first + j].n;
-            jobs.words[j] = static_cast<uint32_t*>(filters_out[first + j]);
-            jobs.n_blocks[j] = (uint32_t)n_blocks[first + j];
-            most_blocks = n_blocks[first + j] > most_blocks ? n_blocks[first + j] : most_blocks;
-            most_entries = runs[first + j].n > most_entries ? runs[first + j].n : most_entries;
-        }
-        if (most_blocks <= kBloomSmallBlocks && most_entries <= kBloomSmallKeys) {
-            launch_bloom_small(jobs, count, stream);
-            continue;
-        }
-        uint64_t cx = (most_blocks + 255) / 256, ix = (most_entries + 255) / 256;
-        if (cx > 1024) cx = 1024;
-        if (ix > 4096) ix = 4096;
-        hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((uint32_t)cx, count), dim3(256), 0, stream, jobs);
-        if (most_entries > 0) hipLaunchKernelGGL(bloom_insert_batch_kernel, dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs);
-    }
-    return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+    return build_filters(runs, filters_out, n_blocks, n_runs, false, static_cast<hipStream_t>(stream_v));
 }

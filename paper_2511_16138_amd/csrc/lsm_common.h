@@ -159,8 +159,10 @@ __device__ __forceinline__ uint64_t bloom_key_hash(const Key& k) {
     for (int i = 0; i < 4; i++) h = mix64(h ^ k.w[i]);
     return h;
 }
+// the bit positions, seven bits each from the lowest up
+__device__ __forceinline__ uint64_t bloom_bits(uint64_t h) { return mix64(h ^ 0x9E3779B97F4A7C15ull); }
 __device__ __forceinline__ uint4 bloom_mask(uint64_t h) {
-    const uint64_t g = mix64(h ^ 0x9E3779B97F4A7C15ull);
+    const uint64_t g = bloom_bits(h);
     uint32_t m[4] = {0, 0, 0, 0};
 #pragma unroll
     for (int j = 0; j < 6; j++) {
@@ -197,9 +199,19 @@ struct RunTable {
 };
 __device__ __forceinline__ uint64_t run_len(const RunTable& rt, uint32_t j) { return rt.n_dev ? rt.n_dev[j] : rt.n[j]; }
 
+// Calls between the parts of the library (arguments are checked by the caller).
+struct ClearSpan {  // device memory to be zeroed by a launch that is made anyway; 16-byte aligned
+    void* p = nullptr;
+    size_t bytes = 0;  // a multiple of 16
+};
+// lsm_compact and lsm_compact_batch that also zero a span (per job).  *cleared: whether lsm_compact had a launch to do it in.
+int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
+                     const ClearSpan& clear, bool* cleared, hipStream_t stream);
+int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, const ClearSpan* clear, hipStream_t stream);
+// lsm_build_bloom_batch; `cleared`: the filters are known to be all zero.
+int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t stream);
 // Compaction of runs whose exact lengths are only known on the device (n_upper[j] >= n_dev[j]; launch sizes come from
-// the upper bounds, surplus tiles stay empty).  Used inside the library; arguments are checked by the caller.
-// Needs a workspace of lsm_compact_workspace_bytes(n_upper, k) bytes.
+// the upper bounds, surplus tiles stay empty).  Needs a workspace of lsm_compact_workspace_bytes(n_upper, k) bytes.
 int compact_device_lengths(const lsm_entry_t* const* ptr, const uint64_t* n_upper, const uint64_t* n_dev, uint32_t k, uint32_t flags,
                            const lsm_out_t* out, void* workspace, size_t workspace_bytes, hipStream_t stream);
 

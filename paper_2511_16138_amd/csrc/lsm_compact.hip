@@ -75,6 +75,8 @@ struct Workspace {
     uint64_t* ycoarse;  // [(n_coarse + 2) * k]   sample-space splits of every kCoarseStride-th boundary
     uint64_t* ywin;     // [2 * (n_tiles - 1) * k] sample-space brackets of every boundary
     SampleTable st;
+    uint4* clear;       // zeroed by the partition launch for a later kernel of the caller
+    uint64_t clear_n;
 };
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -385,6 +387,28 @@ __device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, cons
     }
 }
 
+// split_two by a whole wave (all lanes get the result): 64 counts of [lo, hi] are tried together, so a step leaves a
+// 64th of the range.
+__device__ __forceinline__ void split_two_wave(const lsm_entry_t* a, const uint64_t na, const lsm_entry_t* b, const uint64_t nb, const uint64_t r,
+                                               uint64_t& ia, uint64_t& ib) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint64_t d = r < na + nb ? r : na + nb;
+    uint64_t lo = d > nb ? d - nb : 0, hi = d < na ? d : na;
+    while (lo < hi) {
+        const uint64_t w = hi - lo;
+        auto tried = [&](uint64_t l) { return lo + ((l + 1) * w + kWave - 1) / kWave; };  // ascending, the last is hi
+        const uint64_t mid = tried(lane);
+        const bool fits = !key_less(load_key(b + (d - mid)), load_key(a + mid - 1));  // mid entries of a are among the first d: true up to the count
+        const uint32_t n = __popcll(__ballot(fits));
+        const uint64_t new_lo = n > 0 ? tried(n - 1) : lo, new_hi = n < (uint32_t)kWave ? tried(n) - 1 : hi;
+        lo = new_lo;
+        hi = new_hi;
+    }
+    ia = lo;
+    ib = d - lo;
+    if (ia > 0 && ib < nb && key_equal(load_key(a + ia - 1), load_key(b + ib))) ia--;
+}
+
 // Lane bookkeeping shared by the partition kernels: which problem and which sequence a lane has.
 struct GroupLane {
     int member, group_base;
@@ -408,13 +432,28 @@ __device__ __forceinline__ void partition_init(const RunTable& rt, const Workspa
     if (!kInit) return;
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = i; t < n_tiles; t += stride) ws.status[t] = 0;
+    for (uint64_t c = i; c < ws.clear_n; c += stride) ws.clear[c] = make_uint4(0, 0, 0, 0);
     if (i < rt.k) {
         ws.splits[i] = 0;
         ws.splits[n_tiles * rt.k + i] = run_len(rt, (uint32_t)i);
     }
 }
 
-// two runs (every merge of a leveled tree): one lane per boundary
+// two runs (every merge of a leveled tree): one wave per boundary up to kTwoWaves boundaries, then one lane, whose search
+// reads a thirtieth of the records but takes log2 instead of log64 of the shorter run in dependent steps (10 boundaries of
+// 3,600 + 36,000 entries: 7.7 us with one lane each, about 4 with a wave; 10,000 of 2M + 20M: 21 us with one lane)
+constexpr uint64_t kTwoWaves = 1024;
+template <bool kInit>
+__global__ void __launch_bounds__(kWave) partition_two_wave_kernel(RunTable rt, Workspace ws, uint64_t n_tiles) {
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint64_t b = blockIdx.x + 1;
+    uint64_t ia, ib;
+    split_two_wave(rt.ptr[0], run_len(rt, 0), rt.ptr[1], run_len(rt, 1), b * tile_nominal(2), ia, ib);
+    if (threadIdx.x == 0) {
+        ws.splits[b * 2 + 0] = ia;
+        ws.splits[b * 2 + 1] = ib;
+    }
+}
 constexpr int kTwoThreads = 64;
 template <bool kInit>
 __global__ void __launch_bounds__(kTwoThreads) partition_two_kernel(RunTable rt, Workspace ws, uint64_t n_tiles) {
@@ -587,8 +626,10 @@ struct JobDesc {       // one compaction of a batch (device memory, written by t
     uint64_t* n_out;
     uint4* fence_out;      // optional fence index of the job's output
     uint32_t n_tiles, k, flags, fence_stride;
+    uint4* clear;          // optional memory the partition launch zeroes for a later kernel
+    uint64_t clear_n;
 };
-static_assert(sizeof(JobDesc) == 64, "descriptor layout");
+static_assert(sizeof(JobDesc) == 80, "descriptor layout");
 
 struct ModeArgs {
     // single form: optional filter hashes of the output's keys (kExtras = 2)
@@ -752,8 +793,12 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         uint64_t a = 0, b = 0;
         if (kMode == kModeSingle) {
             if (lane < (int)kk) {
-                a = ws.splits[t * kk + lane];
-                b = ws.splits[(t + 1) * kk + lane];
+                if (n_tiles == 1) {  // one tile is the whole input: launched on its own, without a split table
+                    b = run_len(rt, lane);
+                } else {
+                    a = ws.splits[t * kk + lane];
+                    b = ws.splits[(t + 1) * kk + lane];
+                }
                 s.run[lane] = rt.ptr[lane];
             }
         } else if (kMode == kModeRange) {
@@ -1250,19 +1295,45 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
 // last tile also write the first (all zero) and the last (run lengths) row of its split table, and every wave clears its
 // tile's status word.
 // ---------------------------------------------------------------------------------------
-template <int kPerLane>
-__global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, ModeArgs ma, int group_log) {
+// A batch that is small enough travels as a kernel argument (kInline): the partition's waves take their job from there,
+// and those of the jobs' first tiles put the descriptors where the merge kernel looks for them.  (Copying the table first
+// was a transfer of 4 us before the first kernel, and a wait of the host for the previous one.)
+constexpr uint32_t kInlineJobs = 20, kInlineRuns = 56;
+struct BatchInline {
+    JobDesc jobs[kInlineJobs];
+    const lsm_entry_t* run_ptr[kInlineRuns];
+    uint64_t run_n[kInlineRuns];
+    uint32_t n_jobs;
+};
+static_assert(sizeof(BatchInline) <= 2560, "fits the argument segment of a launch beside the rest");
+
+template <int kPerLane, bool kInline>
+__global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, ModeArgs ma, int group_log, BatchInline table) {
     __shared__ WindowShared<kPerLane> s;
-    const JobDesc d = ma.jobs[ma.tile_job[blockIdx.x]];
+    uint32_t job = 0;
+    if (kInline) {
+        for (uint32_t q = 1; q < table.n_jobs; q++) job = table.jobs[q].first_tile <= blockIdx.x ? q : job;
+        if (threadIdx.x == 0) const_cast<uint32_t*>(ma.tile_job)[blockIdx.x] = job;
+    } else {
+        job = ma.tile_job[blockIdx.x];
+    }
+    const JobDesc d = kInline ? table.jobs[job] : ma.jobs[job];
+    const lsm_entry_t* const* run_ptr = kInline ? table.run_ptr : ma.run_ptr;
+    const uint64_t* run_n = kInline ? table.run_n : ma.run_n;
     const uint32_t t = (uint32_t)(blockIdx.x - d.first_tile);
+    if (kInline && t == 0) {
+        if (threadIdx.x == 0) const_cast<JobDesc*>(ma.jobs)[job] = d;
+        if (threadIdx.x < d.k) const_cast<const lsm_entry_t**>(ma.run_ptr)[d.run_off + threadIdx.x] = run_ptr[d.run_off + threadIdx.x];
+    }
+    for (uint64_t c = t * (uint64_t)kWave + threadIdx.x; c < d.clear_n; c += (uint64_t)d.n_tiles * kWave) d.clear[c] = make_uint4(0, 0, 0, 0);
     const uint32_t lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
     const bool own = j < d.k;
-    const lsm_entry_t* run = own ? ma.run_ptr[d.run_off + j] : nullptr;
-    const uint64_t len = own ? ma.run_n[d.run_off + j] : 0;
+    const lsm_entry_t* run = own ? run_ptr[d.run_off + j] : nullptr;
+    const uint64_t len = own ? run_n[d.run_off + j] : 0;
     uint64_t best = 0;
-    if (t > 0 && d.k == 2) {  // every lane walks the merge path (the same reads)
+    if (t > 0 && d.k == 2) {
         uint64_t ia, ib;
-        split_two(ma.run_ptr[d.run_off], ma.run_n[d.run_off], ma.run_ptr[d.run_off + 1], ma.run_n[d.run_off + 1], t * tile_nominal(2), ia, ib);
+        split_two_wave(run_ptr[d.run_off], run_n[d.run_off], run_ptr[d.run_off + 1], run_n[d.run_off + 1], t * tile_nominal(2), ia, ib);
         best = j == 0 ? ia : ib;
     } else if (t > 0) {
         best = window_split<kPerLane>(s, run, (uint32_t)len, t * (uint32_t)tile_nominal(d.k), group_log);
@@ -1341,7 +1412,8 @@ namespace lsm {
 
 // Enqueues the kernels of one compaction.  rt.n are the run lengths the launch sizes are taken from.
 static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t* out, void* workspace, hipStream_t stream,
-                             const uint64_t* remap_base, uint32_t remap_files, const lsm_compact_events_t* ev) {
+                             const uint64_t* remap_base, uint32_t remap_files, const lsm_compact_events_t* ev, const ClearSpan& clear = ClearSpan(),
+                             bool* cleared = nullptr) {
     const uint32_t n_runs = rt.k;
     uint64_t total = 0;
     for (uint32_t j = 0; j < n_runs; j++) total += rt.n[j];
@@ -1349,11 +1421,18 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     if (n_tiles >= (1ull << 31)) return LSM_ERR_BAD_ARG;
     Workspace ws;
     carve(workspace, rt.n, n_runs, &ws);
+    ws.clear = nullptr;
+    ws.clear_n = 0;
     const uint64_t n_coarse = coarse_rows(n_tiles);  // boundaries kCoarseStride, 2 * kCoarseStride, ... < n_tiles
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
     const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs == 2);  // two runs: bisection on the merge path at any size
-    const bool fused_init = direct && !(flags & LSM_VALIDATE);
+    const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
+    if (clear.bytes != 0 && direct && fused_init) {
+        ws.clear = static_cast<uint4*>(clear.p);
+        ws.clear_n = clear.bytes / 16;
+        *cleared = true;
+    }
     if (!fused_init) {
         uint32_t init_blocks = (uint32_t)((n_tiles + 255) / 256);
         if (init_blocks == 0) init_blocks = 1;
@@ -1382,7 +1461,9 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
             const dim3 waves((uint32_t)(n_tiles - 1));
             auto launch = [&](auto init) {
                 constexpr bool kInit = decltype(init)::value;
-                if (n_runs == 2)
+                if (n_runs == 2 && n_tiles <= kTwoWaves)
+                    hipLaunchKernelGGL(partition_two_wave_kernel<kInit>, waves, dim3(kWave), 0, stream, rt, ws, n_tiles);
+                else if (n_runs == 2)
                     hipLaunchKernelGGL(partition_two_kernel<kInit>, dim3((uint32_t)((n_tiles - 1 + kTwoThreads - 1) / kTwoThreads)), dim3(kTwoThreads), 0,
                                        stream, rt, ws, n_tiles);
                 else if (records_per_lane(group_log) == 4)
@@ -1452,9 +1533,10 @@ int compact_device_lengths(const lsm_entry_t* const* ptr, const uint64_t* n_uppe
 
 }  // namespace lsm
 
-extern "C" int lsm_compact_remap(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace,
-                                 size_t workspace_bytes, void* stream_v, const lsm_remap_t* remap, const lsm_compact_events_t* ev) {
-    using namespace lsm;
+namespace lsm {
+// The checks of a compaction's arguments, and its launch.
+static int checked_compaction(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
+                              hipStream_t stream, const lsm_remap_t* remap, const lsm_compact_events_t* ev, const ClearSpan& clear, bool* cleared) {
     if (remap != nullptr && remap->n_files != 0 && remap->base == nullptr) return LSM_ERR_NULL;
     const uint64_t* remap_base = remap ? remap->base : nullptr;
     const uint32_t remap_files = remap ? remap->n_files : 0;
@@ -1484,7 +1566,20 @@ extern "C" int lsm_compact_remap(const lsm_run_t* runs, uint32_t n_runs, uint32_
     if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 ||
         workspace_bytes < lsm_compact_workspace_bytes(rt.n, n_runs))
         return LSM_ERR_WORKSPACE;
-    return launch_compaction(rt, flags, out, workspace, static_cast<hipStream_t>(stream_v), remap_base, remap_files, ev);
+    return launch_compaction(rt, flags, out, workspace, stream, remap_base, remap_files, ev, clear, cleared);
+}
+
+int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
+                     const ClearSpan& clear, bool* cleared, hipStream_t stream) {
+    *cleared = false;
+    return checked_compaction(runs, n_runs, flags, out, workspace, workspace_bytes, stream, nullptr, nullptr, clear, cleared);
+}
+}  // namespace lsm
+
+extern "C" int lsm_compact_remap(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace,
+                                 size_t workspace_bytes, void* stream, const lsm_remap_t* remap, const lsm_compact_events_t* ev) {
+    return lsm::checked_compaction(runs, n_runs, flags, out, workspace, workspace_bytes, static_cast<hipStream_t>(stream), remap, ev, lsm::ClearSpan(),
+                                   nullptr);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1612,10 +1707,8 @@ extern "C" size_t lsm_compact_batch_workspace_bytes(const lsm_compact_job_t* job
     return l.total;
 }
 
-extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, void* stream_v) {
-    using namespace lsm;
-    if (n_jobs == 0) return LSM_OK;
-    if (jobs == nullptr) return LSM_ERR_NULL;
+namespace lsm {
+int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, const ClearSpan* clear, hipStream_t stream) {
     BatchLayout l;
     const int rc = batch_layout(jobs, n_jobs, &l);
     if (rc != LSM_OK) return rc;
@@ -1632,17 +1725,27 @@ extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs,
         if (job.out.capacity < total) return LSM_ERR_CAPACITY;
     }
     if (workspace == nullptr || (reinterpret_cast<uintptr_t>(workspace) & 255) != 0 || workspace_bytes < l.total) return LSM_ERR_WORKSPACE;
-    // the host's table is built in pinned host memory kept per thread (so the copy below really is asynchronous) and
+    const bool fits_inline = n_jobs <= kInlineJobs && l.runs <= kInlineRuns;
+    BatchInline table = {};
+    JobDesc* desc = table.jobs;
+    const lsm_entry_t** run_ptr = table.run_ptr;
+    uint64_t* run_n = table.run_n;
+    // a larger table is built in pinned host memory kept per thread (so the copy below really is asynchronous) and
     // is not written again before the copy of the previous call from this thread has finished
     static thread_local BatchStaging staging;
     const size_t table_bytes = l.total - l.tile_job;
-    unsigned char* table = staging.acquire(table_bytes);
-    if (table == nullptr) return LSM_ERR_HIP;
-    memset(table, 0, table_bytes);
-    uint32_t* tile_job = reinterpret_cast<uint32_t*>(table);
-    JobDesc* desc = reinterpret_cast<JobDesc*>(table + (l.jobs - l.tile_job));
-    const lsm_entry_t** run_ptr = reinterpret_cast<const lsm_entry_t**>(table + (l.run_ptr - l.tile_job));
-    uint64_t* run_n = reinterpret_cast<uint64_t*>(table + (l.run_n - l.tile_job));
+    unsigned char* copied = nullptr;
+    uint32_t* tile_job = nullptr;
+    if (!fits_inline) {
+        copied = staging.acquire(table_bytes);
+        if (copied == nullptr) return LSM_ERR_HIP;
+        memset(copied, 0, table_bytes);
+        tile_job = reinterpret_cast<uint32_t*>(copied);
+        desc = reinterpret_cast<JobDesc*>(copied + (l.jobs - l.tile_job));
+        run_ptr = reinterpret_cast<const lsm_entry_t**>(copied + (l.run_ptr - l.tile_job));
+        run_n = reinterpret_cast<uint64_t*>(copied + (l.run_n - l.tile_job));
+    }
+    table.n_jobs = n_jobs;
     uint64_t tile = 0, split_word = 0, run = 0;
     bool any_fences = false;
     for (uint32_t j = 0; j < n_jobs; j++) {
@@ -1667,15 +1770,18 @@ extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs,
         d.n_tiles = (uint32_t)nt;
         d.k = job.n_runs;
         d.flags = job.flags;
-        for (uint64_t t = 0; t < nt; t++) tile_job[tile + t] = j;
+        d.clear = clear ? static_cast<uint4*>(clear[j].p) : nullptr;
+        d.clear_n = clear ? clear[j].bytes / 16 : 0;
+        for (uint64_t t = 0; tile_job != nullptr && t < nt; t++) tile_job[tile + t] = j;
         tile += nt;
         split_word += (nt + 1) * job.n_runs;
         run += job.n_runs;
     }
-    hipStream_t stream = static_cast<hipStream_t>(stream_v);
     char* base = static_cast<char*>(workspace);
-    if (hipMemcpyAsync(base + l.tile_job, table, table_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return LSM_ERR_HIP;
-    if (!staging.copy_enqueued(stream)) return LSM_ERR_HIP;
+    if (!fits_inline) {
+        if (hipMemcpyAsync(base + l.tile_job, copied, table_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return LSM_ERR_HIP;
+        if (!staging.copy_enqueued(stream)) return LSM_ERR_HIP;
+    }
     Workspace ws = {};
     ws.status = reinterpret_cast<uint64_t*>(base + l.status);
     ws.splits = reinterpret_cast<uint64_t*>(base + l.splits);
@@ -1685,10 +1791,14 @@ extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs,
     ma.run_ptr = reinterpret_cast<const lsm_entry_t* const*>(base + l.run_ptr);
     ma.run_n = reinterpret_cast<const uint64_t*>(base + l.run_n);
     const int group_log = log2_ceil(l.k_max);
-    if (records_per_lane(group_log) == 4)
-        hipLaunchKernelGGL(partition_batch_kernel<4>, dim3((uint32_t)l.tiles), dim3(kWave), 0, stream, ws, ma, group_log);
-    else
-        hipLaunchKernelGGL(partition_batch_kernel<8>, dim3((uint32_t)l.tiles), dim3(kWave), 0, stream, ws, ma, group_log);
+    const dim3 waves((uint32_t)l.tiles), wave(kWave);
+    if (records_per_lane(group_log) == 4) {
+        if (fits_inline) hipLaunchKernelGGL((partition_batch_kernel<4, true>), waves, wave, 0, stream, ws, ma, group_log, table);
+        else hipLaunchKernelGGL((partition_batch_kernel<4, false>), waves, wave, 0, stream, ws, ma, group_log, table);
+    } else {
+        if (fits_inline) hipLaunchKernelGGL((partition_batch_kernel<8, true>), waves, wave, 0, stream, ws, ma, group_log, table);
+        else hipLaunchKernelGGL((partition_batch_kernel<8, false>), waves, wave, 0, stream, ws, ma, group_log, table);
+    }
     RunTable rt = {};
     rt.k = 1;
     if (any_fences)  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
@@ -1698,6 +1808,13 @@ extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs,
         hipLaunchKernelGGL((merge_kernel<0, kModeBatch>), dim3((uint32_t)l.tiles), dim3(kMergeThreads), 0, stream, rt, ws, l.tiles, 0u,
                            (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+}
+}  // namespace lsm
+
+extern "C" int lsm_compact_batch(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, void* stream) {
+    if (n_jobs == 0) return LSM_OK;
+    if (jobs == nullptr) return LSM_ERR_NULL;
+    return lsm::compact_batch_clearing(jobs, n_jobs, workspace, workspace_bytes, nullptr, static_cast<hipStream_t>(stream));
 }
 
 // ---------------------------------------------------------------------------------------
