@@ -208,6 +208,18 @@ struct ClearSpan {  // device memory to be zeroed by a launch that is made anywa
 int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
                      const ClearSpan& clear, bool* cleared, hipStream_t stream);
 int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, const ClearSpan* clear, hipStream_t stream);
+struct IngestJob {  // a copy of a run with its fence index; clear_n 16-byte words are zeroed along with it
+    const lsm_entry_t* from;
+    lsm_entry_t* to;
+    uint64_t n;
+    void* fences;
+    uint4* clear;
+    uint64_t clear_n;
+};
+int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t fence_stride, hipStream_t stream);
+// Sum of hit_len[0 .. n_req) and number of values above zero, written to stats[0] and stats[1] (pinned host memory);
+// then stats[2] = ticket.
+int probe_stats(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket, hipStream_t stream);
 // lsm_build_bloom_batch; `cleared`: the filters are known to be all zero.
 int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t stream);
 // Compaction of runs whose exact lengths are only known on the device (n_upper[j] >= n_dev[j]; launch sizes come from

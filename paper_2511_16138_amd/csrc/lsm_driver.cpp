@@ -3,18 +3,24 @@
 // 3.3 (operation counts over a sliding window, a new (T, K) search when the mix has moved by more than a threshold)
 // and the lazy transition of appendix C (a level takes the current T and K when a run next arrives at it).  Nothing
 // here touches entries: merging, fence indices, filters, hash indices, lookups and the cost model are the library's
-// own entry points.  Merges, flushes and lookups are enqueued on the caller's stream; the lookup structures of a run
-// that has come to rest (fence index, filter, hash index) are built on a second stream of the driver's own, beside the
-// next compaction: a small merge and the filter of the run before it each keep the GPU busy for some 20 us on a few
-// compute units, and nothing but a lookup has to wait for the filter.
+// own entry points, and all of their work is enqueued on the caller's stream.
+//
+// A flush is a chain of small kernels whose lengths the host has to learn one by one (it decides by the number of entries a
+// merge left), so what counts is the number of launches and how the host learns a count.  It watches the word in pinned
+// memory that the merge writes: launch to count is 6 us where a stream synchronisation takes 11 (it enqueues a marker and
+// waits for that), and the filter of the run is enqueued while the merge's last stores drain.  A merge zeroes the memory of
+// the filter in its partition launch, so that the filter is one launch; a flushed run that comes to rest is copied, fenced
+// and has its filter zeroed in one.  (With the filters on a second stream, every cascade waited for that stream before
+// memory could go back to the pool, and the single workgroup that built a filter took 22 us beside a merge of 19:
+// 59 us a flush.)
 //
 // Device memory of the runs the driver creates comes from a pool that keeps every block for reuse (hipMalloc and
 // hipFree cost more than a small compaction, and hipFree waits for the device).  A block that is given back may still
 // be read by work already enqueued on the caller's stream; that is safe because its next user's work is enqueued later
-// on the same stream.  Memory that work on the second stream may still touch is given back only after that stream has
-// been waited for (finish_builds).
+// on the same stream.
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstring>
 #include <deque>
@@ -23,6 +29,7 @@
 #include <unordered_map>
 #include <vector>
 
+#include "lsm_common.h"
 #include "lsm_index.h"
 
 namespace {
@@ -73,6 +80,7 @@ struct Run {
     uint8_t* fences = nullptr;
     void* bloom = nullptr;
     uint64_t n_blocks = 0;
+    bool bloom_clear = false;  // bloom is memory that has been zeroed, not a filter yet
     void* index = nullptr;
     uint64_t n_buckets = 0;
 };
@@ -89,15 +97,21 @@ struct Batch {
 
 uint64_t ceil_div(uint64_t a, uint64_t b) { return (a + b - 1) / b; }
 
+constexpr uint64_t kCountUnset = UINT64_MAX - 1;  // a count word that no kernel has written yet (UINT64_MAX reports a failed merge)
+// Runs of at least this many entries get their filter from the keys' hashes, sorted by block range.
+constexpr uint64_t kHashedFilterEntries = 1ull << 20;
+
+void cpu_pause() {
+#if defined(__x86_64__)
+    __builtin_ia32_pause();
+#endif
+}
+
 }  // namespace
 
 struct lsm_driver {
     lsm_driver_config_t cfg;
     hipStream_t stream = nullptr;  // the caller's
-    hipStream_t side = nullptr;    // builds of lookup structures
-    hipEvent_t ordered = nullptr;  // makes `side` wait for what `stream` has been given so far
-    bool builds_pending = false;
-    std::vector<void*> build_scratch;  // temporaries of builds in flight
     double p = 1.0;
     uint32_t T = 0, K = 0;  // what the controller asks for now
     std::vector<Level> levels;
@@ -110,8 +124,9 @@ struct lsm_driver {
     void* workspace = nullptr;
     size_t workspace_bytes = 0;
     uint64_t* n_host = nullptr;  // pinned: the kernels write a compaction's count here
-    uint32_t* hit_host = nullptr;  // pinned copy of a probe batch's hit_len
-    size_t hit_host_count = 0;
+    uint64_t* stats_host = nullptr;  // pinned: what a probe batch found, and a ticket that says which batch
+    uint64_t tickets = 0;
+    Run* resting = nullptr;  // a run that has come to rest and still lacks lookup structures (see settle_all)
     uint64_t* counts_host = nullptr;  // pinned: the counts of a batch of compactions (lsm_driver_flush_many)
     size_t counts_host_count = 0;
     void* batch_workspace = nullptr;
@@ -155,104 +170,153 @@ struct lsm_driver {
 
     int wait() { return hipStreamSynchronize(stream) == hipSuccess ? LSM_OK : LSM_ERR_HIP; }
 
+    // Waits until a kernel of the stream has written *word (anything but `unset`).  The stream is asked now and then, so
+    // that an error there ends the wait.
+    int watch(const uint64_t* word, uint64_t unset) {
+        const volatile uint64_t* w = word;
+        for (uint32_t spins = 1; *w == unset; spins++) {
+            cpu_pause();
+            if (spins % 16384 != 0) continue;
+            const hipError_t e = hipStreamQuery(stream);
+            if (e == hipErrorNotReady) continue;
+            if (e != hipSuccess || *w == unset) return LSM_ERR_HIP;
+        }
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return LSM_OK;
+    }
+
     // What the driver needs of the GPU runtime is created by the first call that works on runs, so that the controller
     // (note_writes, note_reads, the log) can be used, and tested, on its own.
     int gpu_ready() {
         if (n_host != nullptr) return LSM_OK;
-        if (hipStreamCreateWithFlags(&side, hipStreamNonBlocking) != hipSuccess) return LSM_ERR_HIP;
-        if (hipEventCreateWithFlags(&ordered, hipEventDisableTiming) != hipSuccess) return LSM_ERR_HIP;
+        if (stats_host == nullptr && hipHostMalloc(reinterpret_cast<void**>(&stats_host), 4 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess)
+            return LSM_ERR_HIP;
+        stats_host[2] = 0;
         return hipHostMalloc(reinterpret_cast<void**>(&n_host), sizeof(uint64_t), hipHostMallocDefault) == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
 
-    // Waits for the builds on the second stream.  Needed before a lookup uses the structures, and before any memory the
-    // builds read or write goes back to the pool.
-    int finish_builds() {
-        if (!builds_pending) return LSM_OK;
-        builds_pending = false;
-        const bool ok = hipStreamSynchronize(side) == hipSuccess;
-        for (void* p : build_scratch) pool.give(p);
-        build_scratch.clear();
-        return ok ? LSM_OK : LSM_ERR_HIP;
-    }
+    bool wants_index(uint64_t n) const { return cfg.hash_index_from != 0 && n >= cfg.hash_index_from && n <= (1ull << 27); }
+    // filters that are built straight from the entries, on memory zeroed beforehand
+    bool plain_filter(uint64_t n) const { return cfg.bloom_bits != 0 && n < kHashedFilterEntries && !wants_index(n) && lsm_bloom_blocks(n, cfg.bloom_bits) != 0; }
 
-    // Filter and hash index of a run that has come to rest; the keys are hashed once for both.  Second stream.
-    int build_lookup(Run& r) {
-        hipStream_t stream = side;
-        auto scratch = [this](size_t bytes) {
+    // Filter and hash index of a run that has come to rest, from the keys' hashes (computed once for both).  The
+    // temporaries go back to the pool at once: their next user's work comes later on the stream.
+    int build_hashed(Run& r) {
+        std::vector<void*> scratch;
+        auto take = [&](size_t bytes) {
             void* p = pool.take(bytes);
-            if (p != nullptr) build_scratch.push_back(p);
+            if (p != nullptr) scratch.push_back(p);
             return p;
         };
-        const bool indexed = cfg.hash_index_from != 0 && r.n >= cfg.hash_index_from && r.n <= (1ull << 27);
+        const bool indexed = wants_index(r.n) && r.index == nullptr;
         const lsm_run_t run{r.entries, r.n};
-        uint64_t* hashes = nullptr;
-        int rc = LSM_OK;
-        if (indexed) {
-            hashes = static_cast<uint64_t*>(scratch(r.n * 8));
-            if (hashes == nullptr) return LSM_ERR_HIP;
-            rc = lsm_hash_keys(&run, hashes, stream);
-        }
+        uint64_t* hashes = static_cast<uint64_t*>(take(r.n * 8));
+        int rc = hashes == nullptr ? (int)LSM_ERR_HIP : lsm_hash_keys(&run, hashes, stream);
         if (rc == LSM_OK && cfg.bloom_bits != 0 && r.bloom == nullptr) {
             r.n_blocks = lsm_bloom_blocks(r.n, cfg.bloom_bits);
             if (r.n_blocks != 0) {
                 r.bloom = pool.take(r.n_blocks * 16);
                 if (r.bloom == nullptr) rc = LSM_ERR_HIP;
-                // a long run: the filter is built from the hashes, sorted by block range (no atomic traffic on the filter)
-                const size_t ws_bytes = (hashes != nullptr || r.n >= (1ull << 20)) ? lsm_bloom_workspace_bytes(r.n, r.n_blocks) : 0;
-                if (rc == LSM_OK && ws_bytes != 0) {
-                    if (hashes == nullptr) {
-                        hashes = static_cast<uint64_t*>(scratch(r.n * 8));
-                        rc = hashes == nullptr ? (int)LSM_ERR_HIP : lsm_hash_keys(&run, hashes, stream);
-                    }
-                    void* ws = rc == LSM_OK ? scratch(ws_bytes) : nullptr;
-                    if (rc == LSM_OK) rc = ws == nullptr ? (int)LSM_ERR_HIP : lsm_build_bloom_hashed(hashes, r.n, r.bloom, r.n_blocks, ws, ws_bytes, stream);
-                } else if (rc == LSM_OK) {
+                const size_t ws_bytes = lsm_bloom_workspace_bytes(r.n, r.n_blocks);
+                void* ws = rc == LSM_OK && ws_bytes != 0 ? take(ws_bytes) : nullptr;
+                if (rc == LSM_OK && ws_bytes != 0)
+                    rc = ws == nullptr ? (int)LSM_ERR_HIP : lsm_build_bloom_hashed(hashes, r.n, r.bloom, r.n_blocks, ws, ws_bytes, stream);
+                else if (rc == LSM_OK)
                     rc = lsm_build_bloom(&run, r.bloom, r.n_blocks, stream);
-                }
             }
         }
         if (rc == LSM_OK && indexed) {
             r.n_buckets = lsm_hash_index_buckets(r.n);
             const size_t ws_bytes = lsm_hash_index_workspace_bytes(r.n);
             r.index = pool.take(r.n_buckets * 64);
-            void* ws = scratch(ws_bytes);
+            void* ws = take(ws_bytes);
             rc = (r.index == nullptr || ws == nullptr) ? (int)LSM_ERR_HIP : lsm_build_hash_index(hashes, r.n, r.index, ws, ws_bytes, stream);
         }
+        for (void* p : scratch) pool.give(p);
         return rc;
     }
 
-    // A run that comes to rest in a level gets whatever lookup structure it still lacks.  (Runs that are merged away at
-    // once - a flushed run arriving at a full level, a run moved down onto another - never get any.)
-    // The entries of a merged run are complete (its count has been waited for, and with it the caller's stream); those of
-    // a flushed or loaded run are whatever the caller's stream has been given so far, so the second stream is made to
-    // wait for that.
-    int settle(Run& r) {
-        if (r.n == 0) return LSM_OK;
-        const bool from_caller = r.transient || !r.owned;
-        if (r.transient) {
-            void* copy = pool.take(r.n * sizeof(lsm_entry_t));
-            if (copy == nullptr) return LSM_ERR_HIP;
-            if (hipMemcpyAsync(copy, r.entries, r.n * sizeof(lsm_entry_t), hipMemcpyDeviceToDevice, stream) != hipSuccess) return LSM_ERR_HIP;
-            r.entries = static_cast<const lsm_entry_t*>(copy);
-            r.owned = true, r.transient = false;
-        }
-        if (from_caller && (hipEventRecord(ordered, stream) != hipSuccess || hipStreamWaitEvent(side, ordered, 0) != hipSuccess)) return LSM_ERR_HIP;
-        builds_pending = true;
-        if (r.fences == nullptr) {
-            r.fences = static_cast<uint8_t*>(pool.take(ceil_div(r.n, cfg.fence_stride) * LSM_KEY_BYTES));
-            if (r.fences == nullptr) return LSM_ERR_HIP;
-            const lsm_run_t run{r.entries, r.n};
-            const int rc = lsm_build_fences(&run, cfg.fence_stride, r.fences, side);
-            if (rc != LSM_OK) return rc;
-        }
-        const bool wants_index = cfg.hash_index_from != 0 && r.n >= cfg.hash_index_from && r.n <= (1ull << 27);
-        if (r.index == nullptr && (r.bloom == nullptr || wants_index)) return build_lookup(r);  // the filter may be there already (batch)
-        return LSM_OK;
+    // Memory for the filter of a run of at most `n` entries, to be zeroed by a launch that is made anyway.
+    int take_filter(Run& r, uint64_t n, lsm::ClearSpan* clear) {
+        r.bloom = nullptr, r.bloom_clear = false;
+        clear->p = nullptr, clear->bytes = 0;
+        if (n == 0 || !plain_filter(n)) return LSM_OK;
+        clear->bytes = lsm_bloom_blocks(n, cfg.bloom_bits) * 16;
+        clear->p = r.bloom = pool.take(clear->bytes);
+        return r.bloom != nullptr ? LSM_OK : LSM_ERR_HIP;
     }
 
-    // All runs of a level into one; the fence index of the output is written in the same pass.  Waits for the count
-    // (the kernels store it to pinned host memory).  Watching that word from the host instead of synchronising the
-    // stream was measured and is no faster: the store becomes visible when the kernel ends.
+    // The runs that have come to rest in `count` drivers (of one stream) get whatever lookup structure they still lack: the
+    // copies of flushed runs in one launch, and the filters of all short runs in one.  (Runs that are merged away at once -
+    // a flushed run arriving at a full level, a run moved down onto another - never get any.)
+    static int settle_all(lsm_driver* const* drivers, uint32_t count) {
+        std::vector<lsm::IngestJob> ingest;
+        std::vector<lsm_run_t> runs[2];  // [1]: with a filter memory that is zeroed by then
+        std::vector<void*> filters[2];
+        std::vector<uint64_t> blocks[2];
+        hipStream_t stream = nullptr;
+        uint32_t stride = 1;
+        for (uint32_t i = 0; i < count; i++) {
+            lsm_driver* d = drivers[i];
+            Run* r = d->resting;
+            if (r == nullptr || r->n == 0) continue;
+            stream = d->stream;
+            if (r->transient) {
+                lsm_entry_t* copy = static_cast<lsm_entry_t*>(d->pool.take(r->n * sizeof(lsm_entry_t)));
+                r->fences = static_cast<uint8_t*>(d->pool.take(ceil_div(r->n, d->cfg.fence_stride) * LSM_KEY_BYTES));
+                lsm::ClearSpan clear;
+                if (copy == nullptr || r->fences == nullptr || d->take_filter(*r, r->n, &clear) != LSM_OK) return LSM_ERR_HIP;
+                if (!ingest.empty() && stride != d->cfg.fence_stride) {  // one stride per launch
+                    const int rc = lsm::ingest_runs(ingest.data(), (uint32_t)ingest.size(), stride, stream);
+                    if (rc != LSM_OK) return rc;
+                    ingest.clear();
+                }
+                stride = d->cfg.fence_stride;
+                ingest.push_back(lsm::IngestJob{r->entries, copy, r->n, r->fences, static_cast<uint4*>(clear.p), clear.bytes / 16});
+                r->entries = copy, r->owned = true, r->transient = false, r->bloom_clear = r->bloom != nullptr;
+            } else if (r->fences == nullptr) {
+                r->fences = static_cast<uint8_t*>(d->pool.take(ceil_div(r->n, d->cfg.fence_stride) * LSM_KEY_BYTES));
+                if (r->fences == nullptr) return LSM_ERR_HIP;
+                const lsm_run_t run{r->entries, r->n};
+                const int rc = lsm_build_fences(&run, d->cfg.fence_stride, r->fences, stream);
+                if (rc != LSM_OK) return rc;
+            }
+        }
+        int rc = ingest.empty() ? (int)LSM_OK : lsm::ingest_runs(ingest.data(), (uint32_t)ingest.size(), stride, stream);
+        for (uint32_t i = 0; i < count && rc == LSM_OK; i++) {
+            lsm_driver* d = drivers[i];
+            Run* r = d->resting;
+            d->resting = nullptr;
+            if (r == nullptr || r->n == 0) continue;
+            if (d->plain_filter(r->n)) {
+                const int zeroed = r->bloom != nullptr && r->bloom_clear ? 1 : 0;
+                r->n_blocks = lsm_bloom_blocks(r->n, d->cfg.bloom_bits);
+                if (r->bloom == nullptr) r->bloom = d->pool.take(r->n_blocks * 16);
+                if (r->bloom == nullptr) return LSM_ERR_HIP;
+                r->bloom_clear = false;
+                runs[zeroed].push_back(lsm_run_t{r->entries, r->n});
+                filters[zeroed].push_back(r->bloom);
+                blocks[zeroed].push_back(r->n_blocks);
+                continue;
+            }
+            if (r->bloom_clear) {  // sized before the run's length was known, and then it became a run of another kind
+                d->pool.give(r->bloom);
+                r->bloom = nullptr, r->bloom_clear = false;
+            }
+            if (d->cfg.bloom_bits != 0 || d->wants_index(r->n)) rc = d->build_hashed(*r);
+        }
+        for (int zeroed = 0; zeroed < 2 && rc == LSM_OK; zeroed++)
+            if (!runs[zeroed].empty())
+                rc = lsm::build_filters(runs[zeroed].data(), filters[zeroed].data(), blocks[zeroed].data(), (uint32_t)runs[zeroed].size(), zeroed == 1, stream);
+        return rc;
+    }
+    int settle() {
+        lsm_driver* self = this;
+        return settle_all(&self, 1);
+    }
+
+    // All runs of a level into one; the fence index of the output is written in the same pass.  Waits for the count (the
+    // kernels store it to pinned host memory); what else the merge does is ordered before whatever is enqueued next.
     int compact(const std::vector<Run>& in, uint32_t flags, uint32_t level, Run* merged) {
         if (in.size() > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
         lsm_run_t runs[LSM_MAX_RUNS];
@@ -277,31 +341,32 @@ struct lsm_driver {
         const uint64_t room = total > 0 ? total : 1;
         lsm_entry_t* entries = static_cast<lsm_entry_t*>(pool.take(room * sizeof(lsm_entry_t)));
         uint8_t* fences = static_cast<uint8_t*>(pool.take(ceil_div(room, cfg.fence_stride) * LSM_KEY_BYTES));
-        if (entries == nullptr || fences == nullptr) return LSM_ERR_HIP;
+        *merged = Run();
+        lsm::ClearSpan clear;
+        if (entries == nullptr || fences == nullptr || take_filter(*merged, total, &clear) != LSM_OK) return LSM_ERR_HIP;
         const lsm_out_t out{entries, room, n_host, fences, cfg.fence_stride, nullptr};
-        int rc = lsm_compact(runs, k, flags, &out, workspace, workspace_bytes, stream);
-        if (rc == LSM_OK) rc = wait();
+        *static_cast<volatile uint64_t*>(n_host) = kCountUnset;
+        int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, workspace_bytes, clear, &merged->bloom_clear, stream);
+        if (rc == LSM_OK) rc = watch(n_host, kCountUnset);
         if (rc == LSM_OK && *n_host > room) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
+        if (rc == LSM_OK && cfg.observer != nullptr) rc = wait();   // the observer sees a complete output
         if (rc != LSM_OK) {
             pool.give(entries);
             pool.give(fences);
+            pool.give(merged->bloom);
+            *merged = Run();
             return rc;
         }
-        *merged = Run();
         merged->n = *n_host;
         if (cfg.observer != nullptr) cfg.observer(cfg.observer_ctx, level + 1, entries, merged->n);
-        if (merged->n == 0) {
-            pool.give(entries);
-            pool.give(fences);
-        } else {
-            merged->entries = entries, merged->owned = true, merged->fences = fences;
-        }
+        merged->entries = entries, merged->owned = true, merged->fences = fences;
+        if (merged->n == 0) drop(*merged);
         return LSM_OK;
     }
 
     // A run arrives at a level (0-based).  The cascade this starts is cut into steps, so that a caller who drives several
     // trees can run the compactions of their current steps as one batch: arrive_begin places the run and either
-    // settles it or leaves a compaction to be done in `due`; arrive_merged takes that compaction's output and either
+    // leaves it in `resting` or a compaction to be done in `due`; arrive_merged takes that compaction's output and either
     // places it, or moves it down (arrive_begin at the next level, which may leave the next compaction in `due`).
     struct Due {
         bool active = false;
@@ -315,7 +380,10 @@ struct lsm_driver {
         if (lv.T != T || lv.K != K) record(LSM_EV_ADOPT, level + 1, T, K, 0, 0);
         lv.T = T, lv.K = K;  // lazy transition: the level takes the current parameters when data flows into it
         lv.runs.insert(lv.runs.begin(), moving);
-        if (lv.runs.size() <= lv.K) return settle(lv.runs[0]);
+        if (lv.runs.size() <= lv.K) {
+            resting = &lv.runs[0];
+            return LSM_OK;
+        }
         bool deeper_empty = true;
         for (size_t i = level + 1; i < levels.size(); i++) deeper_empty = deeper_empty && levels[i].runs.empty();
         due.active = true, due.level = level, due.flags = deeper_empty ? (uint32_t)LSM_BOTTOMMOST : 0u, due.n_in = 0;
@@ -328,8 +396,6 @@ struct lsm_driver {
         Level& lv = levels[level];
         due.active = false;
         record(LSM_EV_COMPACT, level + 1, (uint32_t)lv.runs.size(), due.flags, due.n_in, merged.n);
-        const int built = finish_builds();  // a run that is merged away may still be read by the build of its own filter
-        if (built != LSM_OK) return built;
         for (Run& r : lv.runs) drop(r);
         lv.runs.clear();
         if (merged.n > capacity(level)) {
@@ -338,7 +404,7 @@ struct lsm_driver {
         }
         if (merged.n > 0) {
             lv.runs.push_back(merged);
-            return settle(lv.runs[0]);
+            resting = &lv.runs[0];
         }
         return LSM_OK;
     }
@@ -354,7 +420,7 @@ struct lsm_driver {
     int arrive(uint32_t level, const Run& moving) {
         int rc = arrive_begin(level, moving);
         while (rc == LSM_OK && due.active) rc = compact_due();
-        return rc;
+        return rc == LSM_OK ? settle() : rc;
     }
 
     // One batch of operation counts enters the window; the (T, K) search is re-run when the mix has moved.
@@ -432,13 +498,10 @@ extern "C" int lsm_driver_create(const lsm_driver_config_t* config, void* stream
 
 extern "C" void lsm_driver_destroy(lsm_driver_t* d) {
     if (d == nullptr) return;
-    if (d->n_host != nullptr || d->side != nullptr) (void)hipStreamSynchronize(d->stream);  // else no GPU call was ever made
-    if (d->side != nullptr) (void)hipStreamSynchronize(d->side);
+    if (d->n_host != nullptr) (void)hipStreamSynchronize(d->stream);  // else no GPU call was ever made
     d->pool.free_all();
-    if (d->side != nullptr) (void)hipStreamDestroy(d->side);
-    if (d->ordered != nullptr) (void)hipEventDestroy(d->ordered);
     if (d->n_host != nullptr) (void)hipHostFree(d->n_host);
-    if (d->hit_host != nullptr) (void)hipHostFree(d->hit_host);
+    if (d->stats_host != nullptr) (void)hipHostFree(d->stats_host);
     if (d->counts_host != nullptr) (void)hipHostFree(d->counts_host);
     delete d;
 }
@@ -453,7 +516,8 @@ extern "C" int lsm_driver_load_run(lsm_driver_t* d, uint32_t level, const lsm_en
     r.entries = entries, r.n = n;
     std::vector<Run>& runs = d->levels[level - 1].runs;
     runs.push_back(r);
-    return d->settle(runs.back());
+    d->resting = &runs.back();
+    return d->settle();
 } catch (...) {  // host memory ran out: nothing may be thrown through the C ABI
     return LSM_ERR_INTERNAL;
 }
@@ -493,25 +557,27 @@ extern "C" int lsm_driver_flush_unsorted(lsm_driver_t* d, const lsm_entry_t* buf
     if (ready != LSM_OK) return ready;
     const uint64_t room = n > 0 ? n : 1;
     const size_t ws_bytes = lsm_flush_workspace_bytes(n);
+    Run r;
+    r.owned = true;
     lsm_entry_t* sorted = static_cast<lsm_entry_t*>(d->pool.take(room * sizeof(lsm_entry_t)));
+    r.entries = sorted;
+    r.fences = static_cast<uint8_t*>(d->pool.take(ceil_div(room, d->cfg.fence_stride) * LSM_KEY_BYTES));
     void* ws = d->pool.take(ws_bytes > 0 ? ws_bytes : 4);
-    uint64_t* n_dev = static_cast<uint64_t*>(d->pool.take(sizeof(uint64_t)));  // the kernels count with atomics: device memory
-    int rc = (sorted == nullptr || ws == nullptr || n_dev == nullptr) ? (int)LSM_ERR_HIP : (int)LSM_OK;
+    int rc = (sorted == nullptr || r.fences == nullptr || ws == nullptr) ? (int)LSM_ERR_HIP : (int)LSM_OK;
     if (rc == LSM_OK) {
-        const lsm_out_t out{sorted, room, n_dev, nullptr, 0, nullptr};
+        const lsm_out_t out{sorted, room, d->n_host, r.fences, d->cfg.fence_stride, nullptr};
+        *static_cast<volatile uint64_t*>(d->n_host) = kCountUnset;
         rc = lsm_flush_buffer(buffer, n, &out, ws, ws_bytes > 0 ? ws_bytes : 4, d->stream);
     }
-    if (rc == LSM_OK && hipMemcpyAsync(d->n_host, n_dev, sizeof(uint64_t), hipMemcpyDeviceToHost, d->stream) != hipSuccess) rc = LSM_ERR_HIP;
-    if (rc == LSM_OK) rc = d->wait();
+    if (rc == LSM_OK) rc = d->watch(d->n_host, kCountUnset);
     d->pool.give(ws);
-    d->pool.give(n_dev);
     if (rc == LSM_OK && *d->n_host > room) rc = LSM_ERR_INTERNAL;
     if (rc != LSM_OK) {
-        d->pool.give(sorted);
+        d->drop(r);
         return rc;
     }
-    Run r;
-    r.entries = sorted, r.n = *d->n_host, r.owned = true;
+    r.n = *d->n_host;
+    if (r.n == 0) d->drop(r);
     return d->arrive(0, r);
 } catch (...) {  // host memory ran out: nothing may be thrown through the C ABI
     return LSM_ERR_INTERNAL;
@@ -552,9 +618,7 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
     std::vector<std::vector<lsm_run_t>> inputs;
     std::vector<lsm_compact_job_t> jobs;
     std::vector<Run> merged;
-    std::vector<lsm_run_t> filtered;
-    std::vector<void*> filters;
-    std::vector<uint64_t> filter_blocks;
+    std::vector<lsm::ClearSpan> clear;
     for (;;) {
         // the compactions that are due now: the long ones on their own, the others as one batch
         active.clear();
@@ -566,11 +630,12 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             }
             if (d->due.active) active.push_back(d);
         }
-        if (active.empty()) return LSM_OK;
+        if (active.empty()) return lsm_driver::settle_all(drivers, count);
         const uint32_t n_jobs = (uint32_t)active.size();
         inputs.assign(n_jobs, {});
         jobs.assign(n_jobs, lsm_compact_job_t{});
         merged.assign(n_jobs, Run());
+        clear.assign(n_jobs, lsm::ClearSpan());
         int rc = LSM_OK;
         for (uint32_t j = 0; j < n_jobs && rc == LSM_OK; j++) {
             lsm_driver_t* d = active[j];
@@ -580,8 +645,10 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             const uint64_t room = d->due.n_in > 0 ? d->due.n_in : 1;
             lsm_entry_t* entries = static_cast<lsm_entry_t*>(d->pool.take(room * sizeof(lsm_entry_t)));
             uint8_t* fences = static_cast<uint8_t*>(d->pool.take(ceil_div(room, d->cfg.fence_stride) * LSM_KEY_BYTES));
-            if (entries == nullptr || fences == nullptr) rc = LSM_ERR_HIP;
+            if (entries == nullptr || fences == nullptr || d->take_filter(merged[j], d->due.n_in, &clear[j]) != LSM_OK) rc = LSM_ERR_HIP;
+            merged[j].bloom_clear = merged[j].bloom != nullptr;
             merged[j].entries = entries, merged[j].owned = true, merged[j].fences = fences;  // given back through drop() on failure
+            static_cast<volatile uint64_t*>(first->counts_host)[j] = kCountUnset;
             jobs[j].runs = inputs[j].data(), jobs[j].n_runs = (uint32_t)inputs[j].size(), jobs[j].flags = d->due.flags;
             jobs[j].out = lsm_out_t{entries, room, first->counts_host + j, fences, d->cfg.fence_stride, nullptr};
         }
@@ -593,41 +660,29 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             first->batch_workspace = first->pool.take(first->batch_workspace_bytes);
             if (first->batch_workspace == nullptr) first->batch_workspace_bytes = 0, rc = LSM_ERR_HIP;
         }
-        if (rc == LSM_OK) rc = lsm_compact_batch(jobs.data(), n_jobs, first->batch_workspace, first->batch_workspace_bytes, first->stream);
-        if (rc == LSM_OK) rc = first->wait();
-        for (uint32_t j = 0; j < n_jobs && rc == LSM_OK; j++)
-            if (first->counts_host[j] > jobs[j].out.capacity) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
+        if (rc == LSM_OK)
+            rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, first->batch_workspace, first->batch_workspace_bytes, clear.data(), first->stream);
+        bool observed = false;
+        for (uint32_t j = 0; j < n_jobs && rc == LSM_OK; j++) {
+            rc = first->watch(first->counts_host + j, kCountUnset);
+            if (rc == LSM_OK && first->counts_host[j] > jobs[j].out.capacity) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
+            observed = observed || active[j]->cfg.observer != nullptr;
+        }
+        if (rc == LSM_OK && observed) rc = first->wait();  // observers see complete outputs
         if (rc != LSM_OK) {
             for (uint32_t j = 0; j < n_jobs; j++) active[j]->drop(merged[j]);
             return rc;
         }
-        // the filters of all outputs in one call
-        filtered.clear(), filters.clear(), filter_blocks.clear();
         for (uint32_t j = 0; j < n_jobs; j++) {
             lsm_driver_t* d = active[j];
-            merged[j].n = first->counts_host[j];
-            if (d->cfg.observer != nullptr) d->cfg.observer(d->cfg.observer_ctx, d->due.level + 1, merged[j].entries, merged[j].n);
-            if (merged[j].n == 0) {
+            if (rc != LSM_OK) {
                 d->drop(merged[j]);
                 continue;
             }
-            const uint64_t n_blocks = d->cfg.bloom_bits != 0 ? lsm_bloom_blocks(merged[j].n, d->cfg.bloom_bits) : 0;
-            if (n_blocks == 0) continue;
-            merged[j].bloom = d->pool.take(n_blocks * 16);
-            merged[j].n_blocks = n_blocks;
-            if (merged[j].bloom == nullptr) rc = LSM_ERR_HIP;
-            filtered.push_back(lsm_run_t{merged[j].entries, merged[j].n});
-            filters.push_back(merged[j].bloom);
-            filter_blocks.push_back(n_blocks);
-        }
-        if (rc == LSM_OK && !filtered.empty())
-            rc = lsm_build_bloom_batch(filtered.data(), filters.data(), filter_blocks.data(), (uint32_t)filtered.size(), first->stream);
-        for (uint32_t j = 0; j < n_jobs; j++) {
-            if (rc != LSM_OK) {
-                active[j]->drop(merged[j]);
-                continue;
-            }
-            rc = active[j]->arrive_merged(merged[j]);
+            merged[j].n = first->counts_host[j];
+            if (d->cfg.observer != nullptr) d->cfg.observer(d->cfg.observer_ctx, d->due.level + 1, merged[j].entries, merged[j].n);
+            if (merged[j].n == 0) d->drop(merged[j]);
+            rc = d->arrive_merged(merged[j]);
         }
         if (rc != LSM_OK) return rc;
     }
@@ -643,24 +698,16 @@ extern "C" int lsm_driver_probe(lsm_driver_t* d, const lsm_queries_t* queries, c
     for (uint32_t i = 0; i < n_runs; i++) runs[i].level = i;
     const lsm_tree_t tree{runs, n_runs};
     int rc = d->gpu_ready();
-    if (rc == LSM_OK) rc = d->finish_builds();
     if (rc == LSM_OK) rc = lsm_probe(queries, &tree, out_hits, d->stream);
     if (rc != LSM_OK) return rc;
     const uint32_t n_req = queries->n_req;
-    if (n_req > d->hit_host_count) {
-        if (d->hit_host != nullptr) (void)hipHostFree(d->hit_host);
-        d->hit_host = nullptr, d->hit_host_count = 0;
-        if (hipHostMalloc(reinterpret_cast<void**>(&d->hit_host), (size_t)n_req * sizeof(uint32_t), hipHostMallocDefault) != hipSuccess) return LSM_ERR_HIP;
-        d->hit_host_count = n_req;
-    }
-    if (n_req > 0 && hipMemcpyAsync(d->hit_host, out_hits->hit_len, (size_t)n_req * sizeof(uint32_t), hipMemcpyDeviceToHost, d->stream) != hipSuccess)
-        return LSM_ERR_HIP;
-    rc = d->wait();
-    if (rc != LSM_OK) return rc;
     uint64_t hits = 0, blocks = 0;
-    for (uint32_t i = 0; i < n_req; i++) {
-        hits += d->hit_host[i] > 0;
-        blocks += d->hit_host[i];
+    if (n_req > 0) {
+        const uint64_t before = d->tickets++;
+        rc = lsm::probe_stats(out_hits->hit_len, n_req, d->stats_host, d->tickets, d->stream);
+        if (rc == LSM_OK) rc = d->watch(d->stats_host + 2, before);
+        if (rc != LSM_OK) return rc;
+        blocks = d->stats_host[0], hits = d->stats_host[1];
     }
     d->record(LSM_EV_PROBE, 0, n_req, (uint32_t)hits, 0, blocks);
     return d->count(0, hits, n_req - hits, (double)blocks);
@@ -683,7 +730,7 @@ extern "C" int lsm_driver_level(const lsm_driver_t* d, uint32_t level, uint32_t*
 extern "C" int lsm_driver_tree(lsm_driver_t* d, lsm_tree_run_t* runs_out, uint32_t capacity, uint32_t* n_runs) try {
     if (d == nullptr || n_runs == nullptr || (capacity > 0 && runs_out == nullptr)) return LSM_ERR_NULL;
     *n_runs = d->tree(runs_out, capacity);
-    return d->finish_builds();
+    return d->n_host != nullptr ? d->wait() : (int)LSM_OK;
 } catch (...) {  // host memory ran out: nothing may be thrown through the C ABI
     return LSM_ERR_INTERNAL;
 }
@@ -705,7 +752,6 @@ extern "C" uint64_t lsm_driver_log(const lsm_driver_t* d, uint64_t first, lsm_dr
 extern "C" int lsm_driver_read(lsm_driver_t* d, const void* device_src, void* dst, size_t bytes) try {
     if (d == nullptr || (bytes > 0 && (device_src == nullptr || dst == nullptr))) return LSM_ERR_NULL;
     int rc = d->gpu_ready();
-    if (rc == LSM_OK) rc = d->finish_builds();
     if (rc != LSM_OK) return rc;
     if (bytes > 0 && hipMemcpyAsync(dst, device_src, bytes, hipMemcpyDefault, d->stream) != hipSuccess) return LSM_ERR_HIP;
     return d->wait();

@@ -17,6 +17,44 @@ __global__ void __launch_bounds__(256) fence_kernel(const lsm_entry_t* run, uint
     }
 }
 
+// A caller's runs become runs of their own: entries copied, fence index written, filter zeroed, all in one launch.
+// blockIdx.y = run; four lanes per entry.
+constexpr uint32_t kIngestBatch = 32;
+struct IngestJobs {
+    IngestJob job[kIngestBatch];
+};
+__global__ void __launch_bounds__(256) ingest_kernel(IngestJobs jobs, uint32_t stride) {
+    const IngestJob& d = jobs.job[blockIdx.y];
+    const uint4* src = reinterpret_cast<const uint4*>(d.from);
+    uint4* dst = reinterpret_cast<uint4*>(d.to);
+    uint4* fences = reinterpret_cast<uint4*>(d.fences);
+    const uint64_t first = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, step = (uint64_t)gridDim.x * blockDim.x;
+    for (uint64_t u = first; u < d.n * 4; u += step) {
+        const uint4 v = src[u];
+        dst[u] = v;
+        const uint64_t e = u >> 2;
+        const uint32_t part = (uint32_t)u & 3;
+        if (part < 2 && e % stride == 0) fences[(e / stride) * 2 + part] = v;
+    }
+    for (uint64_t c = first; c < d.clear_n; c += step) d.clear[c] = make_uint4(0, 0, 0, 0);
+}
+
+int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t stride, hipStream_t stream) {
+    for (uint32_t first = 0; first < count; first += kIngestBatch) {
+        IngestJobs batch = {};
+        const uint32_t n = count - first < kIngestBatch ? count - first : kIngestBatch;
+        uint64_t most = 1;
+        for (uint32_t j = 0; j < n; j++) {
+            batch.job[j] = jobs[first + j];
+            most = jobs[first + j].n > most ? jobs[first + j].n : most;
+        }
+        uint64_t blocks = (most * 4 + 255) / 256;
+        if (blocks > 16384) blocks = 16384;
+        hipLaunchKernelGGL(ingest_kernel, dim3((uint32_t)blocks, n), dim3(256), 0, stream, batch, stride);
+    }
+    return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+}
+
 }  // namespace lsm
 
 extern "C" int lsm_build_fences(const lsm_run_t* run, uint32_t stride, uint8_t* fence_keys_out, void* stream) {

@@ -1,7 +1,7 @@
 // lsm_probe: batched longest-cached-prefix lookup (paper appendix B, "Probe"; section 2.2,
 // "Point Lookups": runs are checked newest to oldest and the first match is the result).
 //
-// One wave per request, requests taken round-robin by the waves of a fixed-size grid.  Every
+// One, two or four waves per request, requests taken round-robin by the workgroups of a fixed-size grid.  Every
 // workgroup first copies a top-level fence table into LDS: for each run of the tree, an evenly
 // spaced subset of its fence keys (all of them for small runs).  A request's block keys are
 // handled 64 at a time, one key per lane.  A lane first reads the Bloom filters of the runs that have one
@@ -32,13 +32,15 @@ struct TreeTable {
     uint32_t n_runs;
 };
 
-constexpr int kProbeThreads = 256;
+constexpr int kProbeThreads = 512;
 constexpr int kProbeWays = 3;     // fan-out of a search step in global memory (measured: 2: 0.072 ms per batch, 3: 0.067, 4: 0.069, 6: 0.074, 8: 0.080)
 constexpr int kTopSlots = 1024;  // top-level fence keys held in LDS per workgroup (32 KB)
 
+template <bool kTop>
 struct ProbeShared {
-    uint4 top_lo[kTopSlots];  // first 16 bytes of each top-level fence key
-    uint4 top_hi[kTopSlots];  // last 16 bytes
+    uint4 top_lo[kTop ? kTopSlots : 1];  // first 16 bytes of each top-level fence key
+    uint4 top_hi[kTop ? kTopSlots : 1];  // last 16 bytes
+    uint32_t first_dead[2][kProbeThreads / kWave];  // first block that is not live, by wave
     uint32_t first_slot[LSM_MAX_RUNS];  // slots of run r: [first_slot[r], first_slot[r] + n_top[r])
     uint32_t n_top[LSM_MAX_RUNS];
     uint32_t top_stride[LSM_MAX_RUNS];  // top key i of run r = fence i * top_stride[r]
@@ -70,7 +72,7 @@ __device__ __forceinline__ int compare_key(const Key& q, uint4 lo, LoadHi load_h
 // Without the table (every run has a hash index, so the fences are only searched for keys of crowded buckets) a fence
 // search starts from the whole fence array.
 template <bool kTop>
-__device__ __forceinline__ void probe_setup(ProbeShared& s, const TreeTable& tree, const int tid) {
+__device__ __forceinline__ void probe_setup(ProbeShared<kTop>& s, const TreeTable& tree, const int tid) {
     const uint32_t n_runs = tree.n_runs;
     // ---- top-level fence table: an equal share of the slots for every run
     const uint32_t share = (kTop && n_runs) ? kTopSlots / n_runs : 0;
@@ -114,7 +116,7 @@ __device__ __forceinline__ bool index_admits(const uint4 w, const uint32_t tag) 
 // Looks one block key per lane up in the tree (every lane of the wave calls this; lanes with mine == false idle).
 // Returns whether the key's newest version is a live PUT (true for idle lanes) and sets h to its hit record.
 template <bool kTop>
-__device__ __forceinline__ bool probe_lookup(const ProbeShared& s, const TreeTable& tree, const uint32_t n_runs,
+__device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const TreeTable& tree, const uint32_t n_runs,
                                              const uint64_t run_mask, const bool any_filter, const bool mine, const Key& q, uint4& h) {
     bool live = !mine, found = !mine;
     // (0) Bloom filters of the runs that have one: one 16-byte read per run, all runs of a group of
@@ -292,45 +294,58 @@ __device__ __forceinline__ bool probe_lookup(const ProbeShared& s, const TreeTab
     return live;
 }
 
-template <bool kTop>
+// kSpread waves share a request, 64 consecutive keys each.  What bounds a batch is the chain of dependent reads of its
+// longest request: some 16 us per 64 keys looked up one after the other.  With more waves per request the chain is shorter,
+// and the keys behind the first miss that are then looked up for nothing cost reads, but no time as long as there is room
+// for the waves (spread_for).
+template <bool kTop, int kSpread>
 __global__ void __launch_bounds__(kProbeThreads) probe_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks,
                                                                uint32_t n_req, uint32_t max_blocks, uint32_t* hit_len,
                                                                lsm_hit_t* hits) {
-    __shared__ ProbeShared s;
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1);
+    __shared__ ProbeShared<kTop> s;
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
+    constexpr uint32_t kRequests = kProbeThreads / kWave / kSpread;  // requests a workgroup handles at a time
     const uint32_t n_runs = tree.n_runs;
-    probe_setup<kTop>(s, tree, tid);
+    probe_setup<kTop>(s, tree, (int)tid);
     const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
     bool any_filter = false;  // a Bloom filter or a hash index
     for (uint32_t r = 0; r < n_runs; r++) any_filter = any_filter || tree.run[r].bloom_blocks != 0 || tree.run[r].index != nullptr;
-    const uint32_t waves = gridDim.x * (kProbeThreads / kWave);
-    for (uint32_t req = blockIdx.x * (kProbeThreads / kWave) + tid / kWave; req < n_req; req += waves) {
-        uint32_t nb = n_blocks[req];
-        if (nb > max_blocks) nb = max_blocks;
+    uint32_t turn = 0;
+    for (uint32_t first_req = blockIdx.x * kRequests; first_req < n_req; first_req += gridDim.x * kRequests) {
+        const uint32_t req = first_req + wave / kSpread;
+        uint32_t nb = 0;
+        if (req < n_req) nb = min(n_blocks[req], max_blocks);
         const uint8_t* qrow = qkeys + (uint64_t)req * max_blocks * LSM_KEY_BYTES;
         uint4* hrow = reinterpret_cast<uint4*>(hits + (uint64_t)req * max_blocks);
         uint32_t result = nb;
         bool done = false;
-        for (uint32_t c0 = 0; c0 < max_blocks; c0 += kWave) {
-            const uint32_t j = c0 + lane;
+        for (uint32_t c0 = 0; c0 < max_blocks; c0 += kWave * kSpread) {
+            const uint32_t start = c0 + (wave % kSpread) * kWave, j = start + lane;
             uint4 h = make_uint4(0, 0, 0, 0);
-            if (!done && c0 < nb) {
+            uint32_t first = ~0u;
+            if (!done && start < nb) {
                 const bool mine = j < nb;  // lanes past the request's length do not end the prefix
                 Key q = {{0, 0, 0, 0}};
                 if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
                 const bool live = probe_lookup<kTop>(s, tree, n_runs, run_mask, any_filter, mine, q, h);
                 const uint64_t dead = __ballot(!live);
-                if (dead) {
-                    const uint32_t first = (uint32_t)__ffsll((unsigned long long)dead) - 1;
-                    result = c0 + first;
-                    done = true;
-                    if ((uint32_t)lane >= first) h = make_uint4(0, 0, 0, 0);
-                }
+                if (dead) first = start + (uint32_t)__ffsll((unsigned long long)dead) - 1;
             }
-            if (j < max_blocks) hrow[j] = h;
+            if (kSpread > 1) {  // the same trips for all waves of the workgroup
+                if (lane == 0) s.first_dead[turn & 1][wave] = first;
+                __syncthreads();
+#pragma unroll
+                for (int w = 0; w < kSpread; w++) first = min(first, s.first_dead[turn & 1][wave / kSpread * kSpread + w]);
+                turn++;
+            }
+            if (!done && first != ~0u) {
+                result = first;
+                done = true;
+            }
+            if (j >= result) h = make_uint4(0, 0, 0, 0);
+            if (req < n_req && j < max_blocks) hrow[j] = h;
         }
-        if (lane == 0) hit_len[req] = result;
+        if (lane == 0 && wave % kSpread == 0 && req < n_req) hit_len[req] = result;
     }
 }
 
@@ -341,7 +356,7 @@ __global__ void __launch_bounds__(kProbeThreads) probe_kernel(TreeTable tree, co
 template <bool kTop>
 __global__ void __launch_bounds__(kProbeThreads) probe_length_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks,
                                                                       uint32_t n_req, uint32_t max_blocks, uint32_t* hit_len) {
-    __shared__ ProbeShared s;
+    __shared__ ProbeShared<kTop> s;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const uint32_t n_runs = tree.n_runs;
@@ -387,6 +402,35 @@ __global__ void range_bounds_kernel(TreeTable tree, Key lo_key, Key hi_key, uint
     const TreeRun& run = tree.run[t >> 1];
     bool eq;
     bounds[t] = run.n ? lower_bound_eq(run.entries, 0, run.n, (t & 1) ? hi_key : lo_key, eq) : 0;
+}
+
+// What the driver's controller needs to know of a batch, without a copy of the lengths to the host.
+constexpr int kStatsThreads = 1024;
+__global__ void __launch_bounds__(kStatsThreads) probe_stats_kernel(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket) {
+    __shared__ uint64_t wave_blocks[kStatsThreads / kWave], wave_hits[kStatsThreads / kWave];
+    uint64_t blocks = 0, hits = 0;
+    for (uint32_t i = threadIdx.x; i < n_req; i += kStatsThreads) {
+        const uint32_t h = hit_len[i];
+        blocks += h;
+        hits += h > 0 ? 1 : 0;
+    }
+    blocks = wave_sum_u64(blocks);
+    hits = wave_sum_u64(hits);
+    if ((threadIdx.x & (kWave - 1)) == 0) wave_blocks[threadIdx.x / kWave] = blocks, wave_hits[threadIdx.x / kWave] = hits;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    blocks = hits = 0;
+    for (int w = 0; w < kStatsThreads / kWave; w++) blocks += wave_blocks[w], hits += wave_hits[w];
+    volatile uint64_t* out = stats;
+    out[0] = blocks;
+    out[1] = hits;
+    __threadfence_system();  // the host takes the other two when it sees the ticket
+    out[2] = ticket;
+}
+
+int probe_stats(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket, hipStream_t stream) {
+    hipLaunchKernelGGL(probe_stats_kernel, dim3(1), dim3(kStatsThreads), 0, stream, hit_len, n_req, stats, ticket);
+    return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 
 }  // namespace lsm
@@ -441,16 +485,38 @@ static int make_tree_table(const lsm_tree_t* tree, lsm::TreeTable& tt) {
     return LSM_OK;
 }
 
-// Workgroups for n_req requests (one wave each): at most four per compute unit, each striding over the requests.
-static int probe_grid(uint32_t n_req, uint32_t& blocks) {
+// Workgroups for n_req requests of `spread` waves each: at most four per compute unit (32 waves), each striding over the
+// requests.
+static int probe_grid(uint32_t n_req, uint32_t spread, uint32_t& blocks) {
     int device = 0, cus = 0;
     if (hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
         return LSM_ERR_HIP;
-    const uint32_t per_block = lsm::kProbeThreads / lsm::kWave;
+    const uint32_t per_block = lsm::kProbeThreads / lsm::kWave / spread;
     blocks = (n_req + per_block - 1) / per_block;
     if (blocks > (uint32_t)cus * 4) blocks = (uint32_t)cus * 4;
     return LSM_OK;
+}
+
+// Waves per request: four up to 512 requests, two up to 2,048 (about 4,096 waves, half of what the chip holds; beyond, the
+// lookups behind the first miss cost more than the shorter chains save).  100M-entry tree with filters, one / two / four
+// waves: 64 requests 29 / 21 / 20 us, 512: 38 / 26 / 26, 1,024: 44 / 29 / 30, 2,048: 48 / 35 / 51, 4,096: 55 / 64 / 92.
+static uint32_t spread_for(uint32_t n_req, uint32_t max_blocks) {
+    uint32_t most = 1;
+    while (most < 4 && most * lsm::kWave < max_blocks) most *= 2;  // no more than the longest request has use for
+    const uint32_t spread = n_req <= 512 ? 4 : (n_req <= 2048 ? 2 : 1);
+    return spread < most ? spread : most;
+}
+
+template <bool kTop>
+static void launch_probe(uint32_t spread, uint32_t blocks, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits, hipStream_t stream) {
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(lsm::kProbeThreads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req, queries->max_blocks,
+                           out_hits->hit_len, out_hits->hits);
+    };
+    if (spread == 4) launch(lsm::probe_kernel<kTop, 4>);
+    else if (spread == 2) launch(lsm::probe_kernel<kTop, 2>);
+    else launch(lsm::probe_kernel<kTop, 1>);
 }
 
 extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, const lsm_hits_t* out_hits, void* stream) {
@@ -465,14 +531,11 @@ extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, c
     TreeTable tt;
     uint32_t blocks = 0;
     int rc = make_tree_table(tree, tt);
-    if (rc == LSM_OK) rc = probe_grid(queries->n_req, blocks);
+    const uint32_t spread = spread_for(queries->n_req, queries->max_blocks);
+    if (rc == LSM_OK) rc = probe_grid(queries->n_req, spread, blocks);
     if (rc != LSM_OK) return rc;
-    if (all_indexed(tt))
-        hipLaunchKernelGGL(probe_kernel<false>, dim3(blocks), dim3(kProbeThreads), 0, static_cast<hipStream_t>(stream), tt, queries->keys,
-                           queries->n_blocks, queries->n_req, queries->max_blocks, out_hits->hit_len, out_hits->hits);
-    else
-        hipLaunchKernelGGL(probe_kernel<true>, dim3(blocks), dim3(kProbeThreads), 0, static_cast<hipStream_t>(stream), tt, queries->keys,
-                           queries->n_blocks, queries->n_req, queries->max_blocks, out_hits->hit_len, out_hits->hits);
+    if (all_indexed(tt)) launch_probe<false>(spread, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    else launch_probe<true>(spread, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 
@@ -486,7 +549,7 @@ extern "C" int lsm_probe_length(const lsm_queries_t* queries, const lsm_tree_t* 
     TreeTable tt;
     uint32_t blocks = 0;
     int rc = make_tree_table(tree, tt);
-    if (rc == LSM_OK) rc = probe_grid(queries->n_req, blocks);
+    if (rc == LSM_OK) rc = probe_grid(queries->n_req, 1, blocks);
     if (rc != LSM_OK) return rc;
     if (all_indexed(tt))
         hipLaunchKernelGGL(probe_length_kernel<false>, dim3(blocks), dim3(kProbeThreads), 0, static_cast<hipStream_t>(stream), tt, queries->keys,

@@ -348,6 +348,17 @@ def test_probe_empty_tree_and_empty_runs(g, oracle, cfg1):
     assert_probe_equal(oracle, probe_gpu(g, q, nb, tree), want)
 
 
+@pytest.mark.parametrize("n_req", [1, 2, 3, 511, 512, 513, 2047, 2048, 2049])  # four, two and one wave per request
+@pytest.mark.parametrize("row", [256, 192, 64, 17])                            # key rows that need four, three or one of them
+def test_probe_batches_of_all_sizes(g, oracle, cfg1, n_req, row):
+    from workloads import lsm
+    print("probe batch", n_req, row, flush=True)
+    q, nb = lsm.queries_config1(cfg1, n_req, stream=n_req)
+    q, nb = q[:, :row].contiguous(), nb.clamp(max=row)
+    want = oracle.probe(q, nb, [r.cpu() for r in cfg1.runs])
+    assert_probe_equal(oracle, probe_gpu(g, q, nb, build_tree(g, cfg1.runs)), want)
+
+
 # ------------------------------------------------------------------ Bloom filters
 @pytest.mark.parametrize("bits_per_key", [8, 16])
 def test_bloom_filter_bytes_equal_the_checker(g, oracle, cfg1, bits_per_key):
