@@ -232,14 +232,37 @@ def _count(t: torch.Tensor, what: str) -> torch.Tensor:
 
 
 _raw_current_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream_ptr(stream) -> int:
     if stream is None:
         if _raw_current_stream is not None:   # the handle alone: building a Stream object costs more than a small launch
+            if _raw_device is not None and torch.cuda.is_initialized():
+                return _raw_current_stream(_raw_device())
             return int(_raw_current_stream(torch.cuda.current_device()))
         stream = torch.cuda.current_stream()
     return int(stream.cuda_stream) if hasattr(stream, "cuda_stream") else int(stream)
+
+
+# Descriptor arrays are filled as flat arrays of 64-bit words (every field of these structs is one, or two 32-bit halves of
+# one): building a ctypes structure per run costs several times as much as reading its tensor's address and length.
+assert C.sizeof(_Run) == 16 and C.sizeof(_TreeRun) == 80 and C.sizeof(_CompactJob) == 64
+
+
+def _run_words(runs: Sequence[torch.Tensor], what: str = "run") -> List[int]:
+    """[address, length] of every run, one after the other."""
+    words: List[int] = []
+    for r in runs:
+        if not (r.is_cuda and r.is_contiguous()):
+            _dev(r, what)  # says which
+        words.append(r.data_ptr())
+        words.append(r.size(0))
+    return words
+
+
+def _words(words: List[int]):
+    return (C.c_uint64 * max(1, len(words)))(*words)
 
 
 def lsm_strerror(code: int) -> str:
@@ -264,17 +287,17 @@ def lsm_compact(runs: Sequence[torch.Tensor], flags: int = 0, out: Optional[torc
     that receives the fence index of the result (its first ceil(n_out / fence_stride) rows); `key_hashes` = int64
     [>= capacity] that receives the filter hash of every output key (for lsm_build_bloom_hashed)."""
     L = _load()
-    runs = [_dev(r, "run") for r in runs]
-    total = sum(int(r.shape[0]) for r in runs)
+    words = _run_words(runs)
+    total = sum(words[1::2])
     dev = runs[0].device if runs else torch.device("cuda")
     if out is None:
         out = torch.empty((max(total, 1), 8), dtype=torch.int64, device=dev)
     if n_out is None:
         n_out = torch.empty(1, dtype=torch.int64, device=dev)
     if workspace is None:
-        need = lsm_compact_workspace_bytes([int(r.shape[0]) for r in runs]) if runs else 0
+        need = lsm_compact_workspace_bytes(words[1::2]) if runs else 0
         workspace = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
-    rd = (_Run * max(1, len(runs)))(*[_Run(r.data_ptr(), int(r.shape[0])) for r in runs])
+    rd = C.cast(_words(words), C.POINTER(_Run))
     od = _Out(_dev(out, "out").data_ptr(), int(out.shape[0]), _count(n_out, "n_out").data_ptr(),
               _dev(fences, "fences").data_ptr() if fences is not None else None, fence_stride if fences is not None else 0,
               _dev(key_hashes, "key hashes").data_ptr() if key_hashes is not None else None)
@@ -452,16 +475,18 @@ def lsm_build_bloom_batch(runs: Sequence[torch.Tensor], bits_per_key: int = 16, 
     L = _load()
     if not runs:
         return []
-    blocks = [lsm_bloom_blocks(int(_dev(r, "run").shape[0]), bits_per_key) for r in runs]
+    words = _run_words(runs)
+    blocks = [-(-n * bits_per_key // 128) or 1 for n in words[1::2]]  # as lsm_bloom_blocks
+    if bits_per_key <= 0 or max(blocks) >= 1 << 32:
+        raise LsmError(-2, "lsm_build_bloom_batch")
     all_f = torch.empty((sum(blocks), 4), dtype=torch.int32, device=runs[0].device)
-    outs, at = [], 0
+    outs = list(all_f.split(blocks))
+    at, ptrs = all_f.data_ptr(), []
     for b in blocks:
-        outs.append(all_f[at:at + b])
-        at += b
-    rd = (_Run * len(runs))(*[_Run(r.data_ptr(), int(r.shape[0])) for r in runs])
-    fp = (C.c_void_p * len(runs))(*[o.data_ptr() for o in outs])
-    nb = (C.c_uint64 * len(runs))(*blocks)
-    rc = L.lsm_build_bloom_batch(rd, fp, nb, len(runs), _stream_ptr(stream))
+        ptrs.append(at)
+        at += 16 * b
+    rc = L.lsm_build_bloom_batch(C.cast(_words(words), C.POINTER(_Run)), C.cast(_words(ptrs), C.POINTER(C.c_void_p)), _words(blocks), len(runs),
+                                 _stream_ptr(stream))
     if rc != 0:
         raise LsmError(rc, "lsm_build_bloom_batch")
     return outs
@@ -478,16 +503,28 @@ class TreeRun:
 
 
 def _tree_descriptor(tree: Sequence[TreeRun]):
-    tr = (_TreeRun * max(1, len(tree)))()
-    for i, t in enumerate(tree):
-        tr[i].run = _Run(_dev(t.run, "tree run").data_ptr(), int(t.run.shape[0]))
-        tr[i].fence = _Fence(_dev(t.fences, "fences").data_ptr(), int(t.fences.shape[0]), t.stride)
-        if t.bloom is not None:
-            tr[i].bloom = _Bloom(_dev(t.bloom, "bloom filter").data_ptr(), int(t.bloom.shape[0]))
-        tr[i].level = t.level
-        if t.index is not None:
-            tr[i].index = _HashIndex(_dev(t.index, "hash index").data_ptr(), int(t.index.shape[0]))
-    return _Tree(tr, len(tree)), tr  # tr must outlive the call
+    words: List[int] = []
+    for t in tree:
+        run, fences, bloom, index = t.run, t.fences, t.bloom, t.index
+        if not (run.is_cuda and run.is_contiguous()):
+            _dev(run, "tree run")
+        if not (fences.is_cuda and fences.is_contiguous()):
+            _dev(fences, "fences")
+        words += (run.data_ptr(), run.size(0), fences.data_ptr(), fences.size(0), t.stride)
+        if bloom is not None:
+            if not (bloom.is_cuda and bloom.is_contiguous()):
+                _dev(bloom, "bloom filter")
+            words += (bloom.data_ptr(), bloom.size(0), t.level)
+        else:
+            words += (0, 0, t.level)
+        if index is not None:
+            if not (index.is_cuda and index.is_contiguous()):
+                _dev(index, "hash index")
+            words += (index.data_ptr(), index.size(0))
+        else:
+            words += (0, 0)
+    tr = _words(words)
+    return _Tree(C.cast(tr, C.POINTER(_TreeRun)), len(tree)), tr  # tr must outlive the call
 
 
 def lsm_probe_length(qkeys: torch.Tensor, n_blocks: torch.Tensor, tree: Sequence[TreeRun],
@@ -553,33 +590,37 @@ def lsm_compact_batch(jobs: Sequence[Tuple[Sequence[torch.Tensor], int]], stream
     L = _load()
     n_jobs = len(jobs)
     dev = next((r.device for runs, _ in jobs for r in runs), torch.device("cuda"))
-    totals = [sum(int(r.shape[0]) for r in runs) for runs, _ in jobs]
+    run_words, totals, first = [], [], []
+    for runs, _ in jobs:
+        w = _run_words(runs)
+        first.append(len(run_words))
+        run_words += w
+        totals.append(sum(w[1::2]))
+    rd = _words(run_words)
     out_all = torch.empty((max(sum(totals), 1), 8), dtype=torch.int64, device=dev)
     n_out = torch.empty(max(n_jobs, 1), dtype=torch.int64, device=dev)
-    outs, keep, jd, at = [], [], (_CompactJob * max(1, n_jobs))(), 0
-    fences, f_at = [], 0
-    if fence_stride > 0:
-        f_rows = [(t + fence_stride - 1) // fence_stride for t in totals]
-        fence_all = torch.empty((max(sum(f_rows), 1), 4), dtype=torch.int64, device=dev)
-    for j, ((runs, flags), total) in enumerate(zip(jobs, totals)):
-        rd = (_Run * max(1, len(runs)))(*[_Run(_dev(r, "run").data_ptr(), int(r.shape[0])) for r in runs])
-        keep.append(rd)
-        outs.append(out_all[at:at + total])
-        jd[j].runs, jd[j].n_runs, jd[j].flags = rd, len(runs), flags
-        jd[j].out = _Out(out_all.data_ptr() + at * 64, total, n_out.data_ptr() + 8 * j, None, 0)
-        if fence_stride > 0:
-            fences.append(fence_all[f_at:f_at + f_rows[j]])
-            jd[j].out.fence_keys, jd[j].out.fence_stride = fence_all.data_ptr() + f_at * 32, fence_stride
-            f_at += f_rows[j]
-        at += total
-    need = int(L.lsm_compact_batch_workspace_bytes(jd, n_jobs)) if n_jobs else 0
+    rows = [-(-t // fence_stride) for t in totals] if fence_stride > 0 else []
+    fence_all = torch.empty((max(sum(rows), 1), 4), dtype=torch.int64, device=dev) if fence_stride > 0 else None
+    at, n_at, f_at, r_at = out_all.data_ptr(), n_out.data_ptr(), fence_all.data_ptr() if fence_all is not None else 0, C.addressof(rd)
+    words: List[int] = []
+    for j, (runs, flags) in enumerate(jobs):
+        words += (r_at + 8 * first[j], len(runs) | flags << 32, at, totals[j], n_at + 8 * j, f_at, fence_stride if f_at else 0, 0)
+        at += 64 * totals[j]
+        if f_at:
+            f_at += 32 * rows[j]
+    jw = _words(words)
+    jd = C.cast(jw, C.POINTER(_CompactJob))
+    need = L.lsm_compact_batch_workspace_bytes(jd, n_jobs) if n_jobs else 0
     if n_jobs and need == 0:
         raise LsmError(-2, "lsm_compact_batch_workspace_bytes")
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=dev)
     rc = L.lsm_compact_batch(jd, n_jobs, ws.data_ptr(), ws.numel(), _stream_ptr(stream))
     if rc != 0:
         raise LsmError(rc, "lsm_compact_batch")
-    return (outs, n_out[:n_jobs], fences) if fence_stride > 0 else (outs, n_out[:n_jobs])
+    outs = list(out_all[: sum(totals)].split(totals)) if n_jobs else []
+    if fence_stride > 0:
+        return outs, n_out[:n_jobs], list(fence_all[: sum(rows)].split(rows)) if n_jobs else []
+    return outs, n_out[:n_jobs]
 
 
 def lsm_probe(qkeys: torch.Tensor, n_blocks: torch.Tensor, tree: Sequence[TreeRun],
