@@ -792,6 +792,51 @@ def test_batched_range_scans(g, oracle, cfg1, which):
     assert c1.numel() == 0
 
 
+def _numbered_runs(oracle, rs, lengths, spread):
+    """Runs of the given lengths as [n, 64] uint8 arrays, sorted.  Keys carry a random number below 2^spread behind a common
+    prefix: in the last eight bytes (dense, many keys in several runs, all first halves equal) for spreads up to 18, else
+    in bytes 8..15."""
+    runs = []
+    for n in lengths:
+        some = np.arange(1 << spread) if spread <= 18 else np.unique(rs.randint(0, 1 << spread, size=2 * n + 8))
+        lead = np.sort(rs.permutation(some)[:n]).astype(np.int64)
+        a = np.zeros((n, 64), dtype=np.uint8)
+        a[:, :32] = 0x33
+        at = 24 if spread <= 18 else 8
+        a[:, at:at + 8] = lead.astype(">u8").view(np.uint8).reshape(n, 8)
+        rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+        rec["seqno"] = ((len(lengths) - len(runs)) << 32) + rs.permutation(n)  # newest run first
+        rec["type"] = (rs.rand(n) < 0.1).astype(np.uint8)
+        rec["vptr"] = np.arange(n)
+        runs.append(a)
+    return runs
+
+
+@pytest.mark.parametrize("k", [1, 2, 8, 9, 16, 17, 32, 33, 64])   # 32, 16, 8 or 4 lanes per search
+@pytest.mark.parametrize("spread", [13, 40])                      # keys that differ behind byte 24, or in the first 16
+def test_range_scan_by_runs(g, oracle, k, spread):
+    """Range ends found by shared searches: runs from empty to a few thousand entries, bounds below, between, at and
+    above the stored keys."""
+    print("range scan by runs", k, spread, flush=True)
+    rs = np.random.RandomState(100 * k + spread)
+    runs = _numbered_runs(oracle, rs, [(0, 1, 31, 33, 700, 4099)[(j + 5) % 6] if j else 4099 for j in range(k)], spread)
+    tree = build_tree(g, [to_dev(a) for a in runs])
+    full = oracle.compact(runs, 1)
+    every = np.unique(np.concatenate([a[:, :32] for a in runs]), axis=0)
+    cut = np.sort(rs.randint(0, len(every), size=(200, 2)), axis=1)
+    cut[:, 1] = np.minimum(cut[:, 1], cut[:, 0] + rs.randint(0, 40, size=200))
+    ranges = [(bytes(every[i]), bytes(every[j])) for i, j in cut]
+    ranges += [(bytes(32), bytes(every[3])), (bytes(every[-5]), b"\xff" * 32), (bytes(every[5]), bytes(every[2])), (b"\xff" * 32, b"\xff" * 32)]
+    ranges += [(lo[:31] + b"\x01", hi[:31] + b"\x02") for lo, hi in ranges[:40]]
+    ent, cnt = g.lsm_range_scan(tree, _keys_tensor([lo for lo, _ in ranges]), _keys_tensor([hi for _, hi in ranges]), 2048)
+    cnt, got = cnt.cpu().numpy(), as_bytes(ent).reshape(len(ranges), 2048, 64)
+    keys = [bytes(x) for x in full[:, :32]]
+    for i, (lo, hi) in enumerate(ranges):
+        want = full[[j for j, x in enumerate(keys) if lo <= x < hi]]
+        assert cnt[i] == want.shape[0], (i, cnt[i], want.shape[0])
+        assert np.array_equal(got[i, : want.shape[0]], want), i
+
+
 def test_batch_of_small_compactions(g, oracle, cfg1):
     """Many independent compactions in one call: every job's output and count equal the checker's for that job -
     1 to 9 runs per job, empty runs and empty jobs, both flag values, jobs of one tile and of dozens of tiles."""
