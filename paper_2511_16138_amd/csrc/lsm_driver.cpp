@@ -27,6 +27,7 @@
 #include <map>
 #include <new>
 #include <unordered_map>
+#include <utility>
 #include <vector>
 
 #include "lsm_common.h"
@@ -83,6 +84,7 @@ struct Run {
     bool bloom_clear = false;  // bloom is memory that has been zeroed, not a filter yet
     void* index = nullptr;
     uint64_t n_buckets = 0;
+    bool settled = false;  // has every lookup structure it is to get (see settle_all)
 };
 
 struct Level {
@@ -126,7 +128,6 @@ struct lsm_driver {
     uint64_t* n_host = nullptr;  // pinned: the kernels write a compaction's count here
     uint64_t* stats_host = nullptr;  // pinned: what a probe batch found, and a ticket that says which batch
     uint64_t tickets = 0;
-    Run* resting = nullptr;  // a run that has come to rest and still lacks lookup structures (see settle_all)
     uint64_t* counts_host = nullptr;  // pinned: the counts of a batch of compactions (lsm_driver_flush_many)
     size_t counts_host_count = 0;
     void* batch_workspace = nullptr;
@@ -178,7 +179,10 @@ struct lsm_driver {
             cpu_pause();
             if (spins % 16384 != 0) continue;
             const hipError_t e = hipStreamQuery(stream);
-            if (e == hipErrorNotReady) continue;
+            if (e == hipErrorNotReady) {
+                (void)hipGetLastError();  // not an error of the next launch
+                continue;
+            }
             if (e != hipSuccess || *w == unset) return LSM_ERR_HIP;
         }
         std::atomic_thread_fence(std::memory_order_acquire);
@@ -254,13 +258,14 @@ struct lsm_driver {
         std::vector<lsm_run_t> runs[2];  // [1]: with a filter memory that is zeroed by then
         std::vector<void*> filters[2];
         std::vector<uint64_t> blocks[2];
-        hipStream_t stream = nullptr;
+        std::vector<std::pair<lsm_driver*, Run*>> resting;
+        for (uint32_t i = 0; i < count; i++)
+            for (Level& lv : drivers[i]->levels)
+                for (Run& r : lv.runs)
+                    if (!r.settled && r.n != 0) resting.emplace_back(drivers[i], &r);
+        const hipStream_t stream = count != 0 ? drivers[0]->stream : nullptr;
         uint32_t stride = 1;
-        for (uint32_t i = 0; i < count; i++) {
-            lsm_driver* d = drivers[i];
-            Run* r = d->resting;
-            if (r == nullptr || r->n == 0) continue;
-            stream = d->stream;
+        for (const auto& [d, r] : resting) {
             if (r->transient) {
                 lsm_entry_t* copy = static_cast<lsm_entry_t*>(d->pool.take(r->n * sizeof(lsm_entry_t)));
                 r->fences = static_cast<uint8_t*>(d->pool.take(ceil_div(r->n, d->cfg.fence_stride) * LSM_KEY_BYTES));
@@ -283,11 +288,9 @@ struct lsm_driver {
             }
         }
         int rc = ingest.empty() ? (int)LSM_OK : lsm::ingest_runs(ingest.data(), (uint32_t)ingest.size(), stride, stream);
-        for (uint32_t i = 0; i < count && rc == LSM_OK; i++) {
-            lsm_driver* d = drivers[i];
-            Run* r = d->resting;
-            d->resting = nullptr;
-            if (r == nullptr || r->n == 0) continue;
+        for (const auto& [d, r] : resting) {
+            if (rc != LSM_OK) break;
+            r->settled = true;
             if (d->plain_filter(r->n)) {
                 const int zeroed = r->bloom != nullptr && r->bloom_clear ? 1 : 0;
                 r->n_blocks = lsm_bloom_blocks(r->n, d->cfg.bloom_bits);
@@ -365,9 +368,10 @@ struct lsm_driver {
     }
 
     // A run arrives at a level (0-based).  The cascade this starts is cut into steps, so that a caller who drives several
-    // trees can run the compactions of their current steps as one batch: arrive_begin places the run and either
-    // leaves it in `resting` or a compaction to be done in `due`; arrive_merged takes that compaction's output and either
+    // trees can run the compactions of their current steps as one batch: arrive_begin places the run and leaves a
+    // compaction to be done in `due` if the level is too full; arrive_merged takes that compaction's output and either
     // places it, or moves it down (arrive_begin at the next level, which may leave the next compaction in `due`).
+    // settle_all completes the runs that stay where they were placed.
     struct Due {
         bool active = false;
         uint32_t level = 0, flags = 0;
@@ -380,10 +384,7 @@ struct lsm_driver {
         if (lv.T != T || lv.K != K) record(LSM_EV_ADOPT, level + 1, T, K, 0, 0);
         lv.T = T, lv.K = K;  // lazy transition: the level takes the current parameters when data flows into it
         lv.runs.insert(lv.runs.begin(), moving);
-        if (lv.runs.size() <= lv.K) {
-            resting = &lv.runs[0];
-            return LSM_OK;
-        }
+        if (lv.runs.size() <= lv.K) return LSM_OK;
         bool deeper_empty = true;
         for (size_t i = level + 1; i < levels.size(); i++) deeper_empty = deeper_empty && levels[i].runs.empty();
         due.active = true, due.level = level, due.flags = deeper_empty ? (uint32_t)LSM_BOTTOMMOST : 0u, due.n_in = 0;
@@ -402,10 +403,7 @@ struct lsm_driver {
             record(LSM_EV_MOVE, level + 1, level + 2, 0, 0, merged.n);
             return arrive_begin(level + 1, merged);
         }
-        if (merged.n > 0) {
-            lv.runs.push_back(merged);
-            resting = &lv.runs[0];
-        }
+        if (merged.n > 0) lv.runs.push_back(merged);
         return LSM_OK;
     }
 
@@ -516,7 +514,6 @@ extern "C" int lsm_driver_load_run(lsm_driver_t* d, uint32_t level, const lsm_en
     r.entries = entries, r.n = n;
     std::vector<Run>& runs = d->levels[level - 1].runs;
     runs.push_back(r);
-    d->resting = &runs.back();
     return d->settle();
 } catch (...) {  // host memory ran out: nothing may be thrown through the C ABI
     return LSM_ERR_INTERNAL;
@@ -614,6 +611,11 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
         const int rc = drivers[i]->arrive_begin(0, r);
         if (rc != LSM_OK) return rc;
     }
+    // a compaction of one tree failed: the runs that have come to rest in the others still get their copies and structures
+    auto failed = [&](int rc) {
+        (void)lsm_driver::settle_all(drivers, count);
+        return rc;
+    };
     std::vector<lsm_driver_t*> active;
     std::vector<std::vector<lsm_run_t>> inputs;
     std::vector<lsm_compact_job_t> jobs;
@@ -626,7 +628,7 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             lsm_driver_t* d = drivers[i];
             while (d->due.active && d->due.n_in >= kBatchJobEntries) {
                 const int rc = d->compact_due();
-                if (rc != LSM_OK) return rc;
+                if (rc != LSM_OK) return failed(rc);
             }
             if (d->due.active) active.push_back(d);
         }
@@ -671,7 +673,7 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
         if (rc == LSM_OK && observed) rc = first->wait();  // observers see complete outputs
         if (rc != LSM_OK) {
             for (uint32_t j = 0; j < n_jobs; j++) active[j]->drop(merged[j]);
-            return rc;
+            return failed(rc);
         }
         for (uint32_t j = 0; j < n_jobs; j++) {
             lsm_driver_t* d = active[j];
@@ -684,7 +686,7 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             if (merged[j].n == 0) d->drop(merged[j]);
             rc = d->arrive_merged(merged[j]);
         }
-        if (rc != LSM_OK) return rc;
+        if (rc != LSM_OK) return failed(rc);
     }
 } catch (...) {  // host memory ran out: nothing may be thrown through the C ABI
     return LSM_ERR_INTERNAL;

@@ -417,3 +417,31 @@ def test_flush_many_on_degenerate_trees(oracle, seed):
     for (k, tg, b, ix), nat, cpu in zip(cfgs, nats, cpus):
         check_native_tree(oracle, nat, cpu, b, ix)
         nat.close()
+
+
+def test_flush_many_when_one_tree_fails(oracle):
+    """A tree whose compaction is refused (65 runs in a level) ends lsm_driver_flush_many with an error; the run that has
+    come to rest in the other tree is complete all the same: a copy of the caller's buffer, with fences and a filter."""
+    import brute
+    from gpu_util import to_dev
+    from paper_2511_16138_amd import LsmDriver, LsmError, lsm_driver_flush_many
+    key_of = lambda k: int(k).to_bytes(32, "big")
+    run_of = lambda keys: brute.run_from_raw([brute.pack_entry(key_of(k), 1, brute.PUT, vptr=k, vlen=k) for k in keys])
+    good, bad = LsmDriver(200, size_ratio=4, bloom_bits=16), LsmDriver(200, size_ratio=4, bloom_bits=16)
+    for i in range(64):
+        bad.load_run(1, to_dev(run_of([i])))
+    want = run_of(range(150))
+    buffer = to_dev(want)
+    with pytest.raises(LsmError):
+        lsm_driver_flush_many([good, bad], [buffer, to_dev(run_of([70]))])
+    buffer.zero_()
+    q = np.stack([np.stack([np.frombuffer(key_of(k), np.uint8) for k in range(r, r + 8)]) for r in range(0, 200, 8)])
+    gq = torch.from_numpy(q.view(np.int64).reshape(len(q), 8, 4).copy()).to(dev())
+    nb = np.full(len(q), 8, np.int32)
+    hit_len, hits = good.probe(gq, torch.from_numpy(nb).to(dev()))
+    want_len, want_hits = oracle.probe(gq.cpu(), torch.from_numpy(nb), [to_dev(want).cpu()])
+    assert np.array_equal(hit_len.cpu().numpy(), np.asarray(want_len).reshape(-1))
+    for r, n in enumerate(np.asarray(want_len).reshape(-1)):
+        assert hits[r, :n].cpu().numpy().tobytes() == np.asarray(want_hits)[r, :n].tobytes()
+    good.flush(to_dev(run_of(range(150, 180))))  # the tree goes on
+    assert good.levels()[0][2] == 1
