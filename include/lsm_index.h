@@ -273,7 +273,8 @@ int lsm_compact_remap(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, co
 int lsm_compact_static(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* stream);
 
 /* Bytes of workspace lsm_compact needs for runs of these lengths (HOST array). 0 on bad arguments.
- * About one byte per input entry (a copy of every 32nd key) plus 24 * n_runs bytes per (2048 - n_runs) entries. */
+ * About one byte per input entry (a copy of every 32nd key) plus 24 * n_runs bytes per tile: (2048 - n_runs)
+ * entries each, fewer (512 at least) where that would give less than 256 tiles. */
 size_t lsm_compact_workspace_bytes(const uint64_t* run_lens, uint32_t n_runs);
 
 /*

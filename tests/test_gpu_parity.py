@@ -37,6 +37,9 @@ def _check_compact(g, oracle, runs, flags):
 
 
 # ------------------------------------------------------------------ compaction
+SHORT, FILL = 512, 256  # shortest tile spacing, tiles an input is spread over before its tiles grow
+
+
 @pytest.mark.parametrize("flags", [0, 1])
 def test_config1_compaction(g, oracle, cfg1, flags):
     print("config1 compaction flags", flags, flush=True)
@@ -346,6 +349,50 @@ def test_probe_empty_tree_and_empty_runs(g, oracle, cfg1):
     tree = build_tree(g, [empty, cfg1.runs[3], empty])
     want = oracle.probe(q, nb, [empty.cpu(), cfg1.runs[3].cpu(), empty.cpu()])
     assert_probe_equal(oracle, probe_gpu(g, q, nb, tree), want)
+
+
+def _runs_of(oracle, rs, lens, keys):
+    """Sorted runs of these lengths, keys spread evenly over about range(keys)."""
+    runs = []
+    for n in lens:
+        lead = np.cumsum(rs.randint(1, max(2, 2 * keys // max(n, 1)), size=n))
+        a = np.zeros((n, 64), dtype=np.uint8)
+        a[:, :8] = lead.astype(">u8").view(np.uint8).reshape(n, 8)
+        rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+        rec["seqno"] = rs.randint(0, 1 << 40, size=n)
+        rec["type"] = (rs.rand(n) < 0.1).astype(np.uint8)
+        runs.append(to_dev(a))
+    return runs
+
+
+@pytest.mark.parametrize("k", [1, 2, 3, 16, 64])
+def test_tile_spacing_edges(g, oracle, k):
+    """Inputs around the totals where the tile spacing changes: one tile or several, the shortest spacing, one that grows
+    with the input, the longest."""
+    rs = np.random.RandomState(k)
+    full = 2048 - k
+    for total in (full, full + 1, SHORT, SHORT * FILL, SHORT * FILL + 1, 777 * FILL + 5, full * FILL - 1, full * FILL + 1):
+        print("tile spacing", k, total, flush=True)
+        cuts = np.sort(rs.randint(0, total + 1, size=k - 1)) if k > 1 else np.zeros(0, np.int64)
+        lens = np.diff(np.concatenate([[0], cuts, [total]])).astype(int)
+        _check_compact(g, oracle, _runs_of(oracle, rs, lens, 2 * total + 100), int(total & 1))
+
+
+@pytest.mark.parametrize("jobs", [1, 3, 30])  # 30: the job table is copied
+def test_batch_tile_spacing_edges(g, oracle, jobs):
+    """The same for a batch: its spacing follows from the entries of all jobs, a job's own run count caps it."""
+    rs = np.random.RandomState(jobs)
+    for total in (SHORT * FILL - 3, SHORT * FILL + 3, 2000 * FILL, 2047 * FILL):
+        print("batch tile spacing", jobs, total, flush=True)
+        todo = []
+        for j in range(jobs):
+            k, n = (1, 2, 3, 17)[(j + jobs) % 4], total // jobs
+            todo.append((_runs_of(oracle, rs, [n // k] * (k - 1) + [n - (k - 1) * (n // k)], 2 * n + 100), j & 1))
+        outs, n_out = g.lsm_compact_batch(todo)
+        for (runs, flags), out, n in zip(todo, outs, n_out.tolist()):
+            want = oracle.compact([r.cpu() for r in runs], flags)
+            assert n == want.shape[0]
+            assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
 
 
 @pytest.mark.parametrize("n_req", [1, 2, 3, 511, 512, 513, 2047, 2048, 2049])  # four, two and one wave per request

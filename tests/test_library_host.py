@@ -199,3 +199,16 @@ def test_cost_model_matches_the_checker(lib, oracle):
     assert g.lsm_policy_choose(0, 0.3, 0.3, 0.4, 400_000_000, 3600, 10, 10, 64.0, 1.0, 64.0) == (10, 1)
     with pytest.raises(g.LsmError):
         g.lsm_policy_choose(1, 0, 0, 0, 10, 0, 2, 4, 64.0, 1.0, 0.0)
+
+
+def test_compaction_workspace_grows_with_the_input(lib):
+    """A workspace that is large enough for an input is large enough for a shorter one with as many runs, also where the
+    tile spacing changes with the length; the static scratch takes what it took."""
+    for k in (1, 2, 5, 16, 64):
+        last = 0
+        for total in sorted({t + d for t in (1, 2048 - k, 2048, 512 * 256, 700 * 256, (2048 - k) * 256, 1 << 20, 3 << 20) for d in (-1, 0, 1, 255, 256)}):
+            lens = (C.c_uint64 * k)(*([total // k] * (k - 1) + [total - (k - 1) * (total // k)]))
+            need = lib.lsm_compact_workspace_bytes(lens, k)
+            assert need >= last, (k, total)
+            last = need - 512  # the last run's part of the samples can shrink by two of them
+        assert need < 8 << 20
