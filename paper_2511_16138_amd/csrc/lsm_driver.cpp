@@ -80,7 +80,7 @@ struct Run {
     bool transient = false;  // entries belong to the caller of a flush: copied if the run comes to rest
     uint8_t* fences = nullptr;
     void* bloom = nullptr;
-    uint64_t n_blocks = 0;
+    uint64_t n_blocks = 0;     // 0: bloom is memory for a filter at most
     bool bloom_clear = false;  // bloom is memory that has been zeroed, not a filter yet
     void* index = nullptr;
     uint64_t n_buckets = 0;
@@ -204,7 +204,8 @@ struct lsm_driver {
     bool plain_filter(uint64_t n) const { return cfg.bloom_bits != 0 && n < kHashedFilterEntries && !wants_index(n) && lsm_bloom_blocks(n, cfg.bloom_bits) != 0; }
 
     // Filter and hash index of a run that has come to rest, from the keys' hashes (computed once for both).  The
-    // temporaries go back to the pool at once: their next user's work comes later on the stream.
+    // temporaries go back to the pool at once: their next user's work comes later on the stream.  The run gets both when
+    // the launches that fill them have been made, or neither.
     int build_hashed(Run& r) {
         std::vector<void*> scratch;
         auto take = [&](size_t bytes) {
@@ -214,30 +215,38 @@ struct lsm_driver {
         };
         const bool indexed = wants_index(r.n) && r.index == nullptr;
         const lsm_run_t run{r.entries, r.n};
+        void *bloom = nullptr, *index = nullptr;
+        uint64_t n_blocks = 0, n_buckets = 0;
         uint64_t* hashes = static_cast<uint64_t*>(take(r.n * 8));
         int rc = hashes == nullptr ? (int)LSM_ERR_HIP : lsm_hash_keys(&run, hashes, stream);
-        if (rc == LSM_OK && cfg.bloom_bits != 0 && r.bloom == nullptr) {
-            r.n_blocks = lsm_bloom_blocks(r.n, cfg.bloom_bits);
-            if (r.n_blocks != 0) {
-                r.bloom = pool.take(r.n_blocks * 16);
-                if (r.bloom == nullptr) rc = LSM_ERR_HIP;
-                const size_t ws_bytes = lsm_bloom_workspace_bytes(r.n, r.n_blocks);
-                void* ws = rc == LSM_OK && ws_bytes != 0 ? take(ws_bytes) : nullptr;
-                if (rc == LSM_OK && ws_bytes != 0)
-                    rc = ws == nullptr ? (int)LSM_ERR_HIP : lsm_build_bloom_hashed(hashes, r.n, r.bloom, r.n_blocks, ws, ws_bytes, stream);
-                else if (rc == LSM_OK)
-                    rc = lsm_build_bloom(&run, r.bloom, r.n_blocks, stream);
-            }
+        if (rc == LSM_OK && cfg.bloom_bits != 0 && r.bloom == nullptr) n_blocks = lsm_bloom_blocks(r.n, cfg.bloom_bits);
+        if (n_blocks != 0) {
+            bloom = pool.take(n_blocks * 16);
+            if (bloom == nullptr) rc = LSM_ERR_HIP;
+            const size_t ws_bytes = lsm_bloom_workspace_bytes(r.n, n_blocks);
+            void* ws = rc == LSM_OK && ws_bytes != 0 ? take(ws_bytes) : nullptr;
+            if (rc == LSM_OK && ws_bytes != 0)
+                rc = ws == nullptr ? (int)LSM_ERR_HIP : lsm_build_bloom_hashed(hashes, r.n, bloom, n_blocks, ws, ws_bytes, stream);
+            else if (rc == LSM_OK)
+                rc = lsm_build_bloom(&run, bloom, n_blocks, stream);
         }
         if (rc == LSM_OK && indexed) {
-            r.n_buckets = lsm_hash_index_buckets(r.n);
+            n_buckets = lsm_hash_index_buckets(r.n);
             const size_t ws_bytes = lsm_hash_index_workspace_bytes(r.n);
-            r.index = pool.take(r.n_buckets * 64);
+            index = pool.take(n_buckets * 64);
             void* ws = take(ws_bytes);
-            rc = (r.index == nullptr || ws == nullptr) ? (int)LSM_ERR_HIP : lsm_build_hash_index(hashes, r.n, r.index, ws, ws_bytes, stream);
+            rc = (index == nullptr || ws == nullptr) ? (int)LSM_ERR_HIP : lsm_build_hash_index(hashes, r.n, index, ws, ws_bytes, stream);
         }
         for (void* p : scratch) pool.give(p);
-        return rc;
+        if (rc != LSM_OK) {
+            pool.give(bloom);
+            pool.give(index);
+            return rc;
+        }
+        if (bloom != nullptr) r.bloom = bloom, r.n_blocks = n_blocks;
+        if (index != nullptr) r.index = index, r.n_buckets = n_buckets;
+        r.settled = true;
+        return LSM_OK;
     }
 
     // Memory for the filter of a run of at most `n` entries, to be zeroed by a launch that is made anyway.
@@ -253,65 +262,119 @@ struct lsm_driver {
     // The runs that have come to rest in `count` drivers (of one stream) get whatever lookup structure they still lack: the
     // copies of flushed runs in one launch, and the filters of all short runs in one.  (Runs that are merged away at once -
     // a flushed run arriving at a full level, a run moved down onto another - never get any.)
+    // A run is changed only when the launch that fills the memory it points to has been made, and what fails for one run
+    // (memory, mostly) leaves out that run and no other; the first error is returned.  A run that was left out has no
+    // structure rather than an unfinished one, and the next call completes it.
     static int settle_all(lsm_driver* const* drivers, uint32_t count) {
-        std::vector<lsm::IngestJob> ingest;
-        std::vector<lsm_run_t> runs[2];  // [1]: with a filter memory that is zeroed by then
-        std::vector<void*> filters[2];
-        std::vector<uint64_t> blocks[2];
-        std::vector<std::pair<lsm_driver*, Run*>> resting;
+        struct Resting {
+            lsm_driver* d;
+            Run* r;
+            lsm_entry_t* copy;  // of a flushed run
+            uint8_t* fences;
+            void* bloom;
+        };
+        int first_error = LSM_OK;
+        auto fails = [&](int rc) {
+            if (rc != LSM_OK && first_error == LSM_OK) first_error = rc;
+            return rc != LSM_OK;
+        };
+        std::vector<Resting> resting;
         for (uint32_t i = 0; i < count; i++)
             for (Level& lv : drivers[i]->levels)
                 for (Run& r : lv.runs)
-                    if (!r.settled && r.n != 0) resting.emplace_back(drivers[i], &r);
-        const hipStream_t stream = count != 0 ? drivers[0]->stream : nullptr;
+                    if (!r.settled && r.n != 0) resting.push_back(Resting{drivers[i], &r, nullptr, nullptr, nullptr});
+        if (resting.empty()) return LSM_OK;
+        const hipStream_t stream = drivers[0]->stream;
+        std::vector<lsm::IngestJob> ingest;
+        std::vector<size_t> ingested;
+        ingest.reserve(resting.size()), ingested.reserve(resting.size());
         uint32_t stride = 1;
-        for (const auto& [d, r] : resting) {
-            if (r->transient) {
-                lsm_entry_t* copy = static_cast<lsm_entry_t*>(d->pool.take(r->n * sizeof(lsm_entry_t)));
-                r->fences = static_cast<uint8_t*>(d->pool.take(ceil_div(r->n, d->cfg.fence_stride) * LSM_KEY_BYTES));
-                lsm::ClearSpan clear;
-                if (copy == nullptr || r->fences == nullptr || d->take_filter(*r, r->n, &clear) != LSM_OK) return LSM_ERR_HIP;
-                if (!ingest.empty() && stride != d->cfg.fence_stride) {  // one stride per launch
-                    const int rc = lsm::ingest_runs(ingest.data(), (uint32_t)ingest.size(), stride, stream);
-                    if (rc != LSM_OK) return rc;
-                    ingest.clear();
+        auto launch_ingest = [&] {
+            const bool failed = !ingest.empty() && fails(lsm::ingest_runs(ingest.data(), (uint32_t)ingest.size(), stride, stream));
+            for (size_t i : ingested) {
+                const Resting& x = resting[i];
+                if (failed) {
+                    x.d->pool.give(x.copy);
+                    x.d->pool.give(x.fences);
+                    x.d->pool.give(x.bloom);
+                    continue;
                 }
-                stride = d->cfg.fence_stride;
-                ingest.push_back(lsm::IngestJob{r->entries, copy, r->n, r->fences, static_cast<uint4*>(clear.p), clear.bytes / 16});
-                r->entries = copy, r->owned = true, r->transient = false, r->bloom_clear = r->bloom != nullptr;
-            } else if (r->fences == nullptr) {
-                r->fences = static_cast<uint8_t*>(d->pool.take(ceil_div(r->n, d->cfg.fence_stride) * LSM_KEY_BYTES));
-                if (r->fences == nullptr) return LSM_ERR_HIP;
-                const lsm_run_t run{r->entries, r->n};
-                const int rc = lsm_build_fences(&run, d->cfg.fence_stride, r->fences, stream);
-                if (rc != LSM_OK) return rc;
+                x.r->entries = x.copy, x.r->owned = true, x.r->transient = false;
+                x.r->fences = x.fences;
+                x.r->bloom = x.bloom, x.r->bloom_clear = x.bloom != nullptr;
             }
-        }
-        int rc = ingest.empty() ? (int)LSM_OK : lsm::ingest_runs(ingest.data(), (uint32_t)ingest.size(), stride, stream);
-        for (const auto& [d, r] : resting) {
-            if (rc != LSM_OK) break;
-            r->settled = true;
-            if (d->plain_filter(r->n)) {
-                const int zeroed = r->bloom != nullptr && r->bloom_clear ? 1 : 0;
-                r->n_blocks = lsm_bloom_blocks(r->n, d->cfg.bloom_bits);
-                if (r->bloom == nullptr) r->bloom = d->pool.take(r->n_blocks * 16);
-                if (r->bloom == nullptr) return LSM_ERR_HIP;
-                r->bloom_clear = false;
-                runs[zeroed].push_back(lsm_run_t{r->entries, r->n});
-                filters[zeroed].push_back(r->bloom);
-                blocks[zeroed].push_back(r->n_blocks);
+            ingest.clear(), ingested.clear();
+        };
+        for (size_t i = 0; i < resting.size(); i++) {
+            Resting& x = resting[i];
+            lsm_driver* const d = x.d;
+            Run& r = *x.r;
+            if (!r.transient && r.fences != nullptr) continue;
+            x.fences = static_cast<uint8_t*>(d->pool.take(ceil_div(r.n, d->cfg.fence_stride) * LSM_KEY_BYTES));
+            if (!r.transient) {
+                const lsm_run_t run{r.entries, r.n};
+                if (fails(x.fences == nullptr ? (int)LSM_ERR_HIP : lsm_build_fences(&run, d->cfg.fence_stride, x.fences, stream))) d->pool.give(x.fences);
+                else r.fences = x.fences;
                 continue;
             }
-            if (r->bloom_clear) {  // sized before the run's length was known, and then it became a run of another kind
-                d->pool.give(r->bloom);
-                r->bloom = nullptr, r->bloom_clear = false;
+            x.copy = static_cast<lsm_entry_t*>(d->pool.take(r.n * sizeof(lsm_entry_t)));
+            lsm::ClearSpan clear;
+            if (d->plain_filter(r.n)) {
+                clear.bytes = lsm_bloom_blocks(r.n, d->cfg.bloom_bits) * 16;
+                clear.p = x.bloom = d->pool.take(clear.bytes);
             }
-            if (d->cfg.bloom_bits != 0 || d->wants_index(r->n)) rc = d->build_hashed(*r);
+            if (x.copy == nullptr || x.fences == nullptr || (clear.bytes != 0 && x.bloom == nullptr)) {
+                (void)fails(LSM_ERR_HIP);
+                d->pool.give(x.copy);
+                d->pool.give(x.fences);
+                d->pool.give(x.bloom);
+                continue;
+            }
+            if (stride != d->cfg.fence_stride) launch_ingest();  // one stride per launch
+            stride = d->cfg.fence_stride;
+            ingest.push_back(lsm::IngestJob{r.entries, x.copy, r.n, x.fences, static_cast<uint4*>(clear.p), clear.bytes / 16});
+            ingested.push_back(i);
         }
-        for (int zeroed = 0; zeroed < 2 && rc == LSM_OK; zeroed++)
-            if (!runs[zeroed].empty())
-                rc = lsm::build_filters(runs[zeroed].data(), filters[zeroed].data(), blocks[zeroed].data(), (uint32_t)runs[zeroed].size(), zeroed == 1, stream);
-        return rc;
+        launch_ingest();
+        // filters: [1] on memory that is zeroed by then
+        std::vector<lsm_run_t> runs[2];
+        std::vector<void*> filters[2];
+        std::vector<uint64_t> blocks[2];
+        std::vector<size_t> filtered[2];
+        for (size_t i = 0; i < resting.size(); i++) {
+            Resting& x = resting[i];
+            lsm_driver* const d = x.d;
+            Run& r = *x.r;
+            if (r.transient || r.fences == nullptr) continue;  // left out above
+            if (d->plain_filter(r.n)) {
+                const int zeroed = r.bloom != nullptr && r.bloom_clear ? 1 : 0;
+                x.bloom = r.bloom != nullptr ? r.bloom : d->pool.take(lsm_bloom_blocks(r.n, d->cfg.bloom_bits) * 16);
+                if (x.bloom == nullptr) {
+                    (void)fails(LSM_ERR_HIP);
+                    continue;
+                }
+                r.bloom = x.bloom;  // n_blocks stays 0: not a filter yet
+                runs[zeroed].push_back(lsm_run_t{r.entries, r.n});
+                filters[zeroed].push_back(x.bloom);
+                blocks[zeroed].push_back(lsm_bloom_blocks(r.n, d->cfg.bloom_bits));
+                filtered[zeroed].push_back(i);
+            } else if (d->cfg.bloom_bits != 0 || d->wants_index(r.n)) {
+                (void)fails(d->build_hashed(r));
+            } else {
+                r.settled = true;
+            }
+        }
+        for (int zeroed = 0; zeroed < 2; zeroed++) {
+            if (runs[zeroed].empty()) continue;
+            const bool failed = fails(lsm::build_filters(runs[zeroed].data(), filters[zeroed].data(), blocks[zeroed].data(), (uint32_t)runs[zeroed].size(),
+                                                         zeroed == 1, stream));
+            for (size_t q = 0; q < filtered[zeroed].size(); q++) {
+                Run& r = *resting[filtered[zeroed][q]].r;
+                r.bloom_clear = false;  // a launch that failed may have set bits all the same
+                if (!failed) r.n_blocks = blocks[zeroed][q], r.settled = true;
+            }
+        }
+        return first_error;
     }
     int settle() {
         lsm_driver* self = this;
@@ -467,7 +530,7 @@ struct lsm_driver {
                     std::memset(&t, 0, sizeof(t));
                     t.run = lsm_run_t{r.entries, r.n};
                     t.fence = lsm_fence_t{r.fences, r.fences ? ceil_div(r.n, cfg.fence_stride) : 0, cfg.fence_stride};
-                    t.bloom = lsm_bloom_t{r.bloom, r.bloom ? r.n_blocks : 0};
+                    t.bloom = lsm_bloom_t{r.n_blocks ? r.bloom : nullptr, r.n_blocks};  // n_blocks is set when the filter is built
                     t.level = (uint32_t)l + 1;
                     t.index = lsm_hash_index_t{r.index, r.index ? r.n_buckets : 0};
                     out[n] = t;

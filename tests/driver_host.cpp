@@ -1,0 +1,203 @@
+// The library's driver (lsm_driver.cpp) on the CPU: the calls it makes of the HIP runtime and of the library's kernels,
+// answered by the checker in host memory.  What the driver decides - which runs are merged, what becomes of them when a
+// call of it fails - can then be tested without a GPU, failures included.  Test infrastructure only.
+//
+// "Device" memory is filled with 0xAB, so that memory that was handed out but never written is seen.  Work is done when it
+// is enqueued, which is one of the orders a stream allows.
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+#include <cstdlib>
+#include <cstring>
+#include <vector>
+
+#include "lsm_common.h"
+#include "lsm_index.h"
+
+extern "C" {
+uint64_t oracle_compact(const lsm_entry_t* const* runs, const uint64_t* lens, uint32_t n_runs, uint32_t flags, lsm_entry_t* out);
+void oracle_build_fences(const lsm_entry_t* run, uint64_t n, uint32_t stride, uint8_t* fence_keys);
+uint64_t oracle_bloom_blocks(uint64_t n, uint32_t bits_per_key);
+void oracle_build_bloom(const lsm_entry_t* run, uint64_t n, uint8_t* filter, uint64_t n_blocks);
+int oracle_bloom_may_contain(const uint8_t* filter, uint64_t n_blocks, const uint8_t* key);
+
+// What a test sets and reads.  *_in: the call of that kind, counted from 1, that fails next (0 = none does).
+int64_t host_malloc_in = 0;   // device memory runs out
+int64_t host_kernel_in = 0;   // a kernel call is refused, nothing was launched
+int64_t host_late_in = 0;     // a kernel call reports an error although its work is done
+uint64_t host_mallocs = 0, host_kernels = 0;
+uint32_t host_pinned_flags = ~0u;   // flags that every pinned allocation was made with
+uint64_t host_dirty_filters = 0;    // filters built on memory that was promised to be zero and was not
+
+void host_reset() {
+    host_malloc_in = host_kernel_in = host_late_in = 0;
+    host_mallocs = host_kernels = host_dirty_filters = 0;
+    host_pinned_flags = ~0u;
+}
+
+// ---------------------------------------------------------------------------------------------------- HIP runtime
+hipError_t hipMalloc(void** p, size_t bytes) {
+    host_mallocs++;
+    if (host_malloc_in > 0 && --host_malloc_in == 0) return hipErrorOutOfMemory;
+    *p = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
+    std::memset(*p, 0xAB, (bytes + 255) / 256 * 256);
+    return hipSuccess;
+}
+hipError_t hipFree(void* p) {
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipHostMalloc(void** p, size_t bytes, unsigned int flags) {
+    host_pinned_flags &= flags;
+    *p = std::malloc(bytes);
+    return hipSuccess;
+}
+hipError_t hipHostFree(void* p) {
+    std::free(p);
+    return hipSuccess;
+}
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamQuery(hipStream_t) { return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t) {
+    std::memcpy(dst, src, bytes);
+    return hipSuccess;
+}
+
+// ---------------------------------------------------------------------------------------------------- kernels
+static bool refused() {
+    host_kernels++;
+    return host_kernel_in > 0 && --host_kernel_in == 0;
+}
+static int done() { return host_late_in > 0 && --host_late_in == 0 ? LSM_ERR_HIP : LSM_OK; }
+
+static int merge(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, const lsm::ClearSpan& clear) {
+    std::vector<const lsm_entry_t*> ptr;
+    std::vector<uint64_t> len;
+    for (uint32_t j = 0; j < n_runs; j++) ptr.push_back(runs[j].entries), len.push_back(runs[j].n);
+    if (clear.bytes != 0) std::memset(clear.p, 0, clear.bytes);
+    *out->n_out = oracle_compact(ptr.data(), len.data(), n_runs, flags, out->entries);
+    if (out->fence_keys != nullptr) oracle_build_fences(out->entries, *out->n_out, out->fence_stride, static_cast<uint8_t*>(out->fence_keys));
+    return LSM_OK;
+}
+
+size_t lsm_compact_workspace_bytes(const uint64_t*, uint32_t n_runs) { return n_runs > LSM_MAX_RUNS ? 0 : 1024; }
+size_t lsm_compact_batch_workspace_bytes(const lsm_compact_job_t* jobs, uint32_t n_jobs) {
+    for (uint32_t j = 0; j < n_jobs; j++)
+        if (jobs[j].n_runs > LSM_MAX_RUNS) return 0;
+    return 1024 * n_jobs;
+}
+size_t lsm_flush_workspace_bytes(uint64_t n) { return 4 * n; }
+int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm_out_t* out, void*, size_t, void*) {
+    if (refused()) return LSM_ERR_HIP;
+    std::vector<lsm_entry_t> v(buffer, buffer + n);
+    std::reverse(v.begin(), v.end());
+    std::stable_sort(v.begin(), v.end(), [](const lsm_entry_t& a, const lsm_entry_t& b) {
+        const int c = std::memcmp(a.key, b.key, LSM_KEY_BYTES);
+        return c != 0 ? c < 0 : a.seqno > b.seqno;
+    });
+    uint64_t m = 0;
+    for (uint64_t i = 0; i < n; i++)
+        if (i == 0 || std::memcmp(v[i].key, v[i - 1].key, LSM_KEY_BYTES) != 0) out->entries[m++] = v[i];
+    *out->n_out = m;
+    if (out->fence_keys != nullptr) oracle_build_fences(out->entries, m, out->fence_stride, static_cast<uint8_t*>(out->fence_keys));
+    return done();
+}
+int lsm_build_fences(const lsm_run_t* run, uint32_t stride, uint8_t* keys, void*) {
+    if (refused()) return LSM_ERR_HIP;
+    oracle_build_fences(run->entries, run->n, stride, keys);
+    return done();
+}
+uint64_t lsm_bloom_blocks(uint64_t n, uint32_t bits_per_key) { return oracle_bloom_blocks(n, bits_per_key); }
+int lsm_build_bloom(const lsm_run_t* run, void* filter, uint64_t n_blocks, void*) {
+    if (refused()) return LSM_ERR_HIP;
+    oracle_build_bloom(run->entries, run->n, static_cast<uint8_t*>(filter), n_blocks);
+    return done();
+}
+size_t lsm_bloom_workspace_bytes(uint64_t, uint64_t) { return 0; }  // lsm_build_bloom is used instead
+int lsm_build_bloom_hashed(const uint64_t*, uint64_t, void*, uint64_t, void*, size_t, void*) { return LSM_ERR_INTERNAL; }
+int lsm_hash_keys(const lsm_run_t* run, uint64_t* hashes, void*) {
+    if (refused()) return LSM_ERR_HIP;
+    std::memset(hashes, 0, run->n * 8);
+    return done();
+}
+uint64_t lsm_hash_index_buckets(uint64_t n) { return n ? (n + 3) / 4 : 1; }
+size_t lsm_hash_index_workspace_bytes(uint64_t n) { return 16 * n + 256; }
+int lsm_build_hash_index(const uint64_t*, uint64_t n, void* buckets, void*, size_t, void*) {  // a mark: built
+    if (refused()) return LSM_ERR_HIP;
+    std::memset(buckets, 0x11, lsm_hash_index_buckets(n) * 64);
+    return done();
+}
+// A lookup believes the filters, as the kernel does: a run whose filter excludes the key is not searched.
+int lsm_probe(const lsm_queries_t* q, const lsm_tree_t* tree, const lsm_hits_t* out, void*) {
+    if (refused()) return LSM_ERR_HIP;
+    for (uint32_t r = 0; r < q->n_req; r++) {
+        lsm_hit_t* row = out->hits + (uint64_t)r * q->max_blocks;
+        std::memset(row, 0, sizeof(lsm_hit_t) * q->max_blocks);
+        uint32_t j = 0;
+        for (; j < q->n_blocks[r]; j++) {
+            const uint8_t* key = q->keys + ((uint64_t)r * q->max_blocks + j) * LSM_KEY_BYTES;
+            const lsm_entry_t* found = nullptr;
+            for (uint32_t i = 0; i < tree->n_runs && found == nullptr; i++) {
+                const lsm_tree_run_t& t = tree->runs[i];
+                if (t.bloom.n_blocks != 0 && !oracle_bloom_may_contain(static_cast<const uint8_t*>(t.bloom.blocks), t.bloom.n_blocks, key)) continue;
+                for (uint64_t e = 0; e < t.run.n; e++)
+                    if (std::memcmp(t.run.entries[e].key, key, LSM_KEY_BYTES) == 0) found = t.run.entries + e;
+                if (found != nullptr) row[j].run_idx = i;
+            }
+            if (found == nullptr || found->type != LSM_PUT) {
+                row[j].run_idx = 0;
+                break;
+            }
+            row[j].vptr = found->vptr, row[j].vlen = found->vlen;
+        }
+        out->hit_len[r] = j;
+    }
+    return done();
+}
+}  // extern "C"
+
+namespace lsm {
+int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void*, size_t, const ClearSpan& clear, bool* cleared,
+                     hipStream_t) {
+    *cleared = false;
+    if (n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
+    if (refused()) return LSM_ERR_HIP;
+    *cleared = clear.bytes != 0;
+    const int rc = merge(runs, n_runs, flags, out, clear);
+    return rc != LSM_OK ? rc : done();
+}
+int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*, size_t, const ClearSpan* clear, hipStream_t) {
+    for (uint32_t j = 0; j < n_jobs; j++)
+        if (jobs[j].n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
+    if (refused()) return LSM_ERR_HIP;
+    for (uint32_t j = 0; j < n_jobs; j++) (void)merge(jobs[j].runs, jobs[j].n_runs, jobs[j].flags, &jobs[j].out, clear ? clear[j] : ClearSpan());
+    return done();
+}
+int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t fence_stride, hipStream_t) {
+    if (refused()) return LSM_ERR_HIP;
+    for (uint32_t j = 0; j < count; j++) {
+        std::memcpy(jobs[j].to, jobs[j].from, jobs[j].n * sizeof(lsm_entry_t));
+        oracle_build_fences(jobs[j].to, jobs[j].n, fence_stride, static_cast<uint8_t*>(jobs[j].fences));
+        if (jobs[j].clear_n != 0) std::memset(jobs[j].clear, 0, jobs[j].clear_n * 16);
+    }
+    return done();
+}
+int build_filters(const lsm_run_t* runs, void* const* filters, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t) {
+    if (refused()) return LSM_ERR_HIP;
+    for (uint32_t j = 0; j < n_runs; j++) {
+        const uint8_t* f = static_cast<const uint8_t*>(filters[j]);
+        if (cleared && std::any_of(f, f + 16 * n_blocks[j], [](uint8_t b) { return b != 0; })) host_dirty_filters++;
+        oracle_build_bloom(runs[j].entries, runs[j].n, static_cast<uint8_t*>(filters[j]), n_blocks[j]);
+    }
+    return done();
+}
+int probe_stats(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket, hipStream_t) {
+    if (refused()) return LSM_ERR_HIP;
+    stats[0] = stats[1] = 0;
+    for (uint32_t i = 0; i < n_req; i++) stats[0] += hit_len[i], stats[1] += hit_len[i] > 0;
+    stats[2] = ticket;
+    return done();
+}
+}  // namespace lsm

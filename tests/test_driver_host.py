@@ -1,0 +1,196 @@
+"""The library's driver on the CPU (tests/driver_host.cpp answers its calls): what becomes of the trees when device memory
+runs out or a launch is refused, at every place where that can happen.  A run that lookups can reach is complete or has no
+filter: never an unwritten copy, never a filter that rules out keys of its run."""
+import ctypes as C
+import os
+import subprocess
+
+import brute
+import numpy as np
+import pytest
+
+from oracle.lsm_driver_oracle import DriverOracle
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2511_16138_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+BAD_ARG, HIP = -2, -7
+
+
+@pytest.fixture(scope="module")
+def host(tmp_path_factory, oracle):
+    import paper_2511_16138_amd.binding as B
+    d = tmp_path_factory.mktemp("driver_host")
+    inc = ["-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
+    objects = []
+    for src in (os.path.join(CSRC, "lsm_driver.cpp"), os.path.join(ROOT, "tests", "driver_host.cpp")):
+        objects.append(str(d / (os.path.basename(src) + ".o")))
+        subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-fPIC", "--offload-host-only", "-x", "hip", *inc, "-c", src, "-o", objects[-1]])
+    objects.append(str(d / "oracle.o"))
+    subprocess.check_call(["gcc", "-O1", "-fPIC", "-c", os.path.join(ROOT, "oracle", "lsm_oracle.c"), "-o", objects[-1]])
+    lib = str(d / "libdriver_host.so")
+    # calls stay inside the library, whatever else the process has loaded
+    subprocess.check_call(["g++", "-shared", "-fPIC", "-Wl,-Bsymbolic", "-Wl,--no-undefined", "-o", lib, *objects, *inc,
+                           os.path.join(CSRC, "lsm_policy.cpp"), "-lpthread"])
+    L = C.CDLL(lib)
+    L.lsm_driver_create.argtypes = [C.POINTER(B._DriverConfig), C.c_void_p, C.POINTER(C.c_void_p)]
+    L.lsm_driver_destroy.argtypes = [C.c_void_p]
+    L.lsm_driver_destroy.restype = None
+    L.lsm_driver_load_run.argtypes = [C.c_void_p, C.c_uint32, C.c_void_p, C.c_uint64]
+    L.lsm_driver_flush.argtypes = L.lsm_driver_flush_unsorted.argtypes = [C.c_void_p, C.c_void_p, C.c_uint64]
+    L.lsm_driver_flush_many.argtypes = [C.POINTER(C.c_void_p), C.POINTER(C.c_void_p), C.POINTER(C.c_uint64), C.c_uint32]
+    L.lsm_driver_probe.argtypes = [C.c_void_p, C.POINTER(B._Queries), C.POINTER(B._Hits)]
+    L.lsm_driver_tree.argtypes = [C.c_void_p, C.POINTER(B._TreeRun), C.c_uint32, C.POINTER(C.c_uint32)]
+    L.lsm_driver_log.argtypes = [C.c_void_p, C.c_uint64, C.POINTER(B._DriverEvent), C.c_uint64]
+    L.lsm_driver_log.restype = C.c_uint64
+    return L
+
+
+@pytest.fixture
+def knobs(host):
+    host.host_reset()
+
+    class Knobs:
+        def __setattr__(self, name, value):
+            C.c_int64.in_dll(host, "host_" + name).value = value
+
+        def read(self, name, kind=C.c_uint64):
+            return kind.in_dll(host, "host_" + name).value
+    return Knobs()
+
+
+def run_of(keys, seq):
+    """Sorted run of these key numbers, 64-byte aligned."""
+    raw = np.zeros(len(keys) * 64 + 64, np.uint8)
+    at = -raw.ctypes.data % 64
+    run = raw[at:at + len(keys) * 64].reshape(-1, 64)
+    for i, k in enumerate(sorted(keys)):
+        run[i] = np.frombuffer(brute.pack_entry(int(k).to_bytes(32, "big"), seq, brute.PUT, vptr=1000 * seq + k, vlen=k + 1), np.uint8)
+    return run
+
+
+class Tree:
+    """A driver beside the plain replay of the same tree."""
+
+    def __init__(self, host, buffer=100, T=4, K=1, bits=16, stride=64, index=0, loaded=()):
+        import paper_2511_16138_amd.binding as B
+        self.B, self.host, self.bits, self.stride, self.index = B, host, bits, stride, index
+        cfg = B._DriverConfig(buffer, T, K, 1 << 40, 0.2, 2, 16, 64.0, 0.01, stride, bits, index, B._DriverObserver(), None)
+        self.h = C.c_void_p()
+        assert host.lsm_driver_create(C.byref(cfg), None, C.byref(self.h)) == 0
+        self.plain = DriverOracle(buffer, T, K, window_ops=1 << 40)
+        self.loaded = [(level, run) for level, run in loaded]
+        for level, run in self.loaded:
+            assert host.lsm_driver_load_run(self.h, level, run.ctypes.data, len(run)) == 0
+        for level in {level for level, _ in self.loaded}:
+            self.plain.install(level, [run for at, run in self.loaded if at == level])
+
+    def close(self):
+        self.host.lsm_driver_destroy(self.h)
+
+    def runs(self):
+        n = C.c_uint32(0)
+        assert self.host.lsm_driver_tree(self.h, None, 0, C.byref(n)) == 0
+        out = (self.B._TreeRun * max(1, n.value))()
+        assert self.host.lsm_driver_tree(self.h, out, n.value, C.byref(n)) == 0
+        return [out[i] for i in range(n.value)]
+
+    def unfinished(self, oracle):
+        """What the tree lacks against the plain replay ("" = it is complete).  Anything wrong, as opposed to missing, fails."""
+        lacks = []
+        got = self.runs()
+        want = [r for r in self.plain.runs_newest_first()]
+        same_runs = len(got) == len(want)
+        for i, t in enumerate(got):
+            n = t.run.n
+            if n == 0:
+                continue
+            entries = np.ctypeslib.as_array(C.cast(t.run.entries, C.POINTER(C.c_uint8)), (n, 64))
+            if same_runs and not np.array_equal(entries, want[i]):
+                same_runs = False
+            keys = [bytes(e[:32]) for e in entries]
+            assert keys == sorted(keys) and not any(k.startswith(b"\xab" * 8) for k in keys), "a run of unwritten memory"
+            if t.fence.n == 0:
+                lacks.append(f"fences of run {i}")  # a lookup is refused
+            else:
+                fences = np.ctypeslib.as_array(C.cast(t.fence.keys, C.POINTER(C.c_uint8)), (t.fence.n, 32))
+                assert np.array_equal(fences, oracle.build_fences(entries, self.stride)), "wrong fences"
+            if t.bloom.n_blocks != 0:
+                words = np.ctypeslib.as_array(C.cast(t.bloom.blocks, C.POINTER(C.c_uint8)), (t.bloom.n_blocks, 16))
+                assert np.array_equal(words, oracle.build_bloom(entries, t.bloom.n_blocks)), "a filter that is not the run's"
+            elif self.bits:
+                lacks.append(f"filter of run {i}")
+            if t.index.n_buckets != 0:
+                table = np.ctypeslib.as_array(C.cast(t.index.buckets, C.POINTER(C.c_uint8)), (t.index.n_buckets * 64,))
+                assert (table == 0x11).all(), "an index that was not built"
+            elif self.index and n >= self.index:
+                lacks.append(f"index of run {i}")
+        if not same_runs:
+            lacks.append("runs")
+        return ", ".join(lacks)
+
+    def log(self):
+        total = self.host.lsm_driver_log(self.h, 0, None, 0)
+        out = (self.B._DriverEvent * max(1, total))()
+        self.host.lsm_driver_log(self.h, 0, out, total)
+        names = {1: lambda e: ("adopt", e.level, e.a, e.b), 2: lambda e: ("compact", e.level, e.a, e.n_in, e.n_out, e.b),
+                 3: lambda e: ("move", e.level, e.a, e.n_out), 4: lambda e: ("probe", e.a, e.b, e.n_out)}
+        return [names[out[i].kind](out[i]) for i in range(total)]
+
+
+def flush_many(host, trees, runs):
+    hd = (C.c_void_p * len(trees))(*[t.h for t in trees])
+    ptr = (C.c_void_p * len(trees))(*[None if r is None else r.ctypes.data for r in runs])
+    n = (C.c_uint64 * len(trees))(*[0 if r is None else len(r) for r in runs])
+    for t, r in zip(trees, runs):
+        if r is not None:
+            t.plain.flush(r.copy())
+    return host.lsm_driver_flush_many(hd, ptr, n, len(trees))
+
+
+def resting_trees(host):
+    """Trees whose flushed run comes to rest at once: copies with two fence strides, a filter from hashes and an index, no
+    filter at all."""
+    old = lambda: [(1, run_of(range(0, 300, 3), 1))]  # noqa: E731
+    return [Tree(host, K=3, loaded=old()), Tree(host, K=3), Tree(host, K=3, stride=16, loaded=old()), Tree(host, K=3, index=1, loaded=old()),
+            Tree(host, K=3, bits=0), Tree(host, K=3, stride=16)]
+
+
+FAULTS = ["malloc_in", "kernel_in", "late_in"]
+
+
+def sweep(host, knobs, oracle, fault, trees_of, flushes):
+    """Every place at which `fault` can strike one flush_many: yields (place, status, trees, what each lacks)."""
+    for place in range(1, 1000):
+        trees = trees_of(host)
+        runs = flushes()
+        setattr(knobs, fault, place)
+        rc = flush_many(host, trees, runs)
+        struck = knobs.read(fault, C.c_int64) == 0
+        setattr(knobs, fault, 0)
+        lacks = [t.unfinished(oracle) for t in trees]
+        for t, r, missing in zip(trees, runs, lacks):
+            if r is not None and not missing:
+                r[:] = 0xEE  # the caller's memory again: a complete tree does not refer to it
+                assert t.unfinished(oracle) == ""
+        yield place, rc, trees, lacks
+        assert knobs.read("dirty_filters") == 0
+        for t in trees:
+            t.close()
+        if not struck:
+            assert rc == 0
+            return
+    raise AssertionError("the sweep did not end")
+
+
+@pytest.mark.parametrize("fault", FAULTS)
+def test_a_failure_while_runs_are_completed_leaves_out_no_other_tree(host, knobs, oracle, fault):
+    flushes = lambda: [run_of(range(j, 90 + j), 2) for j in range(6)]  # noqa: E731
+    for place, rc, trees, lacks in sweep(host, knobs, oracle, fault, resting_trees, flushes):
+        missing = [x for x in lacks if x]
+        assert rc == (HIP if missing else 0), (place, rc, lacks)
+        if fault == "malloc_in":
+            assert len(missing) <= 1, (place, lacks)
+        # the next call that gets through makes up for what was left out
+        assert flush_many(host, trees, [run_of(range(200 + j, 260 + j), 3) for j in range(6)]) == 0
+        assert not any(t.unfinished(oracle) for t in trees), place
