@@ -667,90 +667,106 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             return LSM_ERR_HIP;
         first->counts_host_count = count;
     }
+    std::vector<int> status(count, LSM_OK);  // a tree that has failed takes no further step; the others end as they would alone
     for (uint32_t i = 0; i < count; i++) {
         if (runs[i] == nullptr) continue;  // nothing to flush for this tree
         Run r;
         if (n[i] > 0) r.entries = runs[i], r.n = n[i], r.transient = true;
-        const int rc = drivers[i]->arrive_begin(0, r);
-        if (rc != LSM_OK) return rc;
+        status[i] = drivers[i]->arrive_begin(0, r);
     }
-    // a compaction of one tree failed: the runs that have come to rest in the others still get their copies and structures
-    auto failed = [&](int rc) {
-        (void)lsm_driver::settle_all(drivers, count);
-        return rc;
+    struct Step {  // one compaction of a batch
+        uint32_t tree;
+        Run merged;
     };
-    std::vector<lsm_driver_t*> active;
+    std::vector<Step> steps;
     std::vector<std::vector<lsm_run_t>> inputs;
     std::vector<lsm_compact_job_t> jobs;
-    std::vector<Run> merged;
     std::vector<lsm::ClearSpan> clear;
     for (;;) {
         // the compactions that are due now: the long ones on their own, the others as one batch
-        active.clear();
+        steps.clear(), inputs.clear(), jobs.clear(), clear.clear();
         for (uint32_t i = 0; i < count; i++) {
             lsm_driver_t* d = drivers[i];
-            while (d->due.active && d->due.n_in >= kBatchJobEntries) {
-                const int rc = d->compact_due();
-                if (rc != LSM_OK) return failed(rc);
-            }
-            if (d->due.active) active.push_back(d);
-        }
-        if (active.empty()) return lsm_driver::settle_all(drivers, count);
-        const uint32_t n_jobs = (uint32_t)active.size();
-        inputs.assign(n_jobs, {});
-        jobs.assign(n_jobs, lsm_compact_job_t{});
-        merged.assign(n_jobs, Run());
-        clear.assign(n_jobs, lsm::ClearSpan());
-        int rc = LSM_OK;
-        for (uint32_t j = 0; j < n_jobs && rc == LSM_OK; j++) {
-            lsm_driver_t* d = active[j];
+            while (status[i] == LSM_OK && d->due.active && d->due.n_in >= kBatchJobEntries) status[i] = d->compact_due();
+            if (status[i] != LSM_OK || !d->due.active) continue;
             const std::vector<Run>& in = d->levels[d->due.level].runs;
-            if (in.size() > LSM_MAX_RUNS) rc = LSM_ERR_BAD_ARG;
-            for (const Run& r : in) inputs[j].push_back(lsm_run_t{r.entries, r.n});
+            if (in.size() > LSM_MAX_RUNS) {
+                status[i] = LSM_ERR_BAD_ARG;
+                continue;
+            }
             const uint64_t room = d->due.n_in > 0 ? d->due.n_in : 1;
+            Run merged;
+            lsm::ClearSpan zeroed;
             lsm_entry_t* entries = static_cast<lsm_entry_t*>(d->pool.take(room * sizeof(lsm_entry_t)));
-            uint8_t* fences = static_cast<uint8_t*>(d->pool.take(ceil_div(room, d->cfg.fence_stride) * LSM_KEY_BYTES));
-            if (entries == nullptr || fences == nullptr || d->take_filter(merged[j], d->due.n_in, &clear[j]) != LSM_OK) rc = LSM_ERR_HIP;
-            merged[j].bloom_clear = merged[j].bloom != nullptr;
-            merged[j].entries = entries, merged[j].owned = true, merged[j].fences = fences;  // given back through drop() on failure
-            static_cast<volatile uint64_t*>(first->counts_host)[j] = kCountUnset;
-            jobs[j].runs = inputs[j].data(), jobs[j].n_runs = (uint32_t)inputs[j].size(), jobs[j].flags = d->due.flags;
-            jobs[j].out = lsm_out_t{entries, room, first->counts_host + j, fences, d->cfg.fence_stride, nullptr};
+            merged.entries = entries, merged.owned = true;  // given back through drop() on failure
+            merged.fences = static_cast<uint8_t*>(d->pool.take(ceil_div(room, d->cfg.fence_stride) * LSM_KEY_BYTES));
+            status[i] = d->take_filter(merged, d->due.n_in, &zeroed);
+            if (entries == nullptr || merged.fences == nullptr) status[i] = LSM_ERR_HIP;
+            if (status[i] != LSM_OK) {
+                d->drop(merged);
+                continue;
+            }
+            merged.bloom_clear = merged.bloom != nullptr;
+            inputs.emplace_back();
+            for (const Run& r : in) inputs.back().push_back(lsm_run_t{r.entries, r.n});
+            lsm_compact_job_t job{};
+            job.runs = inputs.back().data(), job.n_runs = (uint32_t)inputs.back().size(), job.flags = d->due.flags;
+            job.out = lsm_out_t{entries, room, first->counts_host + jobs.size(), merged.fences, d->cfg.fence_stride, nullptr};
+            static_cast<volatile uint64_t*>(first->counts_host)[jobs.size()] = kCountUnset;
+            jobs.push_back(job);
+            clear.push_back(zeroed);
+            steps.push_back(Step{i, merged});
         }
-        const size_t need = rc == LSM_OK ? lsm_compact_batch_workspace_bytes(jobs.data(), n_jobs) : 0;
-        if (rc == LSM_OK && need == 0) rc = LSM_ERR_BAD_ARG;
+        const uint32_t n_jobs = (uint32_t)jobs.size();
+        if (n_jobs == 0) break;
+        int rc = LSM_OK;
+        const size_t need = lsm_compact_batch_workspace_bytes(jobs.data(), n_jobs);
+        if (need == 0) rc = LSM_ERR_BAD_ARG;
         if (rc == LSM_OK && need > first->batch_workspace_bytes) {
             first->pool.give(first->batch_workspace);
             first->batch_workspace_bytes = 2 * need;
             first->batch_workspace = first->pool.take(first->batch_workspace_bytes);
             if (first->batch_workspace == nullptr) first->batch_workspace_bytes = 0, rc = LSM_ERR_HIP;
         }
-        if (rc == LSM_OK)
+        if (rc == LSM_OK) {
             rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, first->batch_workspace, first->batch_workspace_bytes, clear.data(), first->stream);
+            // an error may be that of an earlier call, with this launch under way: its counts must not meet the next batch's
+            if (rc != LSM_OK) (void)first->wait();
+        }
+        if (rc != LSM_OK) {  // what the trees shared failed: every tree's compaction on its own
+            for (Step& step : steps) {
+                drivers[step.tree]->drop(step.merged);
+                status[step.tree] = drivers[step.tree]->compact_due();
+            }
+            continue;
+        }
         bool observed = false;
-        for (uint32_t j = 0; j < n_jobs && rc == LSM_OK; j++) {
-            rc = first->watch(first->counts_host + j, kCountUnset);
-            if (rc == LSM_OK && first->counts_host[j] > jobs[j].out.capacity) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
-            observed = observed || active[j]->cfg.observer != nullptr;
-        }
-        if (rc == LSM_OK && observed) rc = first->wait();  // observers see complete outputs
-        if (rc != LSM_OK) {
-            for (uint32_t j = 0; j < n_jobs; j++) active[j]->drop(merged[j]);
-            return failed(rc);
-        }
         for (uint32_t j = 0; j < n_jobs; j++) {
-            lsm_driver_t* d = active[j];
-            if (rc != LSM_OK) {
-                d->drop(merged[j]);
+            int& st = status[steps[j].tree];
+            st = first->watch(first->counts_host + j, kCountUnset);
+            if (st == LSM_OK && first->counts_host[j] > jobs[j].out.capacity) st = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
+            observed = observed || drivers[steps[j].tree]->cfg.observer != nullptr;
+        }
+        const int seen = observed ? first->wait() : (int)LSM_OK;  // observers see complete outputs
+        for (uint32_t j = 0; j < n_jobs; j++) {
+            lsm_driver_t* d = drivers[steps[j].tree];
+            Run& merged = steps[j].merged;
+            int& st = status[steps[j].tree];
+            if (st == LSM_OK) st = seen;
+            if (st != LSM_OK) {
+                d->drop(merged);
                 continue;
             }
-            merged[j].n = first->counts_host[j];
-            if (d->cfg.observer != nullptr) d->cfg.observer(d->cfg.observer_ctx, d->due.level + 1, merged[j].entries, merged[j].n);
-            if (merged[j].n == 0) d->drop(merged[j]);
-            rc = d->arrive_merged(merged[j]);
+            merged.n = first->counts_host[j];
+            if (d->cfg.observer != nullptr) d->cfg.observer(d->cfg.observer_ctx, d->due.level + 1, merged.entries, merged.n);
+            if (merged.n == 0) d->drop(merged);
+            st = d->arrive_merged(merged);
         }
-        if (rc != LSM_OK) return failed(rc);
     }
+    const int settled = lsm_driver::settle_all(drivers, count);
+    for (int st : status)
+        if (st != LSM_OK) return st;
+    return settled;
 } catch (...) {  // host memory ran out: nothing may be thrown through the C ABI
     return LSM_ERR_INTERNAL;
 }

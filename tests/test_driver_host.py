@@ -194,3 +194,47 @@ def test_a_failure_while_runs_are_completed_leaves_out_no_other_tree(host, knobs
         # the next call that gets through makes up for what was left out
         assert flush_many(host, trees, [run_of(range(200 + j, 260 + j), 3) for j in range(6)]) == 0
         assert not any(t.unfinished(oracle) for t in trees), place
+
+
+def merging_trees(host):
+    """Trees with compactions due: one that stays, one whose output moves down onto a run, one that only rests, one with an
+    index, a chain of three levels."""
+    return [Tree(host, loaded=[(1, run_of(range(0, 300, 3), 1))]),
+            Tree(host, loaded=[(1, run_of(range(0, 790, 2), 2)), (2, run_of(range(1, 1800, 2), 1))]),
+            Tree(host, K=2, stride=16, loaded=[(1, run_of(range(40, 90), 1))]),
+            Tree(host, index=150, loaded=[(1, run_of(range(0, 300, 3), 1)), (2, run_of(range(600, 700), 0))]),
+            Tree(host, buffer=50, T=2, loaded=[(1, run_of(range(0, 99), 3)), (2, run_of(range(150, 349), 2)), (3, run_of(range(500, 600), 1))])]
+
+
+@pytest.mark.parametrize("fault", FAULTS)
+def test_a_failure_in_one_tree_s_compaction_leaves_the_others_as_after_their_own_flush(host, knobs, oracle, fault):
+    flushes = lambda: [run_of(range(j, 90 + j), 4) for j in range(5)]  # noqa: E731
+    places = 0
+    for place, rc, trees, lacks in sweep(host, knobs, oracle, fault, merging_trees, flushes):
+        places += 1
+        missing = [x for x in lacks if x]
+        if fault == "malloc_in":  # memory is the tree's own, and what the trees share can be done without
+            assert len(missing) <= 1, (place, lacks)
+        assert rc == (HIP if missing else 0), (place, rc, lacks)
+        for t, x in zip(trees, lacks):
+            assert x or t.log() == t.plain.log, place
+    assert places > (20 if fault == "malloc_in" else 5)
+
+
+def test_a_tree_with_too_many_runs_does_not_stop_the_others(host, knobs, oracle):
+    """65 runs in a level are refused; the compactions that were due beside that one are done, in the first step of the call
+    and in later ones."""
+    trees = merging_trees(host) + [Tree(host, loaded=[(1, run_of([j], 1)) for j in range(64)])]
+    runs = [run_of(range(j, 90 + j), 4) for j in range(6)]
+    assert flush_many(host, trees, runs) == BAD_ARG
+    for r in runs[:5]:
+        r[:] = 0xEE
+    for t in trees[:5]:
+        assert t.unfinished(oracle) == ""
+        assert t.log() == t.plain.log
+    assert flush_many(host, trees[:5], [run_of(range(100 + j, 190 + j), 5) for j in range(5)]) == 0  # the trees go on
+    for t in trees[:5]:
+        assert t.unfinished(oracle) == ""
+        assert t.log() == t.plain.log
+    for t in trees:
+        t.close()
