@@ -171,11 +171,12 @@ struct lsm_driver {
 
     int wait() { return hipStreamSynchronize(stream) == hipSuccess ? LSM_OK : LSM_ERR_HIP; }
 
-    // Waits until a kernel of the stream has written *word (anything but `unset`).  The stream is asked now and then, so
-    // that an error there ends the wait.
-    int watch(const uint64_t* word, uint64_t unset) {
+    // Waits until a kernel of the stream has made ready(*word) true.  The stream is asked now and then, so that an error
+    // there ends the wait.
+    template <typename Ready>
+    int watch(const uint64_t* word, Ready ready) {
         const volatile uint64_t* w = word;
-        for (uint32_t spins = 1; *w == unset; spins++) {
+        for (uint32_t spins = 1; !ready(*w); spins++) {
             cpu_pause();
             if (spins % 16384 != 0) continue;
             const hipError_t e = hipStreamQuery(stream);
@@ -183,10 +184,13 @@ struct lsm_driver {
                 (void)hipGetLastError();  // not an error of the next launch
                 continue;
             }
-            if (e != hipSuccess || *w == unset) return LSM_ERR_HIP;
+            if (e != hipSuccess || !ready(*w)) return LSM_ERR_HIP;
         }
         std::atomic_thread_fence(std::memory_order_acquire);
         return LSM_OK;
+    }
+    int watch_count(const uint64_t* word) {
+        return watch(word, [](uint64_t v) { return v != kCountUnset; });
     }
 
     // What the driver needs of the GPU runtime is created by the first call that works on runs, so that the controller
@@ -413,7 +417,7 @@ struct lsm_driver {
         const lsm_out_t out{entries, room, n_host, fences, cfg.fence_stride, nullptr};
         *static_cast<volatile uint64_t*>(n_host) = kCountUnset;
         int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, workspace_bytes, clear, &merged->bloom_clear, stream);
-        if (rc == LSM_OK) rc = watch(n_host, kCountUnset);
+        if (rc == LSM_OK) rc = watch_count(n_host);
         if (rc == LSM_OK && *n_host > room) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
         if (rc == LSM_OK && cfg.observer != nullptr) rc = wait();   // the observer sees a complete output
         if (rc != LSM_OK) {
@@ -629,7 +633,7 @@ extern "C" int lsm_driver_flush_unsorted(lsm_driver_t* d, const lsm_entry_t* buf
         *static_cast<volatile uint64_t*>(d->n_host) = kCountUnset;
         rc = lsm_flush_buffer(buffer, n, &out, ws, ws_bytes > 0 ? ws_bytes : 4, d->stream);
     }
-    if (rc == LSM_OK) rc = d->watch(d->n_host, kCountUnset);
+    if (rc == LSM_OK) rc = d->watch_count(d->n_host);
     d->pool.give(ws);
     if (rc == LSM_OK && *d->n_host > room) rc = LSM_ERR_INTERNAL;
     if (rc != LSM_OK) {
@@ -743,7 +747,7 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
         bool observed = false;
         for (uint32_t j = 0; j < n_jobs; j++) {
             int& st = status[steps[j].tree];
-            st = first->watch(first->counts_host + j, kCountUnset);
+            st = first->watch_count(first->counts_host + j);
             if (st == LSM_OK && first->counts_host[j] > jobs[j].out.capacity) st = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
             observed = observed || drivers[steps[j].tree]->cfg.observer != nullptr;
         }
@@ -784,9 +788,9 @@ extern "C" int lsm_driver_probe(lsm_driver_t* d, const lsm_queries_t* queries, c
     const uint32_t n_req = queries->n_req;
     uint64_t hits = 0, blocks = 0;
     if (n_req > 0) {
-        const uint64_t before = d->tickets++;
-        rc = lsm::probe_stats(out_hits->hit_len, n_req, d->stats_host, d->tickets, d->stream);
-        if (rc == LSM_OK) rc = d->watch(d->stats_host + 2, before);
+        const uint64_t ticket = ++d->tickets;  // this batch's: after a call that failed the word may hold any earlier one
+        rc = lsm::probe_stats(out_hits->hit_len, n_req, d->stats_host, ticket, d->stream);
+        if (rc == LSM_OK) rc = d->watch(d->stats_host + 2, [ticket](uint64_t v) { return v == ticket; });
         if (rc != LSM_OK) return rc;
         blocks = d->stats_host[0], hits = d->stats_host[1];
     }

@@ -238,3 +238,31 @@ def test_a_tree_with_too_many_runs_does_not_stop_the_others(host, knobs, oracle)
         assert t.log() == t.plain.log
     for t in trees:
         t.close()
+
+
+def probe(host, tree, keys, blocks=4):
+    """One request per key: the numbers from it upwards.  Returns the call's status and hit_len."""
+    B = tree.B
+    q = np.zeros((len(keys), blocks, 32), np.uint8)
+    for r, k in enumerate(keys):
+        for j in range(blocks):
+            q[r, j] = np.frombuffer(int(k + j).to_bytes(32, "big"), np.uint8)
+    nb, hit_len = np.full(len(keys), blocks, np.uint32), np.zeros(len(keys), np.uint32)
+    hits = np.zeros((len(keys), blocks, 16), np.uint8)
+    qd, hd = B._Queries(q.ctypes.data, nb.ctypes.data, len(keys), blocks), B._Hits(hit_len.ctypes.data, hits.ctypes.data)
+    return host.lsm_driver_probe(tree.h, C.byref(qd), C.byref(hd)), hit_len
+
+
+@pytest.mark.parametrize("fault", ["kernel_in", "late_in"])
+@pytest.mark.parametrize("place", [1, 2])  # the lookup, the launch that adds up what it found
+def test_what_a_batch_found_is_its_own_after_a_batch_that_failed(host, knobs, oracle, fault, place):
+    """The statistics that reach the log are those of the batch of this call, however long they take to arrive."""
+    tree = Tree(host, loaded=[(1, run_of(range(100), 1))])
+    knobs.slow_stats = 1
+    assert probe(host, tree, [0, 50, 98, 200])[0] == 0           # 4 + 4 + 2 blocks
+    setattr(knobs, fault, place)
+    assert probe(host, tree, [300])[0] == HIP
+    assert probe(host, tree, [10])[0] == 0
+    assert probe(host, tree, [97, 98, 99])[0] == 0               # 3 + 2 + 1
+    assert tree.log() == [("probe", 4, 3, 10), ("probe", 1, 1, 4), ("probe", 3, 3, 6)]
+    tree.close()
