@@ -194,13 +194,14 @@ struct lsm_driver {
     }
 
     // What the driver needs of the GPU runtime is created by the first call that works on runs, so that the controller
-    // (note_writes, note_reads, the log) can be used, and tested, on its own.
+    // (note_writes, note_reads, the log) can be used, and tested, on its own.  Words that the host watches are asked for as
+    // coherent memory: where the default is another, a count would be seen only when its kernel has ended.
     int gpu_ready() {
         if (n_host != nullptr) return LSM_OK;
-        if (stats_host == nullptr && hipHostMalloc(reinterpret_cast<void**>(&stats_host), 4 * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess)
+        if (stats_host == nullptr && hipHostMalloc(reinterpret_cast<void**>(&stats_host), 4 * sizeof(uint64_t), hipHostMallocCoherent) != hipSuccess)
             return LSM_ERR_HIP;
         stats_host[2] = 0;
-        return hipHostMalloc(reinterpret_cast<void**>(&n_host), sizeof(uint64_t), hipHostMallocDefault) == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+        return hipHostMalloc(reinterpret_cast<void**>(&n_host), sizeof(uint64_t), hipHostMallocCoherent) == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
 
     bool wants_index(uint64_t n) const { return cfg.hash_index_from != 0 && n >= cfg.hash_index_from && n <= (1ull << 27); }
@@ -667,7 +668,7 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
     if (count > first->counts_host_count) {
         if (first->counts_host != nullptr) (void)hipHostFree(first->counts_host);
         first->counts_host = nullptr, first->counts_host_count = 0;
-        if (hipHostMalloc(reinterpret_cast<void**>(&first->counts_host), (size_t)count * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess)
+        if (hipHostMalloc(reinterpret_cast<void**>(&first->counts_host), (size_t)count * sizeof(uint64_t), hipHostMallocCoherent) != hipSuccess)
             return LSM_ERR_HIP;
         first->counts_host_count = count;
     }

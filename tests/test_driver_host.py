@@ -266,3 +266,13 @@ def test_what_a_batch_found_is_its_own_after_a_batch_that_failed(host, knobs, or
     assert probe(host, tree, [97, 98, 99])[0] == 0               # 3 + 2 + 1
     assert tree.log() == [("probe", 4, 3, 10), ("probe", 1, 1, 4), ("probe", 3, 3, 6)]
     tree.close()
+
+
+def test_words_the_host_watches_are_in_coherent_memory(host, knobs):
+    """The host reads counts and statistics while kernels run: whatever the runtime's default for pinned memory is, these
+    words are asked for as coherent."""
+    tree = Tree(host, loaded=[(1, run_of(range(100), 1))])
+    assert flush_many(host, [tree], [run_of(range(50), 2)]) == 0
+    assert probe(host, tree, [0])[0] == 0
+    assert knobs.read("pinned_flags", C.c_uint32) & 0x40000000  # hipHostMallocCoherent, in every allocation
+    tree.close()
