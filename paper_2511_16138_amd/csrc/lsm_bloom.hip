@@ -78,8 +78,9 @@ constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a 
 constexpr int kBloomSmallThreads = 1024;
 template <uint32_t kBlocks, int kAhead>
 __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs jobs) {
-    __shared__ uint64_t words[kBlocks * 2];
-    uint32_t* f = reinterpret_cast<uint32_t*>(words);
+    __shared__ uint4 blocks[kBlocks];
+    uint32_t* f = reinterpret_cast<uint32_t*>(blocks);
+    uint64_t* words = reinterpret_cast<uint64_t*>(blocks);
     constexpr uint32_t kShare = kAhead * kBloomSmallThreads;
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
     const uint64_t n = jobs.n[blockIdx.y], first = (uint64_t)blockIdx.x * kShare;
@@ -103,7 +104,7 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
     __syncthreads();
     if (n <= kShare) {
         uint4* out = reinterpret_cast<uint4*>(jobs.words[blockIdx.y]);
-        for (uint32_t b = threadIdx.x; b < n_blocks; b += kBloomSmallThreads) out[b] = reinterpret_cast<const uint4*>(words)[b];
+        for (uint32_t b = threadIdx.x; b < n_blocks; b += kBloomSmallThreads) out[b] = blocks[b];
     } else {
         unsigned long long* out = reinterpret_cast<unsigned long long*>(jobs.words[blockIdx.y]);
         for (uint32_t w = threadIdx.x; w < n_blocks * 2; w += kBloomSmallThreads)
@@ -149,7 +150,8 @@ __global__ void hash_keys_kernel(const lsm_entry_t* entries, uint64_t n, uint64_
 template <bool kScan>
 __global__ void __launch_bounds__(kPartThreads) bloom_fill_kernel(const uint64_t* hashes, uint64_t n, const uint32_t* totals, uint32_t n_blocks,
                                                                  uint32_t unit_log, uint4* filter) {
-    __shared__ uint32_t f[kMaxRangeUnits * 4];
+    __shared__ uint4 part[kMaxRangeUnits];
+    uint32_t* f = reinterpret_cast<uint32_t*>(part);
     const uint32_t range = blockIdx.x, first_block = range << unit_log;
     const uint32_t blocks = min(1u << unit_log, n_blocks - first_block);
     for (uint32_t w = threadIdx.x; w < blocks * 4; w += kPartThreads) f[w] = 0;
@@ -165,8 +167,7 @@ __global__ void __launch_bounds__(kPartThreads) bloom_fill_kernel(const uint64_t
         bloom_set_lds(f + block * 4, h);
     });
     __syncthreads();
-    const uint4* src = reinterpret_cast<const uint4*>(f);
-    for (uint32_t b = threadIdx.x; b < blocks; b += kPartThreads) filter[first_block + b] = src[b];
+    for (uint32_t b = threadIdx.x; b < blocks; b += kPartThreads) filter[first_block + b] = part[b];
 }
 
 }  // namespace lsm
