@@ -287,6 +287,7 @@ def lsm_compact(runs: Sequence[torch.Tensor], flags: int = 0, out: Optional[torc
     that receives the fence index of the result (its first ceil(n_out / fence_stride) rows); `key_hashes` = int64
     [>= capacity] that receives the filter hash of every output key (for lsm_build_bloom_hashed)."""
     L = _load()
+    runs = list(runs)  # any iterable of tensors, a stacked tensor among them
     words = _run_words(runs)
     total = sum(words[1::2])
     dev = runs[0].device if runs else torch.device("cuda")

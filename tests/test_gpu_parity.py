@@ -87,6 +87,17 @@ def test_run_counts_and_ragged_lengths(g, oracle, k):
         _check_compact(g, oracle, runs, flags)
 
 
+def test_runs_from_any_iterable(g, oracle):
+    """lsm_compact takes its runs as any iterable: a list, a generator, one tensor of runs of the same length."""
+    rs = np.random.RandomState(3)
+    stacked = torch.stack(_runs_of(oracle, rs, [500, 500, 500], 4000))
+    want = oracle.compact([r.cpu() for r in stacked], 0)
+    for runs in (list(stacked), (r for r in stacked), stacked):
+        out, n_out = g.lsm_compact(runs, 0)
+        assert int(n_out.item()) == want.shape[0]
+        assert np.array_equal(as_bytes(out[: want.shape[0]]).reshape(-1, 64), want)
+
+
 @pytest.mark.parametrize("k", [3, 4, 5, 16, 32, 33, 64])
 @pytest.mark.parametrize("shape", ["nested", "stairs", "copies", "one long"])
 def test_tile_boundaries_of_uneven_runs(g, oracle, k, shape):
