@@ -130,19 +130,26 @@ __global__ void __launch_bounds__(kPlaceThreads) flush_place_kernel(const lsm_en
 // first.  Every thread sorts eight consecutive records in registers, then log2(segment / 8) rounds of merge-path merges
 // double the sorted lists, a thread producing eight outputs per round from eight records of either list (bitonic
 // half-cleaner and merge network).  Positions whose 14 bytes equal a neighbour's (versions of a key, and keys that
-// differ further on) are settled afterwards, each by comparing itself with the whole group: by the rest of the key,
-// seqno and age.  Bound by LDS operations of one compute unit per segment; all pairs of a segment instead (the step
-// that this one replaced) took 936 us for 100,001 entries, the whole call 1052 us against 149 us.  The entries themselves are read a second time for the output (they come from the L2).
+// differ further on) are settled afterwards by the rest of the key, seqno and age: each by comparing itself with the whole
+// group, or, where some group has more than kTieWalk members, by a merge sort of the whole segment that compares these.  Bound by LDS operations of one compute unit per segment; all pairs of a segment instead (the step
+// that this one replaced) took 936 us for 100,001 entries, the whole call 1052 us against 122 us.  The entries themselves are
+// read a second time for the output (they come from the L2).
 // ---------------------------------------------------------------------------------------
 constexpr uint64_t kFlushSegment = 4096;
 constexpr int kSortThreads = 512;
 constexpr int kSortItems = 8;
 static_assert(kSortThreads * kSortItems == kFlushSegment, "a segment fills the workgroup");
 static_assert(kFlushSegment * LSM_MAX_RUNS >= LSM_MAX_BUFFER, "the segments of the largest buffer must fit one compaction");
+// Members a group may have for its positions to be compared one by one: a serial chain of LDS reads that grows with the
+// square of the members (one group of 4,096: 10.6 ms a segment), where the merge sort takes about as long as the first sort
+// whatever the groups (8,193 versions of one key 139 us in all, 68 for distinct keys).  100,001 entries in groups of about 10
+// / 20 / 64 members: 164 / 181 / 313 us one by one, 174 / 170 / 166 by the merge sort.
+constexpr uint32_t kTieWalk = 16;
 
 struct SortShared {
     uint4 buf[2][kFlushSegment];       // records, two sides; then the rest of the key and the seqno of tied positions
     uint16_t order[kFlushSegment];     // final position -> age
+    uint16_t other[kFlushSegment];     // second side of the merge sort of tied positions
     uint32_t wave_count[kSortThreads / kWave];
     alignas(4) uint8_t flag[kFlushSegment + 8];  // sorted position: 1 = same 14 bytes as the one before
     alignas(4) uint8_t lose[kFlushSegment];      // final position: 1 = shadowed
@@ -168,6 +175,77 @@ __device__ __forceinline__ void rec_order(Rec& a, Rec& b) {
 // where position p sits in the 16-byte arrays: threads own eight consecutive positions (a stride of 128 bytes, one bank
 // quarter), so the positions of a group of eight are permuted by the group's number
 __device__ __forceinline__ uint32_t rec_at(uint32_t p) { return p ^ ((p >> 3) & 7); }
+
+// What orders tied positions: their group (the group's first position, above key bytes 14..15), key bytes 16..31, then the
+// newest version first.
+struct Tied {
+    uint32_t head, age;
+    uint64_t k2, k3, seq;
+};
+__device__ __forceinline__ Tied tied_load(const uint4* info0, const uint4* info1, uint32_t p) {
+    const uint4 a = info0[p], b = info1[p];
+    return Tied{a.z, a.w, __builtin_bswap64(((uint64_t)b.y << 32) | b.x), __builtin_bswap64(((uint64_t)b.w << 32) | b.z), ((uint64_t)a.y << 32) | a.x};
+}
+__device__ __forceinline__ bool tied_same_key(const Tied& a, const Tied& b) { return (a.head == b.head) & (a.k2 == b.k2) & (a.k3 == b.k3); }
+__device__ __forceinline__ bool tied_newer(const Tied& a, const Tied& b) { return a.seq > b.seq || (a.seq == b.seq && a.age < b.age); }
+__device__ __forceinline__ bool tied_less(const Tied& a, const Tied& b) {
+    if (a.head != b.head) return a.head < b.head;
+    if (a.k2 != b.k2) return a.k2 < b.k2;
+    if (a.k3 != b.k3) return a.k3 < b.k3;
+    return tied_newer(a, b);
+}
+
+// Merge sort of all positions of the segment by tied_less, `len` of them in use: s.order[p] becomes the age of the p-th and
+// s.lose[p] whether it is shadowed.  The whole workgroup calls; the info arrays are filled for every position.
+__device__ void flush_sort_tied(SortShared& s, const uint4* info0, const uint4* info1, const uint32_t len) {
+    const uint32_t o = threadIdx.x * kSortItems;
+    uint16_t *from = s.order, *to = s.other;
+    for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
+        const Tied x = tied_load(info0, info1, o + i);
+        uint32_t k = i;
+        for (; k > 0 && tied_less(x, tied_load(info0, info1, from[o + k - 1])); k--) from[o + k] = from[o + k - 1];
+        from[o + k] = (uint16_t)(o + i);
+    }
+    __syncthreads();
+    for (uint32_t width = kSortItems; width < len; width <<= 1) {
+        const uint32_t sa = o & ~(2 * width - 1), sb = sa + width, d = o - sa;
+        uint32_t lo = d > width ? d - width : 0, hi = min(d, width);
+        while (lo < hi) {
+            const uint32_t mid = (lo + hi) >> 1;
+            if (tied_less(tied_load(info0, info1, from[sa + mid]), tied_load(info0, info1, from[sb + (d - 1 - mid)]))) lo = mid + 1;
+            else hi = mid;
+        }
+        uint32_t a = lo, b = d - lo;
+        Tied x = {}, y = {};
+        if (a < width) x = tied_load(info0, info1, from[sa + a]);
+        if (b < width) y = tied_load(info0, info1, from[sb + b]);
+        for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
+            if (b >= width || (a < width && tied_less(x, y))) {
+                to[o + i] = from[sa + a];
+                if (++a < width) x = tied_load(info0, info1, from[sa + a]);
+            } else {
+                to[o + i] = from[sb + b];
+                if (++b < width) y = tied_load(info0, info1, from[sb + b]);
+            }
+        }
+        __syncthreads();
+        uint16_t* const swap = from;
+        from = to;
+        to = swap;
+    }
+    uint16_t age[kSortItems];
+    Tied prev = tied_load(info0, info1, from[o > 0 ? o - 1 : 0]);
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++) {
+        const Tied x = tied_load(info0, info1, from[o + i]);
+        age[i] = (uint16_t)x.age;
+        s.lose[o + i] = o + i > 0 && tied_same_key(prev, x) ? 1 : 0;
+        prev = x;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kSortItems; i++) s.order[o + i] = age[i];
+}
 
 __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entry_t* buffer, uint32_t n, lsm_entry_t* out, uint64_t* counts) {
     __shared__ SortShared s;
@@ -254,47 +332,65 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
     }
     if (tid == 0) s.flag[kFlushSegment] = 0;
     if (__syncthreads_or(any)) {
+        // where the group of every position starts: the last position without a flag up to it
+        uint32_t start[kSortItems], last = 0;
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) last = s.flag[o + i] == 0 ? o + i : last;
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t v = __shfl_up(last, off, kWave);
+            if ((int)(tid & (kWave - 1)) >= off) last = max(last, v);
+        }
+        if ((tid & (kWave - 1)) == kWave - 1) s.wave_count[tid / kWave] = last;
+        last = __shfl_up(last, 1, kWave);
+        if ((tid & (kWave - 1)) == 0) last = 0;
+        __syncthreads();
+        for (uint32_t w = 0; w < tid / kWave; w++) last = max(last, s.wave_count[w]);
+        bool deep = false;
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) {
+            last = s.flag[o + i] == 0 ? o + i : last;
+            start[i] = last;
+            deep = deep || o + i - last >= kTieWalk;
+        }
+        deep = __syncthreads_or(deep) != 0;
         // members of groups post the rest of their key, seqno and age at their sorted position
-        uint4* info0 = s.buf[0];  // {seqno, key bytes 14..15, age}
+        uint4* info0 = s.buf[0];  // {seqno, group and key bytes 14..15, age}
         uint4* info1 = s.buf[1];  // key bytes 16..31
 #pragma unroll
         for (int i = 0; i < kSortItems; i++) {
-            const uint32_t p = o + i;
+            const uint32_t p = o + i, age = (uint32_t)c[i].lo & 0xFFFF;
             if (p < len && (s.flag[p] | s.flag[p + 1]) != 0) {
-                const uint32_t age = (uint32_t)c[i].lo & 0xFFFF;
                 const uint4* e = reinterpret_cast<const uint4*>(src + (len - 1 - age));
                 const uint4 k0 = e[0], meta = e[2];
-                info0[p] = make_uint4(meta.x, meta.y, __builtin_bswap32(k0.w) & 0xFFFF, age);
+                info0[p] = make_uint4(meta.x, meta.y, (start[i] << 16) | (__builtin_bswap32(k0.w) & 0xFFFF), age);
                 info1[p] = e[1];
+            } else if (deep) {
+                info0[p] = make_uint4(0, 0, p << 16, age);
+                info1[p] = make_uint4(0, 0, 0, 0);
             }
         }
         __syncthreads();
-        for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
-            const uint32_t p = o + i;
-            if (p >= len || (s.flag[p] | s.flag[p + 1]) == 0) continue;
-            uint32_t start = p;
-            while (s.flag[start] != 0) start--;  // flag[0] is 0
-            const uint4 a0 = info0[p], a1 = info1[p];
-            const uint64_t seq = ((uint64_t)a0.y << 32) | a0.x;
-            const uint64_t t2 = __builtin_bswap64(((uint64_t)a1.y << 32) | a1.x), t3 = __builtin_bswap64(((uint64_t)a1.w << 32) | a1.z);
-            uint32_t rank = 0;
-            bool shadowed = false;
-            uint32_t q = start;
-            do {
-                if (q != p) {
-                    const uint4 b0 = info0[q], b1 = info1[q];
-                    const uint64_t oseq = ((uint64_t)b0.y << 32) | b0.x;
-                    const uint64_t u2 = __builtin_bswap64(((uint64_t)b1.y << 32) | b1.x), u3 = __builtin_bswap64(((uint64_t)b1.w << 32) | b1.z);
-                    const bool same = b0.z == a0.z && u2 == t2 && u3 == t3;
-                    const bool less = b0.z != a0.z ? b0.z < a0.z : (u2 != t2 ? u2 < t2 : u3 < t3);
-                    const bool newer = same && (oseq > seq || (oseq == seq && b0.w < a0.w));
-                    shadowed = shadowed || newer;
-                    rank += (same ? newer : less) ? 1 : 0;
-                }
-                q++;
-            } while (s.flag[q] != 0);  // flag[len ..] is 0
-            s.order[start + rank] = (uint16_t)a0.w;
-            s.lose[start + rank] = shadowed ? 1 : 0;
+        if (deep) {
+            flush_sort_tied(s, info0, info1, len);
+        } else {
+            for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
+                const uint32_t p = o + i;
+                if (p >= len || (s.flag[p] | s.flag[p + 1]) == 0) continue;
+                const Tied a = tied_load(info0, info1, p);
+                const uint32_t first_member = a.head >> 16;
+                uint32_t rank = 0, q = first_member;
+                bool shadowed = false;
+                do {
+                    if (q != p) {
+                        const Tied b = tied_load(info0, info1, q);
+                        shadowed = shadowed || (tied_same_key(a, b) && tied_newer(b, a));
+                        rank += tied_less(b, a) ? 1 : 0;
+                    }
+                    q++;
+                } while (s.flag[q] != 0);  // flag[len ..] is 0
+                s.order[first_member + rank] = (uint16_t)a.age;
+                s.lose[first_member + rank] = shadowed ? 1 : 0;
+            }
         }
         __syncthreads();
     }

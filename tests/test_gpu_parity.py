@@ -753,6 +753,65 @@ def test_flush_of_keys_with_common_prefixes(g, oracle, n, shared):
     assert np.array_equal(as_bytes(out[: want.shape[0]]).reshape(-1, 64), want)
 
 
+WALK = 16  # members up to which a segment's groups of equal 14-byte prefixes are settled one position at a time
+
+
+@pytest.mark.parametrize("sizes", [[WALK - 1, WALK, 1, 2], [WALK + 1, 1, 2, 3], [WALK, 200, 1, 5], [4096], [8192 + WALK], [8192 + WALK + 1], [700, 1300, 90]])
+@pytest.mark.parametrize("kind", ["versions", "tails", "both"])
+def test_flush_of_groups_of_equal_prefixes(g, oracle, sizes, kind):
+    """Groups of entries that share the 14 bytes a segment is sorted by first, around the size at which they are sorted
+    instead of compared one by one: versions of one key, keys that differ further on, both; sequence numbers in no order."""
+    print("flush, groups", sizes, kind, flush=True)
+    rs = np.random.RandomState(sum(sizes))
+    n = max(8193 + 77, sum(sizes))
+    heads = np.repeat(np.arange(len(sizes)), sizes)
+    heads = np.concatenate([heads, len(sizes) + np.arange(n - heads.size)])[rs.permutation(n)]
+    a = np.zeros((n, 64), dtype=np.uint8)
+    a[:, :8] = heads.astype(">u8").view(np.uint8).reshape(n, 8)
+    if kind != "versions":
+        a[:, 14 + rs.randint(0, 18, size=n)[0]] = rs.randint(0, 5, size=n)
+        a[:, 20] = rs.randint(0, 256 if kind == "tails" else 2, size=n)
+    rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+    rec["seqno"] = rs.randint(0, 1 << 40, size=n) if kind == "versions" else rs.randint(0, 3, size=n)
+    rec["vptr"] = np.arange(n)
+    out, n_out = g.lsm_flush_buffer(to_dev(a))
+    torch.cuda.synchronize()
+    want = oracle.flush_buffer(a)
+    assert int(n_out.item()) == want.shape[0]
+    assert np.array_equal(as_bytes(out[: want.shape[0]]).reshape(-1, 64), want)
+
+
+def _best_us(call, passes=5, reps=5):
+    """Shortest mean time of `reps` calls, in us."""
+    call()
+    best = float("inf")
+    for _ in range(passes):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        for _ in range(reps):
+            call()
+        t1.record()
+        t1.synchronize()
+        best = min(best, t0.elapsed_time(t1) / reps * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("kind", ["one key", "prefixes"])
+def test_flush_of_hot_keys_is_not_quadratic(g, oracle, kind):
+    """A buffer of versions of one key, or of keys with a common prefix, takes at most five times as long as one of
+    scattered keys: two sorts of every segment instead of one, of longer records.  (Comparing every entry of a segment
+    with every other takes more than a hundred times as long.)"""
+    rs = np.random.RandomState(5)
+    spread = torch.from_numpy(rs.randint(0, 1 << 62, size=(20_000, 8))).to(dev())
+    spread[:, 5] = 0
+    hot = spread.clone()
+    hot[:, :4 if kind == "one key" else 2] = 0
+    out, n_out = torch.empty_like(hot), torch.zeros(1, dtype=torch.int64, device=dev())
+    base, took = [_best_us(lambda: g.lsm_flush_buffer(buf, out, n_out)) for buf in (spread, hot)]
+    print(f"flush of 20,000 entries: {base:.0f} us, {kind} {took:.0f} us", flush=True)
+    assert took < 5 * base
+
+
 # ------------------------------------------------------------------ range lookups (section 2.2, appendix B get_batch)
 def test_range_scan_equals_filtered_compaction(g, oracle, cfg1):
     """Entries of a key range, newest version of each, live only = the checker's last-level compaction of all runs
