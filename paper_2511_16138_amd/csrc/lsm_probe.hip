@@ -32,7 +32,8 @@ struct TreeTable {
     uint32_t n_runs;
 };
 
-constexpr int kProbeThreads = 512;
+constexpr int kProbeThreads = 512;       // threads of a workgroup; kProbeThreadsFew: see threads_for
+constexpr int kProbeThreadsFew = 256;
 constexpr int kProbeWays = 3;     // fan-out of a search step in global memory (measured: 2: 0.072 ms per batch, 3: 0.067, 4: 0.069, 6: 0.074, 8: 0.080)
 constexpr int kTopSlots = 1024;  // top-level fence keys held in LDS per workgroup (32 KB)
 
@@ -71,7 +72,7 @@ __device__ __forceinline__ int compare_key(const Key& q, uint4 lo, LoadHi load_h
 // Copies the run descriptors and, with kTop, the top-level fence table into LDS (all threads of the workgroup call this).
 // Without the table (every run has a hash index, so the fences are only searched for keys of crowded buckets) a fence
 // search starts from the whole fence array.
-template <bool kTop>
+template <bool kTop, int kThreads>
 __device__ __forceinline__ void probe_setup(ProbeShared<kTop>& s, const TreeTable& tree, const int tid) {
     const uint32_t n_runs = tree.n_runs;
     // ---- top-level fence table: an equal share of the slots for every run
@@ -92,7 +93,7 @@ __device__ __forceinline__ void probe_setup(ProbeShared<kTop>& s, const TreeTabl
     }
     __syncthreads();
     if (kTop) {
-        for (uint32_t slot = tid; slot < share * n_runs; slot += kProbeThreads) {
+        for (uint32_t slot = tid; slot < share * n_runs; slot += kThreads) {
             const uint32_t r = slot / share, i = slot - r * share;
             if (i < s.n_top[r]) {
                 const uint4* f = reinterpret_cast<const uint4*>(tree.run[r].fences + (uint64_t)i * s.top_stride[r] * LSM_KEY_BYTES);
@@ -298,15 +299,15 @@ __device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const T
 // longest request: some 16 us per 64 keys looked up one after the other.  With more waves per request the chain is shorter,
 // and the keys behind the first miss that are then looked up for nothing cost reads, but no time as long as there is room
 // for the waves (spread_for).
-template <bool kTop, int kSpread>
-__global__ void __launch_bounds__(kProbeThreads) probe_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks,
-                                                               uint32_t n_req, uint32_t max_blocks, uint32_t* hit_len,
-                                                               lsm_hit_t* hits) {
+template <bool kTop, int kSpread, int kThreads>
+__global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks,
+                                                          uint32_t n_req, uint32_t max_blocks, uint32_t* hit_len,
+                                                          lsm_hit_t* hits) {
     __shared__ ProbeShared<kTop> s;
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-    constexpr uint32_t kRequests = kProbeThreads / kWave / kSpread;  // requests a workgroup handles at a time
+    constexpr uint32_t kRequests = kThreads / kWave / kSpread;  // requests a workgroup handles at a time
     const uint32_t n_runs = tree.n_runs;
-    probe_setup<kTop>(s, tree, (int)tid);
+    probe_setup<kTop, kThreads>(s, tree, (int)tid);
     const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
     bool any_filter = false;  // a Bloom filter or a hash index
     for (uint32_t r = 0; r < n_runs; r++) any_filter = any_filter || tree.run[r].bloom_blocks != 0 || tree.run[r].index != nullptr;
@@ -353,19 +354,19 @@ __global__ void __launch_bounds__(kProbeThreads) probe_kernel(TreeTable tree, co
 // lookup of every block key: valid when the tree is prefix-closed (block j of a request live => blocks 0..j-1
 // live).  One wave per request, two rounds: 64 evenly spaced blocks, then the blocks between the last live and the
 // first dead one of those.
-template <bool kTop>
-__global__ void __launch_bounds__(kProbeThreads) probe_length_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks,
-                                                                      uint32_t n_req, uint32_t max_blocks, uint32_t* hit_len) {
+template <bool kTop, int kThreads>
+__global__ void __launch_bounds__(kThreads) probe_length_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks,
+                                                                 uint32_t n_req, uint32_t max_blocks, uint32_t* hit_len) {
     __shared__ ProbeShared<kTop> s;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const uint32_t n_runs = tree.n_runs;
-    probe_setup<kTop>(s, tree, tid);
+    probe_setup<kTop, kThreads>(s, tree, tid);
     const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
     bool any_filter = false;  // a Bloom filter or a hash index
     for (uint32_t r = 0; r < n_runs; r++) any_filter = any_filter || tree.run[r].bloom_blocks != 0 || tree.run[r].index != nullptr;
-    const uint32_t waves = gridDim.x * (kProbeThreads / kWave);
-    for (uint32_t req = blockIdx.x * (kProbeThreads / kWave) + tid / kWave; req < n_req; req += waves) {
+    const uint32_t waves = gridDim.x * (kThreads / kWave);
+    for (uint32_t req = blockIdx.x * (kThreads / kWave) + tid / kWave; req < n_req; req += waves) {
         uint32_t nb = n_blocks[req];
         if (nb > max_blocks) nb = max_blocks;
         const uint8_t* qrow = qkeys + (uint64_t)req * max_blocks * LSM_KEY_BYTES;
@@ -485,14 +486,14 @@ static int make_tree_table(const lsm_tree_t* tree, lsm::TreeTable& tt) {
     return LSM_OK;
 }
 
-// Workgroups for n_req requests of `spread` waves each: at most four per compute unit (32 waves), each striding over the
+// Workgroups of `threads` for n_req requests of `spread` waves each: at most four per compute unit, each striding over the
 // requests.
-static int probe_grid(uint32_t n_req, uint32_t spread, uint32_t& blocks) {
+static int probe_grid(uint32_t n_req, uint32_t spread, int threads, uint32_t& blocks) {
     int device = 0, cus = 0;
     if (hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
         return LSM_ERR_HIP;
-    const uint32_t per_block = lsm::kProbeThreads / lsm::kWave / spread;
+    const uint32_t per_block = threads / lsm::kWave / spread;
     blocks = (n_req + per_block - 1) / per_block;
     if (blocks > (uint32_t)cus * 4) blocks = (uint32_t)cus * 4;
     return LSM_OK;
@@ -500,7 +501,10 @@ static int probe_grid(uint32_t n_req, uint32_t spread, uint32_t& blocks) {
 
 // Waves per request: four up to 512 requests, two up to 2,048 (about 4,096 waves, half of what the chip holds; beyond, the
 // lookups behind the first miss cost more than the shorter chains save).  100M-entry tree with filters, one / two / four
-// waves: 64 requests 29 / 21 / 20 us, 512: 38 / 26 / 26, 1,024: 44 / 29 / 30, 2,048: 48 / 35 / 51, 4,096: 55 / 64 / 92.
+// waves: 64 requests 29 / 21 / 20 us, 512: 38 / 26 / 26, 1,024: 44 / 29 / 30, 2,048: 48 / 35 / 51, 4,096: 55 / 64 / 92.  Without
+// filters, where a key behind the first miss is searched in every run: 64 / 39 / 37, 71 / 43 / 41, 74 / 47 / 49, 80 / 59 / 92,
+// 93 / 114 / 172; hash indices only: 35 / 25 / 25, 45 / 30 / 31, 47 / 34 / 38, 53 / 45 / 64, 69 / 80 / 119.  The lines lie in the
+// same place, so the rule does not look at what the runs carry.
 static uint32_t spread_for(uint32_t n_req, uint32_t max_blocks) {
     uint32_t most = 1;
     while (most < 4 && most * lsm::kWave < max_blocks) most *= 2;  // no more than the longest request has use for
@@ -508,15 +512,33 @@ static uint32_t spread_for(uint32_t n_req, uint32_t max_blocks) {
     return spread < most ? spread : most;
 }
 
+// Threads of a workgroup.  A batch of up to 1,024 requests of one wave each does not fill a workgroup of 512 for every compute
+// unit: shorter ones put the waves on more of them.  Beyond, the fence tables copied into LDS are what the longer ones halve.
+// 256 / 512 threads, prefix length on 100M entries without filters: 16 requests 51.5 / 59.2 us, 256: 62.5 / 66.6, 1,024:
+// 67.9 / 71.0, 1,536: 74.7 / 74.4; with hash indices, 512: 34.8 / 37.9; rows of 64 keys with filters, 256: 25.5 / 27.1, 1,536:
+// 29.9 / 28.7, 4,096: 39.8 / 38.2.
+static int threads_for(uint32_t n_req, uint32_t spread) { return spread == 1 && n_req <= 1024 ? lsm::kProbeThreadsFew : lsm::kProbeThreads; }
+
 template <bool kTop>
-static void launch_probe(uint32_t spread, uint32_t blocks, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits, hipStream_t stream) {
+static void launch_probe(uint32_t spread, int threads, uint32_t blocks, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits,
+                         hipStream_t stream) {
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(lsm::kProbeThreads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req, queries->max_blocks,
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req, queries->max_blocks,
                            out_hits->hit_len, out_hits->hits);
     };
-    if (spread == 4) launch(lsm::probe_kernel<kTop, 4>);
-    else if (spread == 2) launch(lsm::probe_kernel<kTop, 2>);
-    else launch(lsm::probe_kernel<kTop, 1>);
+    if (spread == 4) launch(lsm::probe_kernel<kTop, 4, lsm::kProbeThreads>);
+    else if (spread == 2) launch(lsm::probe_kernel<kTop, 2, lsm::kProbeThreads>);
+    else if (threads == lsm::kProbeThreads) launch(lsm::probe_kernel<kTop, 1, lsm::kProbeThreads>);
+    else launch(lsm::probe_kernel<kTop, 1, lsm::kProbeThreadsFew>);
+}
+
+template <bool kTop>
+static void launch_probe_length(int threads, uint32_t blocks, const lsm::TreeTable& tt, const lsm_queries_t* queries, uint32_t* hit_len, hipStream_t stream) {
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req, queries->max_blocks, hit_len);
+    };
+    if (threads == lsm::kProbeThreads) launch(lsm::probe_length_kernel<kTop, lsm::kProbeThreads>);
+    else launch(lsm::probe_length_kernel<kTop, lsm::kProbeThreadsFew>);
 }
 
 extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, const lsm_hits_t* out_hits, void* stream) {
@@ -532,10 +554,11 @@ extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, c
     uint32_t blocks = 0;
     int rc = make_tree_table(tree, tt);
     const uint32_t spread = spread_for(queries->n_req, queries->max_blocks);
-    if (rc == LSM_OK) rc = probe_grid(queries->n_req, spread, blocks);
+    const int threads = threads_for(queries->n_req, spread);
+    if (rc == LSM_OK) rc = probe_grid(queries->n_req, spread, threads, blocks);
     if (rc != LSM_OK) return rc;
-    if (all_indexed(tt)) launch_probe<false>(spread, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
-    else launch_probe<true>(spread, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    if (all_indexed(tt)) launch_probe<false>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    else launch_probe<true>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 
@@ -549,14 +572,11 @@ extern "C" int lsm_probe_length(const lsm_queries_t* queries, const lsm_tree_t* 
     TreeTable tt;
     uint32_t blocks = 0;
     int rc = make_tree_table(tree, tt);
-    if (rc == LSM_OK) rc = probe_grid(queries->n_req, 1, blocks);
+    const int threads = threads_for(queries->n_req, 1);
+    if (rc == LSM_OK) rc = probe_grid(queries->n_req, 1, threads, blocks);
     if (rc != LSM_OK) return rc;
-    if (all_indexed(tt))
-        hipLaunchKernelGGL(probe_length_kernel<false>, dim3(blocks), dim3(kProbeThreads), 0, static_cast<hipStream_t>(stream), tt, queries->keys,
-                           queries->n_blocks, queries->n_req, queries->max_blocks, hit_len);
-    else
-        hipLaunchKernelGGL(probe_length_kernel<true>, dim3(blocks), dim3(kProbeThreads), 0, static_cast<hipStream_t>(stream), tt, queries->keys,
-                           queries->n_blocks, queries->n_req, queries->max_blocks, hit_len);
+    if (all_indexed(tt)) launch_probe_length<false>(threads, blocks, tt, queries, hit_len, static_cast<hipStream_t>(stream));
+    else launch_probe_length<true>(threads, blocks, tt, queries, hit_len, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 

@@ -417,6 +417,23 @@ def test_probe_batches_of_all_sizes(g, oracle, cfg1, n_req, row):
     assert_probe_equal(oracle, probe_gpu(g, q, nb, build_tree(g, cfg1.runs)), want)
 
 
+@pytest.mark.parametrize("n_req", [1024, 1025])  # one wave per request: workgroups of 256 threads up to 1,024 requests, of 512 beyond
+@pytest.mark.parametrize("indexed", [False, True])
+def test_probe_workgroup_sizes(g, oracle, cfg1, n_req, indexed):
+    """lsm_probe with rows of at most 64 keys and lsm_probe_length on both sides of the line, with and without the fence
+    table in LDS."""
+    from workloads import lsm
+    print("probe workgroups", n_req, indexed, flush=True)
+    q, nb = lsm.queries_config1(cfg1, n_req)
+    q, nb = q[:, :64].contiguous(), nb.clamp(max=64)
+    tree = build_tree(g, cfg1.runs)
+    if indexed:
+        tree = [g.TreeRun(t.run, t.fences, t.stride, t.level, None, g.lsm_build_hash_index(g.lsm_hash_keys(t.run))) for t in tree]
+    want = oracle.probe(q, nb, [r.cpu() for r in cfg1.runs])
+    assert_probe_equal(oracle, probe_gpu(g, q, nb, tree), want)
+    assert np.array_equal(g.lsm_probe_length(q, nb, tree).cpu().numpy().astype(np.uint32), want[0])
+
+
 # ------------------------------------------------------------------ Bloom filters
 @pytest.mark.parametrize("bits_per_key", [8, 16])
 def test_bloom_filter_bytes_equal_the_checker(g, oracle, cfg1, bits_per_key):
