@@ -268,6 +268,13 @@ __device__ __forceinline__ void split_two(const lsm_entry_t* a, const uint64_t n
 // the windows that remain more finely.  Once no window is longer than m all bounds are exact.
 // Usually some three gaps per run remain of a window.  Where the runs' keys lie so that less than half of the
 // candidates goes, one pivot is placed exactly (searched in the runs themselves), which halves the widest window.
+// More than 32 runs (kMany): a round has eight records per run and a step one pivot.  Runs that cover different keys then
+// cost a step each where the widest window was the first of many as wide, and a round each where a window's ends were not
+// among its records (a run beyond the answer was known only to within a gap).  The pivot's window is therefore any of those
+// within a quarter of the widest, by a hash of its number and the step, and a window's first and last records are read.  64
+// runs of 65,536 entries in all: one after the other 381 -> 96 us, in turns of 100 entries 415 -> 178, mixed 78 -> 66 (the
+// constant group).  With fewer runs, where a step tries several pivots and a round reads more of a window, the ends cost
+// mixed runs up to 9 % and are left out.
 // ---------------------------------------------------------------------------------------
 // Sum / max over aligned groups of 1, 2, 4, ... 64 lanes; every lane of the wave must call.  Up to 16 lanes by DPP.
 template <typename Op>
@@ -287,6 +294,10 @@ __device__ __forceinline__ uint32_t group_max_u32(uint32_t v, int group) {
     return group_reduce(v, group, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
 }
 
+constexpr uint32_t kFewRuns = 32;
+constexpr int kGapBits = 9;  // fractional bits of a distance between records
+static_assert(kSampledMinTiles * kTileCap <= (1ull << (32 - kGapBits)), "positions in 32 bits");
+
 template <int kPerLane>  // records a lane reads per round
 struct WindowShared {
     ulonglong2 lo[kWave * kPerLane + kWave];  // key bytes 0..15 of record i of window j at j * (m + 1) + i: lists start in different banks
@@ -295,22 +306,28 @@ struct WindowShared {
 
 // The lower bound in run j = lane % group of the key with the largest L <= r.  The whole wave calls; lanes without a run
 // pass len = 0.  Fewer than 2^32 entries in all.
-template <int kPerLane>
+template <int kPerLane, bool kMany>
 __device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, const lsm_entry_t* run, const uint32_t len, const uint32_t r,
-                                                 const int group_log) {
+                                                 const int group_log_any) {
+    const int group_log = kMany ? 6 : group_log_any;
     const int lane = threadIdx.x & (kWave - 1), group = 1 << group_log;
     const uint32_t j = lane & (group - 1), g = (uint32_t)lane >> group_log;
     const int groups_log = 6 - group_log;
     const uint32_t groups = 1u << groups_log, m = groups * kPerLane;
     ulonglong2* const my_lo = s.lo + j * (m + 1);
     ulonglong2* const my_hi = s.hi + j * (m + 1);
-    uint32_t lo = 0, hi = len;
+    uint32_t lo = 0, hi = len, turn = 0;
     for (;;) {
         const uint32_t width = hi - lo;
         const bool exact = __ballot(width > m) == 0;
-        const uint32_t gap = width > m ? width / m : 1;
-        const uint32_t first = lo + (width > m ? gap >> 1 : 0);  // record i of the window is at first + i * gap
         const uint32_t count = width < m ? width : m;
+        // record i of the window
+        const uint32_t gap = width <= m ? 1 << (kMany ? kGapBits : 0) : (kMany ? ((width - 1) << kGapBits) / (m - 1) : width / m);
+        const uint32_t first = lo + (!kMany && width > m ? gap >> 1 : 0);
+        auto position = [&](uint32_t i) {
+            if (kMany) return i + 1 < count ? lo + ((i * gap) >> kGapBits) : hi - 1;
+            return first + i * gap;
+        };
         __syncthreads();  // one wave: the last round's reads are done
         {
             uint4 a[kPerLane], b[kPerLane];
@@ -318,7 +335,7 @@ __device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, cons
             for (int c = 0; c < kPerLane; c++) {
                 const uint32_t i = g + c * groups;
                 if (i < count) {
-                    const uint4* e = reinterpret_cast<const uint4*>(run + first + i * gap);
+                    const uint4* e = reinterpret_cast<const uint4*>(run + position(i));
                     a[c] = load_global_u4(e);
                     b[c] = load_global_u4(e + 1);
                 }
@@ -336,9 +353,15 @@ __device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, cons
         __syncthreads();
         uint32_t left = 0, right = count;         // records of this window that are not settled
         uint32_t next_lo = lo, next_hi = hi;
-        for (;;) {
-            const uint32_t widest = (uint32_t)__builtin_amdgcn_readfirstlane((int)group_max_u32(((right - left) << 6) | j, group));
-            const uint32_t w = widest >> 6, jw = widest & 63;
+        for (;; turn++) {
+            const uint32_t open = right - left;
+            uint32_t order = open;
+            if (kMany && open != 0) {  // length to two bits behind the first, a hash: distinct windows in a different order every step
+                const uint32_t bits = 32 - __builtin_clz(open);
+                order = (((bits << 2) | (((open << 2) >> (bits - 1)) & 3)) << 6) | (((j + turn) * 0x9E3779B1u) >> 26);
+            }
+            const uint32_t chosen = (uint32_t)__builtin_amdgcn_readfirstlane((int)group_max_u32((order << 6) | j, group));
+            const uint32_t jw = chosen & 63, w = kMany ? (uint32_t)__builtin_amdgcn_readlane((int)open, (int)jw) : chosen >> 6;
             if (w == 0) break;
             const uint32_t from = (uint32_t)__builtin_amdgcn_readlane((int)left, (int)jw);
             const uint32_t at_w = from + (w >= groups ? ((2 * g + 1) * w) >> (groups_log + 1) : (g < w ? g : w - 1));
@@ -360,9 +383,8 @@ __device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, cons
                 end = less ? end : mid;
                 same = less ? same : equal;
             }
-            const uint32_t at = first + y * gap;
-            const uint32_t xmax = own || y < count ? at : hi;
-            const uint32_t xmin = own ? at : (y > 0 ? at - gap + 1 : lo);
+            const uint32_t xmax = own || y < count ? position(y) : hi;
+            const uint32_t xmin = own ? xmax : (y > 0 ? position(y - 1) + 1 : lo);
             const uint64_t below = __ballot(group_sum_u32(xmax, group) <= r), above = __ballot(group_sum_u32(xmin, group) > r);
             if ((below | above) == 0) break;  // all in doubt
             // the groups' records ascend: the last one that is not above the answer, the first one that is
@@ -480,14 +502,28 @@ __global__ void __launch_bounds__(kTwoThreads) partition_two_kernel(RunTable rt,
 }
 
 // other run counts: one wave per boundary
-template <bool kInit, int kPerLane>
+template <bool kInit, int kPerLane, bool kMany>
 __global__ void __launch_bounds__(kWave) partition_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, int group_log) {
     __shared__ WindowShared<kPerLane> s;
     partition_init<kInit>(rt, ws, n_tiles);
     const uint32_t b = blockIdx.x + 1, lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
-    const uint32_t best = window_split<kPerLane>(s, j < rt.k ? rt.ptr[j] : nullptr, j < rt.k ? (uint32_t)run_len(rt, j) : 0,
-                                                 b * ws.spacing, group_log);
+    const bool own = j < rt.k;
+    const uint32_t best = window_split<kPerLane, kMany>(s, own ? rt.ptr[j] : nullptr, own ? (uint32_t)run_len(rt, j) : 0, b * ws.spacing, group_log);
     if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
+}
+// With many runs and many tiles the records that the waves' rounds read are more than the memory takes (a round of 64 runs is
+// 512 lines of 128 bytes): beyond kWindowPieces pieces of tiles in runs the pivoting selection, whose searches share their
+// first records, is the faster one for mixed runs.  Windows / pivoting: 64 runs, 2M entries 210 / 221 us, 2.5M 258 / 237,
+// 3.9M 573 / 343; 48 runs, 2.5M 233 / 241, 3.2M 320 / 282, 3.9M 354 / 327; 33 runs, 3.9M 312 / 326.  (Runs one after the
+// other the other way round, 64 runs of 3.9M 267 / 565: not what a tree's levels look like.)
+constexpr uint64_t kWindowPieces = 65536;
+template <bool kInit>
+__global__ void __launch_bounds__(kWave) partition_many_kernel(RunTable rt, Workspace ws, uint64_t n_tiles) {
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint32_t b = blockIdx.x + 1, lane = threadIdx.x;
+    const bool own = lane < rt.k;
+    const uint64_t best = select_split<false>(own ? rt.ptr[lane] : nullptr, 0, own ? run_len(rt, lane) : 0, b * (uint64_t)ws.spacing, own, (int)lane, kWave, 0);
+    if (own) ws.splits[(uint64_t)b * rt.k + lane] = best;
 }
 static_assert(kSampledMinTiles * kTileCap < (1ull << 32), "the window search counts in 32 bits");
 
@@ -1342,7 +1378,7 @@ struct BatchInline {
 };
 static_assert(sizeof(BatchInline) <= 2560, "fits the argument segment of a launch beside the rest");
 
-template <int kPerLane, bool kInline>
+template <int kPerLane, bool kMany, bool kInline>
 __global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, ModeArgs ma, int group_log, BatchInline table) {
     __shared__ WindowShared<kPerLane> s;
     uint32_t job = 0;
@@ -1371,7 +1407,7 @@ __global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, Mo
         split_two_wave(run_ptr[d.run_off], run_n[d.run_off], run_ptr[d.run_off + 1], run_n[d.run_off + 1], t * (uint64_t)tile_spacing(ws.spacing, 2), ia, ib);
         best = j == 0 ? ia : ib;
     } else if (t > 0) {
-        best = window_split<kPerLane>(s, run, (uint32_t)len, t * tile_spacing(ws.spacing, d.k), group_log);
+        best = window_split<kPerLane, kMany>(s, run, (uint32_t)len, t * tile_spacing(ws.spacing, d.k), group_log);
     }
     if (lane < d.k) {
         uint64_t* rows = ws.splits + d.splits_off;
@@ -1508,9 +1544,13 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                     hipLaunchKernelGGL(partition_two_kernel<kInit>, dim3((uint32_t)((n_tiles - 1 + kTwoThreads - 1) / kTwoThreads)), dim3(kTwoThreads), 0,
                                        stream, rt, ws, n_tiles);
                 else if (records_per_lane(group_log) == 4)
-                    hipLaunchKernelGGL((partition_kernel<kInit, 4>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+                    hipLaunchKernelGGL((partition_kernel<kInit, 4, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+                else if (n_runs <= kFewRuns || rt.n_dev != nullptr)  // or the segments of a write buffer: mixed, and few tiles (64 of them 144 / 150 us)
+                    hipLaunchKernelGGL((partition_kernel<kInit, 8, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+                else if (n_tiles * n_runs > kWindowPieces)
+                    hipLaunchKernelGGL(partition_many_kernel<kInit>, waves, dim3(kWave), 0, stream, rt, ws, n_tiles);
                 else
-                    hipLaunchKernelGGL((partition_kernel<kInit, 8>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+                    hipLaunchKernelGGL((partition_kernel<kInit, 8, true>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
             };
             if (fused_init) launch(std::true_type{});
             else launch(std::false_type{});
@@ -1840,13 +1880,14 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
     ma.run_n = reinterpret_cast<const uint64_t*>(base + l.run_n);
     const int group_log = log2_ceil(l.k_max);
     const dim3 waves((uint32_t)l.tiles), wave(kWave);
-    if (records_per_lane(group_log) == 4) {
-        if (fits_inline) hipLaunchKernelGGL((partition_batch_kernel<4, true>), waves, wave, 0, stream, ws, ma, group_log, table);
-        else hipLaunchKernelGGL((partition_batch_kernel<4, false>), waves, wave, 0, stream, ws, ma, group_log, table);
-    } else {
-        if (fits_inline) hipLaunchKernelGGL((partition_batch_kernel<8, true>), waves, wave, 0, stream, ws, ma, group_log, table);
-        else hipLaunchKernelGGL((partition_batch_kernel<8, false>), waves, wave, 0, stream, ws, ma, group_log, table);
-    }
+    auto launch = [&](auto inline_table) {
+        constexpr bool kInline = decltype(inline_table)::value;
+        if (records_per_lane(group_log) == 4) hipLaunchKernelGGL((partition_batch_kernel<4, false, kInline>), waves, wave, 0, stream, ws, ma, group_log, table);
+        else if (l.k_max <= kFewRuns) hipLaunchKernelGGL((partition_batch_kernel<8, false, kInline>), waves, wave, 0, stream, ws, ma, group_log, table);
+        else hipLaunchKernelGGL((partition_batch_kernel<8, true, kInline>), waves, wave, 0, stream, ws, ma, group_log, table);
+    };
+    if (fits_inline) launch(std::true_type{});
+    else launch(std::false_type{});
     RunTable rt = {};
     rt.k = 1;
     if (any_fences)  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)

@@ -376,6 +376,60 @@ def _runs_of(oracle, rs, lens, keys):
     return runs
 
 
+def _best_us(call, passes=5, reps=5):
+    """Shortest mean time of `reps` calls, in us."""
+    call()
+    best = float("inf")
+    for _ in range(passes):
+        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        t0.record()
+        for _ in range(reps):
+            call()
+        t1.record()
+        t1.synchronize()
+        best = min(best, t0.elapsed_time(t1) / reps * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("k,total", [(64, 1024 * 1984), (64, 1024 * 1984 + 1), (33, 200_001)])  # 65,536 pieces of tiles in runs, more
+@pytest.mark.parametrize("shape", ["mixed", "stairs", "one long"])
+def test_many_runs(g, oracle, k, total, shape):
+    """More than 32 runs on both sides of the line where the boundaries' search changes; runs one after the other or one
+    long run must not take the boundaries apart."""
+    print("many runs", k, total, shape, flush=True)
+    rs = np.random.RandomState(k)
+    lens = np.full(k, total // k)
+    if shape == "one long":
+        lens[:] = rs.randint(0, 40, size=k)
+    lens[k // 2] += total - lens.sum()
+    runs = _runs_of(oracle, rs, lens, 2 * total)
+    if shape == "stairs":
+        for j, r in enumerate(runs):  # the keys' first byte, as stored
+            r[:, 0] |= (j * 7) % k + 1
+    _check_compact(g, oracle, runs, 1)
+    if total < 1 << 20:  # a batch of it and a small job
+        few = _runs_of(oracle, rs, [700, 900, 30], 4000)
+        outs, n_out = g.lsm_compact_batch([(runs, 1), (few, 0)])
+        for rr, flags, out, n in zip((runs, few), (1, 0), outs, n_out.tolist()):
+            want = oracle.compact([r.cpu() for r in rr], flags)
+            assert n == want.shape[0]
+            assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
+
+
+def test_many_runs_one_after_the_other_are_not_slow(g, oracle):
+    """64 runs that cover different keys take at most three times as long as 64 mixed ones.  (Trying the records of one run
+    after the other for every boundary took five times as long.)"""
+    rs = np.random.RandomState(8)
+    runs = _runs_of(oracle, rs, [1024] * 64, 1 << 18)
+    apart = [r.clone() for r in runs]
+    for j, r in enumerate(apart):
+        r[:, 0] |= j + 1
+    out, n_out = torch.empty((1 << 16, 8), dtype=torch.int64, device=dev()), torch.zeros(1, dtype=torch.int64, device=dev())
+    base, took = [_best_us(lambda: g.lsm_compact(rr, 0, out, n_out)) for rr in (runs, apart)]
+    print(f"64 runs of 1,024 entries: mixed {base:.0f} us, one after the other {took:.0f} us", flush=True)
+    assert took < 3 * base
+
+
 @pytest.mark.parametrize("k", [1, 2, 3, 16, 64])
 def test_tile_spacing_edges(g, oracle, k):
     """Inputs around the totals where the tile spacing changes: one tile or several, the shortest spacing, one that grows
@@ -796,21 +850,6 @@ def test_flush_of_groups_of_equal_prefixes(g, oracle, sizes, kind):
     want = oracle.flush_buffer(a)
     assert int(n_out.item()) == want.shape[0]
     assert np.array_equal(as_bytes(out[: want.shape[0]]).reshape(-1, 64), want)
-
-
-def _best_us(call, passes=5, reps=5):
-    """Shortest mean time of `reps` calls, in us."""
-    call()
-    best = float("inf")
-    for _ in range(passes):
-        t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        t0.record()
-        for _ in range(reps):
-            call()
-        t1.record()
-        t1.synchronize()
-        best = min(best, t0.elapsed_time(t1) / reps * 1e3)
-    return best
 
 
 @pytest.mark.parametrize("kind", ["one key", "prefixes"])
