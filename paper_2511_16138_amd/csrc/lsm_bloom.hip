@@ -3,6 +3,8 @@
 // OR its six bits into the 16-byte block (two 64-bit atomics at most).  Bits only ever get set, so the result is the same for any order.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "lsm_common.h"
 #include "lsm_partition.h"
 
@@ -114,8 +116,12 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
 
 // The runs of `jobs`, all with small filters; `cleared`: the filters are known to be all zero.  A thread hashes one key
 // (hashing is some 800 cycles a key and wave: four per thread took 11 us where one takes 6), or two when one would be
-// more than a workgroup of them for every compute unit (16 x 30,000 keys: 19 us against 22).
-static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, bool cleared, hipStream_t stream) {
+// more than a workgroup of them for every compute unit (16 x 30,000 keys: 19 us against 22).  On memory that is not zero,
+// shares are two launches, and up to `one_launch` keys a workgroup takes a whole run: 2,500 keys 5.0 us against 7.0, 4,096 6.9
+// against 7.0, 5,000 8.2 against 7.1.  Calls for many runs are bound by the host, which the second launch costs 2.5 us (one run
+// of 5,000 keys 8.7 against 11.4, of 8,192 12.1 against 12.4).
+constexpr uint64_t kOneLaunch = 4 * kBloomSmallThreads, kOneLaunchBatch = 8 * kBloomSmallThreads;
+static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, bool cleared, uint64_t one_launch, hipStream_t stream) {
     uint64_t most_keys = 0, all_keys = 0;
     uint32_t most_blocks = 0;
     for (uint32_t j = 0; j < count; j++) {
@@ -123,15 +129,23 @@ static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, bool clear
         most_blocks = jobs.n_blocks[j] > most_blocks ? jobs.n_blocks[j] : most_blocks;
         all_keys += jobs.n[j];
     }
-    const bool two = all_keys > 256ull * kBloomSmallThreads || (most_keys > kBloomSmallThreads && most_keys <= 2 * kBloomSmallThreads);
-    const uint64_t share = (two ? 2 : 1) * (uint64_t)kBloomSmallThreads;
+    int ahead = all_keys > 256ull * kBloomSmallThreads || (most_keys > kBloomSmallThreads && most_keys <= 2 * kBloomSmallThreads) ? 2 : 1;
+    if (!cleared && most_keys > 2 * kBloomSmallThreads && most_keys <= one_launch) ahead = most_keys <= 4 * kBloomSmallThreads ? 4 : 8;
+    const uint64_t share = ahead * (uint64_t)kBloomSmallThreads;
     const dim3 grid(most_keys ? (uint32_t)((most_keys + share - 1) / share) : 1, count), threads(kBloomSmallThreads);
-    if (grid.x > 1 && !cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
-    const bool large = most_blocks > kBloomSmallBlocks / 2;
-    if (large && two) hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks, 2>), grid, threads, 0, stream, jobs);
-    else if (large) hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks, 1>), grid, threads, 0, stream, jobs);
-    else if (two) hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks / 2, 2>), grid, threads, 0, stream, jobs);
-    else hipLaunchKernelGGL((bloom_small_kernel<kBloomSmallBlocks / 2, 1>), grid, threads, 0, stream, jobs);
+    if (grid.x > 1 && !cleared && count == 1)  // the smaller argument block: 1 us of the host's time
+        hipLaunchKernelGGL(bloom_clear_kernel, dim3((most_blocks + 255) / 256), dim3(256), 0, stream, reinterpret_cast<uint4*>(jobs.words[0]), (uint64_t)most_blocks);
+    else if (grid.x > 1 && !cleared)
+        hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
+    auto launch = [&](auto blocks) {
+        constexpr uint32_t kBlocks = decltype(blocks)::value;
+        if (ahead == 8) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 8>), grid, threads, 0, stream, jobs);
+        else if (ahead == 4) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 4>), grid, threads, 0, stream, jobs);
+        else if (ahead == 2) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 2>), grid, threads, 0, stream, jobs);
+        else hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 1>), grid, threads, 0, stream, jobs);
+    };
+    if (most_blocks > kBloomSmallBlocks / 2) launch(std::integral_constant<uint32_t, kBloomSmallBlocks>{});
+    else launch(std::integral_constant<uint32_t, kBloomSmallBlocks / 2>{});
 }
 
 // ---------------------------------------------------------------------------------------
@@ -232,7 +246,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
         jobs.n[0] = run->n;
         jobs.words[0] = static_cast<uint32_t*>(filter_out);
         jobs.n_blocks[0] = (uint32_t)n_blocks;
-        launch_bloom_small(jobs, 1, false, stream);
+        launch_bloom_small(jobs, 1, false, kOneLaunch, stream);
         return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
     uint64_t clear_blocks = (n_blocks + 255) / 256;
@@ -257,7 +271,7 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
         for (uint32_t j = 0; j <= n_runs; j++) {
             if (count == kBloomBatch || (j == n_runs && count > 0)) {
                 if (large == 0) {
-                    launch_bloom_small(jobs, count, cleared, stream);
+                    launch_bloom_small(jobs, count, cleared, kOneLaunchBatch, stream);
                 } else {
                     uint64_t cx = (most_blocks + 255) / 256, ix = (most_entries + 255) / 256;
                     if (cx > 1024) cx = 1024;

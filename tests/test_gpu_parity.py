@@ -719,6 +719,24 @@ def test_filter_and_index_at_the_edges_of_their_builds(g, oracle, n):
     assert oracle.hash_index_check(run.cpu(), table.cpu().numpy()) == 0
 
 
+@pytest.mark.parametrize("n", [2048, 2049, 4095, 4097, 8192, 8193])  # keys per thread: two, four, shares; in a batch eight up to 8,192
+@pytest.mark.parametrize("bits", [3, 16, 64])                        # 64: filters of more than 64 KiB from 8,192 keys on
+def test_short_filters_in_one_launch(g, oracle, n, bits):
+    from workloads import lsm
+    print("short filters", n, bits, flush=True)
+    run = torch.cat([r for r in lsm.config3(device=dev(), scale=1024).runs])[:n].contiguous()
+    assert int(run.shape[0]) == n
+    blocks = g.lsm_bloom_blocks(n, bits)
+    want = oracle.build_bloom(run.cpu(), blocks)
+    got = g.lsm_build_bloom(run, bits, out=torch.full((blocks, 4), -1, dtype=torch.int32, device=dev()))
+    rows = torch.full((3 * blocks, 4), -1, dtype=torch.int32, device=dev())  # what the allocations below start with
+    del rows
+    batch = g.lsm_build_bloom_batch([run, run[:1], run], bits)
+    torch.cuda.synchronize()
+    for f in (got, batch[0], batch[2], g.lsm_build_bloom_batch([run], bits)[0]):
+        assert np.array_equal(as_bytes(f).reshape(-1, 16), want)
+
+
 # ------------------------------------------------------------------ prefix length by search (appendix B)
 def test_probe_length_equals_probe_on_prefix_closed_data(g, oracle, cfg1):
     """The generator evicts leaf first, so its trees are prefix-closed: the search over the prefix length gives the
