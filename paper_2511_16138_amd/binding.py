@@ -144,7 +144,7 @@ def _load(path: Optional[str] = None) -> C.CDLL:
     L.lsm_build_bloom.restype = C.c_int
     L.lsm_build_bloom.argtypes = [C.POINTER(_Run), C.c_void_p, C.c_uint64, C.c_void_p]
     L.lsm_build_bloom_batch.restype = C.c_int
-    L.lsm_build_bloom_batch.argtypes = [C.POINTER(_Run), C.POINTER(C.c_void_p), C.POINTER(C.c_uint64), C.c_uint32, C.c_void_p]
+    L.lsm_build_bloom_batch.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, C.c_uint32, C.c_void_p]  # arrays, as flat words
     L.lsm_bloom_workspace_bytes.restype = C.c_size_t
     L.lsm_bloom_workspace_bytes.argtypes = [C.c_uint64, C.c_uint64]
     L.lsm_hash_keys.restype = C.c_int
@@ -486,8 +486,7 @@ def lsm_build_bloom_batch(runs: Sequence[torch.Tensor], bits_per_key: int = 16, 
     for b in blocks:
         ptrs.append(at)
         at += 16 * b
-    rc = L.lsm_build_bloom_batch(C.cast(_words(words), C.POINTER(_Run)), C.cast(_words(ptrs), C.POINTER(C.c_void_p)), _words(blocks), len(runs),
-                                 _stream_ptr(stream))
+    rc = L.lsm_build_bloom_batch(_words(words), _words(ptrs), _words(blocks), len(runs), _stream_ptr(stream))
     if rc != 0:
         raise LsmError(rc, "lsm_build_bloom_batch")
     return outs
