@@ -324,8 +324,9 @@ int lsm_build_bloom_batch(const lsm_run_t* runs, void* const* filters_out, const
  * read-modify-write traffic on the filter (section 2.2 has every new run carry a filter, so the build is part
  * of every compaction's cost).  lsm_hash_keys writes hashes_out[i] = h of entry i's key (the h of lsm_bloom_t;
  * DEVICE, 8-byte aligned, run->n values); lsm_compact can write the same values for its output in its own
- * pass (lsm_out_t.key_hashes).  lsm_build_bloom_hashed sorts the n hashes into ranges of 4,096 filter blocks
- * inside the workspace, builds each range in on-chip memory and writes it once; filter_out as for
+ * pass (lsm_out_t.key_hashes).  lsm_build_bloom_hashed sorts the n hashes into ranges of 256 to 4,096 filter blocks
+ * inside the workspace (up to 65,536 hashes are not sorted), builds each range in on-chip memory and writes it once;
+ * filter_out as for
  * lsm_build_bloom and with the same bytes as its result.  The hashes are only read.
  * lsm_bloom_workspace_bytes(n, n_blocks): bytes the build needs (DEVICE, 256-byte aligned, about 8 n), or 0
  * when it does not apply (n >= 2^32, n_blocks == 0 or more than 2^25 blocks: use lsm_build_bloom).
@@ -340,8 +341,8 @@ int lsm_build_bloom_hashed(const uint64_t* hashes, uint64_t n, void* filter_out,
  * lsm_build_hash_index -- the hash index of a run (see lsm_hash_index_t) from the filter hashes of its keys in
  * run order (hashes[i] belongs to entry i: from lsm_hash_keys, or from lsm_compact's key_hashes).  buckets_out:
  * DEVICE, 64-byte aligned, lsm_hash_index_buckets(n) x 64 bytes, every byte written.  The hashes are sorted by
- * ranges of 4,096 buckets inside the workspace and every range is filled by one workgroup (no atomic traffic
- * on the table).  lsm_hash_index_workspace_bytes(n): DEVICE, 256-byte aligned, about 16 n bytes; 0 when the
+ * ranges of 256 to 4,096 buckets inside the workspace (up to 65,536 hashes are not sorted) and every range is filled by
+ * one workgroup (no atomic traffic on the table).  lsm_hash_index_workspace_bytes(n): DEVICE, 256-byte aligned, about 16 n bytes; 0 when the
  * build does not apply (n > 2^27).
  * Errors: LSM_ERR_NULL, LSM_ERR_BAD_ARG (misaligned pointers, n too large), LSM_ERR_WORKSPACE, LSM_ERR_HIP.
  */
@@ -546,19 +547,22 @@ int lsm_driver_note_writes(lsm_driver_t* driver, uint64_t n_ops);
  * Neither this call nor lsm_driver_note_writes touches the GPU. */
 int lsm_driver_note_reads(lsm_driver_t* driver, uint64_t successful, uint64_t empty, uint64_t blocks);
 
-/* A sorted run from the write buffer enters level 1; every compaction and move this triggers is done before the call
- * returns.  run: DEVICE, strictly ascending; it is read only by work that the call enqueues on the driver's stream (a
- * run that comes to rest is copied), so the caller may reuse the memory in stream order afterwards. */
+/* A sorted run from the write buffer enters level 1.  When the call returns, every compaction and move this triggers has
+ * been made and its number of entries is known (the host watches for the counts meanwhile); the last stores of a merge, and
+ * the copy, fences and filters of runs that have come to rest, may still be under way on the driver's stream
+ * (lsm_driver_tree waits for them).  run: DEVICE, strictly ascending; it is read only by work that the call enqueues on
+ * the driver's stream (a run that comes to rest is copied), so the caller may reuse the memory in stream order afterwards. */
 int lsm_driver_flush(lsm_driver_t* driver, const lsm_entry_t* run, uint64_t n);
 /* The same for a write buffer as it was filled (any order, repeated keys; n <= LSM_MAX_BUFFER): sorted and reduced to
  * the newest version of every key by lsm_flush_buffer first. */
 int lsm_driver_flush_unsorted(lsm_driver_t* driver, const lsm_entry_t* buffer, uint64_t n);
 
 /* One flush for each of `count` independent trees (key-range shards of one index, or one index per tenant), stepped
- * together: the compactions that the trees' cascades need at the same step go to the GPU as one lsm_compact_batch (the
- * fence indices written in the same pass) and the filters of their outputs as one lsm_build_bloom_batch, until every tree
- * is settled; a compaction of 2^21 entries or more is run on its own.  Every tree ends exactly as after its own
- * lsm_driver_flush.  drivers, runs, n: HOST arrays of `count` elements; runs[i] == NULL = tree i has nothing to flush
+ * together: the compactions that the trees' cascades need at the same step go to the GPU as one batch (the fence indices
+ * written in the same pass); a compaction of 2^21 entries or more is run on its own.  When no tree has a step left, the
+ * flushed runs that have come to rest are copied in one launch and the filters of all short runs built in one.  Every tree
+ * ends exactly as after its own lsm_driver_flush; a failure in one tree ends that tree's steps only, and the first error is
+ * returned.  drivers, runs, n: HOST arrays of `count` elements; runs[i] == NULL = tree i has nothing to flush
  * (an empty write buffer, which is still a flush, is a non-NULL runs[i] with n[i] == 0).
  * The drivers must be distinct and share one stream (LSM_ERR_BAD_ARG otherwise). */
 int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_entry_t* const* runs, const uint64_t* n, uint32_t count);

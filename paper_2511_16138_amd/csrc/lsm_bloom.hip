@@ -1,6 +1,9 @@
-// lsm_build_bloom: blocked Bloom filter of a run (paper section 2.2 names Bloom filters as the structure that
-// lets a lookup skip a run; appendix B uses point lookups in "Probe").  One thread per entry: hash the key,
-// OR its six bits into the 16-byte block (two 64-bit atomics at most).  Bits only ever get set, so the result is the same for any order.
+// lsm_build_bloom and its forms: blocked Bloom filter of a run (paper section 2.2 names Bloom filters as the structure that
+// lets a lookup skip a run; appendix B uses point lookups in "Probe").  A key sets six bits of one 16-byte block.  Bits only
+// ever get set, so every way of building a filter gives the same bytes:
+//   bloom_small_kernel    short runs: shares of the keys in LDS, one launch where the memory is zero or one share is all
+//   bloom_insert_kernel   longer ones from the entries: one thread per key, two 64-bit atomics at most
+//   bloom_fill_kernel     from the keys' hashes, sorted by range of blocks: built in LDS, written once
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

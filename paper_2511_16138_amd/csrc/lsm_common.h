@@ -152,8 +152,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t x) {
     x ^= x >> 31;
     return x;
 }
-// the hash h of a key (its top half picks the block) and the six bits as four 32-bit masks
-// h of a key, and the six bits (as a 128-bit mask) that h selects inside its block
+// the hash h of a key; its top half picks the block
 __device__ __forceinline__ uint64_t bloom_key_hash(const Key& k) {
     uint64_t h = 0x5EED251116138ull;
     for (int i = 0; i < 4; i++) h = mix64(h ^ k.w[i]);

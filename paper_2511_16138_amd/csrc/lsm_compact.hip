@@ -2,17 +2,18 @@
 //
 // Kernels, on one stream:
 //   init_kernel       clears the per-call scratch (tile status words) and writes the
-//                     first and last partition rows (inputs of a few tiles: done by the
-//                     partition launch instead).
-//   partition         one group of lanes per interior tile boundary: multi-sequence selection
-//                     over the k runs.  For target rank r it finds the key x with the largest
+//                     first and last partition rows (inputs of fewer than 2,048 tiles: done by
+//                     the partition launch instead; an input of one tile needs neither).
+//   partition         multi-sequence selection over the k runs for every interior tile
+//                     boundary.  For target rank r it finds the key x with the largest
 //                     L(x) = sum_j |{e in run j : e.key < x}| that is still <= r, and stores
 //                     the k lower bounds.  Boundaries are therefore key-aligned (all versions
 //                     of a key fall into the same tile) and tile sizes are within k of the
-//                     nominal size.  Small inputs search the runs directly (partition_kernel);
-//                     large ones first bracket every boundary on a copy of every 32nd key
-//                     (sample_kernel, sample_coarse_kernel, sample_fine_kernel) and search the
-//                     runs only inside the brackets (bracket_partition_kernel).
+//                     nominal size.  Small inputs search the runs directly, one wave per
+//                     boundary (partition_kernel, partition_two_*, partition_many_kernel); large
+//                     ones first bracket every boundary, a group of lanes each, on a copy of every
+//                     32nd key (sample_kernel, sample_coarse_kernel, sample_fine_kernel) and search
+//                     the runs only inside the brackets (bracket_partition_kernel).
 //   merge_kernel      one workgroup per tile: every thread loads its share of the tile's entries
 //                     into registers, 16-byte surrogates (14 key bytes + index) are merged in LDS
 //                     by ceil(log2 k) rounds of stable two-way merge-path merges, the newest
