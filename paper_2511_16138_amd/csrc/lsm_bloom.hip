@@ -34,20 +34,21 @@ __global__ void bloom_insert_kernel(const lsm_entry_t* entries, uint64_t n, uint
 // The same two steps for up to kBloomBatch runs per launch (blockIdx.y = run), for the many small runs that a round of
 // flushes into several trees produces.
 constexpr uint32_t kBloomBatch = 64;
+template <uint32_t kRuns>
 struct BloomJobs {
-    const lsm_entry_t* entries[kBloomBatch];
-    uint64_t n[kBloomBatch];
-    uint32_t* words[kBloomBatch];
-    uint32_t n_blocks[kBloomBatch];
+    const lsm_entry_t* entries[kRuns];
+    uint64_t n[kRuns];
+    uint32_t* words[kRuns];
+    uint32_t n_blocks[kRuns];
 };
 
-__global__ void bloom_clear_batch_kernel(BloomJobs jobs) {
+__global__ void bloom_clear_batch_kernel(BloomJobs<kBloomBatch> jobs) {
     uint4* blocks = reinterpret_cast<uint4*>(jobs.words[blockIdx.y]);
     const uint64_t n_blocks = jobs.n_blocks[blockIdx.y], stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_blocks; i += stride) blocks[i] = make_uint4(0, 0, 0, 0);
 }
 
-__global__ void bloom_insert_batch_kernel(BloomJobs jobs) {
+__global__ void bloom_insert_batch_kernel(BloomJobs<kBloomBatch> jobs) {
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
     uint32_t* words = jobs.words[blockIdx.y];
     const uint64_t n = jobs.n[blockIdx.y], stride = (uint64_t)gridDim.x * blockDim.x;
@@ -81,8 +82,8 @@ __device__ __forceinline__ void bloom_set_lds(uint32_t* block, uint64_t h) {
 constexpr uint32_t kBloomSmallBlocks = 8192;
 constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a filter is left to the atomics
 constexpr int kBloomSmallThreads = 1024;
-template <uint32_t kBlocks, int kAhead>
-__global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs jobs) {
+template <uint32_t kBlocks, int kAhead, uint32_t kRuns>
+__global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs<kRuns> jobs) {
     __shared__ uint4 blocks[kBlocks];
     uint32_t* f = reinterpret_cast<uint32_t*>(blocks);
     uint64_t* words = reinterpret_cast<uint64_t*>(blocks);
@@ -124,7 +125,8 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
 // against 7.0, 5,000 8.2 against 7.1.  Calls for many runs are bound by the host, which the second launch costs 2.5 us (one run
 // of 5,000 keys 8.7 against 11.4, of 8,192 12.1 against 12.4).
 constexpr uint64_t kOneLaunch = 4 * kBloomSmallThreads, kOneLaunchBatch = 8 * kBloomSmallThreads;
-static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, bool cleared, uint64_t one_launch, hipStream_t stream) {
+template <uint32_t kRuns>
+static void launch_bloom_small(const BloomJobs<kRuns>& jobs, uint32_t count, bool cleared, uint64_t one_launch, hipStream_t stream) {
     uint64_t most_keys = 0, all_keys = 0;
     uint32_t most_blocks = 0;
     for (uint32_t j = 0; j < count; j++) {
@@ -136,16 +138,18 @@ static void launch_bloom_small(const BloomJobs& jobs, uint32_t count, bool clear
     if (!cleared && most_keys > 2 * kBloomSmallThreads && most_keys <= one_launch) ahead = most_keys <= 4 * kBloomSmallThreads ? 4 : 8;
     const uint64_t share = ahead * (uint64_t)kBloomSmallThreads;
     const dim3 grid(most_keys ? (uint32_t)((most_keys + share - 1) / share) : 1, count), threads(kBloomSmallThreads);
-    if (grid.x > 1 && !cleared && count == 1)  // the smaller argument block: 1 us of the host's time
-        hipLaunchKernelGGL(bloom_clear_kernel, dim3((most_blocks + 255) / 256), dim3(256), 0, stream, reinterpret_cast<uint4*>(jobs.words[0]), (uint64_t)most_blocks);
-    else if (grid.x > 1 && !cleared)
-        hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
+    if (grid.x > 1 && !cleared) {
+        if constexpr (kRuns == 1)
+            hipLaunchKernelGGL(bloom_clear_kernel, dim3((most_blocks + 255) / 256), dim3(256), 0, stream, reinterpret_cast<uint4*>(jobs.words[0]), (uint64_t)most_blocks);
+        else
+            hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
+    }
     auto launch = [&](auto blocks) {
         constexpr uint32_t kBlocks = decltype(blocks)::value;
-        if (ahead == 8) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 8>), grid, threads, 0, stream, jobs);
-        else if (ahead == 4) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 4>), grid, threads, 0, stream, jobs);
-        else if (ahead == 2) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 2>), grid, threads, 0, stream, jobs);
-        else hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 1>), grid, threads, 0, stream, jobs);
+        if (ahead == 8) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 8, kRuns>), grid, threads, 0, stream, jobs);
+        else if (ahead == 4) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 4, kRuns>), grid, threads, 0, stream, jobs);
+        else if (ahead == 2) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 2, kRuns>), grid, threads, 0, stream, jobs);
+        else hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 1, kRuns>), grid, threads, 0, stream, jobs);
     };
     if (most_blocks > kBloomSmallBlocks / 2) launch(std::integral_constant<uint32_t, kBloomSmallBlocks>{});
     else launch(std::integral_constant<uint32_t, kBloomSmallBlocks / 2>{});
@@ -244,7 +248,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
         return LSM_ERR_BAD_ARG;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     if (n_blocks <= kBloomSmallBlocks && run->n <= kBloomSmallKeys) {
-        BloomJobs jobs = {};
+        BloomJobs<1> jobs = {};  // 28 bytes of arguments: the 1.8 KB of a batch cost the host 1 us per launch
         jobs.entries[0] = run->entries;
         jobs.n[0] = run->n;
         jobs.words[0] = static_cast<uint32_t*>(filter_out);
@@ -268,7 +272,7 @@ namespace lsm {
 int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t stream) {
     // a launch takes runs of one kind: small filters, or any
     for (int large = 0; large < 2; large++) {
-        BloomJobs jobs = {};
+        BloomJobs<kBloomBatch> jobs = {};
         uint32_t count = 0;
         uint64_t most_blocks = 1, most_entries = 0;
         for (uint32_t j = 0; j <= n_runs; j++) {
@@ -282,7 +286,7 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
                     if (!cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((uint32_t)cx, count), dim3(256), 0, stream, jobs);
                     if (most_entries > 0) hipLaunchKernelGGL(bloom_insert_batch_kernel, dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs);
                 }
-                jobs = BloomJobs{};
+                jobs = {};
                 count = 0, most_blocks = 1, most_entries = 0;
             }
             if (j == n_runs) break;
