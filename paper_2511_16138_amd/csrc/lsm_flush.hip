@@ -131,8 +131,9 @@ __global__ void __launch_bounds__(kPlaceThreads) flush_place_kernel(const lsm_en
 // double the sorted lists, a thread producing eight outputs per round from eight records of either list (bitonic
 // half-cleaner and merge network).  Positions whose 14 bytes equal a neighbour's (versions of a key, and keys that
 // differ further on) are settled afterwards by the rest of the key, seqno and age: each by comparing itself with the whole
-// group, or, where some group has more than kTieWalk members, by a merge sort of the whole segment that compares these.  Bound by LDS operations of one compute unit per segment; all pairs of a segment instead (the step
-// that this one replaced) took 936 us for 100,001 entries, the whole call 1052 us against 122 us.  The entries themselves are
+// group, or, where some group is long, by a merge sort of the whole segment that compares these.  Bound by LDS
+// operations of one compute unit per segment; all pairs of a segment instead (the step that this one replaced) took 936 us for
+// 100,001 entries, the whole call 1052 us against 122 us.  The entries themselves are
 // read a second time for the output (they come from the L2).
 // ---------------------------------------------------------------------------------------
 constexpr uint64_t kFlushSegment = 4096;
@@ -140,17 +141,17 @@ constexpr int kSortThreads = 512;
 constexpr int kSortItems = 8;
 static_assert(kSortThreads * kSortItems == kFlushSegment, "a segment fills the workgroup");
 static_assert(kFlushSegment * LSM_MAX_RUNS >= LSM_MAX_BUFFER, "the segments of the largest buffer must fit one compaction");
-// Members a group may have for its positions to be compared one by one: a serial chain of LDS reads that grows with the
-// square of the members (one group of 4,096: 10.6 ms a segment), where the merge sort takes about as long as the first sort
-// whatever the groups (8,193 versions of one key 139 us in all, 68 for distinct keys).  100,001 entries in groups of about 10
-// / 20 / 64 members: 164 / 181 / 313 us one by one, 174 / 170 / 166 by the merge sort.
-constexpr uint32_t kTieWalk = 16;
-
+// Groups are settled by comparing their positions one by one, a serial chain of LDS reads that grows with the square of the
+// members (one group of 4,096: 10.6 ms a segment), unless two lanes next to each other have nothing but positions that
+// share their 14 bytes with the one before: the merge sort takes about as long as the first sort whatever the groups
+// (8,193 versions of one key 128 us in all, 62 for distinct keys).  That is so for every group of 32 members and for none of 16.
+// 100,001 entries in groups of about 10 / 20 / 64 members: 164 / 181 / 313 us one by one, 174 / 170 / 166 by the merge sort.
 struct SortShared {
     uint4 buf[2][kFlushSegment];       // records, two sides; then the rest of the key and the seqno of tied positions
     uint16_t order[kFlushSegment];     // final position -> age
     uint16_t other[kFlushSegment];     // second side of the merge sort of tied positions
     uint32_t wave_count[kSortThreads / kWave];
+    uint32_t deep;                     // some group is long
     alignas(4) uint8_t flag[kFlushSegment + 8];  // sorted position: 1 = same 14 bytes as the one before
     alignas(4) uint8_t lose[kFlushSegment];      // final position: 1 = shadowed
 };
@@ -256,6 +257,7 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
     const uint32_t len = min((uint32_t)kFlushSegment, n - first);
     const lsm_entry_t* src = buffer + first;
 
+    if (tid == 0) s.deep = 0;
     // ---- records; age a = entry len - 1 - a of the segment.  Unused positions hold the largest value.
 #pragma unroll
     for (int i = 0; i < kSortItems; i++) {
@@ -316,7 +318,7 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
     }
 
     // ---- which positions share their 14 bytes with a neighbour?  c[] holds this thread's eight sorted records.
-    bool any = false;
+    bool any = false, all = true;
     {
         Rec prev = c[0];
         if (o > 0) prev = rec_load(&s.buf[cur][rec_at(o - 1)]);
@@ -327,32 +329,35 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
             s.lose[o + i] = 0;
             s.order[o + i] = (uint16_t)(c[i].lo & 0xFFFF);
             any = any || eq;
+            all = all && eq;
             prev = c[i];
         }
     }
+    const bool all_before = __shfl_up(all ? 1 : 0, 1, kWave) != 0;
+    if (all && all_before && (tid & (kWave - 1)) != 0) s.deep = 1;
     if (tid == 0) s.flag[kFlushSegment] = 0;
     if (__syncthreads_or(any)) {
-        // where the group of every position starts: the last position without a flag up to it
-        uint32_t start[kSortItems], last = 0;
+        const bool deep = s.deep != 0;
+        uint32_t start[kSortItems] = {};
+        if (deep) {  // where the group of every position starts: the last position without a flag up to it
+            uint32_t last = 0;
 #pragma unroll
-        for (int i = 0; i < kSortItems; i++) last = s.flag[o + i] == 0 ? o + i : last;
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t v = __shfl_up(last, off, kWave);
-            if ((int)(tid & (kWave - 1)) >= off) last = max(last, v);
-        }
-        if ((tid & (kWave - 1)) == kWave - 1) s.wave_count[tid / kWave] = last;
-        last = __shfl_up(last, 1, kWave);
-        if ((tid & (kWave - 1)) == 0) last = 0;
-        __syncthreads();
-        for (uint32_t w = 0; w < tid / kWave; w++) last = max(last, s.wave_count[w]);
-        bool deep = false;
+            for (int i = 0; i < kSortItems; i++) last = s.flag[o + i] == 0 ? o + i : last;
+            for (int off = 1; off < kWave; off <<= 1) {
+                const uint32_t v = __shfl_up(last, off, kWave);
+                if ((int)(tid & (kWave - 1)) >= off) last = max(last, v);
+            }
+            if ((tid & (kWave - 1)) == kWave - 1) s.wave_count[tid / kWave] = last;
+            last = __shfl_up(last, 1, kWave);
+            if ((tid & (kWave - 1)) == 0) last = 0;
+            __syncthreads();
+            for (uint32_t w = 0; w < tid / kWave; w++) last = max(last, s.wave_count[w]);
 #pragma unroll
-        for (int i = 0; i < kSortItems; i++) {
-            last = s.flag[o + i] == 0 ? o + i : last;
-            start[i] = last;
-            deep = deep || o + i - last >= kTieWalk;
+            for (int i = 0; i < kSortItems; i++) {
+                last = s.flag[o + i] == 0 ? o + i : last;
+                start[i] = last;
+            }
         }
-        deep = __syncthreads_or(deep) != 0;
         // members of groups post the rest of their key, seqno and age at their sorted position
         uint4* info0 = s.buf[0];  // {seqno, group and key bytes 14..15, age}
         uint4* info1 = s.buf[1];  // key bytes 16..31
@@ -376,15 +381,18 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
             for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
                 const uint32_t p = o + i;
                 if (p >= len || (s.flag[p] | s.flag[p + 1]) == 0) continue;
+                uint32_t first_member = p;
+                while (s.flag[first_member] != 0) first_member--;  // flag[0] is 0
                 const Tied a = tied_load(info0, info1, p);
-                const uint32_t first_member = a.head >> 16;
                 uint32_t rank = 0, q = first_member;
                 bool shadowed = false;
                 do {
                     if (q != p) {
                         const Tied b = tied_load(info0, info1, q);
-                        shadowed = shadowed || (tied_same_key(a, b) && tied_newer(b, a));
-                        rank += tied_less(b, a) ? 1 : 0;
+                        const bool same = tied_same_key(a, b), newer = same && tied_newer(b, a);
+                        const bool less = b.head != a.head ? b.head < a.head : (b.k2 != a.k2 ? b.k2 < a.k2 : b.k3 < a.k3);
+                        shadowed = shadowed || newer;
+                        rank += (same ? newer : less) ? 1 : 0;
                     }
                     q++;
                 } while (s.flag[q] != 0);  // flag[len ..] is 0
