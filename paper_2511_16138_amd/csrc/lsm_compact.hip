@@ -9,9 +9,12 @@
 //                     L(x) = sum_j |{e in run j : e.key < x}| that is still <= r, and stores
 //                     the k lower bounds.  Boundaries are therefore key-aligned (all versions
 //                     of a key fall into the same tile) and tile sizes are within k of the
-//                     nominal size.  Small inputs search the runs directly, one wave per
-//                     boundary (partition_kernel, partition_two_*, partition_many_kernel); large
-//                     ones first bracket every boundary, a group of lanes each, on a copy of every
+//                     nominal size.  Two runs: bisection on the merge path (partition_two_*).
+//                     Inputs of up to 512 tiles take sample keys as boundaries instead of exact
+//                     ranks (partition_ranked_kernel: tile sizes vary, within the capacity).
+//                     Larger ones search the runs directly, one wave per boundary
+//                     (partition_kernel, partition_many_kernel), and from 2,048 tiles on
+//                     first bracket every boundary, a group of lanes each, on a copy of every
 //                     32nd key (sample_kernel, sample_coarse_kernel, sample_fine_kernel) and search
 //                     the runs only inside the brackets (bracket_partition_kernel).
 //   merge_kernel      one workgroup per tile: every thread loads its share of the tile's entries
@@ -53,6 +56,14 @@ inline uint32_t fill_spacing(uint64_t total) {
     return even < (uint64_t)kTileCap ? (uint32_t)even : (uint32_t)kTileCap;
 }
 __host__ __device__ inline uint32_t tile_spacing(uint32_t fill, uint32_t k) { return fill < (uint32_t)tile_nominal(k) ? fill : (uint32_t)tile_nominal(k); }
+// Boundaries at ranked samples (three runs or more, see ranked_row): the inputs that 512 tiles hold, two on every compute unit.
+// They have 512 entries at least; more tiles than that would run in turns, and the work of the launch grows with the samples,
+// which get denser as a tile's mean size comes closer to its capacity: beyond kMostSamples the other searches are as fast
+// (partition and merge, sampled against the window search: 16 runs, 600k entries 55 / 77 us with 10,300 samples, 750k 70 / 79
+// with 19,700, 900k 130 / 83 with 47,000; 64 runs of 300k in all 64 / 57 us with 23,000; 48 runs 40 / 57 with 16,700).
+constexpr uint64_t kRankedTiles = 512;
+constexpr uint64_t kMostSamples = 20480;
+constexpr uint32_t kMinStride = 8;
 constexpr uint64_t kCoarseStride = 16;                 // every 16th boundary is searched over whole sequences first
 constexpr uint64_t kSampleStride = 32;                 // one key in 32 is copied for the sampled partition
 constexpr uint64_t kSampledMinTiles = 2048;            // inputs of fewer tiles search the runs directly (measured crossover)
@@ -82,6 +93,7 @@ struct SampleTable {
 };
 
 struct Workspace {
+    uint64_t n_tiles;
     Header* hdr;
     uint64_t* status;   // [n_tiles]
     uint64_t* splits;   // [(n_tiles + 1) * k]
@@ -91,6 +103,7 @@ struct Workspace {
     uint4* clear;       // zeroed by the partition launch for a later kernel of the caller
     uint64_t clear_n;
     uint32_t spacing;   // boundary spacing of the direct partition (batch form: to be capped by tile_spacing for each job)
+    uint32_t stride, per_tile, samples;  // entries from sample to sample, samples from boundary to boundary, in all (single form; see ranked_row)
 };
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -445,6 +458,99 @@ __device__ __forceinline__ void split_two_wave(const lsm_entry_t* a, const uint6
     if (ia > 0 && ib < nb && key_equal(load_key(a + ia - 1), load_key(b + ib))) ia--;
 }
 
+// Inclusive prefix sum over the lanes of a wave: shifts inside rows of 16 lanes (0 comes in at a row's start), then the sums
+// of the rows below.
+template <int kOff>
+__device__ __forceinline__ uint32_t row_shift_up(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x110 | kOff, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+    v += row_shift_up<1>(v);
+    v += row_shift_up<2>(v);
+    v += row_shift_up<4>(v);
+    v += row_shift_up<8>(v);
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 15), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
+    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+    return v + (lane >= 16 ? a : 0) + (lane >= 32 ? b : 0) + (lane >= 48 ? c : 0);
+}
+
+// ---------------------------------------------------------------------------------------
+// Boundaries at sample keys, for small inputs of three runs or more: one launch in which every boundary is found without the
+// others.  Every `stride`-th entry of every run is a sample.  A wave takes one sample c and counts the samples before it in
+// every run (equal keys: those of lower runs count as before it), 64 / group lanes per run, each step one evenly spaced record
+// per lane.  The sum t is c's place in the order of all samples, known without sorting them, and distinct for every sample:
+// the samples with t = per_tile * row are the boundaries, and their waves go on to the lower bounds of c in the entries
+// between two samples.  Tile sizes vary, but a tile holds per_tile samples, and less than `stride` entries of a run before
+// its first one: at most (per_tile + k - 1) * stride entries, which the host keeps within the capacity.
+// What bounds it: four or five dependent reads.  The window search below, three rounds of reads and some fifteen dependent
+// searches in LDS, against this one: 4 x 16,384 entries 16.5 -> 4.5 us, 24 x 2,730 44 -> 7.3, 8 x 37,500 24.5 -> 6.5, 16 runs of
+// 8,000 entries one after the other 39.8 -> 4.7; tiles of uneven size cost the merge up to 2 us of it (4 x 16,384: 17.4 -> 18.1).
+// len: run lengths; upper: what the launch counts samples by (the same, or an upper bound: samples beyond a run's end come last, and
+// their rows are the runs' ends).
+// ---------------------------------------------------------------------------------------
+__device__ __forceinline__ void ranked_row(const lsm_entry_t* run, const uint32_t len, const uint32_t upper, const uint32_t p, const uint32_t k,
+                                            const int group_log, const uint32_t stride, const uint32_t per_tile, uint64_t* splits) {
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const int lanes_log = 6 - group_log;
+    const uint32_t lanes = 1u << lanes_log, member = lane >> lanes_log, part = lane & (lanes - 1), shift = member << lanes_log;
+    const uint64_t lanes_mask = lanes == (uint32_t)kWave ? ~0ull : (1ull << lanes) - 1;
+    const bool head = part == 0 && member < k;
+    const uint32_t real = (len + stride - 1) / stride, launched = (upper + stride - 1) / stride;
+    // which run the sample belongs to: samples are numbered run by run
+    const uint32_t upto = wave_scan_u32(head ? launched : 0);
+    const uint32_t own = (uint32_t)__popcll(__ballot(head && upto <= p));
+    const int own_lane = (int)(own << lanes_log);
+    const uint32_t index = p - (uint32_t)__shfl((int)(upto - launched), own_lane, kWave);
+    const uint32_t own_real = (uint32_t)__shfl((int)real, own_lane, kWave);
+    uint32_t t, lo = 0, hi = 0;
+    Key key = {{0, 0, 0, 0}};
+    if (index < own_real) {
+        const lsm_entry_t* own_run = reinterpret_cast<const lsm_entry_t*>(__shfl(reinterpret_cast<uint64_t>(run), own_lane, kWave));
+        const uint4* e = reinterpret_cast<const uint4*>(own_run + (uint64_t)index * stride);
+        const uint4 k0 = load_global_u4(e), k1 = load_global_u4(e + 1);
+        key = key_from_raw(k0, k1);
+        // first record in [lo, hi) of the records `step` entries apart that is not before the key
+        auto search = [&](const lsm_entry_t* from, uint32_t step, bool equal_is_before) {
+            while (__ballot(lo < hi) != 0) {
+                const uint32_t w = hi - lo;
+                auto tried = [&](uint32_t m) { return lo + (((2 * m + 1) * w) >> (lanes_log + 1)); };  // ascending with m, below hi
+                bool before = false;
+                if (lo < hi) {
+                    const uint4* q = reinterpret_cast<const uint4*>(from + (uint64_t)tried(part) * step);
+                    const uint4 q0 = load_global_u4(q), q1 = load_global_u4(q + 1);
+                    const Key other = key_from_raw(q0, q1);
+                    before = equal_is_before ? !key_less(key, other) : key_less(other, key);
+                }
+                const uint32_t n = (uint32_t)__popcll((__ballot(before) >> shift) & lanes_mask);  // the first n are before
+                if (lo < hi) {
+                    const uint32_t new_lo = n > 0 ? tried(n - 1) + 1 : lo, new_hi = n < lanes ? tried(n) : hi;
+                    lo = new_lo;
+                    hi = new_hi < new_lo ? new_lo : new_hi;  // only runs that are not sorted
+                }
+            }
+        };
+        lo = member == own ? index : 0;
+        hi = member == own ? index : (member < k ? real : 0);
+        search(run, stride, member < own);
+        t = wave_scan_u32(head ? lo : 0);
+        t = (uint32_t)__builtin_amdgcn_readlane((int)t, kWave - 1);
+        if (t % per_tile != 0) return;
+        // the lower bound: after the last sample before the key, or that sample if its key is the same
+        hi = min(lo * stride, len);
+        lo = lo > 0 ? (lo - 1) * stride : 0;
+        if (member == own) lo = hi = index * stride;
+        search(run, 1, false);
+    } else {  // beyond the run's end
+        const uint32_t surplus = wave_scan_u32(head ? launched - real : 0), all = wave_scan_u32(head ? real : 0);
+        t = (uint32_t)__builtin_amdgcn_readlane((int)all, kWave - 1) + (uint32_t)__shfl((int)(surplus - (launched - real)), own_lane, kWave) + index - own_real;
+        if (t % per_tile != 0) return;
+        lo = len;
+    }
+    const uint32_t row = t / per_tile;
+    if (head && row > 0) splits[(uint64_t)row * k + member] = lo;
+}
+
 // Lane bookkeeping shared by the partition kernels: which problem and which sequence a lane has.
 struct GroupLane {
     int member, group_base;
@@ -511,6 +617,14 @@ __global__ void __launch_bounds__(kWave) partition_kernel(RunTable rt, Workspace
     const bool own = j < rt.k;
     const uint32_t best = window_split<kPerLane, kMany>(s, own ? rt.ptr[j] : nullptr, own ? (uint32_t)run_len(rt, j) : 0, b * ws.spacing, group_log);
     if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
+}
+template <bool kInit>
+__global__ void __launch_bounds__(kWave) partition_ranked_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, int group_log) {
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint32_t member = (threadIdx.x & (kWave - 1)) >> (6 - group_log);
+    const bool mine = member < rt.k;
+    ranked_row(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, blockIdx.x, rt.k, group_log,
+                ws.stride, ws.per_tile, ws.splits);
 }
 // With many runs and many tiles the records that the waves' rounds read are more than the memory takes (a round of 64 runs is
 // 512 lines of 128 bytes): beyond kWindowPieces pieces of tiles in runs the pivoting selection, whose searches share their
@@ -669,15 +783,18 @@ struct MergeShared {
 enum : int { kModeSingle = 0, kModeRange = 1, kModeBatch = 2 };
 
 struct JobDesc {       // one compaction of a batch (device memory, written by the host)
-    uint64_t first_tile;   // number of its first tile in the launch
-    uint64_t run_off;      // where its runs start in the run pointer / length arrays
+    uint32_t first_tile;   // number of its first tile in the launch
+    uint32_t first_wave;   // number of its first wave in the partition launch
+    uint32_t run_off;      // where its runs start in the run pointer / length arrays
+    uint16_t stride, per_tile;  // entries from sample to sample, samples from boundary to boundary; stride 0: exact ranks, a wave per tile
     uint64_t splits_off;   // where its split table starts (in 64-bit words)
     lsm_entry_t* out;
     uint64_t* n_out;
     uint4* fence_out;      // optional fence index of the job's output
     uint32_t n_tiles, k, flags, fence_stride;
     uint4* clear;          // optional memory the partition launch zeroes for a later kernel
-    uint64_t clear_n;
+    uint32_t clear_n;
+    uint32_t waves;        // of the partition launch
 };
 static_assert(sizeof(JobDesc) == 80, "descriptor layout");
 
@@ -865,7 +982,7 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         __builtin_amdgcn_s_setprio(3);  // the other waves wait for this one: let it issue first
         uint64_t t = blockIdx.x;        // tile number inside its compaction
         uint32_t kk = rt.k;
-        uint64_t a = 0, b = 0;
+        uint64_t a = 0, b = 0, len = ~0ull;
         if (kMode == kModeSingle) {
             if (lane < (int)kk) {
                 if (n_tiles == 1) {  // one tile is the whole input: launched on its own, without a split table
@@ -873,6 +990,7 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                 } else {
                     a = ws.splits[t * kk + lane];
                     b = ws.splits[(t + 1) * kk + lane];
+                    if (ws.stride != 0) len = run_len(rt, lane);  // exact ranks write every row, within the runs
                 }
                 s.run[lane] = rt.ptr[lane];
             }
@@ -892,6 +1010,7 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                 a = ws.splits[d.splits_off + t * kk + lane];
                 b = ws.splits[d.splits_off + (t + 1) * kk + lane];
                 s.run[lane] = ma.run_ptr[d.run_off + lane];
+                if (d.stride != 0) len = ma.run_n[d.run_off + lane];
             }
             if (lane == 0) {
                 s.k = kk;
@@ -905,10 +1024,10 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
             }
         }
         const bool mine = lane < (int)kk;
-        // piece lengths -> offsets (inclusive scan over the lanes); split rows never exceed the run
-        // lengths, and only inputs that break the precondition can make a row pair inconsistent
+        // piece lengths -> offsets (inclusive scan over the lanes); only inputs that break the precondition can make a row
+        // pair inconsistent, or leave a row of the sampled ranks unwritten
         // (a key range may simply hold more than a tile: reported as an overflow of that range)
-        const bool bad = mine && (b < a || b - a > (uint64_t)kTileCap);
+        const bool bad = mine && (b < a || b > len || b - a > (uint64_t)kTileCap);
         uint32_t incl = (mine && !bad) ? (uint32_t)(b - a) : 0;
         for (int off = 1; off < kWave; off <<= 1) {
             const uint32_t v = __shfl_up(incl, off, kWave);
@@ -1375,47 +1494,62 @@ struct BatchInline {
     JobDesc jobs[kInlineJobs];
     const lsm_entry_t* run_ptr[kInlineRuns];
     uint64_t run_n[kInlineRuns];
-    uint32_t n_jobs;
 };
 static_assert(sizeof(BatchInline) <= 2560, "fits the argument segment of a launch beside the rest");
 
 template <int kPerLane, bool kMany, bool kInline>
-__global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, ModeArgs ma, int group_log, BatchInline table) {
+__global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, ModeArgs ma, int group_log, uint32_t n_jobs, BatchInline table) {
     __shared__ WindowShared<kPerLane> s;
+    const JobDesc* const jobs = kInline ? table.jobs : ma.jobs;
     uint32_t job = 0;
     if (kInline) {
-        for (uint32_t q = 1; q < table.n_jobs; q++) job = table.jobs[q].first_tile <= blockIdx.x ? q : job;
-        if (threadIdx.x == 0) const_cast<uint32_t*>(ma.tile_job)[blockIdx.x] = job;
+        for (uint32_t q = 1; q < n_jobs; q++) job = jobs[q].first_wave <= blockIdx.x ? q : job;
     } else {
-        job = ma.tile_job[blockIdx.x];
+        for (uint32_t left = n_jobs - 1; left > 0;) {  // last job whose first wave is not beyond this one
+            const uint32_t half = (left + 1) / 2, at = job + half;
+            if (jobs[at].first_wave <= blockIdx.x) job = at, left -= half;
+            else left = half - 1;
+        }
     }
-    const JobDesc d = kInline ? table.jobs[job] : ma.jobs[job];
+    const JobDesc d = jobs[job];
     const lsm_entry_t* const* run_ptr = kInline ? table.run_ptr : ma.run_ptr;
     const uint64_t* run_n = kInline ? table.run_n : ma.run_n;
-    const uint32_t t = (uint32_t)(blockIdx.x - d.first_tile);
-    if (kInline && t == 0) {
-        if (threadIdx.x == 0) const_cast<JobDesc*>(ma.jobs)[job] = d;
-        if (threadIdx.x < d.k) const_cast<const lsm_entry_t**>(ma.run_ptr)[d.run_off + threadIdx.x] = run_ptr[d.run_off + threadIdx.x];
+    const uint32_t lane = threadIdx.x, w = blockIdx.x - d.first_wave, waves = d.waves;
+    if (kInline && w == 0) {
+        if (lane == 0) const_cast<JobDesc*>(ma.jobs)[job] = d;
+        if (lane < d.k) const_cast<const lsm_entry_t**>(ma.run_ptr)[d.run_off + lane] = run_ptr[d.run_off + lane];
+        if (lane < d.k) const_cast<uint64_t*>(ma.run_n)[d.run_off + lane] = run_n[d.run_off + lane];
     }
-    for (uint64_t c = t * (uint64_t)kWave + threadIdx.x; c < d.clear_n; c += (uint64_t)d.n_tiles * kWave) d.clear[c] = make_uint4(0, 0, 0, 0);
-    const uint32_t lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
-    const bool own = j < d.k;
-    const lsm_entry_t* run = own ? run_ptr[d.run_off + j] : nullptr;
-    const uint64_t len = own ? run_n[d.run_off + j] : 0;
-    uint64_t best = 0;
-    if (t > 0 && d.k == 2) {
+    for (uint64_t c = w * (uint64_t)kWave + lane; c < d.clear_n; c += (uint64_t)waves * kWave) d.clear[c] = make_uint4(0, 0, 0, 0);
+    for (uint32_t t = w * kWave + lane; t < d.n_tiles; t += waves * kWave) {
+        const_cast<uint32_t*>(ma.tile_job)[d.first_tile + t] = job;
+        ws.status[d.first_tile + t] = 0;
+    }
+    uint64_t* const rows = ws.splits + d.splits_off;
+    if (w == 0 && lane < d.k) {
+        rows[lane] = 0;
+        rows[(uint64_t)d.n_tiles * d.k + lane] = run_n[d.run_off + lane];
+    }
+    if (d.stride != 0) {
+        const int log = 32 - __builtin_clz(d.k - 1);
+        const uint32_t member = lane >> (6 - log);
+        const bool mine = member < d.k;
+        const uint32_t len = mine ? (uint32_t)run_n[d.run_off + member] : 0;
+        ranked_row(mine ? run_ptr[d.run_off + member] : nullptr, len, len, w, d.k, log, d.stride, d.per_tile, rows);
+        return;
+    }
+    if (w == 0) return;  // the boundary of tile w
+    if (d.k == 2) {
         uint64_t ia, ib;
-        split_two_wave(run_ptr[d.run_off], run_n[d.run_off], run_ptr[d.run_off + 1], run_n[d.run_off + 1], t * (uint64_t)tile_spacing(ws.spacing, 2), ia, ib);
-        best = j == 0 ? ia : ib;
-    } else if (t > 0) {
-        best = window_split<kPerLane, kMany>(s, run, (uint32_t)len, t * tile_spacing(ws.spacing, d.k), group_log);
+        split_two_wave(run_ptr[d.run_off], run_n[d.run_off], run_ptr[d.run_off + 1], run_n[d.run_off + 1], w * (uint64_t)tile_spacing(ws.spacing, 2), ia, ib);
+        if (lane < 2) rows[w * 2 + lane] = lane == 0 ? ia : ib;
+        return;
     }
-    if (lane < d.k) {
-        uint64_t* rows = ws.splits + d.splits_off;
-        rows[t * d.k + lane] = best;
-        if (t + 1 == d.n_tiles) rows[(t + 1) * d.k + lane] = len;
-    }
-    if (lane == 0) ws.status[blockIdx.x] = 0;
+    const uint32_t j = lane & ((1u << group_log) - 1);
+    const bool own = j < d.k;
+    const uint32_t best = window_split<kPerLane, kMany>(s, own ? run_ptr[d.run_off + j] : nullptr, own ? (uint32_t)run_n[d.run_off + j] : 0,
+                                                        w * tile_spacing(ws.spacing, d.k), group_log);
+    if (lane < d.k) rows[w * d.k + lane] = best;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1439,13 +1573,45 @@ static uint32_t single_spacing(uint64_t total, uint32_t k) {
     return total <= tile_nominal(k) ? (uint32_t)tile_nominal(k) : tile_spacing(fill_spacing(total), k);
 }
 static uint64_t tiles_for(uint64_t total, uint32_t spacing) { return (total + spacing - 1) / spacing; }
+// How a compaction is cut into tiles: at merged ranks `spacing` apart, or (stride != 0) at ranked samples.
+struct Cut {
+    uint32_t spacing = 0;
+    uint64_t tiles = 0;
+    uint32_t stride = 0, per_tile = 0, samples = 0;
+};
+// `all`: entries of everything in the same launch, this compaction's among them.
+static Cut cut_runs(const uint64_t* run_lens, uint32_t k, uint32_t spacing, uint64_t all) {
+    uint64_t total = 0;
+    for (uint32_t j = 0; j < k; j++) total += run_lens[j];
+    Cut exact;
+    exact.spacing = spacing;
+    exact.tiles = tiles_for(total, spacing);
+    const uint64_t even = (all + kRankedTiles - 1) / kRankedTiles, mean = even < kMinSpacing ? kMinSpacing : even;
+    if (k < 3 || exact.tiles < 2 || mean >= (uint64_t)kTileCap) return exact;
+    // the densest samples the tile capacity asks for, and four to a tile for even sizes
+    const uint64_t most_tiles = tiles_for(total, (uint32_t)mean), most_samples = kMostSamples * total / all;
+    Cut cut = exact;
+    cut.stride = (uint32_t)(kTileCap - mean) / (k - 1);
+    if (cut.stride > mean / 4) cut.stride = (uint32_t)mean / 4;
+    for (; cut.stride >= kMinStride; cut.stride -= (cut.stride + 15) / 16) {
+        uint64_t samples = 0;
+        for (uint32_t j = 0; j < k; j++) samples += (run_lens[j] + cut.stride - 1) / cut.stride;
+        if (samples > most_samples + k) return exact;
+        cut.samples = (uint32_t)samples;
+        cut.per_tile = (uint32_t)((samples + most_tiles - 1) / most_tiles);
+        cut.tiles = (samples + cut.per_tile - 1) / cut.per_tile;
+        if ((cut.per_tile + k - 1) * cut.stride <= (uint32_t)kTileCap) return cut;
+    }
+    return exact;
+}
 static uint64_t coarse_rows(uint64_t n_tiles) { return n_tiles > 1 ? (n_tiles - 1) / kCoarseStride : 0; }
 
 // Lays the workspace out; with base == nullptr it only measures.  Returns the bytes used.
 static size_t carve(void* base, const uint64_t* run_lens, uint32_t k, Workspace* ws) {
     uint64_t total = 0;
     for (uint32_t j = 0; j < k; j++) total += run_lens[j];
-    const uint64_t n_tiles = tiles_for(total, single_spacing(total, k)), n_coarse = coarse_rows(n_tiles);
+    const Cut cut = cut_runs(run_lens, k, single_spacing(total, k), total);
+    const uint64_t n_tiles = tiles_for(total, cut.spacing), n_coarse = coarse_rows(n_tiles);
     char* p = static_cast<char*>(base);
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1463,6 +1629,23 @@ static size_t carve(void* base, const uint64_t* run_lens, uint32_t k, Workspace*
         w.st.m[j] = j < k ? (run_lens[j] + kSampleStride - 1) / kSampleStride : 0;
         w.st.ptr[j] = j < k ? reinterpret_cast<SampleKey*>(take(w.st.m[j] * sizeof(SampleKey))) : nullptr;
     }
+    w.n_tiles = n_tiles;
+    if (cut.stride != 0) {  // may be more tiles, but without the samples' copies: a fraction of the space above
+        const size_t all = off;
+        off = 0;
+        w.hdr = reinterpret_cast<Header*>(take(sizeof(Header)));
+        w.status = reinterpret_cast<uint64_t*>(take(cut.tiles * sizeof(uint64_t)));
+        w.splits = reinterpret_cast<uint64_t*>(take((cut.tiles + 1) * (uint64_t)k * sizeof(uint64_t)));
+        w.ycoarse = reinterpret_cast<uint64_t*>(take((coarse_rows(cut.tiles) + 2) * (uint64_t)k * sizeof(uint64_t)));
+        w.n_tiles = cut.tiles;
+        if (off < all) off = all;
+    }
+    w.clear = nullptr;
+    w.clear_n = 0;
+    w.spacing = cut.spacing;
+    w.stride = cut.stride;
+    w.per_tile = cut.per_tile;
+    w.samples = cut.samples;
     if (ws) *ws = w;
     return off;
 }
@@ -1493,14 +1676,10 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     const uint32_t n_runs = rt.k;
     uint64_t total = 0;
     for (uint32_t j = 0; j < n_runs; j++) total += rt.n[j];
-    const uint32_t spacing = single_spacing(total, n_runs);
-    const uint64_t n_tiles = tiles_for(total, spacing);
-    if (n_tiles >= (1ull << 31)) return LSM_ERR_BAD_ARG;
+    if (tiles_for(total, single_spacing(total, n_runs)) >= (1ull << 31)) return LSM_ERR_BAD_ARG;
     Workspace ws;
     carve(workspace, rt.n, n_runs, &ws);
-    ws.clear = nullptr;
-    ws.clear_n = 0;
-    ws.spacing = spacing;
+    const uint64_t n_tiles = ws.n_tiles;
     const uint64_t n_coarse = coarse_rows(n_tiles);  // boundaries kCoarseStride, 2 * kCoarseStride, ... < n_tiles
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
@@ -1544,9 +1723,11 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                 else if (n_runs == 2)
                     hipLaunchKernelGGL(partition_two_kernel<kInit>, dim3((uint32_t)((n_tiles - 1 + kTwoThreads - 1) / kTwoThreads)), dim3(kTwoThreads), 0,
                                        stream, rt, ws, n_tiles);
+                else if (ws.stride != 0)
+                    hipLaunchKernelGGL(partition_ranked_kernel<kInit>, dim3(ws.samples), dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (records_per_lane(group_log) == 4)
                     hipLaunchKernelGGL((partition_kernel<kInit, 4, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
-                else if (n_runs <= kFewRuns || rt.n_dev != nullptr)  // or the segments of a write buffer: mixed, and few tiles (64 of them 144 / 150 us)
+                else if (n_runs <= kFewRuns)
                     hipLaunchKernelGGL((partition_kernel<kInit, 8, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (n_tiles * n_runs > kWindowPieces)
                     hipLaunchKernelGGL(partition_many_kernel<kInit>, waves, dim3(kWave), 0, stream, rt, ws, n_tiles);
@@ -1712,6 +1893,7 @@ namespace lsm {
 struct BatchLayout {
     uint64_t tiles, split_words, runs;
     size_t status, splits, tile_job, jobs, run_ptr, run_n, total;
+    uint64_t all;  // entries
     uint32_t k_max, spacing;
 };
 // Pinned host memory for the job table of one thread, with an event that tells when the last copy out of it is done.
@@ -1748,12 +1930,12 @@ struct BatchStaging {
 static int batch_layout(const lsm_compact_job_t* jobs, uint32_t n_jobs, BatchLayout* l) {
     l->tiles = l->split_words = l->runs = 0;
     l->k_max = 1;
-    uint64_t all = 0;
+    l->all = 0;
     for (uint32_t j = 0; j < n_jobs; j++) {
         if (jobs[j].runs == nullptr || jobs[j].n_runs > LSM_MAX_RUNS) continue;  // refused below
-        for (uint32_t r = 0; r < jobs[j].n_runs; r++) all += jobs[j].runs[r].n;
+        for (uint32_t r = 0; r < jobs[j].n_runs; r++) l->all += jobs[j].runs[r].n;
     }
-    l->spacing = fill_spacing(all);
+    l->spacing = fill_spacing(l->all);
     for (uint32_t j = 0; j < n_jobs; j++) {
         const lsm_compact_job_t& job = jobs[j];
         if (job.runs == nullptr) return LSM_ERR_NULL;
@@ -1761,11 +1943,12 @@ static int batch_layout(const lsm_compact_job_t* jobs, uint32_t n_jobs, BatchLay
         if (job.out.fence_keys != nullptr && (job.out.fence_stride == 0 || (reinterpret_cast<uintptr_t>(job.out.fence_keys) & 15) != 0))
             return LSM_ERR_BAD_ARG;
         if (job.out.key_hashes != nullptr) return LSM_ERR_BAD_ARG;  // filters of a batch: lsm_build_bloom_batch
-        uint64_t total = 0;
-        for (uint32_t r = 0; r < job.n_runs; r++) total += job.runs[r].n;
-        uint64_t nt = tiles_for(total, tile_spacing(l->spacing, job.n_runs));
-        if (nt >= kSampledMinTiles) return LSM_ERR_BAD_ARG;  // a large compaction: lsm_compact
-        if (nt == 0) nt = 1;                                  // an empty job keeps one (empty) tile, which writes its count
+        uint64_t total = 0, lens[LSM_MAX_RUNS];
+        for (uint32_t r = 0; r < job.n_runs; r++) total += lens[r] = job.runs[r].n;
+        const uint32_t spacing = tile_spacing(l->spacing, job.n_runs);
+        if (tiles_for(total, spacing) >= kSampledMinTiles) return LSM_ERR_BAD_ARG;  // a large compaction: lsm_compact
+        uint64_t nt = cut_runs(lens, job.n_runs, spacing, l->all).tiles;
+        if (nt == 0) nt = 1;  // an empty job keeps one (empty) tile, which writes its count
         l->tiles += nt;
         l->split_words += (nt + 1) * job.n_runs;
         l->runs += job.n_runs;
@@ -1780,8 +1963,8 @@ static int batch_layout(const lsm_compact_job_t* jobs, uint32_t n_jobs, BatchLay
     };
     l->status = take(l->tiles * sizeof(uint64_t));
     l->splits = take(l->split_words * sizeof(uint64_t));
-    l->tile_job = take(l->tiles * sizeof(uint32_t));  // from here on: written by the host, one copy
-    l->jobs = take((size_t)n_jobs * sizeof(JobDesc));
+    l->tile_job = take(l->tiles * sizeof(uint32_t));
+    l->jobs = take((size_t)n_jobs * sizeof(JobDesc));  // from here on: written by the host, one copy
     l->run_ptr = take(l->runs * sizeof(void*));
     l->run_n = take(l->runs * sizeof(uint64_t));
     l->total = off;
@@ -1821,34 +2004,33 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
     // a larger table is built in pinned host memory kept per thread (so the copy below really is asynchronous) and
     // is not written again before the copy of the previous call from this thread has finished
     static thread_local BatchStaging staging;
-    const size_t table_bytes = l.total - l.tile_job;
+    const size_t table_bytes = l.total - l.jobs;
     unsigned char* copied = nullptr;
-    uint32_t* tile_job = nullptr;
     if (!fits_inline) {
         copied = staging.acquire(table_bytes);
         if (copied == nullptr) return LSM_ERR_HIP;
         memset(copied, 0, table_bytes);
-        tile_job = reinterpret_cast<uint32_t*>(copied);
-        desc = reinterpret_cast<JobDesc*>(copied + (l.jobs - l.tile_job));
-        run_ptr = reinterpret_cast<const lsm_entry_t**>(copied + (l.run_ptr - l.tile_job));
-        run_n = reinterpret_cast<uint64_t*>(copied + (l.run_n - l.tile_job));
+        desc = reinterpret_cast<JobDesc*>(copied);
+        run_ptr = reinterpret_cast<const lsm_entry_t**>(copied + (l.run_ptr - l.jobs));
+        run_n = reinterpret_cast<uint64_t*>(copied + (l.run_n - l.jobs));
     }
-    table.n_jobs = n_jobs;
-    uint64_t tile = 0, split_word = 0, run = 0;
+    uint64_t tile = 0, wave = 0, split_word = 0, run = 0;
     bool any_fences = false;
     for (uint32_t j = 0; j < n_jobs; j++) {
         const lsm_compact_job_t& job = jobs[j];
-        uint64_t total = 0;
         for (uint32_t r = 0; r < job.n_runs; r++) {
             run_ptr[run + r] = job.runs[r].entries;
             run_n[run + r] = job.runs[r].n;
-            total += job.runs[r].n;
         }
-        uint64_t nt = tiles_for(total, tile_spacing(l.spacing, job.n_runs));
-        if (nt == 0) nt = 1;
+        const Cut cut = cut_runs(run_n + run, job.n_runs, tile_spacing(l.spacing, job.n_runs), l.all);
+        const uint64_t nt = cut.tiles ? cut.tiles : 1;
         JobDesc& d = desc[j];
-        d.first_tile = tile;
-        d.run_off = run;
+        d.first_tile = (uint32_t)tile;
+        d.first_wave = (uint32_t)wave;
+        d.waves = cut.stride != 0 ? cut.samples : (uint32_t)nt;
+        d.stride = (uint16_t)cut.stride;
+        d.per_tile = (uint16_t)cut.per_tile;
+        d.run_off = (uint32_t)run;
         d.splits_off = split_word;
         d.out = job.out.entries;
         d.n_out = job.out.n_out;
@@ -1859,15 +2041,15 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
         d.k = job.n_runs;
         d.flags = job.flags;
         d.clear = clear ? static_cast<uint4*>(clear[j].p) : nullptr;
-        d.clear_n = clear ? clear[j].bytes / 16 : 0;
-        for (uint64_t t = 0; tile_job != nullptr && t < nt; t++) tile_job[tile + t] = j;
+        d.clear_n = clear ? (uint32_t)(clear[j].bytes / 16) : 0;
         tile += nt;
+        wave += d.waves;
         split_word += (nt + 1) * job.n_runs;
         run += job.n_runs;
     }
     char* base = static_cast<char*>(workspace);
     if (!fits_inline) {
-        if (hipMemcpyAsync(base + l.tile_job, copied, table_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return LSM_ERR_HIP;
+        if (hipMemcpyAsync(base + l.jobs, copied, table_bytes, hipMemcpyHostToDevice, stream) != hipSuccess) return LSM_ERR_HIP;
         if (!staging.copy_enqueued(stream)) return LSM_ERR_HIP;
     }
     Workspace ws = {};
@@ -1880,22 +2062,22 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
     ma.run_ptr = reinterpret_cast<const lsm_entry_t* const*>(base + l.run_ptr);
     ma.run_n = reinterpret_cast<const uint64_t*>(base + l.run_n);
     const int group_log = log2_ceil(l.k_max);
-    const dim3 waves((uint32_t)l.tiles), wave(kWave);
+    const dim3 waves((uint32_t)wave), threads(kWave);
     auto launch = [&](auto inline_table) {
         constexpr bool kInline = decltype(inline_table)::value;
-        if (records_per_lane(group_log) == 4) hipLaunchKernelGGL((partition_batch_kernel<4, false, kInline>), waves, wave, 0, stream, ws, ma, group_log, table);
-        else if (l.k_max <= kFewRuns) hipLaunchKernelGGL((partition_batch_kernel<8, false, kInline>), waves, wave, 0, stream, ws, ma, group_log, table);
-        else hipLaunchKernelGGL((partition_batch_kernel<8, true, kInline>), waves, wave, 0, stream, ws, ma, group_log, table);
+        if (records_per_lane(group_log) == 4) hipLaunchKernelGGL((partition_batch_kernel<4, false, kInline>), waves, threads, 0, stream, ws, ma, group_log, n_jobs, table);
+        else if (l.k_max <= kFewRuns) hipLaunchKernelGGL((partition_batch_kernel<8, false, kInline>), waves, threads, 0, stream, ws, ma, group_log, n_jobs, table);
+        else hipLaunchKernelGGL((partition_batch_kernel<8, true, kInline>), waves, threads, 0, stream, ws, ma, group_log, n_jobs, table);
     };
     if (fits_inline) launch(std::true_type{});
     else launch(std::false_type{});
     RunTable rt = {};
     rt.k = 1;
     if (any_fences)  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
-        hipLaunchKernelGGL((merge_kernel<1, kModeBatch>), dim3((uint32_t)l.tiles), dim3(kMergeThreads), 0, stream, rt, ws, l.tiles, 0u,
+        hipLaunchKernelGGL((merge_kernel<1, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
                            (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
     else
-        hipLaunchKernelGGL((merge_kernel<0, kModeBatch>), dim3((uint32_t)l.tiles), dim3(kMergeThreads), 0, stream, rt, ws, l.tiles, 0u,
+        hipLaunchKernelGGL((merge_kernel<0, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
                            (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }

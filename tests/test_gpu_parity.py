@@ -460,6 +460,38 @@ def test_batch_tile_spacing_edges(g, oracle, jobs):
             assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
 
 
+@pytest.mark.parametrize("k", [3, 4, 9, 17, 40, 64])  # 16, 16, 4, 2, 1 and 1 lanes per search
+@pytest.mark.parametrize("shape", ["mixed", "copies", "ragged"])
+def test_boundaries_at_ranked_samples(g, oracle, k, shape):
+    """Three runs or more of up to 512 tiles: totals at the shortest mean tile, where it grows, and on both sides of the
+    longest (samples get denser up to there; with many runs the limit on samples is met first).  Copies: every sample key is
+    in every run.  Ragged: empty runs and runs shorter than the distance between two samples."""
+    rs = np.random.RandomState(k)
+    totals = [2048 - k + 1, 4099, 512 * 512, 512 * 512 + 1, 512 * 700 + 3]
+    if shape == "mixed":
+        totals += [512 * 1200, 512 * 2030 + 1, 512 * 2047 - 1, 512 * 2047 + 1]
+    for total in totals:
+        print("ranked samples", k, shape, total, flush=True)
+        lens = np.full(k, total // k)
+        if shape == "ragged":
+            lens = np.where(rs.rand(k) < 0.4, rs.randint(0, 12, size=k), lens)
+        lens[rs.randint(k)] += max(0, total - lens.sum())
+        if shape == "copies":
+            one = _runs_of(oracle, rs, [int(lens.max())], 3 * int(lens.max()))[0]
+            runs = [one[:n].clone() for n in lens]
+            for r in runs:
+                r[:, 4] = torch.randint(0, 1 << 40, (r.shape[0],), device=dev())
+        else:
+            runs = _runs_of(oracle, rs, lens, 2 * total)
+        _check_compact(g, oracle, runs, int(total & 1))
+    few = _runs_of(oracle, rs, [700, 900], 4000)  # a batch: a job with samples, one without
+    outs, n_out = g.lsm_compact_batch([(few, 1), (runs, 0), (few, 0)])
+    for rr, flags, out, n in zip((few, runs, few), (1, 0, 0), outs, n_out.tolist()):
+        want = oracle.compact([r.cpu() for r in rr], flags)
+        assert n == want.shape[0]
+        assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
+
+
 @pytest.mark.parametrize("n_req", [1, 2, 3, 511, 512, 513, 2047, 2048, 2049])  # four, two and one wave per request
 @pytest.mark.parametrize("row", [256, 192, 64, 17])                            # key rows that need four, three or one of them
 def test_probe_batches_of_all_sizes(g, oracle, cfg1, n_req, row):
