@@ -1,7 +1,8 @@
 // lsm_probe: batched longest-cached-prefix lookup (paper appendix B, "Probe"; section 2.2,
 // "Point Lookups": runs are checked newest to oldest and the first match is the result).
 //
-// One, two or four waves per request, requests taken round-robin by the workgroups of a fixed-size grid.  Every
+// One, two or four waves per request (large batches: 16 requests pooled in a workgroup, see probe_pool_kernel), requests
+// taken round-robin by the workgroups of a fixed-size grid.  Every
 // workgroup first copies a top-level fence table into LDS: for each run of the tree, an evenly
 // spaced subset of its fence keys (all of them for small runs).  A request's block keys are
 // handled 64 at a time, one key per lane.  A lane first reads the Bloom filters of the runs that have one
@@ -114,16 +115,13 @@ __device__ __forceinline__ bool index_admits(const uint4 w, const uint32_t tag) 
     return any;
 }
 
-// Looks one block key per lane up in the tree (every lane of the wave calls this; lanes with mine == false idle).
-// Returns whether the key's newest version is a live PUT (true for idle lanes) and sets h to its hit record.
-template <bool kTop>
-__device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const TreeTable& tree, const uint32_t n_runs,
-                                             const uint64_t run_mask, const bool any_filter, const bool mine, const Key& q, uint4& h) {
-    bool live = !mine, found = !mine;
-    // (0) Bloom filters of the runs that have one: one 16-byte read per run, all runs of a group of
-    //     eight requested together, decides which runs this key is searched in
+// Which runs a lane's key has to be searched in, newest in the lowest bit: those whose Bloom filter or hash index does not rule
+// it out, and those that have neither.  bh: the key's filter hash.
+__device__ __forceinline__ uint64_t probe_admit(const TreeTable& tree, const uint32_t n_runs, const uint64_t run_mask, const bool any_filter,
+                                                const bool mine, const Key& q, uint64_t& bh) {
+    // (0) one 16-byte read per run, all runs of a group of eight requested together
     uint64_t maybe = ~0ull;
-    const uint64_t bh = mine ? bloom_key_hash(q) : 0;
+    bh = mine ? bloom_key_hash(q) : 0;
     const uint32_t tag = (uint32_t)bh & kIndexTagMask;
     if (mine && any_filter) {
         // one 16-byte read per run: the tags of the key's bucket in the run's hash index, else the key's filter block
@@ -153,7 +151,15 @@ __device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const T
             }
         }
     }
-    maybe &= run_mask;
+    return maybe & run_mask;
+}
+
+// Looks one block key per lane up in the runs `maybe` (every lane of the wave calls this; lanes with mine == false idle).
+// Returns whether the key's newest version is a live PUT (true for idle lanes) and sets h to its hit record.
+template <bool kTop>
+__device__ __forceinline__ bool probe_walk(const ProbeShared<kTop>& s, uint64_t maybe, const uint64_t bh, const bool mine, const Key& q, uint4& h) {
+    bool live = !mine, found = !mine;
+    const uint32_t tag = (uint32_t)bh & kIndexTagMask;
     // every lane walks its own list of admitted runs, newest first, so lanes that need different
     // runs search them at the same time; the walk of a lane ends at the first run that holds its key
     while (__ballot(!found && maybe != 0) != 0) {
@@ -295,6 +301,14 @@ __device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const T
     return live;
 }
 
+template <bool kTop>
+__device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const TreeTable& tree, const uint32_t n_runs,
+                                             const uint64_t run_mask, const bool any_filter, const bool mine, const Key& q, uint4& h) {
+    uint64_t bh;
+    const uint64_t maybe = probe_admit(tree, n_runs, run_mask, any_filter, mine, q, bh);
+    return probe_walk<kTop>(s, maybe, bh, mine, q, h);
+}
+
 // kSpread waves share a request, 64 consecutive keys each.  What bounds a batch is the chain of dependent reads of its
 // longest request: some 16 us per 64 keys looked up one after the other.  With more waves per request the chain is shorter,
 // and the keys behind the first miss that are then looked up for nothing cost reads, but no time as long as there is room
@@ -347,6 +361,91 @@ __global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const u
             if (req < n_req && j < max_blocks) hrow[j] = h;
         }
         if (lane == 0 && wave % kSpread == 0 && req < n_req) hit_len[req] = result;
+    }
+}
+
+// Large batches on trees whose runs all have a filter or an index: one workgroup of 16 requests per compute unit, in two phases.
+// First every wave admits its request's keys, 64 at a time, up to the first key that every run rules out, which ends the
+// prefix; then the admitted keys of all 16 are looked up, shared out evenly over the threads.  What bounds a wave per request
+// (probe_kernel) is the chain of its longest requests, which look up two or three chunks of keys one after the other, while
+// the waves of requests that share nothing with the tree (30 %) are done at once; here nearly every workgroup has one round of
+// lookups, and its fence table is read once per compute unit.  4,096 requests, a wave each / pooled: 100M entries with
+// filters 62.1 / 51.4 us, with indices as well 42.8 / 38.1; 20M 50.2 / 39.4 and 36.2 / 31.4, indices only 54.2 / 42.2; 1M
+// 41.9 / 34.5.  Eight requests in 512 threads (two workgroups per compute unit) 58.8 us for the first, eight in 1,024 76.9.
+constexpr int kPoolRequests = 16;
+constexpr int kPoolThreads = 1024;
+template <bool kTop>
+__global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks, uint32_t n_req,
+                                                              uint32_t max_blocks, uint32_t* hit_len, lsm_hit_t* hits) {
+    __shared__ ProbeShared<kTop> s;
+    __shared__ uint64_t admitted[kPoolRequests * LSM_MAX_BLOCKS], hashed[kPoolRequests * LSM_MAX_BLOCKS];  // of key j of request r at r * LSM_MAX_BLOCKS + j
+    __shared__ uint32_t first_out[kPoolRequests];   // first key that every run rules out, or the request's length
+    __shared__ uint32_t first_dead[kPoolRequests];  // first key looked up that is not live
+    static_assert(kPoolRequests * kWave == kPoolThreads, "a wave admits a request's keys");
+    const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), my_r = tid / kWave;
+    const uint32_t n_runs = tree.n_runs;
+    probe_setup<kTop, kPoolThreads>(s, tree, (int)tid);
+    const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
+    for (uint32_t first_req = blockIdx.x * kPoolRequests; first_req < n_req; first_req += gridDim.x * kPoolRequests) {
+        const uint32_t req = first_req + my_r;
+        const uint32_t nb = req < n_req ? min(n_blocks[req], max_blocks) : 0;
+        const uint8_t* qrow = qkeys + (uint64_t)req * max_blocks * LSM_KEY_BYTES;
+        __syncthreads();  // the last requests' lists have been read
+        uint32_t out_at = nb;
+        for (uint32_t start = 0; start < nb; start += kWave) {
+            const uint32_t j = start + lane;
+            const bool mine = j < nb;
+            Key q = {{0, 0, 0, 0}};
+            if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
+            uint64_t bh;
+            const uint64_t maybe = probe_admit(tree, n_runs, run_mask, true, mine, q, bh);
+            if (mine) {
+                admitted[my_r * LSM_MAX_BLOCKS + j] = maybe;
+                hashed[my_r * LSM_MAX_BLOCKS + j] = bh;
+            }
+            const uint64_t out = __ballot(mine && maybe == 0);
+            if (out != 0) {
+                out_at = start + (uint32_t)__ffsll((unsigned long long)out) - 1;
+                break;
+            }
+        }
+        if (lane == 0) {
+            first_out[my_r] = out_at;
+            first_dead[my_r] = ~0u;
+        }
+        __syncthreads();
+        uint32_t from[kPoolRequests + 1];  // where a request's keys start in the list of all
+        from[0] = 0;
+#pragma unroll
+        for (int r = 0; r < kPoolRequests; r++) from[r + 1] = from[r] + first_out[r];
+        for (uint32_t i0 = 0; i0 < from[kPoolRequests]; i0 += kPoolThreads) {
+            const uint32_t i = i0 + tid;
+            const bool mine = i < from[kPoolRequests];
+            uint32_t r = 0, base = 0;
+#pragma unroll
+            for (int q = 1; q < kPoolRequests; q++)
+                if (i >= from[q]) r = q, base = from[q];
+            const uint32_t j = i - base;
+            Key q = {{0, 0, 0, 0}};
+            uint64_t maybe = 0, bh = 0;
+            if (mine) {
+                q = load_key(qkeys + ((uint64_t)(first_req + r) * max_blocks + j) * LSM_KEY_BYTES);
+                maybe = admitted[r * LSM_MAX_BLOCKS + j];
+                bh = hashed[r * LSM_MAX_BLOCKS + j];
+            }
+            uint4 h = make_uint4(0, 0, 0, 0);
+            const bool live = probe_walk<kTop>(s, maybe, bh, mine, q, h);
+            if (!live) atomicMin(&first_dead[r], j);
+            __syncthreads();
+            // the next rounds hold later keys of a request only: what they find dead does not change this
+            if (mine && j < first_dead[r]) reinterpret_cast<uint4*>(hits)[(uint64_t)(first_req + r) * max_blocks + j] = h;
+        }
+        if (req < n_req) {
+            const uint32_t result = min(out_at, first_dead[my_r]);
+            if (lane == 0) hit_len[req] = result;
+            uint4* hrow = reinterpret_cast<uint4*>(hits + (uint64_t)req * max_blocks);
+            for (uint32_t j = result + lane; j < max_blocks; j += kWave) hrow[j] = make_uint4(0, 0, 0, 0);
+        }
     }
 }
 
@@ -519,6 +618,30 @@ static uint32_t spread_for(uint32_t n_req, uint32_t max_blocks) {
 // 29.9 / 28.7, 4,096: 39.8 / 38.2.
 static int threads_for(uint32_t n_req, uint32_t spread) { return spread == 1 && n_req <= 1024 ? lsm::kProbeThreadsFew : lsm::kProbeThreads; }
 
+// Workgroups of the pooled form, 0 where it does not apply: more requests than fill the chip with two waves each (2,049 requests,
+// 1M entries with filters: 35.4 / 29.8 us; 2,048 with two waves each 24.4 against 28.6), rows of more than one chunk of keys
+// (4,096 requests on 20M entries with filters, rows of 64 keys 32.6 / 33.6 us, of 100 48.6 / 38.3), and every run ruled out by a
+// filter or an index.  One workgroup per compute unit, each striding over the requests; beyond one turn of them a tree that is indexed
+// throughout, whose workgroups read no fence table, has nothing left to gain (8,192 requests, indices and filters 40.0 / 45.9 us
+// on 1M entries; filters only 64.0 / 57.8).
+static uint32_t pool_groups(const lsm::TreeTable& tt, const lsm_queries_t& queries) {
+    int device = 0, cus = 0;
+    if (queries.n_req <= 2048 || queries.max_blocks <= (uint32_t)lsm::kWave || hipGetDevice(&device) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
+        return 0;
+    for (uint32_t r = 0; r < tt.n_runs; r++)
+        if (tt.run[r].n != 0 && tt.run[r].bloom_blocks == 0 && tt.run[r].index == nullptr) return 0;
+    const uint32_t groups = (queries.n_req - 1) / lsm::kPoolRequests + 1;
+    if (groups <= (uint32_t)cus) return groups;
+    return all_indexed(tt) ? 0 : (uint32_t)cus;
+}
+
+template <bool kTop>
+static void launch_pool(uint32_t groups, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits, hipStream_t stream) {
+    hipLaunchKernelGGL(lsm::probe_pool_kernel<kTop>, dim3(groups), dim3(lsm::kPoolThreads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req,
+                       queries->max_blocks, out_hits->hit_len, out_hits->hits);
+}
+
 template <bool kTop>
 static void launch_probe(uint32_t spread, int threads, uint32_t blocks, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits,
                          hipStream_t stream) {
@@ -526,7 +649,7 @@ static void launch_probe(uint32_t spread, int threads, uint32_t blocks, const ls
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req, queries->max_blocks,
                            out_hits->hit_len, out_hits->hits);
     };
-    if (spread == 4) launch(lsm::probe_kernel<kTop, 4, lsm::kProbeThreads>);
+if (spread == 4) launch(lsm::probe_kernel<kTop, 4, lsm::kProbeThreads>);
     else if (spread == 2) launch(lsm::probe_kernel<kTop, 2, lsm::kProbeThreads>);
     else if (threads == lsm::kProbeThreads) launch(lsm::probe_kernel<kTop, 1, lsm::kProbeThreads>);
     else launch(lsm::probe_kernel<kTop, 1, lsm::kProbeThreadsFew>);
@@ -557,7 +680,10 @@ extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, c
     const int threads = threads_for(queries->n_req, spread);
     if (rc == LSM_OK) rc = probe_grid(queries->n_req, spread, threads, blocks);
     if (rc != LSM_OK) return rc;
-    if (all_indexed(tt)) launch_probe<false>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    const uint32_t pools = pool_groups(tt, *queries);
+    if (pools != 0 && all_indexed(tt)) launch_pool<false>(pools, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    else if (pools != 0) launch_pool<true>(pools, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    else if (all_indexed(tt)) launch_probe<false>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     else launch_probe<true>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }

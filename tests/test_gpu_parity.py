@@ -520,6 +520,29 @@ def test_probe_workgroup_sizes(g, oracle, cfg1, n_req, indexed):
     assert np.array_equal(g.lsm_probe_length(q, nb, tree).cpu().numpy().astype(np.uint32), want[0])
 
 
+@pytest.mark.parametrize("n_req", [2049, 4096, 4097, 9001])  # pooled lookups: the smallest batch, one turn of the workgroups, several
+@pytest.mark.parametrize("row", [256, 65, 64])  # 64: one chunk of keys, a wave per request as before
+@pytest.mark.parametrize("ruled_out_by", ["filters", "indices", "both", "either", "tiny filters"])
+def test_probe_pooled_lookups(g, oracle, cfg1, n_req, row, ruled_out_by):
+    """Batches of more than 2,048 requests on trees whose runs all have a filter or an index, an empty run without either
+    among them; tiny filters admit every key, so that every key of every request is looked up."""
+    from workloads import lsm
+    print("pooled lookups", n_req, row, ruled_out_by, flush=True)
+    q, nb = lsm.queries_config1(cfg1, n_req, stream=row)
+    q, nb = q[:, :row].contiguous(), nb.clamp(max=row)
+    nb[::7] = 0
+    tree = build_tree(g, list(cfg1.runs) + [cfg1.runs[0][:0]])
+    for i, t in enumerate(tree[:-1]):
+        if ruled_out_by in ("filters", "both") or (ruled_out_by == "either" and i % 2 == 0):
+            t.bloom = g.lsm_build_bloom(t.run, 16)
+        if ruled_out_by == "tiny filters":
+            t.bloom = g.lsm_build_bloom(t.run, 16, out=torch.empty((1, 4), dtype=torch.int32, device=dev()))
+        if ruled_out_by in ("indices", "both") or (ruled_out_by == "either" and i % 2 == 1):
+            t.index = g.lsm_build_hash_index(g.lsm_hash_keys(t.run))
+    want = oracle.probe(q, nb, [r.cpu() for r in cfg1.runs])
+    assert_probe_equal(oracle, probe_gpu(g, q, nb, tree), want)
+
+
 # ------------------------------------------------------------------ Bloom filters
 @pytest.mark.parametrize("bits_per_key", [8, 16])
 def test_bloom_filter_bytes_equal_the_checker(g, oracle, cfg1, bits_per_key):
