@@ -2,12 +2,13 @@
 // sorted run).  Total order of the buffer's entries: key ascending, then newest first (larger seqno; equal seqnos: the
 // one written later); an entry survives unless its predecessor in that order has the same key.
 //
-// Up to kFlushDirect entries: by counting, in two launches without a clearing pass or global atomics.
+// Up to kFlushDirect entries: by counting, in two launches without a clearing pass or global atomics (one launch up to
+// kSmallEntries, flush_small_kernel).
 //   flush_rank_kernel   the number of entries that precede entry i in the total order (its rank), and whether i is
 //                       shadowed, by comparing it with every other entry;
 //   flush_place_kernel  an entry that is not shadowed goes to position rank - |{shadowed j : rank_j < rank_i}|, from a
 //                       bitmap of the shadowed ranks that every workgroup makes for itself in LDS.
-// A larger buffer is cut into segments of kFlushSegment entries in write order, every segment is sorted by one workgroup
+// A larger buffer is cut into segments of 2,048 or 4,096 entries in write order, every segment is sorted by one workgroup
 // (flush_sort_kernel), and the sorted segments are merged by the compaction kernels (the segment written last is the
 // newest run, so that among equal sequence numbers the later write wins there as well).
 #include <hip/hip_runtime.h>
@@ -24,46 +25,86 @@ __device__ __forceinline__ int key_cmp(const Key& a, const Key& b) {
 
 constexpr uint32_t kShadowed = 0x80000000u;  // flag in a packed rank
 
+// The first 16 key bytes as a 128-bit number, lowest word first.
+__device__ __forceinline__ uint4 key_head(const uint4 q) {
+    return make_uint4(__builtin_bswap32(q.w), __builtin_bswap32(q.z), __builtin_bswap32(q.y), __builtin_bswap32(q.x));
+}
+// Adds one to rank if a < b, as 128-bit numbers; returns zero only if they are equal.  One subtraction with its borrow: the
+// compiler makes three 64-bit compares and two selects of the same (64-bit compares take twice the time of these).
+__device__ __forceinline__ uint32_t count_less(const uint4 a, const uint4 b, uint32_t& rank) {
+    uint32_t d0, d1, d2, d3;
+    asm("v_sub_co_u32 %0, vcc, %5, %9\n\tv_subb_co_u32 %1, vcc, %6, %10, vcc\n\tv_subb_co_u32 %2, vcc, %7, %11, vcc\n\t"
+        "v_subb_co_u32 %3, vcc, %8, %12, vcc\n\tv_addc_co_u32 %4, vcc, 0, %4, vcc"
+        : "=&v"(d0), "=&v"(d1), "=&v"(d2), "=&v"(d3), "+v"(rank)
+        : "v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(b.x), "v"(b.y), "v"(b.z), "v"(b.w)
+        : "vcc");
+    return d0 | d1 | d2 | d3;
+}
+
+// Ranks one entry against `count` others, of which this thread takes every `slices`-th: heads[c] = the first 16 bytes of entry
+// base + c's key, padded with all ones to a multiple of 4 * slices.  The rest of a key and the seqno are read from the
+// buffer on a 16-byte tie only: an entry with itself, versions of a key.
+__device__ __forceinline__ void rank_against(const uint4* heads, const uint32_t base, const uint32_t count, const uint32_t slice, const uint32_t slices,
+                                             const lsm_entry_t* buffer, const uint32_t n, const uint32_t i, const uint4 head, const Key& key,
+                                             const uint64_t seq, uint32_t& rank, bool& shadowed) {
+    for (uint32_t c = slice; c < count; c += 4 * slices) {
+        uint4 o[4];
+        uint32_t diff[4];
+#pragma unroll
+        for (int a = 0; a < 4; a++) o[a] = heads[c + a * slices];
+#pragma unroll
+        for (int a = 0; a < 4; a++) diff[a] = count_less(o[a], head, rank);
+        if (min(min(diff[0], diff[1]), min(diff[2], diff[3])) == 0) {
+#pragma unroll
+            for (int a = 0; a < 4; a++) {
+                const uint32_t e = base + c + a * slices;
+                if (diff[a] != 0 || e == i || e >= n) continue;
+                const lsm_entry_t* other = buffer + e;
+                const int cmp = key_cmp(load_key(other), key);
+                const bool newer = cmp == 0 && (other->seqno > seq || (other->seqno == seq && e > i));
+                shadowed = shadowed || newer;
+                rank += (cmp < 0 || newer) ? 1 : 0;
+            }
+        }
+    }
+}
+
 // n^2 compares of 16-byte key halves.  A workgroup ranks only kRankEntries entries, so that a buffer of a few thousand
 // is hundreds of workgroups (one thread per entry left 15 workgroups with 3,600 serial compares each: 387 us for this
-// step on 3,600 entries, 1009 us for the whole call; now 21 us): 16 lanes hold 16 entries, and the 32 groups of 16 lanes share the other entries out, which are
-// staged in LDS (first 16 key bytes as two numbers; the lanes of a wave read four records at a time).  The rest of a key
-// and the seqno are read from the buffer on a 16-byte tie only: an entry with itself, versions of a key.
+// step on 3,600 entries): 16 lanes hold 16 entries, and the 32 groups of 16 lanes share the other entries out, which are
+// staged in LDS (the lanes of a wave read four records at a time).  Bound by the instructions of the compares: eight a pair, and
+// 15.9 -> 11.5 us for 3,600 entries, 34.4 -> 27.3 for
+// 8,192, since they are a subtraction with borrow.
 constexpr int kRankThreads = 512;
 constexpr int kRankEntries = 16;
 constexpr int kRankTile = 2048;  // records staged at a time
 __global__ void __launch_bounds__(kRankThreads) flush_rank_kernel(const lsm_entry_t* buffer, uint32_t n, uint32_t* packed) {
-    __shared__ ulonglong2 tile[kRankTile];
+    constexpr uint32_t kSlices = kRankThreads / kRankEntries;
+    static_assert(kRankTile % (4 * kSlices) == 0 && kRankTile % kRankThreads == 0, "padding of the staged records");
+    __shared__ uint4 tile[kRankTile];
     __shared__ uint32_t part[kRankThreads / kWave][kRankEntries];
-    constexpr int kSlices = kRankThreads / kRankEntries;
     const uint32_t i = blockIdx.x * kRankEntries + threadIdx.x % kRankEntries;
     const uint32_t slice = threadIdx.x / kRankEntries;
     const lsm_entry_t* me = buffer + (i < n ? i : 0);
     const Key key = load_key(me);
+    const uint4 head = key_head(*reinterpret_cast<const uint4*>(me));
     const uint64_t seq = me->seqno;
     uint32_t rank = 0;
     bool shadowed = false;
     for (uint32_t t0 = 0; t0 < n; t0 += kRankTile) {
         const uint32_t count = min((uint32_t)kRankTile, n - t0);
         __syncthreads();
-        for (uint32_t c = threadIdx.x; c < count; c += kRankThreads) {
-            const uint4 q = *reinterpret_cast<const uint4*>(buffer + t0 + c);
-            tile[c] = make_ulonglong2(__builtin_bswap64(((uint64_t)q.y << 32) | q.x), __builtin_bswap64(((uint64_t)q.w << 32) | q.z));
+        uint4 q[kRankTile / kRankThreads];
+#pragma unroll
+        for (int a = 0; a < kRankTile / kRankThreads; a++) {
+            const uint32_t c = threadIdx.x + a * kRankThreads;
+            q[a] = make_uint4(~0u, ~0u, ~0u, ~0u);
+            if (c < count) q[a] = *reinterpret_cast<const uint4*>(buffer + t0 + c);
         }
+#pragma unroll
+        for (int a = 0; a < kRankTile / kRankThreads; a++) tile[threadIdx.x + a * kRankThreads] = key_head(q[a]);
         __syncthreads();
-#pragma unroll 4
-        for (uint32_t c = slice; c < count; c += kSlices) {
-            const ulonglong2 o = tile[c];
-            const bool tie = (o.x == key.w[0]) & (o.y == key.w[1]);
-            rank += ((o.x < key.w[0]) | ((o.x == key.w[0]) & (o.y < key.w[1]))) ? 1 : 0;
-            if (tie && t0 + c != i) {
-                const lsm_entry_t* other = buffer + t0 + c;
-                const int cmp = key_cmp(load_key(other), key);
-                const bool newer = cmp == 0 && (other->seqno > seq || (other->seqno == seq && t0 + c > i));
-                shadowed = shadowed || newer;
-                rank += (cmp < 0 || newer) ? 1 : 0;
-            }
-        }
+        rank_against(tile, t0, count, slice, kSlices, buffer, n, i, head, key, seq, rank, shadowed);
     }
     // both results of the 32 slices in one word: the sums stay below 2^16 (rank) and 2^6 (slices that saw a newer version)
     uint32_t v = rank | (shadowed ? 1u << 16 : 0u);
@@ -78,8 +119,62 @@ __global__ void __launch_bounds__(kRankThreads) flush_rank_kernel(const lsm_entr
     }
 }
 
-// Up to here ranks by comparing all pairs: 8,192 entries are 67M compares, some 25 us of the whole chip, where sorting
-// segments and merging them is three dependent launches of about 15 us each.
+// A buffer of up to kSmallEntries entries in one launch of one workgroup: eight threads rank an entry, the shadowed ranks are a bitmap
+// in LDS, four threads copy an entry.  Such calls are bound by the host, which the second launch costs 2.5 us; 256 entries
+// would be longer on the GPU than in two launches (8.9 us with four threads an entry, against 7.1).
+constexpr uint32_t kSmallEntries = 128;
+constexpr int kSmallThreads = 1024;
+__global__ void __launch_bounds__(kSmallThreads) flush_small_kernel(const lsm_entry_t* buffer, uint32_t n, lsm_entry_t* out, uint64_t* n_out,
+                                                                   uint4* fence_out, uint32_t fence_stride) {
+    constexpr uint32_t kSlices = kSmallThreads / kSmallEntries;
+    static_assert(kSmallEntries % (4 * kSlices) == 0, "padding of the records");
+    __shared__ uint4 heads[kSmallEntries];
+    __shared__ uint32_t packed[kSlices][kSmallEntries];  // by slice; the first row becomes the result
+    __shared__ uint32_t bits[kSmallEntries / 32];        // bit r: the entry of rank r is shadowed
+    const uint32_t tid = threadIdx.x;
+    const uint32_t copied = tid / 4 < n ? tid / 4 : n;  // the entry that this thread copies a quarter of
+    const uint4 part = copied < n ? reinterpret_cast<const uint4*>(buffer + copied)[tid & 3] : make_uint4(0, 0, 0, 0);
+    if (tid < kSmallEntries) {
+        uint4 q = make_uint4(~0u, ~0u, ~0u, ~0u);
+        if (tid < n) q = *reinterpret_cast<const uint4*>(buffer + tid);
+        heads[tid] = key_head(q);
+    }
+    if (tid < kSmallEntries / 32) bits[tid] = 0;
+    const uint32_t i = tid % kSmallEntries, slice = tid / kSmallEntries;
+    uint32_t rank = 0;
+    bool shadowed = false;
+    __syncthreads();
+    if (i < n) {
+        const Key key = load_key(buffer + i);
+        rank_against(heads, 0, n, slice, kSlices, buffer, n, i, heads[i], key, buffer[i].seqno, rank, shadowed);
+    }
+    packed[slice][i] = rank | (shadowed ? 1u << 16 : 0u);
+    __syncthreads();
+    if (tid < n) {
+        uint32_t v = 0;
+        for (uint32_t g = 0; g < kSlices; g++) v += packed[g][tid];
+        v = (v & 0xFFFF) | ((v >> 16) != 0 ? kShadowed : 0u);
+        packed[0][tid] = v;
+        if (v & kShadowed) atomicOr(&bits[(v & 0xFFFF) >> 5], 1u << (v & 31));
+    }
+    __syncthreads();
+    const uint32_t p = copied < n ? packed[0][copied] : kShadowed;
+    uint32_t before = 0, total = 0;
+#pragma unroll
+    for (uint32_t w = 0; w < kSmallEntries / 32; w++) {
+        const uint32_t b = bits[w], c = __popc(b);
+        total += c;
+        before += w < (p & 0xFFFF) >> 5 ? c : (w == (p & 0xFFFF) >> 5 ? __popc(b & ((1u << (p & 31)) - 1)) : 0);
+    }
+    if (tid == 0) *n_out = n - total;
+    if (p & kShadowed) return;
+    const uint32_t at = p - before;
+    reinterpret_cast<uint4*>(out + at)[tid & 3] = part;
+    if (fence_out != nullptr && (tid & 3) < 2 && at % fence_stride == 0) fence_out[(at / fence_stride) * 2 + (tid & 3)] = part;
+}
+
+// Up to here ranks by comparing all pairs: 8,192 entries take 32 us, where sorting segments and merging them takes 50 us for
+// 8,193 (three dependent launches).
 constexpr uint64_t kFlushDirect = 8192;
 
 // Four lanes per entry.  Every workgroup reads all packed ranks (at most 32 KB, from the L2).
@@ -96,9 +191,14 @@ __global__ void __launch_bounds__(kPlaceThreads) flush_place_kernel(const lsm_en
     const uint32_t i = blockIdx.x * (kPlaceThreads / 4) + tid / 4;
     const uint32_t p = i < n ? packed[i] : kShadowed;
     const uint4 part = i < n ? reinterpret_cast<const uint4*>(buffer + i)[tid & 3] : make_uint4(0, 0, 0, 0);
-    for (uint32_t e = tid; e < n; e += kPlaceThreads) {
-        const uint32_t r = packed[e];
-        if (r & kShadowed) atomicOr(&bits[(r & ~kShadowed) >> 5], 1u << (r & 31));
+    constexpr int kAhead = 8;  // ranks a thread reads before it looks at the first
+    for (uint32_t e0 = tid; e0 < n; e0 += kAhead * kPlaceThreads) {
+        uint32_t r[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; a++) r[a] = e0 + a * kPlaceThreads < n ? packed[e0 + a * kPlaceThreads] : 0;
+#pragma unroll
+        for (int a = 0; a < kAhead; a++)
+            if (r[a] & kShadowed) atomicOr(&bits[(r[a] & ~kShadowed) >> 5], 1u << (r[a] & 31));
     }
     __syncthreads();
     const uint32_t count = __popc(bits[tid]);
@@ -127,26 +227,31 @@ __global__ void __launch_bounds__(kPlaceThreads) flush_place_kernel(const lsm_en
 // One workgroup sorts one segment.
 // What moves through LDS is a 16-byte record per entry: the first 14 key bytes as a 112-bit number and, below, the
 // entry's age (0 = written last), so records are distinct and versions of a key come in write order, newest write
-// first.  Every thread sorts eight consecutive records in registers, then log2(segment / 8) rounds of merge-path merges
-// double the sorted lists, a thread producing eight outputs per round from eight records of either list (bitonic
+// first.  Every thread sorts four consecutive records in registers, then log2(segment / 4) rounds of merge-path merges
+// double the sorted lists, a thread producing four outputs per round from four records of either list (bitonic
 // half-cleaner and merge network).  Positions whose 14 bytes equal a neighbour's (versions of a key, and keys that
 // differ further on) are settled afterwards by the rest of the key, seqno and age: each by comparing itself with the whole
 // group, or, where some group is long, by a merge sort of the whole segment that compares these.  Bound by LDS
-// operations of one compute unit per segment; all pairs of a segment instead (the step that this one replaced) took 936 us for
-// 100,001 entries, the whole call 1052 us against 122 us.  The entries themselves are
+// operations of one compute unit per segment; all pairs of a segment instead took 936 us for 100,001 entries, this 27.  The entries themselves are
 // read a second time for the output (they come from the L2).
 // ---------------------------------------------------------------------------------------
-constexpr uint64_t kFlushSegment = 4096;
-constexpr int kSortThreads = 512;
-constexpr int kSortItems = 8;
-static_assert(kSortThreads * kSortItems == kFlushSegment, "a segment fills the workgroup");
-static_assert(kFlushSegment * LSM_MAX_RUNS >= LSM_MAX_BUFFER, "the segments of the largest buffer must fit one compaction");
+// Short segments put more compute units to work (a segment is a serial chain on one), at the price of one merge round more and more
+// runs to find boundaries in: 100,001 entries 47.3 + 7.7 + 25.9 us (sort, partition, merge) with segments of 4,096, 27.3 + 10.4 + 30.4
+// with 2,048; segments of 1,024 (up to 65,536 entries) gain nothing more (50,000: 62.8 us in all, 60.2 with 1,024; 20,000: 55.1
+// both).  Beyond 64 short ones, the most a merge takes, long segments.  Four records per thread: with eight, half as many waves,
+// a segment of 4,096 takes 47.5 us instead of 41.8, of 2,048 37.7 instead of 27.5.
+constexpr uint64_t kLongSegment = 4096, kShortSegment = 2048;
+constexpr int kSortItems = 4;
+constexpr uint64_t kMostShort = kShortSegment * LSM_MAX_RUNS;
+static_assert(kLongSegment * LSM_MAX_RUNS >= LSM_MAX_BUFFER, "the segments of the largest buffer must fit one compaction");
 // Groups are settled by comparing their positions one by one, a serial chain of LDS reads that grows with the square of the
-// members (one group of 4,096: 10.6 ms a segment), unless two lanes next to each other have nothing but positions that
+// members (one group of 4,096: 10.6 ms a segment), unless four lanes in a row have nothing but positions that
 // share their 14 bytes with the one before: the merge sort takes about as long as the first sort whatever the groups
 // (8,193 versions of one key 128 us in all, 62 for distinct keys).  That is so for every group of 32 members and for none of 16.
 // 100,001 entries in groups of about 10 / 20 / 64 members: 164 / 181 / 313 us one by one, 174 / 170 / 166 by the merge sort.
+template <int kSortThreads>
 struct SortShared {
+    static constexpr uint32_t kFlushSegment = kSortThreads * kSortItems;
     uint4 buf[2][kFlushSegment];       // records, two sides; then the rest of the key and the seqno of tied positions
     uint16_t order[kFlushSegment];     // final position -> age
     uint16_t other[kFlushSegment];     // second side of the merge sort of tied positions
@@ -173,9 +278,9 @@ __device__ __forceinline__ void rec_order(Rec& a, Rec& b) {
     a.hi = swap ? b.hi : a.hi, a.lo = swap ? b.lo : a.lo;
     b.hi = swap ? t.hi : b.hi, b.lo = swap ? t.lo : b.lo;
 }
-// where position p sits in the 16-byte arrays: threads own eight consecutive positions (a stride of 128 bytes, one bank
-// quarter), so the positions of a group of eight are permuted by the group's number
-__device__ __forceinline__ uint32_t rec_at(uint32_t p) { return p ^ ((p >> 3) & 7); }
+// where position p sits in the 16-byte arrays: threads own four consecutive positions (a stride of 64 bytes), so the positions of
+// a group of four are permuted by the group's number
+__device__ __forceinline__ uint32_t rec_at(uint32_t p) { return p ^ ((p >> 3) & (kSortItems - 1)); }
 
 // What orders tied positions: their group (the group's first position, above key bytes 14..15), key bytes 16..31, then the
 // newest version first.
@@ -198,7 +303,8 @@ __device__ __forceinline__ bool tied_less(const Tied& a, const Tied& b) {
 
 // Merge sort of all positions of the segment by tied_less, `len` of them in use: s.order[p] becomes the age of the p-th and
 // s.lose[p] whether it is shadowed.  The whole workgroup calls; the info arrays are filled for every position.
-__device__ void flush_sort_tied(SortShared& s, const uint4* info0, const uint4* info1, const uint32_t len) {
+template <int kSortThreads>
+__device__ void flush_sort_tied(SortShared<kSortThreads>& s, const uint4* info0, const uint4* info1, const uint32_t len) {
     const uint32_t o = threadIdx.x * kSortItems;
     uint16_t *from = s.order, *to = s.other;
     for (uint32_t i = 0; i < (uint32_t)kSortItems; i++) {
@@ -248,8 +354,11 @@ __device__ void flush_sort_tied(SortShared& s, const uint4* info0, const uint4* 
     for (int i = 0; i < kSortItems; i++) s.order[o + i] = age[i];
 }
 
+template <int kSortThreads>
 __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entry_t* buffer, uint32_t n, lsm_entry_t* out, uint64_t* counts) {
-    __shared__ SortShared s;
+    __shared__ SortShared<kSortThreads> s;
+    constexpr uint32_t kFlushSegment = kSortThreads * kSortItems;
+    static_assert(kSortItems == 4, "the sorting network is written for four");
     const uint32_t tid = threadIdx.x;
     // segments are numbered newest first, the order in which the merge takes them as runs
     const uint32_t seg = gridDim.x - 1 - blockIdx.x;
@@ -275,13 +384,10 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
     Rec c[kSortItems];
 #pragma unroll
     for (int i = 0; i < kSortItems; i++) c[i] = rec_load(&s.buf[0][rec_at(o + i)]);
-    // odd-even merge sort of eight (Batcher): 19 exchanges
-    rec_order(c[0], c[1]), rec_order(c[2], c[3]), rec_order(c[4], c[5]), rec_order(c[6], c[7]);
-    rec_order(c[0], c[2]), rec_order(c[1], c[3]), rec_order(c[4], c[6]), rec_order(c[5], c[7]);
-    rec_order(c[1], c[2]), rec_order(c[5], c[6]);
-    rec_order(c[0], c[4]), rec_order(c[1], c[5]), rec_order(c[2], c[6]), rec_order(c[3], c[7]);
-    rec_order(c[2], c[4]), rec_order(c[3], c[5]);
-    rec_order(c[1], c[2]), rec_order(c[3], c[4]), rec_order(c[5], c[6]);
+    // odd-even merge sort of four (Batcher): five exchanges
+    rec_order(c[0], c[1]), rec_order(c[2], c[3]);
+    rec_order(c[0], c[2]), rec_order(c[1], c[3]);
+    rec_order(c[1], c[2]);
 #pragma unroll
     for (int i = 0; i < kSortItems; i++) rec_store(&s.buf[0][rec_at(o + i)], c[i]);
     __syncthreads();
@@ -300,7 +406,7 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
         const uint32_t a = lo, b = d - lo;
 #pragma unroll
         for (int i = 0; i < kSortItems; i++) {
-            // the eight smallest of two ascending lists of eight: element i of one against element 7 - i of the other
+            // the smallest half of two ascending lists: element i of one against the other's element as far from its end
             Rec x = {~0ull, ~0ull}, y = {~0ull, ~0ull};
             if (a + i < width) x = rec_load(&in[rec_at(sa + a + i)]);
             if (b + kSortItems - 1 - i < width) y = rec_load(&in[rec_at(sb + b + kSortItems - 1 - i)]);
@@ -333,8 +439,8 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
             prev = c[i];
         }
     }
-    const bool all_before = __shfl_up(all ? 1 : 0, 1, kWave) != 0;
-    if (all && all_before && (tid & (kWave - 1)) != 0) s.deep = 1;
+    const uint64_t full = __ballot(all);
+    if ((full & full >> 1 & full >> 2 & full >> 3) != 0) s.deep = 1;
     if (tid == 0) s.flag[kFlushSegment] = 0;
     if (__syncthreads_or(any)) {
         const bool deep = s.deep != 0;
@@ -440,15 +546,17 @@ __host__ inline size_t up256(size_t x) { return (x + 255) & ~size_t(255); }
 struct FlushLayout {
     size_t sorted, counts, compact, total;
     uint32_t segments;
+    uint64_t segment;  // entries
     uint64_t upper[LSM_MAX_RUNS];  // entries per segment, newest segment first (the order the compaction takes them in)
 };
 static FlushLayout flush_layout(uint64_t n) {
     FlushLayout l;
-    l.segments = (uint32_t)((n + kFlushSegment - 1) / kFlushSegment);
+    l.segment = n <= kMostShort ? kShortSegment : kLongSegment;
+    l.segments = (uint32_t)((n + l.segment - 1) / l.segment);
     for (uint32_t j = 0; j < LSM_MAX_RUNS; j++) l.upper[j] = 0;
     for (uint32_t g = 0; g < l.segments; g++) {
-        const uint64_t lo = g * kFlushSegment;
-        l.upper[l.segments - 1 - g] = (n - lo < kFlushSegment) ? n - lo : kFlushSegment;
+        const uint64_t lo = g * l.segment;
+        l.upper[l.segments - 1 - g] = (n - lo < l.segment) ? n - lo : l.segment;
     }
     l.sorted = 0;
     l.counts = up256(n * sizeof(lsm_entry_t));
@@ -461,7 +569,10 @@ static FlushLayout flush_layout(uint64_t n) {
 
 extern "C" size_t lsm_flush_workspace_bytes(uint64_t n) {
     if (n > LSM_MAX_BUFFER) return 0;
-    return n <= lsm::kFlushDirect ? (size_t)n * sizeof(uint32_t) : lsm::flush_layout(n).total;
+    if (n <= lsm::kFlushDirect) return (size_t)n * sizeof(uint32_t);
+    // never less than for a smaller buffer: more, shorter segments take more room to merge
+    const size_t mine = lsm::flush_layout(n).total, shorter = lsm::flush_layout(n < lsm::kMostShort ? n : lsm::kMostShort).total;
+    return mine > shorter ? mine : shorter;
 }
 
 extern "C" int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
@@ -483,6 +594,10 @@ extern "C" int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm
     uint4* fence_out = reinterpret_cast<uint4*>(out->fence_keys);
     const uint32_t fence_stride = out->fence_keys ? out->fence_stride : 1u;
     if (direct) {
+        if (n > 0 && n <= kSmallEntries) {
+            hipLaunchKernelGGL(flush_small_kernel, dim3(1), dim3(kSmallThreads), 0, stream, buffer, (uint32_t)n, out->entries, out->n_out, fence_out, fence_stride);
+            return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+        }
         uint32_t* packed = static_cast<uint32_t*>(workspace);
         const uint32_t per_block = kPlaceThreads / 4;
         if (n > 0)
@@ -496,10 +611,14 @@ extern "C" int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm
     char* base = static_cast<char*>(workspace);
     lsm_entry_t* sorted = reinterpret_cast<lsm_entry_t*>(base + l.sorted);
     uint64_t* counts = reinterpret_cast<uint64_t*>(base + l.counts);  // newest segment first
-    hipLaunchKernelGGL(flush_sort_kernel, dim3(l.segments), dim3(kSortThreads), 0, stream, buffer, (uint32_t)n, sorted, counts);
+    auto sort = [&](auto kernel, int threads) {
+        hipLaunchKernelGGL(kernel, dim3(l.segments), dim3(threads), 0, stream, buffer, (uint32_t)n, sorted, counts);
+    };
+    if (l.segment == kShortSegment) sort(flush_sort_kernel<kShortSegment / kSortItems>, kShortSegment / kSortItems);
+    else sort(flush_sort_kernel<kLongSegment / kSortItems>, kLongSegment / kSortItems);
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
     // one merge of the sorted segments, the one written last first; their lengths stay on the device
     const lsm_entry_t* ptr[LSM_MAX_RUNS];
-    for (uint32_t j = 0; j < l.segments; j++) ptr[j] = sorted + (uint64_t)(l.segments - 1 - j) * kFlushSegment;
+    for (uint32_t j = 0; j < l.segments; j++) ptr[j] = sorted + (uint64_t)(l.segments - 1 - j) * l.segment;
     return compact_device_lengths(ptr, l.upper, counts, l.segments, 0, out, base + l.compact, workspace_bytes - l.compact, stream);
 }

@@ -897,6 +897,31 @@ def test_flush_of_keys_with_common_prefixes(g, oracle, n, shared):
     assert np.array_equal(as_bytes(out[: want.shape[0]]).reshape(-1, 64), want)
 
 
+@pytest.mark.parametrize("n", [3, 127, 128, 129, 255, 8193, 131_072, 131_073])  # one launch up to 128; segments of 2,048 and, beyond 64 of them, 4,096
+@pytest.mark.parametrize("lead", [0, 14, 16])
+def test_flush_around_its_kernels(g, oracle, n, lead):
+    """Keys that share their first `lead` bytes, every third of them all ones there (what unused records hold), each written
+    about three times, seqnos that repeat."""
+    print("flush kernels", n, lead, flush=True)
+    rs = np.random.RandomState(n + lead)
+    keys = rs.randint(0, 256, size=(n // 3 + 1, 32)).astype(np.uint8)
+    keys[:, :lead] = 7
+    keys[::3, :16] = 255
+    a = np.zeros((n, 64), dtype=np.uint8)
+    a[:, :32] = keys[rs.randint(0, len(keys), size=n)]
+    rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+    rec["seqno"] = rs.randint(0, max(2, n // 2), size=n)
+    rec["type"] = (rs.rand(n) < 0.2).astype(np.uint8)
+    rec["vptr"] = np.arange(n)
+    fences = torch.full(((n + 6) // 7, 4), -1, dtype=torch.int64, device=dev())
+    out, n_out = g.lsm_flush_buffer(to_dev(a), fences=fences, fence_stride=7)
+    want = oracle.flush_buffer(a)
+    m = int(n_out.item())
+    assert m == want.shape[0]
+    assert np.array_equal(as_bytes(out[:m]).reshape(-1, 64), want)
+    assert np.array_equal(as_bytes(fences[: (m + 6) // 7]).reshape(-1, 32), oracle.build_fences(want, 7))
+
+
 WALK = 16  # members up to which a segment's groups of equal 14-byte prefixes are settled one position at a time
 
 
