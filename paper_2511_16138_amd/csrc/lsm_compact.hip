@@ -749,15 +749,16 @@ __global__ void __launch_bounds__(256) bracket_partition_kernel(RunTable rt, Wor
 // (one thread, insertion sort by the tail), and a tile with a longer group is redone by the
 // exact path below (ranks by binary search over the tile's pieces with full 32-byte compares).
 // ---------------------------------------------------------------------------------------
-enum : uint8_t { kFlagEq = 1, kFlagFullEq = 2, kFlagSurvive = 4 };
+enum : uint8_t { kFlagEq = 1, kFlagFullEq = 2 };
+constexpr uint32_t kNoSlot = 0xFFFF;          // of an entry that does not survive
 constexpr int kRepairMax = 32;                // longest prefix-tie group one thread puts in key order
 constexpr int kStageEntries = kTileCap / 2;  // output staging: 64 bytes per survivor, two passes at most
 
 struct MergeShared {
     uint4 buf[2][kTileCap];          // surrogate ping-pong; then 2 x uint4 of key tail/seqno/type per position; then output staging
     uint16_t rank[kTileCap];         // tile-local entry index -> merged position
-    uint16_t prefix[kTileCap];       // survivors before this merged position
-    alignas(4) uint8_t flag[kTileCap + 8];  // per merged position: kFlagEq | kFlagFullEq | kFlagSurvive
+    alignas(8) uint16_t prefix[kTileCap];  // survivors before this merged position, kNoSlot if its entry does not survive
+    alignas(4) uint8_t flag[kTileCap + 8];  // per merged position: kFlagEq | kFlagFullEq; on the exact path: 1 = survives
     uint32_t seg[LSM_MAX_RUNS + 1];  // start of each run's piece in tile-local index space
     uint64_t lo[LSM_MAX_RUNS];       // first entry of each run's piece
     const lsm_entry_t* run[LSM_MAX_RUNS];  // copy of the run pointers (indexed per lane)
@@ -1273,6 +1274,7 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         }
     }
 
+    uint32_t survive = 0;  // bit i: the entry at this thread's position i is an output entry
     if (s.inexact != 2) {
         // ---- survivors: newest version of each key (largest seqno, ties to the earlier = lower run),
         //      minus winning tombstones when the output is the last level.  Groups of equal keys are short and
@@ -1293,7 +1295,6 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                 seq[i] = ((uint64_t)me.y << 32) | me.x;
                 type[i] = me.z & 0xFF;
             }
-            uint32_t g = f;
 #pragma unroll
             for (int i = 0; i < kMergeItems; i++) {
                 bool win = true, chain = true;
@@ -1319,9 +1320,8 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                         if ((((uint64_t)v.y << 32) | v.x) > seq[i]) win = false;
                     }
                 if (win && (flags & LSM_BOTTOMMOST) && type[i] == LSM_TOMBSTONE) win = false;
-                if (win && o0 + i < n) g |= (uint32_t)kFlagSurvive << (8 * i);
+                if (win && o0 + i < n) survive |= 1u << i;
             }
-            if (g != f) *reinterpret_cast<uint32_t*>(&s.flag[o0]) = g;
         }
     } else {
         // ---- exact path: merged position and winner of every entry by binary search over the
@@ -1368,35 +1368,37 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                 }
                 if (win && (flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) win = false;
                 pos[i] = p;
-                if (win) s.flag[p] = kFlagSurvive;
+                if (win) s.flag[p] = 1;
             }
         }
+        __syncthreads();
+        if (tid * kMergeItems < n) {
+            const uint32_t f = *reinterpret_cast<const uint32_t*>(&s.flag[tid * kMergeItems]);
+#pragma unroll
+            for (int i = 0; i < kMergeItems; i++) survive |= tid * kMergeItems + i < n ? ((f >> (8 * i)) & 1) << i : 0;
+        }
     }
-    __syncthreads();
 
     // ---- survivors before each merged position (block-wide exclusive prefix sum in position order)
     uint32_t total = 0;
     {
-        const uint32_t o0 = tid * kMergeItems;
-        uint32_t my_count = 0;
-        for (uint32_t o = o0; o < min(o0 + (uint32_t)kMergeItems, n); o++) my_count += (s.flag[o] & kFlagSurvive) ? 1 : 0;
-        uint32_t incl = my_count;
-        for (int off = 1; off < kWave; off <<= 1) {
-            uint32_t v = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += v;
-        }
+        const uint32_t mine = __popc(survive), incl = wave_scan_u32(mine);
         if (lane == kWave - 1) s.wave_count[wave] = incl;
         __syncthreads();
-        uint32_t before = incl - my_count;
+        uint32_t before = incl - mine;
+#pragma unroll
         for (int w = 0; w < kMergeThreads / kWave; w++) {
             const uint32_t c = s.wave_count[w];
-            if (w < wave) before += c;
+            before += w < wave ? c : 0;
             total += c;
         }
-        for (uint32_t o = o0; o < min(o0 + (uint32_t)kMergeItems, n); o++) {
-            s.prefix[o] = (uint16_t)before;
-            before += (s.flag[o] & kFlagSurvive) ? 1 : 0;
+        uint32_t slot[kMergeItems];
+#pragma unroll
+        for (int i = 0; i < kMergeItems; i++) {
+            slot[i] = (survive >> i) & 1 ? before : kNoSlot;
+            before += (survive >> i) & 1;
         }
+        *reinterpret_cast<uint2*>(&s.prefix[tid * kMergeItems]) = make_uint2(slot[0] | slot[1] << 16, slot[2] | slot[3] << 16);
     }
 
     __syncthreads();  // prefix[] complete, last reads of info[] done: the staging area is free
@@ -1430,14 +1432,15 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
 #pragma unroll
         for (int i = 0; i < kMergeItems; i++) {
             const uint32_t e = tid + i * kMergeThreads;
-            if (e < n && (s.flag[pos[i]] & kFlagSurvive)) {
+            const uint32_t at = e < n ? s.prefix[pos[i]] : kNoSlot;
+            if (at != kNoSlot) {
                 // pointer rewrite for merged tensor files (paper section 3.4): vptr = base[file] + offset
                 if (kExtras && first == 0 && remap_files != 0 && (ent[i][2].z & 0xFF) == LSM_PUT && ent[i][3].y < remap_files) {
                     const uint64_t v = remap_base[ent[i][3].y] + ent[i][3].x;
                     ent[i][3].x = (uint32_t)v;
                     ent[i][3].y = (uint32_t)(v >> 32);
                 }
-                const uint32_t slot = (uint32_t)s.prefix[pos[i]] - first;  // wraps for slots before this pass
+                const uint32_t slot = at - first;  // wraps for slots before this pass
                 if (slot < (uint32_t)kStageEntries) {
 #pragma unroll
                     for (int part = 0; part < 4; part++) stage[slot * 4 + (part ^ (slot & 3))] = ent[i][part];
@@ -1462,12 +1465,16 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         uint4* dst = reinterpret_cast<uint4*>(out + base + first);
         for (uint32_t c = tid; c < count * 4; c += kMergeThreads) {
             const uint32_t part = (c ^ (c >> 2)) & 3;  // which 16 bytes of the entry stage[c] holds
-            const uint4 v = stage[c];
-            dst[(c & ~3u) | part] = v;
-            // fence index of the new run: the key of every fence_stride-th output entry
-            if (kExtras && fence_out != nullptr && part < 2) {
-                const uint64_t at = base + first + (c >> 2);
-                if (at % fence_stride == 0) fence_out[(at / fence_stride) * 2 + part] = v;
+            dst[(c & ~3u) | part] = stage[c];
+        }
+        if (kExtras && fence_out != nullptr) {
+            // fence index of the new run: the key of every fence_stride-th output entry.  The first one of this pass is the only
+            // division (one per output entry was XX)
+            const uint64_t fence = (base + first + fence_stride - 1) / fence_stride;
+            const uint64_t skip = fence * fence_stride - (base + first);  // entries before it
+            for (uint64_t q = tid; skip + (q >> 1) * fence_stride < count; q += kMergeThreads) {
+                const uint32_t slot = (uint32_t)(skip + (q >> 1) * fence_stride), part = q & 1;
+                fence_out[fence * 2 + q] = stage[slot * 4 + (part ^ (slot & 3))];
             }
         }
         if (kExtras == 2 && kMode == kModeSingle && ma.key_hashes != nullptr) {
