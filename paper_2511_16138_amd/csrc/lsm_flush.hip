@@ -29,16 +29,33 @@ constexpr uint32_t kShadowed = 0x80000000u;  // flag in a packed rank
 __device__ __forceinline__ uint4 key_head(const uint4 q) {
     return make_uint4(__builtin_bswap32(q.w), __builtin_bswap32(q.z), __builtin_bswap32(q.y), __builtin_bswap32(q.x));
 }
-// Adds one to rank if a < b, as 128-bit numbers; returns zero only if they are equal.  One subtraction with its borrow: the
-// compiler makes three 64-bit compares and two selects of the same (64-bit compares take twice the time of these).
-__device__ __forceinline__ uint32_t count_less(const uint4 a, const uint4 b, uint32_t& rank) {
-    uint32_t d0, d1, d2, d3;
-    asm("v_sub_co_u32 %0, vcc, %5, %9\n\tv_subb_co_u32 %1, vcc, %6, %10, vcc\n\tv_subb_co_u32 %2, vcc, %7, %11, vcc\n\t"
-        "v_subb_co_u32 %3, vcc, %8, %12, vcc\n\tv_addc_co_u32 %4, vcc, 0, %4, vcc"
-        : "=&v"(d0), "=&v"(d1), "=&v"(d2), "=&v"(d3), "+v"(rank)
-        : "v"(a.x), "v"(a.y), "v"(a.z), "v"(a.w), "v"(b.x), "v"(b.y), "v"(b.z), "v"(b.w)
-        : "vcc");
-    return d0 | d1 | d2 | d3;
+// Adds to rank how many of the four numbers o[] are below `head`, all as 128-bit numbers; diff[i] is zero only if o[i] is equal to
+// it.  One subtraction with borrow each, where the compiler makes three 64-bit compares and two selects of the same (64-bit
+// compares take twice the time of these).  The four chains are interleaved: a vector instruction may read a carry that another
+// one has written only two instructions later.
+__device__ __forceinline__ void count_less(const uint4 (&o)[4], const uint4 head, uint32_t& rank, uint32_t (&diff)[4]) {
+    uint32_t a0, a1, a2, a3, b0, b1, b2, b3, c0, c1, c2, c3, d0, d1, d2, d3;
+    uint64_t ca, cb, cc, cd;  // borrows
+    asm("v_sub_co_u32_e64 %[a0], %[ca], %[ax], %[hx]\n\tv_sub_co_u32_e64 %[b0], %[cb], %[bx], %[hx]\n\t"
+        "v_sub_co_u32_e64 %[c0], %[cc], %[cx], %[hx]\n\tv_sub_co_u32_e64 %[d0], %[cd], %[dx], %[hx]\n\t"
+        "v_subb_co_u32_e64 %[a1], %[ca], %[ay], %[hy], %[ca]\n\tv_subb_co_u32_e64 %[b1], %[cb], %[by], %[hy], %[cb]\n\t"
+        "v_subb_co_u32_e64 %[c1], %[cc], %[cy], %[hy], %[cc]\n\tv_subb_co_u32_e64 %[d1], %[cd], %[dy], %[hy], %[cd]\n\t"
+        "v_subb_co_u32_e64 %[a2], %[ca], %[az], %[hz], %[ca]\n\tv_subb_co_u32_e64 %[b2], %[cb], %[bz], %[hz], %[cb]\n\t"
+        "v_subb_co_u32_e64 %[c2], %[cc], %[cz], %[hz], %[cc]\n\tv_subb_co_u32_e64 %[d2], %[cd], %[dz], %[hz], %[cd]\n\t"
+        "v_subb_co_u32_e64 %[a3], %[ca], %[aw], %[hw], %[ca]\n\tv_subb_co_u32_e64 %[b3], %[cb], %[bw], %[hw], %[cb]\n\t"
+        "v_subb_co_u32_e64 %[c3], %[cc], %[cw], %[hw], %[cc]\n\tv_subb_co_u32_e64 %[d3], %[cd], %[dw], %[hw], %[cd]\n\t"
+        "v_addc_co_u32_e64 %[rank], %[ca], 0, %[rank], %[ca]\n\tv_addc_co_u32_e64 %[rank], %[cb], 0, %[rank], %[cb]\n\t"
+        "v_addc_co_u32_e64 %[rank], %[cc], 0, %[rank], %[cc]\n\tv_addc_co_u32_e64 %[rank], %[cd], 0, %[rank], %[cd]\n\ts_nop 1"
+        : [a0] "=&v"(a0), [a1] "=&v"(a1), [a2] "=&v"(a2), [a3] "=&v"(a3), [b0] "=&v"(b0), [b1] "=&v"(b1), [b2] "=&v"(b2), [b3] "=&v"(b3),
+          [c0] "=&v"(c0), [c1] "=&v"(c1), [c2] "=&v"(c2), [c3] "=&v"(c3), [d0] "=&v"(d0), [d1] "=&v"(d1), [d2] "=&v"(d2), [d3] "=&v"(d3),
+          [ca] "=&s"(ca), [cb] "=&s"(cb), [cc] "=&s"(cc), [cd] "=&s"(cd), [rank] "+v"(rank)
+        : [ax] "v"(o[0].x), [ay] "v"(o[0].y), [az] "v"(o[0].z), [aw] "v"(o[0].w), [bx] "v"(o[1].x), [by] "v"(o[1].y), [bz] "v"(o[1].z), [bw] "v"(o[1].w),
+          [cx] "v"(o[2].x), [cy] "v"(o[2].y), [cz] "v"(o[2].z), [cw] "v"(o[2].w), [dx] "v"(o[3].x), [dy] "v"(o[3].y), [dz] "v"(o[3].z), [dw] "v"(o[3].w),
+          [hx] "v"(head.x), [hy] "v"(head.y), [hz] "v"(head.z), [hw] "v"(head.w));
+    diff[0] = a0 | a1 | a2 | a3;
+    diff[1] = b0 | b1 | b2 | b3;
+    diff[2] = c0 | c1 | c2 | c3;
+    diff[3] = d0 | d1 | d2 | d3;
 }
 
 // Ranks one entry against `count` others, of which this thread takes every `slices`-th: heads[c] = the first 16 bytes of entry
@@ -52,8 +69,7 @@ __device__ __forceinline__ void rank_against(const uint4* heads, const uint32_t 
         uint32_t diff[4];
 #pragma unroll
         for (int a = 0; a < 4; a++) o[a] = heads[c + a * slices];
-#pragma unroll
-        for (int a = 0; a < 4; a++) diff[a] = count_less(o[a], head, rank);
+        count_less(o, head, rank, diff);
         if (min(min(diff[0], diff[1]), min(diff[2], diff[3])) == 0) {
 #pragma unroll
             for (int a = 0; a < 4; a++) {
