@@ -1469,7 +1469,8 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         }
         if (kExtras && fence_out != nullptr) {
             // fence index of the new run: the key of every fence_stride-th output entry.  The first one of this pass is the only
-            // division (one per output entry was XX)
+            // division: one per output entry, and flags read byte by byte for the prefix sum above, cost the merge of 2M + 20M
+            // entries 29 us of 704
             const uint64_t fence = (base + first + fence_stride - 1) / fence_stride;
             const uint64_t skip = fence * fence_stride - (base + first);  // entries before it
             for (uint64_t q = tid; skip + (q >> 1) * fence_stride < count; q += kMergeThreads) {
