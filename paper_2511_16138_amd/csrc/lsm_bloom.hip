@@ -42,17 +42,38 @@ struct BloomJobs {
     uint32_t n_blocks[kRuns];
 };
 
-__global__ void bloom_clear_batch_kernel(BloomJobs<kBloomBatch> jobs) {
+// What the kernels are told of the runs beside their jobs: nothing, or that the lengths in the jobs are upper bounds and the true
+// ones are in device memory, in tile status words.
+struct KnownLengths {
+    __device__ __forceinline__ void look_up(uint32_t, uint64_t&, uint32_t&) const {}
+};
+template <uint32_t kRuns>
+struct CountedLengths {
+    const uint64_t* status[kRuns];
+    uint32_t bits[kRuns];
+    __device__ __forceinline__ void look_up(uint32_t run, uint64_t& n, uint32_t& n_blocks) const {
+        const uint64_t word = *status[run], counted = word & kStValueMask;
+        n = (word >> kStShift) != kStPrefix ? 0 : (counted < n ? counted : n);
+        const uint32_t blocks = (uint32_t)((n * bits[run] + 127) / 128);  // as lsm_bloom_blocks
+        n_blocks = blocks == 0 ? 1 : blocks;
+    }
+};
+
+template <uint32_t kRuns>
+__global__ void bloom_clear_batch_kernel(BloomJobs<kRuns> jobs) {
     uint4* blocks = reinterpret_cast<uint4*>(jobs.words[blockIdx.y]);
     const uint64_t n_blocks = jobs.n_blocks[blockIdx.y], stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_blocks; i += stride) blocks[i] = make_uint4(0, 0, 0, 0);
 }
 
-__global__ void bloom_insert_batch_kernel(BloomJobs<kBloomBatch> jobs) {
+template <uint32_t kRuns, typename Lengths>
+__global__ void bloom_insert_batch_kernel(BloomJobs<kRuns> jobs, Lengths lengths) {
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
     uint32_t* words = jobs.words[blockIdx.y];
-    const uint64_t n = jobs.n[blockIdx.y], stride = (uint64_t)gridDim.x * blockDim.x;
-    const uint32_t n_blocks = jobs.n_blocks[blockIdx.y];
+    const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
+    uint64_t n = jobs.n[blockIdx.y];
+    uint32_t n_blocks = jobs.n_blocks[blockIdx.y];
+    lengths.look_up(blockIdx.y, n, n_blocks);
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         uint4 mask;
         const uint32_t block = bloom_block(bloom_hash(load_key(entries + i), mask), n_blocks);
@@ -82,16 +103,18 @@ __device__ __forceinline__ void bloom_set_lds(uint32_t* block, uint64_t h) {
 constexpr uint32_t kBloomSmallBlocks = 8192;
 constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a filter is left to the atomics
 constexpr int kBloomSmallThreads = 1024;
-template <uint32_t kBlocks, int kAhead, uint32_t kRuns>
-__global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs<kRuns> jobs) {
+template <uint32_t kBlocks, int kAhead, uint32_t kRuns, typename Lengths>
+__global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs<kRuns> jobs, Lengths lengths) {
     __shared__ uint4 blocks[kBlocks];
     uint32_t* f = reinterpret_cast<uint32_t*>(blocks);
     uint64_t* words = reinterpret_cast<uint64_t*>(blocks);
     constexpr uint32_t kShare = kAhead * kBloomSmallThreads;
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
-    const uint64_t n = jobs.n[blockIdx.y], first = (uint64_t)blockIdx.x * kShare;
-    if (blockIdx.x > 0 && first >= n) return;             // a shorter run than the longest of the batch
-    const uint32_t n_blocks = jobs.n_blocks[blockIdx.y];  // <= kBlocks (checked by the host)
+    const uint64_t first = (uint64_t)blockIdx.x * kShare;
+    uint64_t n = jobs.n[blockIdx.y];
+    uint32_t n_blocks = jobs.n_blocks[blockIdx.y];  // <= kBlocks (checked by the host)
+    lengths.look_up(blockIdx.y, n, n_blocks);       // no more than that
+    if (blockIdx.x > 0 && first >= n) return;       // a shorter run than the longest of the batch
     // all keys of a thread are read before the first is hashed
     Key key[kAhead];
 #pragma unroll
@@ -125,8 +148,8 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
 // against 7.0, 5,000 8.2 against 7.1.  Calls for many runs are bound by the host, which the second launch costs 2.5 us (one run
 // of 5,000 keys 8.7 against 11.4, of 8,192 12.1 against 12.4).
 constexpr uint64_t kOneLaunch = 4 * kBloomSmallThreads, kOneLaunchBatch = 8 * kBloomSmallThreads;
-template <uint32_t kRuns>
-static void launch_bloom_small(const BloomJobs<kRuns>& jobs, uint32_t count, bool cleared, uint64_t one_launch, hipStream_t stream) {
+template <uint32_t kRuns, typename Lengths>
+static void launch_bloom_small(const BloomJobs<kRuns>& jobs, const Lengths& lengths, uint32_t count, bool cleared, uint64_t one_launch, hipStream_t stream) {
     uint64_t most_keys = 0, all_keys = 0;
     uint32_t most_blocks = 0;
     for (uint32_t j = 0; j < count; j++) {
@@ -142,14 +165,14 @@ static void launch_bloom_small(const BloomJobs<kRuns>& jobs, uint32_t count, boo
         if constexpr (kRuns == 1)
             hipLaunchKernelGGL(bloom_clear_kernel, dim3((most_blocks + 255) / 256), dim3(256), 0, stream, reinterpret_cast<uint4*>(jobs.words[0]), (uint64_t)most_blocks);
         else
-            hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
+            hipLaunchKernelGGL(bloom_clear_batch_kernel<kRuns>, dim3((most_blocks + 255) / 256, count), dim3(256), 0, stream, jobs);
     }
     auto launch = [&](auto blocks) {
         constexpr uint32_t kBlocks = decltype(blocks)::value;
-        if (ahead == 8) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 8, kRuns>), grid, threads, 0, stream, jobs);
-        else if (ahead == 4) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 4, kRuns>), grid, threads, 0, stream, jobs);
-        else if (ahead == 2) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 2, kRuns>), grid, threads, 0, stream, jobs);
-        else hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 1, kRuns>), grid, threads, 0, stream, jobs);
+        if (ahead == 8) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 8, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
+        else if (ahead == 4) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 4, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
+        else if (ahead == 2) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 2, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
+        else hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 1, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
     };
     if (most_blocks > kBloomSmallBlocks / 2) launch(std::integral_constant<uint32_t, kBloomSmallBlocks>{});
     else launch(std::integral_constant<uint32_t, kBloomSmallBlocks / 2>{});
@@ -253,7 +276,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
         jobs.n[0] = run->n;
         jobs.words[0] = static_cast<uint32_t*>(filter_out);
         jobs.n_blocks[0] = (uint32_t)n_blocks;
-        launch_bloom_small(jobs, 1, false, kOneLaunch, stream);
+        launch_bloom_small(jobs, KnownLengths(), 1, false, kOneLaunch, stream);
         return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
     uint64_t clear_blocks = (n_blocks + 255) / 256;
@@ -278,13 +301,15 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
         for (uint32_t j = 0; j <= n_runs; j++) {
             if (count == kBloomBatch || (j == n_runs && count > 0)) {
                 if (large == 0) {
-                    launch_bloom_small(jobs, count, cleared, kOneLaunchBatch, stream);
+                    launch_bloom_small(jobs, KnownLengths(), count, cleared, kOneLaunchBatch, stream);
                 } else {
                     uint64_t cx = (most_blocks + 255) / 256, ix = (most_entries + 255) / 256;
                     if (cx > 1024) cx = 1024;
                     if (ix > 4096) ix = 4096;
-                    if (!cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel, dim3((uint32_t)cx, count), dim3(256), 0, stream, jobs);
-                    if (most_entries > 0) hipLaunchKernelGGL(bloom_insert_batch_kernel, dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs);
+                    if (!cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel<kBloomBatch>, dim3((uint32_t)cx, count), dim3(256), 0, stream, jobs);
+                    if (most_entries > 0)
+                        hipLaunchKernelGGL((bloom_insert_batch_kernel<kBloomBatch, KnownLengths>), dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs,
+                                           KnownLengths());
                 }
                 jobs = {};
                 count = 0, most_blocks = 1, most_entries = 0;
@@ -300,6 +325,47 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
             count++;
         }
     }
+    return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+}
+}  // namespace lsm
+
+namespace lsm {
+template <uint32_t kRuns>
+static void launch_counted(const CountedFilter* filters, uint32_t count, hipStream_t stream) {
+    // a launch takes filters of one kind, as above
+    for (int large = 0; large < 2; large++) {
+        BloomJobs<kRuns> jobs = {};
+        CountedLengths<kRuns> lengths = {};
+        uint32_t taken = 0;
+        uint64_t most = 0;
+        for (uint32_t j = 0; j < count; j++) {
+            const CountedFilter& f = filters[j];
+            const uint64_t blocks = lsm_bloom_blocks(f.most, f.bits);
+            if ((blocks > kBloomSmallBlocks || f.most > kBloomSmallKeys) != (large == 1)) continue;
+            jobs.entries[taken] = f.entries;
+            jobs.n[taken] = f.most;
+            jobs.words[taken] = static_cast<uint32_t*>(f.filter);
+            jobs.n_blocks[taken] = (uint32_t)blocks;
+            lengths.status[taken] = f.status;
+            lengths.bits[taken] = f.bits;
+            most = f.most > most ? f.most : most;
+            taken++;
+        }
+        if (taken == 0) continue;
+        if (large == 0) {
+            launch_bloom_small(jobs, lengths, taken, true, kOneLaunchBatch, stream);
+        } else {
+            const uint64_t blocks = (most + 255) / 256;
+            hipLaunchKernelGGL((bloom_insert_batch_kernel<kRuns, CountedLengths<kRuns>>), dim3((uint32_t)(blocks > 4096 ? 4096 : blocks), taken), dim3(256), 0,
+                               stream, jobs, lengths);
+        }
+    }
+}
+int build_filters_counted(const CountedFilter* filters, uint32_t count, hipStream_t stream) {
+    constexpr uint32_t kRuns = 16;  // a smaller argument block than that of a batch
+    if (count == 1) launch_counted<1>(filters, 1, stream);
+    else
+        for (uint32_t j = 0; j < count; j += kRuns) launch_counted<kRuns>(filters + j, count - j < kRuns ? count - j : kRuns, stream);
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
 }  // namespace lsm

@@ -189,6 +189,11 @@ constexpr uint32_t kIndexNoEntry = 0xFFFFFFFFu;
 constexpr uint32_t kIndexTagMask = 0x7FFFu;
 __host__ __device__ inline uint64_t index_buckets(uint64_t n) { return n ? (n + 3) / 4 : 1; }
 
+// Tile status word of a compaction: top two bits = state, low 62 bits = value.  The last tile's holds the number of output entries.
+constexpr uint64_t kStEmpty = 0, kStAggregate = 1, kStPrefix = 2, kStFailed = 3;
+constexpr int kStShift = 62;
+constexpr uint64_t kStValueMask = (1ull << kStShift) - 1;
+
 // Run descriptors passed to kernels by value.
 struct RunTable {
     const lsm_entry_t* ptr[LSM_MAX_RUNS];
@@ -202,8 +207,13 @@ __device__ __forceinline__ uint64_t run_len(const RunTable& rt, uint32_t j) { re
 struct ClearSpan {  // device memory to be zeroed by a launch that is made anyway; 16-byte aligned
     void* p = nullptr;
     size_t bytes = 0;  // a multiple of 16
+    // not 0: the span is for the Bloom filter of the compaction's output, which is to be built there as well, with so many bits
+    // per key; filter_built says whether the launch for it has been made
+    uint32_t filter_bits = 0;
+    mutable bool filter_built = false;
 };
-// lsm_compact and lsm_compact_batch that also zero a span (per job).  *cleared: whether lsm_compact had a launch to do it in.
+// lsm_compact and lsm_compact_batch that also zero a span (per job), and build a filter in it.  *cleared: whether lsm_compact had
+// a launch to zero it in.
 int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
                      const ClearSpan& clear, bool* cleared, hipStream_t stream);
 int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, const ClearSpan* clear, hipStream_t stream);
@@ -221,6 +231,16 @@ int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t fence_stride, hi
 int probe_stats(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket, hipStream_t stream);
 // lsm_build_bloom_batch; `cleared`: the filters are known to be all zero.
 int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t stream);
+// Filters, on memory that is zero, of runs whose lengths are on the device: a tile status word (the last of a compaction), and no
+// more than `most`.  A run whose compaction failed gets none.
+struct CountedFilter {
+    const lsm_entry_t* entries;
+    uint64_t most;
+    const uint64_t* status;
+    void* filter;
+    uint32_t bits;
+};
+int build_filters_counted(const CountedFilter* filters, uint32_t count, hipStream_t stream);
 // Compaction of runs whose exact lengths are only known on the device (n_upper[j] >= n_dev[j]; launch sizes come from
 // the upper bounds, surplus tiles stay empty).  Needs a workspace of lsm_compact_workspace_bytes(n_upper, k) bytes.
 int compact_device_lengths(const lsm_entry_t* const* ptr, const uint64_t* n_upper, const uint64_t* n_dev, uint32_t k, uint32_t flags,

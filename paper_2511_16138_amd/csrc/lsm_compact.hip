@@ -69,11 +69,6 @@ constexpr uint64_t kSampleStride = 32;                 // one key in 32 is copie
 constexpr uint64_t kSampledMinTiles = 2048;            // inputs of fewer tiles search the runs directly (measured crossover)
 constexpr uint32_t kSpinLimit = 1u << 22;              // polls of one look-back window before giving up
 
-// Tile status word: top two bits = state, low 62 bits = value.
-constexpr uint64_t kStEmpty = 0, kStAggregate = 1, kStPrefix = 2, kStFailed = 3;
-constexpr int kStShift = 62;
-constexpr uint64_t kStValueMask = (1ull << kStShift) - 1;
-
 struct Header {  // first 256 bytes of the workspace
     uint32_t unused;
     uint32_t validate_status;
@@ -1775,6 +1770,11 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     if (ev && ev->after_merge && hipEventRecord(static_cast<hipEvent_t>(ev->after_merge), stream) != hipSuccess)
         return LSM_ERR_HIP;
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
+    if (ws.clear_n != 0 && clear.filter_bits != 0) {
+        const CountedFilter filter = {out->entries, total, ws.status + n_tiles - 1, clear.p, clear.filter_bits};
+        if (build_filters_counted(&filter, 1, stream) != LSM_OK) return LSM_ERR_HIP;
+        clear.filter_built = true;
+    }
     if (flags & LSM_VALIDATE) {
         uint64_t n = 0;
         if (hipMemcpyAsync(&n, out->n_out, sizeof(n), hipMemcpyDeviceToHost, stream) != hipSuccess) return LSM_ERR_HIP;
@@ -2087,7 +2087,22 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
     else
         hipLaunchKernelGGL((merge_kernel<0, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
                            (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
-    return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
+    if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
+    for (uint32_t j = 0; clear != nullptr && j < n_jobs;) {
+        CountedFilter filters[kInlineJobs];
+        const uint32_t first = j;
+        uint32_t count = 0;
+        for (; j < n_jobs && count < kInlineJobs; j++) {
+            const JobDesc& d = desc[j];
+            if (d.clear_n == 0 || clear[j].filter_bits == 0) continue;
+            uint64_t total = 0;
+            for (uint32_t r = 0; r < d.k; r++) total += run_n[d.run_off + r];
+            filters[count++] = CountedFilter{d.out, total, ws.status + d.first_tile + d.n_tiles - 1, clear[j].p, clear[j].filter_bits};
+        }
+        if (count != 0 && build_filters_counted(filters, count, stream) != LSM_OK) return LSM_ERR_HIP;
+        for (uint32_t q = first; q < j; q++) clear[q].filter_built = desc[q].clear_n != 0 && clear[q].filter_bits != 0;
+    }
+    return LSM_OK;
 }
 }  // namespace lsm
 

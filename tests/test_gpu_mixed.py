@@ -445,3 +445,38 @@ def test_flush_many_when_one_tree_fails(oracle):
         assert hits[r, :n].cpu().numpy().tobytes() == np.asarray(want_hits)[r, :n].tobytes()
     good.flush(to_dev(run_of(range(150, 180))))  # the tree goes on
     assert good.levels()[0][2] == 1
+
+
+@pytest.mark.parametrize("buffer_entries,trees", [(300, 1), (1500, 1), (3600, 1), (9000, 1), (40, 2), (1500, 18), (9000, 3)])
+@pytest.mark.parametrize("bits", [3, 16, 64])
+def test_filters_of_driver_runs_byte_for_byte(oracle, buffer_entries, trees, bits):
+    """Every run of a live tree has the filter of its entries whenever a flush has returned: filters built right behind the
+    merge (in LDS, one share and several, two sizes, and with atomics), those of runs that may move down, and those of flushed runs;
+    a third of all writes repeat keys or delete, so that lengths fall short of their upper bounds."""
+    from paper_2511_16138_amd import LsmDriver, lsm_driver_flush_many
+    print("driver filters", buffer_entries, trees, bits, flush=True)
+    rs = np.random.RandomState(buffer_entries + bits)
+    drivers = [LsmDriver(buffer_entries, size_ratio=4, window_ops=1 << 30, bloom_bits=bits) for _ in range(trees)]
+    seq = 0
+    for step in range(7):
+        runs = []
+        for _ in drivers:
+            lead = np.unique(rs.randint(0, buffer_entries * 12, size=buffer_entries))
+            a = np.zeros((len(lead), 64), dtype=np.uint8)
+            a[:, :8] = lead.astype(">u8").view(np.uint8).reshape(-1, 8)
+            rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+            rec["seqno"] = seq + np.arange(len(lead))
+            rec["type"] = rs.rand(len(lead)) < 0.2
+            seq += len(lead)
+            runs.append(torch.from_numpy(a.view(np.int64).reshape(-1, 8)).to(dev()))
+        if trees == 1:
+            drivers[0].flush(runs[0])
+        else:
+            lsm_driver_flush_many(drivers, runs)
+        for d in drivers[:: max(1, trees // 3)]:
+            for t in d.tree():
+                n, blocks = int(t.run.n), int(t.bloom.n_blocks)
+                assert n > 0 and blocks == oracle.bloom_blocks(n, bits)
+                entries = d.read(t.run.entries, n, 8).cpu()
+                got = d.read(t.bloom.blocks, blocks, 2).cpu().numpy().view(np.uint8).reshape(-1, 16)
+                assert np.array_equal(got, oracle.build_bloom(entries, blocks)), (step, n, blocks)
