@@ -2,7 +2,7 @@
 //
 // Kernels, on one stream:
 //   init_kernel       clears the per-call scratch (tile status words) and writes the
-//                     first and last partition rows (inputs of fewer than 2,048 tiles: done by
+//                     first and last partition rows (where the runs are searched directly: done by
 //                     the partition launch instead; an input of one tile needs neither).
 //   partition         multi-sequence selection over the k runs for every interior tile
 //                     boundary.  For target rank r it finds the key x with the largest
@@ -13,9 +13,9 @@
 //                     Inputs of up to 512 tiles take sample keys as boundaries instead of exact
 //                     ranks (partition_ranked_kernel: tile sizes vary, within the capacity).
 //                     Larger ones search the runs directly, one wave per boundary
-//                     (partition_kernel, partition_many_kernel), and from 2,048 tiles on
-//                     first bracket every boundary, a group of lanes each, on a copy of every
-//                     32nd key (sample_kernel, sample_coarse_kernel, sample_fine_kernel) and search
+//                     (partition_kernel, partition_many_kernel), and from 2,048 to 10,240 tiles on
+//                     (the fewer runs, the later) first bracket every boundary, a group of lanes each, on a copy of every
+//                     32nd key (sample_kernel, sample_rank_kernel, sample_fine_kernel) and search
 //                     the runs only inside the brackets (bracket_partition_kernel).
 //   merge_kernel      one workgroup per tile: every thread loads its share of the tile's entries
 //                     into registers, 16-byte surrogates (14 key bytes + index) are merged in LDS
@@ -64,9 +64,18 @@ __host__ __device__ inline uint32_t tile_spacing(uint32_t fill, uint32_t k) { re
 constexpr uint64_t kRankedTiles = 512;
 constexpr uint64_t kMostSamples = 20480;
 constexpr uint32_t kMinStride = 8;
-constexpr uint64_t kCoarseStride = 16;                 // every 16th boundary is searched over whole sequences first
-constexpr uint64_t kSampleStride = 32;                 // one key in 32 is copied for the sampled partition
-constexpr uint64_t kSampledMinTiles = 2048;            // inputs of fewer tiles search the runs directly (measured crossover)
+// Samples from one ranked sample to the next (sampled partition): ranked rows + boundaries between them, 16 x 4M entries 51 + 124
+// us with 128, 25 + 132 with 256; 24 x 1M 21 + 92 and 12 + 100; 4 x 4M 8.7 + 34 and 6.7 + 33.
+constexpr uint32_t kRowStride = 256;
+constexpr uint64_t kSampleStride = 32;  // one key in 32 is copied for the sampled partition
+// Inputs of fewer tiles search the runs directly, a wave per boundary, larger ones on a copy of every 32nd key first.  The samples
+// cost some 100 us in four dependent launches whatever the input, the direct search grows with the boundaries, and with the runs.
+// Direct / sampled: 3 runs of 4.3M entries in all 29 / 105 us, 18M 103 / 133, 26M 140 / 146; 4 runs, 18M 124 / 141, 22M 151 /
+// 146; 8 runs, 4.3M 44 / 111, 13M 121 / 144, 18M 156 / 159; 16 runs, 4.3M 59 / 123, 10.5M 152 / 153; 32 runs, 4.3M 140 / 141,
+// 6M 165 / 149.
+constexpr uint64_t kSampledMinTiles = 2048;
+constexpr uint64_t kDirectMostTiles = 10240;
+__host__ __device__ inline uint64_t direct_tiles(uint32_t k) { return k <= 4 ? kDirectMostTiles : (k <= 8 ? 8192 : (k <= 16 ? 5120 : kSampledMinTiles)); }
 constexpr uint32_t kSpinLimit = 1u << 22;              // polls of one look-back window before giving up
 
 struct Header {  // first 256 bytes of the workspace
@@ -91,8 +100,7 @@ struct Workspace {
     uint64_t n_tiles;
     Header* hdr;
     uint64_t* status;   // [n_tiles]
-    uint64_t* splits;   // [(n_tiles + 1) * k]
-    uint64_t* ycoarse;  // [(n_coarse + 2) * k]   sample-space splits of every kCoarseStride-th boundary
+    uint64_t* splits;   // [(n_tiles + 1) * k]; the sampled partition first keeps its ranked rows there
     uint64_t* ywin;     // [2 * (n_tiles - 1) * k] sample-space brackets of every boundary
     SampleTable st;
     uint4* clear;       // zeroed by the partition launch for a later kernel of the caller
@@ -103,7 +111,7 @@ struct Workspace {
 
 __host__ __device__ inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
-__global__ void init_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint64_t n_coarse, uint64_t* n_out) {
+__global__ void init_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint64_t* n_out) {
     uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     if (i == 0) {
@@ -114,8 +122,6 @@ __global__ void init_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint64_
     if (i < rt.k) {
         ws.splits[i] = 0;
         ws.splits[n_tiles * rt.k + i] = run_len(rt, (uint32_t)i);
-        ws.ycoarse[i] = 0;
-        ws.ycoarse[(n_coarse + 1) * rt.k + i] = ws.st.m[i];
     }
 }
 
@@ -305,7 +311,7 @@ __device__ __forceinline__ uint32_t group_max_u32(uint32_t v, int group) {
 
 constexpr uint32_t kFewRuns = 32;
 constexpr int kGapBits = 9;  // fractional bits of a distance between records
-static_assert(kSampledMinTiles * kTileCap <= (1ull << (32 - kGapBits)), "positions in 32 bits");
+static_assert(kSampledMinTiles * kTileCap <= (1ull << (32 - kGapBits)), "positions of more than kFewRuns runs in 32 bits");
 
 template <int kPerLane>  // records a lane reads per round
 struct WindowShared {
@@ -484,7 +490,8 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
 // len: run lengths; upper: what the launch counts samples by (the same, or an upper bound: samples beyond a run's end come last, and
 // their rows are the runs' ends).
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ void ranked_row(const lsm_entry_t* run, const uint32_t len, const uint32_t upper, const uint32_t p, const uint32_t k,
+template <typename E>  // entries, or bare keys
+__device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, const uint32_t upper, const uint32_t p, const uint32_t k,
                                             const int group_log, const uint32_t stride, const uint32_t per_tile, uint64_t* splits) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const int lanes_log = 6 - group_log;
@@ -501,12 +508,12 @@ __device__ __forceinline__ void ranked_row(const lsm_entry_t* run, const uint32_
     uint32_t t, lo = 0, hi = 0;
     Key key = {{0, 0, 0, 0}};
     if (index < own_real) {
-        const lsm_entry_t* own_run = reinterpret_cast<const lsm_entry_t*>(__shfl(reinterpret_cast<uint64_t>(run), own_lane, kWave));
+        const E* own_run = reinterpret_cast<const E*>(__shfl(reinterpret_cast<uint64_t>(run), own_lane, kWave));
         const uint4* e = reinterpret_cast<const uint4*>(own_run + (uint64_t)index * stride);
         const uint4 k0 = load_global_u4(e), k1 = load_global_u4(e + 1);
         key = key_from_raw(k0, k1);
         // first record in [lo, hi) of the records `step` entries apart that is not before the key
-        auto search = [&](const lsm_entry_t* from, uint32_t step, bool equal_is_before) {
+        auto search = [&](const E* from, uint32_t step, bool equal_is_before) {
             while (__ballot(lo < hi) != 0) {
                 const uint32_t w = hi - lo;
                 auto tried = [&](uint32_t m) { return lo + (((2 * m + 1) * w) >> (lanes_log + 1)); };  // ascending with m, below hi
@@ -546,6 +553,15 @@ __device__ __forceinline__ void ranked_row(const lsm_entry_t* run, const uint32_
     if (head && row > 0) splits[(uint64_t)row * k + member] = lo;
 }
 
+// The boundaries that a workgroup works on, as a number in ascending order of the boundaries.  Workgroups go to the eight dies in
+// turn; with this a die gets one contiguous eighth of the boundaries, and neighbours, whose searches end in the same records, share an
+// L2.
+constexpr uint32_t kDies = 8;
+__device__ __forceinline__ uint32_t near_block() {
+    const uint32_t die = blockIdx.x % kDies, each = gridDim.x / kDies, more = gridDim.x % kDies;  // the first `more` dies get one more
+    return die * each + min(die, more) + blockIdx.x / kDies;
+}
+
 // Lane bookkeeping shared by the partition kernels: which problem and which sequence a lane has.
 struct GroupLane {
     int member, group_base;
@@ -556,12 +572,12 @@ __device__ __forceinline__ GroupLane group_lane(int group) {
     GroupLane g;
     g.member = lane & (group - 1);
     g.group_base = lane - g.member;
-    const uint64_t wave_id = (uint64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave;
+    const uint64_t wave_id = (uint64_t)near_block() * (blockDim.x / kWave) + threadIdx.x / kWave;
     g.slot = wave_id * (uint64_t)(kWave / group) + (uint64_t)(lane / group);
     return g;
 }
 
-// Search over whole runs, for inputs of up to kSampledMinTiles tiles, and of two runs at any size: one launch.
+// Search over whole runs, for inputs of up to direct_tiles tiles, and of two runs at any size: one launch.
 // kInit: the launch also clears the tile status words and writes the first and last split rows, which saves the
 // separate init launch (a small compaction is then two launches: this one and the merge).
 template <bool kInit>
@@ -608,7 +624,7 @@ template <bool kInit, int kPerLane, bool kMany>
 __global__ void __launch_bounds__(kWave) partition_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, int group_log) {
     __shared__ WindowShared<kPerLane> s;
     partition_init<kInit>(rt, ws, n_tiles);
-    const uint32_t b = blockIdx.x + 1, lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
+    const uint32_t b = near_block() + 1, lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
     const bool own = j < rt.k;
     const uint32_t best = window_split<kPerLane, kMany>(s, own ? rt.ptr[j] : nullptr, own ? (uint32_t)run_len(rt, j) : 0, b * ws.spacing, group_log);
     if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
@@ -630,12 +646,12 @@ constexpr uint64_t kWindowPieces = 65536;
 template <bool kInit>
 __global__ void __launch_bounds__(kWave) partition_many_kernel(RunTable rt, Workspace ws, uint64_t n_tiles) {
     partition_init<kInit>(rt, ws, n_tiles);
-    const uint32_t b = blockIdx.x + 1, lane = threadIdx.x;
+    const uint32_t b = near_block() + 1, lane = threadIdx.x;
     const bool own = lane < rt.k;
     const uint64_t best = select_split<false>(own ? rt.ptr[lane] : nullptr, 0, own ? run_len(rt, lane) : 0, b * (uint64_t)ws.spacing, own, (int)lane, kWave, 0);
     if (own) ws.splits[(uint64_t)b * rt.k + lane] = best;
 }
-static_assert(kSampledMinTiles * kTileCap < (1ull << 32), "the window search counts in 32 bits");
+static_assert(kDirectMostTiles * kTileCap < (1ull << 32), "the window search counts in 32 bits");
 
 static int log2_ceil(uint32_t k) {
     int log = 0;
@@ -658,8 +674,10 @@ static int records_per_lane(int group_log) { return group_log <= 4 ? 4 : 8; }
 //   upper bracket: the sample key with the largest Y <= ceil(r / s) + 2k - 1 has, if a larger sample
 //                  exists at all, Y >= ceil(r / s) + k and therefore L > r: it is > x.
 // The answer's lower bound in run j then lies in [s * (ylo_j - 1) + 1, s * yhi_j] (clamped to the run).
-// The sample-space problems are themselves solved coarse first: every kCoarseStride-th boundary
-// over whole sample arrays, the rest between the coarse rows that enclose their targets.
+// The sample-space problems start from ranked samples (ranked_row above): every kRowStride-th sample of every run, its lower bounds
+// in all runs' samples, in order.  With s2 = kRowStride, row t has s2 * (t - k) <= Y <= s2 * t, so the answer for a target Y lies
+// between row floor(Y / s2) and row floor(Y / s2) + 1 + k.  (Every 16th boundary searched over whole sample arrays instead was a
+// chain of some ninety dependent reads, 70 us for 16 x 4M entries and 52 for 4 x 4M, where the rows take 25 and 7.)
 // ---------------------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) sample_kernel(RunTable rt, SampleTable st) {
     const uint32_t j = blockIdx.y;
@@ -675,34 +693,31 @@ __device__ __forceinline__ uint64_t sample_target(uint64_t b, int side, uint32_t
     return side ? (r + kSampleStride - 1) / kSampleStride + 2ull * k - 1 : r / kSampleStride;
 }
 
-// coarse rows: row c (1 <= c <= n_coarse) = lower bracket of boundary c * kCoarseStride over whole sample arrays
-__global__ void __launch_bounds__(256) sample_coarse_kernel(Workspace ws, uint32_t k, uint64_t n_coarse, int group) {
-    const GroupLane g = group_lane(group);
-    const uint64_t c = g.slot + 1;
-    const bool own = c <= n_coarse && g.member < (int)k;
-    const SampleKey* run = own ? ws.st.ptr[g.member] : nullptr;
-    const uint64_t best = select_split<true>(run, 0, own ? ws.st.m[g.member] : 0, sample_target(c * kCoarseStride, 0, k), own,
-                                       g.member, group, g.group_base);
-    if (own) ws.ycoarse[c * k + g.member] = best;
+// the ranked rows: one wave per ranked sample, all of them boundaries of the sample arrays
+__global__ void __launch_bounds__(kWave) sample_rank_kernel(Workspace ws, uint32_t k, int group_log) {
+    const uint32_t member = threadIdx.x >> (6 - group_log);
+    const bool mine = member < k;
+    const uint32_t m = mine ? (uint32_t)ws.st.m[member] : 0;
+    ranked_row(mine ? ws.st.ptr[member] : nullptr, m, m, blockIdx.x, k, group_log, kRowStride, 1, ws.splits);
 }
 
-// problem p = 2 * (b - 1) + side for boundary b; targets of boundaries [c * stride, (c + 1) * stride) lie
-// between those of coarse rows c and c + 2 (the upper bracket overshoots by 2k - 1 <= one coarse step)
-__global__ void __launch_bounds__(256) sample_fine_kernel(Workspace ws, uint32_t k, uint64_t n_tiles, uint64_t n_coarse, int group) {
+// problem p = 2 * (b - 1) + side for boundary b, between the ranked rows that enclose its target
+__global__ void __launch_bounds__(256) sample_fine_kernel(Workspace ws, uint32_t k, uint64_t n_tiles, uint64_t n_rows, int group) {
     const GroupLane g = group_lane(group);
     const uint64_t b = g.slot / 2 + 1;
     const int side = (int)(g.slot & 1);
     const bool own = b < n_tiles && g.member < (int)k;
     const SampleKey* run = own ? ws.st.ptr[g.member] : nullptr;
+    const uint64_t target = sample_target(b, side, k);
     uint64_t lo = 0, hi = 0;
     if (own) {
-        const uint64_t c = b / kCoarseStride, above = c + 2 < n_coarse + 1 ? c + 2 : n_coarse + 1;
-        lo = ws.ycoarse[c * k + g.member];
-        hi = ws.ycoarse[above * k + g.member];
+        const uint64_t row = target / kRowStride, from = row < n_rows ? row : n_rows - 1, above = row + 1 + k;
+        lo = ws.splits[from * k + g.member];
+        hi = above < n_rows ? ws.splits[above * k + g.member] : ws.st.m[g.member];
         if (hi > ws.st.m[g.member]) hi = ws.st.m[g.member];  // only inputs that break the precondition
         if (lo > hi) lo = hi;
     }
-    const uint64_t best = select_split<true>(run, lo, hi, sample_target(b, side, k), own, g.member, group, g.group_base);
+    const uint64_t best = select_split<true>(run, lo, hi, target, own, g.member, group, g.group_base);
     if (own) ws.ywin[g.slot * k + g.member] = best;
 }
 
@@ -1607,14 +1622,13 @@ static Cut cut_runs(const uint64_t* run_lens, uint32_t k, uint32_t spacing, uint
     }
     return exact;
 }
-static uint64_t coarse_rows(uint64_t n_tiles) { return n_tiles > 1 ? (n_tiles - 1) / kCoarseStride : 0; }
 
 // Lays the workspace out; with base == nullptr it only measures.  Returns the bytes used.
 static size_t carve(void* base, const uint64_t* run_lens, uint32_t k, Workspace* ws) {
     uint64_t total = 0;
     for (uint32_t j = 0; j < k; j++) total += run_lens[j];
     const Cut cut = cut_runs(run_lens, k, single_spacing(total, k), total);
-    const uint64_t n_tiles = tiles_for(total, cut.spacing), n_coarse = coarse_rows(n_tiles);
+    const uint64_t n_tiles = tiles_for(total, cut.spacing);
     char* p = static_cast<char*>(base);
     size_t off = 0;
     auto take = [&](size_t bytes) {
@@ -1626,7 +1640,6 @@ static size_t carve(void* base, const uint64_t* run_lens, uint32_t k, Workspace*
     w.hdr = reinterpret_cast<Header*>(take(sizeof(Header)));
     w.status = reinterpret_cast<uint64_t*>(take(n_tiles * sizeof(uint64_t)));
     w.splits = reinterpret_cast<uint64_t*>(take((n_tiles + 1) * (uint64_t)k * sizeof(uint64_t)));
-    w.ycoarse = reinterpret_cast<uint64_t*>(take((n_coarse + 2) * (uint64_t)k * sizeof(uint64_t)));
     w.ywin = reinterpret_cast<uint64_t*>(take(2 * (n_tiles ? n_tiles - 1 : 0) * (uint64_t)k * sizeof(uint64_t)));
     for (uint32_t j = 0; j < LSM_MAX_RUNS; j++) {
         w.st.m[j] = j < k ? (run_lens[j] + kSampleStride - 1) / kSampleStride : 0;
@@ -1639,7 +1652,6 @@ static size_t carve(void* base, const uint64_t* run_lens, uint32_t k, Workspace*
         w.hdr = reinterpret_cast<Header*>(take(sizeof(Header)));
         w.status = reinterpret_cast<uint64_t*>(take(cut.tiles * sizeof(uint64_t)));
         w.splits = reinterpret_cast<uint64_t*>(take((cut.tiles + 1) * (uint64_t)k * sizeof(uint64_t)));
-        w.ycoarse = reinterpret_cast<uint64_t*>(take((coarse_rows(cut.tiles) + 2) * (uint64_t)k * sizeof(uint64_t)));
         w.n_tiles = cut.tiles;
         if (off < all) off = all;
     }
@@ -1683,10 +1695,9 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     Workspace ws;
     carve(workspace, rt.n, n_runs, &ws);
     const uint64_t n_tiles = ws.n_tiles;
-    const uint64_t n_coarse = coarse_rows(n_tiles);  // boundaries kCoarseStride, 2 * kCoarseStride, ... < n_tiles
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
-    const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs == 2);  // two runs: bisection on the merge path at any size
+    const bool direct = n_tiles > 1 && (n_tiles < direct_tiles(n_runs) || n_runs == 2);  // two runs: bisection on the merge path at any size
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
     if (clear.bytes != 0 && direct && fused_init) {
         ws.clear = static_cast<uint4*>(clear.p);
@@ -1697,7 +1708,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
         uint32_t init_blocks = (uint32_t)((n_tiles + 255) / 256);
         if (init_blocks == 0) init_blocks = 1;
         if (init_blocks > 1024) init_blocks = 1024;
-        hipLaunchKernelGGL(init_kernel, dim3(init_blocks), dim3(256), 0, stream, rt, ws, n_tiles, n_coarse, out->n_out);
+        hipLaunchKernelGGL(init_kernel, dim3(init_blocks), dim3(256), 0, stream, rt, ws, n_tiles, out->n_out);
     }
 
     if (flags & LSM_VALIDATE) {
@@ -1740,13 +1751,16 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
             if (fused_init) launch(std::true_type{});
             else launch(std::false_type{});
         } else {
-            uint64_t m_max = 0;
-            for (uint32_t j = 0; j < n_runs; j++) m_max = ws.st.m[j] > m_max ? ws.st.m[j] : m_max;
+            uint64_t m_max = 0, n_rows = 0;  // fewer rows than tiles: a row stands for kRowStride * kSampleStride entries
+            for (uint32_t j = 0; j < n_runs; j++) {
+                m_max = ws.st.m[j] > m_max ? ws.st.m[j] : m_max;
+                n_rows += (ws.st.m[j] + kRowStride - 1) / kRowStride;
+            }
             uint64_t sample_blocks = (2 * m_max + 255) / 256;
             if (sample_blocks > 4096) sample_blocks = 4096;
             hipLaunchKernelGGL(sample_kernel, dim3((uint32_t)sample_blocks, n_runs), dim3(256), 0, stream, rt, ws.st);
-            hipLaunchKernelGGL(sample_coarse_kernel, blocks(n_coarse), dim3(256), 0, stream, ws, n_runs, n_coarse, group);
-            hipLaunchKernelGGL(sample_fine_kernel, blocks(2 * (n_tiles - 1)), dim3(256), 0, stream, ws, n_runs, n_tiles, n_coarse, group);
+            hipLaunchKernelGGL(sample_rank_kernel, dim3((uint32_t)n_rows), dim3(kWave), 0, stream, ws, n_runs, log2_ceil(n_runs));
+            hipLaunchKernelGGL(sample_fine_kernel, blocks(2 * (n_tiles - 1)), dim3(256), 0, stream, ws, n_runs, n_tiles, n_rows, group);
             hipLaunchKernelGGL(bracket_partition_kernel, blocks(n_tiles - 1), dim3(256), 0, stream, rt, ws, n_tiles, group);
         }
     }

@@ -430,6 +430,23 @@ def test_many_runs_one_after_the_other_are_not_slow(g, oracle):
     assert took < 3 * base
 
 
+@pytest.mark.parametrize("k,tiles", [(3, 10240), (5, 8192), (16, 5120), (17, 2048), (40, 2048)])
+def test_searched_directly_or_on_samples(g, oracle, k, tiles):
+    """The longest input whose boundaries are searched in the runs themselves and the shortest that is sampled; runs of very
+    different lengths, an empty one among them, and ones that cover a part of the keys only."""
+    rs = np.random.RandomState(k)
+    for total in ((tiles - 1) * (2048 - k), (tiles - 1) * (2048 - k) + 1):
+        print("direct or sampled", k, total, flush=True)
+        lens = np.maximum(1, (total * rs.dirichlet(np.full(k, 0.7)) * 0.999).astype(np.int64))
+        lens[0] = 0
+        lens[-1] += total - lens.sum()
+        runs = _runs_of(oracle, rs, lens, 2 * total)
+        runs[1][:, 0] |= 1  # the keys' first byte, as stored: a run behind all others
+        _check_compact(g, oracle, runs, int(total & 1))
+        del runs
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("k", [1, 2, 3, 16, 64])
 def test_tile_spacing_edges(g, oracle, k):
     """Inputs around the totals where the tile spacing changes: one tile or several, the shortest spacing, one that grows
