@@ -430,6 +430,8 @@ struct lsm_driver {
         const lsm_out_t out{entries, room, n_host, fences, cfg.fence_stride, nullptr};
         *static_cast<volatile uint64_t*>(n_host) = kCountUnset;
         int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, workspace_bytes, clear, &merged->bloom_clear, stream);
+        // an error may be that of the filter's launch, or of an earlier call, with the merge under way: its count must not meet the next one's
+        if (rc != LSM_OK) (void)wait();
         if (rc == LSM_OK) rc = watch_count(n_host);
         if (rc == LSM_OK && *n_host > room) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
         if (rc == LSM_OK && cfg.observer != nullptr) rc = wait();   // the observer sees a complete output
@@ -646,6 +648,7 @@ extern "C" int lsm_driver_flush_unsorted(lsm_driver_t* d, const lsm_entry_t* buf
         const lsm_out_t out{sorted, room, d->n_host, r.fences, d->cfg.fence_stride, nullptr};
         *static_cast<volatile uint64_t*>(d->n_host) = kCountUnset;
         rc = lsm_flush_buffer(buffer, n, &out, ws, ws_bytes > 0 ? ws_bytes : 4, d->stream);
+        if (rc != LSM_OK) (void)d->wait();  // some of its launches may have been made: see compact
     }
     if (rc == LSM_OK) rc = d->watch_count(d->n_host);
     d->pool.give(ws);

@@ -3,13 +3,14 @@
 // call of it fails - can then be tested without a GPU, failures included.  Test infrastructure only.
 //
 // "Device" memory is filled with 0xAB, so that memory that was handed out but never written is seen.  Work is done when it
-// is enqueued, which is one of the orders a stream allows.
+// is enqueued, which is one of the orders a stream allows, or, where a test asks for it, as late as one allows.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <cstdint>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <functional>
 #include <utility>
 #include <vector>
@@ -32,9 +33,10 @@ uint64_t host_mallocs = 0, host_kernels = 0;
 uint32_t host_pinned_flags = ~0u;   // flags that every pinned allocation was made with
 uint64_t host_dirty_filters = 0;    // filters built on memory that was promised to be zero and was not
 int64_t host_slow_stats = 0;        // what a probe batch found is written when the stream is next asked or waited for, no earlier
+int64_t host_slow_merges = 0;       // the same for merges and sorted write buffers; every time the stream is asked, one of them ends
 
 void host_reset() {
-    host_malloc_in = host_kernel_in = host_late_in = host_slow_stats = 0;
+    host_malloc_in = host_kernel_in = host_late_in = host_slow_stats = host_slow_merges = 0;
     host_mallocs = host_kernels = host_dirty_filters = 0;
     host_pinned_flags = ~0u;
 }
@@ -60,13 +62,21 @@ hipError_t hipHostFree(void* p) {
     std::free(p);
     return hipSuccess;
 }
-static std::function<void()> under_way;
+static std::deque<std::function<void()>> under_way;
+static hipError_t step() {
+    if (!under_way.empty()) {
+        const std::function<void()> work = std::move(under_way.front());
+        under_way.pop_front();
+        work();
+    }
+    return under_way.empty() ? hipSuccess : hipErrorNotReady;
+}
 static hipError_t catch_up() {
-    if (under_way) std::exchange(under_way, nullptr)();
+    while (step() != hipSuccess) {}
     return hipSuccess;
 }
 hipError_t hipStreamSynchronize(hipStream_t) { return catch_up(); }
-hipError_t hipStreamQuery(hipStream_t) { return catch_up(); }
+hipError_t hipStreamQuery(hipStream_t) { return step(); }
 hipError_t hipGetLastError() { return hipSuccess; }
 hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, hipMemcpyKind, hipStream_t) {
     std::memcpy(dst, src, bytes);
@@ -78,16 +88,23 @@ static bool refused() {
     host_kernels++;
     return host_kernel_in > 0 && --host_kernel_in == 0;
 }
+// work of a kernel, behind what the stream still has to do
+static void enqueue(int64_t slow, std::function<void()> work) {
+    under_way.push_back(std::move(work));
+    if (slow == 0) (void)catch_up();
+}
 static int done() { return host_late_in > 0 && --host_late_in == 0 ? LSM_ERR_HIP : LSM_OK; }
 
-static int merge(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, const lsm::ClearSpan& clear) {
+static void merge(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t& out, const lsm::ClearSpan& clear) {
     std::vector<const lsm_entry_t*> ptr;
     std::vector<uint64_t> len;
     for (uint32_t j = 0; j < n_runs; j++) ptr.push_back(runs[j].entries), len.push_back(runs[j].n);
-    if (clear.bytes != 0) std::memset(clear.p, 0, clear.bytes);
-    *out->n_out = oracle_compact(ptr.data(), len.data(), n_runs, flags, out->entries);
-    if (out->fence_keys != nullptr) oracle_build_fences(out->entries, *out->n_out, out->fence_stride, static_cast<uint8_t*>(out->fence_keys));
-    return LSM_OK;
+    enqueue(host_slow_merges, [=, clear_p = clear.p, clear_bytes = clear.bytes] {
+        if (clear_bytes != 0) std::memset(clear_p, 0, clear_bytes);
+        const uint64_t n = oracle_compact(ptr.data(), len.data(), n_runs, flags, out.entries);
+        if (out.fence_keys != nullptr) oracle_build_fences(out.entries, n, out.fence_stride, static_cast<uint8_t*>(out.fence_keys));
+        *out.n_out = n;
+    });
 }
 
 size_t lsm_compact_workspace_bytes(const uint64_t*, uint32_t n_runs) { return n_runs > LSM_MAX_RUNS ? 0 : 1024; }
@@ -97,19 +114,21 @@ size_t lsm_compact_batch_workspace_bytes(const lsm_compact_job_t* jobs, uint32_t
     return 1024 * n_jobs;
 }
 size_t lsm_flush_workspace_bytes(uint64_t n) { return 4 * n; }
-int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm_out_t* out, void*, size_t, void*) {
+int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm_out_t* out_at, void*, size_t, void*) {
     if (refused()) return LSM_ERR_HIP;
-    std::vector<lsm_entry_t> v(buffer, buffer + n);
-    std::reverse(v.begin(), v.end());
-    std::stable_sort(v.begin(), v.end(), [](const lsm_entry_t& a, const lsm_entry_t& b) {
-        const int c = std::memcmp(a.key, b.key, LSM_KEY_BYTES);
-        return c != 0 ? c < 0 : a.seqno > b.seqno;
+    enqueue(host_slow_merges, [=, out = *out_at] {
+        std::vector<lsm_entry_t> v(buffer, buffer + n);
+        std::reverse(v.begin(), v.end());
+        std::stable_sort(v.begin(), v.end(), [](const lsm_entry_t& a, const lsm_entry_t& b) {
+            const int c = std::memcmp(a.key, b.key, LSM_KEY_BYTES);
+            return c != 0 ? c < 0 : a.seqno > b.seqno;
+        });
+        uint64_t m = 0;
+        for (uint64_t i = 0; i < n; i++)
+            if (i == 0 || std::memcmp(v[i].key, v[i - 1].key, LSM_KEY_BYTES) != 0) out.entries[m++] = v[i];
+        if (out.fence_keys != nullptr) oracle_build_fences(out.entries, m, out.fence_stride, static_cast<uint8_t*>(out.fence_keys));
+        *out.n_out = m;
     });
-    uint64_t m = 0;
-    for (uint64_t i = 0; i < n; i++)
-        if (i == 0 || std::memcmp(v[i].key, v[i - 1].key, LSM_KEY_BYTES) != 0) out->entries[m++] = v[i];
-    *out->n_out = m;
-    if (out->fence_keys != nullptr) oracle_build_fences(out->entries, m, out->fence_stride, static_cast<uint8_t*>(out->fence_keys));
     return done();
 }
 int lsm_build_fences(const lsm_run_t* run, uint32_t stride, uint8_t* keys, void*) {
@@ -173,14 +192,14 @@ int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, con
     if (n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
     if (refused()) return LSM_ERR_HIP;
     *cleared = clear.bytes != 0;
-    const int rc = merge(runs, n_runs, flags, out, clear);
-    return rc != LSM_OK ? rc : done();
+    merge(runs, n_runs, flags, *out, clear);
+    return done();
 }
 int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*, size_t, const ClearSpan* clear, hipStream_t) {
     for (uint32_t j = 0; j < n_jobs; j++)
         if (jobs[j].n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
     if (refused()) return LSM_ERR_HIP;
-    for (uint32_t j = 0; j < n_jobs; j++) (void)merge(jobs[j].runs, jobs[j].n_runs, jobs[j].flags, &jobs[j].out, clear ? clear[j] : ClearSpan());
+    for (uint32_t j = 0; j < n_jobs; j++) merge(jobs[j].runs, jobs[j].n_runs, jobs[j].flags, jobs[j].out, clear ? clear[j] : ClearSpan());
     return done();
 }
 int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t fence_stride, hipStream_t) {
@@ -203,12 +222,9 @@ int build_filters(const lsm_run_t* runs, void* const* filters, const uint64_t* n
 }
 int probe_stats(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket, hipStream_t) {
     if (refused()) return LSM_ERR_HIP;
-    under_way = [=] {
-        stats[0] = stats[1] = 0;
-        for (uint32_t i = 0; i < n_req; i++) stats[0] += hit_len[i], stats[1] += hit_len[i] > 0;
-        stats[2] = ticket;
-    };
-    if (host_slow_stats == 0) (void)catch_up();
+    uint64_t blocks = 0, hits = 0;
+    for (uint32_t i = 0; i < n_req; i++) blocks += hit_len[i], hits += hit_len[i] > 0;
+    enqueue(host_slow_stats, [=] { stats[0] = blocks, stats[1] = hits, stats[2] = ticket; });
     return done();
 }
 }  // namespace lsm

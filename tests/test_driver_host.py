@@ -268,6 +268,25 @@ def test_what_a_batch_found_is_its_own_after_a_batch_that_failed(host, knobs, or
     tree.close()
 
 
+@pytest.mark.parametrize("call", ["flush", "flush_unsorted"])
+def test_a_count_is_that_of_its_own_merge_after_a_call_that_failed(host, knobs, oracle, call):
+    """A call that reports an error may leave a merge (or a sort) under way, which stores its count when it ends: the next
+    call's runs have their own lengths all the same, however long that takes."""
+    old, failed, last = run_of(range(0, 300, 3), 1), run_of(range(90), 2), run_of(range(1000, 1040), 3)
+    tree = Tree(host, loaded=[(1, old)])
+    flush = getattr(host, "lsm_driver_" + call)
+    knobs.slow_merges = 1
+    knobs.late_in = 1
+    assert flush(tree.h, failed.ctypes.data, len(failed)) == HIP
+    assert flush(tree.h, last.ctypes.data, len(last)) == 0
+    # the sorted run had entered the tree when its merge failed; a write buffer that was not sorted had not
+    want = oracle.compact([last, failed, old] if call == "flush" else [last, old], 1)
+    runs = tree.runs()
+    assert len(runs) == 1 and runs[0].run.n == len(want)
+    assert np.array_equal(np.ctypeslib.as_array(C.cast(runs[0].run.entries, C.POINTER(C.c_uint8)), (len(want), 64)), want)
+    tree.close()
+
+
 def test_words_the_host_watches_are_in_coherent_memory(host, knobs):
     """The host reads counts and statistics while kernels run: whatever the runtime's default for pinned memory is, these
     words are asked for as coherent."""
