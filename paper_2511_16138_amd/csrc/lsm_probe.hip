@@ -30,6 +30,7 @@ static_assert(sizeof(TreeRun) == 48, "64 of these travel as a kernel argument");
 
 struct TreeTable {
     TreeRun run[LSM_MAX_RUNS];
+    uint64_t holding;  // bit r: run r holds entries; the others hold no key, whether or not they have a filter that says so
     uint32_t n_runs;
 };
 
@@ -116,9 +117,9 @@ __device__ __forceinline__ bool index_admits(const uint4 w, const uint32_t tag) 
 }
 
 // Which runs a lane's key has to be searched in, newest in the lowest bit: those whose Bloom filter or hash index does not rule
-// it out, and those that have neither.  bh: the key's filter hash.
-__device__ __forceinline__ uint64_t probe_admit(const TreeTable& tree, const uint32_t n_runs, const uint64_t run_mask, const bool any_filter,
-                                                const bool mine, const Key& q, uint64_t& bh) {
+// it out, and those that hold entries and have neither.  bh: the key's filter hash.
+__device__ __forceinline__ uint64_t probe_admit(const TreeTable& tree, const uint32_t n_runs, const bool any_filter, const bool mine, const Key& q,
+                                                uint64_t& bh) {
     // (0) one 16-byte read per run, all runs of a group of eight requested together
     uint64_t maybe = ~0ull;
     bh = mine ? bloom_key_hash(q) : 0;
@@ -151,7 +152,7 @@ __device__ __forceinline__ uint64_t probe_admit(const TreeTable& tree, const uin
             }
         }
     }
-    return maybe & run_mask;
+    return maybe & tree.holding;
 }
 
 // Looks one block key per lane up in the runs `maybe` (every lane of the wave calls this; lanes with mine == false idle).
@@ -302,10 +303,10 @@ __device__ __forceinline__ bool probe_walk(const ProbeShared<kTop>& s, uint64_t 
 }
 
 template <bool kTop>
-__device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const TreeTable& tree, const uint32_t n_runs,
-                                             const uint64_t run_mask, const bool any_filter, const bool mine, const Key& q, uint4& h) {
+__device__ __forceinline__ bool probe_lookup(const ProbeShared<kTop>& s, const TreeTable& tree, const uint32_t n_runs, const bool any_filter,
+                                             const bool mine, const Key& q, uint4& h) {
     uint64_t bh;
-    const uint64_t maybe = probe_admit(tree, n_runs, run_mask, any_filter, mine, q, bh);
+    const uint64_t maybe = probe_admit(tree, n_runs, any_filter, mine, q, bh);
     return probe_walk<kTop>(s, maybe, bh, mine, q, h);
 }
 
@@ -322,7 +323,6 @@ __global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const u
     constexpr uint32_t kRequests = kThreads / kWave / kSpread;  // requests a workgroup handles at a time
     const uint32_t n_runs = tree.n_runs;
     probe_setup<kTop, kThreads>(s, tree, (int)tid);
-    const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
     bool any_filter = false;  // a Bloom filter or a hash index
     for (uint32_t r = 0; r < n_runs; r++) any_filter = any_filter || tree.run[r].bloom_blocks != 0 || tree.run[r].index != nullptr;
     uint32_t turn = 0;
@@ -342,7 +342,7 @@ __global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const u
                 const bool mine = j < nb;  // lanes past the request's length do not end the prefix
                 Key q = {{0, 0, 0, 0}};
                 if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
-                const bool live = probe_lookup<kTop>(s, tree, n_runs, run_mask, any_filter, mine, q, h);
+                const bool live = probe_lookup<kTop>(s, tree, n_runs, any_filter, mine, q, h);
                 const uint64_t dead = __ballot(!live);
                 if (dead) first = start + (uint32_t)__ffsll((unsigned long long)dead) - 1;
             }
@@ -385,7 +385,6 @@ __global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), my_r = tid / kWave;
     const uint32_t n_runs = tree.n_runs;
     probe_setup<kTop, kPoolThreads>(s, tree, (int)tid);
-    const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
     for (uint32_t first_req = blockIdx.x * kPoolRequests; first_req < n_req; first_req += gridDim.x * kPoolRequests) {
         const uint32_t req = first_req + my_r;
         const uint32_t nb = req < n_req ? min(n_blocks[req], max_blocks) : 0;
@@ -398,7 +397,7 @@ __global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree
             Key q = {{0, 0, 0, 0}};
             if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
             uint64_t bh;
-            const uint64_t maybe = probe_admit(tree, n_runs, run_mask, true, mine, q, bh);
+            const uint64_t maybe = probe_admit(tree, n_runs, true, mine, q, bh);
             if (mine) {
                 admitted[my_r * LSM_MAX_BLOCKS + j] = maybe;
                 hashed[my_r * LSM_MAX_BLOCKS + j] = bh;
@@ -461,7 +460,6 @@ __global__ void __launch_bounds__(kThreads) probe_length_kernel(TreeTable tree, 
     const int lane = tid & (kWave - 1);
     const uint32_t n_runs = tree.n_runs;
     probe_setup<kTop, kThreads>(s, tree, tid);
-    const uint64_t run_mask = n_runs >= 64 ? ~0ull : (1ull << n_runs) - 1;
     bool any_filter = false;  // a Bloom filter or a hash index
     for (uint32_t r = 0; r < n_runs; r++) any_filter = any_filter || tree.run[r].bloom_blocks != 0 || tree.run[r].index != nullptr;
     const uint32_t waves = gridDim.x * (kThreads / kWave);
@@ -479,7 +477,7 @@ __global__ void __launch_bounds__(kThreads) probe_length_kernel(TreeTable tree, 
             Key q = {{0, 0, 0, 0}};
             if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
             uint4 h;
-            const bool live = probe_lookup<kTop>(s, tree, n_runs, run_mask, any_filter, mine, q, h);
+            const bool live = probe_lookup<kTop>(s, tree, n_runs, any_filter, mine, q, h);
             const uint64_t dead = __ballot(!live);
             if (dead == 0) {
                 lo = hi;  // block hi - 1 is live: so is everything below it
@@ -552,6 +550,7 @@ static int make_tree_table(const lsm_tree_t* tree, lsm::TreeTable& tt) {
     if (tree->n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
     if (tree->n_runs > 0 && tree->runs == nullptr) return LSM_ERR_NULL;
     tt.n_runs = 0;
+    tt.holding = 0;
     for (uint32_t r = 0; r < tree->n_runs; r++) {
         const lsm_tree_run_t& tr = tree->runs[r];
         TreeRun& d = tt.run[r];
@@ -571,6 +570,7 @@ static int make_tree_table(const lsm_tree_t* tree, lsm::TreeTable& tt) {
             (tr.bloom.n_blocks == 0 || tr.bloom.n_blocks >= (1ull << 32) || (reinterpret_cast<uintptr_t>(tr.bloom.blocks) & 15) != 0))
             return LSM_ERR_BAD_ARG;
         if (tr.run.n > 0) {
+            tt.holding |= 1ull << r;
             if (tr.run.entries == nullptr || tr.fence.keys == nullptr) return LSM_ERR_NULL;
             if (tr.fence.stride == 0 || tr.fence.n != (tr.run.n + tr.fence.stride - 1) / tr.fence.stride) return LSM_ERR_BAD_ARG;
             if (tr.fence.n >= (1ull << 31)) return LSM_ERR_BAD_ARG;
