@@ -364,88 +364,107 @@ __global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const u
     }
 }
 
-// Large batches on trees whose runs all have a filter or an index: one workgroup of 16 requests per compute unit, in two phases.
+// Large batches on trees whose runs all have a filter or an index: one workgroup of up to 16 requests per compute unit.
 // First every wave admits its request's keys, 64 at a time, up to the first key that every run rules out, which ends the
-// prefix; then the admitted keys of all 16 are looked up, shared out evenly over the threads.  What bounds a wave per request
+// prefix; then the admitted keys of all requests are looked up, shared out evenly over the threads.  What bounds a wave per request
 // (probe_kernel) is the chain of its longest requests, which look up two or three chunks of keys one after the other, while
 // the waves of requests that share nothing with the tree (30 %) are done at once; here nearly every workgroup has one round of
-// lookups, and its fence table is read once per compute unit.  4,096 requests, a wave each / pooled: 100M entries with
-// filters 62.1 / 51.4 us, with indices as well 42.8 / 38.1; 20M 50.2 / 39.4 and 36.2 / 31.4, indices only 54.2 / 42.2; 1M
-// 41.9 / 34.5.  Eight requests in 512 threads (two workgroups per compute unit) 58.8 us for the first, eight in 1,024 76.9.
+// lookups, and its fence table is read once per compute unit.  A wave each / pooled, trees with filters: 4,096 requests on
+// 100M entries 58.2 / 47.5 us (with indices as well 44.8 / 40.3), on 20M 52.5 / 46.0, on 1M 41.6 / 38.7; 2,500 requests on 100M
+// 54.2 / 40.4, on 1M 33.6 / 29.7; indices only, 4,096 on 100M 62.1 / 56.7.
+// Where waves have nothing to share, each goes on with its own request, and a key behind one that is not live is not
+// looked up: 4,096 requests of 256 keys on 20M entries whose first key is a tombstone 86.6 us with a wave each, 314 with all
+// keys shared out, 86.2 so; whose keys are all live 315 / 308 / 318, on 1M entries with filters and indices 84 / 107 / 90.
 constexpr int kPoolRequests = 16;
 constexpr int kPoolThreads = 1024;
 template <bool kTop>
 __global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree, const uint8_t* qkeys, const uint32_t* n_blocks, uint32_t n_req,
-                                                              uint32_t max_blocks, uint32_t* hit_len, lsm_hit_t* hits) {
+                                                              uint32_t max_blocks, uint32_t* hit_len, lsm_hit_t* hits, uint32_t per_group) {
     __shared__ ProbeShared<kTop> s;
     __shared__ uint64_t admitted[kPoolRequests * LSM_MAX_BLOCKS], hashed[kPoolRequests * LSM_MAX_BLOCKS];  // of key j of request r at r * LSM_MAX_BLOCKS + j
-    __shared__ uint32_t first_out[kPoolRequests];   // first key that every run rules out, or the request's length
-    __shared__ uint32_t first_dead[kPoolRequests];  // first key looked up that is not live
+    __shared__ uint32_t admitted_keys[2][kPoolRequests];  // of the first chunk, of all
+    __shared__ uint32_t first_dead[kPoolRequests];        // first key looked up that is not live
     static_assert(kPoolRequests * kWave == kPoolThreads, "a wave admits a request's keys");
     const uint32_t tid = threadIdx.x, lane = tid & (kWave - 1), my_r = tid / kWave;
     const uint32_t n_runs = tree.n_runs;
     probe_setup<kTop, kPoolThreads>(s, tree, (int)tid);
-    for (uint32_t first_req = blockIdx.x * kPoolRequests; first_req < n_req; first_req += gridDim.x * kPoolRequests) {
-        const uint32_t req = first_req + my_r;
-        const uint32_t nb = req < n_req ? min(n_blocks[req], max_blocks) : 0;
-        const uint8_t* qrow = qkeys + (uint64_t)req * max_blocks * LSM_KEY_BYTES;
-        __syncthreads();  // the last requests' lists have been read
-        uint32_t out_at = nb;
-        for (uint32_t start = 0; start < nb; start += kWave) {
-            const uint32_t j = start + lane;
-            const bool mine = j < nb;
-            Key q = {{0, 0, 0, 0}};
-            if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
-            uint64_t bh;
-            const uint64_t maybe = probe_admit(tree, n_runs, true, mine, q, bh);
-            if (mine) {
-                admitted[my_r * LSM_MAX_BLOCKS + j] = maybe;
-                hashed[my_r * LSM_MAX_BLOCKS + j] = bh;
-            }
-            const uint64_t out = __ballot(mine && maybe == 0);
-            if (out != 0) {
-                out_at = start + (uint32_t)__ffsll((unsigned long long)out) - 1;
-                break;
-            }
+    const uint32_t first_req = blockIdx.x * per_group, requests = min(per_group, n_req - first_req), req = first_req + my_r;
+    const uint32_t nb = my_r < requests ? min(n_blocks[req], max_blocks) : 0;
+    const uint8_t* qrow = qkeys + (uint64_t)req * max_blocks * LSM_KEY_BYTES;
+    if (lane == 0) first_dead[my_r] = ~0u;
+    uint32_t out_at = nb, admitted_to = 0;
+    auto admit = [&]() {
+        const uint32_t j = admitted_to + lane;
+        const bool mine = j < nb;
+        Key q = {{0, 0, 0, 0}};
+        if (mine) q = load_key(qrow + (uint64_t)j * LSM_KEY_BYTES);
+        uint64_t bh;
+        const uint64_t maybe = probe_admit(tree, n_runs, true, mine, q, bh);
+        if (mine) {
+            admitted[my_r * LSM_MAX_BLOCKS + j] = maybe;
+            hashed[my_r * LSM_MAX_BLOCKS + j] = bh;
         }
-        if (lane == 0) {
-            first_out[my_r] = out_at;
-            first_dead[my_r] = ~0u;
-        }
+        const uint64_t out = __ballot(mine && maybe == 0);
+        if (out != 0) out_at = admitted_to + (uint32_t)__ffsll((unsigned long long)out) - 1;
+        admitted_to = min(admitted_to + (uint32_t)kWave, out_at);
+    };
+    bool alone = false;                // whether every wave looks up its own request's keys, 64 at a time
+    uint32_t from[kPoolRequests + 1];  // where a request's keys start in the list of all
+    from[0] = 0;
+    for (int rest = 0; rest < 2 && !alone; rest++) {
+        while (admitted_to < out_at && (rest != 0 || admitted_to == 0)) admit();
+        if (lane == 0) admitted_keys[rest][my_r] = admitted_to;
         __syncthreads();
-        uint32_t from[kPoolRequests + 1];  // where a request's keys start in the list of all
-        from[0] = 0;
 #pragma unroll
-        for (int r = 0; r < kPoolRequests; r++) from[r + 1] = from[r] + first_out[r];
-        for (uint32_t i0 = 0; i0 < from[kPoolRequests]; i0 += kPoolThreads) {
-            const uint32_t i = i0 + tid;
-            const bool mine = i < from[kPoolRequests];
-            uint32_t r = 0, base = 0;
+        for (int r = 0; r < kPoolRequests; r++) from[r + 1] = from[r] + admitted_keys[rest][r];
+        // Nothing to share: (nearly) every wave has a chunk of keys, or there are more keys than threads
+        alone = rest == 0 ? from[kPoolRequests] >= requests * (kWave - kWave / 16) : from[kPoolRequests] > (uint32_t)kPoolThreads;
+    }
+    uint32_t dead_at = ~0u;
+    for (uint32_t start = 0;; start += kWave) {
+        uint32_t r = my_r, j = start + lane;
+        bool mine;
+        if (alone) {
+            if (start == admitted_to && start < out_at) admit();
+            if (start >= out_at) break;
+            mine = j < admitted_to;
+        } else {
+            uint32_t base = 0;
+            r = 0;
 #pragma unroll
             for (int q = 1; q < kPoolRequests; q++)
-                if (i >= from[q]) r = q, base = from[q];
-            const uint32_t j = i - base;
-            Key q = {{0, 0, 0, 0}};
-            uint64_t maybe = 0, bh = 0;
-            if (mine) {
-                q = load_key(qkeys + ((uint64_t)(first_req + r) * max_blocks + j) * LSM_KEY_BYTES);
-                maybe = admitted[r * LSM_MAX_BLOCKS + j];
-                bh = hashed[r * LSM_MAX_BLOCKS + j];
-            }
-            uint4 h = make_uint4(0, 0, 0, 0);
-            const bool live = probe_walk<kTop>(s, maybe, bh, mine, q, h);
+                if (tid >= from[q]) r = q, base = from[q];
+            j = tid - base;
+            mine = tid < from[kPoolRequests];
+        }
+        Key q = {{0, 0, 0, 0}};
+        uint64_t maybe = 0, bh = 0;
+        if (mine) {
+            q = load_key(qkeys + ((uint64_t)(first_req + r) * max_blocks + j) * LSM_KEY_BYTES);
+            maybe = admitted[r * LSM_MAX_BLOCKS + j];
+            bh = hashed[r * LSM_MAX_BLOCKS + j];
+        }
+        uint4 h = make_uint4(0, 0, 0, 0);
+        const bool live = probe_walk<kTop>(s, maybe, bh, mine, q, h);
+        uint32_t dead;  // of request r, so far
+        if (alone) {
+            const uint64_t not_live = __ballot(!live);
+            if (not_live != 0) dead_at = start + (uint32_t)__ffsll((unsigned long long)not_live) - 1;
+            dead = dead_at;
+        } else {
             if (!live) atomicMin(&first_dead[r], j);
             __syncthreads();
-            // the next rounds hold later keys of a request only: what they find dead does not change this
-            if (mine && j < first_dead[r]) reinterpret_cast<uint4*>(hits)[(uint64_t)(first_req + r) * max_blocks + j] = h;
+            dead = first_dead[r];
+            dead_at = first_dead[my_r];
         }
-        if (req < n_req) {
-            const uint32_t result = min(out_at, first_dead[my_r]);
-            if (lane == 0) hit_len[req] = result;
-            uint4* hrow = reinterpret_cast<uint4*>(hits + (uint64_t)req * max_blocks);
-            for (uint32_t j = result + lane; j < max_blocks; j += kWave) hrow[j] = make_uint4(0, 0, 0, 0);
-        }
+        if (mine && j < dead) reinterpret_cast<uint4*>(hits)[(uint64_t)(first_req + r) * max_blocks + j] = h;
+        if (!alone || dead_at != ~0u) break;
     }
+    if (my_r >= requests) return;
+    const uint32_t result = min(out_at, dead_at);
+    if (lane == 0) hit_len[req] = result;
+    uint4* hrow = reinterpret_cast<uint4*>(hits + (uint64_t)req * max_blocks);
+    for (uint32_t j = result + lane; j < max_blocks; j += kWave) hrow[j] = make_uint4(0, 0, 0, 0);
 }
 
 // The length of the longest cached prefix by a search over the prefix length (appendix B, "Probe") instead of a
@@ -618,28 +637,29 @@ static uint32_t spread_for(uint32_t n_req, uint32_t max_blocks) {
 // 29.9 / 28.7, 4,096: 39.8 / 38.2.
 static int threads_for(uint32_t n_req, uint32_t spread) { return spread == 1 && n_req <= 1024 ? lsm::kProbeThreadsFew : lsm::kProbeThreads; }
 
-// Workgroups of the pooled form, 0 where it does not apply: more requests than fill the chip with two waves each (2,049 requests,
-// 1M entries with filters: 35.4 / 29.8 us; 2,048 with two waves each 24.4 against 28.6), rows of more than one chunk of keys
-// (4,096 requests on 20M entries with filters, rows of 64 keys 32.6 / 33.6 us, of 100 48.6 / 38.3), and every run ruled out by a
-// filter or an index.  One workgroup per compute unit, each striding over the requests; beyond one turn of them a tree that is indexed
-// throughout, whose workgroups read no fence table, has nothing left to gain (8,192 requests, indices and filters 40.0 / 45.9 us
-// on 1M entries; filters only 64.0 / 57.8).
-static uint32_t pool_groups(const lsm::TreeTable& tt, const lsm_queries_t& queries) {
+// Workgroups of the pooled form, 0 where it does not apply: more requests than fill the chip with two waves each (2,048 requests on
+// 1M entries with filters 24.4 us with two waves each, 28.6 pooled; 2,049 with a wave each 31.4, pooled 26.0), no more than one
+// workgroup per compute unit takes (5,000 on 1M entries, one and two turns 43.2 / 50.0 us, on 100M 63.2 / 88.1), rows of more than
+// one chunk of keys (4,096 requests on 20M entries with filters, rows of 64 keys 32.6 / 33.6 us, of 100 48.6 / 38.3), and every
+// run ruled out by a filter or an index.  The requests are spread over all compute units: 2,049 of 256 live keys on 20M entries
+// 161 us with a wave each, 166 with nine requests in a workgroup, 230 with 16.
+static uint32_t pool_groups(const lsm::TreeTable& tt, const lsm_queries_t& queries, uint32_t& per_group) {
     int device = 0, cus = 0;
     if (queries.n_req <= 2048 || queries.max_blocks <= (uint32_t)lsm::kWave || hipGetDevice(&device) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
         return 0;
     for (uint32_t r = 0; r < tt.n_runs; r++)
         if (tt.run[r].n != 0 && tt.run[r].bloom_blocks == 0 && tt.run[r].index == nullptr) return 0;
-    const uint32_t groups = (queries.n_req - 1) / lsm::kPoolRequests + 1;
-    if (groups <= (uint32_t)cus) return groups;
-    return all_indexed(tt) ? 0 : (uint32_t)cus;
+    if (queries.n_req > lsm::kPoolRequests * (uint32_t)cus) return 0;
+    per_group = (queries.n_req - 1) / (uint32_t)cus + 1;
+    return (queries.n_req - 1) / per_group + 1;
 }
 
 template <bool kTop>
-static void launch_pool(uint32_t groups, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits, hipStream_t stream) {
+static void launch_pool(uint32_t groups, uint32_t per_group, const lsm::TreeTable& tt, const lsm_queries_t* queries, const lsm_hits_t* out_hits,
+                        hipStream_t stream) {
     hipLaunchKernelGGL(lsm::probe_pool_kernel<kTop>, dim3(groups), dim3(lsm::kPoolThreads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req,
-                       queries->max_blocks, out_hits->hit_len, out_hits->hits);
+                       queries->max_blocks, out_hits->hit_len, out_hits->hits, per_group);
 }
 
 template <bool kTop>
@@ -680,9 +700,10 @@ extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, c
     const int threads = threads_for(queries->n_req, spread);
     if (rc == LSM_OK) rc = probe_grid(queries->n_req, spread, threads, blocks);
     if (rc != LSM_OK) return rc;
-    const uint32_t pools = pool_groups(tt, *queries);
-    if (pools != 0 && all_indexed(tt)) launch_pool<false>(pools, tt, queries, out_hits, static_cast<hipStream_t>(stream));
-    else if (pools != 0) launch_pool<true>(pools, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    uint32_t per_group = 0;
+    const uint32_t pools = pool_groups(tt, *queries, per_group);
+    if (pools != 0 && all_indexed(tt)) launch_pool<false>(pools, per_group, tt, queries, out_hits, static_cast<hipStream_t>(stream));
+    else if (pools != 0) launch_pool<true>(pools, per_group, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     else if (all_indexed(tt)) launch_probe<false>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     else launch_probe<true>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;

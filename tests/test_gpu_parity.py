@@ -537,7 +537,7 @@ def test_probe_workgroup_sizes(g, oracle, cfg1, n_req, indexed):
     assert np.array_equal(g.lsm_probe_length(q, nb, tree).cpu().numpy().astype(np.uint32), want[0])
 
 
-@pytest.mark.parametrize("n_req", [2049, 4096, 4097, 9001])  # pooled lookups: the smallest batch, one turn of the workgroups, several
+@pytest.mark.parametrize("n_req", [2049, 4096, 4097, 9001])  # pooled lookups: the smallest batch, the largest; beyond, a wave per request
 @pytest.mark.parametrize("row", [256, 65, 64])  # 64: one chunk of keys, a wave per request as before
 @pytest.mark.parametrize("ruled_out_by", ["filters", "indices", "both", "either", "tiny filters"])
 def test_probe_pooled_lookups(g, oracle, cfg1, n_req, row, ruled_out_by):
@@ -557,6 +557,47 @@ def test_probe_pooled_lookups(g, oracle, cfg1, n_req, row, ruled_out_by):
         if ruled_out_by in ("indices", "both") or (ruled_out_by == "either" and i % 2 == 1):
             t.index = g.lsm_build_hash_index(g.lsm_hash_keys(t.run))
     want = oracle.probe(q, nb, [r.cpu() for r in cfg1.runs])
+    assert_probe_equal(oracle, probe_gpu(g, q, nb, tree), want)
+
+
+def _stored_keys(g, n, tombstones):
+    """Keys of a two-run tree with filters: n live ones and, behind them, some whose newest version is a tombstone."""
+    rs = np.random.RandomState(5)
+    old = np.zeros((n + tombstones, 64), dtype=np.uint8)
+    old[:, :8] = np.cumsum(rs.randint(1, 1 << 40, size=n + tombstones)).astype(">u8").view(np.uint8).reshape(-1, 8)
+    new = old[n:].copy()
+    new[:, 32], new[:, 40] = 9, TOMBSTONE
+    runs = [to_dev(new), to_dev(old)]
+    tree = build_tree(g, runs)
+    for t in tree:
+        t.bloom = g.lsm_build_bloom(t.run, 16)
+    return runs, tree, runs[1][:, :4].clone()
+
+
+@pytest.mark.parametrize("n_req", [2049, 2305, 4096])  # 9, 10 and 16 requests in a workgroup
+def test_probe_pooled_and_alone(g, oracle, n_req):
+    """Requests whose prefix ends at an edge of a chunk of keys, by a key that is not in the tree or by a tombstone, in
+    workgroups of every kind: keys shared out, just as many as threads and one more, first chunks just full enough to go on
+    alone, and one key fewer."""
+    print("pooled or alone", n_req, flush=True)
+    n, dead = 40_000, 1_000
+    runs, tree, stored = _stored_keys(g, n, dead)
+    rs = np.random.RandomState(n_req)
+    per = -(-n_req // 256)
+    edges = [0, 1, 63, 64, 65, 127, 128, 129, 255, 256]
+    groups = [lambda i: int(rs.choice(edges)), lambda i: 256, lambda i: 256 if i < 4 else 0, lambda i: 256 if i < 4 else (1 if i == 4 else 0),
+              lambda i: 60, lambda i: 59 if i == 0 else 60,  # 60 keys on average go on alone
+              lambda i: 0, lambda i: int(rs.choice([0, 200])), lambda i: int(rs.choice([0, 17, 64, 80]))]
+    cut = np.array([groups[r // per % len(groups)](r % per) for r in range(n_req)])
+    nb = np.where(rs.rand(n_req) < 0.3, np.maximum(cut, 1), 256)
+    at = rs.randint(0, n - 256, size=n_req)[:, None] + np.arange(256)
+    ends = rs.rand(n_req) < 0.2  # by a tombstone somewhere before the cut
+    where = (rs.rand(n_req) * cut).astype(np.int64)
+    at[np.arange(n_req)[ends], where[ends]] = n + rs.randint(0, dead, size=int(ends.sum()))
+    q = stored[torch.from_numpy(at).to(dev())]
+    q[:, :, 3] = torch.from_numpy(np.arange(256)[None, :] >= cut[:, None]).to(dev()).to(torch.int64)  # a key of no run from the cut on
+    nb = torch.from_numpy(nb.astype(np.int32)).to(dev())
+    want = oracle.probe(q, nb, [r.cpu() for r in runs])
     assert_probe_equal(oracle, probe_gpu(g, q, nb, tree), want)
 
 
@@ -595,6 +636,23 @@ def test_an_empty_run_does_not_slow_lookups_down(g, oracle, cfg1, n_req):
     without, beside = _times(calls)
     print(f"{n_req} requests: {without:.1f} us, beside an empty run {beside:.1f}", flush=True)
     assert beside < 1.6 * without
+    assert int(hit_len.max()) == 0 and not hits.any()
+
+
+@pytest.mark.parametrize("n_req", [2049, 4096, 4097])
+def test_keys_behind_a_tombstone_do_not_slow_lookups_down(g, n_req):
+    """Requests of 256 stored keys, the first a tombstone, against their first 64 keys alone: looking all of them up took
+    three times as long."""
+    _, tree, stored = _stored_keys(g, 200_000, 5_000)
+    rs = np.random.RandomState(n_req)
+    at = rs.randint(0, 199_000, size=(n_req, 256))
+    at[:, 0] = 200_000 + rs.randint(0, 5_000, size=n_req)
+    q = stored[torch.from_numpy(at).to(dev())]
+    hit_len, hits = torch.empty(n_req, dtype=torch.int32, device=dev()), torch.empty((n_req, 256, 2), dtype=torch.int64, device=dev())
+    nb = [torch.full((n_req,), n, dtype=torch.int32, device=dev()) for n in (64, 256)]
+    first, all_keys = _times([lambda b=b: g.lsm_probe(q, b, tree, hit_len, hits) for b in nb])
+    print(f"{n_req} requests: 64 keys {first:.1f} us, 256 keys {all_keys:.1f}", flush=True)
+    assert all_keys < 1.6 * first
     assert int(hit_len.max()) == 0 and not hits.any()
 
 
