@@ -604,17 +604,19 @@ static int make_tree_table(const lsm_tree_t* tree, lsm::TreeTable& tt) {
     return LSM_OK;
 }
 
+static int compute_units(uint32_t& cus) {
+    int device = 0, n = 0;
+    if (hipGetDevice(&device) != hipSuccess || hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || n <= 0)
+        return LSM_ERR_HIP;
+    cus = (uint32_t)n;
+    return LSM_OK;
+}
+
 // Workgroups of `threads` for n_req requests of `spread` waves each: at most four per compute unit, each striding over the
 // requests.
-static int probe_grid(uint32_t n_req, uint32_t spread, int threads, uint32_t& blocks) {
-    int device = 0, cus = 0;
-    if (hipGetDevice(&device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
-        return LSM_ERR_HIP;
-    const uint32_t per_block = threads / lsm::kWave / spread;
-    blocks = (n_req + per_block - 1) / per_block;
-    if (blocks > (uint32_t)cus * 4) blocks = (uint32_t)cus * 4;
-    return LSM_OK;
+static uint32_t probe_grid(uint32_t n_req, uint32_t spread, int threads, uint32_t cus) {
+    const uint32_t per_block = threads / lsm::kWave / spread, blocks = (n_req + per_block - 1) / per_block;
+    return blocks > cus * 4 ? cus * 4 : blocks;
 }
 
 // Waves per request: four up to 512 requests, two up to 2,048 (about 4,096 waves, half of what the chip holds; beyond, the
@@ -643,15 +645,11 @@ static int threads_for(uint32_t n_req, uint32_t spread) { return spread == 1 && 
 // one chunk of keys (4,096 requests on 20M entries with filters, rows of 64 keys 32.6 / 33.6 us, of 100 48.6 / 38.3), and every
 // run ruled out by a filter or an index.  The requests are spread over all compute units: 2,049 of 256 live keys on 20M entries
 // 161 us with a wave each, 166 with nine requests in a workgroup, 230 with 16.
-static uint32_t pool_groups(const lsm::TreeTable& tt, const lsm_queries_t& queries, uint32_t& per_group) {
-    int device = 0, cus = 0;
-    if (queries.n_req <= 2048 || queries.max_blocks <= (uint32_t)lsm::kWave || hipGetDevice(&device) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess || cus <= 0)
-        return 0;
+static uint32_t pool_groups(const lsm::TreeTable& tt, const lsm_queries_t& queries, uint32_t cus, uint32_t& per_group) {
+    if (queries.n_req <= 2048 || queries.n_req > lsm::kPoolRequests * cus || queries.max_blocks <= (uint32_t)lsm::kWave) return 0;
     for (uint32_t r = 0; r < tt.n_runs; r++)
         if (tt.run[r].n != 0 && tt.run[r].bloom_blocks == 0 && tt.run[r].index == nullptr) return 0;
-    if (queries.n_req > lsm::kPoolRequests * (uint32_t)cus) return 0;
-    per_group = (queries.n_req - 1) / (uint32_t)cus + 1;
+    per_group = (queries.n_req - 1) / cus + 1;
     return (queries.n_req - 1) / per_group + 1;
 }
 
@@ -669,7 +667,7 @@ static void launch_probe(uint32_t spread, int threads, uint32_t blocks, const ls
         hipLaunchKernelGGL(kernel, dim3(blocks), dim3(threads), 0, stream, tt, queries->keys, queries->n_blocks, queries->n_req, queries->max_blocks,
                            out_hits->hit_len, out_hits->hits);
     };
-if (spread == 4) launch(lsm::probe_kernel<kTop, 4, lsm::kProbeThreads>);
+    if (spread == 4) launch(lsm::probe_kernel<kTop, 4, lsm::kProbeThreads>);
     else if (spread == 2) launch(lsm::probe_kernel<kTop, 2, lsm::kProbeThreads>);
     else if (threads == lsm::kProbeThreads) launch(lsm::probe_kernel<kTop, 1, lsm::kProbeThreads>);
     else launch(lsm::probe_kernel<kTop, 1, lsm::kProbeThreadsFew>);
@@ -694,14 +692,13 @@ extern "C" int lsm_probe(const lsm_queries_t* queries, const lsm_tree_t* tree, c
     if ((reinterpret_cast<uintptr_t>(queries->keys) & 15) != 0 || (reinterpret_cast<uintptr_t>(out_hits->hits) & 15) != 0)
         return LSM_ERR_BAD_ARG;
     TreeTable tt;
-    uint32_t blocks = 0;
+    uint32_t cus = 0, per_group = 0;
     int rc = make_tree_table(tree, tt);
+    if (rc == LSM_OK) rc = compute_units(cus);
+    if (rc != LSM_OK) return rc;
     const uint32_t spread = spread_for(queries->n_req, queries->max_blocks);
     const int threads = threads_for(queries->n_req, spread);
-    if (rc == LSM_OK) rc = probe_grid(queries->n_req, spread, threads, blocks);
-    if (rc != LSM_OK) return rc;
-    uint32_t per_group = 0;
-    const uint32_t pools = pool_groups(tt, *queries, per_group);
+    const uint32_t blocks = probe_grid(queries->n_req, spread, threads, cus), pools = pool_groups(tt, *queries, cus, per_group);
     if (pools != 0 && all_indexed(tt)) launch_pool<false>(pools, per_group, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     else if (pools != 0) launch_pool<true>(pools, per_group, tt, queries, out_hits, static_cast<hipStream_t>(stream));
     else if (all_indexed(tt)) launch_probe<false>(spread, threads, blocks, tt, queries, out_hits, static_cast<hipStream_t>(stream));
@@ -717,11 +714,12 @@ extern "C" int lsm_probe_length(const lsm_queries_t* queries, const lsm_tree_t* 
     if (queries->keys == nullptr || queries->n_blocks == nullptr || hit_len == nullptr) return LSM_ERR_NULL;
     if ((reinterpret_cast<uintptr_t>(queries->keys) & 15) != 0) return LSM_ERR_BAD_ARG;
     TreeTable tt;
-    uint32_t blocks = 0;
+    uint32_t cus = 0;
     int rc = make_tree_table(tree, tt);
-    const int threads = threads_for(queries->n_req, 1);
-    if (rc == LSM_OK) rc = probe_grid(queries->n_req, 1, threads, blocks);
+    if (rc == LSM_OK) rc = compute_units(cus);
     if (rc != LSM_OK) return rc;
+    const int threads = threads_for(queries->n_req, 1);
+    const uint32_t blocks = probe_grid(queries->n_req, 1, threads, cus);
     if (all_indexed(tt)) launch_probe_length<false>(threads, blocks, tt, queries, hit_len, static_cast<hipStream_t>(stream));
     else launch_probe_length<true>(threads, blocks, tt, queries, hit_len, static_cast<hipStream_t>(stream));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
