@@ -144,12 +144,14 @@ __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJo
 // The runs of `jobs`, all with small filters; `cleared`: the filters are known to be all zero.  A thread hashes one key
 // (hashing is some 800 cycles a key and wave: four per thread took 11 us where one takes 6), or two when one would be
 // more than a workgroup of them for every compute unit (16 x 30,000 keys: 19 us against 22).  On memory that is not zero,
-// shares are two launches, and up to `one_launch` keys a workgroup takes a whole run: 2,500 keys 5.0 us against 7.0, 4,096 6.9
+// shares are two launches, and up to kOneLaunch keys a workgroup takes a whole run: 2,500 keys 5.0 us against 7.0, 4,096 6.9
 // against 7.0, 5,000 8.2 against 7.1.  Calls for many runs are bound by the host, which the second launch costs 2.5 us (one run
-// of 5,000 keys 8.7 against 11.4, of 8,192 12.1 against 12.4).
-constexpr uint64_t kOneLaunch = 4 * kBloomSmallThreads, kOneLaunchBatch = 8 * kBloomSmallThreads;
+// of 5,000 keys 8.7 against 11.4, of 8,192 12.1 against 12.4).  Filters of runs whose lengths are on the device are built on
+// cleared memory only.
 template <uint32_t kRuns, typename Lengths>
-static void launch_bloom_small(const BloomJobs<kRuns>& jobs, const Lengths& lengths, uint32_t count, bool cleared, uint64_t one_launch, hipStream_t stream) {
+static void launch_bloom_small(const BloomJobs<kRuns>& jobs, const Lengths& lengths, uint32_t count, bool cleared, hipStream_t stream) {
+    constexpr int kMostAhead = !std::is_same<Lengths, KnownLengths>::value ? 2 : (kRuns == 1 ? 4 : 8);
+    constexpr uint64_t kOneLaunch = (uint64_t)kMostAhead * kBloomSmallThreads;
     uint64_t most_keys = 0, all_keys = 0;
     uint32_t most_blocks = 0;
     for (uint32_t j = 0; j < count; j++) {
@@ -158,7 +160,7 @@ static void launch_bloom_small(const BloomJobs<kRuns>& jobs, const Lengths& leng
         all_keys += jobs.n[j];
     }
     int ahead = all_keys > 256ull * kBloomSmallThreads || (most_keys > kBloomSmallThreads && most_keys <= 2 * kBloomSmallThreads) ? 2 : 1;
-    if (!cleared && most_keys > 2 * kBloomSmallThreads && most_keys <= one_launch) ahead = most_keys <= 4 * kBloomSmallThreads ? 4 : 8;
+    if (!cleared && most_keys > 2 * kBloomSmallThreads && most_keys <= kOneLaunch) ahead = most_keys <= 4 * kBloomSmallThreads ? 4 : 8;
     const uint64_t share = ahead * (uint64_t)kBloomSmallThreads;
     const dim3 grid(most_keys ? (uint32_t)((most_keys + share - 1) / share) : 1, count), threads(kBloomSmallThreads);
     if (grid.x > 1 && !cleared) {
@@ -169,10 +171,11 @@ static void launch_bloom_small(const BloomJobs<kRuns>& jobs, const Lengths& leng
     }
     auto launch = [&](auto blocks) {
         constexpr uint32_t kBlocks = decltype(blocks)::value;
-        if (ahead == 8) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 8, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
-        else if (ahead == 4) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 4, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
-        else if (ahead == 2) hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 2, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
-        else hipLaunchKernelGGL((bloom_small_kernel<kBlocks, 1, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths);
+        auto with = [&](auto keys) { hipLaunchKernelGGL((bloom_small_kernel<kBlocks, decltype(keys)::value, kRuns, Lengths>), grid, threads, 0, stream, jobs, lengths); };
+        if (ahead == 1) with(std::integral_constant<int, 1>{});
+        else if (ahead == 2) with(std::integral_constant<int, 2>{});
+        else if (ahead == 4) with(std::integral_constant<int, kMostAhead < 4 ? kMostAhead : 4>{});
+        else with(std::integral_constant<int, kMostAhead>{});
     };
     if (most_blocks > kBloomSmallBlocks / 2) launch(std::integral_constant<uint32_t, kBloomSmallBlocks>{});
     else launch(std::integral_constant<uint32_t, kBloomSmallBlocks / 2>{});
@@ -276,7 +279,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
         jobs.n[0] = run->n;
         jobs.words[0] = static_cast<uint32_t*>(filter_out);
         jobs.n_blocks[0] = (uint32_t)n_blocks;
-        launch_bloom_small(jobs, KnownLengths(), 1, false, kOneLaunch, stream);
+        launch_bloom_small(jobs, KnownLengths(), 1, false, stream);
         return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
     }
     uint64_t clear_blocks = (n_blocks + 255) / 256;
@@ -301,7 +304,7 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
         for (uint32_t j = 0; j <= n_runs; j++) {
             if (count == kBloomBatch || (j == n_runs && count > 0)) {
                 if (large == 0) {
-                    launch_bloom_small(jobs, KnownLengths(), count, cleared, kOneLaunchBatch, stream);
+                    launch_bloom_small(jobs, KnownLengths(), count, cleared, stream);
                 } else {
                     uint64_t cx = (most_blocks + 255) / 256, ix = (most_entries + 255) / 256;
                     if (cx > 1024) cx = 1024;
@@ -353,7 +356,7 @@ static void launch_counted(const CountedFilter* filters, uint32_t count, hipStre
         }
         if (taken == 0) continue;
         if (large == 0) {
-            launch_bloom_small(jobs, lengths, taken, true, kOneLaunchBatch, stream);
+            launch_bloom_small(jobs, lengths, taken, true, stream);
         } else {
             const uint64_t blocks = (most + 255) / 256;
             hipLaunchKernelGGL((bloom_insert_batch_kernel<kRuns, CountedLengths<kRuns>>), dim3((uint32_t)(blocks > 4096 ? 4096 : blocks), taken), dim3(256), 0,
