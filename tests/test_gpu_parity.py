@@ -52,7 +52,7 @@ def test_generator_is_identical_on_cpu_and_gpu(cfg1):
     assert all(torch.equal(a.cpu(), b) for a, b in zip(cfg1.runs, w.runs))
 
 
-@pytest.mark.parametrize("scale,flags", [(256, 1), (256, 0), (64, 1), (12, 1)])  # scale 12: 5.6M entries, the sampled partition
+@pytest.mark.parametrize("scale,flags", [(256, 1), (256, 0), (64, 1), (12, 1), (6, 1)])  # 5.6M entries: searched directly; 11.2M: sampled
 def test_scaled_config3_tiered_16way(g, oracle, scale, flags):
     from workloads import lsm
     print("config3 scale", scale, "flags", flags, flush=True)
@@ -430,18 +430,28 @@ def test_many_runs_one_after_the_other_are_not_slow(g, oracle):
     assert took < 3 * base
 
 
-@pytest.mark.parametrize("k,tiles", [(3, 10240), (5, 8192), (16, 5120), (17, 2048), (40, 2048)])
-def test_searched_directly_or_on_samples(g, oracle, k, tiles):
+@pytest.mark.parametrize("k,tiles,shape", [(k, tiles, "uneven") for k, tiles in [(1, 10240), (3, 10240), (5, 8192), (16, 5120), (17, 2048), (40, 2048)]]
+                         + [(17, 2048, "copies"), (40, 2048, "copies")])
+def test_searched_directly_or_on_samples(g, oracle, k, tiles, shape):
     """The longest input whose boundaries are searched in the runs themselves and the shortest that is sampled; runs of very
-    different lengths, an empty one among them, and ones that cover a part of the keys only."""
+    different lengths, an empty one among them, and ones that cover a part of the keys only; or the same keys in every run, so
+    that the samples tie."""
     rs = np.random.RandomState(k)
     for total in ((tiles - 1) * (2048 - k), (tiles - 1) * (2048 - k) + 1):
-        print("direct or sampled", k, total, flush=True)
-        lens = np.maximum(1, (total * rs.dirichlet(np.full(k, 0.7)) * 0.999).astype(np.int64))
-        lens[0] = 0
-        lens[-1] += total - lens.sum()
-        runs = _runs_of(oracle, rs, lens, 2 * total)
-        runs[1][:, 0] |= 1  # the keys' first byte, as stored: a run behind all others
+        print("direct or sampled", k, total, shape, flush=True)
+        if shape == "copies":
+            lens = np.full(k, total // k)
+            lens[0] += total - lens.sum()
+            one = _runs_of(oracle, rs, [int(lens[0])], 2 * total)[0]
+            runs = [one[:n].clone() for n in lens]
+            for r in runs:
+                r[:, 4] = torch.randint(0, 1 << 40, (r.shape[0],), device=dev())
+        else:
+            lens = np.maximum(1, (total * rs.dirichlet(np.full(k, 0.7)) * 0.999).astype(np.int64))
+            lens[0] = 0
+            lens[-1] += total - lens.sum()
+            runs = _runs_of(oracle, rs, lens, 2 * total)
+            runs[min(1, k - 1)][:, 0] |= 1  # the keys' first byte, as stored: a run behind all others
         _check_compact(g, oracle, runs, int(total & 1))
         del runs
         torch.cuda.empty_cache()
@@ -814,7 +824,8 @@ def test_filter_hashes_written_by_the_compaction(g, oracle, cfg1, case):
     elif case == "empty":
         runs = [cfg1.runs[0][:0].contiguous()]
     else:
-        runs = lsm.config3(device=dev(), scale=12).runs   # 5.6M entries: the sampled partition, thousands of tiles
+        runs = lsm.config3(device=dev(), scale=12).runs
+        runs = runs[:-1] + [runs[-1][::2].contiguous(), runs[-1][1::2].contiguous()]  # 17 runs, 5.6M entries: the sampled partition, thousands of tiles
     total = sum(int(r.shape[0]) for r in runs)
     for flags, bits in ((1, 16), (0, 7)):
         hashes = torch.full((max(total, 1),), -1, dtype=torch.int64, device=dev())
