@@ -69,10 +69,12 @@ constexpr uint32_t kMinStride = 8;
 constexpr uint32_t kRowStride = 256;
 constexpr uint64_t kSampleStride = 32;  // one key in 32 is copied for the sampled partition
 // Inputs of fewer tiles search the runs directly, a wave per boundary, larger ones on a copy of every 32nd key first.  The samples
-// cost some 100 us in four dependent launches whatever the input, the direct search grows with the boundaries, and with the runs.
-// Direct / sampled: 3 runs of 4.3M entries in all 29 / 105 us, 18M 103 / 133, 26M 140 / 146; 4 runs, 18M 124 / 141, 22M 151 /
+// cost 100 to 150 us in four dependent launches up to there, the direct search grows with the boundaries, and with the runs.
+// Direct / sampled, mixed runs: 3 runs of 4.3M entries in all 29 / 105 us, 18M 103 / 133, 26M 140 / 146; 4 runs, 18M 124 / 141, 22M 151 /
 // 146; 8 runs, 4.3M 44 / 111, 13M 121 / 144, 18M 156 / 159; 16 runs, 4.3M 59 / 123, 10.5M 152 / 153; 32 runs, 4.3M 140 / 141,
-// 6M 165 / 149.
+// 6M 165 / 149.  Runs that cover different keys cost either search more, the samples the most.  Whole calls, runs one after the
+// other / in turns of 100 entries / with the same keys: 4 runs of 18M entries in all, direct 597 / 651 / 508 us, sampled
+// 775 / 734 / 542; 8 runs, 15M, 558 / 631 / 507 and 736 / 701 / 517; 16 runs, 9.5M, 487 / 483 / 452 and 626 / 694 / 450.
 constexpr uint64_t kSampledMinTiles = 2048;
 constexpr uint64_t kDirectMostTiles = 10240;
 __host__ __device__ inline uint64_t direct_tiles(uint32_t k) { return k <= 4 ? kDirectMostTiles : (k <= 8 ? 8192 : (k <= 16 ? 5120 : kSampledMinTiles)); }
@@ -1499,13 +1501,13 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
 }
 
 // ---------------------------------------------------------------------------------------
-// Partition of a batch of independent compactions: one wave per tile of the launch.  The wave of a job's tile number
-// t > 0 searches boundary t over the job's whole runs (the jobs of a batch are small); the waves of a job's first and
-// last tile also write the first (all zero) and the last (run lengths) row of its split table, and every wave clears its
-// tile's status word.
+// Partition of a batch of independent compactions.  A job of boundaries at ranked samples has a wave per sample (ranked_row),
+// any other one a wave per tile, the wave of tile t > 0 searching boundary t over the job's whole runs (the jobs of a batch are
+// small).  A job's first wave also writes the first (all zero) and the last (run lengths) row of its split table; its waves
+// together write the job number and clear the status word of each of its tiles.
 // ---------------------------------------------------------------------------------------
 // A batch that is small enough travels as a kernel argument (kInline): the partition's waves take their job from there,
-// and those of the jobs' first tiles put the descriptors where the merge kernel looks for them.  (Copying the table first
+// and the jobs' first ones put the descriptors where the merge kernel looks for them.  (Copying the table first
 // was a transfer of 4 us before the first kernel, and a wait of the host for the previous one.)
 constexpr uint32_t kInlineJobs = 20, kInlineRuns = 56;
 struct BatchInline {

@@ -439,7 +439,7 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
         cur ^= 1;
     }
 
-    // ---- which positions share their 14 bytes with a neighbour?  c[] holds this thread's eight sorted records.
+    // ---- which positions share their 14 bytes with a neighbour?  c[] holds this thread's four sorted records.
     bool any = false, all = true;
     {
         Rec prev = c[0];
