@@ -370,11 +370,12 @@ __global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const u
 // (probe_kernel) is the chain of its longest requests, which look up two or three chunks of keys one after the other, while
 // the waves of requests that share nothing with the tree (30 %) are done at once; here nearly every workgroup has one round of
 // lookups, and its fence table is read once per compute unit.  A wave each / pooled, trees with filters: 4,096 requests on
-// 100M entries 58.2 / 47.5 us (with indices as well 44.8 / 40.3), on 20M 52.5 / 46.0, on 1M 41.6 / 38.7; 2,500 requests on 100M
-// 54.2 / 40.4, on 1M 33.6 / 29.7; indices only, 4,096 on 100M 62.1 / 56.7.
-// Where waves have nothing to share, each goes on with its own request, and a key behind one that is not live is not
-// looked up: 4,096 requests of 256 keys on 20M entries whose first key is a tombstone 86.6 us with a wave each, 314 with all
-// keys shared out, 86.2 so; whose keys are all live 315 / 308 / 318, on 1M entries with filters and indices 84 / 107 / 90.
+// 100M entries 58.2 / 48.6 us (with indices as well 48.0 / 40.6), on 20M 52.3 / 46.2, on 1M 42.0 / 35.8; 2,500 requests on 100M
+// 54.5 / 41.4, on 1M 34.3 / 29.2; indices only, 4,096 on 100M 63.2 / 56.3.
+// Where waves have nothing to share, each goes on with its own request, and so it does behind the first round where there are more
+// keys than threads: a key behind one that is not live is not looked up.  4,096 requests of 256 keys on 20M entries
+// whose first key is a tombstone 87 us with a wave each, 314 with all keys shared out, 87 so; whose keys are all live
+// 314 / 308 / 321, on 1M entries with filters and indices 85 / 107 / 87.
 constexpr int kPoolRequests = 16;
 constexpr int kPoolThreads = 1024;
 template <bool kTop>
@@ -408,20 +409,24 @@ __global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree
         if (out != 0) out_at = admitted_to + (uint32_t)__ffsll((unsigned long long)out) - 1;
         admitted_to = min(admitted_to + (uint32_t)kWave, out_at);
     };
-    bool alone = false;                // whether every wave looks up its own request's keys, 64 at a time
-    uint32_t from[kPoolRequests + 1];  // where a request's keys start in the list of all
-    from[0] = 0;
+    bool alone = false;  // whether every wave looks up its own request's keys, 64 at a time
+    uint32_t cap = 0;    // most keys of a request that are shared out: with all, there would be more than threads
     for (int rest = 0; rest < 2 && !alone; rest++) {
         while (admitted_to < out_at && (rest != 0 || admitted_to == 0)) admit();
         if (lane == 0) admitted_keys[rest][my_r] = admitted_to;
         __syncthreads();
+        uint32_t all = 0, capped = 0;
 #pragma unroll
-        for (int r = 0; r < kPoolRequests; r++) from[r + 1] = from[r] + admitted_keys[rest][r];
-        // Nothing to share: (nearly) every wave has a chunk of keys, or there are more keys than threads
-        alone = rest == 0 ? from[kPoolRequests] >= requests * (kWave - kWave / 16) : from[kPoolRequests] > (uint32_t)kPoolThreads;
+        for (int r = 0; r < kPoolRequests; r++) {
+            const uint32_t n = admitted_keys[rest][r];
+            all += n;
+            capped += min(n, 4 * (lane + 1));
+        }
+        alone = rest == 0 && all >= requests * (kWave - kWave / 16);  // nothing to share: (nearly) every wave has a chunk of keys
+        cap = 4 * (uint32_t)__popcll(__ballot(capped <= (uint32_t)kPoolThreads));  // 64 at least, 256 where all keys have a thread
     }
-    uint32_t dead_at = ~0u;
-    for (uint32_t start = 0;; start += kWave) {
+    uint32_t dead_at = ~0u, start = 0;
+    for (;;) {
         uint32_t r = my_r, j = start + lane;
         bool mine;
         if (alone) {
@@ -429,13 +434,15 @@ __global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree
             if (start >= out_at) break;
             mine = j < admitted_to;
         } else {
-            uint32_t base = 0;
+            uint32_t from = 0, base = 0;  // where a request's keys start in the list of all
             r = 0;
 #pragma unroll
-            for (int q = 1; q < kPoolRequests; q++)
-                if (tid >= from[q]) r = q, base = from[q];
+            for (int q = 0; q < kPoolRequests; q++) {
+                if (tid >= from) r = q, base = from;
+                from += min(admitted_keys[1][q], cap);
+            }
             j = tid - base;
-            mine = tid < from[kPoolRequests];
+            mine = tid < from;
         }
         Key q = {{0, 0, 0, 0}};
         uint64_t maybe = 0, bh = 0;
@@ -446,19 +453,23 @@ __global__ void __launch_bounds__(kPoolThreads) probe_pool_kernel(TreeTable tree
         }
         uint4 h = make_uint4(0, 0, 0, 0);
         const bool live = probe_walk<kTop>(s, maybe, bh, mine, q, h);
-        uint32_t dead;  // of request r, so far
+        uint32_t dead;  // first key of request r that is not live, so far
         if (alone) {
             const uint64_t not_live = __ballot(!live);
             if (not_live != 0) dead_at = start + (uint32_t)__ffsll((unsigned long long)not_live) - 1;
             dead = dead_at;
+            start += kWave;
         } else {
             if (!live) atomicMin(&first_dead[r], j);
             __syncthreads();
             dead = first_dead[r];
             dead_at = first_dead[my_r];
+            alone = true;  // with the keys beyond the cap, if any
+            start = min(admitted_to, cap);
         }
+        // a request's later keys come later: what is found dead among them does not change this
         if (mine && j < dead) reinterpret_cast<uint4*>(hits)[(uint64_t)(first_req + r) * max_blocks + j] = h;
-        if (!alone || dead_at != ~0u) break;
+        if (dead_at != ~0u) break;
     }
     if (my_r >= requests) return;
     const uint32_t result = min(out_at, dead_at);

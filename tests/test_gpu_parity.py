@@ -587,8 +587,8 @@ def _stored_keys(g, n, tombstones):
 @pytest.mark.parametrize("n_req", [2049, 2305, 4096])  # 9, 10 and 16 requests in a workgroup
 def test_probe_pooled_and_alone(g, oracle, n_req):
     """Requests whose prefix ends at an edge of a chunk of keys, by a key that is not in the tree or by a tombstone, in
-    workgroups of every kind: keys shared out, just as many as threads and one more, first chunks just full enough to go on
-    alone, and one key fewer."""
+    workgroups of every kind: keys shared out, just as many as threads and more, so that the waves go on with the rest, first
+    chunks just full enough to go on without, and one key fewer."""
     print("pooled or alone", n_req, flush=True)
     n, dead = 40_000, 1_000
     runs, tree, stored = _stored_keys(g, n, dead)
