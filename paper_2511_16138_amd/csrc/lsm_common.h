@@ -143,6 +143,9 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
 // table, so the compiler cannot tell): a global instead of a flat load.
 __device__ __forceinline__ uint4 load_global_u4(const uint4* p) { typedef uint32_t v4 __attribute__((ext_vector_type(4))); const v4 v = *(const __attribute__((address_space(1))) v4*)p; return make_uint4(v.x, v.y, v.z, v.w); }
 
+// 16-byte store of output that nothing on the chip reads soon: it does not displace what the L2 holds.
+__device__ __forceinline__ void store_streaming_u4(uint4* p, const uint4 q) { typedef uint32_t v4 __attribute__((ext_vector_type(4))); const v4 v = {q.x, q.y, q.z, q.w}; __builtin_nontemporal_store(v, (__attribute__((address_space(1))) v4*)p); }
+
 // Bloom filter addressing: the block of a key and the six bits it sets or tests there, as four 32-bit masks.
 __device__ __forceinline__ uint64_t mix64(uint64_t x) {
     x ^= x >> 30;

@@ -1473,11 +1473,16 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
             if (kMode != kModeRange && tile == last_tile && tid == 0) *n_out = failed ? ~0ull : base + total;
             if (failed) return;
         }
+        // Nontemporal: whole lines leave the L2 at once and take no place from the lines that other tiles are loading (each is
+        // asked for four times, 16 bytes at a time).  2M + 20M entries 675 -> 635 us, 4.4 TB/s; 16 x 4M 2648 -> 2508, 8 x 500k with
+        // fences and hashes 338 -> 325; inputs of a few tiles are the same.  Nontemporal loads instead lose (2M + 20M 800 us): a
+        // line is gone before its other three quarters are asked for.  So do loads of whole lines by four lanes (660, 2540), which
+        // cost a transposition in registers, and reading the tile 256 to 1,024 further on ahead (737 to 823, 2725 to 2930).
         const uint32_t count = min(total - first, (uint32_t)kStageEntries);
         uint4* dst = reinterpret_cast<uint4*>(out + base + first);
         for (uint32_t c = tid; c < count * 4; c += kMergeThreads) {
             const uint32_t part = (c ^ (c >> 2)) & 3;  // which 16 bytes of the entry stage[c] holds
-            dst[(c & ~3u) | part] = stage[c];
+            store_streaming_u4(&dst[(c & ~3u) | part], stage[c]);
         }
         if (kExtras && fence_out != nullptr) {
             // fence index of the new run: the key of every fence_stride-th output entry.  The first one of this pass is the only
