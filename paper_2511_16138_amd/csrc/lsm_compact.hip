@@ -17,6 +17,7 @@
 //                     (the fewer runs, the later) first bracket every boundary, a group of lanes each, on a copy of every
 //                     32nd key (sample_kernel, sample_rank_kernel, sample_fine_kernel) and search
 //                     the runs only inside the brackets (bracket_partition_kernel).
+//   merge_short_kernel  inputs of up to a tile per compute unit (below: what it does differently).
 //   merge_kernel      one workgroup per tile: every thread loads its share of the tile's entries
 //                     into registers, 16-byte surrogates (14 key bytes + index) are merged in LDS
 //                     by ceil(log2 k) rounds of stable two-way merge-path merges, the newest
@@ -47,9 +48,16 @@ __host__ __device__ inline uint64_t tile_nominal(uint32_t k) { return (uint64_t)
 // An input of fewer tiles than the chip has compute units is cut into shorter ones: a tile is a serial chain (load, merge
 // rounds, look-back, store) on one compute unit, and with fewer entries every step of it has less to move.
 // Long tiles throughout against this: 4 x 16,384 entries 37.8 -> 36.2 us, a write buffer of 100,001 128.5 -> 122.6, 96
-// driver flushes 3.59 -> 3.22 ms.  256 or 1,024 as the shortest, or 512 tiles, are within 4 % of it.
+// driver flushes 3.59 -> 3.22 ms.  256 as the shortest is within 4 % of it, 960 up to 2 us slower for three runs or more.
 constexpr uint64_t kFillTiles = 256;
 constexpr uint64_t kMinSpacing = 512;
+// Up to a tile for every compute unit the tile is merged by merge_short_kernel: with one workgroup on a compute unit what counts is
+// the chain of dependent steps, not how much the unit gets done, and one thread per entry has the shorter chain.  Both forms, us a call:
+// 2 runs of 4,000 entries in all 15.2 / 13.5, 60,000 17.9 / 14.7, 300,000 24.0 / 21.4, 500,000 27.6 / 27.1; 8 runs, 4,000 23.8 /
+// 18.5, 100,000 27.3 / 21.9; 24 runs, 100,000 35.2 / 31.1.  More tiles take turns, and merge_kernel gets more of them done.
+constexpr int kShortThreads = 1024;
+constexpr int kShortItems = kTileCap / kShortThreads;
+constexpr uint64_t kShortTiles = kFillTiles;
 inline uint32_t fill_spacing(uint64_t total) {
     const uint64_t even = (total + kFillTiles - 1) / kFillTiles;
     if (even < kMinSpacing) return (uint32_t)kMinSpacing;
@@ -62,6 +70,14 @@ __host__ __device__ inline uint32_t tile_spacing(uint32_t fill, uint32_t k) { re
 // (partition and merge, sampled against the window search: 16 runs, 600k entries 55 / 77 us with 10,300 samples, 750k 70 / 79
 // with 19,700, 900k 130 / 83 with 47,000; 64 runs of 300k in all 64 / 57 us with 23,000; 48 runs 40 / 57 with 16,700).
 constexpr uint64_t kRankedTiles = 512;
+// No more than a tile for every compute unit where they have up to kShortMean entries in the mean: 512 / 256 tiles, 200k entries, 4
+// runs 26.4 / 23.3 us, 8 runs 29.8 / 27.5, 24 runs 39.6 / 33.8; 300k 28.7 / 28.1, 31.9 / 30.2, 43.2 / 44.4; 400k 30.1 / 29.7, 33.8 /
+// 36.7, 48.4 / 92 (samples would be too many).  A tile of more than kShortThreads entries gives its threads two each, and every later
+// tile waits for it: samples are dense enough that there is none, if kShortSamples do.  4,000 entries, 8 / 16 / 24 runs, any tile up to the
+// capacity 17.7 / 24.3 / 26.0 us, none so long 16.6 / 18.7 / 20.2.  With 16,384 samples the partition loses what the tiles gain
+// (130k, 16 runs 28.6 -> 26.9, but 200k 29.3 -> 40.1).
+constexpr uint64_t kShortMean = 1280;
+constexpr uint64_t kShortSamples = 6144;
 constexpr uint64_t kMostSamples = 20480;
 constexpr uint32_t kMinStride = 8;
 // Samples from one ranked sample to the next (sampled partition): ranked rows + boundaries between them, 16 x 4M entries 51 + 124
@@ -766,19 +782,13 @@ constexpr uint32_t kNoSlot = 0xFFFF;          // of an entry that does not survi
 constexpr int kRepairMax = 32;                // longest prefix-tie group one thread puts in key order
 constexpr int kStageEntries = kTileCap / 2;  // output staging: 64 bytes per survivor, two passes at most
 
-struct MergeShared {
-    uint4 buf[2][kTileCap];          // surrogate ping-pong; then 2 x uint4 of key tail/seqno/type per position; then output staging
-    uint16_t rank[kTileCap];         // tile-local entry index -> merged position
-    alignas(8) uint16_t prefix[kTileCap];  // survivors before this merged position, kNoSlot if its entry does not survive
-    alignas(4) uint8_t flag[kTileCap + 8];  // per merged position: kFlagEq | kFlagFullEq; on the exact path: 1 = survives
+struct TileHead {  // what the whole workgroup knows of its tile
     uint32_t seg[LSM_MAX_RUNS + 1];  // start of each run's piece in tile-local index space
     uint64_t lo[LSM_MAX_RUNS];       // first entry of each run's piece
     const lsm_entry_t* run[LSM_MAX_RUNS];  // copy of the run pointers (indexed per lane)
-    uint32_t wave_count[kMergeThreads / kWave];
     uint32_t tile;                   // number of the tile inside its compaction (what the look-back counts in)
     uint32_t n;
     uint32_t failed;
-    uint32_t inexact;                // some position has an equal surrogate but a different key tail
     uint64_t base;
     // batched compactions only: what the single form takes from its kernel arguments
     uint32_t k, flags, job_tiles, fence_stride;
@@ -786,6 +796,15 @@ struct MergeShared {
     uint64_t* n_out;
     uint64_t* status;
     uint4* fence_out;
+};
+
+struct MergeShared : TileHead {
+    uint4 buf[2][kTileCap];          // surrogate ping-pong; then 2 x uint4 of key tail/seqno/type per position; then output staging
+    uint16_t rank[kTileCap];         // tile-local entry index -> merged position
+    alignas(8) uint16_t prefix[kTileCap];  // survivors before this merged position, kNoSlot if its entry does not survive
+    alignas(4) uint8_t flag[kTileCap + 8];  // per merged position: kFlagEq | kFlagFullEq; on the exact path: 1 = survives
+    uint32_t wave_count[kMergeThreads / kWave];
+    uint32_t inexact;                // some position has an equal surrogate but a different key tail
 };
 
 // The tile kernel has three forms.  Single: one compaction, tile = workgroup, pieces from the split table.
@@ -964,6 +983,84 @@ __device__ __forceinline__ void range_bounds(const RunTable& rt, const ModeArgs&
     if (own && member == 0) bounds[problem] = lo;
 }
 
+// The tile's k pieces; called by wave 0 only.  Tile number = workgroup number: the look-back below waits only for
+// tiles with smaller numbers, and workgroups are handed to the compute units in ascending order, so the
+// tiles waited for are resident or done.  (A ticket taken with an atomic would make that independent
+// of the dispatch order, but it costs a second dependent memory round trip before the first load: the
+// tickets come back in a different order than the workgroup numbers for 99 % of the tiles.)  The waits
+// are bounded in any case.
+template <int kMode>
+__device__ __forceinline__ void tile_pieces(TileHead& s, const RunTable& rt, const Workspace& ws, const uint64_t n_tiles, const ModeArgs& ma, const uint64_t* bounds) {
+    const int lane = threadIdx.x & (kWave - 1);
+    __builtin_amdgcn_s_setprio(3);  // the other waves wait for this one: let it issue first
+    uint64_t t = blockIdx.x;        // tile number inside its compaction
+    uint32_t kk = rt.k;
+    uint64_t a = 0, b = 0, len = ~0ull;
+    if (kMode == kModeSingle) {
+        if (lane < (int)kk) {
+            if (n_tiles == 1) {  // one tile is the whole input: launched on its own, without a split table
+                b = run_len(rt, lane);
+            } else {
+                a = ws.splits[t * kk + lane];
+                b = ws.splits[(t + 1) * kk + lane];
+                if (ws.stride != 0) len = run_len(rt, lane);  // exact ranks write every row, within the runs
+            }
+            s.run[lane] = rt.ptr[lane];
+        }
+    } else if (kMode == kModeRange) {
+        // the part of every run inside [lo_key, hi_key)
+        const Key lo_key = load_key(ma.lo_keys + t * LSM_KEY_BYTES), hi_key = load_key(ma.hi_keys + t * LSM_KEY_BYTES);
+        if (lane < (int)kk) {
+            a = bounds[2 * lane];
+            b = key_less(lo_key, hi_key) ? bounds[2 * lane + 1] : a;
+            s.run[lane] = rt.ptr[lane];
+        }
+    } else {
+        const JobDesc d = ma.jobs[ma.tile_job[t]];  // the same words for every lane
+        kk = d.k;
+        t -= d.first_tile;
+        if (lane < (int)kk) {
+            a = ws.splits[d.splits_off + t * kk + lane];
+            b = ws.splits[d.splits_off + (t + 1) * kk + lane];
+            s.run[lane] = ma.run_ptr[d.run_off + lane];
+            if (d.stride != 0) len = ma.run_n[d.run_off + lane];
+        }
+        if (lane == 0) {
+            s.k = kk;
+            s.flags = d.flags;
+            s.job_tiles = d.n_tiles;
+            s.out = d.out;
+            s.n_out = d.n_out;
+            s.status = ws.status + d.first_tile;
+            s.fence_out = d.fence_out;
+            s.fence_stride = d.fence_stride;
+        }
+    }
+    const bool mine = lane < (int)kk;
+    // piece lengths -> offsets (inclusive scan over the lanes); only inputs that break the precondition can make a row
+    // pair inconsistent, or leave a row of the sampled ranks unwritten
+    // (a key range may simply hold more than a tile: reported as an overflow of that range)
+    const bool bad = mine && (b < a || b > len || b - a > (uint64_t)kTileCap);
+    uint32_t incl = (mine && !bad) ? (uint32_t)(b - a) : 0;
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t v = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += v;
+    }
+    const uint32_t total = __shfl(incl, kWave - 1, kWave);
+    const bool ok = __ballot(bad) == 0 && total <= (uint32_t)kTileCap;
+    if (mine) {
+        s.lo[lane] = a;
+        s.seg[lane + 1] = ok ? incl : 0;
+    }
+    if (lane == 0) {
+        s.seg[0] = 0;
+        s.tile = (uint32_t)t;
+        s.n = ok ? total : 0;
+        s.failed = ok ? 0 : 1;
+    }
+    __builtin_amdgcn_s_setprio(0);
+}
+
 // two workgroups per compute unit = four waves per SIMD: at most 128 vector registers.
 // kExtras: what else the output pass does (compiled out otherwise).  1: rewrites value pointers and / or writes the fence
 // index; 2: also writes the filter hash of every survivor's key.
@@ -985,81 +1082,9 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         __syncthreads();
     }
 
-    // ---- the tile's k pieces, by wave 0.  Tile number = workgroup number: the look-back below waits only for
-    //      tiles with smaller numbers, and workgroups are handed to the compute units in ascending order, so the
-    //      tiles waited for are resident or done.  (A ticket taken with an atomic would make that independent
-    //      of the dispatch order, but it costs a second dependent memory round trip before the first load: the
-    //      tickets come back in a different order than the workgroup numbers for 99 % of the tiles.)  The waits
-    //      are bounded in any case.
     if (wave == 0) {
-        __builtin_amdgcn_s_setprio(3);  // the other waves wait for this one: let it issue first
-        uint64_t t = blockIdx.x;        // tile number inside its compaction
-        uint32_t kk = rt.k;
-        uint64_t a = 0, b = 0, len = ~0ull;
-        if (kMode == kModeSingle) {
-            if (lane < (int)kk) {
-                if (n_tiles == 1) {  // one tile is the whole input: launched on its own, without a split table
-                    b = run_len(rt, lane);
-                } else {
-                    a = ws.splits[t * kk + lane];
-                    b = ws.splits[(t + 1) * kk + lane];
-                    if (ws.stride != 0) len = run_len(rt, lane);  // exact ranks write every row, within the runs
-                }
-                s.run[lane] = rt.ptr[lane];
-            }
-        } else if (kMode == kModeRange) {
-            // the part of every run inside [lo_key, hi_key)
-            const Key lo_key = load_key(ma.lo_keys + t * LSM_KEY_BYTES), hi_key = load_key(ma.hi_keys + t * LSM_KEY_BYTES);
-            if (lane < (int)kk) {
-                a = bounds[2 * lane];
-                b = key_less(lo_key, hi_key) ? bounds[2 * lane + 1] : a;
-                s.run[lane] = rt.ptr[lane];
-            }
-        } else {
-            const JobDesc d = ma.jobs[ma.tile_job[t]];  // the same words for every lane
-            kk = d.k;
-            t -= d.first_tile;
-            if (lane < (int)kk) {
-                a = ws.splits[d.splits_off + t * kk + lane];
-                b = ws.splits[d.splits_off + (t + 1) * kk + lane];
-                s.run[lane] = ma.run_ptr[d.run_off + lane];
-                if (d.stride != 0) len = ma.run_n[d.run_off + lane];
-            }
-            if (lane == 0) {
-                s.k = kk;
-                s.flags = d.flags;
-                s.job_tiles = d.n_tiles;
-                s.out = d.out;
-                s.n_out = d.n_out;
-                s.status = ws.status + d.first_tile;
-                s.fence_out = d.fence_out;
-                s.fence_stride = d.fence_stride;
-            }
-        }
-        const bool mine = lane < (int)kk;
-        // piece lengths -> offsets (inclusive scan over the lanes); only inputs that break the precondition can make a row
-        // pair inconsistent, or leave a row of the sampled ranks unwritten
-        // (a key range may simply hold more than a tile: reported as an overflow of that range)
-        const bool bad = mine && (b < a || b > len || b - a > (uint64_t)kTileCap);
-        uint32_t incl = (mine && !bad) ? (uint32_t)(b - a) : 0;
-        for (int off = 1; off < kWave; off <<= 1) {
-            const uint32_t v = __shfl_up(incl, off, kWave);
-            if (lane >= off) incl += v;
-        }
-        const uint32_t total = __shfl(incl, kWave - 1, kWave);
-        const bool ok = __ballot(bad) == 0 && total <= (uint32_t)kTileCap;
-        if (mine) {
-            s.lo[lane] = a;
-            s.seg[lane + 1] = ok ? incl : 0;
-        }
-        if (lane == 0) {
-            s.seg[0] = 0;
-            s.tile = (uint32_t)t;
-            s.n = ok ? total : 0;
-            s.failed = ok ? 0 : 1;
-            s.inexact = 0;
-        }
-        __builtin_amdgcn_s_setprio(0);
+        if (lane == 0) s.inexact = 0;
+        tile_pieces<kMode>(s, rt, ws, n_tiles, ma, bounds);
     }
     __syncthreads();
     const uint64_t tile = s.tile;
@@ -1506,6 +1531,314 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
 }
 
 // ---------------------------------------------------------------------------------------
+// Tile merge where there is a compute unit for every tile: the time of a call is one tile's chain of dependent steps.
+//   - One thread per entry (two in tiles of more than kShortThreads).  It finds the entry's place in a merge round by one binary search
+//     in the other list of the pair and keeps surrogate and place in registers, so nothing is read back: 1.2 us a round of 512 entries,
+//     where merge_kernel, four outputs a thread, has two waves at work and takes 2.0.
+//   - Key tails, seqnos and types lie in LDS by entry from the load on.  An entry looks at its two neighbours in the final order, and
+//     only where one has the same 14 bytes goes on to the group's other members: order by the rest of the key, newest version and
+//     survival come out at once, without the passes that post them by position, compare, repair and count (1.1 us, 3.9 there).  A group longer
+//     than kRepairMax sends the tile to the exact path, as there.
+//   - Survivors are bits by position; every wave adds up the 64 words for itself.
+//   - The look-back asks for all earlier tiles' words at once.
+// LDS: 130 KB, one workgroup on a compute unit.  Whole kernel, 128 tiles of 512 entries of four runs 17.0 -> 11.4 us; one tile of a driver's merge 11.0 -> 8.6.
+// What is left of the 11.4: pieces 1.3, load 1.2, rounds 2.4, neighbours 1.4, look-back 2.6 (two trips through the
+// memory-side cache, and the spread of the tiles), stage and store 1.1.
+// ---------------------------------------------------------------------------------------
+constexpr int kShortWindows = (int)((kShortTiles + kWave - 1) / kWave);
+
+struct ShortShared : TileHead {
+    uint4 mem[4 * kTileCap];          // surrogate ping-pong, key tails, seqno / type by entry index; then output staging
+    uint32_t alive[kTileCap / 32];    // bit p: the entry at merged position p is an output entry
+    uint32_t deep;                    // some prefix-tie group is long
+};
+
+// lookback for tiles with no more than kShortTiles - 1 before them: all their status words are asked for at once.
+__device__ uint64_t lookback_few(uint64_t* status, const uint32_t tile, const uint64_t count, const bool self_failed, bool* failed) {
+    const int lane = threadIdx.x & (kWave - 1);
+    *failed = self_failed;
+    if (self_failed || tile == 0) {
+        if (lane == 0) __hip_atomic_store(&status[tile], self_failed ? kStFailed << kStShift : (kStPrefix << kStShift) | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return 0;
+    }
+    if (lane == 0) __hip_atomic_store(&status[tile], (kStAggregate << kStShift) | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    uint64_t base = 0;
+    bool bad = false;
+    for (uint32_t spins = 0;; spins++) {
+        uint64_t st[kShortWindows];  // lane l, window w: tile - 1 - 64 w - l
+#pragma unroll
+        for (int w = 0; w < kShortWindows; w++) {
+            const int t = (int)tile - 1 - w * kWave - lane;
+            st[w] = kStPrefix << kStShift;  // tiles before tile 0: an empty prefix
+            if (t >= 0) st[w] = __hip_atomic_load(&status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        bool ready = true, open = true;  // open: no prefix nearer than window w
+        base = 0;
+#pragma unroll
+        for (int w = 0; w < kShortWindows; w++) {
+            const uint64_t state = st[w] >> kStShift, pmask = __ballot(state == kStPrefix);
+            const int first = pmask ? __ffsll((unsigned long long)pmask) - 1 : kWave - 1;  // nearest tile with a full prefix
+            if (open) {
+                ready = ready && __ballot(lane <= first && state == kStEmpty) == 0;
+                bad = bad || __ballot(lane <= first && state == kStFailed) != 0;
+                base += lane <= first ? st[w] & kStValueMask : 0;
+            }
+            open = open && pmask == 0;
+        }
+        if (ready || bad) break;
+        bad = spins >= kSpinLimit;
+        if (bad) break;
+        __builtin_amdgcn_s_sleep(1);
+    }
+    base = wave_sum_u64(base);
+    *failed = bad;
+    const uint64_t word = bad ? (kStFailed << kStShift) : ((kStPrefix << kStShift) | (base + count));
+    if (lane == 0) __hip_atomic_store(&status[tile], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return base;
+}
+
+// The tile from its loaded entries to the merged positions: at[i] = position of entry tid + i * kShortThreads among the tile's
+// entries in the order (key, run); the bits of the survivors are set in s.alive.  All threads of the workgroup.
+template <int kItems>
+__device__ __forceinline__ void short_rank(ShortShared& s, const uint4 (&ent)[kShortItems][4], const uint32_t (&piece)[kShortItems], uint32_t (&at)[kShortItems],
+                                           const uint32_t n, const uint32_t k, const uint32_t flags) {
+    const uint32_t tid = threadIdx.x;
+    uint4* const tails = s.mem + 2 * kTileCap;  // by entry: key bytes 16..31
+    uint4* const infos = s.mem + 3 * kTileCap;  // by entry: seqno, type | key bytes 14..15 << 8
+    Sur sur[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t e = tid + i * kShortThreads;
+        at[i] = e;
+        const Key key = key_from_raw(ent[i][0], ent[i][1]);
+        sur[i].hi = key.w[0];
+        sur[i].lo = (key.w[1] & ~0xFFFFull) | e;
+        if (e < n) {
+            sur_store(&s.mem[e], sur[i]);
+            tails[e] = ent[i][1];
+            infos[e] = make_uint4(ent[i][2].x, ent[i][2].y, (ent[i][2].z & 0xFF) | (ent[i][0].w & 0xFFFF0000u) >> 8, 0);
+        }
+    }
+    __syncthreads();
+    // ---- merge rounds: an entry's place in the merged list is its place in its own list and the number of smaller ones in the
+    //      other list of the pair
+    uint4* in = s.mem;
+    uint4* dst = s.mem + kTileCap;
+    for (uint32_t width = 1; width < k; width <<= 1) {
+        uint32_t lo[kItems], hi[kItems], from[kItems];
+#pragma unroll
+        for (int i = 0; i < kItems; i++) {
+            const uint32_t j = piece[i], first = j & ~(width - 1), other = first ^ width;  // lists of `width` runs
+            const uint32_t begin = s.seg[min(other, k)], end = s.seg[min(other + width, k)];
+            const bool valid = tid + i * kShortThreads < n;
+            lo[i] = from[i] = begin;
+            hi[i] = valid ? end : begin;
+        }
+        bool go = true;
+        while (go) {
+            go = false;
+#pragma unroll
+            for (int i = 0; i < kItems; i++) {
+                if (lo[i] < hi[i]) {
+                    const uint32_t mid = (lo[i] + hi[i]) >> 1;
+                    const bool less = sur_less(sur_load(&in[mid]), sur[i]);
+                    lo[i] = less ? mid + 1 : lo[i];
+                    hi[i] = less ? hi[i] : mid;
+                    go = go || lo[i] < hi[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kItems; i++) {
+            const uint32_t below = lo[i] - from[i];
+            const bool right = (piece[i] & width) != 0;  // at[] counts the whole of the other list, which lies before this one
+            at[i] += right ? below - (s.seg[piece[i] & ~(width - 1)] - from[i]) : below;
+            if (tid + i * kShortThreads < n) sur_store(&dst[at[i]], sur[i]);
+        }
+        __syncthreads();
+        uint4* const t = in;
+        in = dst, dst = t;
+    }
+    // ---- neighbours with the same 14 bytes: the rest of the key orders them, the newest version of a key survives
+    bool win[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t e = tid + i * kShortThreads, p = at[i];
+        win[i] = e < n;
+        if (!win[i]) continue;
+        const Sur me = sur[i];
+        const uint4 my_info = make_uint4(ent[i][2].x, ent[i][2].y, (ent[i][2].z & 0xFF) | (ent[i][0].w & 0xFFFF0000u) >> 8, 0), my_tail = ent[i][1];
+        const uint64_t seq = ((uint64_t)my_info.y << 32) | my_info.x;
+        uint32_t left = 0, right = 0, before = 0;
+        auto meet = [&](const uint32_t other) {
+            const uint4 info = infos[other], tail = tails[other];
+            const bool same = ((info.z ^ my_info.z) >> 8) == 0 && tail.x == my_tail.x && tail.y == my_tail.y && tail.z == my_tail.z && tail.w == my_tail.w;
+            if (same) {
+                const uint64_t its = ((uint64_t)info.y << 32) | info.x;
+                if (its > seq || (its == seq && other < e)) win[i] = false;
+                before += other < e;
+            } else {
+                before += tail_less(info, tail, my_info, my_tail);
+            }
+        };
+        Sur l = sur_load(&in[p > 0 ? p - 1 : 0]), r = sur_load(&in[min(p + 1, n - 1)]);  // both at once: most entries have no such neighbour
+        while (left < p && sur_same_key(l, me) && left <= (uint32_t)kRepairMax) {
+            meet((uint32_t)l.lo & 0xFFFF);
+            left++;
+            l = sur_load(&in[p > left ? p - left - 1 : 0]);
+        }
+        while (p + right + 1 < n && sur_same_key(r, me) && right <= (uint32_t)kRepairMax) {
+            meet((uint32_t)r.lo & 0xFFFF);
+            right++;
+            r = sur_load(&in[min(p + right + 1, n - 1)]);
+        }
+        if (left + right >= (uint32_t)kRepairMax) s.deep = 1;
+        at[i] = p - left + before;
+        if ((flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) win[i] = false;
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; i++)
+        if (win[i]) atomicOr(&s.alive[at[i] >> 5], 1u << (at[i] & 31));
+    __syncthreads();
+    if (s.deep == 0) return;
+    // ---- exact path, as in merge_kernel: binary search over the tile's other pieces with full 32-byte compares
+    __syncthreads();
+    uint4* const heads = s.mem;  // by entry: key bytes 0..15
+#pragma unroll
+    for (int i = 0; i < kItems; i++)
+        if (tid + i * kShortThreads < n) heads[tid + i * kShortThreads] = ent[i][0];
+    if (tid < kTileCap / 32) s.alive[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t e = tid + i * kShortThreads, j = piece[i];
+        if (e >= n) continue;
+        const Key x = key_from_raw(ent[i][0], ent[i][1]);
+        const uint64_t seq = ((uint64_t)ent[i][2].y << 32) | ent[i][2].x;
+        uint32_t p = e - s.seg[j];
+        bool wins = true;
+        for (uint32_t j2 = 0; j2 < k; j2++) {
+            if (j2 == j) continue;
+            const uint32_t first = s.seg[j2], last = s.seg[j2 + 1];
+            uint32_t lb = first, ub = last;
+            while (lb < ub) {
+                const uint32_t mid = (lb + ub) >> 1;
+                if (entry_key_less(&heads[mid], &tails[mid], x)) lb = mid + 1;
+                else ub = mid;
+            }
+            p += lb - first;
+            if (lb < last && key_equal(key_from_raw(heads[lb], tails[lb]), x)) {
+                const uint64_t other = ((uint64_t)infos[lb].y << 32) | infos[lb].x;
+                if (other > seq || (other == seq && j2 < j)) wins = false;
+                if (j2 < j) p++;
+            }
+        }
+        if (wins && (flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) wins = false;
+        at[i] = p;
+        if (wins) atomicOr(&s.alive[p >> 5], 1u << (p & 31));
+    }
+    __syncthreads();
+}
+
+template <int kExtras, int kMode>
+__global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint32_t flags_arg, lsm_entry_t* out_arg,
+                                                                   uint64_t* n_out_arg, const uint64_t* remap_base, uint32_t remap_files,
+                                                                   uint4* fence_out_arg, uint32_t fence_stride_arg, ModeArgs ma) {
+    static_assert(kMode == kModeSingle || kMode == kModeBatch, "ranges have tiles of their own");
+    __shared__ ShortShared s;
+    __shared__ uint64_t hash_stage[kExtras == 2 ? kTileCap : 1];
+    const uint32_t tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    if (wave == 0) tile_pieces<kMode>(s, rt, ws, n_tiles, ma, nullptr);
+    else if (wave == 1) s.alive[lane] = 0;
+    else if (wave == 2 && lane == 0) s.deep = 0;
+    static_assert(kTileCap / 32 == kWave, "a wave holds the survivors' bits");
+    __syncthreads();
+    const uint32_t n = s.n, tile = s.tile;
+    const uint32_t k = kMode == kModeBatch ? s.k : rt.k;
+    const uint32_t flags = kMode == kModeBatch ? s.flags : flags_arg;
+    const uint32_t top_step = k > 1 ? 1u << (31 - __builtin_clz(k - 1)) : 0;
+    uint4 ent[kShortItems][4];
+    uint32_t piece[kShortItems], at[kShortItems];
+    {
+        const uint4* src[kShortItems];
+#pragma unroll
+        for (int i = 0; i < kShortItems; i++) {
+            const uint32_t e = tid + i * kShortThreads, ee = e < n ? e : 0;
+            piece[i] = piece_of(s.seg, k, top_step, ee);
+            src[i] = reinterpret_cast<const uint4*>(s.run[piece[i]] + s.lo[piece[i]] + (ee - s.seg[piece[i]]));
+        }
+#pragma unroll
+        for (int i = 0; i < kShortItems; i++)
+#pragma unroll
+            for (int part = 0; part < 4; part++) {
+                ent[i][part] = make_uint4(0, 0, 0, 0);
+                if (tid + i * kShortThreads < n) ent[i][part] = load_global_u4(src[i] + part);
+            }
+    }
+    if (n <= (uint32_t)kShortThreads) short_rank<1>(s, ent, piece, at, n, k, flags);
+    else short_rank<kShortItems>(s, ent, piece, at, n, k, flags);
+
+    // ---- survivors before each position, by every wave for itself; s.alive is complete
+    const uint32_t bits = s.alive[lane], incl = wave_scan_u32(__popc(bits));
+    const uint32_t total = __shfl(incl, kWave - 1, kWave), before = incl - __popc(bits);
+    uint32_t slot[kShortItems];
+#pragma unroll
+    for (int i = 0; i < kShortItems; i++) {
+        const bool mine = tid + i * kShortThreads < n;
+        const uint32_t word = mine ? at[i] >> 5 : 0, bit = at[i] & 31;
+        const uint32_t b = __shfl(bits, word, kWave), r = __shfl(before, word, kWave) + __popc(b & ((1u << bit) - 1));
+        slot[i] = mine && ((b >> bit) & 1) ? r : kNoSlot;
+    }
+
+    // ---- output offset of this tile: wave 0 looks back while the other waves stage their survivors
+    if (wave == 0) {
+        __builtin_amdgcn_s_setprio(3);
+        bool failed;
+        const uint64_t base = lookback_few(kMode == kModeBatch ? s.status : ws.status, tile, total, s.failed != 0, &failed);
+        if (lane == 0) {
+            s.base = base;
+            if (failed) s.failed = 1;
+        }
+    }
+    uint4* const stage = s.mem;
+#pragma unroll
+    for (int i = 0; i < kShortItems; i++) {
+        if (slot[i] == kNoSlot) continue;
+        if (kExtras && remap_files != 0 && (ent[i][2].z & 0xFF) == LSM_PUT && ent[i][3].y < remap_files) {
+            const uint64_t v = remap_base[ent[i][3].y] + ent[i][3].x;
+            ent[i][3].x = (uint32_t)v;
+            ent[i][3].y = (uint32_t)(v >> 32);
+        }
+#pragma unroll
+        for (int part = 0; part < 4; part++) stage[slot[i] * 4 + (part ^ (slot[i] & 3))] = ent[i][part];
+        if (kExtras == 2 && ma.key_hashes != nullptr) hash_stage[slot[i]] = bloom_key_hash(key_from_raw(ent[i][0], ent[i][1]));
+    }
+    __syncthreads();
+    const bool failed = s.failed != 0;
+    const uint64_t base = s.base;
+    const uint32_t last_tile = kMode == kModeBatch ? s.job_tiles - 1 : (uint32_t)n_tiles - 1;
+    if (tile == last_tile && tid == 0) *(kMode == kModeBatch ? s.n_out : n_out_arg) = failed ? ~0ull : base + total;
+    if (failed) return;
+    uint4* const dst = reinterpret_cast<uint4*>((kMode == kModeBatch ? s.out : out_arg) + base);
+    for (uint32_t c = tid; c < total * 4; c += kShortThreads) {
+        const uint32_t part = (c ^ (c >> 2)) & 3;
+        store_streaming_u4(&dst[(c & ~3u) | part], stage[c]);
+    }
+    uint4* const fence_out = kMode == kModeBatch ? s.fence_out : fence_out_arg;
+    if (kExtras && fence_out != nullptr) {
+        const uint32_t fence_stride = kMode == kModeBatch ? s.fence_stride : fence_stride_arg;
+        const uint64_t fence = (base + fence_stride - 1) / fence_stride, skip = fence * fence_stride - base;
+        for (uint64_t q = tid; skip + (q >> 1) * fence_stride < total; q += kShortThreads) {
+            const uint32_t at_slot = (uint32_t)(skip + (q >> 1) * fence_stride), part = q & 1;
+            fence_out[fence * 2 + q] = stage[at_slot * 4 + (part ^ (at_slot & 3))];
+        }
+    }
+    if (kExtras == 2 && ma.key_hashes != nullptr)
+        for (uint32_t c = tid; c < total; c += kShortThreads) ma.key_hashes[base + c] = hash_stage[c];
+}
+
+// ---------------------------------------------------------------------------------------
 // Partition of a batch of independent compactions.  A job of boundaries at ranked samples has a wave per sample (ranked_row),
 // any other one a wave per tile, the wave of tile t > 0 searching boundary t over the job's whole runs (the jobs of a batch are
 // small).  A job's first wave also writes the first (all zero) and the last (run lengths) row of its split table; its waves
@@ -1611,21 +1944,28 @@ static Cut cut_runs(const uint64_t* run_lens, uint32_t k, uint32_t spacing, uint
     Cut exact;
     exact.spacing = spacing;
     exact.tiles = tiles_for(total, spacing);
-    const uint64_t even = (all + kRankedTiles - 1) / kRankedTiles, mean = even < kMinSpacing ? kMinSpacing : even;
+    const uint64_t few = (all + kShortTiles - 1) / kShortTiles;
+    const uint64_t even = few <= kShortMean ? few : (all + kRankedTiles - 1) / kRankedTiles;
+    const uint64_t mean = even < kMinSpacing ? kMinSpacing : even;
     if (k < 3 || exact.tiles < 2 || mean >= (uint64_t)kTileCap) return exact;
-    // the densest samples the tile capacity asks for, and four to a tile for even sizes
-    const uint64_t most_tiles = tiles_for(total, (uint32_t)mean), most_samples = kMostSamples * total / all;
-    Cut cut = exact;
-    cut.stride = (uint32_t)(kTileCap - mean) / (k - 1);
-    if (cut.stride > mean / 4) cut.stride = (uint32_t)mean / 4;
-    for (; cut.stride >= kMinStride; cut.stride -= (cut.stride + 15) / 16) {
-        uint64_t samples = 0;
-        for (uint32_t j = 0; j < k; j++) samples += (run_lens[j] + cut.stride - 1) / cut.stride;
-        if (samples > most_samples + k) return exact;
-        cut.samples = (uint32_t)samples;
-        cut.per_tile = (uint32_t)((samples + most_tiles - 1) / most_tiles);
-        cut.tiles = (samples + cut.per_tile - 1) / cut.per_tile;
-        if ((cut.per_tile + k - 1) * cut.stride <= (uint32_t)kTileCap) return cut;
+    const uint64_t most_tiles = tiles_for(total, (uint32_t)mean);
+    // the densest samples that the tile capacity asks for, and four to a tile for even sizes; where the samples are few enough, so
+    // dense that no tile has more than an entry for each thread of the short form
+    for (const uint32_t cap : {(uint32_t)kShortThreads, (uint32_t)kTileCap}) {
+        if (mean + (k - 1) * kMinStride > cap) continue;
+        const uint64_t most_samples = (cap == (uint32_t)kTileCap ? kMostSamples : kShortSamples) * total / all;
+        Cut cut = exact;
+        cut.stride = (uint32_t)(cap - mean) / (k - 1);
+        if (cut.stride > mean / 4) cut.stride = (uint32_t)mean / 4;
+        for (; cut.stride >= kMinStride; cut.stride -= (cut.stride + 15) / 16) {
+            uint64_t samples = 0;
+            for (uint32_t j = 0; j < k; j++) samples += (run_lens[j] + cut.stride - 1) / cut.stride;
+            if (samples > most_samples + k) break;
+            cut.samples = (uint32_t)samples;
+            cut.per_tile = (uint32_t)((samples + most_tiles - 1) / most_tiles);
+            cut.tiles = (samples + cut.per_tile - 1) / cut.per_tile;
+            if ((cut.per_tile + k - 1) * cut.stride <= cap) return cut;
+        }
     }
     return exact;
 }
@@ -1778,15 +2118,18 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
         const uint32_t fence_stride = out->fence_keys ? out->fence_stride : 1u;
         ModeArgs extras = {};
         extras.key_hashes = out->key_hashes;
-        if (out->key_hashes != nullptr)
-            hipLaunchKernelGGL((merge_kernel<2, kModeSingle>), dim3((uint32_t)n_tiles), dim3(kMergeThreads), 0, stream, rt, ws, n_tiles, flags,
-                               out->entries, out->n_out, remap_base, remap_files, fence_out, fence_stride, extras);
-        else if (remap_files != 0 || fence_out != nullptr)
-            hipLaunchKernelGGL((merge_kernel<1, kModeSingle>), dim3((uint32_t)n_tiles), dim3(kMergeThreads), 0, stream, rt, ws, n_tiles, flags,
-                               out->entries, out->n_out, remap_base, remap_files, fence_out, fence_stride, ModeArgs{});
-        else
-            hipLaunchKernelGGL((merge_kernel<0, kModeSingle>), dim3((uint32_t)n_tiles), dim3(kMergeThreads), 0, stream, rt, ws, n_tiles, flags,
-                               out->entries, out->n_out, remap_base, remap_files, fence_out, fence_stride, ModeArgs{});
+        auto launch = [&](auto extras_value) {
+            constexpr int kExtras = decltype(extras_value)::value;
+            if (n_tiles <= kShortTiles)
+                hipLaunchKernelGGL((merge_short_kernel<kExtras, kModeSingle>), dim3((uint32_t)n_tiles), dim3(kShortThreads), 0, stream, rt, ws, n_tiles, flags,
+                                   out->entries, out->n_out, remap_base, remap_files, fence_out, fence_stride, extras);
+            else
+                hipLaunchKernelGGL((merge_kernel<kExtras, kModeSingle>), dim3((uint32_t)n_tiles), dim3(kMergeThreads), 0, stream, rt, ws, n_tiles, flags,
+                                   out->entries, out->n_out, remap_base, remap_files, fence_out, fence_stride, extras);
+        };
+        if (out->key_hashes != nullptr) launch(std::integral_constant<int, 2>{});
+        else if (remap_files != 0 || fence_out != nullptr) launch(std::integral_constant<int, 1>{});
+        else launch(std::integral_constant<int, 0>{});
     }
     if (ev && ev->after_merge && hipEventRecord(static_cast<hipEvent_t>(ev->after_merge), stream) != hipSuccess)
         return LSM_ERR_HIP;
@@ -2102,12 +2445,17 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
     else launch(std::false_type{});
     RunTable rt = {};
     rt.k = 1;
-    if (any_fences)  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
-        hipLaunchKernelGGL((merge_kernel<1, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
-                           (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
-    else
-        hipLaunchKernelGGL((merge_kernel<0, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
-                           (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
+    auto launch_merge = [&](auto extras_value) {
+        constexpr int kExtras = decltype(extras_value)::value;
+        if (tile <= kShortTiles)
+            hipLaunchKernelGGL((merge_short_kernel<kExtras, kModeBatch>), dim3((uint32_t)tile), dim3(kShortThreads), 0, stream, rt, ws, tile, 0u,
+                               (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
+        else
+            hipLaunchKernelGGL((merge_kernel<kExtras, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
+                               (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
+    };
+    if (any_fences) launch_merge(std::integral_constant<int, 1>{});  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
+    else launch_merge(std::integral_constant<int, 0>{});
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
     for (uint32_t j = 0; clear != nullptr && j < n_jobs;) {
         CountedFilter filters[kInlineJobs];

@@ -224,6 +224,32 @@ def test_keys_that_tie_in_their_first_14_bytes(g, oracle, n_runs, n_heads, long_
         _check_compact(g, oracle, runs, flags)
 
 
+@pytest.mark.parametrize("k", [2, 5, 17])
+@pytest.mark.parametrize("group", [2, 33, 34, 600])  # members of a prefix-tie group in all runs together, about: settled by neighbours, or not
+def test_prefix_ties_on_both_sides_of_the_short_form(g, oracle, k, group):
+    """One tile, tiles of up to and of more than 1,024 entries, 256 tiles and more: keys that share 14 bytes with others and differ behind."""
+    rs = np.random.RandomState(100 * k + group)
+    for total in (1000, 1100, 1900, 60_000, 300_000, 256 * (2048 - k) - 1, 256 * (2048 - k) + 3000):
+        print("prefix ties, short form", k, group, total, flush=True)
+        runs = []
+        for j in range(k):
+            code = np.unique(rs.randint(0, max(4, int(total * 0.8)), size=total // k))  # a key is in one to three of the runs
+            head, tail = code // group, code % group
+            a = np.zeros((code.size, 64), dtype=np.uint8)
+            a[:, :8] = (head.astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15) >> np.uint64(1)).astype(">u8").view(np.uint8).reshape(-1, 8)
+            spot = np.array([14, 20, 30])[head % 3]
+            a[np.arange(code.size), spot] = tail >> 8
+            a[np.arange(code.size), spot + 1] = tail & 255
+            words = a[:, :32].copy().view(">u8")
+            a = a[np.lexsort((words[:, 3], words[:, 2], words[:, 1], words[:, 0]))]
+            rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+            rec["seqno"] = rs.randint(0, 1 << 40, size=code.size) if total & 1 else rs.randint(0, 3, size=code.size)
+            rec["type"] = (rs.rand(code.size) < 0.1).astype(np.uint8)
+            rec["vptr"] = np.arange(code.size) + (j << 40)
+            runs.append(to_dev(a))
+        _check_compact(g, oracle, runs, int(group & 1))
+
+
 @pytest.mark.parametrize("separate", [False, True])
 def test_first_key_words_that_differ_in_one_bit(g, oracle, separate):
     """Two first key words that differ in their last bit next to one far away (any scaled or
