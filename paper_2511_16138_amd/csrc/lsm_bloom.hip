@@ -66,14 +66,13 @@ __global__ void bloom_clear_batch_kernel(BloomJobs<kRuns> jobs) {
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_blocks; i += stride) blocks[i] = make_uint4(0, 0, 0, 0);
 }
 
-template <uint32_t kRuns, typename Lengths>
-__global__ void bloom_insert_batch_kernel(BloomJobs<kRuns> jobs, Lengths lengths) {
+template <uint32_t kRuns>
+__global__ void bloom_insert_batch_kernel(BloomJobs<kRuns> jobs) {
     const lsm_entry_t* entries = jobs.entries[blockIdx.y];
     uint32_t* words = jobs.words[blockIdx.y];
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
-    uint64_t n = jobs.n[blockIdx.y];
-    uint32_t n_blocks = jobs.n_blocks[blockIdx.y];
-    lengths.look_up(blockIdx.y, n, n_blocks);
+    const uint64_t n = jobs.n[blockIdx.y];
+    const uint32_t n_blocks = jobs.n_blocks[blockIdx.y];
     for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
         uint4 mask;
         const uint32_t block = bloom_block(bloom_hash(load_key(entries + i), mask), n_blocks);
@@ -95,13 +94,11 @@ __device__ __forceinline__ void bloom_set_lds(uint32_t* block, uint64_t h) {
     }
 }
 
-// A filter of at most kBloomSmallBlocks blocks (128 KiB) is built in LDS, for the short runs of a tree's upper levels.
+// A filter of at most kSmallFilterBlocks blocks (128 KiB) is built in LDS, for the short runs of a tree's upper levels.
 // blockIdx.y = run, blockIdx.x = a share of its keys, `ahead` keys per thread.  A run of one share is written out by its
 // only workgroup; the shares of a longer one are combined by atomics in the order of the words (whole lines at a time and
 // one per word, where an atomic per key goes to a line of its own: 16 x 30,000 keys took 39 us that way), on a
 // filter that an earlier launch has cleared.  One workgroup for 36,000 keys took 22 us: it reads 2.3 MB.
-constexpr uint32_t kBloomSmallBlocks = 8192;
-constexpr uint64_t kBloomSmallKeys = 1u << 18;  // a longer run with so small a filter is left to the atomics
 constexpr int kBloomSmallThreads = 1024;
 template <uint32_t kBlocks, int kAhead, uint32_t kRuns, typename Lengths>
 __global__ void __launch_bounds__(kBloomSmallThreads) bloom_small_kernel(BloomJobs<kRuns> jobs, Lengths lengths) {
@@ -177,8 +174,8 @@ static void launch_bloom_small(const BloomJobs<kRuns>& jobs, const Lengths& leng
         else if (ahead == 4) with(std::integral_constant<int, kMostAhead < 4 ? kMostAhead : 4>{});
         else with(std::integral_constant<int, kMostAhead>{});
     };
-    if (most_blocks > kBloomSmallBlocks / 2) launch(std::integral_constant<uint32_t, kBloomSmallBlocks>{});
-    else launch(std::integral_constant<uint32_t, kBloomSmallBlocks / 2>{});
+    if (most_blocks > kSmallFilterBlocks / 2) launch(std::integral_constant<uint32_t, kSmallFilterBlocks>{});
+    else launch(std::integral_constant<uint32_t, kSmallFilterBlocks / 2>{});
 }
 
 // ---------------------------------------------------------------------------------------
@@ -273,7 +270,7 @@ extern "C" int lsm_build_bloom(const lsm_run_t* run, void* filter_out, uint64_t 
     if ((reinterpret_cast<uintptr_t>(filter_out) & 15) != 0 || (reinterpret_cast<uintptr_t>(run->entries) & 63) != 0)
         return LSM_ERR_BAD_ARG;
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
-    if (n_blocks <= kBloomSmallBlocks && run->n <= kBloomSmallKeys) {
+    if (n_blocks <= kSmallFilterBlocks && run->n <= kSmallFilterKeys) {
         BloomJobs<1> jobs = {};  // 28 bytes of arguments: the 1.8 KB of a batch cost the host 1 us per launch
         jobs.entries[0] = run->entries;
         jobs.n[0] = run->n;
@@ -311,14 +308,13 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
                     if (ix > 4096) ix = 4096;
                     if (!cleared) hipLaunchKernelGGL(bloom_clear_batch_kernel<kBloomBatch>, dim3((uint32_t)cx, count), dim3(256), 0, stream, jobs);
                     if (most_entries > 0)
-                        hipLaunchKernelGGL((bloom_insert_batch_kernel<kBloomBatch, KnownLengths>), dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs,
-                                           KnownLengths());
+                        hipLaunchKernelGGL(bloom_insert_batch_kernel<kBloomBatch>, dim3((uint32_t)ix, count), dim3(256), 0, stream, jobs);
                 }
                 jobs = {};
                 count = 0, most_blocks = 1, most_entries = 0;
             }
             if (j == n_runs) break;
-            if ((n_blocks[j] > kBloomSmallBlocks || runs[j].n > kBloomSmallKeys) != (large == 1)) continue;
+            if ((n_blocks[j] > kSmallFilterBlocks || runs[j].n > kSmallFilterKeys) != (large == 1)) continue;
             jobs.entries[count] = runs[j].entries;
             jobs.n[count] = runs[j].n;
             jobs.words[count] = static_cast<uint32_t*>(filters_out[j]);
@@ -332,23 +328,129 @@ int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_
 }
 }  // namespace lsm
 
+// ---------------------------------------------------------------------------------------
+// Filters of merged runs that are too long for one workgroup's LDS, built right behind the merge, whose output pass has written the
+// keys' hashes: the hashes are sorted by range of blocks and every range is built in LDS, as in lsm_build_bloom_hashed, but the
+// lengths are on the device, one launch takes several runs, and a range's part of the scratch memory has room for somewhat more hashes than
+// fall into it, so that none of them has to be counted first.  The atomics of bloom_insert_batch_kernel, two per key on a line of its
+// own, go to memory past the L2s: filters of 8 runs, 1M keys in all, 115 us, this 19 and 3 more in the merge; a run of 70,000 keys 11 either way, of
+// 400,000 60 and 13.  (One launch in which every range's workgroup reads all hashes of its run and keeps its own:
+// 39 us for the 8 runs, 21 for 70,000 keys.)
+// ---------------------------------------------------------------------------------------
 namespace lsm {
 template <uint32_t kRuns>
+struct HashedJobs {
+    uint64_t most[kRuns];  // upper bounds of the lengths
+    uint32_t* cursors[kRuns];
+    const uint64_t* hashes[kRuns];
+    uint64_t* ranged[kRuns];
+    uint4* filter[kRuns];
+    uint32_t unit_log[kRuns], cap[kRuns];
+};
+
+// A workgroup puts its hashes in order of their ranges in LDS, reserves its place in every range with one atomic, and stores them,
+// neighbours next to each other.  Bound by the chain of its steps (7 us for 10 workgroups, 11 for 130).
+constexpr uint32_t kScatterItems = 8, kScatterChunk = kScatterItems * kPartThreads;
+template <uint32_t kRuns>
+__global__ void __launch_bounds__(kPartThreads) bloom_scatter_kernel(HashedJobs<kRuns> jobs, CountedLengths<kRuns> lengths) {
+    __shared__ uint64_t stage[kScatterChunk];
+    __shared__ uint32_t start[kMostFilterRanges], place[kMostFilterRanges];
+    __shared__ uint32_t wave_sum[kPartThreads / kWave];
+    static_assert(kMostFilterRanges <= kPartThreads && kScatterChunk <= 65536, "a range per thread, places in 16 bits");
+    const uint32_t tid = threadIdx.x, run = blockIdx.y, unit_log = jobs.unit_log[run], cap = jobs.cap[run];
+    uint64_t n = jobs.most[run];
+    uint32_t n_blocks = 1;
+    lengths.look_up(run, n, n_blocks);
+    const uint64_t first = (uint64_t)blockIdx.x * kScatterChunk;
+    if (first >= n) return;
+    const uint32_t count = n - first < kScatterChunk ? (uint32_t)(n - first) : kScatterChunk, n_ranges = ((n_blocks - 1) >> unit_log) + 1;
+    const uint64_t* const hashes = jobs.hashes[run] + first;
+    uint64_t h[kScatterItems];
+#pragma unroll
+    for (uint32_t a = 0; a < kScatterItems; a++) h[a] = tid + a * kPartThreads < count ? hashes[tid + a * kPartThreads] : 0;
+    if (tid < kMostFilterRanges) start[tid] = 0;
+    __syncthreads();
+    uint32_t at[kScatterItems];  // range << 16 | place among the workgroup's hashes of the range
+#pragma unroll
+    for (uint32_t a = 0; a < kScatterItems; a++) {
+        const uint32_t r = bloom_block(h[a], n_blocks) >> unit_log;
+        at[a] = r << 16;
+        if (tid + a * kPartThreads < count) at[a] |= atomicAdd(&start[r], 1u);
+    }
+    __syncthreads();
+    const uint32_t mine = tid < n_ranges ? start[tid] : 0;
+    uint32_t reserved = 0;
+    if (mine != 0) reserved = atomicAdd(&jobs.cursors[run][tid], mine);
+    const uint32_t incl = wave_scan_u32(mine);
+    if ((tid & (kWave - 1)) == kWave - 1) wave_sum[tid / kWave] = incl;
+    __syncthreads();
+    uint32_t before = incl - mine;
+    for (uint32_t w = 0; w < tid / kWave; w++) before += wave_sum[w];
+    if (tid < n_ranges) start[tid] = before, place[tid] = reserved;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t a = 0; a < kScatterItems; a++)
+        if (tid + a * kPartThreads < count) stage[start[at[a] >> 16] + (at[a] & 0xFFFF)] = h[a];
+    __syncthreads();
+    for (uint32_t i = tid; i < count; i += kPartThreads) {
+        const uint64_t v = stage[i];
+        const uint32_t r = bloom_block(v, n_blocks) >> unit_log, to = place[r] + (i - start[r]);
+        if (to < cap) jobs.ranged[run][(uint64_t)r * cap + to] = v;
+    }
+}
+
+// One workgroup per range.  A range with more hashes than it has room for is built from all of them.
+template <uint32_t kRuns>
+__global__ void __launch_bounds__(kPartThreads) bloom_ranges_kernel(HashedJobs<kRuns> jobs, CountedLengths<kRuns> lengths) {
+    __shared__ uint4 part[kMaxRangeUnits];
+    const uint32_t run = blockIdx.y, range = blockIdx.x, unit_log = jobs.unit_log[run], first_block = range << unit_log;
+    uint64_t n = jobs.most[run];
+    uint32_t n_blocks = 1;
+    lengths.look_up(run, n, n_blocks);
+    if (first_block >= n_blocks) return;
+    const uint32_t blocks = min(1u << unit_log, n_blocks - first_block), held = n != 0 ? jobs.cursors[run][range] : 0;
+    for (uint32_t b = threadIdx.x; b < blocks; b += kPartThreads) part[b] = make_uint4(0, 0, 0, 0);
+    __syncthreads();
+    const bool all = held > jobs.cap[run];
+    const uint64_t* const hashes = all ? jobs.hashes[run] : jobs.ranged[run] + (uint64_t)range * jobs.cap[run];
+    part_for_each(0, all ? n : held, [&](uint64_t i) { return hashes[i]; }, [&](uint64_t, uint64_t h) {
+        const uint32_t block = bloom_block(h, n_blocks) - first_block;  // wraps for the blocks before the range
+        if (block < blocks) bloom_set_lds(reinterpret_cast<uint32_t*>(part + block), h);
+    });
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < blocks; b += kPartThreads) jobs.filter[run][first_block + b] = part[b];
+}
+
+template <uint32_t kRuns>
 static void launch_counted(const CountedFilter* filters, uint32_t count, hipStream_t stream) {
-    // a launch takes filters of one kind, as above
+    // a launch takes filters of one kind: small ones, or those from hashes
     for (int large = 0; large < 2; large++) {
         BloomJobs<kRuns> jobs = {};
+        HashedJobs<kRuns> hashed = {};
         CountedLengths<kRuns> lengths = {};
-        uint32_t taken = 0;
+        uint32_t taken = 0, most_ranges = 0;
         uint64_t most = 0;
         for (uint32_t j = 0; j < count; j++) {
             const CountedFilter& f = filters[j];
+            if ((f.scratch != nullptr) != (large == 1)) continue;
             const uint64_t blocks = lsm_bloom_blocks(f.most, f.bits);
-            if ((blocks > kBloomSmallBlocks || f.most > kBloomSmallKeys) != (large == 1)) continue;
-            jobs.entries[taken] = f.entries;
-            jobs.n[taken] = f.most;
-            jobs.words[taken] = static_cast<uint32_t*>(f.filter);
-            jobs.n_blocks[taken] = (uint32_t)blocks;
+            if (large == 1) {
+                const FilterScratch at = filter_scratch(f.most, blocks);
+                char* const base = static_cast<char*>(f.scratch);
+                hashed.most[taken] = f.most;
+                hashed.cursors[taken] = reinterpret_cast<uint32_t*>(base);
+                hashed.hashes[taken] = reinterpret_cast<const uint64_t*>(base + at.zeroed);
+                hashed.ranged[taken] = reinterpret_cast<uint64_t*>(base + at.ranged);
+                hashed.filter[taken] = static_cast<uint4*>(f.filter);
+                hashed.unit_log[taken] = at.unit_log;
+                hashed.cap[taken] = at.cap;
+                most_ranges = at.n_ranges > most_ranges ? at.n_ranges : most_ranges;
+            } else {
+                jobs.entries[taken] = f.entries;
+                jobs.n[taken] = f.most;
+                jobs.words[taken] = static_cast<uint32_t*>(f.filter);
+                jobs.n_blocks[taken] = (uint32_t)blocks;
+            }
             lengths.status[taken] = f.status;
             lengths.bits[taken] = f.bits;
             most = f.most > most ? f.most : most;
@@ -358,9 +460,8 @@ static void launch_counted(const CountedFilter* filters, uint32_t count, hipStre
         if (large == 0) {
             launch_bloom_small(jobs, lengths, taken, true, stream);
         } else {
-            const uint64_t blocks = (most + 255) / 256;
-            hipLaunchKernelGGL((bloom_insert_batch_kernel<kRuns, CountedLengths<kRuns>>), dim3((uint32_t)(blocks > 4096 ? 4096 : blocks), taken), dim3(256), 0,
-                               stream, jobs, lengths);
+            hipLaunchKernelGGL(bloom_scatter_kernel<kRuns>, dim3((uint32_t)((most + kScatterChunk - 1) / kScatterChunk), taken), dim3(kPartThreads), 0, stream, hashed, lengths);
+            hipLaunchKernelGGL(bloom_ranges_kernel<kRuns>, dim3(most_ranges, taken), dim3(kPartThreads), 0, stream, hashed, lengths);
         }
     }
 }

@@ -139,6 +139,23 @@ __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
     return v;
 }
 
+// Inclusive prefix sum over the lanes of a wave: shifts inside rows of 16 lanes (0 comes in at a row's start), then the sums
+// of the rows below.
+template <int kOff>
+__device__ __forceinline__ uint32_t row_shift_up(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x110 | kOff, 0xF, 0xF, true);
+}
+__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
+    v += row_shift_up<1>(v);
+    v += row_shift_up<2>(v);
+    v += row_shift_up<4>(v);
+    v += row_shift_up<8>(v);
+    const uint32_t lane = threadIdx.x & (kWave - 1);
+    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 15), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
+    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
+    return v + (lane >= 16 ? a : 0) + (lane >= 32 ? b : 0) + (lane >= 48 ? c : 0);
+}
+
 // 16-byte load through a pointer that is known to be global memory (it went through LDS or a
 // table, so the compiler cannot tell): a global instead of a flat load.
 __device__ __forceinline__ uint4 load_global_u4(const uint4* p) { typedef uint32_t v4 __attribute__((ext_vector_type(4))); const v4 v = *(const __attribute__((address_space(1))) v4*)p; return make_uint4(v.x, v.y, v.z, v.w); }
@@ -214,7 +231,34 @@ struct ClearSpan {  // device memory to be zeroed by a launch that is made anywa
     // per key; filter_built says whether the launch for it has been made
     uint32_t filter_bits = 0;
     mutable bool filter_built = false;
+    void* filter = nullptr;  // not null: p is a FilterScratch, and the filter is built there from the keys' hashes, which the merge writes
+    uint64_t* hashes() const { return filter != nullptr ? reinterpret_cast<uint64_t*>(static_cast<char*>(p) + bytes) : nullptr; }
 };
+// Filters of up to kSmallFilterBlocks blocks are built in a workgroup's LDS, longer ones behind a merge from the keys' hashes, which
+// the merge writes: sorted by ranges of blocks, then every range in LDS.
+constexpr uint32_t kSmallFilterBlocks = 8192;
+constexpr uint64_t kSmallFilterKeys = 1u << 18;  // a longer run with so small a filter is not
+inline bool small_filter(uint64_t n, uint64_t blocks) { return blocks <= kSmallFilterBlocks && n <= kSmallFilterKeys; }
+// Memory for the latter: a cursor for each range, to be zeroed, right behind them the hashes, then [range][cap] hashes by range.
+struct FilterScratch {
+    uint32_t unit_log, n_ranges, cap;  // blocks of a range; hashes it has room for
+    size_t zeroed, ranged, total;      // bytes
+};
+constexpr uint32_t kMostFilterRanges = 1024;
+inline FilterScratch filter_scratch(uint64_t n, uint64_t blocks) {
+    FilterScratch s;
+    s.unit_log = 8;  // a range for three quarters of the compute units, or more, of up to 4,096 blocks (64 KiB)
+    while (s.unit_log < 12 && (blocks >> (s.unit_log + 1)) >= 192) s.unit_log++;
+    const uint64_t ranges = (blocks + (1u << s.unit_log) - 1) >> s.unit_log;
+    s.n_ranges = ranges > kMostFilterRanges ? 0 : (uint32_t)ranges;  // 0: not built this way
+    // eight standard deviations more than the mean; a range with more is built from all hashes
+    const uint64_t mean = (uint64_t)((unsigned __int128)n * (1u << s.unit_log) / blocks) + 1, cap = mean + (uint64_t)(8 * __builtin_sqrt((double)mean)) + 32;
+    s.cap = (uint32_t)(cap > n ? n : cap);
+    s.zeroed = (s.n_ranges * 4 + 255) & ~size_t(255);
+    s.ranged = (s.zeroed + n * 8 + 255) & ~size_t(255);
+    s.total = s.ranged + (size_t)s.n_ranges * s.cap * 8;
+    return s;
+}
 // lsm_compact and lsm_compact_batch that also zero a span (per job), and build a filter in it.  *cleared: whether lsm_compact had
 // a launch to zero it in.
 int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes,
@@ -234,14 +278,15 @@ int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t fence_stride, hi
 int probe_stats(const uint32_t* hit_len, uint32_t n_req, uint64_t* stats, uint64_t ticket, hipStream_t stream);
 // lsm_build_bloom_batch; `cleared`: the filters are known to be all zero.
 int build_filters(const lsm_run_t* runs, void* const* filters_out, const uint64_t* n_blocks, uint32_t n_runs, bool cleared, hipStream_t stream);
-// Filters, on memory that is zero, of runs whose lengths are on the device: a tile status word (the last of a compaction), and no
-// more than `most`.  A run whose compaction failed gets none.
+// Filters of runs whose lengths are on the device: a tile status word (the last of a compaction), and no more than `most`.  A run whose
+// compaction failed gets none.
 struct CountedFilter {
     const lsm_entry_t* entries;
     uint64_t most;
     const uint64_t* status;
     void* filter;
     uint32_t bits;
+    void* scratch;  // not null: a FilterScratch with the keys' hashes; null: a small filter, on memory that is zero
 };
 int build_filters_counted(const CountedFilter* filters, uint32_t count, hipStream_t stream);
 // Compaction of runs whose exact lengths are only known on the device (n_upper[j] >= n_dev[j]; launch sizes come from

@@ -477,23 +477,6 @@ __device__ __forceinline__ void split_two_wave(const lsm_entry_t* a, const uint6
     if (ia > 0 && ib < nb && key_equal(load_key(a + ia - 1), load_key(b + ib))) ia--;
 }
 
-// Inclusive prefix sum over the lanes of a wave: shifts inside rows of 16 lanes (0 comes in at a row's start), then the sums
-// of the rows below.
-template <int kOff>
-__device__ __forceinline__ uint32_t row_shift_up(uint32_t v) {
-    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, 0x110 | kOff, 0xF, 0xF, true);
-}
-__device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
-    v += row_shift_up<1>(v);
-    v += row_shift_up<2>(v);
-    v += row_shift_up<4>(v);
-    v += row_shift_up<8>(v);
-    const uint32_t lane = threadIdx.x & (kWave - 1);
-    const uint32_t a = (uint32_t)__builtin_amdgcn_readlane((int)v, 15), b = (uint32_t)__builtin_amdgcn_readlane((int)v, 31);
-    const uint32_t c = (uint32_t)__builtin_amdgcn_readlane((int)v, 47);
-    return v + (lane >= 16 ? a : 0) + (lane >= 32 ? b : 0) + (lane >= 48 ? c : 0);
-}
-
 // ---------------------------------------------------------------------------------------
 // Boundaries at sample keys, for small inputs of three runs or more: one launch in which every boundary is found without the
 // others.  Every `stride`-th entry of every run is a sample.  A wave takes one sample c and counts the samples before it in
@@ -796,6 +779,7 @@ struct TileHead {  // what the whole workgroup knows of its tile
     uint64_t* n_out;
     uint64_t* status;
     uint4* fence_out;
+    uint64_t* key_hashes;
 };
 
 struct MergeShared : TileHead {
@@ -814,6 +798,7 @@ struct MergeShared : TileHead {
 // arguments comes from the job's descriptor.
 enum : int { kModeSingle = 0, kModeRange = 1, kModeBatch = 2 };
 
+constexpr uint32_t kHashesBehind = 0x80000000u;
 struct JobDesc {       // one compaction of a batch (device memory, written by the host)
     uint32_t first_tile;   // number of its first tile in the launch
     uint32_t first_wave;   // number of its first wave in the partition launch
@@ -825,7 +810,7 @@ struct JobDesc {       // one compaction of a batch (device memory, written by t
     uint4* fence_out;      // optional fence index of the job's output
     uint32_t n_tiles, k, flags, fence_stride;
     uint4* clear;          // optional memory the partition launch zeroes for a later kernel
-    uint32_t clear_n;
+    uint32_t clear_n;      // 16-byte words of it; with kHashesBehind the merge puts the keys' filter hashes behind them
     uint32_t waves;        // of the partition launch
 };
 static_assert(sizeof(JobDesc) == 80, "descriptor layout");
@@ -1034,6 +1019,7 @@ __device__ __forceinline__ void tile_pieces(TileHead& s, const RunTable& rt, con
             s.status = ws.status + d.first_tile;
             s.fence_out = d.fence_out;
             s.fence_stride = d.fence_stride;
+            s.key_hashes = d.clear_n & kHashesBehind ? reinterpret_cast<uint64_t*>(d.clear + (d.clear_n & ~kHashesBehind)) : nullptr;
         }
     }
     const bool mine = lane < (int)kk;
@@ -1097,6 +1083,7 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
     const uint64_t last_tile = kMode == kModeBatch ? (uint64_t)s.job_tiles - 1 : n_tiles - 1;
     uint4* const fence_out = kMode == kModeBatch ? s.fence_out : fence_out_arg;
     const uint32_t fence_stride = kMode == kModeBatch ? s.fence_stride : fence_stride_arg;
+    const auto key_hashes = [&] { return kMode == kModeBatch ? s.key_hashes : ma.key_hashes; };  // read where it is used: no register to spare
     const uint32_t top_step = k > 1 ? 1u << (31 - __builtin_clz(k - 1)) : 0;
 
     // ---- load: entry e = tid + i * kMergeThreads stays in this thread's registers until it is stored
@@ -1483,7 +1470,7 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                     for (int part = 0; part < 4; part++) stage[slot * 4 + (part ^ (slot & 3))] = ent[i][part];
                     // the filter hash of the survivor's key travels with it (paper section 2.2: a new run gets its Bloom
                     // filter; the filter is then built from these 8-byte values, not from the run)
-                    if (kExtras == 2 && kMode == kModeSingle && ma.key_hashes != nullptr) {
+                    if (kExtras == 2 && key_hashes() != nullptr) {
                         const uint64_t h = bloom_key_hash(key_from_raw(ent[i][0], ent[i][1]));
                         if (slot < (uint32_t)kStageEntries / 2) reinterpret_cast<uint64_t*>(s.rank)[slot] = h;
                         else hash_stage_upper[slot - kStageEntries / 2] = h;
@@ -1520,9 +1507,9 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
                 fence_out[fence * 2 + q] = stage[slot * 4 + (part ^ (slot & 3))];
             }
         }
-        if (kExtras == 2 && kMode == kModeSingle && ma.key_hashes != nullptr) {
+        if (kExtras == 2 && key_hashes() != nullptr) {
             for (uint32_t c = tid; c < count; c += kMergeThreads)
-                ma.key_hashes[base + first + c] = c < (uint32_t)kStageEntries / 2 ? reinterpret_cast<const uint64_t*>(s.rank)[c]
+                key_hashes()[base + first + c] = c < (uint32_t)kStageEntries / 2 ? reinterpret_cast<const uint64_t*>(s.rank)[c]
                                                                                   : hash_stage_upper[c - kStageEntries / 2];
         }
         first += kStageEntries;
@@ -1802,6 +1789,7 @@ __global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt,
         }
     }
     uint4* const stage = s.mem;
+    uint64_t* const key_hashes = kExtras != 2 ? nullptr : (kMode == kModeBatch ? s.key_hashes : ma.key_hashes);
 #pragma unroll
     for (int i = 0; i < kShortItems; i++) {
         if (slot[i] == kNoSlot) continue;
@@ -1812,7 +1800,7 @@ __global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt,
         }
 #pragma unroll
         for (int part = 0; part < 4; part++) stage[slot[i] * 4 + (part ^ (slot[i] & 3))] = ent[i][part];
-        if (kExtras == 2 && ma.key_hashes != nullptr) hash_stage[slot[i]] = bloom_key_hash(key_from_raw(ent[i][0], ent[i][1]));
+        if (kExtras == 2 && key_hashes != nullptr) hash_stage[slot[i]] = bloom_key_hash(key_from_raw(ent[i][0], ent[i][1]));
     }
     __syncthreads();
     const bool failed = s.failed != 0;
@@ -1834,8 +1822,8 @@ __global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt,
             fence_out[fence * 2 + q] = stage[at_slot * 4 + (part ^ (at_slot & 3))];
         }
     }
-    if (kExtras == 2 && ma.key_hashes != nullptr)
-        for (uint32_t c = tid; c < total; c += kShortThreads) ma.key_hashes[base + c] = hash_stage[c];
+    if (kExtras == 2 && key_hashes != nullptr)
+        for (uint32_t c = tid; c < total; c += kShortThreads) key_hashes[base + c] = hash_stage[c];
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1878,7 +1866,7 @@ __global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, Mo
         if (lane < d.k) const_cast<const lsm_entry_t**>(ma.run_ptr)[d.run_off + lane] = run_ptr[d.run_off + lane];
         if (lane < d.k) const_cast<uint64_t*>(ma.run_n)[d.run_off + lane] = run_n[d.run_off + lane];
     }
-    for (uint64_t c = w * (uint64_t)kWave + lane; c < d.clear_n; c += (uint64_t)waves * kWave) d.clear[c] = make_uint4(0, 0, 0, 0);
+    for (uint64_t c = w * (uint64_t)kWave + lane; c < (d.clear_n & ~kHashesBehind); c += (uint64_t)waves * kWave) d.clear[c] = make_uint4(0, 0, 0, 0);
     for (uint32_t t = w * kWave + lane; t < d.n_tiles; t += waves * kWave) {
         const_cast<uint32_t*>(ma.tile_job)[d.first_tile + t] = job;
         ws.status[d.first_tile + t] = 0;
@@ -2117,7 +2105,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
         uint4* const fence_out = reinterpret_cast<uint4*>(out->fence_keys);
         const uint32_t fence_stride = out->fence_keys ? out->fence_stride : 1u;
         ModeArgs extras = {};
-        extras.key_hashes = out->key_hashes;
+        extras.key_hashes = out->key_hashes != nullptr ? out->key_hashes : ws.clear_n != 0 ? clear.hashes() : nullptr;
         auto launch = [&](auto extras_value) {
             constexpr int kExtras = decltype(extras_value)::value;
             if (n_tiles <= kShortTiles)
@@ -2127,7 +2115,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                 hipLaunchKernelGGL((merge_kernel<kExtras, kModeSingle>), dim3((uint32_t)n_tiles), dim3(kMergeThreads), 0, stream, rt, ws, n_tiles, flags,
                                    out->entries, out->n_out, remap_base, remap_files, fence_out, fence_stride, extras);
         };
-        if (out->key_hashes != nullptr) launch(std::integral_constant<int, 2>{});
+        if (extras.key_hashes != nullptr) launch(std::integral_constant<int, 2>{});
         else if (remap_files != 0 || fence_out != nullptr) launch(std::integral_constant<int, 1>{});
         else launch(std::integral_constant<int, 0>{});
     }
@@ -2135,7 +2123,8 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
         return LSM_ERR_HIP;
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
     if (ws.clear_n != 0 && clear.filter_bits != 0) {
-        const CountedFilter filter = {out->entries, total, ws.status + n_tiles - 1, clear.p, clear.filter_bits};
+        const bool hashed = clear.filter != nullptr;
+        const CountedFilter filter = {out->entries, total, ws.status + n_tiles - 1, hashed ? clear.filter : clear.p, clear.filter_bits, hashed ? clear.p : nullptr};
         if (build_filters_counted(&filter, 1, stream) != LSM_OK) return LSM_ERR_HIP;
         clear.filter_built = true;
     }
@@ -2387,7 +2376,7 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
         run_n = reinterpret_cast<uint64_t*>(copied + (l.run_n - l.jobs));
     }
     uint64_t tile = 0, wave = 0, split_word = 0, run = 0;
-    bool any_fences = false;
+    bool any_fences = false, any_hashes = false;
     for (uint32_t j = 0; j < n_jobs; j++) {
         const lsm_compact_job_t& job = jobs[j];
         for (uint32_t r = 0; r < job.n_runs; r++) {
@@ -2414,6 +2403,7 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
         d.flags = job.flags;
         d.clear = clear ? static_cast<uint4*>(clear[j].p) : nullptr;
         d.clear_n = clear ? (uint32_t)(clear[j].bytes / 16) : 0;
+        if (clear && clear[j].filter != nullptr) d.clear_n |= kHashesBehind, any_hashes = true;
         tile += nt;
         wave += d.waves;
         split_word += (nt + 1) * job.n_runs;
@@ -2454,7 +2444,8 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
             hipLaunchKernelGGL((merge_kernel<kExtras, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
                                (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
     };
-    if (any_fences) launch_merge(std::integral_constant<int, 1>{});  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
+    if (any_hashes) launch_merge(std::integral_constant<int, 2>{});
+    else if (any_fences) launch_merge(std::integral_constant<int, 1>{});  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
     else launch_merge(std::integral_constant<int, 0>{});
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
     for (uint32_t j = 0; clear != nullptr && j < n_jobs;) {
@@ -2464,9 +2455,10 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
         for (; j < n_jobs && count < kInlineJobs; j++) {
             const JobDesc& d = desc[j];
             if (d.clear_n == 0 || clear[j].filter_bits == 0) continue;
+            const bool hashed = clear[j].filter != nullptr;
             uint64_t total = 0;
             for (uint32_t r = 0; r < d.k; r++) total += run_n[d.run_off + r];
-            filters[count++] = CountedFilter{d.out, total, ws.status + d.first_tile + d.n_tiles - 1, clear[j].p, clear[j].filter_bits};
+            filters[count++] = CountedFilter{d.out, total, ws.status + d.first_tile + d.n_tiles - 1, hashed ? clear[j].filter : clear[j].p, clear[j].filter_bits, hashed ? clear[j].p : nullptr};
         }
         if (count != 0 && build_filters_counted(filters, count, stream) != LSM_OK) return LSM_ERR_HIP;
         for (uint32_t q = first; q < j; q++) clear[q].filter_built = desc[q].clear_n != 0 && clear[q].filter_bits != 0;

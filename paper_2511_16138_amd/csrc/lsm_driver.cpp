@@ -257,15 +257,28 @@ struct lsm_driver {
 
     // Memory for the filter of a merged run of at most `n` entries, to be zeroed by a launch that is made anyway.  A run that is
     // certain to stay at `level` gets its filter in the same call: the launch does not wait for the host to see the count.
-    int take_filter(Run& r, uint64_t n, uint32_t level, lsm::ClearSpan* clear) {
+    // A long filter is built in *scratch_bytes of scratch memory, which the caller gives as clear->p.
+    int take_filter(Run& r, uint64_t n, uint32_t level, lsm::ClearSpan* clear, size_t* scratch_bytes) {
+        *scratch_bytes = 0;
         r.bloom = nullptr, r.bloom_clear = false;
         clear->p = nullptr, clear->bytes = 0;
-        clear->filter_bits = 0, clear->filter_built = false;
+        clear->filter_bits = 0, clear->filter_built = false, clear->filter = nullptr;
         if (n == 0 || !plain_filter(n)) return LSM_OK;
-        if (n <= capacity(level)) clear->filter_bits = cfg.bloom_bits;
-        clear->bytes = lsm_bloom_blocks(n, cfg.bloom_bits) * 16;
-        clear->p = r.bloom = pool.take(clear->bytes);
-        return r.bloom != nullptr ? LSM_OK : LSM_ERR_HIP;
+        const uint64_t blocks = lsm_bloom_blocks(n, cfg.bloom_bits);
+        const bool small = lsm::small_filter(n, blocks);
+        const lsm::FilterScratch scratch = lsm::filter_scratch(n, blocks);
+        if (n <= capacity(level) && (small || scratch.n_ranges != 0)) clear->filter_bits = cfg.bloom_bits;
+        r.bloom = pool.take(blocks * 16);
+        if (r.bloom == nullptr) return LSM_ERR_HIP;
+        if (clear->filter_bits != 0 && !small) {
+            clear->filter = r.bloom;
+            clear->bytes = scratch.zeroed;
+            *scratch_bytes = scratch.total;
+            return LSM_OK;
+        }
+        clear->p = r.bloom;
+        clear->bytes = blocks * 16;
+        return LSM_OK;
     }
 
     // A merged run whose filter has been built by the call that merged it has every structure it is to get (what holds for the
@@ -411,37 +424,41 @@ struct lsm_driver {
             total += in[j].n;
         }
         const uint32_t k = (uint32_t)in.size();
-        const size_t need = lsm_compact_workspace_bytes(lens, k);
+        const uint64_t room = total > 0 ? total : 1;
+        lsm_entry_t* entries = static_cast<lsm_entry_t*>(pool.take(room * sizeof(lsm_entry_t)));
+        uint8_t* fences = static_cast<uint8_t*>(pool.take(ceil_div(room, cfg.fence_stride) * LSM_KEY_BYTES));
+        *merged = Run();
+        lsm::ClearSpan clear;
+        size_t scratch_bytes = 0;
+        auto fails = [&](int rc) {
+            pool.give(entries);
+            pool.give(fences);
+            pool.give(merged->bloom);
+            *merged = Run();
+            return rc;
+        };
+        if (entries == nullptr || fences == nullptr || take_filter(*merged, total, level, &clear, &scratch_bytes) != LSM_OK) return fails(LSM_ERR_HIP);
+        const size_t own = lsm_compact_workspace_bytes(lens, k), need = own + scratch_bytes;  // (a multiple of 256 bytes)
         if (need > workspace_bytes) {
             pool.give(workspace);
             workspace_bytes = 2 * need;
             workspace = pool.take(workspace_bytes);
             if (workspace == nullptr) {
                 workspace_bytes = 0;
-                return LSM_ERR_HIP;
+                return fails(LSM_ERR_HIP);
             }
         }
-        const uint64_t room = total > 0 ? total : 1;
-        lsm_entry_t* entries = static_cast<lsm_entry_t*>(pool.take(room * sizeof(lsm_entry_t)));
-        uint8_t* fences = static_cast<uint8_t*>(pool.take(ceil_div(room, cfg.fence_stride) * LSM_KEY_BYTES));
-        *merged = Run();
-        lsm::ClearSpan clear;
-        if (entries == nullptr || fences == nullptr || take_filter(*merged, total, level, &clear) != LSM_OK) return LSM_ERR_HIP;
+        if (scratch_bytes != 0) clear.p = static_cast<char*>(workspace) + own;
         const lsm_out_t out{entries, room, n_host, fences, cfg.fence_stride, nullptr};
         *static_cast<volatile uint64_t*>(n_host) = kCountUnset;
-        int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, workspace_bytes, clear, &merged->bloom_clear, stream);
+        int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, own, clear, &merged->bloom_clear, stream);
+        if (clear.filter != nullptr) merged->bloom_clear = false;
         // an error may be that of the filter's launch, or of an earlier call, with the merge under way: its count must not meet the next one's
         if (rc != LSM_OK) (void)wait();
         if (rc == LSM_OK) rc = watch_count(n_host);
         if (rc == LSM_OK && *n_host > room) rc = LSM_ERR_INTERNAL;  // the device-side failure mark, or nonsense
         if (rc == LSM_OK && cfg.observer != nullptr) rc = wait();   // the observer sees a complete output
-        if (rc != LSM_OK) {
-            pool.give(entries);
-            pool.give(fences);
-            pool.give(merged->bloom);
-            *merged = Run();
-            return rc;
-        }
+        if (rc != LSM_OK) return fails(rc);
         merged->n = *n_host;
         if (cfg.observer != nullptr) cfg.observer(cfg.observer_ctx, level + 1, entries, merged->n);
         merged->entries = entries, merged->owned = true, merged->fences = fences;
@@ -703,9 +720,10 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
     std::vector<std::vector<lsm_run_t>> inputs;
     std::vector<lsm_compact_job_t> jobs;
     std::vector<lsm::ClearSpan> clear;
+    std::vector<size_t> scratch;  // bytes of the filters' scratch memory
     for (;;) {
         // the compactions that are due now: the long ones on their own, the others as one batch
-        steps.clear(), inputs.clear(), jobs.clear(), clear.clear();
+        steps.clear(), inputs.clear(), jobs.clear(), clear.clear(), scratch.clear();
         for (uint32_t i = 0; i < count; i++) {
             lsm_driver_t* d = drivers[i];
             while (status[i] == LSM_OK && d->due.active && d->due.n_in >= kBatchJobEntries) status[i] = d->compact_due();
@@ -718,16 +736,17 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             const uint64_t room = d->due.n_in > 0 ? d->due.n_in : 1;
             Run merged;
             lsm::ClearSpan zeroed;
+            size_t scratch_bytes = 0;
             lsm_entry_t* entries = static_cast<lsm_entry_t*>(d->pool.take(room * sizeof(lsm_entry_t)));
             merged.entries = entries, merged.owned = true;  // given back through drop() on failure
             merged.fences = static_cast<uint8_t*>(d->pool.take(ceil_div(room, d->cfg.fence_stride) * LSM_KEY_BYTES));
-            status[i] = d->take_filter(merged, d->due.n_in, d->due.level, &zeroed);
+            status[i] = d->take_filter(merged, d->due.n_in, d->due.level, &zeroed, &scratch_bytes);
             if (entries == nullptr || merged.fences == nullptr) status[i] = LSM_ERR_HIP;
             if (status[i] != LSM_OK) {
                 d->drop(merged);
                 continue;
             }
-            merged.bloom_clear = merged.bloom != nullptr;
+            merged.bloom_clear = merged.bloom != nullptr && zeroed.filter == nullptr;
             inputs.emplace_back();
             for (const Run& r : in) inputs.back().push_back(lsm_run_t{r.entries, r.n});
             lsm_compact_job_t job{};
@@ -736,13 +755,16 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             static_cast<volatile uint64_t*>(first->counts_host)[jobs.size()] = kCountUnset;
             jobs.push_back(job);
             clear.push_back(zeroed);
+            scratch.push_back((scratch_bytes + 255) & ~size_t(255));
             steps.push_back(Step{i, merged});
         }
         const uint32_t n_jobs = (uint32_t)jobs.size();
         if (n_jobs == 0) break;
         int rc = LSM_OK;
-        const size_t need = lsm_compact_batch_workspace_bytes(jobs.data(), n_jobs);
-        if (need == 0) rc = LSM_ERR_BAD_ARG;
+        const size_t own = lsm_compact_batch_workspace_bytes(jobs.data(), n_jobs);
+        if (own == 0) rc = LSM_ERR_BAD_ARG;
+        size_t need = own;
+        for (size_t bytes : scratch) need += bytes;
         if (rc == LSM_OK && need > first->batch_workspace_bytes) {
             first->pool.give(first->batch_workspace);
             first->batch_workspace_bytes = 2 * need;
@@ -750,7 +772,13 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
             if (first->batch_workspace == nullptr) first->batch_workspace_bytes = 0, rc = LSM_ERR_HIP;
         }
         if (rc == LSM_OK) {
-            rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, first->batch_workspace, first->batch_workspace_bytes, clear.data(), first->stream);
+            char* at = static_cast<char*>(first->batch_workspace) + own;
+            for (uint32_t j = 0; j < n_jobs; j++) {
+                if (clear[j].filter == nullptr) continue;
+                clear[j].p = at;
+                at += scratch[j];
+            }
+            rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, first->batch_workspace, own, clear.data(), first->stream);
             // an error may be that of an earlier call, with this launch under way: its counts must not meet the next batch's
             if (rc != LSM_OK) (void)first->wait();
         }

@@ -447,11 +447,11 @@ def test_flush_many_when_one_tree_fails(oracle):
     assert good.levels()[0][2] == 1
 
 
-@pytest.mark.parametrize("buffer_entries,trees", [(300, 1), (1500, 1), (3600, 1), (9000, 1), (40, 2), (1500, 18), (9000, 3)])
+@pytest.mark.parametrize("buffer_entries,trees", [(300, 1), (1500, 1), (3600, 1), (9000, 1), (40, 2), (1500, 18), (9000, 3), (30_000, 1), (70_000, 2)])
 @pytest.mark.parametrize("bits", [3, 16, 64])
 def test_filters_of_driver_runs_byte_for_byte(oracle, buffer_entries, trees, bits):
     """Every run of a live tree has the filter of its entries whenever a flush has returned: filters built right behind the
-    merge (in LDS, one share and several, two sizes, and with atomics), those of runs that may move down, and those of flushed runs;
+    merge (in LDS, one share and several, two sizes, from the keys' hashes, and with atomics), those of runs that may move down, and those of flushed runs;
     a third of all writes repeat keys or delete, so that lengths fall short of their upper bounds."""
     from paper_2511_16138_amd import LsmDriver, lsm_driver_flush_many
     print("driver filters", buffer_entries, trees, bits, flush=True)
@@ -480,3 +480,24 @@ def test_filters_of_driver_runs_byte_for_byte(oracle, buffer_entries, trees, bit
                 entries = d.read(t.run.entries, n, 8).cpu()
                 got = d.read(t.bloom.blocks, blocks, 2).cpu().numpy().view(np.uint8).reshape(-1, 16)
                 assert np.array_equal(got, oracle.build_bloom(entries, blocks)), (step, n, blocks)
+
+
+def test_filter_of_keys_whose_hashes_are_close_together(oracle):
+    """A merged run all of whose hashes fall into a twentieth of the filter: ranges of blocks with far more hashes than there is room
+    for are built all the same, and the others stay empty."""
+    from paper_2511_16138_amd import LsmDriver
+    rs = np.random.RandomState(5)
+    a = np.zeros((1_700_000, 64), dtype=np.uint8)
+    a[:, :16] = rs.randint(0, 256, size=(a.shape[0], 16), dtype=np.uint8)
+    a = a[oracle.key_hashes(a) < (1 << 64) // 20][:80_000]
+    assert a.shape[0] == 80_000
+    driver = LsmDriver(40_000, size_ratio=4, window_ops=1 << 30, bloom_bits=16)
+    for part in (a[:40_000], a[40_000:]):
+        words = part[:, :16].copy().view(">u8")
+        part = np.ascontiguousarray(part[np.lexsort((words[:, 1], words[:, 0]))])
+        driver.flush(torch.from_numpy(part.view(np.int64).reshape(-1, 8)).to(dev()))
+    t, = driver.tree()
+    n, blocks = int(t.run.n), int(t.bloom.n_blocks)
+    assert n == 80_000 and blocks == oracle.bloom_blocks(n, 16)
+    got = driver.read(t.bloom.blocks, blocks, 2).cpu().numpy().view(np.uint8).reshape(-1, 16)
+    assert np.array_equal(got, oracle.build_bloom(driver.read(t.run.entries, n, 8).cpu(), blocks))
