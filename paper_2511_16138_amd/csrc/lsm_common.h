@@ -209,10 +209,12 @@ constexpr uint32_t kIndexNoEntry = 0xFFFFFFFFu;
 constexpr uint32_t kIndexTagMask = 0x7FFFu;
 __host__ __device__ inline uint64_t index_buckets(uint64_t n) { return n ? (n + 3) / 4 : 1; }
 
-// Tile status word of a compaction: top two bits = state, low 62 bits = value.  The last tile's holds the number of output entries.
+// Tile status word of a compaction: top two bits = state, then 20 bits that say which call has written it (0 where the call's first
+// launch has zeroed the words), low 42 bits = value.  The last tile's holds the number of output entries.
 constexpr uint64_t kStEmpty = 0, kStAggregate = 1, kStPrefix = 2, kStFailed = 3;
-constexpr int kStShift = 62;
-constexpr uint64_t kStValueMask = (1ull << kStShift) - 1;
+constexpr int kStShift = 62, kStEpochShift = 42, kStEpochBits = 20;
+constexpr uint64_t kStValueMask = (1ull << kStEpochShift) - 1;
+constexpr uint32_t kStEpochs = 1u << kStEpochBits;
 
 // Run descriptors passed to kernels by value.
 struct RunTable {
@@ -224,6 +226,7 @@ struct RunTable {
 __device__ __forceinline__ uint64_t run_len(const RunTable& rt, uint32_t j) { return rt.n_dev ? rt.n_dev[j] : rt.n[j]; }
 
 // Calls between the parts of the library (arguments are checked by the caller).
+constexpr uint64_t kShortTiles = 256;
 struct ClearSpan {  // device memory to be zeroed by a launch that is made anyway; 16-byte aligned
     void* p = nullptr;
     size_t bytes = 0;  // a multiple of 16
@@ -231,6 +234,12 @@ struct ClearSpan {  // device memory to be zeroed by a launch that is made anywa
     // per key; filter_built says whether the launch for it has been made
     uint32_t filter_bits = 0;
     mutable bool filter_built = false;
+    // Status words of the caller's own, kShortTiles of them.  epoch 0: unknown contents, zeroed by a launch that is made anyway if
+    // there is one (status_zeroed says so).  Otherwise every word is zero or of a smaller epoch, and a merge of two runs that is short
+    // enough is one launch.  (In a batch: those of its first job.)
+    uint64_t* status = nullptr;
+    uint32_t epoch = 0;
+    mutable bool status_zeroed = false;
     void* filter = nullptr;  // not null: p is a FilterScratch, and the filter is built there from the keys' hashes, which the merge writes
     uint64_t* hashes() const { return filter != nullptr ? reinterpret_cast<uint64_t*>(static_cast<char*>(p) + bytes) : nullptr; }
 };

@@ -57,9 +57,10 @@ constexpr uint64_t kMinSpacing = 512;
 // 18.5, 100,000 27.3 / 21.9; 24 runs, 100,000 35.2 / 31.1.  More tiles take turns, and merge_kernel gets more of them done.
 constexpr int kShortThreads = 1024;
 constexpr int kShortItems = kTileCap / kShortThreads;
-constexpr uint64_t kShortTiles = kFillTiles;
-inline uint32_t fill_spacing(uint64_t total) {
-    const uint64_t even = (total + kFillTiles - 1) / kFillTiles;
+static_assert(kShortTiles == kFillTiles, "a tile per compute unit");
+// `jobs` compactions in the launch: each may have a tile that is not full.
+inline uint32_t fill_spacing(uint64_t total, uint32_t jobs = 1) {
+    const uint64_t tiles = kFillTiles - (jobs < kFillTiles / 4 ? jobs - 1 : 0), even = (total + tiles - 1) / tiles;
     if (even < kMinSpacing) return (uint32_t)kMinSpacing;
     return even < (uint64_t)kTileCap ? (uint32_t)even : (uint32_t)kTileCap;
 }
@@ -123,6 +124,7 @@ struct Workspace {
     SampleTable st;
     uint4* clear;       // zeroed by the partition launch for a later kernel of the caller
     uint64_t clear_n;
+    uint64_t* fresh;    // kShortTiles status words of the caller's own, zeroed by the partition launch (may be null)
     uint32_t spacing;   // boundary spacing of the direct partition (batch form: to be capped by tile_spacing for each job)
     uint32_t stride, per_tile, samples;  // entries from sample to sample, samples from boundary to boundary, in all (single form; see ranked_row)
 };
@@ -587,6 +589,8 @@ __device__ __forceinline__ void partition_init(const RunTable& rt, const Workspa
     const uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (uint64_t)gridDim.x * blockDim.x;
     for (uint64_t t = i; t < n_tiles; t += stride) ws.status[t] = 0;
     for (uint64_t c = i; c < ws.clear_n; c += stride) ws.clear[c] = make_uint4(0, 0, 0, 0);
+    if (ws.fresh != nullptr)
+        for (uint64_t t = i; t < kShortTiles; t += stride) ws.fresh[t] = 0;
     if (i < rt.k) {
         ws.splits[i] = 0;
         ws.splits[n_tiles * rt.k + i] = run_len(rt, (uint32_t)i);
@@ -780,6 +784,7 @@ struct TileHead {  // what the whole workgroup knows of its tile
     uint64_t* status;
     uint4* fence_out;
     uint64_t* key_hashes;
+    uint64_t epoch;  // of the status words, in its place
 };
 
 struct MergeShared : TileHead {
@@ -1541,14 +1546,17 @@ struct ShortShared : TileHead {
 };
 
 // lookback for tiles with no more than kShortTiles - 1 before them: all their status words are asked for at once.
-__device__ uint64_t lookback_few(uint64_t* status, const uint32_t tile, const uint64_t count, const bool self_failed, bool* failed) {
+__device__ uint64_t lookback_few(uint64_t* status, const uint64_t epoch, const uint32_t tile, const uint64_t count, const bool self_failed, bool* failed) {
     const int lane = threadIdx.x & (kWave - 1);
     *failed = self_failed;
+    auto publish = [&](uint64_t state, uint64_t value) {
+        if (lane == 0) __hip_atomic_store(&status[tile], (state << kStShift) | epoch | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    };
     if (self_failed || tile == 0) {
-        if (lane == 0) __hip_atomic_store(&status[tile], self_failed ? kStFailed << kStShift : (kStPrefix << kStShift) | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        publish(self_failed ? kStFailed : kStPrefix, self_failed ? 0 : count);
         return 0;
     }
-    if (lane == 0) __hip_atomic_store(&status[tile], (kStAggregate << kStShift) | count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    publish(kStAggregate, count);
     uint64_t base = 0;
     bool bad = false;
     for (uint32_t spins = 0;; spins++) {
@@ -1557,7 +1565,10 @@ __device__ uint64_t lookback_few(uint64_t* status, const uint32_t tile, const ui
         for (int w = 0; w < kShortWindows; w++) {
             const int t = (int)tile - 1 - w * kWave - lane;
             st[w] = kStPrefix << kStShift;  // tiles before tile 0: an empty prefix
-            if (t >= 0) st[w] = __hip_atomic_load(&status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (t >= 0) {
+                st[w] = __hip_atomic_load(&status[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (((st[w] ^ epoch) >> kStEpochShift) & (kStEpochs - 1)) st[w] = kStEmpty;  // of an earlier call
+            }
         }
         bool ready = true, open = true;  // open: no prefix nearer than window w
         base = 0;
@@ -1579,8 +1590,7 @@ __device__ uint64_t lookback_few(uint64_t* status, const uint32_t tile, const ui
     }
     base = wave_sum_u64(base);
     *failed = bad;
-    const uint64_t word = bad ? (kStFailed << kStShift) : ((kStPrefix << kStShift) | (base + count));
-    if (lane == 0) __hip_atomic_store(&status[tile], word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    publish(bad ? kStFailed : kStPrefix, bad ? 0 : base + count);
     return base;
 }
 
@@ -1727,23 +1737,13 @@ __device__ __forceinline__ void short_rank(ShortShared& s, const uint4 (&ent)[kS
     __syncthreads();
 }
 
-template <int kExtras, int kMode>
-__global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint32_t flags_arg, lsm_entry_t* out_arg,
-                                                                   uint64_t* n_out_arg, const uint64_t* remap_base, uint32_t remap_files,
-                                                                   uint4* fence_out_arg, uint32_t fence_stride_arg, ModeArgs ma) {
-    static_assert(kMode == kModeSingle || kMode == kModeBatch, "ranges have tiles of their own");
-    __shared__ ShortShared s;
-    __shared__ uint64_t hash_stage[kExtras == 2 ? kTileCap : 1];
+// From the tile's pieces on; s.alive and s.deep are zero.
+template <int kExtras>
+__device__ __forceinline__ void short_tile(ShortShared& s, uint64_t* hash_stage, const uint64_t* remap_base, const uint32_t remap_files) {
     const uint32_t tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
-    if (wave == 0) tile_pieces<kMode>(s, rt, ws, n_tiles, ma, nullptr);
-    else if (wave == 1) s.alive[lane] = 0;
-    else if (wave == 2 && lane == 0) s.deep = 0;
-    static_assert(kTileCap / 32 == kWave, "a wave holds the survivors' bits");
-    __syncthreads();
     const uint32_t n = s.n, tile = s.tile;
-    const uint32_t k = kMode == kModeBatch ? s.k : rt.k;
-    const uint32_t flags = kMode == kModeBatch ? s.flags : flags_arg;
+    const uint32_t k = s.k, flags = s.flags;
     const uint32_t top_step = k > 1 ? 1u << (31 - __builtin_clz(k - 1)) : 0;
     uint4 ent[kShortItems][4];
     uint32_t piece[kShortItems], at[kShortItems];
@@ -1782,14 +1782,14 @@ __global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt,
     if (wave == 0) {
         __builtin_amdgcn_s_setprio(3);
         bool failed;
-        const uint64_t base = lookback_few(kMode == kModeBatch ? s.status : ws.status, tile, total, s.failed != 0, &failed);
+        const uint64_t base = lookback_few(s.status, s.epoch, tile, total, s.failed != 0, &failed);
         if (lane == 0) {
             s.base = base;
             if (failed) s.failed = 1;
         }
     }
     uint4* const stage = s.mem;
-    uint64_t* const key_hashes = kExtras != 2 ? nullptr : (kMode == kModeBatch ? s.key_hashes : ma.key_hashes);
+    uint64_t* const key_hashes = s.key_hashes;
 #pragma unroll
     for (int i = 0; i < kShortItems; i++) {
         if (slot[i] == kNoSlot) continue;
@@ -1805,17 +1805,16 @@ __global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt,
     __syncthreads();
     const bool failed = s.failed != 0;
     const uint64_t base = s.base;
-    const uint32_t last_tile = kMode == kModeBatch ? s.job_tiles - 1 : (uint32_t)n_tiles - 1;
-    if (tile == last_tile && tid == 0) *(kMode == kModeBatch ? s.n_out : n_out_arg) = failed ? ~0ull : base + total;
+    if (tile == s.job_tiles - 1 && tid == 0) *s.n_out = failed ? ~0ull : base + total;
     if (failed) return;
-    uint4* const dst = reinterpret_cast<uint4*>((kMode == kModeBatch ? s.out : out_arg) + base);
+    uint4* const dst = reinterpret_cast<uint4*>(s.out + base);
     for (uint32_t c = tid; c < total * 4; c += kShortThreads) {
         const uint32_t part = (c ^ (c >> 2)) & 3;
         store_streaming_u4(&dst[(c & ~3u) | part], stage[c]);
     }
-    uint4* const fence_out = kMode == kModeBatch ? s.fence_out : fence_out_arg;
+    uint4* const fence_out = s.fence_out;
     if (kExtras && fence_out != nullptr) {
-        const uint32_t fence_stride = kMode == kModeBatch ? s.fence_stride : fence_stride_arg;
+        const uint32_t fence_stride = s.fence_stride;
         const uint64_t fence = (base + fence_stride - 1) / fence_stride, skip = fence * fence_stride - base;
         for (uint64_t q = tid; skip + (q >> 1) * fence_stride < total; q += kShortThreads) {
             const uint32_t at_slot = (uint32_t)(skip + (q >> 1) * fence_stride), part = q & 1;
@@ -1824,6 +1823,109 @@ __global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt,
     }
     if (kExtras == 2 && key_hashes != nullptr)
         for (uint32_t c = tid; c < total; c += kShortThreads) key_hashes[base + c] = hash_stage[c];
+}
+
+template <int kExtras, int kMode>
+__global__ void __launch_bounds__(kShortThreads) merge_short_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint32_t flags, lsm_entry_t* out,
+                                                                   uint64_t* n_out, const uint64_t* remap_base, uint32_t remap_files,
+                                                                   uint4* fence_out, uint32_t fence_stride, ModeArgs ma) {
+    static_assert(kMode == kModeSingle || kMode == kModeBatch, "ranges have tiles of their own");
+    __shared__ ShortShared s;
+    __shared__ uint64_t hash_stage[kExtras == 2 ? kTileCap : 1];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
+    if (wave == 0) {
+        if (kMode == kModeSingle && lane == 0) {
+            s.k = rt.k;
+            s.flags = flags;
+            s.job_tiles = (uint32_t)n_tiles;
+            s.out = out;
+            s.n_out = n_out;
+            s.status = ws.status;
+            s.fence_out = fence_out;
+            s.fence_stride = fence_stride;
+            s.key_hashes = ma.key_hashes;
+        }
+        if (lane == 0) s.epoch = 0;
+        tile_pieces<kMode>(s, rt, ws, n_tiles, ma, nullptr);
+    } else if (wave == 1) {
+        s.alive[lane] = 0;
+    } else if (wave == 2 && lane == 0) {
+        s.deep = 0;
+    }
+    static_assert(kTileCap / 32 == kWave, "a wave holds the survivors' bits");
+    __syncthreads();
+    short_tile<kExtras>(s, hash_stage, remap_base, remap_files);
+}
+
+// Compactions of one or two runs each in a single launch, where the caller keeps status words of its own (see ClearSpan): every workgroup
+// finds the two boundaries of its tile itself, a wave each, and nothing has to be zeroed or written for it beforehand.
+// A launch less is 4 us on the GPU, and the two searches cost the tile two (96 driver flushes 2564 -> 2291 us).
+template <uint32_t kJobs, uint32_t kRuns>
+struct WholeTable {
+    JobDesc jobs[kJobs];
+    const lsm_entry_t* run_ptr[kRuns];
+    uint64_t run_n[kRuns];
+    uint64_t* status;
+    uint64_t epoch;  // in its place
+    uint32_t n_jobs, spacing;
+};
+template <int kExtras, uint32_t kJobs, uint32_t kRuns>
+__global__ void __launch_bounds__(kShortThreads) merge_whole_kernel(WholeTable<kJobs, kRuns> table) {
+    __shared__ ShortShared s;
+    __shared__ uint64_t hash_stage[kExtras == 2 ? kTileCap : 1];
+    __shared__ uint64_t rows[2][2];  // where the tile starts and ends in the two runs
+    const uint32_t tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    uint32_t job = 0;
+    if (kJobs > 1)
+        for (uint32_t q = 1; q < table.n_jobs; q++) job = table.jobs[q].first_tile <= blockIdx.x ? q : job;
+    const JobDesc& d = table.jobs[job];
+    const uint32_t tile = blockIdx.x - d.first_tile;
+    const lsm_entry_t *a = table.run_ptr[d.run_off], *b = d.k > 1 ? table.run_ptr[d.run_off + 1] : a;
+    const uint64_t na = table.run_n[d.run_off], nb = d.k > 1 ? table.run_n[d.run_off + 1] : 0;
+    if (wave < 2) {
+        const uint32_t row = tile + wave;
+        uint64_t ia = 0, ib = 0;
+        if (row >= d.n_tiles) ia = na, ib = nb;
+        else if (row > 0) split_two_wave(a, na, b, nb, row * (uint64_t)tile_spacing(table.spacing, d.k), ia, ib);
+        if (lane == 0) rows[wave][0] = ia, rows[wave][1] = ib;
+    } else if (wave == 2) {
+        s.alive[lane] = 0;
+        if (lane == 0) {
+            s.deep = 0;
+            s.tile = tile;
+            s.k = d.k;
+            s.flags = d.flags;
+            s.job_tiles = d.n_tiles;
+            s.out = d.out;
+            s.n_out = d.n_out;
+            s.status = table.status + d.first_tile;
+            s.epoch = table.epoch;
+            s.fence_out = d.fence_out;
+            s.fence_stride = d.fence_stride;
+            s.key_hashes = d.clear_n & kHashesBehind ? reinterpret_cast<uint64_t*>(d.clear + (d.clear_n & ~kHashesBehind)) : nullptr;
+            s.run[0] = a;
+            s.run[1] = b;
+        }
+    } else {  // what a later kernel needs zeroed
+        constexpr uint32_t kOthers = kShortThreads - 3 * kWave;
+        for (uint32_t c = tile * kOthers + tid - 3 * kWave; c < (d.clear_n & ~kHashesBehind); c += d.n_tiles * kOthers) d.clear[c] = make_uint4(0, 0, 0, 0);
+    }
+    __syncthreads();
+    if (tid == 0) {
+        const uint64_t len_a = rows[1][0] - rows[0][0], len_b = rows[1][1] - rows[0][1];
+        // only inputs that break the precondition can make a pair of rows inconsistent
+        const bool ok = rows[0][0] <= rows[1][0] && rows[0][1] <= rows[1][1] && len_a + len_b <= (uint64_t)kTileCap && len_a <= (uint64_t)kTileCap;
+        s.lo[0] = rows[0][0];
+        s.lo[1] = rows[0][1];
+        s.seg[0] = 0;
+        s.seg[1] = ok ? (uint32_t)len_a : 0;
+        s.seg[2] = ok ? (uint32_t)(len_a + len_b) : 0;
+        s.n = s.seg[2];
+        s.failed = ok ? 0 : 1;
+    }
+    __syncthreads();
+    short_tile<kExtras>(s, hash_stage, nullptr, 0);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1841,6 +1943,8 @@ struct BatchInline {
     const lsm_entry_t* run_ptr[kInlineRuns];
     uint64_t run_n[kInlineRuns];
 };
+constexpr uint32_t kWholeRuns = 2 * kInlineJobs;
+static_assert(kWholeRuns <= kInlineRuns, "the runs of a table of pairs");
 static_assert(sizeof(BatchInline) <= 2560, "fits the argument segment of a launch beside the rest");
 
 template <int kPerLane, bool kMany, bool kInline>
@@ -1867,6 +1971,8 @@ __global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, Mo
         if (lane < d.k) const_cast<uint64_t*>(ma.run_n)[d.run_off + lane] = run_n[d.run_off + lane];
     }
     for (uint64_t c = w * (uint64_t)kWave + lane; c < (d.clear_n & ~kHashesBehind); c += (uint64_t)waves * kWave) d.clear[c] = make_uint4(0, 0, 0, 0);
+    if (ws.fresh != nullptr && blockIdx.x == 0)
+        for (uint32_t t = lane; t < kShortTiles; t += kWave) ws.fresh[t] = 0;
     for (uint32_t t = w * kWave + lane; t < d.n_tiles; t += waves * kWave) {
         const_cast<uint32_t*>(ma.tile_job)[d.first_tile + t] = job;
         ws.status[d.first_tile + t] = 0;
@@ -1992,6 +2098,7 @@ static size_t carve(void* base, const uint64_t* run_lens, uint32_t k, Workspace*
     }
     w.clear = nullptr;
     w.clear_n = 0;
+    w.fresh = nullptr;
     w.spacing = cut.spacing;
     w.stride = cut.stride;
     w.per_tile = cut.per_tile;
@@ -2034,10 +2141,39 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
     const bool direct = n_tiles > 1 && (n_tiles < direct_tiles(n_runs) || n_runs == 2);  // two runs: bisection on the merge path at any size
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
+    auto build_filter = [&](const ClearSpan& span) {  // right behind the merge, if it is asked for
+        if (ws.clear_n == 0 || span.filter_bits == 0) return (int)LSM_OK;
+        const bool hashed = span.filter != nullptr;
+        const CountedFilter filter = {out->entries, total, ws.status + n_tiles - 1, hashed ? span.filter : span.p, span.filter_bits, hashed ? span.p : nullptr};
+        if (build_filters_counted(&filter, 1, stream) != LSM_OK) return (int)LSM_ERR_HIP;
+        span.filter_built = true;
+        return (int)LSM_OK;
+    };
     if (clear.bytes != 0 && direct && fused_init) {
         ws.clear = static_cast<uint4*>(clear.p);
         ws.clear_n = clear.bytes / 16;
         *cleared = true;
+    }
+    const uint32_t fence_stride = out->fence_keys ? out->fence_stride : 1u;
+    if (clear.status != nullptr && clear.epoch == 0 && direct && fused_init) {
+        ws.fresh = clear.status;
+        clear.status_zeroed = true;
+    }
+    if (clear.status != nullptr && clear.epoch != 0 && n_runs <= 2 && n_tiles > 1 && n_tiles <= kShortTiles && fused_init && remap_files == 0 && !ev && !rt.n_dev) {
+        WholeTable<1, 2> table = {};
+        table.jobs[0] = JobDesc{0, 0, 0, 0, 0, 0, out->entries, out->n_out, reinterpret_cast<uint4*>(out->fence_keys), (uint32_t)n_tiles, n_runs, flags,
+                                fence_stride, ws.clear, (uint32_t)ws.clear_n, 0};
+        if (clear.filter != nullptr) table.jobs[0].clear_n |= kHashesBehind;
+        for (uint32_t j = 0; j < n_runs; j++) table.run_ptr[j] = rt.ptr[j], table.run_n[j] = rt.n[j];
+        table.status = ws.status = clear.status;
+        table.epoch = (uint64_t)clear.epoch << kStEpochShift;
+        table.n_jobs = 1;
+        table.spacing = ws.spacing;
+        const dim3 grid((uint32_t)n_tiles), threads(kShortThreads);
+        if (clear.filter != nullptr) hipLaunchKernelGGL((merge_whole_kernel<2, 1, 2>), grid, threads, 0, stream, table);
+        else hipLaunchKernelGGL((merge_whole_kernel<1, 1, 2>), grid, threads, 0, stream, table);
+        if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
+        return build_filter(clear);
     }
     if (!fused_init) {
         uint32_t init_blocks = (uint32_t)((n_tiles + 255) / 256);
@@ -2103,7 +2239,6 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
         return LSM_ERR_HIP;
     if (n_tiles > 0) {
         uint4* const fence_out = reinterpret_cast<uint4*>(out->fence_keys);
-        const uint32_t fence_stride = out->fence_keys ? out->fence_stride : 1u;
         ModeArgs extras = {};
         extras.key_hashes = out->key_hashes != nullptr ? out->key_hashes : ws.clear_n != 0 ? clear.hashes() : nullptr;
         auto launch = [&](auto extras_value) {
@@ -2122,12 +2257,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     if (ev && ev->after_merge && hipEventRecord(static_cast<hipEvent_t>(ev->after_merge), stream) != hipSuccess)
         return LSM_ERR_HIP;
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
-    if (ws.clear_n != 0 && clear.filter_bits != 0) {
-        const bool hashed = clear.filter != nullptr;
-        const CountedFilter filter = {out->entries, total, ws.status + n_tiles - 1, hashed ? clear.filter : clear.p, clear.filter_bits, hashed ? clear.p : nullptr};
-        if (build_filters_counted(&filter, 1, stream) != LSM_OK) return LSM_ERR_HIP;
-        clear.filter_built = true;
-    }
+    if (build_filter(clear) != LSM_OK) return LSM_ERR_HIP;
     if (flags & LSM_VALIDATE) {
         uint64_t n = 0;
         if (hipMemcpyAsync(&n, out->n_out, sizeof(n), hipMemcpyDeviceToHost, stream) != hipSuccess) return LSM_ERR_HIP;
@@ -2296,7 +2426,7 @@ static int batch_layout(const lsm_compact_job_t* jobs, uint32_t n_jobs, BatchLay
         if (jobs[j].runs == nullptr || jobs[j].n_runs > LSM_MAX_RUNS) continue;  // refused below
         for (uint32_t r = 0; r < jobs[j].n_runs; r++) l->all += jobs[j].runs[r].n;
     }
-    l->spacing = fill_spacing(l->all);
+    l->spacing = fill_spacing(l->all, n_jobs);
     for (uint32_t j = 0; j < n_jobs; j++) {
         const lsm_compact_job_t& job = jobs[j];
         if (job.runs == nullptr) return LSM_ERR_NULL;
@@ -2423,6 +2553,11 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
     ma.jobs = reinterpret_cast<const JobDesc*>(base + l.jobs);
     ma.run_ptr = reinterpret_cast<const lsm_entry_t* const*>(base + l.run_ptr);
     ma.run_n = reinterpret_cast<const uint64_t*>(base + l.run_n);
+    if (clear != nullptr && clear[0].status != nullptr && clear[0].epoch == 0) {
+        ws.fresh = clear[0].status;
+        clear[0].status_zeroed = true;
+    }
+    const bool whole = clear != nullptr && clear[0].status != nullptr && clear[0].epoch != 0 && fits_inline && l.k_max <= 2 && tile <= kShortTiles;
     const int group_log = log2_ceil(l.k_max);
     const dim3 waves((uint32_t)wave), threads(kWave);
     auto launch = [&](auto inline_table) {
@@ -2431,8 +2566,22 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
         else if (l.k_max <= kFewRuns) hipLaunchKernelGGL((partition_batch_kernel<8, false, kInline>), waves, threads, 0, stream, ws, ma, group_log, n_jobs, table);
         else hipLaunchKernelGGL((partition_batch_kernel<8, true, kInline>), waves, threads, 0, stream, ws, ma, group_log, n_jobs, table);
     };
-    if (fits_inline) launch(std::true_type{});
-    else launch(std::false_type{});
+    if (whole) {
+        WholeTable<kInlineJobs, kWholeRuns> one = {};
+        memcpy(one.jobs, table.jobs, sizeof(one.jobs));
+        memcpy(one.run_ptr, table.run_ptr, sizeof(one.run_ptr));
+        memcpy(one.run_n, table.run_n, sizeof(one.run_n));
+        one.status = ws.status = clear[0].status;
+        one.epoch = (uint64_t)clear[0].epoch << kStEpochShift;
+        one.n_jobs = n_jobs;
+        one.spacing = l.spacing;
+        if (any_hashes) hipLaunchKernelGGL((merge_whole_kernel<2, kInlineJobs, kWholeRuns>), dim3((uint32_t)tile), dim3(kShortThreads), 0, stream, one);
+        else hipLaunchKernelGGL((merge_whole_kernel<1, kInlineJobs, kWholeRuns>), dim3((uint32_t)tile), dim3(kShortThreads), 0, stream, one);
+    } else if (fits_inline) {
+        launch(std::true_type{});
+    } else {
+        launch(std::false_type{});
+    }
     RunTable rt = {};
     rt.k = 1;
     auto launch_merge = [&](auto extras_value) {
@@ -2444,9 +2593,10 @@ int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*
             hipLaunchKernelGGL((merge_kernel<kExtras, kModeBatch>), dim3((uint32_t)tile), dim3(kMergeThreads), 0, stream, rt, ws, tile, 0u,
                                (lsm_entry_t*)nullptr, (uint64_t*)nullptr, (const uint64_t*)nullptr, 0u, (uint4*)nullptr, 1u, ma);
     };
-    if (any_hashes) launch_merge(std::integral_constant<int, 2>{});
-    else if (any_fences) launch_merge(std::integral_constant<int, 1>{});  // the form that also writes fence indices (a job without one has a null pointer in its descriptor)
-    else launch_merge(std::integral_constant<int, 0>{});
+    // any_fences: the form that also writes fence indices (a job without one has a null pointer in its descriptor)
+    if (!whole && any_hashes) launch_merge(std::integral_constant<int, 2>{});
+    else if (!whole && any_fences) launch_merge(std::integral_constant<int, 1>{});
+    else if (!whole) launch_merge(std::integral_constant<int, 0>{});
     if (hipGetLastError() != hipSuccess) return LSM_ERR_HIP;
     for (uint32_t j = 0; clear != nullptr && j < n_jobs;) {
         CountedFilter filters[kInlineJobs];

@@ -133,6 +133,8 @@ struct lsm_driver {
     size_t counts_host_count = 0;
     void* batch_workspace = nullptr;
     size_t batch_workspace_bytes = 0;
+    uint64_t* status = nullptr;  // status words for merges in one launch (see lsm::ClearSpan)
+    uint32_t epoch = 0;          // of the next merge; 0: the words are not zero yet
 
     void record(uint32_t kind, uint32_t level, uint32_t a, uint32_t b, uint64_t n_in, uint64_t n_out) {
         lsm_driver_event_t e;
@@ -279,6 +281,18 @@ struct lsm_driver {
         clear->p = r.bloom;
         clear->bytes = blocks * 16;
         return LSM_OK;
+    }
+
+    // The driver's status words for one call, and what the call has made of them: from the first that has zeroed them on, every call has
+    // an epoch of its own, until these are used up or a call has failed.
+    int lend_status(lsm::ClearSpan* clear) {
+        if (status == nullptr) status = static_cast<uint64_t*>(pool.take(lsm::kShortTiles * sizeof(uint64_t)));
+        clear->status = status, clear->epoch = epoch, clear->status_zeroed = false;
+        return status != nullptr ? LSM_OK : LSM_ERR_HIP;
+    }
+    void status_used(const lsm::ClearSpan& clear, int rc) {
+        const bool known = rc == LSM_OK && (epoch != 0 || clear.status_zeroed);
+        epoch = known && epoch + 1 < lsm::kStEpochs ? epoch + 1 : 0;
     }
 
     // A merged run whose filter has been built by the call that merged it has every structure it is to get (what holds for the
@@ -449,10 +463,12 @@ struct lsm_driver {
             }
         }
         if (scratch_bytes != 0) clear.p = static_cast<char*>(workspace) + own;
+        if (lend_status(&clear) != LSM_OK) return fails(LSM_ERR_HIP);
         const lsm_out_t out{entries, room, n_host, fences, cfg.fence_stride, nullptr};
         *static_cast<volatile uint64_t*>(n_host) = kCountUnset;
         int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, own, clear, &merged->bloom_clear, stream);
         if (clear.filter != nullptr) merged->bloom_clear = false;
+        status_used(clear, rc);
         // an error may be that of the filter's launch, or of an earlier call, with the merge under way: its count must not meet the next one's
         if (rc != LSM_OK) (void)wait();
         if (rc == LSM_OK) rc = watch_count(n_host);
@@ -778,7 +794,11 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
                 clear[j].p = at;
                 at += scratch[j];
             }
+            rc = first->lend_status(&clear[0]);
+        }
+        if (rc == LSM_OK) {
             rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, first->batch_workspace, own, clear.data(), first->stream);
+            first->status_used(clear[0], rc);
             // an error may be that of an earlier call, with this launch under way: its counts must not meet the next batch's
             if (rc != LSM_OK) (void)first->wait();
         }
