@@ -85,16 +85,25 @@ constexpr uint32_t kMinStride = 8;
 // us with 128, 25 + 132 with 256; 24 x 1M 21 + 92 and 12 + 100; 4 x 4M 8.7 + 34 and 6.7 + 33.
 constexpr uint32_t kRowStride = 256;
 constexpr uint64_t kSampleStride = 32;  // one key in 32 is copied for the sampled partition
-// Inputs of fewer tiles search the runs directly, a wave per boundary, larger ones on a copy of every 32nd key first.  The samples
-// cost 100 to 150 us in four dependent launches up to there, the direct search grows with the boundaries, and with the runs.
-// Direct / sampled, mixed runs: 3 runs of 4.3M entries in all 29 / 105 us, 18M 103 / 133, 26M 140 / 146; 4 runs, 18M 124 / 141, 22M 151 /
-// 146; 8 runs, 4.3M 44 / 111, 13M 121 / 144, 18M 156 / 159; 16 runs, 4.3M 59 / 123, 10.5M 152 / 153; 32 runs, 4.3M 140 / 141,
-// 6M 165 / 149.  Runs that cover different keys cost either search more, the samples the most.  Whole calls, runs one after the
-// other / in turns of 100 entries / with the same keys: 4 runs of 18M entries in all, direct 597 / 651 / 508 us, sampled
-// 775 / 734 / 542; 8 runs, 15M, 558 / 631 / 507 and 736 / 701 / 517; 16 runs, 9.5M, 487 / 483 / 452 and 626 / 694 / 450.
+// How the boundaries of three runs or more are found where ranked samples are too many.
+//   A wave per boundary over the whole runs (partition_kernel): up to four runs, up to kRowsTiles tiles; more than kFewRuns runs.
+//   Rows first (partition_rows_kernel, partition_between_kernel): every row_entries-th entry of every run is ranked in all runs, and a boundary's
+//     wave searches between two of these rows.  Up to 16 runs as long as entries x runs are below kRowsPieces, up to kFewRuns below
+//     kSampledMinTiles tiles.
+//   On a copy of every 32nd key (sample_kernel and the three after it): what is left.
+// Whole calls, us.  A wave per boundary / rows: 4 runs, 2M entries 86.5 / 90.0, 4M 157 / 157, 8M 293 / 286, 16M 570 / 534; 8 runs, 1M 65.4 / 63.3, 4M
+// 176 / 172, 8M 324 / 313, 16M 623 / 573; 16 runs, 2M 126 / 117, 4M 203 / 193, 8M 380 / 358; 24 runs, 2M 158 / 143, 4M 237 / 227.
+// Samples / rows: 3 runs, 32M entries 1108 / 1027; 4 runs, 50M 1613 / 1577; 8 runs, 32M 1134 / 1104; 12 runs, 16M 679 / 637, 50M 1901 / 1852; 16 runs,
+// 16M 688 / 666, 50M 1972 / 1931; but 16 runs, 67M 2517 / 2530; 24 runs, 16M 784 / 816, 50M 2266 / 2390.  Runs that cover
+// different keys gain more: 16 runs one after the other, 9.5M entries, samples / rows 466 / 325, in turns of 100 entries 454 / 462; 8 runs, a wave per
+// boundary / rows 356 / 304 and 375 / 373.
 constexpr uint64_t kSampledMinTiles = 2048;
-constexpr uint64_t kDirectMostTiles = 10240;
-__host__ __device__ inline uint64_t direct_tiles(uint32_t k) { return k <= 4 ? kDirectMostTiles : (k <= 8 ? 8192 : (k <= 16 ? 5120 : kSampledMinTiles)); }
+constexpr uint64_t kRowsTiles = 2048;
+constexpr uint64_t kRowsPieces = 1ull << 30;
+// Entries from row to row.  With fewer, more samples are ranked, with more, more is left between them: 2,048 / 4,096 / 8,192 / 16,384, 8 runs, 2M
+// entries 99.8 / 96.6 / 98.9 / 103.6, 32M 1121 / 1104 / 1094 / 1104; 16 runs, 16M 685 / 666 / 654 / 662, 50M - / 1943 / 1931 / 1970.
+constexpr uint64_t kManyRowsEntries = 12000000;
+inline uint32_t row_entries(uint64_t total) { return total < kManyRowsEntries ? 4096 : 8192; }
 constexpr uint32_t kSpinLimit = 1u << 22;              // polls of one look-back window before giving up
 
 struct Header {  // first 256 bytes of the workspace
@@ -339,10 +348,10 @@ struct WindowShared {
     ulonglong2 hi[kWave * kPerLane + kWave];  // key bytes 16..31
 };
 
-// The lower bound in run j = lane % group of the key with the largest L <= r.  The whole wave calls; lanes without a run
-// pass len = 0.  Fewer than 2^32 entries in all.
+// The lower bound in run j = lane % group of the key with the largest L <= r, which lies in [lo, hi].  The whole wave calls; lanes without
+// a run pass lo = hi = 0.  Fewer than 2^32 entries in all.
 template <int kPerLane, bool kMany>
-__device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, const lsm_entry_t* run, const uint32_t len, const uint32_t r,
+__device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, const lsm_entry_t* run, uint32_t lo, uint32_t hi, const uint32_t r,
                                                  const int group_log_any) {
     const int group_log = kMany ? 6 : group_log_any;
     const int lane = threadIdx.x & (kWave - 1), group = 1 << group_log;
@@ -351,7 +360,7 @@ __device__ __forceinline__ uint32_t window_split(WindowShared<kPerLane>& s, cons
     const uint32_t groups = 1u << groups_log, m = groups * kPerLane;
     ulonglong2* const my_lo = s.lo + j * (m + 1);
     ulonglong2* const my_hi = s.hi + j * (m + 1);
-    uint32_t lo = 0, hi = len, turn = 0;
+    uint32_t turn = 0;
     for (;;) {
         const uint32_t width = hi - lo;
         const bool exact = __ballot(width > m) == 0;
@@ -580,7 +589,7 @@ __device__ __forceinline__ GroupLane group_lane(int group) {
     return g;
 }
 
-// Search over whole runs, for inputs of up to direct_tiles tiles, and of two runs at any size: one launch.
+// Search over whole runs, one launch (where rows come first, in the first launch).
 // kInit: the launch also clears the tile status words and writes the first and last split rows, which saves the
 // separate init launch (a small compaction is then two launches: this one and the merge).
 template <bool kInit>
@@ -631,7 +640,7 @@ __global__ void __launch_bounds__(kWave) partition_kernel(RunTable rt, Workspace
     partition_init<kInit>(rt, ws, n_tiles);
     const uint32_t b = near_block() + 1, lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
     const bool own = j < rt.k;
-    const uint32_t best = window_split<kPerLane, kMany>(s, own ? rt.ptr[j] : nullptr, own ? (uint32_t)run_len(rt, j) : 0, b * ws.spacing, group_log);
+    const uint32_t best = window_split<kPerLane, kMany>(s, own ? rt.ptr[j] : nullptr, 0, own ? (uint32_t)run_len(rt, j) : 0, b * ws.spacing, group_log);
     if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
 }
 template <bool kInit>
@@ -641,6 +650,37 @@ __global__ void __launch_bounds__(kWave) partition_ranked_kernel(RunTable rt, Wo
     const bool mine = member < rt.k;
     ranked_row(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, blockIdx.x, rt.k, group_log,
                 ws.stride, ws.per_tile, ws.splits);
+}
+// Boundaries between rows, two launches.  partition_rows_kernel: the lower bounds of every row_entries-th entry of every run in all runs, in order
+// of the entries' keys, a wave each (ranked_row).  partition_between_kernel: row t has row_entries * (t - k) <= L <= row_entries * t, so the last one that
+// is not beyond a boundary's rank is among k + 1; the boundary lies between it and the next, in some row_entries entries of all runs together, where
+// window_split has two rounds left instead of five.  Bound by the lines that both fetch (a record is 128 bytes of traffic, its neighbour aside).
+template <bool kInit>
+__global__ void __launch_bounds__(kWave) partition_rows_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint32_t row_entries, int group_log) {
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint32_t member = (threadIdx.x & (kWave - 1)) >> (6 - group_log);
+    const bool mine = member < rt.k;
+    ranked_row(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, near_block(), rt.k, group_log,
+                row_entries, 1, ws.ywin);
+}
+template <int kPerLane>
+__global__ void __launch_bounds__(kWave) partition_between_kernel(RunTable rt, Workspace ws, uint32_t n_rows, uint32_t row_entries, int group_log) {
+    __shared__ WindowShared<kPerLane> s;
+    const uint32_t b = near_block() + 1, lane = threadIdx.x, group = 1u << group_log, j = lane & (group - 1), g = lane >> group_log, groups = kWave >> group_log;
+    const bool own = j < rt.k;
+    const uint32_t len = own ? (uint32_t)run_len(rt, j) : 0, r = b * ws.spacing;
+    // the last row that is not beyond r
+    auto row = [&](uint32_t t) { return own && t > 0 ? (t < n_rows ? min((uint32_t)ws.ywin[(uint64_t)t * rt.k + j], len) : len) : 0; };  // inputs that are not sorted may leave a row unwritten
+    uint32_t t = r / row_entries;
+    for (uint32_t c = t + 1;; c += groups) {
+        const uint32_t sum = group_sum_u32(row(c + g), group);
+        const uint64_t below = __ballot(sum <= r && c + g < n_rows);
+        t += __popcll(below) >> group_log;
+        if (~below != 0) break;
+    }
+    const uint32_t lo = row(t), hi = row(t + 1);
+    const uint32_t best = window_split<kPerLane, false>(s, own ? rt.ptr[j] : nullptr, lo, max(lo, hi), r, group_log);
+    if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
 }
 // With many runs and many tiles the records that the waves' rounds read are more than the memory takes (a round of 64 runs is
 // 512 lines of 128 bytes): beyond kWindowPieces pieces of tiles in runs the pivoting selection, whose searches share their
@@ -656,7 +696,6 @@ __global__ void __launch_bounds__(kWave) partition_many_kernel(RunTable rt, Work
     const uint64_t best = select_split<false>(own ? rt.ptr[lane] : nullptr, 0, own ? run_len(rt, lane) : 0, b * (uint64_t)ws.spacing, own, (int)lane, kWave, 0);
     if (own) ws.splits[(uint64_t)b * rt.k + lane] = best;
 }
-static_assert(kDirectMostTiles * kTileCap < (1ull << 32), "the window search counts in 32 bits");
 
 static int log2_ceil(uint32_t k) {
     int log = 0;
@@ -1999,7 +2038,7 @@ __global__ void __launch_bounds__(kWave) partition_batch_kernel(Workspace ws, Mo
     }
     const uint32_t j = lane & ((1u << group_log) - 1);
     const bool own = j < d.k;
-    const uint32_t best = window_split<kPerLane, kMany>(s, own ? run_ptr[d.run_off + j] : nullptr, own ? (uint32_t)run_n[d.run_off + j] : 0,
+    const uint32_t best = window_split<kPerLane, kMany>(s, own ? run_ptr[d.run_off + j] : nullptr, 0, own ? (uint32_t)run_n[d.run_off + j] : 0,
                                                         w * tile_spacing(ws.spacing, d.k), group_log);
     if (lane < d.k) rows[w * d.k + lane] = best;
 }
@@ -2139,7 +2178,10 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     const uint64_t n_tiles = ws.n_tiles;
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
-    const bool direct = n_tiles > 1 && (n_tiles < direct_tiles(n_runs) || n_runs == 2);  // two runs: bisection on the merge path at any size
+    // two runs: bisection on the merge path at any size
+    const bool rows = n_runs > 2 && n_runs <= kFewRuns && ws.stride == 0 && rt.n_dev == nullptr && total * n_runs < (n_runs <= 16 ? kRowsPieces : ~0ull) &&
+                      (n_runs <= 16 || n_tiles < kSampledMinTiles) && n_tiles >= (n_runs <= 4 ? kRowsTiles : 2);
+    const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs == 2 || rows);
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
     auto build_filter = [&](const ClearSpan& span) {  // right behind the merge, if it is asked for
         if (ws.clear_n == 0 || span.filter_bits == 0) return (int)LSM_OK;
@@ -2210,7 +2252,14 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                                        stream, rt, ws, n_tiles);
                 else if (ws.stride != 0)
                     hipLaunchKernelGGL(partition_ranked_kernel<kInit>, dim3(ws.samples), dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
-                else if (records_per_lane(group_log) == 4)
+                else if (rows) {
+                    const uint32_t step = row_entries(total);
+                    uint32_t n_rows = 0;
+                    for (uint32_t j = 0; j < n_runs; j++) n_rows += (uint32_t)((rt.n[j] + step - 1) / step);
+                    hipLaunchKernelGGL(partition_rows_kernel<kInit>, dim3(n_rows), dim3(kWave), 0, stream, rt, ws, n_tiles, step, group_log);
+                    if (records_per_lane(group_log) == 4) hipLaunchKernelGGL(partition_between_kernel<4>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, step, group_log);
+                    else hipLaunchKernelGGL(partition_between_kernel<8>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, step, group_log);
+                } else if (records_per_lane(group_log) == 4)
                     hipLaunchKernelGGL((partition_kernel<kInit, 4, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (n_runs <= kFewRuns)
                     hipLaunchKernelGGL((partition_kernel<kInit, 8, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);

@@ -545,6 +545,30 @@ def test_boundaries_at_ranked_samples(g, oracle, k, shape):
         assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
 
 
+@pytest.mark.parametrize("k,total", [(3, 2048 * 2045 + 1), (4, 2048 * 2044 - 1), (5, 1_100_000), (16, 1_300_003), (17, 2_000_000), (32, 1_500_000)])
+@pytest.mark.parametrize("shape", ["ragged", "copies", "apart"])
+def test_boundaries_between_rows(g, oracle, k, total, shape):
+    """Boundaries that are searched between ranked rows (every 4,096th entry of a run), and with four runs just below.  Ragged: empty runs, runs
+    of one entry, around 4,096 and far longer.  Copies: rows of the same key in every run.  Apart: between two rows lies one run only."""
+    print("between rows", k, total, shape, flush=True)
+    rs = np.random.RandomState(k)
+    lens = np.full(k, total // k)
+    if shape == "ragged":
+        few = np.array([0, 1, 4095, 4096, 4097, 8193])
+        lens = np.where(rs.rand(k) < 0.6, few[rs.randint(0, 6, size=k)], (total * rs.dirichlet(np.full(k, 0.7))).astype(np.int64))
+    lens[rs.randint(k)] += max(0, total - lens.sum())
+    if shape == "copies":
+        one = _runs_of(oracle, rs, [int(lens.max())], 3 * int(lens.max()))[0]
+        runs = [one[:n].clone() for n in lens]
+        for r in runs:
+            r[:, 4] = torch.randint(0, 1 << 40, (r.shape[0],), device=dev())
+    else:
+        runs = _runs_of(oracle, rs, lens, 2 * total)
+        for j in range(k if shape == "apart" else 0):
+            runs[j][:, 0] |= (j * 7) % 64 + 1  # the keys' first byte, as stored
+    _check_compact(g, oracle, runs, int(total & 1))
+
+
 @pytest.mark.parametrize("n_req", [1, 2, 3, 511, 512, 513, 2047, 2048, 2049])  # four, two and one wave per request
 @pytest.mark.parametrize("row", [256, 192, 64, 17])                            # key rows that need four, three or one of them
 def test_probe_batches_of_all_sizes(g, oracle, cfg1, n_req, row):
