@@ -87,11 +87,11 @@ __device__ __forceinline__ void rank_against(const uint4* heads, const uint32_t 
 
 // n^2 compares of 16-byte key halves.  A workgroup ranks only kRankEntries entries, so that a buffer of a few thousand
 // is hundreds of workgroups (one thread per entry left 15 workgroups with 3,600 serial compares each: 387 us for this
-// step on 3,600 entries): 16 lanes hold 16 entries, and the 32 groups of 16 lanes share the other entries out, which are
-// staged in LDS (the lanes of a wave read four records at a time).  Bound by the instructions of the compares: eight a pair, and
-// 15.9 -> 11.5 us for 3,600 entries, 34.4 -> 27.3 for
-// 8,192, since they are a subtraction with borrow.
-constexpr int kRankThreads = 512;
+// step on 3,600 entries): 16 lanes hold 16 entries, and the 64 groups of 16 lanes share the other entries out, which are
+// staged in LDS (the lanes of a wave read four records at a time).  Bound by the instructions of the compares, eight a pair (15.9 -> 11.5 us
+// for 3,600 entries since they are a subtraction with borrow), and by the chain of steps of a workgroup: with 512 threads, 32 groups, a call
+// of 3,600 entries takes 14.3 us, with 1,024 13.4; 4,096 15.4 and 14.1; 8,192 31.3 and 30.0; up to 1,500 the same.
+constexpr int kRankThreads = 1024;
 constexpr int kRankEntries = 16;
 constexpr int kRankTile = 2048;  // records staged at a time
 __global__ void __launch_bounds__(kRankThreads) flush_rank_kernel(const lsm_entry_t* buffer, uint32_t n, uint32_t* packed) {
@@ -122,7 +122,7 @@ __global__ void __launch_bounds__(kRankThreads) flush_rank_kernel(const lsm_entr
         __syncthreads();
         rank_against(tile, t0, count, slice, kSlices, buffer, n, i, head, key, seq, rank, shadowed);
     }
-    // both results of the 32 slices in one word: the sums stay below 2^16 (rank) and 2^6 (slices that saw a newer version)
+    // both results of the 64 slices in one word: the sums stay below 2^16 (rank) and 2^7 (slices that saw a newer version)
     uint32_t v = rank | (shadowed ? 1u << 16 : 0u);
     v += __shfl_xor(v, 16, kWave);
     v += __shfl_xor(v, 32, kWave);
