@@ -13,6 +13,8 @@
 // newest run, so that among equal sequence numbers the later write wins there as well).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "lsm_common.h"
 
 namespace lsm {
@@ -243,12 +245,14 @@ __global__ void __launch_bounds__(kPlaceThreads) flush_place_kernel(const lsm_en
 // One workgroup sorts one segment.
 // What moves through LDS is a 16-byte record per entry: the first 14 key bytes as a 112-bit number and, below, the
 // entry's age (0 = written last), so records are distinct and versions of a key come in write order, newest write
-// first.  Every thread sorts four consecutive records in registers, then log2(segment / 4) rounds of merge-path merges
+// first.  Every thread sorts four consecutive records in registers and every wave its 256, by bitonic merges between lanes (data moves inside
+// rows of 16 lanes by DPP, no LDS and no barrier); then log2(segment / 256) rounds of merge-path merges
 // double the sorted lists, a thread producing four outputs per round from four records of either list (bitonic
 // half-cleaner and merge network).  Positions whose 14 bytes equal a neighbour's (versions of a key, and keys that
 // differ further on) are settled afterwards by the rest of the key, seqno and age: each by comparing itself with the whole
 // group, or, where some group is long, by a merge sort of the whole segment that compares these.  Bound by LDS
-// operations of one compute unit per segment; all pairs of a segment instead took 936 us for 100,001 entries, this 27.  The entries themselves are
+// operations of one compute unit per segment; all pairs of a segment instead took 936 us for 100,001 entries, this 24
+// (27 with merge-path rounds in LDS for lists of less than 256 as well): load 1, sort in waves 6, three rounds 5, ties 3, positions 1, output 3.5.  The entries themselves are
 // read a second time for the output (they come from the L2).
 // ---------------------------------------------------------------------------------------
 // Short segments put more compute units to work (a segment is a serial chain on one), at the price of one merge round more and more
@@ -293,6 +297,63 @@ __device__ __forceinline__ void rec_order(Rec& a, Rec& b) {
     const Rec t = a;
     a.hi = swap ? b.hi : a.hi, a.lo = swap ? b.lo : a.lo;
     b.hi = swap ? t.hi : b.hi, b.lo = swap ? t.lo : b.lo;
+}
+// v of the lane whose number differs in the bits of kMask
+template <int kMask>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+    auto dpp = [](uint32_t x, auto control) { return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, decltype(control)::value, 0xF, 0xF, true); };
+    using std::integral_constant;
+    if constexpr (kMask == 1) return dpp(v, integral_constant<int, 0xB1>{});            // quad_perm 1 0 3 2
+    else if constexpr (kMask == 2) return dpp(v, integral_constant<int, 0x4E>{});       // quad_perm 2 3 0 1
+    else if constexpr (kMask == 3) return dpp(v, integral_constant<int, 0x1B>{});       // quad_perm 3 2 1 0
+    else if constexpr (kMask == 7) return dpp(v, integral_constant<int, 0x141>{});      // mirrored half row
+    else if constexpr (kMask == 15) return dpp(v, integral_constant<int, 0x140>{});     // mirrored row
+    else if constexpr (kMask == 8) return dpp(v, integral_constant<int, 0x128>{});      // row turned by eight
+    else if constexpr (kMask == 4) return lane_xor<3>(lane_xor<7>(v));
+    else return (uint32_t)__shfl_xor((int)v, kMask, kWave);
+}
+// One exchange between lanes: the lane with the lower number keeps the smaller record of each pair.  kMirror: record i meets the other
+// lane's record 3 - i.
+template <int kMask, bool kMirror>
+__device__ __forceinline__ void lanes_order(Rec (&c)[4]) {
+    constexpr int kTop = kMask >= 32 ? 32 : (kMask >= 16 ? 16 : (kMask >= 8 ? 8 : (kMask >= 4 ? 4 : (kMask >= 2 ? 2 : 1))));
+    const bool upper = (threadIdx.x & kTop) != 0;
+    Rec other[4];
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const Rec& x = c[kMirror ? 3 - i : i];
+        other[i].hi = ((uint64_t)lane_xor<kMask>((uint32_t)(x.hi >> 32)) << 32) | lane_xor<kMask>((uint32_t)x.hi);
+        other[i].lo = ((uint64_t)lane_xor<kMask>((uint32_t)(x.lo >> 32)) << 32) | lane_xor<kMask>((uint32_t)x.lo);
+    }
+#pragma unroll
+    for (int i = 0; i < 4; i++) {
+        const bool take = rec_less(other[i], c[i]) != upper;
+        c[i].hi = take ? other[i].hi : c[i].hi;
+        c[i].lo = take ? other[i].lo : c[i].lo;
+    }
+}
+// The wave's 256 records in ascending order, four per lane: lists of four, then bitonic merges of lists twice as long each time.
+template <int kLanes>  // of a list
+__device__ __forceinline__ void lanes_merge(Rec (&c)[4]) {
+    lanes_order<2 * kLanes - 1, true>(c);  // the second list backwards
+    if constexpr (kLanes >= 32) lanes_order<16, false>(c);
+    if constexpr (kLanes >= 16) lanes_order<8, false>(c);
+    if constexpr (kLanes >= 8) lanes_order<4, false>(c);
+    if constexpr (kLanes >= 4) lanes_order<2, false>(c);
+    if constexpr (kLanes >= 2) lanes_order<1, false>(c);
+    rec_order(c[0], c[2]), rec_order(c[1], c[3]);
+    rec_order(c[0], c[1]), rec_order(c[2], c[3]);
+}
+__device__ __forceinline__ void wave_sort(Rec (&c)[4]) {
+    rec_order(c[0], c[1]), rec_order(c[2], c[3]);  // odd-even merge sort of four (Batcher): five exchanges
+    rec_order(c[0], c[2]), rec_order(c[1], c[3]);
+    rec_order(c[1], c[2]);
+    lanes_merge<1>(c);
+    lanes_merge<2>(c);
+    lanes_merge<4>(c);
+    lanes_merge<8>(c);
+    lanes_merge<16>(c);
+    lanes_merge<32>(c);
 }
 // where position p sits in the 16-byte arrays: threads own four consecutive positions (a stride of 64 bytes), so the positions of
 // a group of four are permuted by the group's number
@@ -384,32 +445,26 @@ __global__ void __launch_bounds__(kSortThreads) flush_sort_kernel(const lsm_entr
 
     if (tid == 0) s.deep = 0;
     // ---- records; age a = entry len - 1 - a of the segment.  Unused positions hold the largest value.
-#pragma unroll
-    for (int i = 0; i < kSortItems; i++) {
-        const uint32_t e = tid + i * kSortThreads;
-        Rec r = {~0ull, ~0ull};
-        if (e < len) {
-            const uint4 q = *reinterpret_cast<const uint4*>(src + e);
-            r.hi = __builtin_bswap64(((uint64_t)q.y << 32) | q.x);
-            r.lo = (__builtin_bswap64(((uint64_t)q.w << 32) | q.z) & ~0xFFFFull) | (len - 1 - e);
-        }
-        rec_store(&s.buf[0][rec_at(e)], r);
-    }
-    __syncthreads();
     const uint32_t o = tid * kSortItems;
     Rec c[kSortItems];
+    {
+        uint4 q[kSortItems];
 #pragma unroll
-    for (int i = 0; i < kSortItems; i++) c[i] = rec_load(&s.buf[0][rec_at(o + i)]);
-    // odd-even merge sort of four (Batcher): five exchanges
-    rec_order(c[0], c[1]), rec_order(c[2], c[3]);
-    rec_order(c[0], c[2]), rec_order(c[1], c[3]);
-    rec_order(c[1], c[2]);
+        for (int i = 0; i < kSortItems; i++) q[i] = *reinterpret_cast<const uint4*>(src + min(o + i, len - 1));
+#pragma unroll
+        for (int i = 0; i < kSortItems; i++) {
+            c[i].hi = __builtin_bswap64(((uint64_t)q[i].y << 32) | q[i].x);
+            c[i].lo = (__builtin_bswap64(((uint64_t)q[i].w << 32) | q[i].z) & ~0xFFFFull) | (len - 1 - (o + i));
+            if (o + i >= len) c[i].hi = c[i].lo = ~0ull;
+        }
+    }
+    wave_sort(c);
 #pragma unroll
     for (int i = 0; i < kSortItems; i++) rec_store(&s.buf[0][rec_at(o + i)], c[i]);
     __syncthreads();
     // ---- merge rounds
     uint32_t cur = 0;
-    for (uint32_t width = kSortItems; width < len; width <<= 1) {
+    for (uint32_t width = kSortItems * kWave; width < len; width <<= 1) {
         const uint4* in = s.buf[cur];
         uint4* dst = s.buf[cur ^ 1];
         const uint32_t sa = o & ~(2 * width - 1), sb = sa + width, d = o - sa;  // both lists are `width` long (padding included)
