@@ -1091,6 +1091,150 @@ __device__ __forceinline__ void tile_pieces(TileHead& s, const RunTable& rt, con
     __builtin_amdgcn_s_setprio(0);
 }
 
+// A tile from its loaded entries to the merged positions, kItems entries a thread (see merge_short_kernel): at[i] = position of entry
+// tid + i * kThreads among the tile's entries in the order (key, run); the bits of the survivors are set in alive[], which is zero, as is
+// deep.  mem: 4 * kCap pieces.  All threads of the workgroup.
+template <int kItems, int kThreads, int kCap, int kHeld>
+__device__ __forceinline__ void short_rank(const TileHead& s, uint4* const mem, uint32_t* const alive, uint32_t& deep, const uint4 (&ent)[kHeld][4],
+                                           const uint32_t (&piece)[kHeld], uint32_t (&at)[kHeld], const uint32_t n, const uint32_t k, const uint32_t flags) {
+    const uint32_t tid = threadIdx.x;
+    uint4* const tails = mem + 2 * kCap;  // by entry: key bytes 16..31
+    uint4* const infos = mem + 3 * kCap;  // by entry: seqno, type | key bytes 14..15 << 8
+    Sur sur[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t e = tid + i * kThreads;
+        at[i] = e;
+        const Key key = key_from_raw(ent[i][0], ent[i][1]);
+        sur[i].hi = key.w[0];
+        sur[i].lo = (key.w[1] & ~0xFFFFull) | e;
+        if (e < n) {
+            sur_store(&mem[e], sur[i]);
+            tails[e] = ent[i][1];
+            infos[e] = make_uint4(ent[i][2].x, ent[i][2].y, (ent[i][2].z & 0xFF) | (ent[i][0].w & 0xFFFF0000u) >> 8, 0);
+        }
+    }
+    __syncthreads();
+    // ---- merge rounds: an entry's place in the merged list is its place in its own list and the number of smaller ones in the
+    //      other list of the pair
+    uint4* in = mem;
+    uint4* dst = mem + kCap;
+    for (uint32_t width = 1; width < k; width <<= 1) {
+        uint32_t lo[kItems], hi[kItems], from[kItems];
+#pragma unroll
+        for (int i = 0; i < kItems; i++) {
+            const uint32_t j = piece[i], first = j & ~(width - 1), other = first ^ width;  // lists of `width` runs
+            const uint32_t begin = s.seg[min(other, k)], end = s.seg[min(other + width, k)];
+            const bool valid = tid + i * kThreads < n;
+            lo[i] = from[i] = begin;
+            hi[i] = valid ? end : begin;
+        }
+        bool go = true;
+        while (go) {
+            go = false;
+#pragma unroll
+            for (int i = 0; i < kItems; i++) {
+                if (lo[i] < hi[i]) {
+                    const uint32_t mid = (lo[i] + hi[i]) >> 1;
+                    const bool less = sur_less(sur_load(&in[mid]), sur[i]);
+                    lo[i] = less ? mid + 1 : lo[i];
+                    hi[i] = less ? hi[i] : mid;
+                    go = go || lo[i] < hi[i];
+                }
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kItems; i++) {
+            const uint32_t below = lo[i] - from[i];
+            const bool right = (piece[i] & width) != 0;  // at[] counts the whole of the other list, which lies before this one
+            at[i] += right ? below - (s.seg[piece[i] & ~(width - 1)] - from[i]) : below;
+            if (tid + i * kThreads < n) sur_store(&dst[at[i]], sur[i]);
+        }
+        __syncthreads();
+        uint4* const t = in;
+        in = dst, dst = t;
+    }
+    // ---- neighbours with the same 14 bytes: the rest of the key orders them, the newest version of a key survives
+    bool win[kItems];
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t e = tid + i * kThreads, p = at[i];
+        win[i] = e < n;
+        if (!win[i]) continue;
+        const Sur me = sur[i];
+        const uint4 my_info = make_uint4(ent[i][2].x, ent[i][2].y, (ent[i][2].z & 0xFF) | (ent[i][0].w & 0xFFFF0000u) >> 8, 0), my_tail = ent[i][1];
+        const uint64_t seq = ((uint64_t)my_info.y << 32) | my_info.x;
+        uint32_t left = 0, right = 0, before = 0;
+        auto meet = [&](const uint32_t other) {
+            const uint4 info = infos[other], tail = tails[other];
+            const bool same = ((info.z ^ my_info.z) >> 8) == 0 && tail.x == my_tail.x && tail.y == my_tail.y && tail.z == my_tail.z && tail.w == my_tail.w;
+            if (same) {
+                const uint64_t its = ((uint64_t)info.y << 32) | info.x;
+                if (its > seq || (its == seq && other < e)) win[i] = false;
+                before += other < e;
+            } else {
+                before += tail_less(info, tail, my_info, my_tail);
+            }
+        };
+        Sur l = sur_load(&in[p > 0 ? p - 1 : 0]), r = sur_load(&in[min(p + 1, n - 1)]);  // both at once: most entries have no such neighbour
+        while (left < p && sur_same_key(l, me) && left <= (uint32_t)kRepairMax) {
+            meet((uint32_t)l.lo & 0xFFFF);
+            left++;
+            l = sur_load(&in[p > left ? p - left - 1 : 0]);
+        }
+        while (p + right + 1 < n && sur_same_key(r, me) && right <= (uint32_t)kRepairMax) {
+            meet((uint32_t)r.lo & 0xFFFF);
+            right++;
+            r = sur_load(&in[min(p + right + 1, n - 1)]);
+        }
+        if (left + right >= (uint32_t)kRepairMax) deep = 1;
+        at[i] = p - left + before;
+        if ((flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) win[i] = false;
+    }
+#pragma unroll
+    for (int i = 0; i < kItems; i++)
+        if (win[i]) atomicOr(&alive[at[i] >> 5], 1u << (at[i] & 31));
+    __syncthreads();
+    if (deep == 0) return;
+    // ---- exact path, as in merge_kernel: binary search over the tile's other pieces with full 32-byte compares
+    __syncthreads();
+    uint4* const heads = mem;  // by entry: key bytes 0..15
+#pragma unroll
+    for (int i = 0; i < kItems; i++)
+        if (tid + i * kThreads < n) heads[tid + i * kThreads] = ent[i][0];
+    if (tid < kCap / 32) alive[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kItems; i++) {
+        const uint32_t e = tid + i * kThreads, j = piece[i];
+        if (e >= n) continue;
+        const Key x = key_from_raw(ent[i][0], ent[i][1]);
+        const uint64_t seq = ((uint64_t)ent[i][2].y << 32) | ent[i][2].x;
+        uint32_t p = e - s.seg[j];
+        bool wins = true;
+        for (uint32_t j2 = 0; j2 < k; j2++) {
+            if (j2 == j) continue;
+            const uint32_t first = s.seg[j2], last = s.seg[j2 + 1];
+            uint32_t lb = first, ub = last;
+            while (lb < ub) {
+                const uint32_t mid = (lb + ub) >> 1;
+                if (entry_key_less(&heads[mid], &tails[mid], x)) lb = mid + 1;
+                else ub = mid;
+            }
+            p += lb - first;
+            if (lb < last && key_equal(key_from_raw(heads[lb], tails[lb]), x)) {
+                const uint64_t other = ((uint64_t)infos[lb].y << 32) | infos[lb].x;
+                if (other > seq || (other == seq && j2 < j)) wins = false;
+                if (j2 < j) p++;
+            }
+        }
+        if (wins && (flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) wins = false;
+        at[i] = p;
+        if (wins) atomicOr(&alive[p >> 5], 1u << (p & 31));
+    }
+    __syncthreads();
+}
+
 // two workgroups per compute unit = four waves per SIMD: at most 128 vector registers.
 // kExtras: what else the output pass does (compiled out otherwise).  1: rewrites value pointers and / or writes the fence
 // index; 2: also writes the filter hash of every survivor's key.
@@ -1112,9 +1256,12 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
         __syncthreads();
     }
 
+    uint32_t* const alive = reinterpret_cast<uint32_t*>(s.rank);  // range form
     if (wave == 0) {
         if (lane == 0) s.inexact = 0;
         tile_pieces<kMode>(s, rt, ws, n_tiles, ma, bounds);
+    } else if (kMode == kModeRange && wave == 1) {
+        alive[lane] = 0;
     }
     __syncthreads();
     const uint64_t tile = s.tile;
@@ -1129,6 +1276,35 @@ __global__ void __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per
     const uint32_t fence_stride = kMode == kModeBatch ? s.fence_stride : fence_stride_arg;
     const auto key_hashes = [&] { return kMode == kModeBatch ? s.key_hashes : ma.key_hashes; };  // read where it is used: no register to spare
     const uint32_t top_step = k > 1 ? 1u << (31 - __builtin_clz(k - 1)) : 0;
+
+    if (kMode == kModeRange && n <= (uint32_t)kMergeThreads) {
+        // ---- a range of no more entries than threads, as nearly all are: one entry per thread, as in merge_short_kernel, and stored from
+        //      registers: 500 ranges of a 4M-entry tree 15.3 -> 11.1 us, 2,000 of a 20M-entry tree 51.6 -> 35.9, one of 50,000 entries the same
+        uint4 ent[1][4];
+        uint32_t piece[1], at[1];
+        const uint32_t e = (uint32_t)tid < n ? tid : 0;
+        piece[0] = piece_of(s.seg, k, top_step, e);
+        const uint4* const src = reinterpret_cast<const uint4*>(s.run[piece[0]] + s.lo[piece[0]] + (e - s.seg[piece[0]]));
+#pragma unroll
+        for (int part = 0; part < 4; part++) {
+            ent[0][part] = make_uint4(0, 0, 0, 0);
+            if ((uint32_t)tid < n) ent[0][part] = load_global_u4(src + part);
+        }
+        short_rank<1, kMergeThreads, kMergeThreads>(s, s.buf[0], alive, s.inexact, ent, piece, at, n, k, flags);
+        constexpr uint32_t kWords = kMergeThreads / 32;
+        const uint32_t bits = (uint32_t)lane < kWords ? alive[lane] : 0, incl = wave_scan_u32(__popc(bits));
+        const uint32_t total = __shfl(incl, kWave - 1, kWave);
+        const uint32_t word = at[0] >> 5, bit = at[0] & 31, b = __shfl(bits, word & (kWords - 1), kWave);
+        const uint32_t slot = __shfl(incl - __popc(bits), word & (kWords - 1), kWave) + __popc(b & ((1u << bit) - 1));
+        const bool failed = s.failed != 0 || total > ma.max_entries;
+        if (tid == 0) ma.counts[tile] = failed ? ~0u : total;
+        if (!failed && (uint32_t)tid < n && ((b >> bit) & 1) != 0) {
+            uint4* const dst = reinterpret_cast<uint4*>(out + tile * (uint64_t)ma.max_entries + slot);
+#pragma unroll
+            for (int part = 0; part < 4; part++) dst[part] = ent[0][part];
+        }
+        return;
+    }
 
     // ---- load: entry e = tid + i * kMergeThreads stays in this thread's registers until it is stored
     // the few instructions of a memory phase should not queue behind the other workgroup's merge arithmetic
@@ -1633,149 +1809,6 @@ __device__ uint64_t lookback_few(uint64_t* status, const uint64_t epoch, const u
     return base;
 }
 
-// The tile from its loaded entries to the merged positions: at[i] = position of entry tid + i * kShortThreads among the tile's
-// entries in the order (key, run); the bits of the survivors are set in s.alive.  All threads of the workgroup.
-template <int kItems>
-__device__ __forceinline__ void short_rank(ShortShared& s, const uint4 (&ent)[kShortItems][4], const uint32_t (&piece)[kShortItems], uint32_t (&at)[kShortItems],
-                                           const uint32_t n, const uint32_t k, const uint32_t flags) {
-    const uint32_t tid = threadIdx.x;
-    uint4* const tails = s.mem + 2 * kTileCap;  // by entry: key bytes 16..31
-    uint4* const infos = s.mem + 3 * kTileCap;  // by entry: seqno, type | key bytes 14..15 << 8
-    Sur sur[kItems];
-#pragma unroll
-    for (int i = 0; i < kItems; i++) {
-        const uint32_t e = tid + i * kShortThreads;
-        at[i] = e;
-        const Key key = key_from_raw(ent[i][0], ent[i][1]);
-        sur[i].hi = key.w[0];
-        sur[i].lo = (key.w[1] & ~0xFFFFull) | e;
-        if (e < n) {
-            sur_store(&s.mem[e], sur[i]);
-            tails[e] = ent[i][1];
-            infos[e] = make_uint4(ent[i][2].x, ent[i][2].y, (ent[i][2].z & 0xFF) | (ent[i][0].w & 0xFFFF0000u) >> 8, 0);
-        }
-    }
-    __syncthreads();
-    // ---- merge rounds: an entry's place in the merged list is its place in its own list and the number of smaller ones in the
-    //      other list of the pair
-    uint4* in = s.mem;
-    uint4* dst = s.mem + kTileCap;
-    for (uint32_t width = 1; width < k; width <<= 1) {
-        uint32_t lo[kItems], hi[kItems], from[kItems];
-#pragma unroll
-        for (int i = 0; i < kItems; i++) {
-            const uint32_t j = piece[i], first = j & ~(width - 1), other = first ^ width;  // lists of `width` runs
-            const uint32_t begin = s.seg[min(other, k)], end = s.seg[min(other + width, k)];
-            const bool valid = tid + i * kShortThreads < n;
-            lo[i] = from[i] = begin;
-            hi[i] = valid ? end : begin;
-        }
-        bool go = true;
-        while (go) {
-            go = false;
-#pragma unroll
-            for (int i = 0; i < kItems; i++) {
-                if (lo[i] < hi[i]) {
-                    const uint32_t mid = (lo[i] + hi[i]) >> 1;
-                    const bool less = sur_less(sur_load(&in[mid]), sur[i]);
-                    lo[i] = less ? mid + 1 : lo[i];
-                    hi[i] = less ? hi[i] : mid;
-                    go = go || lo[i] < hi[i];
-                }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kItems; i++) {
-            const uint32_t below = lo[i] - from[i];
-            const bool right = (piece[i] & width) != 0;  // at[] counts the whole of the other list, which lies before this one
-            at[i] += right ? below - (s.seg[piece[i] & ~(width - 1)] - from[i]) : below;
-            if (tid + i * kShortThreads < n) sur_store(&dst[at[i]], sur[i]);
-        }
-        __syncthreads();
-        uint4* const t = in;
-        in = dst, dst = t;
-    }
-    // ---- neighbours with the same 14 bytes: the rest of the key orders them, the newest version of a key survives
-    bool win[kItems];
-#pragma unroll
-    for (int i = 0; i < kItems; i++) {
-        const uint32_t e = tid + i * kShortThreads, p = at[i];
-        win[i] = e < n;
-        if (!win[i]) continue;
-        const Sur me = sur[i];
-        const uint4 my_info = make_uint4(ent[i][2].x, ent[i][2].y, (ent[i][2].z & 0xFF) | (ent[i][0].w & 0xFFFF0000u) >> 8, 0), my_tail = ent[i][1];
-        const uint64_t seq = ((uint64_t)my_info.y << 32) | my_info.x;
-        uint32_t left = 0, right = 0, before = 0;
-        auto meet = [&](const uint32_t other) {
-            const uint4 info = infos[other], tail = tails[other];
-            const bool same = ((info.z ^ my_info.z) >> 8) == 0 && tail.x == my_tail.x && tail.y == my_tail.y && tail.z == my_tail.z && tail.w == my_tail.w;
-            if (same) {
-                const uint64_t its = ((uint64_t)info.y << 32) | info.x;
-                if (its > seq || (its == seq && other < e)) win[i] = false;
-                before += other < e;
-            } else {
-                before += tail_less(info, tail, my_info, my_tail);
-            }
-        };
-        Sur l = sur_load(&in[p > 0 ? p - 1 : 0]), r = sur_load(&in[min(p + 1, n - 1)]);  // both at once: most entries have no such neighbour
-        while (left < p && sur_same_key(l, me) && left <= (uint32_t)kRepairMax) {
-            meet((uint32_t)l.lo & 0xFFFF);
-            left++;
-            l = sur_load(&in[p > left ? p - left - 1 : 0]);
-        }
-        while (p + right + 1 < n && sur_same_key(r, me) && right <= (uint32_t)kRepairMax) {
-            meet((uint32_t)r.lo & 0xFFFF);
-            right++;
-            r = sur_load(&in[min(p + right + 1, n - 1)]);
-        }
-        if (left + right >= (uint32_t)kRepairMax) s.deep = 1;
-        at[i] = p - left + before;
-        if ((flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) win[i] = false;
-    }
-#pragma unroll
-    for (int i = 0; i < kItems; i++)
-        if (win[i]) atomicOr(&s.alive[at[i] >> 5], 1u << (at[i] & 31));
-    __syncthreads();
-    if (s.deep == 0) return;
-    // ---- exact path, as in merge_kernel: binary search over the tile's other pieces with full 32-byte compares
-    __syncthreads();
-    uint4* const heads = s.mem;  // by entry: key bytes 0..15
-#pragma unroll
-    for (int i = 0; i < kItems; i++)
-        if (tid + i * kShortThreads < n) heads[tid + i * kShortThreads] = ent[i][0];
-    if (tid < kTileCap / 32) s.alive[tid] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < kItems; i++) {
-        const uint32_t e = tid + i * kShortThreads, j = piece[i];
-        if (e >= n) continue;
-        const Key x = key_from_raw(ent[i][0], ent[i][1]);
-        const uint64_t seq = ((uint64_t)ent[i][2].y << 32) | ent[i][2].x;
-        uint32_t p = e - s.seg[j];
-        bool wins = true;
-        for (uint32_t j2 = 0; j2 < k; j2++) {
-            if (j2 == j) continue;
-            const uint32_t first = s.seg[j2], last = s.seg[j2 + 1];
-            uint32_t lb = first, ub = last;
-            while (lb < ub) {
-                const uint32_t mid = (lb + ub) >> 1;
-                if (entry_key_less(&heads[mid], &tails[mid], x)) lb = mid + 1;
-                else ub = mid;
-            }
-            p += lb - first;
-            if (lb < last && key_equal(key_from_raw(heads[lb], tails[lb]), x)) {
-                const uint64_t other = ((uint64_t)infos[lb].y << 32) | infos[lb].x;
-                if (other > seq || (other == seq && j2 < j)) wins = false;
-                if (j2 < j) p++;
-            }
-        }
-        if (wins && (flags & LSM_BOTTOMMOST) && (ent[i][2].z & 0xFF) == LSM_TOMBSTONE) wins = false;
-        at[i] = p;
-        if (wins) atomicOr(&s.alive[p >> 5], 1u << (p & 31));
-    }
-    __syncthreads();
-}
-
 // From the tile's pieces on; s.alive and s.deep are zero.
 template <int kExtras>
 __device__ __forceinline__ void short_tile(ShortShared& s, uint64_t* hash_stage, const uint64_t* remap_base, const uint32_t remap_files) {
@@ -1802,8 +1835,8 @@ __device__ __forceinline__ void short_tile(ShortShared& s, uint64_t* hash_stage,
                 if (tid + i * kShortThreads < n) ent[i][part] = load_global_u4(src[i] + part);
             }
     }
-    if (n <= (uint32_t)kShortThreads) short_rank<1>(s, ent, piece, at, n, k, flags);
-    else short_rank<kShortItems>(s, ent, piece, at, n, k, flags);
+    if (n <= (uint32_t)kShortThreads) short_rank<1, kShortThreads, kTileCap>(s, s.mem, s.alive, s.deep, ent, piece, at, n, k, flags);
+    else short_rank<kShortItems, kShortThreads, kTileCap>(s, s.mem, s.alive, s.deep, ent, piece, at, n, k, flags);
 
     // ---- survivors before each position, by every wave for itself; s.alive is complete
     const uint32_t bits = s.alive[lane], incl = wave_scan_u32(__popc(bits));

@@ -224,6 +224,27 @@ def test_keys_that_tie_in_their_first_14_bytes(g, oracle, n_runs, n_heads, long_
         _check_compact(g, oracle, runs, flags)
 
 
+def _tied_runs(oracle, rs, k, group, total, seqnos):
+    """k runs of about `total` entries in all; keys come in groups of `group` that share 14 bytes and differ behind, and are in one to three runs."""
+    runs = []
+    for j in range(k):
+        code = np.unique(rs.randint(0, max(4, int(total * 0.8)), size=total // k))
+        head, tail = code // group, code % group
+        a = np.zeros((code.size, 64), dtype=np.uint8)
+        a[:, :8] = (head.astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15) >> np.uint64(1)).astype(">u8").view(np.uint8).reshape(-1, 8)
+        spot = np.array([14, 20, 30])[head % 3]
+        a[np.arange(code.size), spot] = tail >> 8
+        a[np.arange(code.size), spot + 1] = tail & 255
+        words = a[:, :32].copy().view(">u8")
+        a = a[np.lexsort((words[:, 3], words[:, 2], words[:, 1], words[:, 0]))]
+        rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
+        rec["seqno"] = rs.randint(0, seqnos, size=code.size)
+        rec["type"] = (rs.rand(code.size) < 0.1).astype(np.uint8)
+        rec["vptr"] = np.arange(code.size) + (j << 40)
+        runs.append(a)
+    return runs
+
+
 @pytest.mark.parametrize("k", [2, 5, 17])
 @pytest.mark.parametrize("group", [2, 33, 34, 600])  # members of a prefix-tie group in all runs together, about: settled by neighbours, or not
 def test_prefix_ties_on_both_sides_of_the_short_form(g, oracle, k, group):
@@ -231,23 +252,35 @@ def test_prefix_ties_on_both_sides_of_the_short_form(g, oracle, k, group):
     rs = np.random.RandomState(100 * k + group)
     for total in (1000, 1100, 1900, 60_000, 300_000, 256 * (2048 - k) - 1, 256 * (2048 - k) + 3000):
         print("prefix ties, short form", k, group, total, flush=True)
-        runs = []
-        for j in range(k):
-            code = np.unique(rs.randint(0, max(4, int(total * 0.8)), size=total // k))  # a key is in one to three of the runs
-            head, tail = code // group, code % group
-            a = np.zeros((code.size, 64), dtype=np.uint8)
-            a[:, :8] = (head.astype(np.uint64) * np.uint64(0x9E3779B97F4A7C15) >> np.uint64(1)).astype(">u8").view(np.uint8).reshape(-1, 8)
-            spot = np.array([14, 20, 30])[head % 3]
-            a[np.arange(code.size), spot] = tail >> 8
-            a[np.arange(code.size), spot + 1] = tail & 255
-            words = a[:, :32].copy().view(">u8")
-            a = a[np.lexsort((words[:, 3], words[:, 2], words[:, 1], words[:, 0]))]
-            rec = a.view(oracle.ENTRY_DTYPE).reshape(-1)
-            rec["seqno"] = rs.randint(0, 1 << 40, size=code.size) if total & 1 else rs.randint(0, 3, size=code.size)
-            rec["type"] = (rs.rand(code.size) < 0.1).astype(np.uint8)
-            rec["vptr"] = np.arange(code.size) + (j << 40)
-            runs.append(to_dev(a))
+        runs = [to_dev(r) for r in _tied_runs(oracle, rs, k, group, total, 1 << 40 if total & 1 else 3)]
         _check_compact(g, oracle, runs, int(group & 1))
+
+
+@pytest.mark.parametrize("k", [1, 3, 17])
+@pytest.mark.parametrize("group", [1, 40, 600])
+def test_ranges_of_about_as_many_entries_as_threads(g, oracle, k, group):
+    """Key ranges that hold 1, 505 .. 520, 1,000 and 1,500 entries of the runs: one entry per thread up to 512; keys that share 14 bytes."""
+    print("ranges around 512 entries", k, group, flush=True)
+    rs = np.random.RandomState(k + group)
+    runs = _tied_runs(oracle, rs, k, group, 4000, 4)
+    keys = sorted(bytes(e[:32]) for r in runs for e in r)  # of all runs, in order: range i holds the first n[i] of them, and other versions of the last
+    n = [1, *range(505, 521), 1000, 1500]
+    hi = np.frombuffer(b"".join(keys[i] for i in n), dtype=np.uint8).reshape(-1, 32)
+    lo = np.zeros_like(hi)
+    tree = build_tree(g, [to_dev(r) for r in runs])
+    as_key = lambda x: torch.from_numpy(x.copy().view(np.int64).reshape(-1, 4)).to(dev())  # noqa: E731
+    for slot in (1500, 400):
+        entries, counts = g.lsm_range_scan(tree, as_key(lo), as_key(hi), slot)
+        torch.cuda.synchronize()
+        for i, end in enumerate(hi):
+            cut = [np.ascontiguousarray(r[[bytes(e[:32]) < bytes(end) for e in r]]) for r in runs]
+            want = oracle.compact(cut, 1)
+            count = int(counts[i].item()) & 0xFFFFFFFF
+            if want.shape[0] > slot:
+                assert count == 0xFFFFFFFF
+                continue
+            assert count == want.shape[0]
+            assert np.array_equal(as_bytes(entries[i, :count]).reshape(-1, 64), want)
 
 
 @pytest.mark.parametrize("separate", [False, True])
