@@ -22,13 +22,14 @@
 
 namespace lsm {
 
-// One workgroup per range.  The range is built 1,024 buckets (64 KiB) at a time in LDS and each part leaves with
+// A workgroup per 1,024 buckets (64 KiB) of a range (blockIdx.y: which): they are assembled in LDS and leave with
 // contiguous 16-byte stores: scattered 2- and 4-byte stores straight into the table cost 4.6 bytes of HBM writes per byte
-// of table.  Every part reads the range's hashes again (they stay in the caches).  kScan: the hashes are not sorted
+// of table.  Every part reads the records of the whole range (they
+// stay in the caches); records of 8 bytes instead of 16, 2.7M keys 22.5 -> 16.0 us.  kScan: the hashes are not sorted
 // (`hashes` are all n of them, totals is not used), and the range picks its own.
 constexpr uint32_t kFillBuckets = 1024;
 template <bool kScan>
-__global__ void __launch_bounds__(kPartThreads) index_fill_kernel(const uint64_t* hashes, const uint4* ranged, uint64_t n, const uint32_t* totals,
+__global__ void __launch_bounds__(kPartThreads) index_fill_kernel(const uint64_t* hashes, const uint64_t* ranged, uint64_t n, const uint32_t* totals,
                                                                  uint32_t n_buckets, uint32_t unit_log, uint4* table) {
     __shared__ uint4 part[kFillBuckets * 4];  // the buckets of this pass
     __shared__ uint32_t count[kFillBuckets];
@@ -38,35 +39,39 @@ __global__ void __launch_bounds__(kPartThreads) index_fill_kernel(const uint64_t
         begin = range_begin(totals, blockIdx.x);
         end = begin + totals[blockIdx.x];
     }
-    for (uint32_t first_bucket = range_first; first_bucket < range_last; first_bucket += kFillBuckets) {
-        const uint32_t buckets = min(range_last - first_bucket, kFillBuckets);
-        // every bucket starts empty: tag fields 0, positions all ones, the rest 0
-        for (uint32_t i = threadIdx.x; i < buckets * 4; i += kPartThreads) {
-            const uint32_t fill = ((i & 3) == 1 || (i & 3) == 2) ? kIndexNoEntry : 0u;
-            part[i] = make_uint4(fill, fill, fill, fill);
-        }
-        for (uint32_t b = threadIdx.x; b < buckets; b += kPartThreads) count[b] = 0;
-        __syncthreads();
-        uint16_t* tags = reinterpret_cast<uint16_t*>(part);
-        uint32_t* words = reinterpret_cast<uint32_t*>(part);
-        auto put = [&](uint64_t h, uint32_t position) {
-            const uint32_t b = bloom_block(h, n_buckets) - first_bucket;  // wraps for the buckets before this pass
-            if (b >= buckets) return;
-            const uint32_t k = atomicAdd(&count[b], 1u);
-            if (k >= kIndexSlots) return;  // a crowded bucket keeps the first eight keys that arrive
-            tags[b * 32 + k] = (uint16_t)(h & kIndexTagMask);
-            words[b * 16 + 4 + k] = position;
-        };
-        if (kScan) part_for_each(begin, end, [&](uint64_t i) { return hashes[i]; }, [&](uint64_t i, uint64_t h) { put(h, (uint32_t)i); });
-        else part_for_each(begin, end, [&](uint64_t i) { return ranged[i]; }, [&](uint64_t, const uint4 rec) { put(((uint64_t)rec.y << 32) | rec.x, rec.z); });
-        __syncthreads();
-        for (uint32_t b = threadIdx.x; b < buckets; b += kPartThreads)
-            if (count[b] > kIndexSlots) tags[b * 32] |= 0x8000u;  // crowded
-        __syncthreads();
-        uint4* dst = table + (uint64_t)first_bucket * 4;
-        for (uint32_t i = threadIdx.x; i < buckets * 4; i += kPartThreads) dst[i] = part[i];
-        __syncthreads();  // the LDS arrays are reused by the next pass
+    const uint32_t first_bucket = range_first + blockIdx.y * kFillBuckets;
+    if (first_bucket >= range_last) return;
+    const uint32_t buckets = min(range_last - first_bucket, kFillBuckets);
+    // every bucket starts empty: tag fields 0, positions all ones, the rest 0
+    for (uint32_t i = threadIdx.x; i < buckets * 4; i += kPartThreads) {
+        const uint32_t fill = ((i & 3) == 1 || (i & 3) == 2) ? kIndexNoEntry : 0u;
+        part[i] = make_uint4(fill, fill, fill, fill);
     }
+    for (uint32_t b = threadIdx.x; b < buckets; b += kPartThreads) count[b] = 0;
+    __syncthreads();
+    uint16_t* tags = reinterpret_cast<uint16_t*>(part);
+    uint32_t* words = reinterpret_cast<uint32_t*>(part);
+    auto put = [&](uint32_t bucket, uint32_t tag, uint32_t position) {
+        const uint32_t b = bucket - first_bucket;  // wraps for the buckets before these
+        if (b >= buckets) return;
+        const uint32_t k = atomicAdd(&count[b], 1u);
+        if (k >= kIndexSlots) return;  // a crowded bucket keeps the first eight keys that arrive
+        tags[b * 32 + k] = (uint16_t)tag;
+        words[b * 16 + 4 + k] = position;
+    };
+    static_assert(kIndexTagMask == (1u << kPosTagBits) - 1, "a record holds the tag");
+    if (kScan)
+        part_for_each(begin, end, [&](uint64_t i) { return hashes[i]; },
+                      [&](uint64_t i, uint64_t h) { put(bloom_block(h, n_buckets), (uint32_t)h & kIndexTagMask, (uint32_t)i); });
+    else
+        part_for_each(begin, end, [&](uint64_t i) { return ranged[i]; },
+                      [&](uint64_t, uint64_t rec) { put(range_first + ((uint32_t)rec >> kPosTagBits), (uint32_t)rec & kIndexTagMask, (uint32_t)(rec >> 32)); });
+    __syncthreads();
+    for (uint32_t b = threadIdx.x; b < buckets; b += kPartThreads)
+        if (count[b] > kIndexSlots) tags[b * 32] |= 0x8000u;  // crowded
+    __syncthreads();
+    uint4* dst = table + (uint64_t)first_bucket * 4;
+    for (uint32_t i = threadIdx.x; i < buckets * 4; i += kPartThreads) dst[i] = part[i];
 }
 
 }  // namespace lsm
@@ -90,13 +95,14 @@ extern "C" int lsm_build_hash_index(const uint64_t* hashes, uint64_t n, void* ta
     hipStream_t stream = static_cast<hipStream_t>(stream_v);
     launch_range_partition<true>(hashes, n, n_buckets, l, workspace, stream);
     char* base = static_cast<char*>(workspace);
-    const uint4* ranged = reinterpret_cast<const uint4*>(base + l.ranged);
+    const uint64_t* ranged = reinterpret_cast<const uint64_t*>(base + l.ranged);
     const uint32_t* totals = reinterpret_cast<const uint32_t*>(base + l.totals);
+    const uint32_t parts = ((1u << l.unit_log) + kFillBuckets - 1) / kFillBuckets;
     if (l.scan)
-        hipLaunchKernelGGL(index_fill_kernel<true>, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, hashes, ranged, n, totals, (uint32_t)n_buckets, l.unit_log,
+        hipLaunchKernelGGL(index_fill_kernel<true>, dim3(l.n_ranges, parts), dim3(kPartThreads), 0, stream, hashes, ranged, n, totals, (uint32_t)n_buckets, l.unit_log,
                            static_cast<uint4*>(table_out));
     else
-        hipLaunchKernelGGL(index_fill_kernel<false>, dim3(l.n_ranges), dim3(kPartThreads), 0, stream, hashes, ranged, n, totals, (uint32_t)n_buckets,
+        hipLaunchKernelGGL(index_fill_kernel<false>, dim3(l.n_ranges, parts), dim3(kPartThreads), 0, stream, hashes, ranged, n, totals, (uint32_t)n_buckets,
                            l.unit_log, static_cast<uint4*>(table_out));
     return hipGetLastError() == hipSuccess ? LSM_OK : LSM_ERR_HIP;
 }
