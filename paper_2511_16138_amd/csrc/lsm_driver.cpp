@@ -124,17 +124,19 @@ struct lsm_driver {
     bool searched = false;
     double last_mix[4] = {0, 0, 0, 0};
     DevicePool pool;
-    void* workspace = nullptr;
-    size_t workspace_bytes = 0;
+    // Memory of one compaction after the other: status words for merges in one launch (see lsm::ClearSpan), the compaction's workspace, scratch
+    // memory for filters.
+    struct Workspace {
+        char* p = nullptr;
+        size_t bytes = 0;
+        uint32_t epoch = 0;  // of the next merge; 0: the status words are not zero yet
+    };
+    Workspace workspace, batch_workspace;  // of compactions on their own, and of batches (lsm_driver_flush_many)
     uint64_t* n_host = nullptr;  // pinned: the kernels write a compaction's count here
     uint64_t* stats_host = nullptr;  // pinned: what a probe batch found, and a ticket that says which batch
     uint64_t tickets = 0;
     uint64_t* counts_host = nullptr;  // pinned: the counts of a batch of compactions (lsm_driver_flush_many)
     size_t counts_host_count = 0;
-    void* batch_workspace = nullptr;
-    size_t batch_workspace_bytes = 0;
-    uint64_t* status = nullptr;  // status words for merges in one launch (see lsm::ClearSpan)
-    uint32_t epoch = 0;          // of the next merge; 0: the words are not zero yet
 
     void record(uint32_t kind, uint32_t level, uint32_t a, uint32_t b, uint64_t n_in, uint64_t n_out) {
         lsm_driver_event_t e;
@@ -283,16 +285,27 @@ struct lsm_driver {
         return LSM_OK;
     }
 
-    // The driver's status words for one call, and what the call has made of them: from the first that has zeroed them on, every call has
-    // an epoch of its own, until these are used up or a call has failed.
-    int lend_status(lsm::ClearSpan* clear) {
-        if (status == nullptr) status = static_cast<uint64_t*>(pool.take(lsm::kShortTiles * sizeof(uint64_t)));
-        clear->status = status, clear->epoch = epoch, clear->status_zeroed = false;
-        return status != nullptr ? LSM_OK : LSM_ERR_HIP;
+    // The workspace for one call, with `need` bytes behind the status words.  It starts with room for the first levels, so that a young tree
+    // does not grow it time and again: an allocation takes as long as several flushes.
+    static constexpr size_t kStatusBytes = lsm::kShortTiles * sizeof(uint64_t), kLeastWorkspace = size_t(2) << 20;
+    int reserve(Workspace& w, size_t need) {
+        if (kStatusBytes + need <= w.bytes) return LSM_OK;
+        pool.give(w.p);
+        w = Workspace();
+        const size_t bytes = kStatusBytes + need < kLeastWorkspace / 2 ? kLeastWorkspace : 2 * (kStatusBytes + need);
+        w.p = static_cast<char*>(pool.take(bytes));
+        if (w.p == nullptr) return LSM_ERR_HIP;
+        w.bytes = bytes;
+        return LSM_OK;
     }
-    void status_used(const lsm::ClearSpan& clear, int rc) {
-        const bool known = rc == LSM_OK && (epoch != 0 || clear.status_zeroed);
-        epoch = known && epoch + 1 < lsm::kStEpochs ? epoch + 1 : 0;
+    // Its status words for the call, and what the call has made of them: from the first that has zeroed them on, every call has
+    // an epoch of its own, until these are used up or a call has failed.
+    static void lend_status(const Workspace& w, lsm::ClearSpan* clear) {
+        clear->status = reinterpret_cast<uint64_t*>(w.p), clear->epoch = w.epoch, clear->status_zeroed = false;
+    }
+    static void status_used(Workspace& w, const lsm::ClearSpan& clear, int rc) {
+        const bool known = rc == LSM_OK && (w.epoch != 0 || clear.status_zeroed);
+        w.epoch = known && w.epoch + 1 < lsm::kStEpochs ? w.epoch + 1 : 0;
     }
 
     // A merged run whose filter has been built by the call that merged it has every structure it is to get (what holds for the
@@ -452,23 +465,16 @@ struct lsm_driver {
             return rc;
         };
         if (entries == nullptr || fences == nullptr || take_filter(*merged, total, level, &clear, &scratch_bytes) != LSM_OK) return fails(LSM_ERR_HIP);
-        const size_t own = lsm_compact_workspace_bytes(lens, k), need = own + scratch_bytes;  // (a multiple of 256 bytes)
-        if (need > workspace_bytes) {
-            pool.give(workspace);
-            workspace_bytes = 2 * need;
-            workspace = pool.take(workspace_bytes);
-            if (workspace == nullptr) {
-                workspace_bytes = 0;
-                return fails(LSM_ERR_HIP);
-            }
-        }
-        if (scratch_bytes != 0) clear.p = static_cast<char*>(workspace) + own;
-        if (lend_status(&clear) != LSM_OK) return fails(LSM_ERR_HIP);
+        const size_t own = lsm_compact_workspace_bytes(lens, k);  // a multiple of 256 bytes
+        if (reserve(workspace, own + scratch_bytes) != LSM_OK) return fails(LSM_ERR_HIP);
+        char* const room_at = workspace.p + kStatusBytes;
+        if (scratch_bytes != 0) clear.p = room_at + own;
+        lend_status(workspace, &clear);
         const lsm_out_t out{entries, room, n_host, fences, cfg.fence_stride, nullptr};
         *static_cast<volatile uint64_t*>(n_host) = kCountUnset;
-        int rc = lsm::compact_clearing(runs, k, flags, &out, workspace, own, clear, &merged->bloom_clear, stream);
+        int rc = lsm::compact_clearing(runs, k, flags, &out, room_at, own, clear, &merged->bloom_clear, stream);
         if (clear.filter != nullptr) merged->bloom_clear = false;
-        status_used(clear, rc);
+        status_used(workspace, clear, rc);
         // an error may be that of the filter's launch, or of an earlier call, with the merge under way: its count must not meet the next one's
         if (rc != LSM_OK) (void)wait();
         if (rc == LSM_OK) rc = watch_count(n_host);
@@ -781,24 +787,19 @@ extern "C" int lsm_driver_flush_many(lsm_driver_t* const* drivers, const lsm_ent
         if (own == 0) rc = LSM_ERR_BAD_ARG;
         size_t need = own;
         for (size_t bytes : scratch) need += bytes;
-        if (rc == LSM_OK && need > first->batch_workspace_bytes) {
-            first->pool.give(first->batch_workspace);
-            first->batch_workspace_bytes = 2 * need;
-            first->batch_workspace = first->pool.take(first->batch_workspace_bytes);
-            if (first->batch_workspace == nullptr) first->batch_workspace_bytes = 0, rc = LSM_ERR_HIP;
-        }
+        lsm_driver::Workspace& shared = first->batch_workspace;
+        if (rc == LSM_OK) rc = first->reserve(shared, need);
         if (rc == LSM_OK) {
-            char* at = static_cast<char*>(first->batch_workspace) + own;
+            char* const room_at = shared.p + lsm_driver::kStatusBytes;
+            char* at = room_at + own;
             for (uint32_t j = 0; j < n_jobs; j++) {
                 if (clear[j].filter == nullptr) continue;
                 clear[j].p = at;
                 at += scratch[j];
             }
-            rc = first->lend_status(&clear[0]);
-        }
-        if (rc == LSM_OK) {
-            rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, first->batch_workspace, own, clear.data(), first->stream);
-            first->status_used(clear[0], rc);
+            lsm_driver::lend_status(shared, &clear[0]);
+            rc = lsm::compact_batch_clearing(jobs.data(), n_jobs, room_at, own, clear.data(), first->stream);
+            lsm_driver::status_used(shared, clear[0], rc);
             // an error may be that of an earlier call, with this launch under way: its counts must not meet the next batch's
             if (rc != LSM_OK) (void)first->wait();
         }
