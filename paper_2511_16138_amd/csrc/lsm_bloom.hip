@@ -4,6 +4,7 @@
 //   bloom_small_kernel    short runs: shares of the keys in LDS, one launch where the memory is zero or one share is all
 //   bloom_insert_kernel   longer ones from the entries: one thread per key, two 64-bit atomics at most
 //   bloom_fill_kernel     from the keys' hashes, sorted by range of blocks: built in LDS, written once
+//   bloom_scatter_kernel, bloom_ranges_kernel   the same right behind a merge, lengths on the device, several runs per launch
 #include <hip/hip_runtime.h>
 
 #include <type_traits>

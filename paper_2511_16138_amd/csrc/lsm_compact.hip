@@ -13,8 +13,9 @@
 //                     Inputs of up to 512 tiles take sample keys as boundaries instead of exact
 //                     ranks (partition_ranked_kernel: tile sizes vary, within the capacity).
 //                     Larger ones search the runs directly, one wave per boundary
-//                     (partition_kernel, partition_many_kernel), and from 2,048 to 10,240 tiles on
-//                     (the fewer runs, the later) first bracket every boundary, a group of lanes each, on a copy of every
+//                     (partition_kernel, partition_many_kernel), most of them between rows that are ranked
+//                     first (partition_rows_kernel, partition_between_kernel).  The largest first bracket every
+//                     boundary, a group of lanes each, on a copy of every
 //                     32nd key (sample_kernel, sample_rank_kernel, sample_fine_kernel) and search
 //                     the runs only inside the brackets (bracket_partition_kernel).
 //   merge_short_kernel  inputs of up to a tile per compute unit (below: what it does differently).

@@ -8,7 +8,8 @@
 // A flush is a chain of small kernels whose lengths the host has to learn one by one (it decides by the number of entries a
 // merge left), so what counts is the number of launches and how the host learns a count.  It watches the word in pinned
 // memory that the merge writes: launch to count is 6 us where a stream synchronisation takes 11 (it enqueues a marker and
-// waits for that).  A merge zeroes the memory of the filter in its partition launch, so that the filter is one launch; where
+// waits for that).  A merge of two runs is one launch, on status words that the driver keeps.  A merge zeroes the memory of the filter on
+// the way (a long filter's is built from the keys' hashes, which the merge writes), so that the filter is one launch; where
 // the merged run is certain to stay at its level, whatever its length, that launch follows the merge at once and finds the
 // length on the device, so that the GPU works on while the host sees the count and sets out on the next flush (96 flushes 3.06 -> 2.71 ms).
 // A flushed run that comes to rest is copied, fenced and has its filter zeroed in one launch.  (With the filters on a second stream, every cascade waited for that stream before
