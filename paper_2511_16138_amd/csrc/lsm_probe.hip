@@ -37,9 +37,9 @@ struct TreeTable {
 constexpr int kProbeThreads = 512;       // threads of a workgroup; kProbeThreadsFew: see threads_for
 constexpr int kProbeThreadsFew = 256;
 constexpr int kProbeWays = 3;     // fan-out of a search step in global memory (measured: 2: 0.072 ms per batch, 3: 0.067, 4: 0.069, 6: 0.074, 8: 0.080)
-// Rows of hits are stored nontemporally: most of a row is zeros, 4,096 rows of 256 are 16.8 MB, and they would take the place of fences,
+// Large batches (pooled, or one wave per request) store their rows of hits nontemporally: most of a row is zeros, 4,096 rows of 256 are 16.8 MB, and they would take the place of fences,
 // filters and entries in the L2s.  4,096 requests on 60M entries with filters 50.0 -> 46.5 us, with indices as well 38.4 -> 35.0, on 1M
-// 36.7 -> 36.0; up to 1,024 requests the same.  (Zeros behind the admitted keys stored before the lookups: no gain.)
+// 36.7 -> 36.0; 146 requests on 0.7M entries 12.6 -> 13.1, as their kernel ends with the stores' way to memory.  (Zeros behind the admitted keys stored before the lookups: no gain.)
 constexpr int kTopSlots = 1024;  // top-level fence keys held in LDS per workgroup (32 KB)
 
 template <bool kTop>
@@ -361,7 +361,10 @@ __global__ void __launch_bounds__(kThreads) probe_kernel(TreeTable tree, const u
                 done = true;
             }
             if (j >= result) h = make_uint4(0, 0, 0, 0);
-            if (req < n_req && j < max_blocks) store_streaming_u4(&hrow[j], h);
+            if (req < n_req && j < max_blocks) {
+                if constexpr (kSpread == 1) store_streaming_u4(&hrow[j], h);
+                else hrow[j] = h;
+            }
         }
         if (lane == 0 && wave % kSpread == 0 && req < n_req) hit_len[req] = result;
     }
