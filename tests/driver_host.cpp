@@ -30,6 +30,7 @@ int64_t host_malloc_in = 0;   // device memory runs out
 int64_t host_kernel_in = 0;   // a kernel call is refused, nothing was launched
 int64_t host_late_in = 0;     // a kernel call reports an error although its work is done
 uint64_t host_mallocs = 0, host_kernels = 0;
+uint64_t host_bytes = 0, host_largest = 0;  // of device memory: all that was asked for, and at once
 uint32_t host_pinned_flags = ~0u;   // flags that every pinned allocation was made with
 uint64_t host_dirty_filters = 0;    // filters built on memory that was promised to be zero and was not
 int64_t host_slow_stats = 0;        // what a probe batch found is written when the stream is next asked or waited for, no earlier
@@ -37,13 +38,15 @@ int64_t host_slow_merges = 0;       // the same for merges and sorted write buff
 
 void host_reset() {
     host_malloc_in = host_kernel_in = host_late_in = host_slow_stats = host_slow_merges = 0;
-    host_mallocs = host_kernels = host_dirty_filters = 0;
+    host_mallocs = host_kernels = host_dirty_filters = host_bytes = host_largest = 0;
     host_pinned_flags = ~0u;
 }
 
 // ---------------------------------------------------------------------------------------------------- HIP runtime
 hipError_t hipMalloc(void** p, size_t bytes) {
     host_mallocs++;
+    host_bytes += bytes;
+    host_largest = std::max<uint64_t>(host_largest, bytes);
     if (host_malloc_in > 0 && --host_malloc_in == 0) return hipErrorOutOfMemory;
     *p = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
     std::memset(*p, 0xAB, (bytes + 255) / 256 * 256);

@@ -295,3 +295,18 @@ def test_words_the_host_watches_are_in_coherent_memory(host, knobs):
     assert probe(host, tree, [0])[0] == 0
     assert knobs.read("pinned_flags", C.c_uint32) & 0x40000000  # hipHostMallocCoherent, in every allocation
     tree.close()
+
+
+@pytest.mark.parametrize("trees", [1, 2])
+def test_a_small_tree_takes_little_memory(host, knobs, trees):
+    """The first flushes of new trees with a buffer of 100 entries: alone and in a batch, no block is as large as those that the runtime asks
+    the kernel driver for one by one (2 MB), and all of them together are less than that."""
+    new = [Tree(host, T=10) for _ in range(trees)]
+    for step in range(8):
+        runs = [run_of(range(7 * step + j, 7 * step + j + 90), step) for j in range(trees)]
+        assert flush_many(host, new, runs) == 0
+        assert all(host.lsm_driver_flush(t.h, r.ctypes.data, len(r)) == 0 for t, r in zip(new, runs))
+    assert 0 < knobs.read("largest") <= 512 << 10
+    assert knobs.read("bytes") < 2 << 20
+    for t in new:
+        t.close()
