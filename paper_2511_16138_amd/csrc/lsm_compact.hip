@@ -634,6 +634,15 @@ __global__ void __launch_bounds__(kTwoThreads) partition_two_kernel(RunTable rt,
     ws.splits[b * 2 + 1] = ib;
 }
 
+// one run (a level that is rewritten without its tombstones): nothing to search.  Whole calls, us, on copied samples / a wave per boundary / so:
+// 5M entries 200 / 164 / 136, 20M 595 / 618 / 518; 1M, where a wave per boundary was the rule, 39.8 / 35.1.
+template <bool kInit>
+__global__ void __launch_bounds__(kTwoThreads) partition_one_kernel(RunTable rt, Workspace ws, uint64_t n_tiles) {
+    partition_init<kInit>(rt, ws, n_tiles);
+    const uint64_t b = (uint64_t)blockIdx.x * kTwoThreads + threadIdx.x + 1, at = b * ws.spacing, n = run_len(rt, 0);
+    if (b < n_tiles) ws.splits[b] = at < n ? at : n;
+}
+
 // other run counts: one wave per boundary
 template <bool kInit, int kPerLane, bool kMany>
 __global__ void __launch_bounds__(kWave) partition_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, int group_log) {
@@ -2212,10 +2221,10 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     const uint64_t n_tiles = ws.n_tiles;
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
-    // two runs: bisection on the merge path at any size
+    // one run and two (bisection on the merge path): at any size
     const bool rows = n_runs > 2 && n_runs <= kFewRuns && ws.stride == 0 && rt.n_dev == nullptr && total * n_runs < (n_runs <= 16 ? kRowsPieces : ~0ull) &&
                       (n_runs <= 16 || n_tiles < kSampledMinTiles) && n_tiles >= (n_runs <= 4 ? kRowsTiles : 2);
-    const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs == 2 || rows);
+    const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs <= 2 || rows);
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
     auto build_filter = [&](const ClearSpan& span) {  // right behind the merge, if it is asked for
         if (ws.clear_n == 0 || span.filter_bits == 0) return (int)LSM_OK;
@@ -2279,11 +2288,13 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
             const dim3 waves((uint32_t)(n_tiles - 1));
             auto launch = [&](auto init) {
                 constexpr bool kInit = decltype(init)::value;
-                if (n_runs == 2 && n_tiles <= kTwoWaves)
+                const dim3 lanes((uint32_t)((n_tiles - 1 + kTwoThreads - 1) / kTwoThreads));
+                if (n_runs == 1)
+                    hipLaunchKernelGGL(partition_one_kernel<kInit>, lanes, dim3(kTwoThreads), 0, stream, rt, ws, n_tiles);
+                else if (n_runs == 2 && n_tiles <= kTwoWaves)
                     hipLaunchKernelGGL(partition_two_wave_kernel<kInit>, waves, dim3(kWave), 0, stream, rt, ws, n_tiles);
                 else if (n_runs == 2)
-                    hipLaunchKernelGGL(partition_two_kernel<kInit>, dim3((uint32_t)((n_tiles - 1 + kTwoThreads - 1) / kTwoThreads)), dim3(kTwoThreads), 0,
-                                       stream, rt, ws, n_tiles);
+                    hipLaunchKernelGGL(partition_two_kernel<kInit>, lanes, dim3(kTwoThreads), 0, stream, rt, ws, n_tiles);
                 else if (ws.stride != 0)
                     hipLaunchKernelGGL(partition_ranked_kernel<kInit>, dim3(ws.samples), dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (rows) {

@@ -3,6 +3,8 @@
 Sizes here are ones the checker finishes in seconds; they still span many tiles (a tile is
 about a thousand entries) and ragged tails.  Full-size cases are in test_gpu_fullsize.py.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -514,6 +516,31 @@ def test_searched_directly_or_on_samples(g, oracle, k, tiles, shape):
         _check_compact(g, oracle, runs, int(total & 1))
         del runs
         torch.cuda.empty_cache()
+
+
+def _launches(call):
+    """Kernels (and other work) that a call puts on the stream: the nodes of a graph that records it."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t(0)
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+@pytest.mark.parametrize("tiles", [2, 256, 257, 2047, 2048, 10240, 10241])
+def test_one_run_is_cut_without_a_search(g, oracle, tiles):
+    """One run of any length: the boundaries are multiples of the tile, one launch before the merge's."""
+    print("one run", tiles, flush=True)
+    rs = np.random.RandomState(tiles)
+    full = 2047
+    for n in ((tiles - 1) * full + 1, tiles * full):
+        run = _runs_of(oracle, rs, [n], 2 * n)[0]
+        _check_compact(g, oracle, [run], tiles & 1)
+        out, n_out = torch.empty_like(run), torch.zeros(1, dtype=torch.int64, device=dev())
+        workspace = torch.empty(g.lsm_compact_workspace_bytes([n]), dtype=torch.uint8, device=dev())
+        assert _launches(lambda: g.lsm_compact([run], 1, out, n_out, workspace)) == 2
 
 
 @pytest.mark.parametrize("k", [1, 2, 3, 16, 64])
