@@ -12,10 +12,10 @@
 //                     nominal size.  Two runs: bisection on the merge path (partition_two_*).
 //                     Inputs of up to 512 tiles take sample keys as boundaries instead of exact
 //                     ranks (partition_ranked_kernel: tile sizes vary, within the capacity).
-//                     Larger ones search the runs directly, one wave per boundary
-//                     (partition_kernel, partition_many_kernel), most of them between rows that are ranked
-//                     first (partition_rows_kernel, partition_between_kernel).  The largest first bracket every
-//                     boundary, a group of lanes each, on a copy of every
+//                     Larger ones search the runs, one wave per boundary (partition_kernel,
+//                     partition_many_kernel), most of them between rows that are ranked first
+//                     (partition_rows_kernel, partition_between_kernel).  Long inputs of more than 16 runs
+//                     first bracket every boundary, a group of lanes each, on a copy of every
 //                     32nd key (sample_kernel, sample_rank_kernel, sample_fine_kernel) and search
 //                     the runs only inside the brackets (bracket_partition_kernel).
 //   merge_short_kernel  inputs of up to a tile per compute unit (below: what it does differently).
@@ -87,24 +87,30 @@ constexpr uint32_t kMinStride = 8;
 constexpr uint32_t kRowStride = 256;
 constexpr uint64_t kSampleStride = 32;  // one key in 32 is copied for the sampled partition
 // How the boundaries of three runs or more are found where ranked samples are too many.
-//   A wave per boundary over the whole runs (partition_kernel): up to four runs, up to kRowsTiles tiles; more than kFewRuns runs.
-//   Rows first (partition_rows_kernel, partition_between_kernel): every row_entries-th entry of every run is ranked in all runs, and a boundary's
-//     wave searches between two of these rows.  Up to 16 runs as long as entries x runs are below kRowsPieces, up to kFewRuns below
-//     kSampledMinTiles tiles.
+//   A wave per boundary over the whole runs (partition_kernel): up to four runs, below kSampledMinTiles tiles; more than kFewRuns runs, below that.
+//   Rows first (partition_rows_kernel, partition_between_kernel): some entries of every run are ranked in all runs, and a boundary's wave searches
+//     between two of these rows.  Up to kRowsRuns runs below kRowsPieces, up to kFewRuns below kSampledMinTiles tiles.
 //   On a copy of every 32nd key (sample_kernel and the three after it): what is left.
-// Whole calls, us.  A wave per boundary / rows: 4 runs, 2M entries 86.5 / 90.0, 4M 157 / 157, 8M 293 / 286, 16M 570 / 534; 8 runs, 1M 65.4 / 63.3, 4M
-// 176 / 172, 8M 324 / 313, 16M 623 / 573; 16 runs, 2M 126 / 117, 4M 203 / 193, 8M 380 / 358; 24 runs, 2M 158 / 143, 4M 237 / 227.
-// Samples / rows: 3 runs, 32M entries 1108 / 1027; 4 runs, 50M 1613 / 1577; 8 runs, 32M 1134 / 1104; 12 runs, 16M 679 / 637, 50M 1901 / 1852; 16 runs,
-// 16M 688 / 666, 50M 1972 / 1931; but 16 runs, 67M 2517 / 2530; 24 runs, 16M 784 / 816, 50M 2266 / 2390.  Runs that cover
-// different keys gain more: 16 runs one after the other, 9.5M entries, samples / rows 466 / 325, in turns of 100 entries 454 / 462; 8 runs, a wave per
-// boundary / rows 356 / 304 and 375 / 373.
+// Whole calls, us; mixed runs, runs one after the other, runs in turns of 100 entries, the same keys in every run.
+//   A wave per boundary / rows: 4 runs, 2M entries 87 86 93 74 / 86 75 93 71, 5M 187 174 193 153 / 183 158 186 142; 8 runs, 1M 68 70 79 60 / 64 49 68 56, 4M
+//   168 169 174 149 / 167 138 167 142; 16 runs, 2M 124 145 154 117 / 115 86 119 108, 8M 374 368 407 390 / 339 277 344 347; 24 runs, 1M 105 155 158 95 /
+//   95 64 148 81, 4M 232 274 310 245 / 225 171 289 233.
+//   Samples / rows: 4 runs, 50M 1632 1532 1633 1228 / 1618 1456 1608 1231; 8 runs, 32M 1163 1069 1180 920 / 1142 971 1139 951; 16 runs, 16M 667 655
+//   787 630 / 636 527 659 661, 67M 2546 2359 2775 2501 / 2496 2146 2449 2585, and the same at 80M and 120M; 8 runs of 200M in all 6611 6217 6764 5473 /
+//   6519 5974 6644 5577; 3 runs of 400M within 1 %.  But 17 runs, 10M 505 473 637 466 / 516 399 545 508, 24 runs, 16M 759 715 964 764 / 791 614 886 831: two
+//   lanes per run instead of four.
 constexpr uint64_t kSampledMinTiles = 2048;
-constexpr uint64_t kRowsTiles = 2048;
-constexpr uint64_t kRowsPieces = 1ull << 30;
-// Entries from row to row.  With fewer, more samples are ranked, with more, more is left between them: 2,048 / 4,096 / 8,192 / 16,384, 8 runs, 2M
-// entries 99.8 / 96.6 / 98.9 / 103.6, 32M 1121 / 1104 / 1094 / 1104; 16 runs, 16M 685 / 666 / 654 / 662, 50M - / 1943 / 1931 / 1970.
-constexpr uint64_t kManyRowsEntries = 12000000;
-inline uint32_t row_entries(uint64_t total) { return total < kManyRowsEntries ? 4096 : 8192; }
+constexpr uint32_t kRowsRuns = 16;
+constexpr uint64_t kRowsPieces = 1ull << 30;  // entries x runs
+// Entries from row to row.  With fewer, more samples are ranked, with more, more is left between them.  1,024 / 2,048 / 4,096 / 8,192 / 16,384, mixed
+// and in turns: 5 runs, 1.2M entries 78 78 / 86 79 / 83 82 / 84 82 / -; 16 runs, 1.5M 103 106 / 102 107 / 101 133 / 101 132 / -, 3M 176 177 / 163 164 / 156
+// 182 / 155 177 / -, 8M 388 410 / 365 370 / 348 398 / 340 373 / 342 355, 40M 1723 1706 / 1621 1581 / 1550 1571 / 1551 1516 / 1512 1456; 4 runs, 16M 577 572 / 551
+// 549 / 541 535 / 547 537 / 549 539, 40M 1386 1381 / 1323 1336 / 1302 1284 / 1313 1301 / 1282 1338.
+inline uint32_t row_entries(uint64_t total, uint32_t k) {
+    if (total < 1500000) return 1024;
+    if (total < 2500000) return 2048;
+    return total < 8000000 ? 4096 : k <= 4 ? 8192 : 16384;
+}
 constexpr uint32_t kSpinLimit = 1u << 22;              // polls of one look-back window before giving up
 
 struct Header {  // first 256 bytes of the workspace
@@ -130,7 +136,7 @@ struct Workspace {
     Header* hdr;
     uint64_t* status;   // [n_tiles]
     uint64_t* splits;   // [(n_tiles + 1) * k]; the sampled partition first keeps its ranked rows there
-    uint64_t* ywin;     // [2 * (n_tiles - 1) * k] sample-space brackets of every boundary
+    uint64_t* ywin;     // [2 * (n_tiles - 1) * k] sample-space brackets of every boundary; or, in the room of these and the samples, ranked rows and their sums
     SampleTable st;
     uint4* clear;       // zeroed by the partition launch for a later kernel of the caller
     uint64_t clear_n;
@@ -501,17 +507,22 @@ __device__ __forceinline__ void split_two_wave(const lsm_entry_t* a, const uint6
 // searches in LDS, against this one: 4 x 16,384 entries 16.5 -> 4.5 us, 24 x 2,730 44 -> 7.3, 8 x 37,500 24.5 -> 6.5, 16 runs of
 // 8,000 entries one after the other 39.8 -> 4.7; tiles of uneven size cost the merge up to 2 us of it (4 x 16,384: 17.4 -> 18.1).
 // len: run lengths; upper: what the launch counts samples by (the same, or an upper bound: samples beyond a run's end come last, and
-// their rows are the runs' ends).
+// their rows are the runs' ends).  kApart: a run's second sample is at `offset`
+// (no more than stride) and the others follow from there; sums gets the sum of every row.
 // ---------------------------------------------------------------------------------------
-template <typename E>  // entries, or bare keys
+__host__ __device__ inline uint32_t sample_apart(uint32_t i, uint32_t offset, uint32_t stride) { return i > 0 ? offset + (i - 1) * stride : 0; }
+__host__ __device__ inline uint32_t samples_apart(uint32_t n, uint32_t offset, uint32_t stride) { return (n > 0) + (n > offset ? (n - offset + stride - 1) / stride : 0); }
+template <typename E, bool kApart = false>  // E: entries, or bare keys
 __device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, const uint32_t upper, const uint32_t p, const uint32_t k,
-                                            const int group_log, const uint32_t stride, const uint32_t per_tile, uint64_t* splits) {
+                                            const int group_log, const uint32_t stride, const uint32_t per_tile, uint64_t* splits,
+                                            const uint32_t offset = 0, uint32_t* sums = nullptr) {
     const uint32_t lane = threadIdx.x & (kWave - 1);
     const int lanes_log = 6 - group_log;
     const uint32_t lanes = 1u << lanes_log, member = lane >> lanes_log, part = lane & (lanes - 1), shift = member << lanes_log;
     const uint64_t lanes_mask = lanes == (uint32_t)kWave ? ~0ull : (1ull << lanes) - 1;
     const bool head = part == 0 && member < k;
-    const uint32_t real = (len + stride - 1) / stride, launched = (upper + stride - 1) / stride;
+    auto samples_of = [&](uint32_t n) { return kApart ? samples_apart(n, offset, stride) : (n + stride - 1) / stride; };
+    const uint32_t real = samples_of(len), launched = samples_of(upper);
     // which run the sample belongs to: samples are numbered run by run
     const uint32_t upto = wave_scan_u32(head ? launched : 0);
     const uint32_t own = (uint32_t)__popcll(__ballot(head && upto <= p));
@@ -522,17 +533,19 @@ __device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, con
     Key key = {{0, 0, 0, 0}};
     if (index < own_real) {
         const E* own_run = reinterpret_cast<const E*>(__shfl(reinterpret_cast<uint64_t>(run), own_lane, kWave));
-        const uint4* e = reinterpret_cast<const uint4*>(own_run + (uint64_t)index * stride);
+        const uint32_t own_offset = kApart ? (uint32_t)__shfl((int)offset, own_lane, kWave) : 0;
+        const uint32_t own_at = kApart ? sample_apart(index, own_offset, stride) : index * stride;
+        const uint4* e = reinterpret_cast<const uint4*>(own_run + own_at);
         const uint4 k0 = load_global_u4(e), k1 = load_global_u4(e + 1);
         key = key_from_raw(k0, k1);
-        // first record in [lo, hi) of the records `step` entries apart that is not before the key
-        auto search = [&](const E* from, uint32_t step, bool equal_is_before) {
+        // first record in [lo, hi) of those that place() gives that is not before the key
+        auto search = [&](auto place, bool equal_is_before) {
             while (__ballot(lo < hi) != 0) {
                 const uint32_t w = hi - lo;
                 auto tried = [&](uint32_t m) { return lo + (((2 * m + 1) * w) >> (lanes_log + 1)); };  // ascending with m, below hi
                 bool before = false;
                 if (lo < hi) {
-                    const uint4* q = reinterpret_cast<const uint4*>(from + (uint64_t)tried(part) * step);
+                    const uint4* q = reinterpret_cast<const uint4*>(run + place(tried(part)));
                     const uint4 q0 = load_global_u4(q), q1 = load_global_u4(q + 1);
                     const Key other = key_from_raw(q0, q1);
                     before = equal_is_before ? !key_less(key, other) : key_less(other, key);
@@ -547,15 +560,16 @@ __device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, con
         };
         lo = member == own ? index : 0;
         hi = member == own ? index : (member < k ? real : 0);
-        search(run, stride, member < own);
+        auto sample_at = [&](uint32_t i) { return kApart ? sample_apart(i, offset, stride) : i * stride; };
+        search([&](uint32_t i) { return kApart ? (uint64_t)sample_apart(i, offset, stride) : (uint64_t)i * stride; }, member < own);
         t = wave_scan_u32(head ? lo : 0);
         t = (uint32_t)__builtin_amdgcn_readlane((int)t, kWave - 1);
         if (t % per_tile != 0) return;
         // the lower bound: after the last sample before the key, or that sample if its key is the same
-        hi = min(lo * stride, len);
-        lo = lo > 0 ? (lo - 1) * stride : 0;
-        if (member == own) lo = hi = index * stride;
-        search(run, 1, false);
+        hi = min(sample_at(lo), len);
+        lo = lo > 0 ? sample_at(lo - 1) : 0;
+        if (member == own) lo = hi = own_at;
+        search([](uint32_t i) { return (uint64_t)i; }, false);
     } else {  // beyond the run's end
         const uint32_t surplus = wave_scan_u32(head ? launched - real : 0), all = wave_scan_u32(head ? real : 0);
         t = (uint32_t)__builtin_amdgcn_readlane((int)all, kWave - 1) + (uint32_t)__shfl((int)(surplus - (launched - real)), own_lane, kWave) + index - own_real;
@@ -564,6 +578,10 @@ __device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, con
     }
     const uint32_t row = t / per_tile;
     if (head && row > 0) splits[(uint64_t)row * k + member] = lo;
+    if (kApart) {
+        const uint32_t sum = wave_scan_u32(head ? lo : 0);
+        if (lane == kWave - 1) sums[row] = row > 0 ? sum : 0;
+    }
 }
 
 // The boundaries that a workgroup works on, as a number in ascending order of the boundaries.  Workgroups go to the eight dies in
@@ -662,33 +680,36 @@ __global__ void __launch_bounds__(kWave) partition_ranked_kernel(RunTable rt, Wo
                 ws.stride, ws.per_tile, ws.splits);
 }
 // Boundaries between rows, two launches.  partition_rows_kernel: the lower bounds of every row_entries-th entry of every run in all runs, in order
-// of the entries' keys, a wave each (ranked_row).  partition_between_kernel: row t has row_entries * (t - k) <= L <= row_entries * t, so the last one that
-// is not beyond a boundary's rank is among k + 1; the boundary lies between it and the next, in some row_entries entries of all runs together, where
-// window_split has two rounds left instead of five.  Bound by the lines that both fetch (a record is 128 bytes of traffic, its neighbour aside).
+// of the entries' keys, a wave each (ranked_row).  partition_between_kernel: a boundary lies between the last row that is not beyond its rank and
+// the next, some row_entries entries of all runs together, where window_split has two rounds left instead of five.  Run j's second sample is
+// (j + 1) / k of row_entries into it: with samples at the same places of all runs, the rows of runs that advance together (the same keys in every
+// run, or runs that take turns) come k at a time, and k * row_entries entries lie between them (24 runs in turns of 100 entries, 1M in all 195
+// us, so 150; the same keys in 16 runs, 25M 1040 and 985).
+// Row t has c_j samples of run j before it, t in all, so L is no more than row_entries * t, and no less than the sum of offset_j + row_entries *
+// (c_j - 2), row_entries * (t - 3/2 k).  Bound by the lines that both fetch (a record is 128 bytes of traffic, its neighbour aside).
+__device__ __forceinline__ uint32_t* row_sums(const Workspace& ws, uint32_t n_rows, uint32_t k) { return reinterpret_cast<uint32_t*>(ws.ywin + (uint64_t)n_rows * k); }
+__host__ __device__ inline uint32_t row_offset(uint32_t j, uint32_t k, uint32_t row_entries) { return (j + 1) * row_entries / k; }
 template <bool kInit>
-__global__ void __launch_bounds__(kWave) partition_rows_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint32_t row_entries, int group_log) {
+__global__ void __launch_bounds__(kWave) partition_rows_kernel(RunTable rt, Workspace ws, uint64_t n_tiles, uint32_t n_rows, uint32_t row_entries, int group_log) {
     partition_init<kInit>(rt, ws, n_tiles);
     const uint32_t member = (threadIdx.x & (kWave - 1)) >> (6 - group_log);
     const bool mine = member < rt.k;
-    ranked_row(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, near_block(), rt.k, group_log,
-                row_entries, 1, ws.ywin);
+    ranked_row<lsm_entry_t, true>(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, near_block(), rt.k,
+                                  group_log, row_entries, 1, ws.ywin, mine ? row_offset(member, rt.k, row_entries) : 0, row_sums(ws, n_rows, rt.k));
 }
 template <int kPerLane>
 __global__ void __launch_bounds__(kWave) partition_between_kernel(RunTable rt, Workspace ws, uint32_t n_rows, uint32_t row_entries, int group_log) {
     __shared__ WindowShared<kPerLane> s;
-    const uint32_t b = near_block() + 1, lane = threadIdx.x, group = 1u << group_log, j = lane & (group - 1), g = lane >> group_log, groups = kWave >> group_log;
+    const uint32_t b = near_block() + 1, lane = threadIdx.x, j = lane & ((1u << group_log) - 1);
     const bool own = j < rt.k;
     const uint32_t len = own ? (uint32_t)run_len(rt, j) : 0, r = b * ws.spacing;
-    // the last row that is not beyond r
     auto row = [&](uint32_t t) { return own && t > 0 ? (t < n_rows ? min((uint32_t)ws.ywin[(uint64_t)t * rt.k + j], len) : len) : 0; };  // inputs that are not sorted may leave a row unwritten
-    uint32_t t = r / row_entries;
-    for (uint32_t c = t + 1;; c += groups) {
-        const uint32_t sum = group_sum_u32(row(c + g), group);
-        const uint64_t below = __ballot(sum <= r && c + g < n_rows);
-        t += __popcll(below) >> group_log;
-        if (~below != 0) break;
-    }
-    const uint32_t lo = row(t), hi = row(t + 1);
+    // the last row that is not beyond r: one of 3/2 k + 2, and the first of them is not beyond it
+    static_assert(kFewRuns * 3 / 2 + 2 <= kWave, "a row per lane");
+    const uint32_t first = min(r / row_entries, n_rows - 1);
+    const uint32_t sum = first + lane < n_rows ? row_sums(ws, n_rows, rt.k)[first + lane] : ~0u;
+    const uint32_t at = first + (uint32_t)__popcll(__ballot(sum <= r) & ~1ull);
+    const uint32_t lo = row(at), hi = row(at + 1);
     const uint32_t best = window_split<kPerLane, false>(s, own ? rt.ptr[j] : nullptr, lo, max(lo, hi), r, group_log);
     if (lane < rt.k) ws.splits[(uint64_t)b * rt.k + lane] = best;
 }
@@ -716,7 +737,7 @@ static int log2_ceil(uint32_t k) {
 static int records_per_lane(int group_log) { return group_log <= 4 ? 4 : 8; }
 
 // ---------------------------------------------------------------------------------------
-// Sampled partition, for large inputs.  Searching the runs directly costs tens of scattered
+// Sampled partition, for large inputs of many runs.  Searching the runs directly costs tens of scattered
 // 64-byte reads per boundary and run, which is HBM traffic of the order of the merge itself.
 // Instead every kSampleStride-th key of each run is copied into a compact array (1/64 of the
 // input bytes: it stays in the last-level cache), the selection is done on the samples, and the
@@ -2222,8 +2243,13 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
     // one run and two (bisection on the merge path): at any size
-    const bool rows = n_runs > 2 && n_runs <= kFewRuns && ws.stride == 0 && rt.n_dev == nullptr && total * n_runs < (n_runs <= 16 ? kRowsPieces : ~0ull) &&
-                      (n_runs <= 16 || n_tiles < kSampledMinTiles) && n_tiles >= (n_runs <= 4 ? kRowsTiles : 2);
+    bool rows = n_runs > 2 && ws.stride == 0 && rt.n_dev == nullptr &&
+                (n_runs <= kRowsRuns ? total * n_runs < kRowsPieces && n_tiles >= (n_runs <= 4 ? kSampledMinTiles : 2) : n_runs <= kFewRuns && n_tiles < kSampledMinTiles);
+    const uint32_t row_step = row_entries(total, n_runs);
+    uint32_t n_rows = 0;
+    for (uint32_t j = 0; rows && j < n_runs; j++) n_rows += samples_apart((uint32_t)rt.n[j], row_offset(j, n_runs, row_step), row_step);
+    const char* const rows_end = reinterpret_cast<const char*>(ws.st.ptr[n_runs - 1] + ws.st.m[n_runs - 1]);  // of the room that they share with what copied samples need
+    rows = rows && n_rows != 0 && n_rows <= (uint64_t)(rows_end - reinterpret_cast<const char*>(ws.ywin)) / ((n_runs + 1) * sizeof(uint64_t));
     const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs <= 2 || rows);
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
     auto build_filter = [&](const ClearSpan& span) {  // right behind the merge, if it is asked for
@@ -2298,12 +2324,11 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                 else if (ws.stride != 0)
                     hipLaunchKernelGGL(partition_ranked_kernel<kInit>, dim3(ws.samples), dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (rows) {
-                    const uint32_t step = row_entries(total);
-                    uint32_t n_rows = 0;
-                    for (uint32_t j = 0; j < n_runs; j++) n_rows += (uint32_t)((rt.n[j] + step - 1) / step);
-                    hipLaunchKernelGGL(partition_rows_kernel<kInit>, dim3(n_rows), dim3(kWave), 0, stream, rt, ws, n_tiles, step, group_log);
-                    if (records_per_lane(group_log) == 4) hipLaunchKernelGGL(partition_between_kernel<4>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, step, group_log);
-                    else hipLaunchKernelGGL(partition_between_kernel<8>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, step, group_log);
+                    hipLaunchKernelGGL(partition_rows_kernel<kInit>, dim3(n_rows), dim3(kWave), 0, stream, rt, ws, n_tiles, n_rows, row_step, group_log);
+                    if (records_per_lane(group_log) == 4)
+                        hipLaunchKernelGGL(partition_between_kernel<4>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, row_step, group_log);
+                    else
+                        hipLaunchKernelGGL(partition_between_kernel<8>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, row_step, group_log);
                 } else if (records_per_lane(group_log) == 4)
                     hipLaunchKernelGGL((partition_kernel<kInit, 4, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (n_runs <= kFewRuns)

@@ -54,7 +54,7 @@ def test_generator_is_identical_on_cpu_and_gpu(cfg1):
     assert all(torch.equal(a.cpu(), b) for a, b in zip(cfg1.runs, w.runs))
 
 
-@pytest.mark.parametrize("scale,flags", [(256, 1), (256, 0), (64, 1), (12, 1), (6, 1)])  # 5.6M entries: searched directly; 11.2M: sampled
+@pytest.mark.parametrize("scale,flags", [(256, 1), (256, 0), (64, 1), (12, 1), (6, 1)])  # 5.6M and 11.2M entries: boundaries searched between rows
 def test_scaled_config3_tiered_16way(g, oracle, scale, flags):
     from workloads import lsm
     print("config3 scale", scale, "flags", flags, flush=True)
@@ -491,14 +491,31 @@ def test_many_runs_one_after_the_other_are_not_slow(g, oracle):
     assert took < 3 * base
 
 
-@pytest.mark.parametrize("k,tiles,shape", [(k, tiles, "uneven") for k, tiles in [(1, 10240), (3, 10240), (5, 8192), (16, 5120), (17, 2048), (40, 2048)]]
-                         + [(17, 2048, "copies"), (40, 2048, "copies")])
-def test_searched_directly_or_on_samples(g, oracle, k, tiles, shape):
-    """The longest input whose boundaries are searched in the runs themselves and the shortest that is sampled; runs of very
+def _launches(call):
+    """Kernels (and other work) that a call puts on the stream: the nodes of a graph that records it."""
+    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = ctypes.c_size_t(0)
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
+    return n.value
+
+
+# The longest input whose boundaries are found one way and the shortest of another way, and the launches of either with the merge's: a wave per
+# boundary over the whole runs 2, between rows 3, on copied samples 6.
+LINES = [(3, 2048, 2, 3), (4, 2048, 2, 3), (17, 2048, 3, 6), (32, 2048, 3, 6), (33, 2048, 2, 6), (40, 2048, 2, 6), (64, 2048, 2, 6)]
+
+
+@pytest.mark.parametrize("k,tiles,below,above,shape", [(*line, "uneven") for line in LINES]
+                         + [(1, 10240, 2, 2, "uneven"), (3, 10240, 3, 3, "uneven"), (5, 8192, 3, 3, "uneven"), (16, 5120, 3, 3, "uneven")]
+                         + [(17, 2048, 3, 6, "copies"), (40, 2048, 2, 6, "copies")])
+def test_searched_directly_or_on_samples(g, oracle, k, tiles, below, above, shape):
+    """Both sides of every line between two ways of finding boundaries, and larger inputs; runs of very
     different lengths, an empty one among them, and ones that cover a part of the keys only; or the same keys in every run, so
     that the samples tie."""
     rs = np.random.RandomState(k)
-    for total in ((tiles - 1) * (2048 - k), (tiles - 1) * (2048 - k) + 1):
+    for total, launches in (((tiles - 1) * (2048 - k), below), ((tiles - 1) * (2048 - k) + 1, above)):
         print("direct or sampled", k, total, shape, flush=True)
         if shape == "copies":
             lens = np.full(k, total // k)
@@ -514,19 +531,11 @@ def test_searched_directly_or_on_samples(g, oracle, k, tiles, shape):
             runs = _runs_of(oracle, rs, lens, 2 * total)
             runs[min(1, k - 1)][:, 0] |= 1  # the keys' first byte, as stored: a run behind all others
         _check_compact(g, oracle, runs, int(total & 1))
-        del runs
+        buffers = torch.empty((total, 8), dtype=torch.int64, device=dev()), torch.zeros(1, dtype=torch.int64, device=dev())
+        workspace = torch.empty(g.lsm_compact_workspace_bytes([r.shape[0] for r in runs]), dtype=torch.uint8, device=dev())
+        assert _launches(lambda: g.lsm_compact(runs, 0, *buffers, workspace)) == launches
+        del runs, buffers, workspace
         torch.cuda.empty_cache()
-
-
-def _launches(call):
-    """Kernels (and other work) that a call puts on the stream: the nodes of a graph that records it."""
-    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line)
-    graph = torch.cuda.CUDAGraph(keep_graph=True)
-    with torch.cuda.graph(graph):
-        call()
-    n = ctypes.c_size_t(0)
-    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(n)) == 0
-    return n.value
 
 
 @pytest.mark.parametrize("tiles", [2, 256, 257, 2047, 2048, 10240, 10241])
@@ -605,11 +614,14 @@ def test_boundaries_at_ranked_samples(g, oracle, k, shape):
         assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
 
 
-@pytest.mark.parametrize("k,total", [(3, 2048 * 2045 + 1), (4, 2048 * 2044 - 1), (5, 1_100_000), (16, 1_300_003), (17, 2_000_000), (32, 1_500_000)])
-@pytest.mark.parametrize("shape", ["ragged", "copies", "apart"])
+@pytest.mark.parametrize("k,total", [(3, 2048 * 2045 + 1), (4, 2047 * 2044), (4, 2047 * 2044 + 1), (5, 1_100_000), (5, 1_499_999), (5, 1_500_000), (12, 2_499_999),
+                                     (12, 2_500_000), (16, 1_300_003), (16, 7_999_999), (16, 8_000_000), (17, 2_000_000), (32, 1_500_000)])
+@pytest.mark.parametrize("shape", ["ragged", "copies", "apart", "turns"])
 def test_boundaries_between_rows(g, oracle, k, total, shape):
-    """Boundaries that are searched between ranked rows (every 4,096th entry of a run), and with four runs just below.  Ragged: empty runs, runs
-    of one entry, around 4,096 and far longer.  Copies: rows of the same key in every run.  Apart: between two rows lies one run only."""
+    """Boundaries that are searched between ranked rows, on both sides of the totals where the distance between rows changes (1,024 entries of a run
+    to 16,384), and with four runs just below.  Ragged: empty runs, runs
+    of one entry, around 4,096 and far longer.  Copies: rows of the same key in every run, but for where they start.  Apart: between two rows lies one
+    run only.  Turns: runs that advance together, 100 entries each."""
     print("between rows", k, total, shape, flush=True)
     rs = np.random.RandomState(k)
     lens = np.full(k, total // k)
@@ -622,6 +634,10 @@ def test_boundaries_between_rows(g, oracle, k, total, shape):
         runs = [one[:n].clone() for n in lens]
         for r in runs:
             r[:, 4] = torch.randint(0, 1 << 40, (r.shape[0],), device=dev())
+    elif shape == "turns":
+        one = _runs_of(oracle, rs, [total], 3 * total)[0]
+        turn = torch.arange(total, device=dev()) // 100 % k
+        runs = [one[turn == j].contiguous() for j in range(k)]
     else:
         runs = _runs_of(oracle, rs, lens, 2 * total)
         for j in range(k if shape == "apart" else 0):
