@@ -89,7 +89,7 @@ constexpr uint64_t kSampleStride = 32;  // one key in 32 is copied for the sampl
 // How the boundaries of three runs or more are found where ranked samples are too many.
 //   A wave per boundary over the whole runs (partition_kernel): up to four runs, below kSampledMinTiles tiles; more than kFewRuns runs, below that.
 //   Rows first (partition_rows_kernel, partition_between_kernel): some entries of every run are ranked in all runs, and a boundary's wave searches
-//     between two of these rows.  Up to kRowsRuns runs below kRowsPieces, up to kFewRuns below kSampledMinTiles tiles.
+//     between two of these rows.  Up to kRowsRuns runs of any length, up to kFewRuns below kSampledMinTiles tiles.
 //   On a copy of every 32nd key (sample_kernel and the three after it): what is left.
 // Whole calls, us; mixed runs, runs one after the other, runs in turns of 100 entries, the same keys in every run.
 //   A wave per boundary / rows: 4 runs, 2M entries 87 86 93 74 / 86 75 93 71, 5M 187 174 193 153 / 183 158 186 142; 8 runs, 1M 68 70 79 60 / 64 49 68 56, 4M
@@ -101,7 +101,7 @@ constexpr uint64_t kSampleStride = 32;  // one key in 32 is copied for the sampl
 //   lanes per run instead of four.
 constexpr uint64_t kSampledMinTiles = 2048;
 constexpr uint32_t kRowsRuns = 16;
-constexpr uint64_t kRowsPieces = 1ull << 30;  // entries x runs
+constexpr uint64_t kRowsMost = (1ull << 32) - (1ull << 20);  // positions in 32 bits
 // Entries from row to row.  With fewer, more samples are ranked, with more, more is left between them.  1,024 / 2,048 / 4,096 / 8,192 / 16,384, mixed
 // and in turns: 5 runs, 1.2M entries 78 78 / 86 79 / 83 82 / 84 82 / -; 16 runs, 1.5M 103 106 / 102 107 / 101 133 / 101 132 / -, 3M 176 177 / 163 164 / 156
 // 182 / 155 177 / -, 8M 388 410 / 365 370 / 348 398 / 340 373 / 342 355, 40M 1723 1706 / 1621 1581 / 1550 1571 / 1551 1516 / 1512 1456; 4 runs, 16M 577 572 / 551
@@ -2243,14 +2243,14 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
 
     // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
     // one run and two (bisection on the merge path): at any size
-    bool rows = n_runs > 2 && ws.stride == 0 && rt.n_dev == nullptr &&
-                (n_runs <= kRowsRuns ? total * n_runs < kRowsPieces && n_tiles >= (n_runs <= 4 ? kSampledMinTiles : 2) : n_runs <= kFewRuns && n_tiles < kSampledMinTiles);
+    bool rows = n_runs > 2 && ws.stride == 0 && rt.n_dev == nullptr && total < kRowsMost &&
+                (n_runs <= kRowsRuns ? n_tiles >= (n_runs <= 4 ? kSampledMinTiles : 2) : n_runs <= kFewRuns && n_tiles < kSampledMinTiles);
     const uint32_t row_step = row_entries(total, n_runs);
     uint32_t n_rows = 0;
     for (uint32_t j = 0; rows && j < n_runs; j++) n_rows += samples_apart((uint32_t)rt.n[j], row_offset(j, n_runs, row_step), row_step);
     const char* const rows_end = reinterpret_cast<const char*>(ws.st.ptr[n_runs - 1] + ws.st.m[n_runs - 1]);  // of the room that they share with what copied samples need
     rows = rows && n_rows != 0 && n_rows <= (uint64_t)(rows_end - reinterpret_cast<const char*>(ws.ywin)) / ((n_runs + 1) * sizeof(uint64_t));
-    const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs <= 2 || rows);
+    const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs <= kRowsRuns);
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
     auto build_filter = [&](const ClearSpan& span) {  // right behind the merge, if it is asked for
         if (ws.clear_n == 0 || span.filter_bits == 0) return (int)LSM_OK;
@@ -2329,14 +2329,12 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                         hipLaunchKernelGGL(partition_between_kernel<4>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, row_step, group_log);
                     else
                         hipLaunchKernelGGL(partition_between_kernel<8>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, row_step, group_log);
-                } else if (records_per_lane(group_log) == 4)
+                } else if (n_runs <= kRowsRuns && n_tiles < kSampledMinTiles)
                     hipLaunchKernelGGL((partition_kernel<kInit, 4, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
-                else if (n_runs <= kFewRuns)
-                    hipLaunchKernelGGL((partition_kernel<kInit, 8, false>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
-                else if (n_tiles * n_runs > kWindowPieces)
-                    hipLaunchKernelGGL(partition_many_kernel<kInit>, waves, dim3(kWave), 0, stream, rt, ws, n_tiles);
-                else
+                else if (n_runs > kFewRuns && n_tiles * n_runs <= kWindowPieces)
                     hipLaunchKernelGGL((partition_kernel<kInit, 8, true>), waves, dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
+                else
+                    hipLaunchKernelGGL(partition_many_kernel<kInit>, waves, dim3(kWave), 0, stream, rt, ws, n_tiles);
             };
             if (fused_init) launch(std::true_type{});
             else launch(std::false_type{});

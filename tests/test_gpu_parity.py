@@ -538,6 +538,19 @@ def test_searched_directly_or_on_samples(g, oracle, k, tiles, below, above, shap
         torch.cuda.empty_cache()
 
 
+@pytest.mark.parametrize("k,total", [(16, 1 << 26), (8, 1 << 27), (12, 89_478_486)])
+def test_long_inputs_of_up_to_16_runs_are_cut_one_way(g, k, total):
+    """No line between two ways at 2^30 entries times runs, where measurements show none: the launches are recorded, not run."""
+    print("one way", k, total, flush=True)
+    out, n_out = torch.empty((total + 1, 8), dtype=torch.int64, device=dev()), torch.zeros(1, dtype=torch.int64, device=dev())
+    for n in (total - 1, total, total + 1):
+        runs = list(torch.empty((n, 8), dtype=torch.int64, device=dev()).split(-(-n // k)))
+        workspace = torch.empty(g.lsm_compact_workspace_bytes([r.shape[0] for r in runs]), dtype=torch.uint8, device=dev())
+        assert _launches(lambda: g.lsm_compact(runs, 0, out, n_out, workspace)) == 3  # noqa: B023
+        del runs, workspace
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("tiles", [2, 256, 257, 2047, 2048, 10240, 10241])
 def test_one_run_is_cut_without_a_search(g, oracle, tiles):
     """One run of any length: the boundaries are multiples of the tile, one launch before the merge's."""
