@@ -510,6 +510,7 @@ __device__ __forceinline__ void split_two_wave(const lsm_entry_t* a, const uint6
 // their rows are the runs' ends).  kApart: a run's second sample is at `offset`
 // (no more than stride) and the others follow from there; sums gets the sum of every row.
 // ---------------------------------------------------------------------------------------
+constexpr uint32_t kDies = 8;
 __host__ __device__ inline uint32_t sample_apart(uint32_t i, uint32_t offset, uint32_t stride) { return i > 0 ? offset + (i - 1) * stride : 0; }
 __host__ __device__ inline uint32_t samples_apart(uint32_t n, uint32_t offset, uint32_t stride) { return (n > 0) + (n > offset ? (n - offset + stride - 1) / stride : 0); }
 template <typename E, bool kApart = false>  // E: entries, or bare keys
@@ -523,11 +524,15 @@ __device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, con
     const bool head = part == 0 && member < k;
     auto samples_of = [&](uint32_t n) { return kApart ? samples_apart(n, offset, stride) : (n + stride - 1) / stride; };
     const uint32_t real = samples_of(len), launched = samples_of(upper);
-    // which run the sample belongs to: samples are numbered run by run
-    const uint32_t upto = wave_scan_u32(head ? launched : 0);
-    const uint32_t own = (uint32_t)__popcll(__ballot(head && upto <= p));
+    // which run the sample belongs to: samples are numbered run by run; kApart: the first eighth of each run's, and so on, an eighth for a die
+    const uint32_t die = kApart ? p % kDies : 0, nth = kApart ? p / kDies : p;
+    const uint32_t begin = kApart ? (uint32_t)((uint64_t)launched * die / kDies) : 0;
+    const uint32_t mine = kApart ? (uint32_t)((uint64_t)launched * (die + 1) / kDies) - begin : launched;
+    const uint32_t upto = wave_scan_u32(head ? mine : 0);
+    const uint32_t own = (uint32_t)__popcll(__ballot(head && upto <= nth));
+    if (kApart && own >= k) return;  // the eighths are not all of the same size
     const int own_lane = (int)(own << lanes_log);
-    const uint32_t index = p - (uint32_t)__shfl((int)(upto - launched), own_lane, kWave);
+    const uint32_t index = nth - (uint32_t)__shfl((int)(upto - mine - begin), own_lane, kWave);
     const uint32_t own_real = (uint32_t)__shfl((int)real, own_lane, kWave);
     uint32_t t, lo = 0, hi = 0;
     Key key = {{0, 0, 0, 0}};
@@ -587,7 +592,6 @@ __device__ __forceinline__ void ranked_row(const E* run, const uint32_t len, con
 // The boundaries that a workgroup works on, as a number in ascending order of the boundaries.  Workgroups go to the eight dies in
 // turn; with this a die gets one contiguous eighth of the boundaries, and neighbours, whose searches end in the same records, share an
 // L2.
-constexpr uint32_t kDies = 8;
 __device__ __forceinline__ uint32_t near_block() {
     const uint32_t die = blockIdx.x % kDies, each = gridDim.x / kDies, more = gridDim.x % kDies;  // the first `more` dies get one more
     return die * each + min(die, more) + blockIdx.x / kDies;
@@ -685,6 +689,8 @@ __global__ void __launch_bounds__(kWave) partition_ranked_kernel(RunTable rt, Wo
 // (j + 1) / k of row_entries into it: with samples at the same places of all runs, the rows of runs that advance together (the same keys in every
 // run, or runs that take turns) come k at a time, and k * row_entries entries lie between them (24 runs in turns of 100 entries, 1M in all 195
 // us, so 150; the same keys in 16 runs, 25M 1040 and 985).
+// A die ranks an eighth of every run's samples: their searches read the same lines where runs cover the same keys (12 runs of 6M entries in all 272.7 us
+// with an eighth of all samples, run by run, for a die, 270.0 so; 16 runs, 3M 162.6 and 158.7).
 // Row t has c_j samples of run j before it, t in all, so L is no more than row_entries * t, and no less than the sum of offset_j + row_entries *
 // (c_j - 2), row_entries * (t - 3/2 k).  Bound by the lines that both fetch (a record is 128 bytes of traffic, its neighbour aside).
 __device__ __forceinline__ uint32_t* row_sums(const Workspace& ws, uint32_t n_rows, uint32_t k) { return reinterpret_cast<uint32_t*>(ws.ywin + (uint64_t)n_rows * k); }
@@ -694,7 +700,7 @@ __global__ void __launch_bounds__(kWave) partition_rows_kernel(RunTable rt, Work
     partition_init<kInit>(rt, ws, n_tiles);
     const uint32_t member = (threadIdx.x & (kWave - 1)) >> (6 - group_log);
     const bool mine = member < rt.k;
-    ranked_row<lsm_entry_t, true>(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, near_block(), rt.k,
+    ranked_row<lsm_entry_t, true>(mine ? rt.ptr[member] : nullptr, mine ? (uint32_t)run_len(rt, member) : 0, mine ? (uint32_t)rt.n[member] : 0, blockIdx.x, rt.k,
                                   group_log, row_entries, 1, ws.ywin, mine ? row_offset(member, rt.k, row_entries) : 0, row_sums(ws, n_rows, rt.k));
 }
 template <int kPerLane>
@@ -2246,8 +2252,12 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     bool rows = n_runs > 2 && ws.stride == 0 && rt.n_dev == nullptr && total < kRowsMost &&
                 (n_runs <= kRowsRuns ? n_tiles >= (n_runs <= 4 ? kSampledMinTiles : 2) : n_runs <= kFewRuns && n_tiles < kSampledMinTiles);
     const uint32_t row_step = row_entries(total, n_runs);
-    uint32_t n_rows = 0;
-    for (uint32_t j = 0; rows && j < n_runs; j++) n_rows += samples_apart((uint32_t)rt.n[j], row_offset(j, n_runs, row_step), row_step);
+    uint32_t n_rows = 0, row_blocks = 0;
+    for (uint32_t j = 0; rows && j < n_runs; j++) {
+        const uint32_t samples = samples_apart((uint32_t)rt.n[j], row_offset(j, n_runs, row_step), row_step);
+        n_rows += samples;
+        row_blocks += (samples + kDies - 1) / kDies * kDies;  // an eighth may be one longer than another
+    }
     const char* const rows_end = reinterpret_cast<const char*>(ws.st.ptr[n_runs - 1] + ws.st.m[n_runs - 1]);  // of the room that they share with what copied samples need
     rows = rows && n_rows != 0 && n_rows <= (uint64_t)(rows_end - reinterpret_cast<const char*>(ws.ywin)) / ((n_runs + 1) * sizeof(uint64_t));
     const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs <= kRowsRuns);
@@ -2324,7 +2334,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
                 else if (ws.stride != 0)
                     hipLaunchKernelGGL(partition_ranked_kernel<kInit>, dim3(ws.samples), dim3(kWave), 0, stream, rt, ws, n_tiles, group_log);
                 else if (rows) {
-                    hipLaunchKernelGGL(partition_rows_kernel<kInit>, dim3(n_rows), dim3(kWave), 0, stream, rt, ws, n_tiles, n_rows, row_step, group_log);
+                    hipLaunchKernelGGL(partition_rows_kernel<kInit>, dim3(row_blocks), dim3(kWave), 0, stream, rt, ws, n_tiles, n_rows, row_step, group_log);
                     if (records_per_lane(group_log) == 4)
                         hipLaunchKernelGGL(partition_between_kernel<4>, waves, dim3(kWave), 0, stream, rt, ws, n_rows, row_step, group_log);
                     else
