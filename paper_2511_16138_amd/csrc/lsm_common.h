@@ -212,7 +212,10 @@ __host__ __device__ inline uint64_t index_buckets(uint64_t n) { return n ? (n + 
 // Tile status word of a compaction: top two bits = state, then 20 bits that say which call has written it (0 where the call's first
 // launch has zeroed the words), low 42 bits = value.  The last tile's holds the number of output entries.
 constexpr uint64_t kStEmpty = 0, kStAggregate = 1, kStPrefix = 2, kStFailed = 3;
-constexpr int kStShift = 62, kStEpochShift = 42, kStEpochBits = 20;
+#ifndef LSM_STATUS_EPOCH_BITS
+#define LSM_STATUS_EPOCH_BITS 20  // fewer where a test wants to see them used up
+#endif
+constexpr int kStShift = 62, kStEpochShift = 42, kStEpochBits = LSM_STATUS_EPOCH_BITS;
 constexpr uint64_t kStValueMask = (1ull << kStEpochShift) - 1;
 constexpr uint32_t kStEpochs = 1u << kStEpochBits;
 

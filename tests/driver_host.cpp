@@ -12,6 +12,7 @@
 #include <cstring>
 #include <deque>
 #include <functional>
+#include <map>
 #include <utility>
 #include <vector>
 
@@ -33,16 +34,21 @@ uint64_t host_mallocs = 0, host_kernels = 0;
 uint64_t host_bytes = 0, host_largest = 0;  // of device memory: all that was asked for, and at once
 uint32_t host_pinned_flags = ~0u;   // flags that every pinned allocation was made with
 uint64_t host_dirty_filters = 0;    // filters built on memory that was promised to be zero and was not
+uint64_t host_stale_words = 0;      // status words of a merge in one launch that were neither zero nor of an earlier call
+uint64_t host_outside = 0;          // workspaces and scratch memory that reach beyond their block, or into each other
+uint64_t host_zeroings = 0, host_whole_merges = 0, host_hashed_filters = 0;  // launches that zeroed status words, merges in one launch, filters built in scratch memory
 int64_t host_slow_stats = 0;        // what a probe batch found is written when the stream is next asked or waited for, no earlier
 int64_t host_slow_merges = 0;       // the same for merges and sorted write buffers; every time the stream is asked, one of them ends
 
 void host_reset() {
     host_malloc_in = host_kernel_in = host_late_in = host_slow_stats = host_slow_merges = 0;
     host_mallocs = host_kernels = host_dirty_filters = host_bytes = host_largest = 0;
+    host_stale_words = host_outside = host_zeroings = host_whole_merges = host_hashed_filters = 0;
     host_pinned_flags = ~0u;
 }
 
 // ---------------------------------------------------------------------------------------------------- HIP runtime
+static std::map<char*, size_t> blocks_of_memory;
 hipError_t hipMalloc(void** p, size_t bytes) {
     host_mallocs++;
     host_bytes += bytes;
@@ -50,9 +56,11 @@ hipError_t hipMalloc(void** p, size_t bytes) {
     if (host_malloc_in > 0 && --host_malloc_in == 0) return hipErrorOutOfMemory;
     *p = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
     std::memset(*p, 0xAB, (bytes + 255) / 256 * 256);
+    blocks_of_memory[static_cast<char*>(*p)] = bytes;
     return hipSuccess;
 }
 hipError_t hipFree(void* p) {
+    blocks_of_memory.erase(static_cast<char*>(p));
     std::free(p);
     return hipSuccess;
 }
@@ -98,23 +106,87 @@ static void enqueue(int64_t slow, std::function<void()> work) {
 }
 static int done() { return host_late_in > 0 && --host_late_in == 0 ? LSM_ERR_HIP : LSM_OK; }
 
-static void merge(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t& out, const lsm::ClearSpan& clear) {
-    std::vector<const lsm_entry_t*> ptr;
-    std::vector<uint64_t> len;
-    for (uint32_t j = 0; j < n_runs; j++) ptr.push_back(runs[j].entries), len.push_back(runs[j].n);
-    enqueue(host_slow_merges, [=, clear_p = clear.p, clear_bytes = clear.bytes] {
-        if (clear_bytes != 0) std::memset(clear_p, 0, clear_bytes);
-        const uint64_t n = oracle_compact(ptr.data(), len.data(), n_runs, flags, out.entries);
-        if (out.fence_keys != nullptr) oracle_build_fences(out.entries, n, out.fence_stride, static_cast<uint8_t*>(out.fence_keys));
-        *out.n_out = n;
+// Merges, one or a batch, with what the library does with the memory that the driver lends it: the workspace and a long filter's scratch memory are
+// written all over, status words are zeroed by a call without an epoch, and written by a merge of one or two runs in one launch with one.
+struct Lent {
+    char* at;
+    size_t bytes;
+};
+static void merge_all(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, const lsm::ClearSpan* clear) {
+    struct Job {
+        std::vector<const lsm_entry_t*> ptr;
+        std::vector<uint64_t> len;
+        uint64_t total = 0;
+        uint32_t flags;
+        lsm_out_t out;
+        lsm::ClearSpan clear;
+        Lent scratch{nullptr, 0};
+    };
+    std::vector<Job> work(n_jobs);
+    bool pairs = true;
+    for (uint32_t j = 0; j < n_jobs; j++) {
+        Job& w = work[j];
+        for (uint32_t r = 0; r < jobs[j].n_runs; r++) w.ptr.push_back(jobs[j].runs[r].entries), w.len.push_back(jobs[j].runs[r].n), w.total += jobs[j].runs[r].n;
+        w.flags = jobs[j].flags, w.out = jobs[j].out;
+        if (clear != nullptr) w.clear = clear[j];
+        if (w.clear.filter != nullptr) w.scratch = Lent{static_cast<char*>(w.clear.p), lsm::filter_scratch(w.total, oracle_bloom_blocks(w.total, w.clear.filter_bits)).total};
+        if (clear != nullptr && w.clear.bytes != 0 && w.clear.filter_bits != 0) clear[j].filter_built = true;
+        pairs = pairs && jobs[j].n_runs <= 2;
+    }
+    const lsm::ClearSpan first = clear != nullptr ? clear[0] : lsm::ClearSpan();
+    const bool zeroes = first.status != nullptr && first.epoch == 0, whole = first.status != nullptr && first.epoch != 0 && pairs;
+    if (zeroes) first.status_zeroed = clear[0].status_zeroed = true;
+    const Lent own{static_cast<char*>(workspace), workspace_bytes};
+    enqueue(host_slow_merges, [=] {
+        std::vector<Lent> lent = {own};
+        if (first.status != nullptr) lent.push_back(Lent{reinterpret_cast<char*>(first.status), lsm::kShortTiles * sizeof(uint64_t)});
+        for (const Job& w : work)
+            if (w.scratch.bytes != 0) lent.push_back(w.scratch);
+        for (size_t i = 0; i < lent.size(); i++) {
+            auto block = blocks_of_memory.upper_bound(lent[i].at);
+            const bool inside = block != blocks_of_memory.begin() && (--block, lent[i].at + lent[i].bytes <= block->first + block->second);
+            if (!inside || reinterpret_cast<uintptr_t>(lent[i].at) % 256 != 0) host_outside++;
+            for (size_t q = 0; q < i; q++)
+                if (lent[i].at < lent[q].at + lent[q].bytes && lent[q].at < lent[i].at + lent[i].bytes) host_outside++;
+        }
+        if (zeroes) host_zeroings++, std::memset(first.status, 0, lsm::kShortTiles * sizeof(uint64_t));
+        if (whole) {
+            host_whole_merges++;
+            for (uint64_t t = 0; t < lsm::kShortTiles; t++)
+                if (first.status[t] != 0 && ((first.status[t] << 2) >> (lsm::kStEpochShift + 2)) >= first.epoch) host_stale_words++;  // unwritten memory is of a large one
+            for (uint64_t t = 0; t < work.size() && t < lsm::kShortTiles; t++)
+                first.status[t] = (lsm::kStPrefix << lsm::kStShift) | ((uint64_t)first.epoch << lsm::kStEpochShift) | work[t].total;
+        }
+        const bool ours = host_outside == 0;  // else a test has failed, and nothing is written there
+        if (ours) std::memset(own.at, 0xCD, own.bytes);
+        for (const Job& w : work) {
+            if (ours && w.scratch.bytes != 0) std::memset(w.scratch.at, 0xCE, w.scratch.bytes);
+            if (w.scratch.bytes == 0 && w.clear.bytes != 0) std::memset(w.clear.p, 0, w.clear.bytes);
+            const uint64_t n = oracle_compact(w.ptr.data(), w.len.data(), (uint32_t)w.ptr.size(), w.flags, w.out.entries);
+            if (w.out.fence_keys != nullptr) oracle_build_fences(w.out.entries, n, w.out.fence_stride, static_cast<uint8_t*>(w.out.fence_keys));
+            if (w.clear.bytes != 0 && w.clear.filter_bits != 0) {
+                host_hashed_filters += w.clear.filter != nullptr;
+                uint8_t* const filter = static_cast<uint8_t*>(w.clear.filter != nullptr ? w.clear.filter : w.clear.p);
+                if (n != 0) oracle_build_bloom(w.out.entries, n, filter, oracle_bloom_blocks(n, w.clear.filter_bits));
+            }
+            *w.out.n_out = n;
+        }
     });
 }
 
-size_t lsm_compact_workspace_bytes(const uint64_t*, uint32_t n_runs) { return n_runs > LSM_MAX_RUNS ? 0 : 1024; }
+size_t lsm_compact_workspace_bytes(const uint64_t* lens, uint32_t n_runs) {
+    if (n_runs > LSM_MAX_RUNS) return 0;
+    size_t bytes = 1024;
+    for (uint32_t r = 0; r < n_runs; r++) bytes += (lens[r] * 64 + 255) / 256 * 256;
+    return bytes;
+}
 size_t lsm_compact_batch_workspace_bytes(const lsm_compact_job_t* jobs, uint32_t n_jobs) {
     for (uint32_t j = 0; j < n_jobs; j++)
         if (jobs[j].n_runs > LSM_MAX_RUNS) return 0;
-    return 1024 * n_jobs;
+    size_t bytes = 1024 * n_jobs;
+    for (uint32_t j = 0; j < n_jobs; j++)
+        for (uint32_t r = 0; r < jobs[j].n_runs; r++) bytes += (jobs[j].runs[r].n * 64 + 255) / 256 * 256;
+    return bytes;
 }
 size_t lsm_flush_workspace_bytes(uint64_t n) { return 4 * n; }
 int lsm_flush_buffer(const lsm_entry_t* buffer, uint64_t n, const lsm_out_t* out_at, void*, size_t, void*) {
@@ -189,20 +261,27 @@ int lsm_probe(const lsm_queries_t* q, const lsm_tree_t* tree, const lsm_hits_t* 
 }  // extern "C"
 
 namespace lsm {
-int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void*, size_t, const ClearSpan& clear, bool* cleared,
-                     hipStream_t) {
+// The launch that was to zero the status words has not been made; the call had counted on it.
+static int not_launched(const ClearSpan& clear) {
+    clear.status_zeroed = clear.status != nullptr && clear.epoch == 0;
+    return LSM_ERR_HIP;
+}
+int compact_clearing(const lsm_run_t* runs, uint32_t n_runs, uint32_t flags, const lsm_out_t* out, void* workspace, size_t workspace_bytes, const ClearSpan& clear,
+                     bool* cleared, hipStream_t) {
     *cleared = false;
     if (n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
-    if (refused()) return LSM_ERR_HIP;
+    if (refused()) return not_launched(clear);
     *cleared = clear.bytes != 0;
-    merge(runs, n_runs, flags, *out, clear);
+    lsm_compact_job_t job{};
+    job.runs = runs, job.n_runs = n_runs, job.flags = flags, job.out = *out;
+    merge_all(&job, 1, workspace, workspace_bytes, &clear);
     return done();
 }
-int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void*, size_t, const ClearSpan* clear, hipStream_t) {
+int compact_batch_clearing(const lsm_compact_job_t* jobs, uint32_t n_jobs, void* workspace, size_t workspace_bytes, const ClearSpan* clear, hipStream_t) {
     for (uint32_t j = 0; j < n_jobs; j++)
         if (jobs[j].n_runs > LSM_MAX_RUNS) return LSM_ERR_BAD_ARG;
-    if (refused()) return LSM_ERR_HIP;
-    for (uint32_t j = 0; j < n_jobs; j++) merge(jobs[j].runs, jobs[j].n_runs, jobs[j].flags, jobs[j].out, clear ? clear[j] : ClearSpan());
+    if (refused()) return clear != nullptr ? not_launched(clear[0]) : (int)LSM_ERR_HIP;
+    merge_all(jobs, n_jobs, workspace, workspace_bytes, clear);
     return done();
 }
 int ingest_runs(const IngestJob* jobs, uint32_t count, uint32_t fence_stride, hipStream_t) {

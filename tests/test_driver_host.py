@@ -25,7 +25,7 @@ def host(tmp_path_factory, oracle):
     objects = []
     for src in (os.path.join(CSRC, "lsm_driver.cpp"), os.path.join(ROOT, "tests", "driver_host.cpp")):
         objects.append(str(d / (os.path.basename(src) + ".o")))
-        subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-fPIC", "--offload-host-only", "-x", "hip", *inc, "-c", src, "-o", objects[-1]])
+        subprocess.check_call([HIPCC, "-O1", "-std=c++17", "-fPIC", "--offload-host-only", "-x", "hip", "-DLSM_STATUS_EPOCH_BITS=3", *inc, "-c", src, "-o", objects[-1]])
     objects.append(str(d / "oracle.o"))
     subprocess.check_call(["gcc", "-O1", "-fPIC", "-c", os.path.join(ROOT, "oracle", "lsm_oracle.c"), "-o", objects[-1]])
     lib = str(d / "libdriver_host.so")
@@ -310,3 +310,70 @@ def test_a_small_tree_takes_little_memory(host, knobs, trees):
     assert knobs.read("bytes") < 2 << 20
     for t in new:
         t.close()
+
+
+def flush(host, trees, runs):
+    """One tree by its own call, several by the shared one."""
+    if len(trees) > 1:
+        return flush_many(host, trees, runs)
+    trees[0].plain.flush(runs[0].copy())
+    return host.lsm_driver_flush(trees[0].h, runs[0].ctypes.data, len(runs[0]))
+
+
+def memory_was_used_as_promised(knobs):
+    return knobs.read("stale_words") == 0 and knobs.read("outside") == 0 and knobs.read("dirty_filters") == 0
+
+
+def check(oracle, trees):
+    for t in trees:
+        assert t.unfinished(oracle) == ""
+        assert t.log() == t.plain.log
+
+
+@pytest.mark.parametrize("count", [1, 3])
+def test_no_status_word_of_an_earlier_call_is_taken_for_this_one_s(host, knobs, oracle, count):
+    """Merges in one launch find their status words zero or of a smaller epoch, far beyond the eight epochs of this build, in a workspace that grows
+    (several times) and holds the scratch memory of long filters (4,096 bits a key) beside the compaction's."""
+    sizes = [600] if count == 1 else [100, 200, 300]
+    trees = [Tree(host, buffer=n, T=6, bits=4096) for n in sizes]
+    for step in range(60):
+        runs = [run_of(range(n // 10 * step, n // 10 * step + n), step) for n in sizes]
+        assert flush(host, trees, runs) == 0
+        check(oracle, trees)
+    assert memory_was_used_as_promised(knobs)
+    assert knobs.read("largest") > 256 << 10  # the workspace has grown
+    assert knobs.read("whole_merges") > 30 and knobs.read("zeroings") > 5 and knobs.read("hashed_filters") > 10
+    for t in trees:
+        t.close()
+
+
+def newest_versions(oracle, runs):
+    return oracle.compact([np.array(r) for r in runs if len(r)], 1)
+
+
+@pytest.mark.parametrize("fault", FAULTS)
+@pytest.mark.parametrize("count", [1, 3])
+def test_status_words_are_zeroed_after_a_call_that_failed(host, knobs, oracle, fault, count):
+    """A call that is refused, one that reports an error although its work is done (and its status words are written), memory that runs out where the
+    workspace grows: whatever comes next meets no word of that call, and the trees hold what was flushed."""
+    struck_at = 0
+    for place in range(1, 14):
+        trees = [Tree(host, T=6, bits=4096, loaded=[(1, run_of(range(0, 300, 3), 1))]) for _ in range(count)]
+        kept, results = [], []
+        for step in range(24):
+            if step == 4:
+                zeroed = knobs.read("zeroings")
+                setattr(knobs, fault, place)
+            kept.append([run_of(range(5 * step + j, 5 * step + j + 60), 2 + step) for j in range(count)])  # a call that failed may still refer to them
+            results.append(flush(host, trees, kept[-1]))
+        struck = knobs.read(fault, C.c_int64) == 0
+        setattr(knobs, fault, 0)
+        struck_at += struck
+        assert set(results) <= {0, HIP} and results[-1] == 0 and (HIP in results) <= struck
+        assert memory_was_used_as_promised(knobs), place
+        assert knobs.read("zeroings") > zeroed and knobs.read("whole_merges") > 0
+        for t in trees:
+            got = [np.ctypeslib.as_array(C.cast(r.run.entries, C.POINTER(C.c_uint8)), (r.run.n, 64)) for r in t.runs() if r.run.n]
+            assert np.array_equal(newest_versions(oracle, got), newest_versions(oracle, t.plain.runs_newest_first())), place
+            t.close()
+    assert struck_at > 5
