@@ -160,7 +160,9 @@ __device__ __forceinline__ uint32_t wave_scan_u32(uint32_t v) {
 // table, so the compiler cannot tell): a global instead of a flat load.
 __device__ __forceinline__ uint4 load_global_u4(const uint4* p) { typedef uint32_t v4 __attribute__((ext_vector_type(4))); const v4 v = *(const __attribute__((address_space(1))) v4*)p; return make_uint4(v.x, v.y, v.z, v.w); }
 
-// 16-byte store of output that nothing on the chip reads soon: it does not displace what the L2 holds.
+// 16-byte store of output that does not displace what the L2 holds.  For what is more than the L2s take, or written where nothing on the chip reads it soon;
+// merges of a few tiles use it as well, though a filter or the next merge may read their output at once: 4 x 16,384 entries 18.6 us with plain stores, 18.2
+// so, write buffers of 100,001 57.4 and 56.7; a driver's flushes the same (96 of 3,600 entries 2.25 to 2.31 ms either way).
 __device__ __forceinline__ void store_streaming_u4(uint4* p, const uint4 q) { typedef uint32_t v4 __attribute__((ext_vector_type(4))); const v4 v = {q.x, q.y, q.z, q.w}; __builtin_nontemporal_store(v, (__attribute__((address_space(1))) v4*)p); }
 
 // Bloom filter addressing: the block of a key and the six bits it sets or tests there, as four 32-bit masks.
