@@ -349,55 +349,19 @@ struct HashedJobs {
     uint32_t unit_log[kRuns], cap[kRuns];
 };
 
-// A workgroup puts its hashes in order of their ranges in LDS, reserves its place in every range with one atomic, and stores them,
-// neighbours next to each other.  Bound by the chain of its steps (7 us for 10 workgroups, 11 for 130).
+// Bound by the chain of a workgroup's steps (7 us for 10 workgroups, 11 for 130).
 constexpr uint32_t kScatterItems = 8, kScatterChunk = kScatterItems * kPartThreads;
+static_assert(kMostFilterRanges <= kStagedRanges, "as many as a workgroup scatters to");
 template <uint32_t kRuns>
 __global__ void __launch_bounds__(kPartThreads) bloom_scatter_kernel(HashedJobs<kRuns> jobs, CountedLengths<kRuns> lengths) {
-    __shared__ uint64_t stage[kScatterChunk];
-    __shared__ uint32_t start[kMostFilterRanges], place[kMostFilterRanges];
-    __shared__ uint32_t wave_sum[kPartThreads / kWave];
-    static_assert(kMostFilterRanges <= kPartThreads && kScatterChunk <= 65536, "a range per thread, places in 16 bits");
-    const uint32_t tid = threadIdx.x, run = blockIdx.y, unit_log = jobs.unit_log[run], cap = jobs.cap[run];
+    const uint32_t run = blockIdx.y, unit_log = jobs.unit_log[run];
     uint64_t n = jobs.most[run];
     uint32_t n_blocks = 1;
     lengths.look_up(run, n, n_blocks);
     const uint64_t first = (uint64_t)blockIdx.x * kScatterChunk;
     if (first >= n) return;
-    const uint32_t count = n - first < kScatterChunk ? (uint32_t)(n - first) : kScatterChunk, n_ranges = ((n_blocks - 1) >> unit_log) + 1;
-    const uint64_t* const hashes = jobs.hashes[run] + first;
-    uint64_t h[kScatterItems];
-#pragma unroll
-    for (uint32_t a = 0; a < kScatterItems; a++) h[a] = tid + a * kPartThreads < count ? hashes[tid + a * kPartThreads] : 0;
-    if (tid < kMostFilterRanges) start[tid] = 0;
-    __syncthreads();
-    uint32_t at[kScatterItems];  // range << 16 | place among the workgroup's hashes of the range
-#pragma unroll
-    for (uint32_t a = 0; a < kScatterItems; a++) {
-        const uint32_t r = bloom_block(h[a], n_blocks) >> unit_log;
-        at[a] = r << 16;
-        if (tid + a * kPartThreads < count) at[a] |= atomicAdd(&start[r], 1u);
-    }
-    __syncthreads();
-    const uint32_t mine = tid < n_ranges ? start[tid] : 0;
-    uint32_t reserved = 0;
-    if (mine != 0) reserved = atomicAdd(&jobs.cursors[run][tid], mine);
-    const uint32_t incl = wave_scan_u32(mine);
-    if ((tid & (kWave - 1)) == kWave - 1) wave_sum[tid / kWave] = incl;
-    __syncthreads();
-    uint32_t before = incl - mine;
-    for (uint32_t w = 0; w < tid / kWave; w++) before += wave_sum[w];
-    if (tid < n_ranges) start[tid] = before, place[tid] = reserved;
-    __syncthreads();
-#pragma unroll
-    for (uint32_t a = 0; a < kScatterItems; a++)
-        if (tid + a * kPartThreads < count) stage[start[at[a] >> 16] + (at[a] & 0xFFFF)] = h[a];
-    __syncthreads();
-    for (uint32_t i = tid; i < count; i += kPartThreads) {
-        const uint64_t v = stage[i];
-        const uint32_t r = bloom_block(v, n_blocks) >> unit_log, to = place[r] + (i - start[r]);
-        if (to < cap) jobs.ranged[run][(uint64_t)r * cap + to] = v;
-    }
+    staged_scatter<false, kScatterItems, true>(jobs.hashes[run], n, first, n_blocks, unit_log, ((n_blocks - 1) >> unit_log) + 1, nullptr, jobs.cap[run],
+                                               jobs.cursors[run], jobs.ranged[run]);
 }
 
 // One workgroup per range.  A range with more hashes than it has room for is built from all of them.

@@ -10,9 +10,9 @@
 // slot), the rest is zero.  A bucket that more than eight keys fall into holds eight of them and has bit 15 of its
 // first tag field set, which sends a lookup that finds nothing among the eight to the fence index.
 //
-// Build: the hashes and their positions are sorted by ranges of at most 4,096 buckets (lsm_partition.h); one workgroup per
-// range hands out the slots of its buckets with counters in LDS, assembles the buckets there, and writes every byte of
-// its range exactly once.
+// Build: the hashes and their positions are sorted by ranges of at most 4,096 buckets (lsm_partition.h); a workgroup per
+// 1,024 buckets of a range hands out their slots with counters in LDS, assembles the buckets there, and writes every byte of
+// them exactly once.
 // Which keys of a crowded bucket are kept, and the order of the slots in a bucket, depend on the order the
 // workgroup happens to see the hashes in: lookups give the same answers for every such table.
 #include <hip/hip_runtime.h>

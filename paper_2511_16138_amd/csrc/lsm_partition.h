@@ -126,26 +126,26 @@ __global__ void __launch_bounds__(kPartThreads) range_pass_kernel(const uint64_t
 }
 
 // The same scatter for up to kStagedRanges ranges: a workgroup takes kItems hashes per thread, reads them once, keeps them in registers, puts
-// them in order of their ranges in LDS and stores them from there, neighbours next to each other, where the pass above stores them one by
-// one all over the workspace.  Bound by a workgroup's chain (load 2 us, count, reserve 4, store) and the stores.  2.7M hashes 24.7 -> 16.4 us, with
-// positions 25.5 -> 17.2; whole filter / index of 1M keys 27.8 -> 23.5 / 31.7 -> 26.0 us, 4M 55.0 -> 43.4 / 92.8 -> 60.6, 16M 182 -> 117 / 433 -> 236.
+// them in order of their ranges in LDS, reserves its place in every range with one atomic, and stores them from there, neighbours next to each
+// other, where the pass above stores them one by one all over the workspace.  Bound by a workgroup's chain (load 2 us, count, reserve 4, store) and the
+// stores.  2.7M hashes 24.7 -> 16.4 us, with positions 25.5 -> 17.2; whole filter / index of 1M keys 27.8 -> 23.5 / 31.7 -> 26.0 us, 4M 55.0 -> 43.4 /
+// 92.8 -> 60.6, 16M 182 -> 117 / 433 -> 236.
+// kCapped: no totals are known, a range's part of `ranged` has room for `cap` hashes and what does not fit is left out (its cursor counts it all the same).
 constexpr uint32_t kStagedRanges = 1024;
-template <bool kWithPos, int kItems>
-__global__ void __launch_bounds__(kPartThreads) range_staged_kernel(const uint64_t* hashes, uint64_t n, uint32_t n_units, uint32_t unit_log, uint32_t n_ranges,
-                                                                   const uint32_t* totals, uint32_t* cursors, uint64_t* ranged) {
+template <bool kWithPos, int kItems, bool kCapped>
+__device__ __forceinline__ void staged_scatter(const uint64_t* hashes, const uint64_t n, const uint64_t first, const uint32_t n_units, const uint32_t unit_log,
+                                               const uint32_t n_ranges, const uint32_t* totals, const uint32_t cap, uint32_t* cursors, uint64_t* ranged) {
     constexpr uint32_t kChunk = kItems * kPartThreads;
     __shared__ uint64_t stage[kChunk];
     __shared__ uint16_t range_of[kWithPos ? kChunk : 1];
     __shared__ uint32_t start[kStagedRanges], place[kStagedRanges];
     __shared__ uint32_t wave_sum[2][kPartThreads / kWave];
     static_assert(kStagedRanges <= kPartThreads && kChunk <= 65536, "a range per thread, places in 16 bits");
-    const uint32_t tid = threadIdx.x;
-    const uint64_t first = (uint64_t)blockIdx.x * kChunk;
-    const uint32_t count = n - first < kChunk ? (uint32_t)(n - first) : kChunk;
+    const uint32_t tid = threadIdx.x, count = n - first < kChunk ? (uint32_t)(n - first) : kChunk;
     uint64_t h[kItems];
 #pragma unroll
     for (int a = 0; a < kItems; a++) h[a] = tid + a * kPartThreads < count ? hashes[first + tid + a * kPartThreads] : 0;
-    const uint32_t all = tid < n_ranges ? totals[tid] : 0;
+    const uint32_t all = !kCapped && tid < n_ranges ? totals[tid] : 0;
     if (tid < kStagedRanges) start[tid] = 0;
     __syncthreads();
     uint32_t at[kItems];  // range << 16 | place among the workgroup's hashes of the range
@@ -160,11 +160,14 @@ __global__ void __launch_bounds__(kPartThreads) range_staged_kernel(const uint64
     const uint32_t mine = tid < n_ranges ? start[tid] : 0;
     uint32_t reserved = 0;
     if (mine != 0) reserved = atomicAdd(&cursors[tid], mine);
-    const uint32_t incl = wave_scan_u32(mine), all_incl = wave_scan_u32(all);
+    const uint32_t incl = wave_scan_u32(mine), all_incl = kCapped ? 0 : wave_scan_u32(all);
     if ((tid & (kWave - 1)) == kWave - 1) wave_sum[0][tid / kWave] = incl, wave_sum[1][tid / kWave] = all_incl;
     __syncthreads();
     uint32_t before = incl - mine, all_before = all_incl - all;
-    for (uint32_t w = 0; w < tid / kWave; w++) before += wave_sum[0][w], all_before += wave_sum[1][w];
+    for (uint32_t w = 0; w < tid / kWave; w++) {
+        before += wave_sum[0][w];
+        if (!kCapped) all_before += wave_sum[1][w];
+    }
     if (tid < n_ranges) start[tid] = before, place[tid] = all_before + reserved;
     __syncthreads();
 #pragma unroll
@@ -177,9 +180,15 @@ __global__ void __launch_bounds__(kPartThreads) range_staged_kernel(const uint64
     __syncthreads();
     for (uint32_t i = tid; i < count; i += kPartThreads) {
         const uint64_t v = stage[i];
-        const uint32_t r = kWithPos ? range_of[i] : bloom_block(v, n_units) >> unit_log;
-        ranged[place[r] + (i - start[r])] = v;
+        const uint32_t r = kWithPos ? range_of[i] : bloom_block(v, n_units) >> unit_log, to = place[r] + (i - start[r]);
+        if (!kCapped) ranged[to] = v;
+        else if (to < cap) ranged[(uint64_t)r * cap + to] = v;
     }
+}
+template <bool kWithPos, int kItems>
+__global__ void __launch_bounds__(kPartThreads) range_staged_kernel(const uint64_t* hashes, uint64_t n, uint32_t n_units, uint32_t unit_log, uint32_t n_ranges,
+                                                                   const uint32_t* totals, uint32_t* cursors, uint64_t* ranged) {
+    staged_scatter<kWithPos, kItems, false>(hashes, n, (uint64_t)blockIdx.x * (kItems * kPartThreads), n_units, unit_log, n_ranges, totals, 0, cursors, ranged);
 }
 
 // Workspace of a partition of n hashes into n_ranges ranges: totals, cursors, the hashes (or records) by range.
@@ -200,7 +209,7 @@ inline RangeLayout range_layout(uint64_t n, uint64_t n_units, bool with_pos) {
     l.totals = 0;
     l.cursors = l.totals + up((size_t)l.n_ranges * 4);
     l.ranged = l.cursors + up((size_t)l.n_ranges * 4);
-    l.total = l.ranged + up((size_t)n * (with_pos ? 16 : 8));
+    l.total = l.ranged + up((size_t)n * (with_pos ? 16 : 8));  // 16: what callers have been told; the records of an index take half of it
     return l;
 }
 inline bool range_partition_applies(uint64_t n, uint64_t n_units) {
