@@ -502,20 +502,15 @@ def _launches(call):
     return n.value
 
 
-# The longest input whose boundaries are found one way and the shortest of another way, and the launches of either with the merge's: a wave per
-# boundary over the whole runs 2, between rows 3, on copied samples 6.
-LINES = [(3, 2048, 2, 3), (4, 2048, 2, 3), (17, 2048, 3, 6), (32, 2048, 3, 6), (33, 2048, 2, 6), (40, 2048, 2, 6), (64, 2048, 2, 6)]
-
-
-@pytest.mark.parametrize("k,tiles,below,above,shape", [(*line, "uneven") for line in LINES]
-                         + [(1, 10240, 2, 2, "uneven"), (3, 10240, 3, 3, "uneven"), (5, 8192, 3, 3, "uneven"), (16, 5120, 3, 3, "uneven")]
-                         + [(17, 2048, 3, 6, "copies"), (40, 2048, 2, 6, "copies")])
-def test_searched_directly_or_on_samples(g, oracle, k, tiles, below, above, shape):
-    """Both sides of every line between two ways of finding boundaries, and larger inputs; runs of very
+# For 3 to 16 runs both totals are searched between rows: see test_lines_between_the_ways_of_finding_boundaries.
+@pytest.mark.parametrize("k,tiles,shape", [(k, tiles, "uneven") for k, tiles in [(1, 10240), (3, 10240), (5, 8192), (16, 5120), (17, 2048), (40, 2048)]]
+                         + [(17, 2048, "copies"), (40, 2048, "copies")])
+def test_searched_directly_or_on_samples(g, oracle, k, tiles, shape):
+    """The longest input whose boundaries are searched in the runs themselves and the shortest that is sampled; runs of very
     different lengths, an empty one among them, and ones that cover a part of the keys only; or the same keys in every run, so
     that the samples tie."""
     rs = np.random.RandomState(k)
-    for total, launches in (((tiles - 1) * (2048 - k), below), ((tiles - 1) * (2048 - k) + 1, above)):
+    for total in ((tiles - 1) * (2048 - k), (tiles - 1) * (2048 - k) + 1):
         print("direct or sampled", k, total, shape, flush=True)
         if shape == "copies":
             lens = np.full(k, total // k)
@@ -531,11 +526,25 @@ def test_searched_directly_or_on_samples(g, oracle, k, tiles, below, above, shap
             runs = _runs_of(oracle, rs, lens, 2 * total)
             runs[min(1, k - 1)][:, 0] |= 1  # the keys' first byte, as stored: a run behind all others
         _check_compact(g, oracle, runs, int(total & 1))
-        buffers = torch.empty((total, 8), dtype=torch.int64, device=dev()), torch.zeros(1, dtype=torch.int64, device=dev())
-        workspace = torch.empty(g.lsm_compact_workspace_bytes([r.shape[0] for r in runs]), dtype=torch.uint8, device=dev())
-        assert _launches(lambda: g.lsm_compact(runs, 0, *buffers, workspace)) == launches
-        del runs, buffers, workspace
+        del runs
         torch.cuda.empty_cache()
+
+
+# The longest input whose boundaries are found one way and the shortest of another way, and the launches of either with the merge's: a wave per
+# boundary over the whole runs 2, between rows 3, on copied samples 6.  The last four: totals that nothing changes at.
+@pytest.mark.parametrize("k,tiles,below,above", [(3, 2048, 2, 3), (4, 2048, 2, 3), (17, 2048, 3, 6), (32, 2048, 3, 6), (33, 2048, 2, 6), (40, 2048, 2, 6),
+                                                 (64, 2048, 2, 6), (1, 10240, 2, 2), (3, 10240, 3, 3), (5, 8192, 3, 3), (16, 5120, 3, 3)])
+def test_lines_between_the_ways_of_finding_boundaries(g, oracle, k, tiles, below, above):
+    """Both sides of every line, by the launches that a call makes, and the results there."""
+    for total, launches in (((tiles - 1) * (2048 - k), below), ((tiles - 1) * (2048 - k) + 1, above)):
+        print("line", k, total, flush=True)
+        out, n_out = torch.empty((total, 8), dtype=torch.int64, device=dev()), torch.zeros(1, dtype=torch.int64, device=dev())
+        runs = list(torch.empty((total, 8), dtype=torch.int64, device=dev()).split(-(-total // k)))
+        workspace = torch.empty(g.lsm_compact_workspace_bytes([r.shape[0] for r in runs]), dtype=torch.uint8, device=dev())
+        assert len(runs) == k and _launches(lambda: g.lsm_compact(runs, 0, out, n_out, workspace)) == launches  # noqa: B023
+        del out, n_out, runs, workspace
+    torch.cuda.empty_cache()
+    test_searched_directly_or_on_samples(g, oracle, k, tiles, "uneven")
 
 
 @pytest.mark.parametrize("k,total", [(16, 1 << 26), (8, 1 << 27), (12, 89_478_486)])
@@ -627,14 +636,11 @@ def test_boundaries_at_ranked_samples(g, oracle, k, shape):
         assert np.array_equal(as_bytes(out[:n]).reshape(-1, 64), want)
 
 
-@pytest.mark.parametrize("k,total", [(3, 2048 * 2045 + 1), (4, 2047 * 2044), (4, 2047 * 2044 + 1), (5, 1_100_000), (5, 1_499_999), (5, 1_500_000), (12, 2_499_999),
-                                     (12, 2_500_000), (16, 1_300_003), (16, 7_999_999), (16, 8_000_000), (17, 2_000_000), (32, 1_500_000)])
-@pytest.mark.parametrize("shape", ["ragged", "copies", "apart", "turns"])
+@pytest.mark.parametrize("k,total", [(3, 2048 * 2045 + 1), (4, 2048 * 2044 - 1), (5, 1_100_000), (16, 1_300_003), (17, 2_000_000), (32, 1_500_000)])
+@pytest.mark.parametrize("shape", ["ragged", "copies", "apart"])
 def test_boundaries_between_rows(g, oracle, k, total, shape):
-    """Boundaries that are searched between ranked rows, on both sides of the totals where the distance between rows changes (1,024 entries of a run
-    to 16,384), and with four runs just below.  Ragged: empty runs, runs
-    of one entry, around 4,096 and far longer.  Copies: rows of the same key in every run, but for where they start.  Apart: between two rows lies one
-    run only.  Turns: runs that advance together, 100 entries each."""
+    """Boundaries that are searched between ranked rows (every 4,096th entry of a run), and with four runs just below.  Ragged: empty runs, runs
+    of one entry, around 4,096 and far longer.  Copies: rows of the same key in every run.  Apart: between two rows lies one run only."""
     print("between rows", k, total, shape, flush=True)
     rs = np.random.RandomState(k)
     lens = np.full(k, total // k)
@@ -647,15 +653,29 @@ def test_boundaries_between_rows(g, oracle, k, total, shape):
         runs = [one[:n].clone() for n in lens]
         for r in runs:
             r[:, 4] = torch.randint(0, 1 << 40, (r.shape[0],), device=dev())
-    elif shape == "turns":
-        one = _runs_of(oracle, rs, [total], 3 * total)[0]
-        turn = torch.arange(total, device=dev()) // 100 % k
-        runs = [one[turn == j].contiguous() for j in range(k)]
     else:
         runs = _runs_of(oracle, rs, lens, 2 * total)
         for j in range(k if shape == "apart" else 0):
             runs[j][:, 0] |= (j * 7) % 64 + 1  # the keys' first byte, as stored
     _check_compact(g, oracle, runs, int(total & 1))
+
+@pytest.mark.parametrize("k,total", [(4, 2047 * 2044), (4, 2047 * 2044 + 1), (5, 1_499_999), (5, 1_500_000), (12, 2_499_999), (12, 2_500_000), (16, 7_999_999), (16, 8_000_000)])
+@pytest.mark.parametrize("shape", ["ragged", "copies", "apart", "turns"])
+def test_distances_between_rows(g, oracle, k, total, shape):
+    """Both sides of the totals where the distance between ranked rows changes (1,024 entries of a run to 16,384), and of four runs' first rows.
+    Turns: runs that advance together, 100 entries each."""
+    if shape != "turns":
+        test_boundaries_between_rows(g, oracle, k, total, shape)
+        return
+    print("between rows", k, total, shape, flush=True)
+    one = _runs_of(oracle, np.random.RandomState(k), [total], 3 * total)[0]
+    turn = torch.arange(total, device=dev()) // 100 % k
+    _check_compact(g, oracle, [one[turn == j].contiguous() for j in range(k)], int(total & 1))
+
+
+@pytest.mark.parametrize("k,total", [(3, 2048 * 2045 + 1), (5, 1_100_000), (16, 1_300_003), (17, 2_000_000), (32, 1_500_000)])
+def test_rows_of_runs_in_turns(g, oracle, k, total):
+    test_distances_between_rows(g, oracle, k, total, "turns")
 
 
 @pytest.mark.parametrize("n_req", [1, 2, 3, 511, 512, 513, 2047, 2048, 2049])  # four, two and one wave per request
