@@ -232,6 +232,7 @@ __device__ __forceinline__ uint64_t run_len(const RunTable& rt, uint32_t j) { re
 
 // Calls between the parts of the library (arguments are checked by the caller).
 constexpr uint64_t kShortTiles = 256;
+constexpr uint64_t kMostClearWords = 1ull << 31;  // 16-byte words of a span: fewer than this (a bit of their number is taken, see kHashesBehind)
 struct ClearSpan {  // device memory to be zeroed by a launch that is made anyway; 16-byte aligned
     void* p = nullptr;
     size_t bytes = 0;  // a multiple of 16

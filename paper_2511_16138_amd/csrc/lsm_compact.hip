@@ -895,6 +895,7 @@ struct JobDesc {       // one compaction of a batch (device memory, written by t
     uint32_t waves;        // of the partition launch
 };
 static_assert(sizeof(JobDesc) == 80, "descriptor layout");
+static_assert(kMostClearWords <= kHashesBehind, "the words of a span leave the bit free");
 
 struct ModeArgs {
     // single form: optional filter hashes of the output's keys (kExtras = 2)

@@ -211,8 +211,11 @@ struct lsm_driver {
     }
 
     bool wants_index(uint64_t n) const { return cfg.hash_index_from != 0 && n >= cfg.hash_index_from && n <= (1ull << 27); }
-    // filters that are built straight from the entries, on memory zeroed beforehand
-    bool plain_filter(uint64_t n) const { return cfg.bloom_bits != 0 && n < kHashedFilterEntries && !wants_index(n) && lsm_bloom_blocks(n, cfg.bloom_bits) != 0; }
+    // filters that are built straight from the entries, on memory zeroed beforehand (of 32 GiB and more they are not: the memory is no span)
+    bool plain_filter(uint64_t n) const {
+        const uint64_t blocks = lsm_bloom_blocks(n, cfg.bloom_bits);
+        return blocks != 0 && blocks < lsm::kMostClearWords && n < kHashedFilterEntries && !wants_index(n);
+    }
 
     // Filter and hash index of a run that has come to rest, from the keys' hashes (computed once for both).  The
     // temporaries go back to the pool at once: their next user's work comes later on the stream.  The run gets both when

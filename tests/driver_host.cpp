@@ -54,6 +54,7 @@ hipError_t hipMalloc(void** p, size_t bytes) {
     host_bytes += bytes;
     host_largest = std::max<uint64_t>(host_largest, bytes);
     if (host_malloc_in > 0 && --host_malloc_in == 0) return hipErrorOutOfMemory;
+    if (bytes > size_t(1) << 32) return hipErrorOutOfMemory;  // a small device
     *p = std::aligned_alloc(256, (bytes + 255) / 256 * 256);
     std::memset(*p, 0xAB, (bytes + 255) / 256 * 256);
     blocks_of_memory[static_cast<char*>(*p)] = bytes;

@@ -377,3 +377,16 @@ def test_status_words_are_zeroed_after_a_call_that_failed(host, knobs, oracle, f
             assert np.array_equal(newest_versions(oracle, got), newest_versions(oracle, t.plain.runs_newest_first())), place
             t.close()
     assert struck_at > 5
+
+
+def test_filters_that_are_no_span_do_not_go_through_the_merge(host, knobs):
+    """A span of memory that a merge zeroes has fewer than 2^31 words of 16 bytes.  A filter of more (here 80 keys of 2^32 - 1 bits each, 43 GB)
+    is left to the builds behind the merge: with no memory for it the merge is made all the same."""
+    tree = Tree(host, T=4, bits=(1 << 32) - 1)
+    runs = [run_of(range(40 * step, 40 * step + 40), step) for step in range(2)]
+    for r in runs:
+        tree.plain.flush(r.copy())
+        assert host.lsm_driver_flush(tree.h, r.ctypes.data, len(r)) == HIP  # no memory for the filter
+    assert tree.log() == tree.plain.log  # the merge among them
+    assert [t.run.n for t in tree.runs()] == [80]
+    tree.close()
