@@ -289,19 +289,19 @@ struct lsm_driver {
         return LSM_OK;
     }
 
-    // The workspace for one call, with `need` bytes behind the status words.  It grows by powers of two, so that a young tree does not grow it
-    // time and again, and starts well below the 2 MB from which on the runtime asks the kernel driver for every block on its own: that costs as much as
-    // several flushes, and the runs that a tree allocates meanwhile take longer as well.  First passes of new trees, with blocks that start with 2 MB and
-    // hold twice the need / with these: twelve trees of 1M entries, buffers of 8,000, 8 flushes each 5.6 / 2.7 ms; eight, 24 flushes 5.6 / 4.2; one
-    // tree of 200,000, 16 flushes of 500 352 / 319 us.
+    // The workspace for one call, with `need` bytes behind the status words.  It starts well below the 2 MB from which on the runtime asks the kernel
+    // driver for every block on its own (30 to 300 us each, and what a tree allocates next takes longer as well), and when it is outgrown the
+    // next has room for twice the need, so that a young tree does not grow it time and again.  First passes of new trees, geometric mean over 18
+    // cases (one to 12 trees of 100,000 to 4M entries, 8 to 96 flushes) against blocks that start with 2 MB and hold twice the need: from 256 KB
+    // on, in powers of two 0.96, with twice the need 0.86.
+    // Eight trees of 1M entries, 24 flushes, us: 4,420 / 4,960 / 4,640; ten of 0.9M 4,000 / 3,240 / 2,990; one of 0.9M, 52 flushes 2,250 / 2,840 / 1,560.
     static constexpr size_t kStatusBytes = lsm::kShortTiles * sizeof(uint64_t), kLeastWorkspace = size_t(256) << 10;
     int reserve(Workspace& w, size_t need) {
         if (kStatusBytes + need <= w.bytes) return LSM_OK;
         pool.give(w.p);
         w = Workspace();
-        if (need > (size_t(1) << 60)) return LSM_ERR_HIP;  // no such allocation succeeds; keeps the loop below finite
-        size_t bytes = kLeastWorkspace;
-        while (bytes < kStatusBytes + need) bytes *= 2;
+        if (need > (size_t(1) << 60)) return LSM_ERR_HIP;  // no such allocation succeeds
+        const size_t twice = 2 * (kStatusBytes + need), bytes = twice > kLeastWorkspace ? twice : kLeastWorkspace;
         w.p = static_cast<char*>(pool.take(bytes));
         if (w.p == nullptr) return LSM_ERR_HIP;
         w.bytes = bytes;
