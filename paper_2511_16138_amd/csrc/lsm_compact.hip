@@ -9,7 +9,8 @@
 //                     L(x) = sum_j |{e in run j : e.key < x}| that is still <= r, and stores
 //                     the k lower bounds.  Boundaries are therefore key-aligned (all versions
 //                     of a key fall into the same tile) and tile sizes are within k of the
-//                     nominal size.  Two runs: bisection on the merge path (partition_two_*).
+//                     nominal size.  One run: multiples of the spacing (partition_one_kernel).  Two
+//                     runs: bisection on the merge path (partition_two_*).
 //                     Inputs of up to 512 tiles take sample keys as boundaries instead of exact
 //                     ranks (partition_ranked_kernel: tile sizes vary, within the capacity).
 //                     Larger ones search the runs, one wave per boundary (partition_kernel,
@@ -2248,8 +2249,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     carve(workspace, rt.n, n_runs, &ws);
     const uint64_t n_tiles = ws.n_tiles;
 
-    // a compaction of a few tiles that is not validated: the partition launch does the clearing as well
-    // one run and two (bisection on the merge path): at any size
+    // how the boundaries are found: see kSampledMinTiles
     bool rows = n_runs > 2 && ws.stride == 0 && rt.n_dev == nullptr && total < kRowsMost &&
                 (n_runs <= kRowsRuns ? n_tiles >= (n_runs <= 4 ? kSampledMinTiles : 2) : n_runs <= kFewRuns && n_tiles < kSampledMinTiles);
     const uint32_t row_step = row_entries(total, n_runs);
@@ -2261,6 +2261,7 @@ static int launch_compaction(const RunTable& rt, uint32_t flags, const lsm_out_t
     }
     const char* const rows_end = reinterpret_cast<const char*>(ws.st.ptr[n_runs - 1] + ws.st.m[n_runs - 1]);  // of the room that they share with what copied samples need
     rows = rows && n_rows != 0 && n_rows <= (uint64_t)(rows_end - reinterpret_cast<const char*>(ws.ywin)) / ((n_runs + 1) * sizeof(uint64_t));
+    // everything but copied samples: where the input is not validated, the first launch of the partition does the clearing as well
     const bool direct = n_tiles > 1 && (n_tiles < kSampledMinTiles || n_runs <= kRowsRuns);
     const bool fused_init = (direct || n_tiles == 1) && !(flags & LSM_VALIDATE);  // one tile needs neither status word nor split rows
     auto build_filter = [&](const ClearSpan& span) {  // right behind the merge, if it is asked for
